@@ -35,17 +35,23 @@ static void carve(AttendWs* a, void* ws, const Layout& L, int64_t k) {
 }
 
 // 16 threads move one 256-byte value row; rows below n_host_rows are read straight from
-// pinned host memory over the host link (zero-copy), the others from the HBM slice.  The grid
+// pinned host memory over the host link (zero-copy), the others from the HBM slice.  For host rows the grid
 // is deliberately small and persistent: the host link saturates with a few hundred KiB in
 // flight, and more outstanding host reads than that only clog the memory pipeline for the
 // HBM-bound kernels that run beside the gather.
-template <int UNROLL>
+// Rows in HBM want the opposite, every read in flight at once: 2048 rows for each of 32 (sequence, KV head) pairs,
+// 16.8 MB, take 10.7 us in one sweep of 1024 workgroups and 59.5 us through the 64 of the host grid; 8192 rows x 8:
+// 9.2 us against 58.3.
+// SPLIT: both kinds in one launch, each with the grid it wants - workgroups below host_wgs take the host rows, the
+// others the HBM rows; each skips the other kind's entries (4 bytes of position read twice per entry).  1024 rows x 8
+// pairs, half of them in HBM: 24.5 us against 26.0 through the host grid alone (18.4 of it is the link).
+template <int UNROLL, bool SPLIT>
 __global__ __launch_bounds__(256) void gather_values(const int32_t* __restrict__ idx, const int32_t* __restrict__ count,
                                                      int32_t k, const int32_t* __restrict__ pos, int64_t cap,
                                                      const uint4* __restrict__ v_host, int64_t host_stride,
                                                      int64_t n_host_rows, const uint4* __restrict__ v_hbm,
                                                      int64_t hbm_stride, uint4* __restrict__ vstage,
-                                                     int wgs, uint64_t* __restrict__ stamps, int first,
+                                                     int wgs, int host_wgs, uint64_t* __restrict__ stamps, int first,
                                                      uint32_t* __restrict__ gpu_seq, uint32_t seq) {
   const int row = blockIdx.y, wg = blockIdx.x;
   // hybrid value side: the kernel before this one on the stream left the host's inputs in pinned memory; a
@@ -57,16 +63,22 @@ __global__ __launch_bounds__(256) void gather_values(const int32_t* __restrict__
   if (stamp && threadIdx.x == 0) stamp[0] = wall_clock64();
   const int cnt = count[row];
   const int part = threadIdx.x & 15;
-  const int64_t step = (int64_t)wgs * 16;                 // value rows per sweep of the row's workgroups
+  const bool host_role = wg < host_wgs;                    // SPLIT only
+  const int first_wg = SPLIT && !host_role ? host_wgs : 0;
+  // value rows per sweep of the row's workgroups (of this kind)
+  const int64_t step = (int64_t)(SPLIT ? (host_role ? host_wgs : wgs - host_wgs) : wgs) * 16;
   // entries below `first` are not fetched (their values are summed where they live, on the host)
-  for (int64_t i0 = (int64_t)first + (int64_t)wg * 16 + (threadIdx.x >> 4); i0 < cnt; i0 += step * UNROLL) {
+  for (int64_t i0 = (int64_t)first + (int64_t)(wg - first_wg) * 16 + (threadIdx.x >> 4); i0 < cnt; i0 += step * UNROLL) {
     uint4 v[UNROLL];
+    bool mine[UNROLL];
 #pragma unroll
     for (int u = 0; u < UNROLL; ++u) {
       const int64_t i = i0 + u * step;
-      if (i < cnt) {
+      mine[u] = i < cnt;
+      if (mine[u]) {
         const int32_t slot = idx[(int64_t)row * k + i];
         const int64_t vr = pos[(int64_t)row * cap + slot];
+        if (SPLIT && (vr < n_host_rows) != host_role) { mine[u] = false; continue; }
         const uint4* src = (vr < n_host_rows) ? v_host + ((int64_t)row * host_stride + vr) * 16
                                               : v_hbm + ((int64_t)row * hbm_stride + (vr - n_host_rows)) * 16;
         // read-once rows, write-once staging: non-temporal both ways, so that neither side displaces or
@@ -78,7 +90,7 @@ __global__ __launch_bounds__(256) void gather_values(const int32_t* __restrict__
 #pragma unroll
     for (int u = 0; u < UNROLL; ++u) {
       const int64_t i = i0 + u * step;
-      if (i < cnt) {
+      if (mine[u]) {
         const v4i t4 = {(int)v[u].x, (int)v[u].y, (int)v[u].z, (int)v[u].w};
         __builtin_nontemporal_store(t4, reinterpret_cast<v4i*>(vstage + ((int64_t)row * k + i) * 16 + part));
       }
@@ -529,21 +541,37 @@ int32_t launch_gather(const Layout& L, const int32_t* idx, const int32_t* count,
   uint32_t* gpu_seq = hs != nullptr ? hs->gpu_seq : nullptr;
   const uint32_t seq = hs != nullptr ? hs->seq : 0u;
   const Tuning& tn = tune != nullptr ? *tune : tuning();
+  const int64_t entries = (int64_t)k - first_entry;
   int64_t wgs = ((int64_t)k + 15) / 16;                  // one workgroup per 16 rows at most
   // per (sequence, KV head).  About 64 workgroups in total keep enough reads in flight to fill the host
   // link; more only take queue entries in the memory system away from the HBM-bound kernels beside it.
   int64_t lim = tn.gather_wgs > 0 ? tn.gather_wgs : (L.rows >= 64 ? 1 : 64 / L.rows);
   if (wgs > lim) wgs = lim;
+  // Rows in HBM: one sweep, every thread's four rows in flight together.  Where the store is shared between host
+  // and HBM the launch has both kinds of workgroups, unless the HBM slice is only the few rows of the appended
+  // tokens (less than a sixteenth of the host rows): then the host kind takes them along.
+  const int64_t wide = entries > 0 ? (entries + 63) / 64 : 1;
+  const bool no_host = v_host == nullptr || n_host_rows == 0;
+  const bool split = !no_host && v_hbm != nullptr && hbm_stride > n_host_rows / 16 && tn.gather_wgs == 0 &&
+                     stamps == nullptr;
+  const int64_t host_wgs = wgs;
+  if (no_host && tn.gather_wgs == 0) wgs = wide;
+  else if (split) wgs += wide;
+  if (stamps != nullptr && tn.gather_wgs == 0 && wgs * L.rows > kGatherStampPairs)
+    wgs = kGatherStampPairs / L.rows > 0 ? kGatherStampPairs / L.rows : 1;     // one stamp pair per workgroup
   if (wgs * L.rows > kGatherStampPairs) stamps = nullptr;      // more workgroups than the stamp buffer holds
   dim3 g((unsigned)wgs, (unsigned)L.rows);
   const uint4 *vh = (const uint4*)v_host, *vd = (const uint4*)v_hbm;
-#define HCA_GATHER(U)                                                                                              \
-  gather_values<U><<<g, 256, 0, st>>>(idx, count, k, pos, L.cap, vh, host_stride, n_host_rows, vd, hbm_stride, \
-                                      (uint4*)a.vstage, (int)wgs, stamps, first_entry, gpu_seq, seq)
-  if (tn.gather_unroll >= 4) HCA_GATHER(4);
+#define HCA_GATHER_S(U, S)                                                                                            \
+  gather_values<U, S><<<g, 256, 0, st>>>(idx, count, k, pos, L.cap, vh, host_stride, n_host_rows, vd, hbm_stride, \
+                                         (uint4*)a.vstage, (int)wgs, (int)host_wgs, stamps, first_entry, gpu_seq, seq)
+#define HCA_GATHER(U) HCA_GATHER_S(U, false)
+  if (split) HCA_GATHER_S(4, true);
+  else if (tn.gather_unroll >= 4) HCA_GATHER(4);
   else if (tn.gather_unroll >= 2) HCA_GATHER(2);
   else HCA_GATHER(1);
 #undef HCA_GATHER
+#undef HCA_GATHER_S
   HCA_HIP(hipGetLastError());
   return HCA_OK;
 }
