@@ -149,8 +149,9 @@ int32_t hca_topk_noalloc(const hca_shape* shape, const float* sel, const int64_t
                          int32_t* idx, int32_t* count, void* stream);
 
 /* Steps 2 and 3a in one call (Eq. 2, then the sorted prefix Pi_k of Sec. 3.2): idx and count exactly as
- * hca_score_qkeys followed by hca_topk would leave them, without the score of every slot ever reaching
- * memory.  A strided sample of each row (8192 to 65536 slots) is scored first and gives a threshold that at least k
+ * hca_score_qkeys followed by hca_topk would leave them.  When no row is longer than 40 Ki slots that is what it
+ * does, with the scores in the workspace.  Longer rows are selected without the score of every slot ever reaching
+ * memory: a strided sample of each row (8192 to 65536 slots) is scored first and gives a threshold that at least k
  * slots of the row pass with overwhelming probability; the scan then keeps only the (score, slot) pairs
  * at or above it, and the selection runs on those few thousand pairs.  A row whose sample misled (fewer
  * than k pairs) is scanned a second time inside the same call - with a lower threshold that a count taken
@@ -163,8 +164,8 @@ int32_t hca_score_topk(const hca_shape* shape, const void* kcache, const void* q
 
 /* What the last hca_score_topk on `workspace` did (same shape and n_resident; to be called before the workspace
  * is used for anything else): per row the number of (score, slot) pairs that passed the threshold of the scan
- * that produced the result - all resident slots if that was the second scan - and whether the row needed that
- * second scan.  A monitor for the sampling step with which the top-k of Sec. 3.2 is found here, not part of the
+ * that produced the result - all resident slots if that was the second scan, or if no row was long enough to be
+ * sampled - and whether the row needed that second scan.  A monitor for the sampling step with which the top-k of Sec. 3.2 is found here, not part of the
  * method.
  *   candidates, rescanned  device, int32 [batch, n_kv_heads] each */
 int32_t hca_score_topk_report(const hca_shape* shape, const int64_t* n_resident, void* workspace,

@@ -800,6 +800,287 @@ __global__ __launch_bounds__(256) void tk_emit_lists(int64_t chunk, int nchunks,
 }
 
 
+// the float of an order key (the +0 of the two zeros)
+__device__ __forceinline__ float key_to_float(uint32_t key) {
+  return __uint_as_float((key & 0x80000000u) ? (key & 0x7fffffffu) : ~key);
+}
+
+// ---------------------------------------------------------------------------------------
+// Top-k of short rows in one launch: a 1024-thread workgroup holds a whole row of scores in registers, KPT values per
+// thread, wave w owning the KPT * 64 consecutive slots from w * KPT * 64 on (a wave's x-th load is 64 of them, so slot
+// order is (wave, x, lane)).  hca_topk per call, 8 rows of 4 Ki / 16 Ki / 32 Ki slots: 10 / 12 / 20 us, against 28 / 34 /
+// 37 us for the six launches over the whole chip; with the scan in front (hca_score_topk) 13 / 19 / 28 against 39 / 39 /
+// 41 us for sample, threshold, selecting scan, selection and its fall-back pair.
+//   1. smallest and largest value; 4096 bins spread evenly between them, so that neither the counters are fought over
+//      nor most of them stay empty (the keys of one row share their exponent bits).  Binning by value is monotone in
+//      the key - a difference, a product and a truncation - which is all the selection needs.  Rows with infinities or
+//      NaNs, or too wide for a finite scale, are binned by the key's leading 12 bits.
+//   2. the bin that holds the want-th largest key; its keys are ranked against each other when there are at most 512,
+//      else by radix levels over the distance from the bin's smallest key (ties, one far outlier).
+//   3. the ordered emit, positions by ballot:  selected(j) = key_j > T  or  (key_j == T and fewer than r_eq equals
+//      before it), position(j) = #{i < j : key_i > T} + min(#{i < j : key_i == T}, r_eq).
+// Bound by the issue of one compute unit's vector ALUs, about 40 instructions per slot.  The row in LDS with rolled
+// loops instead of registers: 35.6 us per 32 Ki slots.
+constexpr int kRankMax = 512;
+
+struct RowSelectFused {      // what hca_score_topk keeps beside the result (null spec: a plain top-k)
+  uint32_t* spec;
+  uint32_t* ncand;
+  uint32_t* mon;
+  int32_t nchunks;
+};
+
+template <int KPT>
+__global__ __launch_bounds__(1024) void tk_row_select(const float* __restrict__ vals, int64_t stride, int n_kv_heads,
+                                                      SelRows sr, int32_t k, int32_t* __restrict__ idx,
+                                                      int32_t* __restrict__ count, RowSelectFused fu) {
+  __shared__ uint32_t h[kBins12], list[kRankMax], wsum[16], wlo[16], whi[16], wspecial[16];
+  __shared__ uint32_t s_bin, s_rem, s_cb, s_n, s_T, s_req;
+  const int row = blockIdx.x;
+  const int tid = threadIdx.x, lane = tid & 63, wv = __builtin_amdgcn_readfirstlane(tid >> 6);
+  const int64_t want64 = sr.want[row / n_kv_heads];
+  const uint32_t n = want64 > 0 ? (uint32_t)sr.nsel[row / n_kv_heads] : 0u;
+  if (fu.spec != nullptr) {
+    // every resident slot is a candidate, none of them came through a threshold
+    for (int c = tid; c < fu.nchunks; c += 1024) fu.ncand[(int64_t)row * kSelectMaxChunks + c] = c == 0 ? n : 0u;
+    if (tid == 0) {
+      fu.spec[4 * row + 1] = 0;
+      if (want64 > 0 && fu.mon != nullptr) {
+        uint32_t* m = fu.mon + 4 * row;
+        m[0] += 1;
+        m[1] = n < m[1] ? n : m[1];
+        m[2] = n > m[2] ? n : m[2];
+      }
+    }
+  }
+  if (want64 <= 0) {
+    if (tid == 0) count[row] = 0;
+    return;
+  }
+  const uint32_t want = (uint32_t)want64;
+  const float* v = vals + (int64_t)row * stride;
+  uint32_t s0 = (uint32_t)wv * (KPT * 64) + (uint32_t)lane;
+  float f[KPT];                                             // (lanes past the row's end hold its last slot for now)
+#pragma unroll
+  for (int x = 0; x < KPT; ++x) f[x] = v[s0 + x * 64 < n ? s0 + x * 64 : n - 1];
+  // between the phases: what a phase derived from the values (bins, lane masks, KPT of each) is not carried along in
+  // registers to the next one, which would spill
+  auto forget = [&]() {
+    asm volatile("" : "+v"(s0));
+#pragma unroll
+    for (int x = 0; x < KPT; ++x) asm volatile("" : "+v"(f[x]));
+  };
+  for (int i = tid; i < kBins12; i += 1024) h[i] = 0;
+  if (tid == 0) s_n = 0;
+  float vlo = INFINITY, vhi = -INFINITY;
+  uint32_t mag = 0;                                         // largest magnitude bits: infinities and NaNs show up here
+#pragma unroll
+  for (int x = 0; x < KPT; ++x) {
+    vlo = fminf(vlo, f[x]);
+    vhi = fmaxf(vhi, f[x]);
+    const uint32_t a = __float_as_uint(f[x]) & 0x7fffffffu;
+    mag = a > mag ? a : mag;
+  }
+#pragma unroll
+  for (int o = 32; o >= 1; o >>= 1) {
+    vlo = fminf(vlo, __shfl_xor(vlo, o));
+    vhi = fmaxf(vhi, __shfl_xor(vhi, o));
+    const uint32_t a = __shfl_xor(mag, o);
+    mag = a > mag ? a : mag;
+  }
+  if (lane == 0) { wlo[wv] = __float_as_uint(vlo); whi[wv] = __float_as_uint(vhi); wspecial[wv] = mag; }
+  __syncthreads();
+  vlo = __uint_as_float(wlo[lane & 15]);
+  vhi = __uint_as_float(whi[lane & 15]);
+  mag = wspecial[lane & 15];
+#pragma unroll
+  for (int o = 8; o >= 1; o >>= 1) {
+    vlo = fminf(vlo, __shfl_xor(vlo, o));
+    vhi = fmaxf(vhi, __shfl_xor(vhi, o));
+    const uint32_t a = __shfl_xor(mag, o);
+    mag = a > mag ? a : mag;
+  }
+  forget();
+  const bool finite = mag < 0x7f800000u;
+  const float scale = 4095.0f / (vhi - vlo);
+  const bool by_value = finite && vhi - vlo < INFINITY && scale < INFINITY;
+  // the bin that holds the rem-th largest entry of the counters in h: published to s_bin / s_rem / s_cb
+  auto find_bin = [&](uint32_t rem) {
+    uint32_t hb[4], sum = 0;
+#pragma unroll
+    for (int i = 0; i < 4; ++i) { hb[i] = h[kBins12 - 1 - (4 * tid + i)]; sum += hb[i]; }
+    uint32_t running = block_scan_excl_1024(sum, wsum);
+#pragma unroll
+    for (int i = 0; i < 4; ++i) {
+      if (running < rem && rem <= running + hb[i]) {
+        s_bin = (uint32_t)(kBins12 - 1 - (4 * tid + i));
+        s_rem = rem - running;
+        s_cb = hb[i];
+      }
+      running += hb[i];
+    }
+    __syncthreads();
+  };
+  uint32_t T, req;
+  if (finite && vlo == vhi) {                               // all equal: the want lowest slots
+    T = order_key(vlo);
+    req = want;
+  } else {
+    auto live = [&](int x) { return s0 + x * 64 < n; };
+    auto bin_of = [&](int x) { return by_value ? (uint32_t)((f[x] - vlo) * scale) : order_key(f[x]) >> 20; };
+#pragma unroll
+    for (int x = 0; x < KPT; ++x)
+      if (live(x)) atomicAdd(&h[bin_of(x)], 1u);
+    __syncthreads();
+    find_bin(want);
+    forget();
+    const uint32_t b0 = s_bin;
+    uint32_t rem = s_rem, cb = s_cb;
+    // the keys still in question: those of bin b0, and among them those whose distance from `base` starts with pd
+    uint32_t base = 0, pd = 0;
+    int sbits = 32;                                         // unknown bits of the distance; 32: every key of the bin
+    if (cb > (uint32_t)kRankMax) {
+      uint32_t lo = 0xffffffffu, hi = 0;
+#pragma unroll
+      for (int x = 0; x < KPT; ++x)
+        if (live(x) && bin_of(x) == b0) {
+          const uint32_t kk = order_key(f[x]);
+          lo = kk < lo ? kk : lo;
+          hi = kk > hi ? kk : hi;
+        }
+#pragma unroll
+      for (int o = 32; o >= 1; o >>= 1) {
+        const uint32_t a = __shfl_xor(lo, o), b = __shfl_xor(hi, o);
+        lo = a < lo ? a : lo;
+        hi = b > hi ? b : hi;
+      }
+      __syncthreads();                                      // everybody has read the row's extremes
+      if (lane == 0) { wlo[wv] = lo; whi[wv] = hi; }
+      __syncthreads();
+      for (int x = 0; x < 16; ++x) { lo = wlo[x] < lo ? wlo[x] : lo; hi = whi[x] > hi ? whi[x] : hi; }
+      base = lo;
+      int left = 32 - __clz((int)((hi - lo) | 1u));         // 1 .. 32
+      bool first = true;
+      while (left > 0 && cb > (uint32_t)kRankMax) {         // uniform over the workgroup
+        forget();
+        const int width = left > 12 ? 12 : left, ns = left - width;
+        __syncthreads();
+        for (int i = tid; i < kBins12; i += 1024) h[i] = 0;
+        __syncthreads();
+#pragma unroll
+        for (int x = 0; x < KPT; ++x) {
+          const uint32_t d = order_key(f[x]) - base;
+          lds_count(h, (d >> ns) & ((1u << width) - 1u), live(x) && bin_of(x) == b0 && (first || (d >> left) == pd), true);
+        }
+        __syncthreads();
+        find_bin(rem);
+        pd = first ? s_bin : ((pd << width) | s_bin);
+        rem = s_rem;
+        cb = s_cb;
+        left = ns;
+        first = false;
+      }
+      sbits = left;
+    }
+    forget();
+    if (sbits == 0) {                                       // the distance is fully known
+      T = base + pd;
+      req = rem;
+    } else {
+#pragma unroll
+      for (int x = 0; x < KPT; ++x) {
+        bool hit = live(x) && bin_of(x) == b0;
+        if (__builtin_amdgcn_ballot_w64(hit) == 0) continue;
+        const uint32_t kk = order_key(f[x]);
+        hit = hit && (sbits == 32 || ((kk - base) >> sbits) == pd);
+        const uint64_t m = __builtin_amdgcn_ballot_w64(hit);
+        uint32_t at = 0;
+        if (lane == 0) at = atomicAdd(&s_n, (uint32_t)__popcll(m));
+        at = __builtin_amdgcn_readfirstlane(at);
+        if (hit) list[at + (uint32_t)__popcll(m & ((1ull << lane) - 1))] = kk;
+      }
+      __syncthreads();
+      if ((uint32_t)tid < cb) {
+        const uint32_t ki = list[tid];
+        uint32_t gt = 0, eq = 0;
+        for (uint32_t j = 0; j < cb; ++j) {
+          const uint32_t kj = list[j];
+          gt += kj > ki;
+          eq += kj == ki;
+        }
+        if (gt < rem && rem <= gt + eq) { s_T = ki; s_req = rem - gt; }       // equal keys write equal values
+      }
+      __syncthreads();
+      T = s_T;
+      req = s_req;
+    }
+  }
+  // ordered emit
+  int32_t* out = idx + (int64_t)row * k;
+  if (tid == 0) count[row] = (int32_t)want;
+  auto emit = [&](auto&& above, auto&& equal) {
+    forget();
+    uint32_t ng = 0, ne = 0;
+#pragma unroll
+    for (int x = 0; x < KPT; ++x) {
+      ng += (uint32_t)__popcll(__builtin_amdgcn_ballot_w64(above(x)));
+      ne += (uint32_t)__popcll(__builtin_amdgcn_ballot_w64(equal(x)));
+    }
+    forget();
+    __syncthreads();                                        // (wlo and whi have been read)
+    if (lane == 0) { wlo[wv] = ng; whi[wv] = ne; }
+    __syncthreads();
+    uint32_t pg = 0, pe = 0;
+    for (int x = 0; x < wv; ++x) { pg += wlo[x]; pe += whi[x]; }
+#pragma unroll
+    for (int x = 0; x < KPT; ++x) {
+      const bool is_g = above(x), is_e = equal(x);
+      const uint64_t mg = __builtin_amdgcn_ballot_w64(is_g), me = __builtin_amdgcn_ballot_w64(is_e);
+      if ((mg | me) == 0) continue;
+      const uint32_t g = pg + __builtin_amdgcn_mbcnt_hi((uint32_t)(mg >> 32), __builtin_amdgcn_mbcnt_lo((uint32_t)mg, 0u));
+      if (me == 0) {
+        if (is_g) out[g + (pe < req ? pe : req)] = (int32_t)(s0 + x * 64);
+      } else {
+        const uint32_t e = pe + __builtin_amdgcn_mbcnt_hi((uint32_t)(me >> 32), __builtin_amdgcn_mbcnt_lo((uint32_t)me, 0u));
+        if (is_g || (is_e && e < req)) out[g + (e < req ? e : req)] = (int32_t)(s0 + x * 64);
+        pe += (uint32_t)__popcll(me);
+      }
+      pg += (uint32_t)__popcll(mg);
+    }
+  };
+  if (finite) {
+    // finite values compare like their keys (the two zeros are equal both ways); past the row's end: -inf
+    const float tf = key_to_float(T);
+#pragma unroll
+    for (int x = 0; x < KPT; ++x) f[x] = s0 + x * 64 < n ? f[x] : -INFINITY;
+    emit([&](int x) { return f[x] > tf; }, [&](int x) { return f[x] == tf; });
+  } else {
+    emit([&](int x) { return s0 + x * 64 < n && order_key(f[x]) > T; },
+         [&](int x) { return s0 + x * 64 < n && order_key(f[x]) == T; });
+  }
+}
+
+// Longest row of the one-launch form: one compute unit per row, so its time grows with the row (64 values per thread:
+// 48 us at 64 Ki slots, level with the other form); eight rows of 32 Ki slots 28 us against 41, of 40 Ki 33
+// against 47, of 48 Ki (both sampled) 48.
+// 40 Ki is what fits the 128 registers of a 1024-thread workgroup, and keeps a 32 Ki context on this side while it
+// grows by the tokens it decodes.
+constexpr int64_t kRowSelectMax = 40960;
+
+static int32_t launch_row_select(const float* vals, int64_t stride, int rows, int n_kv_heads, const SelRows& sr,
+                                 int64_t nmax, int32_t k, int32_t* idx, int32_t* count, const RowSelectFused& fu,
+                                 hipStream_t st) {
+#define HCA_ROW_SELECT(KPT) tk_row_select<KPT><<<rows, 1024, 0, st>>>(vals, stride, n_kv_heads, sr, k, idx, count, fu)
+  if (nmax <= 4 * 1024) HCA_ROW_SELECT(4);
+  else if (nmax <= 8 * 1024) HCA_ROW_SELECT(8);
+  else if (nmax <= 16 * 1024) HCA_ROW_SELECT(16);
+  else if (nmax <= 32 * 1024) HCA_ROW_SELECT(32);
+  else HCA_ROW_SELECT(40);
+#undef HCA_ROW_SELECT
+  HCA_HIP(hipGetLastError());
+  return HCA_OK;
+}
+
 // ---------------------------------------------------------------------------------------
 // Top-k straight from the scan (Sec. 3.2): the selecting scan has left, per chunk and in slot order, the
 // (key, slot) pairs at or above the row's sampled threshold.  One workgroup per row strings the chunks' lists
@@ -1433,6 +1714,17 @@ int32_t launch_select_finish_pair(const Layout& L, const void* const kcache[2], 
 
 int32_t launch_score_topk(const Layout& L, const void* kcache, const void* q, const NRes& nr, int64_t nmax, int32_t k,
                           int32_t* idx, int32_t* count, void* ws, hipStream_t st) {
+  if (nmax > 0 && nmax <= kRowSelectMax) {
+    // short rows: every score into the room of the candidate lists (8 B per slot there, 4 needed), then one launch
+    FusedPlan f;
+    int32_t rc = fused_plan(L, nr, nmax, k, ws, &f);
+    if (rc != HCA_OK) return rc;
+    float* scores = reinterpret_cast<float*>(f.t.cand);
+    rc = launch_score(L, kcache, q, nr, nmax, scores, nullptr, st);
+    if (rc != HCA_OK) return rc;
+    return launch_row_select(scores, L.cap, L.rows, L.n_kv_heads, f.sr, nmax, k, idx, count,
+                             RowSelectFused{f.t.spec, f.t.ncand, f.t.mon, f.nchunks}, st);
+  }
   int32_t rc = launch_select_threshold(L, kcache, q, nr, nmax, k, ws, st);
   if (rc != HCA_OK) return rc;
   rc = launch_select_begin(L, kcache, q, nr, nmax, k, ws, st, nullptr);
@@ -1490,9 +1782,6 @@ int32_t launch_select_monitor(const Layout& L, void* ws, int32_t* out, int reset
 // the histogram sums below are exact and independent of the order in which atomics land.  The
 // radix walk is the top-k one with two running totals: it stops in the first bin / digit / equal-key
 // group where the weight reaches the target or the slot count reaches k_max.
-__device__ __forceinline__ float key_to_float(uint32_t key) {
-  return __uint_as_float((key & 0x80000000u) ? (key & 0x7fffffffu) : ~key);
-}
 
 // Integer weight of a logit u <= 0 relative to the row maximum: about exp(u) * 2^31.
 //   t = u * log2(e); below -64 -> 0; fl = floor(t); f = t - fl in [0, 1) (exact);
@@ -1833,6 +2122,8 @@ int32_t launch_topk(const Layout& L, const float* sel, const NRes& nr, int64_t n
     sr.want[b] = nr.n[b] < k ? nr.n[b] : k;
     if (sr.want[b] == 0) sr.want[b] = -1;
   }
+  if (nmax <= kRowSelectMax)
+    return launch_row_select(sel, L.cap, L.rows, L.n_kv_heads, sr, nmax, k, idx, count, RowSelectFused{}, st);
   TopkWs t;
   topk_carve(&t, ws, L.rows, list_cap > 0 ? list_cap : L.cap);
   int64_t chunk;

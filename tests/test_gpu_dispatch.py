@@ -44,3 +44,102 @@ def test_value_rows_are_the_same_wherever_they_live(B, k):
     assert torch.isfinite(out[0]).all()
     for n_host, y in zip((0, 600, 1150, 1), out[1:]):
         assert torch.equal(y, out[0]), f"n_host_rows = {n_host}"
+
+
+def _order_key(x):
+    u = x.view(np.uint32).copy()
+    u[(u << np.uint32(1)) == 0] = 0
+    return np.where(u >> np.uint32(31), ~u, u | np.uint32(0x80000000)).astype(np.uint32)
+
+
+def _scores(kind, n, rng):
+    x = rng.standard_normal(n).astype(np.float32)
+    if kind == "outlier":                                   # one value far above: nearly all others share a bin
+        x[n // 2] = 1e30
+    elif kind == "ties":                                    # a few values, thousands of slots each
+        x = rng.integers(-2, 3, n).astype(np.float32)
+    elif kind == "close":                                   # distinct keys that differ in their last bits, both signs of zero
+        x = (np.float32(7) + rng.integers(0, 4096, n).astype(np.float32) * np.float32(4.7683716e-07)).astype(np.float32)
+        x[:: 97] = 0.0
+        x[1:: 97] = -0.0
+    elif kind == "masked":                                  # infinities and the type's lowest value among the scores
+        x[rng.random(n) < 0.4] = np.finfo(np.float32).min
+        x[rng.random(n) < 0.4] = -np.inf
+        x[rng.random(n) < 0.01] = np.inf
+    elif kind == "nan":                                     # NaNs order by their bits, like every other value
+        x[rng.random(n) < 0.02] = np.nan
+        x[rng.random(n) < 0.02] = -np.nan
+    elif kind == "tiny":
+        x = (x * np.float32(1e-42)).astype(np.float32)
+    elif kind == "equal":
+        x[:] = -3.5
+    elif kind == "wide":                                    # max - min overflows
+        x = (np.clip(x, -2.8, 2.8) * np.float32(1.2e38)).astype(np.float32)
+    return x
+
+
+@pytest.mark.parametrize("kind", ["normal", "outlier", "ties", "close", "masked", "nan", "tiny", "equal", "wide"])
+@pytest.mark.parametrize("n", [1, 63, 65, 1024, 4096, 4097, 8193, 16384, 16385, 32767, 32769, 40960, 40961])
+def test_topk_at_the_edges_of_the_one_launch_form(B, kind, n):
+    """hca_topk with the row in one workgroup's registers (up to 40 Ki slots, five sizes of it) and over the chip."""
+    rng = np.random.default_rng(n + len(kind))
+    lens = [n, max(1, n - 31), 0]
+    cap = n + 3
+    sel = np.full((3, cap), 9e9, np.float32)                # past the row's end: larger than anything in it
+    for b in range(3):
+        sel[b, :lens[b]] = _scores(kind, lens[b], rng) if lens[b] else 0
+    shape = B.make_shape(3, 1, 1, cap)
+    dsel = torch.from_numpy(sel).cuda()
+    for k in sorted({1, min(n, 5), max(1, n // 3), n}):
+        ws = torch.empty(B.hca_workspace_bytes(shape, k, 1), dtype=torch.uint8, device="cuda")
+        idx = torch.full((3, k), -7, dtype=torch.int32, device="cuda")
+        count = torch.full((3,), -7, dtype=torch.int32, device="cuda")
+        B.hca_topk(shape, dsel, lens, k, idx, count, ws)
+        torch.cuda.synchronize()
+        got, c = idx.cpu().numpy(), count.cpu().numpy()
+        for b in range(3):
+            want = min(k, lens[b])
+            assert c[b] == want
+            key = _order_key(sel[b, :lens[b]]).astype(np.int64)
+            ref = np.sort(np.argsort(-key, kind="stable")[:want])
+            assert np.array_equal(got[b, :want], ref), f"row {b}, k {k}"
+            assert np.all(got[b, want:] == -7)
+
+
+@pytest.mark.parametrize("bits,gs", [(4, 32), (2, 64)])
+@pytest.mark.parametrize("n", [40960, 40961])
+def test_score_topk_on_both_sides_of_the_short_row_line(B, oracle, bits, gs, n):
+    """hca_score_topk: rows of up to 40 Ki slots are scored whole and selected in one launch, longer ones go through the
+    sampled threshold; the report and the running monitor describe both."""
+    k = 777
+    w = S.Workload("line", 82 + bits, 2, 8, 2, n, bits, gs, k)
+    d = S.make_layer(w, want_values=False)
+    st = _layer(w, k)
+    st.quantize(d["keys"].cuda())
+    st.n = [n, 1000]
+    R = 4
+    idx = torch.full((R, k), -7, dtype=torch.int32, device="cuda")
+    count = torch.full((R,), -7, dtype=torch.int32, device="cuda")
+    cand, resc = torch.full((R,), -1, dtype=torch.int32, device="cuda"), torch.full((R,), -1, dtype=torch.int32, device="cuda")
+    mon = torch.zeros(R, 4, dtype=torch.int32, device="cuda")
+    st.ws.fill_(255)
+    B.hca_score_topk_monitor(st.shape, st.ws, None, True)
+    B.hca_score_topk(st.shape, st.kcache, d["q"].cuda(), st.n, k, idx, count, st.ws)
+    B.hca_score_topk_report(st.shape, st.n, st.ws, cand, resc)
+    B.hca_score_topk_monitor(st.shape, st.ws, mon, False)
+    torch.cuda.synchronize()
+    oc = oracle.Cache(R, n, 128, bits, gs)
+    oracle.quantize(oc, d["keys"].numpy().reshape(R, n, 128))
+    oc.n[...] = np.repeat(st.n, 2)
+    sel, _ = oracle.score(oc, d["q"].numpy().reshape(-1, 128), want_z=False)
+    ridx, rcount = oracle.topk(sel, oc.n, k)
+    for r in range(R):
+        c = int(rcount[r])
+        assert int(count[r]) == c and np.array_equal(idx[r, :c].cpu().numpy(), ridx[r, :c])
+    cand, mon = cand.cpu().numpy(), mon.cpu().numpy()
+    assert int(resc.sum()) == 0
+    assert np.array_equal(mon[:, 0], [1] * R) and np.array_equal(mon[:, 1], cand) and np.array_equal(mon[:, 2], cand)
+    if n <= 40960:
+        assert np.array_equal(cand, np.repeat(st.n, 2))
+    else:
+        assert k <= cand[0] < n // 2
