@@ -113,141 +113,234 @@ __global__ __launch_bounds__(256) void vq_assign_kernel(int g, int c, int n_kv_h
 //     k 0..3   A = -hi(c_d)            B = x_d        hi(c) = fp16(c), lo(c) = fp16(c - hi(c))
 //     k 4..7   A = -lo(c_d)            B = x_d        (x is fp16 as it arrives)
 //     k 8..10  A = h1, h2, h3          B = 1          h = fp32 |c|^2 / 2 cut into three fp16 pieces
-//     k 11..13 A = 1                   B = t1, t2, t3 pass 2 only: t = -(threshold) in three fp16 pieces
 //   Errors against the exact e(c), with S = |x|^2 + max_c |c|^2 < 2^15 (so that no piece overflows fp16; fp16
-//   denormals are kept by the instruction): c_d - hi - lo is at most 2^-22 |c_d| + 2^-25, h and t lose at most
-//   2^-33 of themselves + 2^-25, the fp32 |c|^2 chain 4 u |c|^2 (u = 2^-24), and the instruction's 15 additions at
+//   denormals are kept by the instruction): c_d - hi - lo is at most 2^-22 |c_d| + 2^-25, h loses at most
+//   2^-33 of itself + 2^-25, the fp32 |c|^2 chain 4 u |c|^2 (u = 2^-24), and the instruction's 15 additions at
 //   most 2^-23 each of sum |terms| <= 2.01 S whatever their order and rounding: together below 2^-17.9 S + 2^-23.
 //   The exact chain d(c) itself is within 7 u d <= 2^-20.2 S of the truth (in units of e).  With
-//   delta = 2^-16 S + 2^-21 - three times the sum of those - the winner c* of the exact chain (first smallest d)
-//   has e(c*) - (min_c e(c) + 2 delta) < 0 as computed in pass 2.
-//   Pass 1 takes min_c e(c) per token (eight v_min3 per instruction).  Pass 2 runs the same products with the
-//   threshold folded in and collects the sign bits (eight v_or3): a centroid whose result is negative is noted
-//   in the lane's candidate list - one or two per token; a candidate that finds the list full goes through the
-//   exact chain at once and only the best of those is kept.  Then the exact chain runs over the list in ascending
-//   index order.  A token whose S is out of range or not a number takes the exact chain over every centroid
-//   instead (same result, the speed of the vector form).
-// One workgroup of 8 waves = 1024 tokens x one group; a wave holds 128 tokens (four 32-token B operands) against
-// centroids that pass through LDS 512 at a time (A operands only, double-buffered, one barrier per chunk).
+//   delta = 2^-17 S + 2^-21 - one and a half times the sum of those - the winner c* of the exact chain (first smallest
+//   d) has e(c*) <= min_c e(c) + 2 delta as computed.
+//   One pass takes the minimum of e over every block of centroids and half wave (eight v_min3 per instruction) and
+//   keeps the smallest ones per token, each with its block's number in the low mantissa bits (4 more per block): a
+//   v_and_or, v_med3 and v_min in place of compares and selects.  That moves a value by less than 2^-16 of itself, so a
+//   block counts as a candidate up to  m1 + 2.1 delta + 2^-14.9 |m1|  (m1 the smallest).  The exact chain then runs over
+//   the 16 rows of a tile that the half wave holds, both halves sharing the work, for one block per token and now and
+//   then two.  Tokens with more blocks in question than were kept, or with S out of range, are noted in an LDS queue
+//   and go through the exact chain of every centroid at the end.
+// What bounds it is the vector ALU's issue (a second pass of products with the threshold folded in, a sign test and a
+// list of candidates in the loop took twice the instructions): 17.6 per matrix instruction with everything, 90 % of
+// the issue slots, the matrix cores 40 % busy.  16 Ki tokens x 8 KV heads against 8192 centroids: 1.23 ms (2.44 in two
+// passes); 64 Ki x 8 against 1024: 0.90 ms (2.30); 100 tokens x 8 against 8192: 0.07 ms (0.94 in the vector form).
 typedef _Float16 v8h __attribute__((ext_vector_type(8)));
+typedef _Float16 v2h __attribute__((ext_vector_type(2)));
 typedef float v16f __attribute__((ext_vector_type(16)));
-constexpr int kAmChunk = 512;       // centroids per LDS chunk
-// the matrix-core form is taken from 1024 tokens x 2048 centroids (or 4096 x 512) on: level with the vector forms
-// at 256 centroids, ahead of them from 512 on, and a workgroup wants 1024 tokens
-constexpr int64_t kAssignMfmaMinTokens = 1024;
-constexpr int kAssignMfmaMinCodewords = 512;
-constexpr int64_t kAssignMfmaMinWork = (int64_t)1 << 21;
-constexpr int kAmCand = 3;          // candidate slots per lane (two lanes per token); further ones are judged at once
 
 __device__ __forceinline__ _Float16 am_f16(float v) { return (_Float16)v; }
 
-template <int DBAR, bool WIDE>
+// The A operands of one centroid (k blocks 0 and 1 of its row) and |c|^2.
+template <int DBAR>
+__device__ __forceinline__ void am_operands(const float (&cv)[DBAR], v8h* ra0, v8h* ra1, float* norm2) {
+  const _Float16 zero = (_Float16)0.f;
+  _Float16 hi[4] = {zero, zero, zero, zero}, lo[4] = {zero, zero, zero, zero};
+  float nn = 0.f;
+#pragma unroll
+  for (int d = 0; d < DBAR; ++d) {
+    nn = fmaf(cv[d], cv[d], nn);
+    hi[d] = am_f16(-cv[d]);
+    lo[d] = am_f16(-cv[d] - (float)hi[d]);
+  }
+  const float hh = 0.5f * nn;
+  const _Float16 h1 = am_f16(hh);
+  const float r1 = hh - (float)h1;
+  const _Float16 h2 = am_f16(r1);
+  const _Float16 h3 = am_f16(r1 - (float)h2);
+  *ra0 = v8h{hi[0], hi[1], hi[2], hi[3], lo[0], lo[1], lo[2], lo[3]};
+  *ra1 = v8h{h1, h2, h3, zero, zero, zero, zero, zero};
+  *norm2 = nn;
+}
+// past the codebook: never among the smallest
+__device__ __forceinline__ void am_no_centroid(v8h* ra0, v8h* ra1) {
+  const _Float16 zero = (_Float16)0.f;
+  *ra0 = v8h{zero, zero, zero, zero, zero, zero, zero, zero};
+  *ra1 = v8h{(_Float16)65504.f, zero, zero, zero, zero, zero, zero, zero};
+}
+// The B operand of this lane's k block for a token's channels (pairs of fp16 as they lie in memory) and |x|^2.
+template <int DBAR>
+__device__ __forceinline__ v8h am_token(const uint32_t (&xw)[DBAR / 2], int kb, float* norm2) {
+  const _Float16 one = (_Float16)1.f, zero = (_Float16)0.f;
+  _Float16 xh[4] = {zero, zero, zero, zero};
+  float n2 = 0.f;
+#pragma unroll
+  for (int d = 0; d < DBAR / 2; ++d) {
+    const v2h pair = __builtin_bit_cast(v2h, xw[d]);
+    n2 = __builtin_amdgcn_fdot2(pair, pair, n2, false);     // (only a bound is needed of it)
+    xh[2 * d] = pair[0];
+    xh[2 * d + 1] = pair[1];
+  }
+  *norm2 = n2;
+  return kb == 0 ? v8h{xh[0], xh[1], xh[2], xh[3], xh[0], xh[1], xh[2], xh[3]}
+                 : v8h{one, one, one, zero, zero, zero, zero, zero};
+}
+// How far above the smallest value a block can still hold the winner.
+__device__ __forceinline__ float am_limit(float m1, float S) {
+  const float delta = S * 7.62939453125e-6f + 4.76837158203125e-7f;       // 2^-17 S + 2^-21
+  return m1 + (2.1f * delta + 3.3e-5f * fabsf(m1));
+}
+// (value of the lower half, value of the upper half) of a wave, on every lane of a column
+struct Halves { uint32_t lo, hi; };
+__device__ __forceinline__ Halves halves_of(uint32_t v) {
+  const auto r = __builtin_amdgcn_permlane32_swap(v, v, false, false);
+  return Halves{r[0], r[1]};
+}
+// (distance, index) as one number that orders by distance, then by index; distances are never negative
+__device__ __forceinline__ uint64_t am_key(float dist, int ci) { return (uint64_t)__float_as_uint(dist) << 32 | (uint32_t)ci; }
+constexpr uint64_t kAmNoKey = ~0ull;
+
+// The exact chain over every centroid of a group for one token, by LANES neighbouring lanes (y = which of them): the
+// winner of the ascending scan of vq_assign_kernel, which starts from centroid 0 whatever its distance - no finite
+// distance at all, or a first distance that is not a number, leave it the winner.
+template <int DBAR, int LANES>
+__device__ __forceinline__ int am_exhaustive(const uint16_t* src, const float* cg, int c, int y) {
+  float x[DBAR];
+#pragma unroll
+  for (int d = 0; d < DBAR; ++d) x[d] = h2f(src[d]);
+  float bd = INFINITY;
+  int bi = 0x7fffffff;
+  int first_nan = 0;
+  for (int c0 = y; c0 < c; c0 += 4 * LANES) {               // four centroids in flight
+    float cv[4][DBAR];
+#pragma unroll
+    for (int u = 0; u < 4; ++u)
+#pragma unroll
+      for (int d = 0; d < DBAR; ++d) cv[u][d] = cg[(c0 + u * LANES < c ? c0 + u * LANES : c0) * DBAR + d];
+#pragma unroll
+    for (int u = 0; u < 4; ++u) {
+      float dist = 0.f;
+#pragma unroll
+      for (int d = 0; d < DBAR; ++d) {
+        const float e = x[d] - cv[u][d];
+        dist = fmaf(e, e, dist);
+      }
+      if (c0 + u * LANES < c && dist < bd) { bd = dist; bi = c0 + u * LANES; }
+      if (c0 == 0 && u == 0) first_nan = dist != dist;
+    }
+  }
+#pragma unroll
+  for (int o = LANES / 2; o >= 1; o >>= 1) {
+    const float od = __shfl_xor(bd, o);
+    const int ob = __shfl_xor(bi, o);
+    first_nan |= __shfl_xor(first_nan, o);
+    if (od < bd || (od == bd && ob < bi)) { bd = od; bi = ob; }
+  }
+  return (bi == 0x7fffffff || first_nan) ? 0 : bi;
+}
+
+// More than 256 centroids (always the wide form).  One workgroup of 8 waves = 1024 tokens x one group; a wave holds
+// 128 tokens (four 32-token B operands) against centroids that pass through LDS 512 at a time (A operands only,
+// double-buffered, one barrier per chunk).  kAmBlock: tiles of 32 centroids per block, two beyond 2048 centroids (128 blocks
+// at 8192, half the bookkeeping), else one (half the rows to look into).  The three smallest values are kept, so two
+// blocks per half wave can be looked into.
+constexpr int kAmChunk = 512;       // centroids per LDS chunk
+
+template <int DBAR, int kAmBlock>
 __global__ __launch_bounds__(512) __attribute__((amdgpu_waves_per_eu(4))) void vq_assign_mfma_kernel(
     int g, int c, int n_kv_heads, int64_t cap, const float* __restrict__ centroids, uint8_t* __restrict__ pcache,
     const uint16_t* __restrict__ k_new, int64_t T, NRes nr, float* __restrict__ acc, int32_t* __restrict__ pos,
     NRes vrow0) {
+  constexpr int TT = 4;
   // A operands: [buffer][tile of 32 centroids][k block 0 / 1][row] x 8 fp16
   __shared__ __align__(16) v8h sA[2][kAmChunk / 32][2][32];
   __shared__ float s_cmax[8];
+  __shared__ uint16_t s_queue[1024];
+  __shared__ uint32_t s_nq;
   const int row = blockIdx.y, grp = blockIdx.z;
   const int tid = threadIdx.x, lane = tid & 63, w = tid >> 6;
   const int col = lane & 31, kb = lane >> 5;
-  const int64_t tok0 = (int64_t)blockIdx.x * 1024 + w * 128;
+  const int64_t wg0 = (int64_t)blockIdx.x * 1024, tok0 = wg0 + w * 128;
+  const int b = row / n_kv_heads;
   const float* cg = centroids + ((int64_t)(row % n_kv_heads) * g + grp) * c * DBAR;
-
-  // this lane's tokens: |x|^2 and the B operand of its k block (x itself is read again for the exact chain)
-  float x2[4];
-  v8h bop[4];
+  const v16f zero16 = {0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f};
+  auto channels_of = [&](int64_t t) { return k_new + ((int64_t)row * T + (t < T ? t : T - 1)) * kHeadDim + grp * DBAR; };
+  auto load_x = [&](int tt, uint32_t (&xw)[DBAR / 2]) {
+    const uint16_t* src = channels_of(tok0 + 32 * tt + col);
 #pragma unroll
-  for (int tt = 0; tt < 4; ++tt) {
-    const int64_t t = tok0 + 32 * tt + col;
-    const int64_t tc = t < T ? t : T - 1;
-    const uint16_t* src = k_new + ((int64_t)row * T + tc) * kHeadDim + grp * DBAR;
-    float n2 = 0.f;
-    _Float16 xh[4] = {(_Float16)0.f, (_Float16)0.f, (_Float16)0.f, (_Float16)0.f};
+    for (int d = 0; d < DBAR / 2; ++d) xw[d] = (uint32_t)src[2 * d] | (uint32_t)src[2 * d + 1] << 16;
+  };
+  const bool wave_live = tok0 < T;                          // (a wave without tokens only helps with the operands)
+  float x2[TT];
+  v8h bop[TT];
 #pragma unroll
-    for (int d = 0; d < DBAR; ++d) {
-      const uint16_t bits = src[d];
-      const float xf = h2f(bits);
-      xh[d] = __builtin_bit_cast(_Float16, bits);
-      n2 = fmaf(xf, xf, n2);
-    }
-    x2[tt] = n2;
-    const _Float16 one = (_Float16)1.f, zero = (_Float16)0.f;
-    if (kb == 0) bop[tt] = v8h{xh[0], xh[1], xh[2], xh[3], xh[0], xh[1], xh[2], xh[3]};
-    else bop[tt] = v8h{one, one, one, zero, zero, zero, zero, zero};
+  for (int tt = 0; tt < TT; ++tt) {
+    uint32_t xw[DBAR / 2];
+    load_x(tt, xw);
+    bop[tt] = am_token<DBAR>(xw, kb, &x2[tt]);
   }
 
   const int nchunk = (c + kAmChunk - 1) / kAmChunk;
-  v8h ra0, ra1;                      // this thread's centroid of the chunk on its way to LDS
-  float rn = 0.f;
+  float cv[DBAR];                    // this thread's centroid of the chunk on its way to LDS
+  float mycmax = 0.f;
   auto fetch = [&](int ch) {
     const int cc = ch * kAmChunk + tid;
-    const _Float16 one = (_Float16)1.f, zero = (_Float16)0.f;
-    ra0 = v8h{zero, zero, zero, zero, zero, zero, zero, zero};
-    ra1 = v8h{(_Float16)65504.f, zero, zero, one, one, one, zero, zero};     // past the codebook: never the minimum
-    rn = 0.f;
-    if (cc < c) {
-      float nn = 0.f;
-      _Float16 hi[4] = {zero, zero, zero, zero}, lo[4] = {zero, zero, zero, zero};
 #pragma unroll
-      for (int d = 0; d < DBAR; ++d) {
-        const float v = cg[(int64_t)cc * DBAR + d];
-        nn = fmaf(v, v, nn);
-        hi[d] = am_f16(-v);
-        lo[d] = am_f16(-v - (float)hi[d]);
-      }
-      const float hh = 0.5f * nn;
-      const _Float16 h1 = am_f16(hh);
-      const float r1 = hh - (float)h1;
-      const _Float16 h2 = am_f16(r1);
-      const _Float16 h3 = am_f16(r1 - (float)h2);
-      ra0 = v8h{hi[0], hi[1], hi[2], hi[3], lo[0], lo[1], lo[2], lo[3]};
-      ra1 = v8h{h1, h2, h3, one, one, one, zero, zero};
-      rn = nn;
+    for (int d = 0; d < DBAR; ++d) cv[d] = cg[(int64_t)(cc < c ? cc : 0) * DBAR + d];
+  };
+  auto commit = [&](int ch) {
+    v8h ra0, ra1;
+    am_no_centroid(&ra0, &ra1);
+    if (ch * kAmChunk + tid < c) {
+      float nn;
+      am_operands<DBAR>(cv, &ra0, &ra1, &nn);
+      mycmax = nn < INFINITY ? fmaxf(mycmax, nn) : INFINITY;     // not finite or not a number: no token is in range
     }
+    sA[ch & 1][tid >> 5][0][tid & 31] = ra0;
+    sA[ch & 1][tid >> 5][1][tid & 31] = ra1;
   };
-  auto commit = [&](int buf) {
-    sA[buf][tid >> 5][0][tid & 31] = ra0;
-    sA[buf][tid >> 5][1][tid & 31] = ra1;
+  auto blocks_of = [&](int ch) {
+    const int left = c - ch * kAmChunk;
+    return ((left < kAmChunk ? left : kAmChunk) + 32 * kAmBlock - 1) / (32 * kAmBlock);
   };
-  auto tiles_of = [&](int ch) { const int left = c - ch * kAmChunk; return left >= kAmChunk ? kAmChunk / 32 : (left + 31) / 32; };
-  const v16f zero16 = {0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f};
 
-  // pass 1: min over the centroids of e(c), and the largest |c|^2
-  float m[4] = {INFINITY, INFINITY, INFINITY, INFINITY};
-  float mycmax = 0.f;
-  bool cbad = false;                 // a centroid whose |c|^2 is not a number or not finite
+  float m1[TT], m2[TT], m3[TT];
+#pragma unroll
+  for (int tt = 0; tt < TT; ++tt) { m1[tt] = INFINITY; m2[tt] = INFINITY; m3[tt] = INFINITY; }
+  if (tid == 0) s_nq = 0;
   fetch(0);
   commit(0);
-  mycmax = rn;
-  cbad = !(rn < INFINITY);
   __syncthreads();
   for (int ch = 0; ch < nchunk; ++ch) {
     const int buf = ch & 1;
     if (ch + 1 < nchunk) fetch(ch + 1);
-    const int ntile = tiles_of(ch);
-    for (int t = 0; t < ntile; ++t) {
-      const v8h a = sA[buf][t][kb][col];
-      v16f d[4];
+    if (wave_live) {
+      const int nblk = blocks_of(ch);
+      for (int bl = 0; bl < nblk; ++bl) {
+        float tm[TT];
 #pragma unroll
-      for (int tt = 0; tt < 4; ++tt) d[tt] = __builtin_amdgcn_mfma_f32_32x32x16_f16(a, bop[tt], zero16, 0, 0, 0);
+        for (int u = 0; u < kAmBlock; ++u) {
+          const v8h a = sA[buf][bl * kAmBlock + u][kb][col];
+          v16f d[TT];
 #pragma unroll
-      for (int tt = 0; tt < 4; ++tt) {
-        float mm = m[tt];
+          for (int tt = 0; tt < TT; ++tt) d[tt] = __builtin_amdgcn_mfma_f32_32x32x16_f16(a, bop[tt], zero16, 0, 0, 0);
 #pragma unroll
-        for (int j = 0; j < 16; j += 2) mm = fminf(fminf(mm, d[tt][j]), d[tt][j + 1]);
-        m[tt] = mm;
+          for (int tt = 0; tt < TT; ++tt) {
+            float mm = u == 0 ? fminf(d[tt][0], d[tt][1]) : fminf(fminf(tm[tt], d[tt][0]), d[tt][1]);
+#pragma unroll
+            for (int j = 2; j < 16; j += 2) mm = fminf(fminf(mm, d[tt][j]), d[tt][j + 1]);
+            tm[tt] = mm;
+          }
+        }
+        const uint32_t blk = (uint32_t)(ch * (kAmChunk / 32 / kAmBlock) + bl);
+#pragma unroll
+        for (int tt = 0; tt < TT; ++tt) {
+          const float pk = __uint_as_float((__float_as_uint(tm[tt]) & ~127u) | blk);
+          m3[tt] = __builtin_amdgcn_fmed3f(m2[tt], m3[tt], pk);
+          m2[tt] = __builtin_amdgcn_fmed3f(m1[tt], m2[tt], pk);
+          m1[tt] = fminf(m1[tt], pk);
+        }
       }
     }
-    if (ch + 1 < nchunk) {
-      commit(buf ^ 1);
-      cbad = cbad || !(rn < INFINITY);
-      if (rn > mycmax) mycmax = rn;
-    }
+    if (ch + 1 < nchunk) commit(ch + 1);
     __syncthreads();
   }
-  if (cbad) mycmax = INFINITY;
 #pragma unroll
   for (int o = 32; o >= 1; o >>= 1) mycmax = fmaxf(mycmax, __shfl_xor(mycmax, o));
   if (lane == 0) s_cmax[w] = mycmax;
@@ -256,162 +349,308 @@ __global__ __launch_bounds__(512) __attribute__((amdgpu_waves_per_eu(4))) void v
 #pragma unroll
   for (int x = 1; x < 8; ++x) cmax2 = fmaxf(cmax2, s_cmax[x]);
 
-  // thresholds into the B operands of k block 1; tokens out of range take the exact chain over everything
-  bool full[4];
-#pragma unroll
-  for (int tt = 0; tt < 4; ++tt) {
-    float mm = fminf(m[tt], __shfl_xor(m[tt], 32));
-    const float S = x2[tt] + cmax2;
-    full[tt] = !(S < 32768.f) || !(mm == mm) || !(fabsf(mm) < 65000.f);
-    const float thr = mm + 2.f * (S * 1.52587890625e-5f + 4.76837158203125e-7f);      // 2^-16 S + 2^-21
-    const float tneg = full[tt] ? 0.f : -thr;
-    const _Float16 t1 = am_f16(tneg);
-    const float r1 = tneg - (float)t1;
-    const _Float16 t2 = am_f16(r1);
-    const _Float16 t3 = am_f16(r1 - (float)t2);
-    if (kb == 1) { bop[tt][3] = t1; bop[tt][4] = t2; bop[tt][5] = t3; }
-    if (full[tt]) {
-      // no shortlist for this token: x = 0 and t = +1 make every result of pass 2 |c|^2 / 2 + 1 > 0
-      const _Float16 one = (_Float16)1.f, zero = (_Float16)0.f;
-      if (kb == 0) bop[tt] = v8h{zero, zero, zero, zero, zero, zero, zero, zero};
-      else bop[tt] = v8h{one, one, one, one, zero, zero, zero, zero};
+  auto put = [&](int64_t t, int win) {
+    if (t >= T) return;
+    const int64_t slot = nr.n[b] + t;
+    reinterpret_cast<uint16_t*>(pcache)[vq_wide_at(g, vq_tiles(cap), row, slot, grp)] = (uint16_t)win;
+    if (grp == 0) {
+      if (acc != nullptr) acc[(int64_t)row * cap + slot] = 0.0f;
+      if (pos != nullptr) pos[(int64_t)row * cap + slot] = (int32_t)(vrow0.n[b] + t);
     }
-  }
-
-  // pass 2: the same products with the threshold folded in; negative results are candidates
-  int cand[4][kAmCand];
-  int ncand[4] = {0, 0, 0, 0};
-  float rest_d[4] = {INFINITY, INFINITY, INFINITY, INFINITY};      // best of the candidates that found the list full
-  int rest_i[4] = {0x7fffffff, 0x7fffffff, 0x7fffffff, 0x7fffffff};
+  };
+  if (wave_live) {
 #pragma unroll
-  for (int tt = 0; tt < 4; ++tt)
+    for (int tt = 0; tt < TT; ++tt) {
+      const float S = x2[tt] + cmax2;
+      const Halves a1 = halves_of(__float_as_uint(m1[tt])), a2 = halves_of(__float_as_uint(m2[tt])),
+                   a3 = halves_of(__float_as_uint(m3[tt]));
+      const float lim = am_limit(fminf(__uint_as_float(a1.lo), __uint_as_float(a1.hi)), S);
+      // the token's candidates, one byte each (block, 255: none): smallest of the lower half, of the upper half, then
+      // the second smallest
+      auto cand = [&](uint32_t v) { return __uint_as_float(v) <= lim ? (v & 127u) : 255u; };
+      uint32_t todo = cand(a1.lo) | cand(a1.hi) << 8 | cand(a2.lo) << 16 | cand(a2.hi) << 24;
+      const bool queue = !(S < 32768.f) || __uint_as_float(a3.lo) <= lim || __uint_as_float(a3.hi) <= lim;
+      if (queue) todo = 0xffffffffu;
+      uint64_t best = kAmNoKey;
+      float x[DBAR];
+      {
+        uint32_t xw[DBAR / 2];
+        load_x(tt, xw);
 #pragma unroll
-    for (int q = 0; q < kAmCand; ++q) cand[tt][q] = 0;
-  fetch(0);
-  commit(0);
-  __syncthreads();
-  for (int ch = 0; ch < nchunk; ++ch) {
-    const int buf = ch & 1;
-    if (ch + 1 < nchunk) fetch(ch + 1);
-    const int ntile = tiles_of(ch);
-    for (int t = 0; t < ntile; ++t) {
-      const v8h a = sA[buf][t][kb][col];
-      v16f d[4];
-#pragma unroll
-      for (int tt = 0; tt < 4; ++tt) d[tt] = __builtin_amdgcn_mfma_f32_32x32x16_f16(a, bop[tt], zero16, 0, 0, 0);
-      uint32_t sg[4];
-#pragma unroll
-      for (int tt = 0; tt < 4; ++tt) {
-        uint32_t o = 0;
-#pragma unroll
-        for (int j = 0; j < 16; j += 2) o = o | __float_as_uint(d[tt][j]) | __float_as_uint(d[tt][j + 1]);
-        sg[tt] = o;
+        for (int d = 0; d < DBAR; ++d) x[d] = h2f((xw[d >> 1] >> (16 * (d & 1))) & 0xffffu);
       }
-      const uint32_t any = sg[0] | sg[1] | sg[2] | sg[3];
-      if (__builtin_amdgcn_ballot_w64((int32_t)any < 0) == 0) continue;     // mostly: no candidate in these 32 x 128
-      const int cbase = ch * kAmChunk + t * 32 + 4 * kb;
+      while (__builtin_amdgcn_ballot_w64(todo != 0xffffffffu) != 0) {
+        if (todo != 0xffffffffu) {
+          const int which = (int)__builtin_ctz(~((todo & 0x80808080u) | 0x7f7f7f7fu)) >> 3;    // first byte below 128
+          const int blk = (int)((todo >> (8 * which)) & 127u), half = which & 1;
+          todo |= 0xffu << (8 * which);
+          // rows of a 32 x 32 result held by a half: 8 (j / 4) + 4 half + j % 4, j < 16; this lane takes j = 8 kb ..
+          float rd = INFINITY;
+          int ri = 0x7fffffff;
 #pragma unroll
-      for (int tt = 0; tt < 4; ++tt) {
-        if (__builtin_amdgcn_ballot_w64((int32_t)sg[tt] < 0) == 0) continue;
+          for (int u = 0; u < kAmBlock; ++u) {
+            const int c0 = (blk * kAmBlock + u) * 32 + 16 * kb + 4 * half;
+            float cc[8][DBAR];
 #pragma unroll
-        for (int j = 0; j < 16; ++j) {
-          // rows of the 32x32 result held by this lane: 8 * (j / 4) + 4 * kb + j % 4, ascending in j
-          if ((int32_t)__float_as_uint(d[tt][j]) < 0) {
-            const int cidx = cbase + 8 * (j >> 2) + (j & 3);
-            if (cidx < c) {
+            for (int j = 0; j < 8; ++j) {
+              const int ci = c0 + 8 * (j >> 2) + (j & 3);
 #pragma unroll
-              for (int q = 0; q < kAmCand; ++q)
-                if (ncand[tt] == q) cand[tt][q] = cidx;
-              if (ncand[tt] >= kAmCand) {
-                // the list is full: this one goes through the exact chain now and only the best of these is kept
-                // (they arrive in ascending index order, so a strict comparison keeps the first smallest)
-                const int64_t tk = tok0 + 32 * tt + col;
-                const uint16_t* src = k_new + ((int64_t)row * T + (tk < T ? tk : T - 1)) * kHeadDim + grp * DBAR;
-                float dist = 0.f;
+              for (int d = 0; d < DBAR; ++d) cc[j][d] = cg[(int64_t)(ci < c ? ci : 0) * DBAR + d];
+            }
 #pragma unroll
-                for (int dd = 0; dd < DBAR; ++dd) {
-                  const float e = h2f(src[dd]) - cg[(int64_t)cidx * DBAR + dd];
-                  dist = fmaf(e, e, dist);
-                }
-                if (dist < rest_d[tt]) { rest_d[tt] = dist; rest_i[tt] = cidx; }
+            for (int j = 0; j < 8; ++j) {
+              const int ci = c0 + 8 * (j >> 2) + (j & 3);
+              float dist = 0.f;
+#pragma unroll
+              for (int d = 0; d < DBAR; ++d) {
+                const float e = x[d] - cc[j][d];
+                dist = fmaf(e, e, dist);
               }
-              ncand[tt] += 1;
+              if (ci < c && dist < rd) { rd = dist; ri = ci; }
             }
           }
+          const uint64_t key = am_key(rd, ri);
+          if (key < best) best = key;
         }
       }
+      const Halves bh = halves_of((uint32_t)(best >> 32)), bl = halves_of((uint32_t)best);
+      const uint64_t k0 = (uint64_t)bh.lo << 32 | bl.lo, k1 = (uint64_t)bh.hi << 32 | bl.hi;
+      if (kb == 0) {
+        if (queue) s_queue[atomicAdd(&s_nq, 1u)] = (uint16_t)(w * 128 + 32 * tt + col);
+        else put(tok0 + 32 * tt + col, (int)(uint32_t)(k0 < k1 ? k0 : k1));
+      }
     }
-    if (ch + 1 < nchunk) commit(buf ^ 1);
-    __syncthreads();
   }
-
-  // the exact chain over the candidates (ascending index per lane), or over every centroid
-  const int b = row / n_kv_heads;
-#pragma unroll
-  for (int tt = 0; tt < 4; ++tt) {
-    float bd = INFINITY;
-    int bi = 0x7fffffff;
-    const int64_t t = tok0 + 32 * tt + col;
-    float xs[DBAR];
-    {
-      const uint16_t* src = k_new + ((int64_t)row * T + (t < T ? t : T - 1)) * kHeadDim + grp * DBAR;
-#pragma unroll
-      for (int dd = 0; dd < DBAR; ++dd) xs[dd] = h2f(src[dd]);
-    }
-    auto exact = [&](int cidx) {
-      float dist = 0.f;
-#pragma unroll
-      for (int dd = 0; dd < DBAR; ++dd) {
-        const float e = xs[dd] - cg[(int64_t)cidx * DBAR + dd];
-        dist = fmaf(e, e, dist);
-      }
-      return dist;
-    };
-    if (full[tt]) {
-      for (int cidx = kb; cidx < c; cidx += 2) {
-        const float dist = exact(cidx);
-        if (dist < bd) { bd = dist; bi = cidx; }
-      }
-    } else {
-#pragma unroll
-      for (int q = 0; q < kAmCand; ++q) {
-        if (q < ncand[tt]) {
-          const float dist = exact(cand[tt][q]);
-          if (dist < bd) { bd = dist; bi = cand[tt][q]; }
-        }
-      }
-      if (rest_d[tt] < bd) { bd = rest_d[tt]; bi = rest_i[tt]; }       // later indices than the list's
-    }
-    const float od = __shfl_xor(bd, 32);
-    const int ob = __shfl_xor(bi, 32);
-    if (od < bd || (od == bd && ob < bi)) { bd = od; bi = ob; }
-    // the ascending scan starts from centroid 0 whatever its distance: no finite distance at all, or a first
-    // distance that is not a number, leave it the winner
-    const float d0 = exact(0);
-    const int win = (bi == 0x7fffffff || d0 != d0) ? 0 : bi;
-    if (kb == 0 && t < T) {
-      const int64_t slot = nr.n[b] + t;
-      if constexpr (WIDE) reinterpret_cast<uint16_t*>(pcache)[vq_wide_at(g, vq_tiles(cap), row, slot, grp)] = (uint16_t)win;
-      else pcache[((int64_t)row * cap + slot) * g + vq_byte_of(grp, slot)] = (uint8_t)win;
-      if (grp == 0) {
-        if (acc != nullptr) acc[(int64_t)row * cap + slot] = 0.0f;
-        if (pos != nullptr) pos[(int64_t)row * cap + slot] = (int32_t)(vrow0.n[b] + t);
-      }
-    }
+  __syncthreads();
+  for (uint32_t e = w; e < s_nq; e += 8) {                   // one wave per queued token
+    const int64_t t = wg0 + s_queue[e];
+    const int win = am_exhaustive<DBAR, 64>(channels_of(t), cg, c, lane);
+    if (lane == 0) put(t, win);
   }
 }
 
-// Few tokens per call (decode appends): one workgroup per (token, row, four groups); a wave takes one group
-// and spreads the group's centroids over its lanes (lane, lane + 64, ...; four distances in flight per lane),
-// then the lanes' candidates are reduced by (distance, index): the smaller distance wins, equal distances go
-// to the lower index - the same winner as the ascending scan with a strict comparison.
-template <int DBAR, bool WIDE>
+// At most 256 centroids: at most eight tiles cover a group, so a group's operands (and the centroids themselves, for the
+// exact chain) sit in LDS at once.  A workgroup of four waves takes 256 tokens through sixteen consecutive groups: the
+// next group's centroids are fetched, split and stored to the other LDS buffer meanwhile (one thread per centroid), one
+// barrier per group, and the sixteen index bytes of a token leave as one 16-byte store (narrow form).  A block is half of
+// a tile's rows in a half wave; two values are kept, a token with rivals in another block (a few in a thousand) goes to
+// the queue.
+// 64 Ki tokens x 8 KV heads against 256 centroids: 0.31 ms (0.99 in the vector form), 64 centroids: 0.17 ms (0.25).
+constexpr int kAsCodewords = 256;
+// Taken from this many (token, KV head, group, centroid) combinations on: below, the launch has too few workgroups and
+// each takes its 25 - 43 us whatever it holds; there the vector form is level (2048 tokens x 8 KV heads against 256
+// centroids: 41 us vector, 43 here; 4096: 69 and 43).  Up to 32 centroids the vector form is ahead at every size.
+constexpr int64_t kAssignMfmaMinWork = (int64_t)1 << 27;
+
+template <int CTRL>
+__device__ __forceinline__ float dpp_max(float v) {
+  return fmaxf(v, __int_as_float(__builtin_amdgcn_update_dpp(0, __float_as_int(v), CTRL, 0xf, 0xf, true)));
+}
+__device__ __forceinline__ float wave_max_nonneg(float v) {
+  v = dpp_max<0xB1>(v);               // quad_perm [1,0,3,2]
+  v = dpp_max<0x4E>(v);               // quad_perm [2,3,0,1]
+  v = dpp_max<0x141>(v);              // row_half_mirror
+  v = dpp_max<0x140>(v);              // row_mirror
+  const auto a = __builtin_amdgcn_permlane16_swap(__float_as_uint(v), __float_as_uint(v), false, false);
+  v = fmaxf(__uint_as_float(a[0]), __uint_as_float(a[1]));
+  const Halves h = halves_of(__float_as_uint(v));
+  return fmaxf(__uint_as_float(h.lo), __uint_as_float(h.hi));
+}
+
+// NT: tiles of 32 centroids (2, 4 or 8)
+template <int DBAR, bool WIDE, int NT>
+__global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(4))) void vq_assign_small_c_kernel(
+    int g, int c, int n_kv_heads, int64_t cap, const float* __restrict__ centroids, uint8_t* __restrict__ pcache,
+    const uint16_t* __restrict__ k_new, int64_t T, NRes nr, float* __restrict__ acc, int32_t* __restrict__ pos,
+    NRes vrow0) {
+  constexpr int kGroups = 16;         // groups per workgroup
+  constexpr int TT = 2;               // 32-token tiles per wave
+  constexpr int kCen = NT * 32;
+  __shared__ __align__(16) v8h sA[2][NT][2][32];
+  __shared__ __align__(16) float sC[2][kCen + 12][DBAR];        // centroids, the tiles' rows shifted (cen_at)
+  __shared__ float s_cmax[2][4];
+  __shared__ __align__(16) uint8_t s_win[WIDE ? 1 : 256][kGroups];         // narrow form: a token's sixteen record bytes
+  __shared__ uint16_t s_queue[512];                             // (token, group) pairs left to the exhaustive chain
+  __shared__ uint32_t s_nq;
+  const int row = blockIdx.y, g0 = blockIdx.z * kGroups;
+  const int tid = threadIdx.x, lane = tid & 63, w = tid >> 6;
+  const int col = lane & 31, kb = lane >> 5;
+  const int64_t wg0 = (int64_t)blockIdx.x * 256, tok0 = wg0 + w * 64;
+  const int b = row / n_kv_heads;
+  const float* cb = centroids + ((int64_t)(row % n_kv_heads) * g + g0) * c * DBAR;
+  const v16f zero16 = {0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f};
+
+  // row r of tile t: 16 lanes that read the same row of their halves in any of the eight tiles are on different banks
+  // (at four channels; a row is 4 banks, the halves are 16 apart)
+  auto cen_at = [](int t, int r) { return t * 32 + r + (t & 3) + (t >> 2) * 8; };
+  // one centroid of a group per thread: fetched to registers, later split into operands and stored
+  float cv[DBAR];
+  auto fetch = [&](int gi) {
+    const float* p = cb + ((int64_t)gi * c + (tid < c ? tid : 0)) * DBAR;
+#pragma unroll
+    for (int d = 0; d < DBAR; ++d) cv[d] = p[d];
+  };
+  auto commit = [&](int buf) {
+    float nn = 0.f;
+    if (kCen == 256 || w * 64 < kCen) {
+      v8h ra0, ra1;
+      am_no_centroid(&ra0, &ra1);
+      if (tid < c) am_operands<DBAR>(cv, &ra0, &ra1, &nn);
+      sA[buf][tid >> 5][0][tid & 31] = ra0;
+      sA[buf][tid >> 5][1][tid & 31] = ra1;
+      // past the codebook: a distance of infinity, never the smallest
+#pragma unroll
+      for (int d = 0; d < DBAR; ++d) sC[buf][cen_at(tid >> 5, tid & 31)][d] = tid < c ? cv[d] : INFINITY;
+    }
+    const float m = wave_max_nonneg(nn < INFINITY ? nn : INFINITY);     // not finite or not a number: no token is in range
+    if (lane == 0) s_cmax[buf][w] = m;
+  };
+  // this lane's tokens: a group's DBAR channels as they lie in memory
+  uint32_t xn[TT][DBAR / 2];
+  const uint32_t* xsrc[TT];
+#pragma unroll
+  for (int tt = 0; tt < TT; ++tt) {
+    const int64_t t = tok0 + 32 * tt + col;
+    xsrc[tt] = reinterpret_cast<const uint32_t*>(k_new + ((int64_t)row * T + (t < T ? t : T - 1)) * kHeadDim + g0 * DBAR);
+  }
+  auto load_x = [&](int gi) {
+#pragma unroll
+    for (int tt = 0; tt < TT; ++tt)
+#pragma unroll
+      for (int d = 0; d < DBAR / 2; ++d) xn[tt][d] = xsrc[tt][gi * (DBAR / 2) + d];
+  };
+  // the winner of token `tok` (of the workgroup's 256) in group gi
+  auto put = [&](int tok, int gi, int win) {
+    const int64_t t = wg0 + tok;
+    if constexpr (WIDE) {
+      if (t < T) reinterpret_cast<uint16_t*>(pcache)[vq_wide_at(g, vq_tiles(cap), row, nr.n[b] + t, g0 + gi)] = (uint16_t)win;
+    } else {
+      s_win[tok][(gi - (int)(nr.n[b] + t)) & 15] = (uint8_t)win;
+    }
+  };
+  fetch(0);
+  load_x(0);
+  commit(0);
+  if (tid == 0) s_nq = 0;
+  __syncthreads();
+  for (int gi = 0; gi < kGroups; ++gi) {
+    const int buf = gi & 1;
+    float x2[TT];
+    v8h bop[TT];
+    uint32_t xw[TT][DBAR / 2];
+#pragma unroll
+    for (int tt = 0; tt < TT; ++tt) {
+#pragma unroll
+      for (int d = 0; d < DBAR / 2; ++d) xw[tt][d] = xn[tt][d];
+      bop[tt] = am_token<DBAR>(xw[tt], kb, &x2[tt]);
+    }
+    if (gi + 1 < kGroups) { fetch(gi + 1); load_x(gi + 1); }
+    float m1[TT], m2[TT];
+#pragma unroll
+    for (int tt = 0; tt < TT; ++tt) { m1[tt] = INFINITY; m2[tt] = INFINITY; }
+#pragma unroll
+    for (int t = 0; t < NT; ++t) {
+      // the empty asm statements keep the tiles in order: the scheduler would start all products at once and spill
+      v8h a = sA[buf][t][kb][col];
+      asm volatile("" : "+v"(a));
+      v16f d[TT];
+#pragma unroll
+      for (int tt = 0; tt < TT; ++tt) d[tt] = __builtin_amdgcn_mfma_f32_32x32x16_f16(a, bop[tt], zero16, 0, 0, 0);
+#pragma unroll
+      for (int tt = 0; tt < TT; ++tt) {
+#pragma unroll
+        for (int q = 0; q < 2; ++q) {                       // the half wave's first and last eight rows
+          float tm = fminf(d[tt][8 * q], d[tt][8 * q + 1]);
+#pragma unroll
+          for (int j = 2; j < 8; j += 2) tm = fminf(fminf(tm, d[tt][8 * q + j]), d[tt][8 * q + j + 1]);
+          const float pk = __uint_as_float((__float_as_uint(tm) & ~15u) | (uint32_t)(2 * t + q));
+          m2[tt] = __builtin_amdgcn_fmed3f(m1[tt], m2[tt], pk);
+          m1[tt] = fminf(m1[tt], pk);
+        }
+        asm volatile("" : "+v"(m1[tt]));
+      }
+    }
+    const float cmax2 = fmaxf(fmaxf(s_cmax[buf][0], s_cmax[buf][1]), fmaxf(s_cmax[buf][2], s_cmax[buf][3]));
+    if (gi + 1 < kGroups) commit(buf ^ 1);
+#pragma unroll
+    for (int tt = 0; tt < TT; ++tt) {
+      const Halves a1 = halves_of(__float_as_uint(m1[tt]));
+      const float f0 = __uint_as_float(a1.lo), f1 = __uint_as_float(a1.hi);
+      const bool upper = f1 < f0;
+      const float S = x2[tt] + cmax2;
+      const float lim = am_limit(upper ? f1 : f0, S);
+      const bool rivals = fmaxf(f0, f1) <= lim || m2[tt] <= lim || !(S < 32768.f);
+      float x[DBAR];
+#pragma unroll
+      for (int d = 0; d < DBAR; ++d) x[d] = h2f((xw[tt][d >> 1] >> (16 * (d & 1))) & 0xffffu);
+      // rows of a 32 x 32 result held by a half: 8 (j / 4) + 4 half + j % 4, j < 16; block 2 t + q has j = 8 q .. 8 q + 7,
+      // this lane takes the four from 8 q + 4 kb on
+      const uint32_t blk = (upper ? a1.hi : a1.lo) & 15u;
+      const int tile = (int)(blk >> 1) & (NT - 1), r0 = 16 * (int)(blk & 1u) + 8 * kb + (upper ? 4 : 0);
+      float bd = 0.f;
+      int bj = 0;
+#pragma unroll
+      for (int j = 0; j < 4; ++j) {
+        float dist = 0.f;
+#pragma unroll
+        for (int d = 0; d < DBAR; ++d) {
+          const float e = x[d] - sC[buf][cen_at(tile, r0) + j][d];
+          dist = fmaf(e, e, dist);
+        }
+        if (j == 0 || dist < bd) { bd = dist; bj = j; }
+      }
+      const uint32_t mine = (uint32_t)(tile * 32 + r0 + bj);
+      const Halves bh = halves_of(__float_as_uint(bd)), bl = halves_of(mine);
+      const float d0 = __uint_as_float(bh.lo), d1 = __uint_as_float(bh.hi);
+      const uint32_t win = d1 < d0 || (d1 == d0 && bl.hi < bl.lo) ? bl.hi : bl.lo;
+      const bool queue = (halves_of((uint32_t)rivals).lo | halves_of((uint32_t)rivals).hi) != 0;
+      if (kb == 0) {
+        const int tok = w * 64 + 32 * tt + col;
+        if (queue) s_queue[atomicAdd(&s_nq, 1u)] = (uint16_t)(tok | gi << 8);
+        else put(tok, gi, (int)win);
+      }
+    }
+    __syncthreads();
+    if (s_nq > 256 || gi + 1 == kGroups) {                  // room for another group's 256 tokens, or the end
+      for (uint32_t e = tid >> 3; e < s_nq; e += 32) {      // eight lanes per queued token
+        const int tok = s_queue[e] & 255, qi = s_queue[e] >> 8;
+        const int64_t t = wg0 + tok;
+        const int win = am_exhaustive<DBAR, 8>(k_new + ((int64_t)row * T + (t < T ? t : T - 1)) * kHeadDim + (g0 + qi) * DBAR,
+                                               cb + (int64_t)qi * c * DBAR, c, tid & 7);
+        if ((tid & 7) == 0) put(tok, qi, win);
+      }
+      __syncthreads();
+      if (tid == 0) s_nq = 0;
+      __syncthreads();
+    }
+  }
+  const int64_t t = wg0 + tid;
+  if (t >= T) return;
+  const int64_t slot = nr.n[b] + t;
+  if constexpr (!WIDE)
+    *reinterpret_cast<uint4*>(pcache + ((int64_t)row * cap + slot) * g + g0) = *reinterpret_cast<const uint4*>(s_win[tid]);
+  if (g0 == 0) {
+    if (acc != nullptr) acc[(int64_t)row * cap + slot] = 0.0f;
+    if (pos != nullptr) pos[(int64_t)row * cap + slot] = (int32_t)(vrow0.n[b] + t);
+  }
+}
+
+// Few tokens per call (decode appends): one workgroup of four waves per (token, row, 4 / SPLIT groups).  SPLIT waves
+// share a group, each takes a part of its centroids and spreads it over its lanes (lane, lane + 64, ...; four distances
+// in flight per lane); the lanes' candidates, then the waves', are reduced by (distance, index): the smaller distance
+// wins, equal distances go to the lower index - the same winner as the ascending scan with a strict comparison.
+// Bound by the latency of a lane's chain of loads: with all four waves on one group (from 1024 centroids on, where a
+// single wave would take four or more rounds of four loads) the append of one token x 8 KV heads takes 8 us at 8192
+// centroids instead of 25.
+template <int DBAR, bool WIDE, int SPLIT>
 __global__ __launch_bounds__(256) void vq_assign_small_kernel(int g, int c, int n_kv_heads, int64_t cap,
                                                               const float* __restrict__ centroids,
                                                               uint8_t* __restrict__ pcache,
                                                               const uint16_t* __restrict__ k_new, int64_t T, NRes nr,
                                                               float* __restrict__ acc, int32_t* __restrict__ pos,
                                                               NRes vrow0) {
+  __shared__ float s_d[4];
+  __shared__ int s_i[4];
   const int row = blockIdx.y;
   const int64_t tt = blockIdx.x;
   const int lane = threadIdx.x & 63, w = threadIdx.x >> 6;
@@ -419,46 +658,49 @@ __global__ __launch_bounds__(256) void vq_assign_small_kernel(int g, int c, int 
   const int64_t slot = nr.n[b] + tt;
   const uint16_t* src = k_new + ((int64_t)row * T + tt) * kHeadDim;
   const float* cb = centroids + (int64_t)(row % n_kv_heads) * g * c * DBAR;
-  const int i = blockIdx.z * 4 + w;
-  if (i < g) {
-    float x[DBAR];
+  const int i = blockIdx.z * (4 / SPLIT) + w / SPLIT;
+  float x[DBAR];
 #pragma unroll
-    for (int dd = 0; dd < DBAR; ++dd) x[dd] = h2f(src[i * DBAR + dd]);
-    float bd = INFINITY;
-    int best = 0x7fffffff;
-    for (int c0 = lane; c0 < c; c0 += 256) {
-      float cv[4][DBAR];
+  for (int dd = 0; dd < DBAR; ++dd) x[dd] = h2f(src[i * DBAR + dd]);
+  float bd = INFINITY;
+  int best = 0x7fffffff;
+  for (int c0 = 256 * (w % SPLIT) + lane; c0 < c; c0 += 256 * SPLIT) {
+    float cv[4][DBAR];
 #pragma unroll
-      for (int u = 0; u < 4; ++u) {
-        const int cc = c0 + 64 * u < c ? c0 + 64 * u : c0;
-        const float* p = cb + ((int64_t)i * c + cc) * DBAR;
+    for (int u = 0; u < 4; ++u) {
+      const int cc = c0 + 64 * u < c ? c0 + 64 * u : c0;
+      const float* p = cb + ((int64_t)i * c + cc) * DBAR;
 #pragma unroll
-        for (int dd = 0; dd < DBAR; ++dd) cv[u][dd] = p[dd];
-      }
+      for (int dd = 0; dd < DBAR; ++dd) cv[u][dd] = p[dd];
+    }
 #pragma unroll
-      for (int u = 0; u < 4; ++u) {
-        const int cc = c0 + 64 * u;
-        if (cc < c) {
-          float d = 0.f;
+    for (int u = 0; u < 4; ++u) {
+      const int cc = c0 + 64 * u;
+      if (cc < c) {
+        float d = 0.f;
 #pragma unroll
-          for (int dd = 0; dd < DBAR; ++dd) {
-            const float e = x[dd] - cv[u][dd];
-            d = fmaf(e, e, d);
-          }
-          if (d < bd || best == 0x7fffffff) { bd = d; best = cc; }
+        for (int dd = 0; dd < DBAR; ++dd) {
+          const float e = x[dd] - cv[u][dd];
+          d = fmaf(e, e, d);
         }
+        if (d < bd || best == 0x7fffffff) { bd = d; best = cc; }
       }
     }
+  }
+  auto take = [&](float od, int ob) {
+    if (ob != 0x7fffffff && (best == 0x7fffffff || od < bd || (od == bd && ob < best))) { bd = od; best = ob; }
+  };
 #pragma unroll
-    for (int o = 32; o >= 1; o >>= 1) {
-      const float od = __shfl_xor(bd, o);
-      const int ob = __shfl_xor(best, o);
-      if (ob != 0x7fffffff && (best == 0x7fffffff || od < bd || (od == bd && ob < best))) { bd = od; best = ob; }
-    }
-    if (lane == 0) {
-      if constexpr (WIDE) reinterpret_cast<uint16_t*>(pcache)[vq_wide_at(g, vq_tiles(cap), row, slot, i)] = (uint16_t)best;
-      else pcache[((int64_t)row * cap + slot) * g + vq_byte_of(i, slot)] = (uint8_t)best;
-    }
+  for (int o = 32; o >= 1; o >>= 1) take(__shfl_xor(bd, o), __shfl_xor(best, o));
+  if constexpr (SPLIT > 1) {
+    if (lane == 0) { s_d[w] = bd; s_i[w] = best; }
+    __syncthreads();
+    if (w % SPLIT == 0)
+      for (int y = 1; y < SPLIT; ++y) take(s_d[w + y], s_i[w + y]);
+  }
+  if (lane == 0 && w % SPLIT == 0) {
+    if constexpr (WIDE) reinterpret_cast<uint16_t*>(pcache)[vq_wide_at(g, vq_tiles(cap), row, slot, i)] = (uint16_t)best;
+    else pcache[((int64_t)row * cap + slot) * g + vq_byte_of(i, slot)] = (uint8_t)best;
   }
   if (threadIdx.x == 0 && blockIdx.z == 0) {
     if (acc != nullptr) acc[(int64_t)row * cap + slot] = 0.0f;
@@ -794,12 +1036,13 @@ int32_t launch_vq_assign(const Layout& L, int g, int c, const float* centroids, 
   if (T == 0) return HCA_OK;
   const uint16_t* kn = (const uint16_t*)k_new;
   const bool wide = vq_is_wide(L, g, c);
-#define HCA_ASSIGN(KERNEL, GRID)                                                                                      \
+#define HCA_ASSIGN_T(SPLIT)                                                                                           \
   do {                                                                                                                \
-    if (g == 32 && wide) KERNEL<4, true><<<GRID, 256, 0, st>>>(g, c, L.n_kv_heads, L.cap, centroids, pcache, kn, T, nr, acc_opt, pos_opt, vrow0); \
-    else if (g == 32) KERNEL<4, false><<<GRID, 256, 0, st>>>(g, c, L.n_kv_heads, L.cap, centroids, pcache, kn, T, nr, acc_opt, pos_opt, vrow0);   \
-    else if (wide) KERNEL<2, true><<<GRID, 256, 0, st>>>(g, c, L.n_kv_heads, L.cap, centroids, pcache, kn, T, nr, acc_opt, pos_opt, vrow0);      \
-    else KERNEL<2, false><<<GRID, 256, 0, st>>>(g, c, L.n_kv_heads, L.cap, centroids, pcache, kn, T, nr, acc_opt, pos_opt, vrow0);               \
+    dim3 gs((unsigned)T, (unsigned)L.rows, (unsigned)(g / (4 / SPLIT)));                                               \
+    if (g == 32 && wide) vq_assign_small_kernel<4, true, SPLIT><<<gs, 256, 0, st>>>(g, c, L.n_kv_heads, L.cap, centroids, pcache, kn, T, nr, acc_opt, pos_opt, vrow0); \
+    else if (g == 32) vq_assign_small_kernel<4, false, SPLIT><<<gs, 256, 0, st>>>(g, c, L.n_kv_heads, L.cap, centroids, pcache, kn, T, nr, acc_opt, pos_opt, vrow0);   \
+    else if (wide) vq_assign_small_kernel<2, true, SPLIT><<<gs, 256, 0, st>>>(g, c, L.n_kv_heads, L.cap, centroids, pcache, kn, T, nr, acc_opt, pos_opt, vrow0);      \
+    else vq_assign_small_kernel<2, false, SPLIT><<<gs, 256, 0, st>>>(g, c, L.n_kv_heads, L.cap, centroids, pcache, kn, T, nr, acc_opt, pos_opt, vrow0);               \
   } while (0)
 #define HCA_ASSIGN_B(GPW, GRID)                                                                                       \
   do {                                                                                                                \
@@ -808,16 +1051,31 @@ int32_t launch_vq_assign(const Layout& L, int g, int c, const float* centroids, 
     else if (wide) vq_assign_kernel<2, true, GPW><<<GRID, 256, 0, st>>>(g, c, L.n_kv_heads, L.cap, centroids, pcache, kn, T, nr, acc_opt, pos_opt, vrow0);      \
     else vq_assign_kernel<2, false, GPW><<<GRID, 256, 0, st>>>(g, c, L.n_kv_heads, L.cap, centroids, pcache, kn, T, nr, acc_opt, pos_opt, vrow0);               \
   } while (0)
-  if (T >= kAssignMfmaMinTokens && c >= kAssignMfmaMinCodewords && T * c >= kAssignMfmaMinWork) {
+  if (c > 32 && c <= kAsCodewords && T >= 256 && T * L.rows * g * c >= kAssignMfmaMinWork) {
+    dim3 gm((unsigned)((T + 255) / 256), (unsigned)L.rows, (unsigned)(g / 16));
+#define HCA_ASSIGN_SC(D, W, NT) vq_assign_small_c_kernel<D, W, NT><<<gm, 256, 0, st>>>(g, c, L.n_kv_heads, L.cap, centroids, pcache, kn, T, nr, acc_opt, pos_opt, vrow0)
+#define HCA_ASSIGN_SCN(D, W)                                                                                          \
+  do {                                                                                                                \
+    if (c <= 64) HCA_ASSIGN_SC(D, W, 2); else if (c <= 128) HCA_ASSIGN_SC(D, W, 4); else HCA_ASSIGN_SC(D, W, 8);      \
+  } while (0)
+    if (g == 32 && wide) HCA_ASSIGN_SCN(4, true);
+    else if (g == 32) HCA_ASSIGN_SCN(4, false);
+    else if (wide) HCA_ASSIGN_SCN(2, true);
+    else HCA_ASSIGN_SCN(2, false);
+#undef HCA_ASSIGN_SCN
+#undef HCA_ASSIGN_SC
+  } else if (c > kAsCodewords && T > 8) {
     // a block or a context: shortlist on the matrix cores, exact chain on the shortlist
     dim3 gm((unsigned)((T + 1023) / 1024), (unsigned)L.rows, (unsigned)g);
-    if (g == 32 && wide) vq_assign_mfma_kernel<4, true><<<gm, 512, 0, st>>>(g, c, L.n_kv_heads, L.cap, centroids, pcache, kn, T, nr, acc_opt, pos_opt, vrow0);
-    else if (g == 32) vq_assign_mfma_kernel<4, false><<<gm, 512, 0, st>>>(g, c, L.n_kv_heads, L.cap, centroids, pcache, kn, T, nr, acc_opt, pos_opt, vrow0);
-    else if (wide) vq_assign_mfma_kernel<2, true><<<gm, 512, 0, st>>>(g, c, L.n_kv_heads, L.cap, centroids, pcache, kn, T, nr, acc_opt, pos_opt, vrow0);
-    else vq_assign_mfma_kernel<2, false><<<gm, 512, 0, st>>>(g, c, L.n_kv_heads, L.cap, centroids, pcache, kn, T, nr, acc_opt, pos_opt, vrow0);
+#define HCA_ASSIGN_M(D, BT) vq_assign_mfma_kernel<D, BT><<<gm, 512, 0, st>>>(g, c, L.n_kv_heads, L.cap, centroids, pcache, kn, T, nr, acc_opt, pos_opt, vrow0)
+    if (g == 32 && c > 2048) HCA_ASSIGN_M(4, 2);
+    else if (g == 32) HCA_ASSIGN_M(4, 1);
+    else if (c > 2048) HCA_ASSIGN_M(2, 2);
+    else HCA_ASSIGN_M(2, 1);
+#undef HCA_ASSIGN_M
   } else if (T <= 8) {                              // decode appends: parallel over centroids, not over tokens
-    dim3 gs((unsigned)T, (unsigned)L.rows, (unsigned)(g / 4));
-    HCA_ASSIGN(vq_assign_small_kernel, gs);
+    if (c >= 1024) HCA_ASSIGN_T(4);
+    else HCA_ASSIGN_T(1);
   } else if ((T + 63) / 64 * L.rows * (g / 4) < 16 * 1024) {
     // a block of a few thousand tokens: with four groups per wave the launch would have at most a few waves per
     // SIMD (the chip has 1024 of them); one group per wave gives four times as many
@@ -828,7 +1086,7 @@ int32_t launch_vq_assign(const Layout& L, int g, int c, const float* centroids, 
     HCA_ASSIGN_B(4, grid);
   }
 #undef HCA_ASSIGN_B
-#undef HCA_ASSIGN
+#undef HCA_ASSIGN_T
   HCA_HIP(hipGetLastError());
   return HCA_OK;
 }

@@ -143,3 +143,48 @@ def test_score_topk_on_both_sides_of_the_short_row_line(B, oracle, bits, gs, n):
         assert np.array_equal(cand, np.repeat(st.n, 2))
     else:
         assert k <= cand[0] < n // 2
+
+
+@pytest.mark.parametrize("g,c,G,T,rows", [
+    (32, 33, 1, 16000, 8), (32, 64, 4, 11000, 6), (32, 65, 1, 8200, 8), (32, 128, 4, 4200, 8), (32, 129, 4, 2100, 16),
+    (32, 255, 1, 2100, 8), (32, 256, 4, 2047, 8), (32, 256, 4, 2303, 8), (64, 256, 4, 1100, 8), (64, 200, 1, 1500, 8),
+    (32, 257, 1, 9, 2), (32, 300, 4, 127, 2), (32, 511, 1, 1025, 1), (64, 513, 1, 300, 3), (32, 1023, 1, 8, 3),
+    (32, 1024, 1, 5, 3), (32, 2048, 1, 700, 1), (64, 2049, 4, 260, 1), (32, 8192, 1, 150, 2), (64, 8191, 1, 33, 1)])
+def test_bulk_assignment_equals_the_exhaustive_chain(B, g, c, G, T, rows):
+    """hca_vq_assign: the matrix-core forms (up to 256 centroids, more than 256) and the vector forms give the indices of
+    single-token calls, whose kernel evaluates the exact chain for every centroid; awkward tokens and centroids included."""
+    dbar = 128 // g
+    gen = torch.Generator(device="cuda").manual_seed(g * c + T)
+    m = torch.ones(128, device="cuda")
+    m[[3, 40, 77, 100]] = 8.0
+    cen = torch.randn(rows, g, c, dbar, generator=gen, device="cuda") * m.view(1, g, 1, dbar)
+    cen[:, 1, c // 2:] = cen[:, 1, : c - c // 2].clone()                   # duplicates: the lower index wins
+    cen[:, 2, 1::2] = cen[:, 2, 0:-1:2][:, : c // 2] * (1 + 2.0 ** -22)     # pairs a last bit or two apart
+    cen[:, 3] *= 1e-4
+    if c > 40:
+        cen[0, 4, 17] = 300.0                                              # |c|^2 beyond the shortlist's range
+    cen = cen.contiguous()
+    k = (torch.randn(1, rows, T, 128, generator=gen, device="cuda") * m).half()
+    k[0, 0, T // 2] = 0.0
+    k[0, 0, T // 3] *= 40.0                                                 # out of range
+    k[0, -1, T - 1] = 65504.0
+    k[0, 0, T // 4, : 2 * dbar] = 6e-8                                      # denormal
+    k[0, 0, T // 5, 8 * dbar] = float("inf")
+    k[0, 0, T // 6, 9 * dbar] = float("nan")
+    at = torch.randint(0, c, (T,), generator=gen, device="cuda")
+    k[0, 0, :, 5 * dbar: 6 * dbar] = cen[0, 5, at].half()                   # tokens on top of a centroid
+    shape = B.make_shape(1, rows * G, rows, T + 9)
+    cb = B.make_codebook(g, c, cen)
+    bulk = torch.zeros(B.hca_vq_pcache_bytes(shape, cb), dtype=torch.uint8, device="cuda")
+    single = torch.zeros_like(bulk)
+    acc = torch.full((1, rows, T + 9), 7.0, device="cuda")
+    pos = torch.full((1, rows, T + 9), -7, dtype=torch.int32, device="cuda")
+    B.hca_vq_assign(shape, cb, bulk, k, T, [4], acc, pos, [100])
+    for t in range(0, T, 8):
+        part = k[:, :, t:t + 8].contiguous()
+        B.hca_vq_assign(shape, cb, single, part, part.shape[2], [4 + t])
+    torch.cuda.synchronize()
+    assert torch.equal(bulk, single)
+    want = torch.arange(100, 100 + T, dtype=torch.int32, device="cuda").expand(rows, T)
+    assert torch.equal(pos[0, :, 4:4 + T], want) and (pos[0, :, :4] == -7).all() and (pos[0, :, 4 + T:] == -7).all()
+    assert (acc[0, :, 4:4 + T] == 0).all() and (acc[0, :, :4] == 7).all() and (acc[0, :, 4 + T:] == 7).all()
