@@ -1,6 +1,8 @@
 // Step 4: accumulated-score eviction with stable compaction.  The keep-set is the newest
 // n_protect slots plus the M - n_protect highest accumulated scores among the others (ties
 // towards the lower slot); kept slots move to the front in ascending old-slot order.
+#include <type_traits>
+
 #include "hca_internal.h"
 
 namespace hca {
@@ -49,12 +51,15 @@ static void carve(EvictWs* e, void* ws, const Layout& L, int64_t M) {
 // kept holds kept[d] = d, which nothing reads - the moves start at the block of the first dropped slot -, so its
 // workgroup returns without touching acc or the list.  The chunk prefixes say so: slots kept below the next
 // chunk's start = #(above T) + min(#(equal to T), r_eq) counted below it.
+// A workgroup takes a chunk, 4096 slots at a time; wave w of it takes 1024 consecutive ones, all sixteen loads per lane
+// in flight, and places them by ballot.  8 rows of 512 Ki slots: 14 us (30 with an atomic minimum per wave and shuffles
+// for the positions).
 __global__ __launch_bounds__(256) void evict_positions(const float* __restrict__ acc, int64_t stride, int64_t chunk,
                                                        int nchunks, int n_kv_heads, SelRows sr, NRes nr,
                                                        uint32_t* __restrict__ state,
-                                                       const uint32_t* __restrict__ coff, int64_t M,
+                                                       const uint32_t* __restrict__ ccount, int64_t M,
                                                        int32_t* __restrict__ kept, int skip_identity) {
-  __shared__ uint32_t wsum[2][4];
+  __shared__ uint32_t red[2][4];
   const int row = blockIdx.y;
   const int b = row / n_kv_heads;
   const int64_t want = sr.want[b];
@@ -65,71 +70,84 @@ __global__ __launch_bounds__(256) void evict_positions(const float* __restrict__
   int64_t c1 = c0 + chunk;
   if (c1 > n) c1 = n;
   const uint32_t T = state[4 * row], req = state[4 * row + 1];
+  const int lane = threadIdx.x & 63, w = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+  // slots above / equal to T in the chunks before this one
+  const uint2* counts = reinterpret_cast<const uint2*>(ccount) + (int64_t)row * nchunks;
+  uint32_t sg = 0, se = 0;
+  for (int c = threadIdx.x; c < (int)blockIdx.x; c += 256) { sg += counts[c].x; se += counts[c].y; }
+#pragma unroll
+  for (int o = 32; o >= 1; o >>= 1) { sg += __shfl_xor(sg, o); se += __shfl_xor(se, o); }
+  if (lane == 0) { red[0][w] = sg; red[1][w] = se; }
+  __syncthreads();
+  uint32_t base_g = red[0][0] + red[0][1] + red[0][2] + red[0][3];
+  uint32_t base_e = red[1][0] + red[1][1] + red[1][2] + red[1][3];
   if (skip_identity && (int)blockIdx.x + 1 < nchunks && c0 + chunk <= nsel) {
-    const uint32_t ng = coff[((int64_t)row * nchunks + blockIdx.x + 1) * 2];
-    const uint32_t ne = coff[((int64_t)row * nchunks + blockIdx.x + 1) * 2 + 1];
+    const uint32_t ng = base_g + counts[blockIdx.x].x, ne = base_e + counts[blockIdx.x].y;
     if ((int64_t)ng + (int64_t)(ne < req ? ne : req) == c0 + chunk) return;
   }
-  uint32_t base_g = coff[((int64_t)row * nchunks + blockIdx.x) * 2];
-  uint32_t base_e = coff[((int64_t)row * nchunks + blockIdx.x) * 2 + 1];
+  // only the first chunk that drops a slot reports it: a minimum from every wave of the row, hundreds of atomics on one
+  // word, was most of this kernel's time
+  const bool first_drop = (int64_t)base_g + (int64_t)(base_e < req ? base_e : req) == c0;
   const float* v = acc + (int64_t)row * stride;
   int32_t* out = kept + (int64_t)row * M;
-  const int lane = threadIdx.x & 63, w = threadIdx.x >> 6;
-  uint32_t hole = 0xffffffffu;               // lowest slot this thread saw dropped
-  for (int64_t s0 = c0; s0 < c1; s0 += 1024) {
-    const int64_t j0 = s0 + 4 * threadIdx.x;
-    bool fg[4], fe[4];
+  const uint64_t lt = (1ull << lane) - 1;
+  int64_t hole = -1;                         // lowest slot this wave saw dropped
+  for (int64_t s0 = c0; s0 < c1; s0 += 4096) {
+    const int64_t w0 = s0 + 1024 * w + lane;
+    float f[16];
+#pragma unroll
+    for (int x = 0; x < 16; ++x) f[x] = v[w0 + 64 * x < nsel ? w0 + 64 * x : 0];
     uint32_t ng = 0, ne = 0;
+    uint64_t mg[16], me[16];
 #pragma unroll
-    for (int i = 0; i < 4; ++i) {
-      const int64_t j = j0 + i;
-      uint32_t key = 0;
-      const bool in = j < nsel;
-      if (in) key = order_key(v[j]);
-      fg[i] = in && key > T;
-      fe[i] = in && key == T;
-      ng += fg[i]; ne += fe[i];
+    for (int x = 0; x < 16; ++x) {
+      const uint32_t key = order_key(f[x]);
+      const bool in = w0 + 64 * x < nsel && w0 + 64 * x < c1;
+      mg[x] = __builtin_amdgcn_ballot_w64(in && key > T);
+      me[x] = __builtin_amdgcn_ballot_w64(in && key == T);
+      ng += (uint32_t)__popcll(mg[x]);
+      ne += (uint32_t)__popcll(me[x]);
     }
-    uint32_t ig = ng, ie = ne;
-#pragma unroll
-    for (int o = 1; o < 64; o <<= 1) {
-      const uint32_t ag = __shfl_up(ig, o), ae = __shfl_up(ie, o);
-      if (lane >= o) { ig += ag; ie += ae; }
-    }
-    if (lane == 63) { wsum[0][w] = ig; wsum[1][w] = ie; }
+    __syncthreads();                          // the previous round's counts have been read
+    if (lane == 0) { red[0][w] = ng; red[1][w] = ne; }
     __syncthreads();
-    uint32_t pg = base_g + ig - ng, pe = base_e + ie - ne;
-    for (int x = 0; x < w; ++x) { pg += wsum[0][x]; pe += wsum[1][x]; }
-    const uint32_t tot_g = wsum[0][0] + wsum[0][1] + wsum[0][2] + wsum[0][3];
-    const uint32_t tot_e = wsum[1][0] + wsum[1][1] + wsum[1][2] + wsum[1][3];
+    uint32_t pg = base_g, pe = base_e;
 #pragma unroll
-    for (int i = 0; i < 4; ++i) {
-      const int64_t j = j0 + i;
-      const bool take = fg[i] || (fe[i] && pe < req);
-      if (take) out[pg + (pe < req ? pe : req)] = (int32_t)j;
-      else if (j < nsel && (uint32_t)j < hole) hole = (uint32_t)j;
-      if (j >= nsel && j < n) out[want + (j - nsel)] = (int32_t)j;  // protected newest slots
-      pg += fg[i]; pe += fe[i];
+    for (int x = 0; x < 4; ++x) {
+      if (x < w) { pg += red[0][x]; pe += red[1][x]; }
+      base_g += red[0][x];
+      base_e += red[1][x];
     }
-    base_g += tot_g; base_e += tot_e;
-    __syncthreads();
+#pragma unroll
+    for (int x = 0; x < 16; ++x) {
+      const int64_t j = w0 + 64 * x;
+      const uint32_t g = pg + (uint32_t)__popcll(mg[x] & lt), e = pe + (uint32_t)__popcll(me[x] & lt);
+      const bool is_e = (me[x] >> lane) & 1, take = ((mg[x] >> lane) & 1) || (is_e && e < req);
+      if (take) out[g + (e < req ? e : req)] = (int32_t)j;
+      const uint64_t gone = __builtin_amdgcn_ballot_w64(!take && j < nsel && j < c1);
+      if (hole < 0 && gone != 0) hole = s0 + 1024 * w + 64 * x + __builtin_ctzll(gone);
+      if (j >= nsel && j < c1) out[want + (j - nsel)] = (int32_t)j;     // protected newest slots
+      pg += (uint32_t)__popcll(mg[x]);
+      pe += (uint32_t)__popcll(me[x]);
+    }
   }
   // every slot below the first dropped one keeps its place: the moves can start there
-#pragma unroll
-  for (int o = 32; o >= 1; o >>= 1) {
-    const uint32_t other = __shfl_xor(hole, o);
-    if (other < hole) hole = other;
-  }
-  if (lane == 0 && hole != 0xffffffffu) atomicMin(&state[4 * row + 2], hole);
+  if (lane == 0 && hole >= 0 && first_drop) atomicMin(&state[4 * row + 2], (uint32_t)hole);
 }
 
-// kept[d] -> staging slot d.  One thread per (d, j) 16-byte (4-bit) or 8-byte (2-bit) piece.
+// kept[d] -> staging slot d.  A wave moves 64 consecutive destination slots at a time: lane (t, j) the j-th piece of slot
+// 16 u + t (16 bytes, or 8 with 2-bit codes), u = 0..3, so that every store instruction fills whole lines of a block, and
+// lane l the meta, accumulated score and value row of slot l.  All seven loads are in flight together, and the next 64
+// keep-list entries behind them.  Bound by memory: where few slots of a block are kept, every 16-byte piece costs its line.
+// 8 rows, 256 Ki of 512 Ki slots kept: 93 us (101 with neighbouring lanes on the four pieces of one slot).
 template <int BITS>
 __global__ __launch_bounds__(256) void evict_gather(Layout L, const uint8_t* __restrict__ kcache,
                                                     const float* __restrict__ acc, const int32_t* __restrict__ pos,
                                                     int n_kv_heads, SelRows sr, int64_t M, int64_t d0, int64_t d1,
                                                     const int32_t* __restrict__ kept, EvictDst e,
                                                     const uint32_t* __restrict__ first_hole) {
+  using Piece = typename std::conditional<BITS == 4, uint4, uint2>::type;
+  constexpr int kShift = BITS == 4 ? 4 : 5;                 // log2 of the tokens per block
   const int row = blockIdx.y;
   if (sr.want[row / n_kv_heads] < 0) return;
   // in place: slots below the block of the first dropped slot already hold their own data, so the walk starts
@@ -143,26 +161,40 @@ __global__ __launch_bounds__(256) void evict_gather(Layout L, const uint8_t* __r
   const uint8_t* mrow = kcache + L.meta_off + (int64_t)row * L.meta_row_bytes();
   uint8_t* cdst = e.codes + (int64_t)row * e.codes_row;
   uint8_t* mdst = e.meta + (int64_t)row * e.meta_row;
-  for (int64_t gid = (int64_t)blockIdx.x * 256 + threadIdx.x; gid < (d1 - d0) * 4; gid += (int64_t)gridDim.x * 256) {
-  const int64_t d = d0 + (gid >> 2);
-  const int j = (int)(gid & 3);
-  const int64_t s = kept[(int64_t)row * M + d];
-  if (BITS == 4) {
-    const uint4 w = *reinterpret_cast<const uint4*>(crow + (s >> 4) * kBlockBytes + ((s & 15) + 16 * j) * 16);
-    *reinterpret_cast<uint4*>(cdst + (d >> 4) * kBlockBytes + ((d & 15) + 16 * j) * 16) = w;
-    if (j == 0)
-      *reinterpret_cast<uint4*>(mdst + (d >> 4) * kMetaBytes + (d & 15) * 16) =
-          *reinterpret_cast<const uint4*>(mrow + (s >> 4) * kMetaBytes + (s & 15) * 16);
-  } else {
-    const uint2 w = *reinterpret_cast<const uint2*>(crow + (s >> 5) * kBlockBytes + ((s & 15) + 16 * j) * 16 +
-                                                    8 * ((s >> 4) & 1));
-    *reinterpret_cast<uint2*>(cdst + (d >> 5) * kBlockBytes + ((d & 15) + 16 * j) * 16 + 8 * ((d >> 4) & 1)) = w;
-    if (j == 0)
-      *reinterpret_cast<uint2*>(mdst + (d >> 5) * kMetaBytes + (d & 31) * 8) =
-          *reinterpret_cast<const uint2*>(mrow + (s >> 5) * kMetaBytes + (s & 31) * 8);
-  }
-  if (j == 1) e.acc[(int64_t)row * e.ap_row + d] = acc[(int64_t)row * L.cap + s];
-  if (j == 2) e.pos[(int64_t)row * e.ap_row + d] = pos[(int64_t)row * L.cap + s];
+  const int32_t* krow = kept + (int64_t)row * M;
+  const float* arow = acc + (int64_t)row * L.cap;
+  const int32_t* prow = pos + (int64_t)row * L.cap;
+  const int lane = threadIdx.x & 63, t = lane & 15, j = lane >> 4;
+  // byte offsets of piece j and of the meta of slot x
+  auto piece_at = [&](int64_t x) {
+    return (x >> kShift) * kBlockBytes + ((x & 15) + 16 * j) * 16 + (BITS == 4 ? 0 : 8 * ((x >> 4) & 1));
+  };
+  auto meta_at = [](int64_t x) { return (x >> kShift) * kMetaBytes + (x & ((1 << kShift) - 1)) * (int)sizeof(Piece); };
+  const int64_t step = (int64_t)gridDim.x * 256;
+  int64_t D = (d0 & ~(int64_t)63) + ((int64_t)blockIdx.x * 4 + (threadIdx.x >> 6)) * 64;
+  auto source = [&](int64_t d) { return d >= d0 && d < d1 ? krow[d] : 0; };
+  int32_t next = D < d1 ? source(D + lane) : 0;
+  for (; D < d1; D += step) {
+    const int32_t s = next;
+    const int64_t d = D + lane;
+    const bool in = d >= d0 && d < d1;
+    Piece c[4];
+#pragma unroll
+    for (int u = 0; u < 4; ++u) c[u] = *reinterpret_cast<const Piece*>(crow + piece_at(__shfl(s, 16 * u + t)));
+    const Piece m = *reinterpret_cast<const Piece*>(mrow + meta_at(s));
+    const float a = arow[s];
+    const int32_t p = prow[s];
+    if (D + step < d1) next = source(D + step + lane);
+#pragma unroll
+    for (int u = 0; u < 4; ++u) {
+      const int64_t x = D + 16 * u + t;
+      if (x >= d0 && x < d1) *reinterpret_cast<Piece*>(cdst + piece_at(x)) = c[u];
+    }
+    if (in) {
+      *reinterpret_cast<Piece*>(mdst + meta_at(d)) = m;
+      e.acc[(int64_t)row * e.ap_row + d] = a;
+      e.pos[(int64_t)row * e.ap_row + d] = p;
+    }
   }
 }
 
@@ -270,7 +302,7 @@ static int32_t evict_prepare(const Layout& L, void* kcache, float* acc, int32_t*
   if (rc != HCA_OK) return rc;
   dim3 g((unsigned)p.nchunks, (unsigned)L.rows);
   pl->state = p.state;
-  evict_positions<<<g, 256, 0, st>>>(acc, L.cap, p.chunk, p.nchunks, L.n_kv_heads, sr, nr, p.state, p.coff, M, pl->kept,
+  evict_positions<<<g, 256, 0, st>>>(acc, L.cap, p.chunk, p.nchunks, L.n_kv_heads, sr, nr, p.state, p.ccount, M, pl->kept,
                                      (!pl->oop && kept == nullptr) ? 1 : 0);
   HCA_HIP(hipGetLastError());
   return HCA_OK;
@@ -460,7 +492,7 @@ int32_t launch_vq_evict(const Layout& L, int g, int c, uint8_t* pcache, float* a
   int32_t rc = select_run(p, acc, L.cap, L.rows, L.n_kv_heads, sr, st);
   if (rc != HCA_OK) return rc;
   dim3 g1((unsigned)p.nchunks, (unsigned)L.rows);
-  evict_positions<<<g1, 256, 0, st>>>(acc, L.cap, p.chunk, p.nchunks, L.n_kv_heads, sr, nr, p.state, p.coff, M, kp, 0);
+  evict_positions<<<g1, 256, 0, st>>>(acc, L.cap, p.chunk, p.nchunks, L.n_kv_heads, sr, nr, p.state, p.ccount, M, kp, 0);
   if (oop) {
     dim3 gg(wgs(M * pieces), (unsigned)L.rows);
     vq_evict_gather<<<gg, 256, 0, st>>>(rb, 0, rb, 0, pieces, wide ? 1 : 0, g, L.cap, L.cap, pcache, acc, pos, L.n_kv_heads,

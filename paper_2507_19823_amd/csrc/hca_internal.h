@@ -64,9 +64,8 @@ struct SelectPlan {
   int32_t nchunks;   // chunks per row (<= 1024)
   // workspace sub-buffers (device pointers)
   uint32_t* hist;    // [rows][3][2048]
-  uint32_t* state;   // [rows][4]: key prefix, remaining count, (unused), (unused)
+  uint32_t* state;   // [rows][4]: threshold key, number of slots equal to it to take, lowest slot not selected, resolved
   uint32_t* ccount;  // [rows][nchunks][2]  (#greater, #equal) per chunk
-  uint32_t* coff;    // [rows][nchunks][2]  exclusive prefix of ccount
 };
 struct SelRows {     // per-sequence selection parameters, by value
   int64_t nsel[kMaxBatch];   // slots [0, nsel) take part
@@ -77,7 +76,7 @@ size_t topk_workspace_bytes(int rows, int64_t cap);
 void select_plan(SelectPlan* p, void* ws, int rows, int64_t nmax);
 // Enqueues the selection passes over `vals` ([rows][stride] fp32).  Afterwards, for row r:
 // state[r][0] = threshold key T, state[r][1] = number of slots with key == T to take (lowest first),
-// coff = exclusive chunk prefixes of (#key > T, #key == T).
+// ccount = per-chunk counts of (#key > T, #key == T).
 int32_t select_run(const SelectPlan& p, const float* vals, int64_t stride, int rows, int n_kv_heads,
                    const SelRows& sr, hipStream_t st);
 

@@ -20,7 +20,7 @@ size_t select_workspace_bytes(int rows, int64_t nmax) {
   size_t b = 0;
   b += align_up((int64_t)rows * 3 * kBins * 4, 256);
   b += align_up((int64_t)rows * 4 * 4, 256);
-  b += 2 * align_up((int64_t)rows * 1024 * 2 * 4, 256);
+  b += align_up((int64_t)rows * 1024 * 2 * 4, 256);
   return b;
 }
 
@@ -33,54 +33,179 @@ void select_plan(SelectPlan* p, void* ws, int rows, int64_t nmax) {
   uint8_t* w = (uint8_t*)ws;
   p->hist = (uint32_t*)w;   w += align_up((int64_t)rows * 3 * kBins * 4, 256);
   p->state = (uint32_t*)w;  w += align_up((int64_t)rows * 4 * 4, 256);
-  p->ccount = (uint32_t*)w; w += align_up((int64_t)rows * 1024 * 2 * 4, 256);
-  p->coff = (uint32_t*)w;
+  p->ccount = (uint32_t*)w;
 }
 
-__global__ void sel_init(uint32_t* hist, uint32_t* state, int rows, int n_kv_heads, SelRows sr) {
-  const int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-  if (i < (int64_t)rows * 3 * kBins) hist[i] = 0;
-  if (i < rows) {
-    const int64_t want = sr.want[i / n_kv_heads];
-    state[4 * i + 0] = (want == 0) ? 0xffffffffu : 0u;
-    state[4 * i + 1] = want > 0 ? (uint32_t)want : 0u;
-    state[4 * i + 2] = 0xffffffffu;          // lowest slot that is not selected (filled in by the eviction's ordered pass)
-    state[4 * i + 3] = 0u;                   // 1: threshold found by the zero-threshold shortcut, the radix passes skip the row
+// Sixteen loads of a 4096-slot tile in flight per thread (256 threads); slots at or past `end` are not live.
+template <typename F>
+__device__ __forceinline__ void sel_each(const float* __restrict__ v, int64_t c0, int64_t c1, F&& f) {
+  for (int64_t s0 = c0; s0 < c1; s0 += 4096) {
+    float x[16];
+#pragma unroll
+    for (int i = 0; i < 16; ++i) {
+      const int64_t j = s0 + i * 256 + threadIdx.x;
+      x[i] = v[j < c1 ? j : c1 - 1];
+    }
+#pragma unroll
+    for (int i = 0; i < 16; ++i) f(order_key(x[i]), s0 + i * 256 + threadIdx.x < c1);
   }
+}
+
+// The bin of a 2048-bin histogram that holds the rem-th largest key, and how many of it are left to take: the same for
+// every thread of the workgroup (256).  Every workgroup of the pass that needs a bin finds it from the finished
+// histogram by itself - 8 KB from L2 - instead of waiting for a launch of its own that would.
+__device__ __forceinline__ void sel_find_bin(const uint32_t* __restrict__ gh, uint32_t* bin, uint32_t* rem) {
+  __shared__ uint32_t wsum[4], s_bin, s_rem;
+  const int t = threadIdx.x, lane = t & 63, w = t >> 6;
+  uint32_t h[8];
+  uint32_t sum = 0;
+#pragma unroll
+  for (int i = 0; i < 8; ++i) { h[i] = gh[kBins - 1 - (8 * t + i)]; sum += h[i]; }     // bins from the top
+  uint32_t inc = sum;
+#pragma unroll
+  for (int o = 1; o < 64; o <<= 1) {
+    const uint32_t x = __shfl_up(inc, o);
+    if (lane >= o) inc += x;
+  }
+  __syncthreads();
+  if (lane == 63) wsum[w] = inc;
+  __syncthreads();
+  uint32_t running = inc - sum;
+  for (int x = 0; x < w; ++x) running += wsum[x];
+  const uint32_t want = *rem;
+#pragma unroll
+  for (int i = 0; i < 8; ++i) {
+    if (running < want && want <= running + h[i]) { s_bin = (uint32_t)(kBins - 1 - (8 * t + i)); s_rem = want - running; }
+    running += h[i];
+  }
+  __syncthreads();
+  *bin = s_bin;
+  *rem = s_rem;
+}
+
+// Leading digits of the threshold key known after PASSES histograms, and how many are left to take among the keys that
+// share them.
+template <int PASSES>
+__device__ __forceinline__ void sel_prefix(const uint32_t* __restrict__ hist, int row, uint32_t want, uint32_t* prefix,
+                                           uint32_t* rem) {
+  *prefix = 0;
+  *rem = want;
+#pragma unroll
+  for (int p = 0; p < PASSES; ++p) {
+    uint32_t bin;
+    sel_find_bin(hist + ((int64_t)row * 3 + p) * kBins, &bin, rem);
+    *prefix |= bin << pass_shift(p);
+  }
+}
+
+// Per-chunk counts of keys above and equal to T; clears the row's histograms on the way (AT_ZERO).
+// AT_ZERO: against the key of +0.0f, before any radix pass (the shortcut below); otherwise against the row's threshold -
+// found here from the three histograms -, and rows that the shortcut resolved keep the counts they already have.
+template <bool AT_ZERO>
+__global__ __launch_bounds__(256) void sel_count(const float* __restrict__ vals, int64_t stride, int64_t chunk,
+                                                 int n_kv_heads, SelRows sr, uint32_t* __restrict__ state,
+                                                 uint32_t* __restrict__ hist, uint32_t* __restrict__ ccount) {
+  __shared__ uint32_t red[2][4];
+  const int row = blockIdx.y;
+  const int64_t want = sr.want[row / n_kv_heads];
+  if (want < 0) return;
+  if (!AT_ZERO && state[4 * row + 3] != 0) return;
+  uint32_t T = order_key(0.0f);
+  if constexpr (AT_ZERO) {
+    uint32_t* gh = hist + (int64_t)row * 3 * kBins;
+    for (int i = blockIdx.x * 256 + threadIdx.x; i < 3 * kBins; i += gridDim.x * 256) gh[i] = 0;
+  } else if (want == 0) {
+    T = 0xffffffffu;
+  } else {
+    uint32_t rem;
+    sel_prefix<3>(hist, row, (uint32_t)want, &T, &rem);
+    if (blockIdx.x == 0 && threadIdx.x == 0) { state[4 * row] = T; state[4 * row + 1] = rem; }
+  }
+  const int64_t nsel = sr.nsel[row / n_kv_heads];
+  const int64_t c0 = (int64_t)blockIdx.x * chunk;
+  int64_t c1 = c0 + chunk;
+  if (c1 > nsel) c1 = nsel;
+  uint32_t gt = 0, eq = 0;
+  sel_each(vals + (int64_t)row * stride, c0, c1, [&](uint32_t key, bool live) {
+    gt += live && key > T;
+    eq += live && key == T;
+  });
+#pragma unroll
+  for (int o = 32; o >= 1; o >>= 1) { gt += __shfl_xor(gt, o); eq += __shfl_xor(eq, o); }
+  const int w = threadIdx.x >> 6;
+  if ((threadIdx.x & 63) == 0) { red[0][w] = gt; red[1][w] = eq; }
+  __syncthreads();
+  if (threadIdx.x == 0) {
+    uint32_t* o = ccount + ((int64_t)row * gridDim.x + blockIdx.x) * 2;
+    o[0] = red[0][0] + red[0][1] + red[0][2] + red[0][3];
+    o[1] = red[1][0] + red[1][1] + red[1][2] + red[1][3];
+  }
+}
+
+// The zero-threshold shortcut, decided by every workgroup of the first histogram pass from the chunk counts (at most
+// 1024 pairs).  Accumulated scores are sums of softmax weights: never negative, and exactly 0 for every token that was
+// never selected - most of a long context.  When fewer than `want` slots lie above 0 and the zeros make up the rest,
+// the want-th largest key is the key of +0.0f and the number of zeros to take is want - #(above 0): exactly what the
+// three radix passes would find, from one pass whose per-chunk counts are also the ones the ordered pass needs.
+__device__ __forceinline__ bool sel_try_zero(const uint32_t* __restrict__ ccount, int nchunks, int row, int64_t want,
+                                             uint32_t* __restrict__ state, bool writer) {
+  __shared__ uint32_t red[2][4];
+  const int t = threadIdx.x;
+  uint32_t g = 0, e = 0;
+  for (int c = t; c < nchunks; c += 256) {
+    g += ccount[((int64_t)row * nchunks + c) * 2];
+    e += ccount[((int64_t)row * nchunks + c) * 2 + 1];
+  }
+#pragma unroll
+  for (int o = 32; o >= 1; o >>= 1) { g += __shfl_xor(g, o); e += __shfl_xor(e, o); }
+  if ((t & 63) == 0) { red[0][t >> 6] = g; red[1][t >> 6] = e; }
+  __syncthreads();
+  const uint64_t above = (uint64_t)red[0][0] + red[0][1] + red[0][2] + red[0][3];
+  const uint64_t zeros = (uint64_t)red[1][0] + red[1][1] + red[1][2] + red[1][3];
+  const bool zero = want > 0 && above < (uint64_t)want && (uint64_t)want <= above + zeros;
+  if (writer && t == 0) {
+    state[4 * row + 0] = zero ? order_key(0.0f) : 0xffffffffu;
+    state[4 * row + 1] = zero ? (uint32_t)((uint64_t)want - above) : 0u;
+    state[4 * row + 2] = 0xffffffffu;        // lowest slot that is not selected (filled in by the eviction's ordered pass)
+    state[4 * row + 3] = zero ? 1u : 0u;     // 1: threshold found here, the radix passes skip the row
+  }
+  return zero;
 }
 
 template <int PASS>
 __global__ __launch_bounds__(256) void sel_hist(const float* __restrict__ vals, int64_t stride, int64_t chunk,
                                                 int n_kv_heads, SelRows sr, uint32_t* __restrict__ hist,
-                                                const uint32_t* __restrict__ state) {
+                                                uint32_t* __restrict__ state, const uint32_t* __restrict__ ccount) {
   __shared__ uint32_t lh[kBins];
   const int row = blockIdx.y;
-  const int64_t nsel = sr.nsel[row / n_kv_heads];
-  if (sr.want[row / n_kv_heads] <= 0 || state[4 * row + 3] != 0) return;
+  const int64_t nsel = sr.nsel[row / n_kv_heads], want = sr.want[row / n_kv_heads];
+  if constexpr (PASS == 0) {
+    if (want < 0) return;
+    if (sel_try_zero(ccount, (int)gridDim.x, row, want, state, blockIdx.x == 0)) return;
+  } else if (want > 0 && state[4 * row + 3] != 0) {
+    return;
+  }
+  if (want <= 0) return;
   const int64_t c0 = (int64_t)blockIdx.x * chunk;
   if (c0 >= nsel) return;
   int64_t c1 = c0 + chunk;
   if (c1 > nsel) c1 = nsel;
+  uint32_t prefix, rem;
+  sel_prefix<PASS>(hist, row, (uint32_t)want, &prefix, &rem);
   for (int i = threadIdx.x; i < kBins; i += 256) lh[i] = 0;
   __syncthreads();
-  const uint32_t prefix = state[4 * row];
-  const float* v = vals + (int64_t)row * stride;
   const int lane = threadIdx.x & 63;
-  for (int64_t j0 = c0; j0 < c1; j0 += 256) {
-    const int64_t j = j0 + threadIdx.x;
-    bool hit = j < c1;
-    uint32_t bin = 0;
-    if (hit) {
-      const uint32_t key = order_key(v[j]);
-      if (PASS == 0) {
-        bin = key >> 21;
-      } else if (PASS == 1) {
-        hit = (key >> 21) == (prefix >> 21);
-        bin = (key >> 10) & 2047u;
-      } else {
-        hit = (key >> 10) == (prefix >> 10);
-        bin = key & 1023u;
-      }
+  sel_each(vals + (int64_t)row * stride, c0, c1, [&](uint32_t key, bool live) {
+    bool hit = live;
+    uint32_t bin;
+    if (PASS == 0) {
+      bin = key >> 21;
+    } else if (PASS == 1) {
+      hit = hit && (key >> 21) == (prefix >> 21);
+      bin = (key >> 10) & 2047u;
+    } else {
+      hit = hit && (key >> 10) == (prefix >> 10);
+      bin = key & 1023u;
     }
     // accumulated scores are mostly equal (0), so a whole wave usually lands in one bin: one
     // atomic for the wave instead of 64 on the same LDS word
@@ -94,7 +219,7 @@ __global__ __launch_bounds__(256) void sel_hist(const float* __restrict__ vals, 
         atomicAdd(&lh[bin], 1u);
       }
     }
-  }
+  });
   __syncthreads();
   uint32_t* gh = hist + ((int64_t)row * 3 + PASS) * kBins;
   for (int i = threadIdx.x; i < kBins; i += 256) {
@@ -103,159 +228,17 @@ __global__ __launch_bounds__(256) void sel_hist(const float* __restrict__ vals, 
   }
 }
 
-// One workgroup per row: picks the bin holding the `remaining`-th largest key.
-template <int PASS>
-__global__ __launch_bounds__(256) void sel_scan(const uint32_t* __restrict__ hist, uint32_t* __restrict__ state,
-                                                int n_kv_heads, SelRows sr) {
-  __shared__ uint32_t s[256];
-  const int row = blockIdx.x;
-  if (sr.want[row / n_kv_heads] <= 0 || state[4 * row + 3] != 0) return;
-  const uint32_t remaining = state[4 * row + 1];
-  const uint32_t* gh = hist + ((int64_t)row * 3 + PASS) * kBins;
-  const int t = threadIdx.x;
-  uint32_t h[8];
-  uint32_t sum = 0;
-#pragma unroll
-  for (int i = 0; i < 8; ++i) { h[i] = gh[8 * t + i]; sum += h[i]; }
-  s[t] = sum;
-  __syncthreads();
-  // inclusive suffix scan over threads (Hillis-Steele)
-  for (int o = 1; o < 256; o <<= 1) {
-    const uint32_t add = (t + o < 256) ? s[t + o] : 0;
-    __syncthreads();
-    s[t] += add;
-    __syncthreads();
-  }
-  uint32_t running = s[t] - sum;  // keys in bins above this thread's range
-#pragma unroll
-  for (int i = 7; i >= 0; --i) {
-    if (running < remaining && remaining <= running + h[i]) {
-      state[4 * row + 0] |= (uint32_t)(8 * t + i) << pass_shift(PASS);
-      state[4 * row + 1] = remaining - running;
-    }
-    running += h[i];
-  }
-}
-
-// AT_ZERO: the counts are taken against the key of +0.0f, before any radix pass (the shortcut below); otherwise
-// against the row's threshold, and rows that the shortcut resolved keep the counts they already have.
-template <bool AT_ZERO>
-__global__ __launch_bounds__(256) void sel_count(const float* __restrict__ vals, int64_t stride, int64_t chunk,
-                                                 int n_kv_heads, SelRows sr, const uint32_t* __restrict__ state,
-                                                 uint32_t* __restrict__ ccount) {
-  __shared__ uint32_t red[2][4];
-  const int row = blockIdx.y;
-  if (sr.want[row / n_kv_heads] < 0) return;
-  if (!AT_ZERO && state[4 * row + 3] != 0) return;
-  const int64_t nsel = sr.nsel[row / n_kv_heads];
-  const int64_t c0 = (int64_t)blockIdx.x * chunk;
-  int64_t c1 = c0 + chunk;
-  if (c1 > nsel) c1 = nsel;
-  const uint32_t T = AT_ZERO ? order_key(0.0f) : state[4 * row];
-  const float* v = vals + (int64_t)row * stride;
-  uint32_t gt = 0, eq = 0;
-  for (int64_t j = c0 + threadIdx.x; j < c1; j += 256) {
-    const uint32_t key = order_key(v[j]);
-    gt += key > T;
-    eq += key == T;
-  }
-#pragma unroll
-  for (int o = 32; o >= 1; o >>= 1) { gt += __shfl_xor(gt, o); eq += __shfl_xor(eq, o); }
-  const int w = threadIdx.x >> 6;
-  if ((threadIdx.x & 63) == 0) { red[0][w] = gt; red[1][w] = eq; }
-  __syncthreads();
-  if (threadIdx.x == 0) {
-    uint32_t* o = ccount + ((int64_t)row * gridDim.x + blockIdx.x) * 2;
-    o[0] = red[0][0] + red[0][1] + red[0][2] + red[0][3];
-    o[1] = red[1][0] + red[1][1] + red[1][2] + red[1][3];
-  }
-}
-
-// The zero-threshold shortcut.  Accumulated scores are sums of softmax weights: never negative, and exactly 0 for
-// every token that was never selected - most of a long context.  When fewer than `want` slots lie above 0 and the
-// zeros make up the rest, the want-th largest key is the key of +0.0f and the number of zeros to take is
-// want - #(above 0): exactly what the three radix passes would find, from one pass whose per-chunk counts are also
-// the ones the ordered pass needs.  One workgroup per row sums the chunk counts and decides.
-__global__ __launch_bounds__(256) void sel_try_zero(const uint32_t* __restrict__ ccount, uint32_t* __restrict__ state,
-                                                    int nchunks, int n_kv_heads, SelRows sr) {
-  __shared__ uint32_t s[2][256];
-  const int row = blockIdx.x;
-  const int64_t want = sr.want[row / n_kv_heads];
-  if (want <= 0) return;
-  const int t = threadIdx.x;
-  uint32_t g = 0, e = 0;
-  for (int c = t; c < nchunks; c += 256) {
-    g += ccount[((int64_t)row * nchunks + c) * 2];
-    e += ccount[((int64_t)row * nchunks + c) * 2 + 1];
-  }
-  s[0][t] = g; s[1][t] = e;
-  __syncthreads();
-  for (int o = 128; o >= 1; o >>= 1) {
-    if (t < o) { s[0][t] += s[0][t + o]; s[1][t] += s[1][t + o]; }
-    __syncthreads();
-  }
-  if (t == 0) {
-    const uint64_t above = s[0][0], zeros = s[1][0];
-    if (above < (uint64_t)want && (uint64_t)want <= above + zeros) {
-      state[4 * row + 0] = order_key(0.0f);
-      state[4 * row + 1] = (uint32_t)((uint64_t)want - above);
-      state[4 * row + 3] = 1u;
-    }
-  }
-}
-
-// Exclusive prefix over the chunks of a row (nchunks <= 1024).
-__global__ __launch_bounds__(256) void sel_offsets(const uint32_t* __restrict__ ccount, uint32_t* __restrict__ coff,
-                                                   int nchunks, int n_kv_heads, SelRows sr) {
-  __shared__ uint32_t s[2][256];
-  const int row = blockIdx.x;
-  if (sr.want[row / n_kv_heads] < 0) return;
-  const int t = threadIdx.x;
-  uint32_t g[4], e[4], sg = 0, se = 0;
-#pragma unroll
-  for (int i = 0; i < 4; ++i) {
-    const int c = 4 * t + i;
-    g[i] = c < nchunks ? ccount[((int64_t)row * nchunks + c) * 2] : 0;
-    e[i] = c < nchunks ? ccount[((int64_t)row * nchunks + c) * 2 + 1] : 0;
-    sg += g[i]; se += e[i];
-  }
-  s[0][t] = sg; s[1][t] = se;
-  __syncthreads();
-  for (int o = 1; o < 256; o <<= 1) {
-    const uint32_t ag = t >= o ? s[0][t - o] : 0, ae = t >= o ? s[1][t - o] : 0;
-    __syncthreads();
-    s[0][t] += ag; s[1][t] += ae;
-    __syncthreads();
-  }
-  uint32_t rg = s[0][t] - sg, re = s[1][t] - se;
-#pragma unroll
-  for (int i = 0; i < 4; ++i) {
-    const int c = 4 * t + i;
-    if (c < nchunks) {
-      coff[((int64_t)row * nchunks + c) * 2] = rg;
-      coff[((int64_t)row * nchunks + c) * 2 + 1] = re;
-    }
-    rg += g[i]; re += e[i];
-  }
-}
-
+// Five launches: counts against 0; first histogram (and the shortcut); second; third; counts against the threshold.
+// The last three find nothing to do for rows that the shortcut resolved.  With a launch each for clearing, for the
+// shortcut, for every bin search and for the chunk prefixes it was eleven: 8 rows of 512 Ki slots 52 us, 25 now.
 int32_t select_run(const SelectPlan& p, const float* vals, int64_t stride, int rows, int n_kv_heads,
                    const SelRows& sr, hipStream_t st) {
-  {
-    const int64_t n = (int64_t)rows * 3 * kBins;
-    sel_init<<<(unsigned)((n + 255) / 256), 256, 0, st>>>(p.hist, p.state, rows, n_kv_heads, sr);
-  }
   dim3 g((unsigned)p.nchunks, (unsigned)rows);
-  sel_count<true><<<g, 256, 0, st>>>(vals, stride, p.chunk, n_kv_heads, sr, p.state, p.ccount);
-  sel_try_zero<<<rows, 256, 0, st>>>(p.ccount, p.state, p.nchunks, n_kv_heads, sr);
-  sel_hist<0><<<g, 256, 0, st>>>(vals, stride, p.chunk, n_kv_heads, sr, p.hist, p.state);
-  sel_scan<0><<<rows, 256, 0, st>>>(p.hist, p.state, n_kv_heads, sr);
-  sel_hist<1><<<g, 256, 0, st>>>(vals, stride, p.chunk, n_kv_heads, sr, p.hist, p.state);
-  sel_scan<1><<<rows, 256, 0, st>>>(p.hist, p.state, n_kv_heads, sr);
-  sel_hist<2><<<g, 256, 0, st>>>(vals, stride, p.chunk, n_kv_heads, sr, p.hist, p.state);
-  sel_scan<2><<<rows, 256, 0, st>>>(p.hist, p.state, n_kv_heads, sr);
-  sel_count<false><<<g, 256, 0, st>>>(vals, stride, p.chunk, n_kv_heads, sr, p.state, p.ccount);
-  sel_offsets<<<rows, 256, 0, st>>>(p.ccount, p.coff, p.nchunks, n_kv_heads, sr);
+  sel_count<true><<<g, 256, 0, st>>>(vals, stride, p.chunk, n_kv_heads, sr, p.state, p.hist, p.ccount);
+  sel_hist<0><<<g, 256, 0, st>>>(vals, stride, p.chunk, n_kv_heads, sr, p.hist, p.state, p.ccount);
+  sel_hist<1><<<g, 256, 0, st>>>(vals, stride, p.chunk, n_kv_heads, sr, p.hist, p.state, p.ccount);
+  sel_hist<2><<<g, 256, 0, st>>>(vals, stride, p.chunk, n_kv_heads, sr, p.hist, p.state, p.ccount);
+  sel_count<false><<<g, 256, 0, st>>>(vals, stride, p.chunk, n_kv_heads, sr, p.state, p.hist, p.ccount);
   HCA_HIP(hipGetLastError());
   return HCA_OK;
 }

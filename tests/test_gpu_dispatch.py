@@ -188,3 +188,56 @@ def test_bulk_assignment_equals_the_exhaustive_chain(B, g, c, G, T, rows):
     want = torch.arange(100, 100 + T, dtype=torch.int32, device="cuda").expand(rows, T)
     assert torch.equal(pos[0, :, 4:4 + T], want) and (pos[0, :, :4] == -7).all() and (pos[0, :, 4 + T:] == -7).all()
     assert (acc[0, :, 4:4 + T] == 0).all() and (acc[0, :, :4] == 7).all() and (acc[0, :, 4 + T:] == 7).all()
+
+
+@pytest.mark.parametrize("bits,gs", [(4, 32), (2, 64)])
+@pytest.mark.parametrize("n,M,protect,kind,spare", [
+    (4096, 4095, 0, "zeros", False), (4097, 2049, 1, "dense", True), (9000, 1, 0, "dense", False),
+    (9001, 4500, 4500, "dense", True), (20483, 20000, 64, "ties", False), (20483, 8191, 16, "ties", True),
+    (8192, 63, 5, "mixed", True), (12289, 12288, 3, "mixed", False)])
+def test_evict_at_chunk_edges(B, bits, gs, n, M, protect, kind, spare):
+    """hca_evict: keep-list, moved scores, value rows and codes on both sides of the 4096-slot chunk and 64-slot wave edges,
+    with the threshold at 0 (one counting pass), above it, below it and inside long ties (radix passes)."""
+    w = S.Workload("ev", 83, 2, 4, 2, n, bits, gs, 8)
+    d = S.make_layer(w, want_values=False)
+    st = _layer(w, 8, m_max=M)
+    st.quantize(d["keys"].cuda())
+    codes0, scale0, zero0 = st.export()
+    rng = np.random.default_rng(n + M)
+    acc = np.zeros((4, n), np.float32)
+    if kind == "zeros":
+        acc[:, ::50] = rng.random((4, len(range(0, n, 50))))
+    elif kind == "dense":
+        acc[:] = rng.random((4, n)) + 0.5
+    elif kind == "ties":
+        acc[:] = rng.integers(1, 4, (4, n))
+    else:                                                    # negative values and both zeros: the threshold lies below 0
+        acc[:] = rng.standard_normal((4, n)) - 2
+        acc[:, ::7], acc[:, 1::7] = 0.0, -0.0
+    lens = [n, max(M, n - 100)]                              # the second sequence may have nothing to evict
+    st.acc.copy_(torch.from_numpy(acc).view(2, 2, n))
+    st.pos.copy_(torch.randint(0, 1 << 20, st.pos.shape, dtype=torch.int32, device="cuda"))
+    pos0 = st.pos.cpu().numpy().reshape(4, n)
+    st.n = list(lens)
+    kept = torch.full((2, 2, M), -5, dtype=torch.int32, device="cuda")
+    dst = (torch.zeros_like(st.kcache), torch.zeros_like(st.acc), torch.zeros_like(st.pos)) if spare else None
+    st.evict(M, protect, kept, spare=dst)
+    codes, scale, zero = st.export()
+    torch.cuda.synchronize()
+    kept = kept.cpu().numpy().reshape(4, M)
+    flat = lambda x: x.cpu().numpy().reshape(4, n, -1)  # noqa: E731
+    for r in range(4):
+        ln = lens[r // 2]
+        if ln <= M:
+            assert np.all(kept[r] == -5)
+            ref = np.arange(ln)
+        else:
+            ns = ln - protect
+            key = _order_key(acc[r, :ns]).astype(np.int64)
+            ref = np.concatenate([np.sort(np.argsort(-key, kind="stable")[:M - protect]), np.arange(ns, ln)])
+            assert np.array_equal(kept[r], ref), f"row {r}"
+        m = len(ref)
+        assert np.array_equal(flat(st.acc)[r, :m, 0], acc[r, ref]) and np.array_equal(flat(st.pos)[r, :m, 0], pos0[r, ref])
+        assert np.array_equal(flat(codes)[r, :m], flat(codes0)[r, ref])
+        assert np.array_equal(flat(scale.view(torch.int16))[r, :m], flat(scale0.view(torch.int16))[r, ref])
+        assert np.array_equal(flat(zero.view(torch.int16))[r, :m], flat(zero0.view(torch.int16))[r, ref])
