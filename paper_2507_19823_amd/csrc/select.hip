@@ -485,17 +485,14 @@ __global__ __launch_bounds__(256) void tk_findbin(int n_kv_heads, SelRows sr, To
 // in bin b* or above into its own list (room for the whole chunk, so it cannot overflow), and
 // counts the ones strictly above the bin.  Lists are per chunk so that no two workgroups ever
 // contend for an append position.
-__global__ __launch_bounds__(256) void tk_collect(const float* __restrict__ vals, int64_t stride, int64_t chunk,
-                                                  int n_kv_heads, SelRows sr, TopkWs t) {
+// bin_of: a key's bin, increasing with the key.
+template <typename F>
+__device__ __forceinline__ void collect_chunk(const float* __restrict__ vals, int64_t stride, int64_t chunk, int64_t nsel,
+                                              int row, const TopkWs& t, const uint32_t bin, F&& bin_of) {
   __shared__ uint32_t wsum[4];
   __shared__ uint32_t pc[64], po[64];
   __shared__ uint32_t s_total;
-  const int row = blockIdx.y;
-  const int64_t want = sr.want[row / n_kv_heads];
-  if (want <= 0) return;
-  const int64_t nsel = sr.nsel[row / n_kv_heads];
   const int64_t c0 = (int64_t)blockIdx.x * chunk;
-  const uint32_t bin = t.state[4 * row + 2];
   uint32_t* ncand = t.ncand + (int64_t)row * kMaxChunks + blockIdx.x;
   if (c0 >= nsel) {
     if (threadIdx.x == 0) { t.above[(int64_t)row * 1024 + blockIdx.x] = 0; *ncand = 0; }
@@ -515,7 +512,7 @@ __global__ __launch_bounds__(256) void tk_collect(const float* __restrict__ vals
     uint64_t mask[16];
 #pragma unroll
     for (int x = 0; x < 16; ++x) {
-      const uint32_t b = key[x] >> 20;
+      const uint32_t b = bin_of(key[x]);
       cnt += valid[x] && b > bin;
       mask[x] = __ballot(valid[x] && b >= bin);
       if (lane == 0) pc[x * 4 + w] = (uint32_t)__popcll(mask[x]);
@@ -551,6 +548,14 @@ __global__ __launch_bounds__(256) void tk_collect(const float* __restrict__ vals
     t.above[(int64_t)row * 1024 + blockIdx.x] = wsum[0] + wsum[1] + wsum[2] + wsum[3];
     *ncand = base;
   }
+}
+
+__global__ __launch_bounds__(256) void tk_collect(const float* __restrict__ vals, int64_t stride, int64_t chunk,
+                                                  int n_kv_heads, SelRows sr, TopkWs t) {
+  const int row = blockIdx.y;
+  if (sr.want[row / n_kv_heads] <= 0) return;
+  collect_chunk(vals, stride, chunk, sr.nsel[row / n_kv_heads], row, t, t.state[4 * row + 2],
+                [](uint32_t key) { return key >> 20; });
 }
 
 // exclusive prefix sum of one value per thread over a 1024-thread workgroup
@@ -1787,21 +1792,34 @@ __device__ __forceinline__ uint64_t tp_weight(float u) {
   return sh >= 64 ? 0 : mant >> sh;
 }
 
-__global__ void tp_init(TopkWs t, int rows) {
-  const int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-  if (i < (int64_t)rows * kBins12) { t.pcount[i] = 0; t.pmass[i] = 0; }
-  if (i < rows * 4) { t.prow[i] = 0; t.pstate[i] = 0; }
-}
+// Bins of the cumulative walk: 32 per factor of two in weight, from the row maximum down (kTpBins - 1) to 2^-64 of it and
+// below (0).  A bin that holds a typical threshold has tens to hundreds of slots in it, so little is left to resolve
+// inside; bins of the key's leading 12 bits, an eighth of an octave of the score, held thousands for a flat row: 8 rows
+// of 500 Ki slots, 8192 to select, 130 us per call in seven launches, 54 now in five (88 of it the resolve stage, 17 now).
+constexpr int kTpBins = 2048;
+struct TpBin {
+  float m, sm;      // the row maximum's logit, the softmax scale
+  __device__ __forceinline__ uint32_t operator()(uint32_t key) const {
+    // increasing with the key: a product with a positive factor, a difference, a product, a truncation
+    const float down = (m - key_to_float(key) * sm) * (1.44269504f * kTpBins / 64.0f);
+    const uint32_t b = (uint32_t)(down < (float)(kTpBins - 1) ? down : (float)(kTpBins - 1));
+    return (uint32_t)(kTpBins - 1) - b;
+  }
+};
 
-// Row maximum of the scores, as an order key.
+// Row maximum of every group of chunks, as an order key (tmax, in the room of the chunk counts), and clean counters for the
+// histogram pass.
 __global__ __launch_bounds__(256) void tp_rowmax(const float* __restrict__ vals, int64_t stride, int64_t chunk,
                                                  int n_kv_heads, SelRows sr, TopkWs t) {
   __shared__ uint32_t wmax[4];
   const int row = blockIdx.y;
   if (sr.want[row / n_kv_heads] <= 0) return;
+  for (int i = blockIdx.x * 256 + threadIdx.x; i < kTpBins; i += gridDim.x * 256) {
+    t.pcount[(int64_t)row * kBins12 + i] = 0;
+    t.pmass[(int64_t)row * kBins12 + i] = 0;
+  }
   const int64_t nsel = sr.nsel[row / n_kv_heads];
   const int64_t c0 = (int64_t)blockIdx.x * chunk;
-  if (c0 >= nsel) return;
   int64_t c1 = c0 + chunk;
   if (c1 > nsel) c1 = nsel;
   const float* v = vals + (int64_t)row * stride;
@@ -1823,15 +1841,15 @@ __global__ __launch_bounds__(256) void tp_rowmax(const float* __restrict__ vals,
   __syncthreads();
   if (threadIdx.x == 0) {
     for (int x = 1; x < 4; ++x) if (wmax[x] > best) best = wmax[x];
-    atomicMax(&t.prow[4 * row], best);
+    t.above[(int64_t)row * 1024 + blockIdx.x] = best;
   }
 }
 
-// 12-bit histogram of slot counts and integer weights.
+// Histogram of slot counts and integer weights.
 __global__ __launch_bounds__(256) void tp_hist(const float* __restrict__ vals, int64_t stride, int64_t chunk,
                                                int n_kv_heads, SelRows sr, float sm_scale, TopkWs t) {
-  __shared__ uint32_t lc[kBins12];
-  __shared__ unsigned long long lm[kBins12];
+  __shared__ uint32_t lc[kTpBins], wmax[4];
+  __shared__ unsigned long long lm[kTpBins];
   const int row = blockIdx.y;
   if (sr.want[row / n_kv_heads] <= 0) return;
   const int64_t nsel = sr.nsel[row / n_kv_heads];
@@ -1839,9 +1857,23 @@ __global__ __launch_bounds__(256) void tp_hist(const float* __restrict__ vals, i
   if (c0 >= nsel) return;
   int64_t c1 = c0 + chunk;
   if (c1 > nsel) c1 = nsel;
-  for (int i = threadIdx.x; i < kBins12; i += 256) { lc[i] = 0; lm[i] = 0; }
+  for (int i = threadIdx.x; i < kTpBins; i += 256) { lc[i] = 0; lm[i] = 0; }
+  uint32_t kmax = 0;
+  for (int c = threadIdx.x; c < (int)gridDim.x; c += 256) {
+    const uint32_t x = t.above[(int64_t)row * 1024 + c];
+    kmax = x > kmax ? x : kmax;
+  }
+#pragma unroll
+  for (int o = 32; o >= 1; o >>= 1) {
+    const uint32_t other = __shfl_xor(kmax, o);
+    if (other > kmax) kmax = other;
+  }
+  if ((threadIdx.x & 63) == 0) wmax[threadIdx.x >> 6] = kmax;
   __syncthreads();
-  const float m = key_to_float(t.prow[4 * row]) * sm_scale;
+  for (int x = 0; x < 4; ++x) if (wmax[x] > kmax) kmax = wmax[x];
+  if (blockIdx.x == 0 && threadIdx.x == 0) t.prow[4 * row] = kmax;
+  const float m = key_to_float(kmax) * sm_scale;
+  const TpBin bin_of{m, sm_scale};
   const float* v = vals + (int64_t)row * stride;
   for (int64_t s0 = c0; s0 < c1; s0 += 4096) {
     uint32_t key[16];
@@ -1851,12 +1883,14 @@ __global__ __launch_bounds__(256) void tp_hist(const float* __restrict__ vals, i
     for (int x = 0; x < 16; ++x)
       if (valid[x]) {
         const uint64_t w = tp_weight(key_to_float(key[x]) * sm_scale - m);
-        atomicAdd(&lc[key[x] >> 20], 1u);
-        if (w) atomicAdd(&lm[key[x] >> 20], (unsigned long long)w);
+        const uint32_t b = bin_of(key[x]);
+        // bin 0 weighs nothing and may hold nearly the whole row: it is not counted (its slots are the row's others)
+        if (b != 0) atomicAdd(&lc[b], 1u);
+        if (w) atomicAdd(&lm[b], (unsigned long long)w);
       }
   }
   __syncthreads();
-  for (int i = threadIdx.x; i < kBins12; i += 256) {
+  for (int i = threadIdx.x; i < kTpBins; i += 256) {
     const uint32_t c = lc[i];
     if (c) {
       atomicAdd(&t.pcount[(int64_t)row * kBins12 + i], c);
@@ -1884,22 +1918,26 @@ __device__ __forceinline__ uint64_t block_scan_excl_256_u64(uint64_t v, uint64_t
   return base + inc - v;
 }
 
-// One workgroup per row: Z, Theta, and the first bin (from the top) in which the running weight reaches
-// Theta or the running count reaches k_max.
-__global__ __launch_bounds__(256) void tp_findbin(int n_kv_heads, SelRows sr, uint64_t tau_fix, bool tau_one,
+// Z, Theta, and the first bin (from the top) in which the running weight reaches Theta or the running count reaches
+// k_max - found by every workgroup from the finished histogram, 24 KB from L2, instead of in a launch of its own - and
+// then the ordered lists of the slots in or above that bin.
+__global__ __launch_bounds__(256) void tp_collect(const float* __restrict__ vals, int64_t stride, int64_t chunk,
+                                                  int n_kv_heads, SelRows sr, float sm_scale, uint64_t tau_fix, bool tau_one,
                                                   uint32_t k_max, TopkWs t, uint64_t* __restrict__ mass_out) {
   __shared__ uint64_t wsum64[4];
-  __shared__ uint32_t wsum[4];
-  const int row = blockIdx.x;
+  __shared__ uint32_t wsum[4], s_bin;
+  const int row = blockIdx.y;
+  const bool writer = blockIdx.x == 0;
   if (sr.want[row / n_kv_heads] <= 0) {
-    if (mass_out != nullptr && threadIdx.x < 2) mass_out[2 * row + threadIdx.x] = 0;
+    if (mass_out != nullptr && writer && threadIdx.x < 2) mass_out[2 * row + threadIdx.x] = 0;
     return;
   }
-  uint32_t hc[16], csum = 0;
-  uint64_t hm[16], msum = 0;
+  constexpr int BPT = kTpBins / 256;
+  uint32_t hc[BPT], csum = 0;
+  uint64_t hm[BPT], msum = 0;
 #pragma unroll
-  for (int i = 0; i < 16; ++i) {
-    const int b = kBins12 - 1 - (16 * threadIdx.x + i);
+  for (int i = 0; i < BPT; ++i) {
+    const int b = kTpBins - 1 - (BPT * threadIdx.x + i);
     hc[i] = t.pcount[(int64_t)row * kBins12 + b];
     hm[i] = t.pmass[(int64_t)row * kBins12 + b];
     csum += hc[i];
@@ -1910,24 +1948,32 @@ __global__ __launch_bounds__(256) void tp_findbin(int n_kv_heads, SelRows sr, ui
   uint32_t run_c = block_scan_excl_256(csum, wsum);
   uint64_t theta = tau_one ? Z : __umul64hi(Z, tau_fix);
   if (theta < 1) theta = 1;
+  if (threadIdx.x == 255) hc[BPT - 1] = (uint32_t)sr.nsel[row / n_kv_heads] - (run_c + csum);     // bin 0
 #pragma unroll
-  for (int i = 0; i < 16; ++i) {
+  for (int i = 0; i < BPT; ++i) {
     const bool before = run_m < theta && run_c < k_max;
     const bool after = run_m + hm[i] >= theta || run_c + hc[i] >= k_max;
     if (before && after && hc[i] > 0) {
-      t.state[4 * row + 2] = kBins12 - 1 - (16 * threadIdx.x + i);   // b*
-      t.pstate[4 * row] = theta - run_m;                              // weight still to reach inside the bin
-      t.prow[4 * row + 1] = k_max - run_c;                            // slots still allowed
-      t.prow[4 * row + 3] = run_c;                                    // slots above the bin
+      s_bin = (uint32_t)(kTpBins - 1 - (BPT * threadIdx.x + i));       // b*
+      if (writer) {
+        t.state[4 * row + 2] = (uint32_t)(kTpBins - 1 - (BPT * threadIdx.x + i));
+        t.pstate[4 * row] = theta - run_m;                              // weight still to reach inside the bin
+        t.prow[4 * row + 1] = k_max - run_c;                            // slots still allowed
+      }
     }
     run_m += hm[i];
     run_c += hc[i];
   }
-  if (threadIdx.x == 0) {
-    t.pstate[4 * row + 1] = theta;
-    t.pstate[4 * row + 2] = Z;
-    if (mass_out != nullptr) { mass_out[2 * row] = theta; mass_out[2 * row + 1] = Z; }
-  }
+  if (writer && threadIdx.x == 0 && mass_out != nullptr) { mass_out[2 * row] = theta; mass_out[2 * row + 1] = Z; }
+  __syncthreads();
+  const TpBin bin_of{key_to_float(t.prow[4 * row]) * sm_scale, sm_scale};
+  collect_chunk(vals, stride, chunk, sr.nsel[row / n_kv_heads], row, t, s_bin, bin_of);
+}
+
+// no resident slot anywhere: only the per-row (Theta, Z) report has to be cleared
+__global__ void tp_no_mass(uint64_t* __restrict__ mass_out, int n) {
+  const int i = blockIdx.x * blockDim.x + threadIdx.x;
+  if (i < n) mass_out[i] = 0;
 }
 
 // exclusive prefix sums over a 1024-thread workgroup (one value per thread)
@@ -1947,14 +1993,14 @@ __device__ __forceinline__ uint64_t block_scan_excl_1024_u64(uint64_t v, uint64_
   return base + inc - v;
 }
 
-// One workgroup per row: finishes the walk inside bin b* (two 10-bit digits, then the group of equal
-// keys, whose members all weigh the same) and builds the chunk offsets for the ordered emit.
+// One workgroup per row: finishes the walk inside bin b* (digits of the distance from the bin's smallest key, then the
+// group of equal keys, whose members all weigh the same) and builds the chunk offsets for the ordered emit.
 __global__ __launch_bounds__(1024) void tp_resolve(int64_t chunk, int nchunks, int n_kv_heads, SelRows sr, float sm_scale,
                                                    TopkWs t) {
-  __shared__ uint32_t h[1024], e[1024], cnt[1024], wsum[16];
+  __shared__ uint32_t h[1024], e[1024], cnt[1024], wsum[16], wmin[16], wmax[16];
   __shared__ unsigned long long hm[1024];
   __shared__ uint64_t wsum64[16];
-  __shared__ uint32_t s_prefix, s_krem, s_n;
+  __shared__ uint32_t s_digit, s_krem, s_n, s_eq;
   __shared__ uint64_t s_mrem;
   __shared__ uint2 lc[kResolveLds];
   const int row = blockIdx.x;
@@ -1963,32 +2009,60 @@ __global__ __launch_bounds__(1024) void tp_resolve(int64_t chunk, int nchunks, i
   const uint2* cand = t.cand + (int64_t)row * t.row_entries;
   const int tid = threadIdx.x, lane = tid & 63, wv = tid >> 6;
   const float m = key_to_float(t.prow[4 * row]) * sm_scale;
-  uint32_t prefix = bin << 20, krem = t.prow[4 * row + 1];
+  const TpBin bin_of{m, sm_scale};
+  uint32_t krem = t.prow[4 * row + 1];
   uint64_t mrem = t.pstate[4 * row];
   cnt[tid] = tid < nchunks ? t.ncand[(int64_t)row * kMaxChunks + tid] : 0;
   if (tid == 0) s_n = 0;
   __syncthreads();
+  // f(key, slot, hit) over every list entry of the row, hit = the entry exists and lies in bin b*; f is called by all lanes
+  // of a wave together.  Each wave takes 8 chunks per step and fetches the first 128 entries of all of them in one batch
+  // of loads, so a step costs one memory round trip; longer lists follow, 8 loads in flight.
   auto sweep = [&](auto&& f) {
-    for (int c0 = 0; c0 < nchunks; c0 += 256) {
-#pragma unroll 1
+    for (int c0 = 0; c0 < nchunks; c0 += 128) {
+      uint2 ent[16];
+      bool has[16];
+#pragma unroll
       for (int u = 0; u < 16; ++u) {
-        const int c = c0 + wv * 16 + u;
-        const uint32_t mu = c < nchunks ? cnt[c] : 0;
-        for (uint32_t i0 = lane; i0 < mu + lane; i0 += 512) {
+        const int c = c0 + (u >> 1) * 16 + wv;
+        const uint32_t i = (uint32_t)(64 * (u & 1) + lane);
+        has[u] = c < nchunks && i < cnt[c < nchunks ? c : 0];
+        ent[u] = uint2{0, 0};
+        if (has[u]) ent[u] = cand[(int64_t)c * chunk + i];
+      }
+#pragma unroll
+      for (int u = 0; u < 16; ++u) f(ent[u].x, ent[u].y, has[u] && bin_of(ent[u].x) == bin);
+#pragma unroll 1
+      for (int u = 0; u < 8; ++u) {
+        const int c = c0 + u * 16 + wv;
+        const uint32_t mc = c < nchunks ? cnt[c] : 0;
+        for (uint32_t i0 = 128 + lane; i0 < mc + lane; i0 += 512) {
           uint2 x[8];
 #pragma unroll
           for (int v = 0; v < 8; ++v) {
             x[v] = uint2{0, 0};
-            if (i0 + 64 * v < mu) x[v] = cand[(int64_t)c * chunk + i0 + 64 * v];
+            if (i0 + 64 * v < mc) x[v] = cand[(int64_t)c * chunk + i0 + 64 * v];
           }
 #pragma unroll
-          for (int v = 0; v < 8; ++v) f(x[v].x, x[v].y, i0 + 64 * v < mu && (x[v].x >> 20) == bin);
+          for (int v = 0; v < 8; ++v) f(x[v].x, x[v].y, i0 + 64 * v < mc && bin_of(x[v].x) == bin);
         }
       }
     }
   };
-  sweep([&](uint32_t key, uint32_t slot, bool hit) { lds_append(&s_n, lc, (uint32_t)kResolveLds, key, slot, hit); });
+  uint32_t lo = 0xffffffffu, hi = 0;                        // smallest and largest key of the bin
+  sweep([&](uint32_t key, uint32_t slot, bool hit) {
+    if (hit) { lo = key < lo ? key : lo; hi = key > hi ? key : hi; }
+    lds_append(&s_n, lc, (uint32_t)kResolveLds, key, slot, hit);
+  });
+#pragma unroll
+  for (int o = 32; o >= 1; o >>= 1) {
+    const uint32_t a = __shfl_xor(lo, o), b = __shfl_xor(hi, o);
+    lo = a < lo ? a : lo;
+    hi = b > hi ? b : hi;
+  }
+  if (lane == 0) { wmin[wv] = lo; wmax[wv] = hi; }
   __syncthreads();
+  for (int x = 0; x < 16; ++x) { lo = wmin[x] < lo ? wmin[x] : lo; hi = wmax[x] > hi ? wmax[x] : hi; }
   const uint32_t nst = s_n;
   const bool staged = nst <= (uint32_t)kResolveLds;
   auto visit = [&](auto&& f) {
@@ -2002,16 +2076,20 @@ __global__ __launch_bounds__(1024) void tp_resolve(int64_t chunk, int nchunks, i
       sweep(f);
     }
   };
-  uint32_t cnt_eq = 0;
-  for (int pass = 0; pass < 2; ++pass) {
-    const int shift = pass == 0 ? 10 : 0;
+  // the distances from lo, 10 bits at a time from the top: pd = the digits found, left = the bits below them
+  uint32_t cnt_eq = 0, pd = 0;
+  int left = 32 - __clz((int)((hi - lo) | 1u));             // 1 .. 32
+  bool first = true;
+  while (left > 0) {                                        // uniform over the workgroup
+    const int width = left > 10 ? 10 : left, ns = left - width;
     h[tid] = 0;
     hm[tid] = 0;
     __syncthreads();
     visit([&](uint32_t key, uint32_t, bool hit) {
-      const bool in = hit && (key >> (shift + 10)) == (prefix >> (shift + 10));
+      const uint32_t d = key - lo;
+      const bool in = hit && (first || (d >> left) == pd);
       const uint64_t w = in ? tp_weight(key_to_float(key) * sm_scale - m) : 0;
-      lds_count_mass(h, hm, (key >> shift) & 1023u, key, w, in, !staged);
+      lds_count_mass(h, hm, (d >> ns) & ((1u << width) - 1u), key, w, in, !staged);
     });
     __syncthreads();
     const uint32_t mine_c = h[1023 - tid];                  // thread tid owns digit 1023 - tid
@@ -2021,18 +2099,21 @@ __global__ __launch_bounds__(1024) void tp_resolve(int64_t chunk, int nchunks, i
     const bool before = run_m < mrem && run_c < krem;
     const bool after = run_m + mine_m >= mrem || run_c + mine_c >= krem;
     if (before && after && mine_c > 0) {
-      s_prefix = prefix | ((uint32_t)(1023 - tid) << shift);
+      s_digit = (uint32_t)(1023 - tid);
+      s_eq = mine_c;
       s_mrem = mrem - run_m;
       s_krem = krem - run_c;
     }
     __syncthreads();
-    prefix = s_prefix;
+    pd = first ? s_digit : ((pd << width) | s_digit);
+    cnt_eq = s_eq;
     mrem = s_mrem;
     krem = s_krem;
-    cnt_eq = h[(prefix >> shift) & 1023u];
+    left = ns;
+    first = false;
     __syncthreads();
   }
-  const uint32_t T = prefix;
+  const uint32_t T = lo + pd;
   // the cnt_eq slots with key == T all weigh w_T: take the least r with r * w_T >= mrem, within the
   // count limit
   const uint64_t wT = tp_weight(key_to_float(T) * sm_scale - m);
@@ -2044,8 +2125,8 @@ __global__ __launch_bounds__(1024) void tp_resolve(int64_t chunk, int nchunks, i
   e[tid] = 0;
   __syncthreads();
   visit([&](uint32_t key, uint32_t slot, bool hit) {
-    lds_count(h, (uint32_t)(slot / chunk), hit && key > T, !staged);
-    lds_count(e, (uint32_t)(slot / chunk), hit && key == T, !staged);
+    lds_count(h, slot / (uint32_t)chunk, hit && key > T, !staged);
+    lds_count(e, slot / (uint32_t)chunk, hit && key == T, !staged);
   });
   __syncthreads();
   const uint32_t g = (tid < nchunks) ? t.above[(int64_t)row * 1024 + tid] + h[tid] : 0;
@@ -2077,17 +2158,13 @@ int32_t launch_topp(const Layout& L, const float* sel, const NRes& nr, int64_t n
   const bool tau_one = tau >= 1.0;
   const uint64_t tau_fix = tau_one ? 0 : (uint64_t)ldexp(tau, 64);
   if (nmax > 0) {
-    const int64_t nz = (int64_t)L.rows * kBins12;
-    tp_init<<<(unsigned)((nz + 255) / 256), 256, 0, st>>>(t, L.rows);
-    dim3 gh((unsigned)((nchunks + 3) / 4), (unsigned)L.rows);
-    tp_rowmax<<<gh, 256, 0, st>>>(sel, L.cap, 4 * chunk, L.n_kv_heads, sr, t);
-    tp_hist<<<gh, 256, 0, st>>>(sel, L.cap, 4 * chunk, L.n_kv_heads, sr, sm_scale, t);
-    tp_findbin<<<L.rows, 256, 0, st>>>(L.n_kv_heads, sr, tau_fix, tau_one, (uint32_t)k_max, t, mass_opt);
-    tk_collect<<<g, 256, 0, st>>>(sel, L.cap, chunk, L.n_kv_heads, sr, t);
+    dim3 gh((unsigned)((nchunks + 1) / 2), (unsigned)L.rows);
+    tp_rowmax<<<gh, 256, 0, st>>>(sel, L.cap, 2 * chunk, L.n_kv_heads, sr, t);
+    tp_hist<<<gh, 256, 0, st>>>(sel, L.cap, 2 * chunk, L.n_kv_heads, sr, sm_scale, t);
+    tp_collect<<<g, 256, 0, st>>>(sel, L.cap, chunk, L.n_kv_heads, sr, sm_scale, tau_fix, tau_one, (uint32_t)k_max, t, mass_opt);
     tp_resolve<<<L.rows, 1024, 0, st>>>(chunk, nchunks, L.n_kv_heads, sr, sm_scale, t);
   } else if (mass_opt != nullptr) {
-    // no resident slot anywhere: only the per-row (Theta, Z) report has to be cleared
-    tp_findbin<<<L.rows, 256, 0, st>>>(L.n_kv_heads, sr, tau_fix, tau_one, (uint32_t)k_max, t, mass_opt);
+    tp_no_mass<<<(unsigned)((2 * L.rows + 255) / 256), 256, 0, st>>>(mass_opt, 2 * L.rows);
   }
   tk_emit_lists<<<g, 256, 0, st>>>(chunk, nchunks, L.n_kv_heads, sr, t, k_max, idx, count, true);
   HCA_HIP(hipGetLastError());

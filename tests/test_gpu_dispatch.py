@@ -241,3 +241,38 @@ def test_evict_at_chunk_edges(B, bits, gs, n, M, protect, kind, spare):
         assert np.array_equal(flat(codes)[r, :m], flat(codes0)[r, ref])
         assert np.array_equal(flat(scale.view(torch.int16))[r, :m], flat(scale0.view(torch.int16))[r, ref])
         assert np.array_equal(flat(zero.view(torch.int16))[r, :m], flat(zero0.view(torch.int16))[r, ref])
+
+
+@pytest.mark.parametrize("kind", ["far", "masked", "steps", "close"])
+@pytest.mark.parametrize("n", [4096, 4097, 8193, 40961])
+def test_topp_at_the_edges_of_its_bins(B, oracle, kind, n):
+    """hca_topp bins by weight, 32 bins per factor of two down to 2^-64: rows whose slots nearly all weigh nothing, lie
+    exactly on bin edges, are masked with -inf or the type's lowest value, or share one bin."""
+    rng = np.random.default_rng(n)
+    cap, R = n + 5, 3
+    sel = np.full((R, cap), 1e30, np.float32)
+    for r in range(R):
+        if kind == "far":
+            x = np.float32(-200) - rng.random(n).astype(np.float32) * 1e4
+            x[rng.integers(0, n, 40)] = rng.standard_normal(40)
+        elif kind == "masked":
+            x = rng.standard_normal(n).astype(np.float32) * 3
+            x[rng.random(n) < 0.5] = -np.inf if r else np.finfo(np.float32).min
+        elif kind == "steps":                                # multiples of the bin width in logit, ln 2 / 32
+            x = (rng.integers(0, 2100, n) * (-np.log(2) / 32)).astype(np.float32)
+        else:
+            x = (5 + rng.random(n) * 1e-5).astype(np.float32)
+        sel[r, :n] = x
+    lens = [n, n - 1, max(1, n // 2)]
+    shape = B.make_shape(3, 1, 1, cap)
+    for tau, k_max in ((0.3, n), (0.999, n), (1.0, n), (0.9, 50)):
+        idx = torch.full((R, k_max), -9, dtype=torch.int32, device="cuda")
+        count = torch.full((R,), -9, dtype=torch.int32, device="cuda")
+        mass = torch.full((R, 2), 7, dtype=torch.int64, device="cuda")
+        ws = torch.full((B.hca_workspace_bytes(shape, k_max, 1),), 255, dtype=torch.uint8, device="cuda")
+        B.hca_topp(shape, torch.from_numpy(sel).cuda(), lens, 1.0, tau, k_max, idx, count, mass, ws)
+        torch.cuda.synchronize()
+        oidx, ocount, _, omass = oracle.topp(sel, lens, 1.0, tau, k_max)
+        assert np.array_equal(mass.cpu().numpy().view(np.uint64), omass) and np.array_equal(count.cpu().numpy(), ocount)
+        for r in range(R):
+            assert np.array_equal(idx[r, :ocount[r]].cpu().numpy(), oidx[r, :ocount[r]]), (r, tau)
