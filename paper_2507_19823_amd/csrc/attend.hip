@@ -5,6 +5,7 @@
 namespace hca {
 
 constexpr int kChunk = kAttendChunk;  // selected tokens per workgroup of the partial kernel
+constexpr int64_t kDirectHostEntries = 16384;
 
 struct AttendWs {
   uint16_t* vstage;  // [rows][k][128] fp16
@@ -115,33 +116,71 @@ __device__ __forceinline__ void partial_empty(float* pmz, float* py) {
   for (int c = threadIdx.x; c < 4 * kHeadDim; c += 256) py[c] = 0.f;
 }
 
+// The first half of the value rows a lane will need: entry 64 w + 4 x + sub of the chunk, 16 bytes (part) of each, x < 8.
+// They depend on nothing but the keep-list, so they are asked for before the logits are formed.
+struct ValueRows { uint4 v[8]; };
+template <typename V>
+__device__ __forceinline__ void value_rows(V&& value, int x0, int nvalid, ValueRows* out) {
+  const int w = threadIdx.x >> 6, sub = (threadIdx.x & 63) >> 4;
+#pragma unroll
+  for (int x = 0; x < 8; ++x) {
+    const int i = 64 * w + 4 * (x0 + x) + sub;
+    out->v[x] = value(i < nvalid ? i : nvalid - 1);
+  }
+}
+
+// What the last stage of a row with a single chunk needs: it writes the result itself and no merge follows.
+struct RowEnd {
+  float* y = nullptr;          // null: more than one chunk, the partial sums go to the workspace
+  float* acc = nullptr;
+  const float* lse = nullptr;
+  const int32_t* idx = nullptr;
+  int gqa = 0;
+  int64_t cap = 0;
+};
+
 // Steps 2 and 3 of a chunk, after its logits sit in ps.lg (and a __syncthreads()): per-head chunk
-// max / exponentials / sum, then the weighted sum of the staged value rows.
-template <bool VALUES = true>
+// max / exponentials / sum, then the weighted sum of the value rows.  value(i): 16 bytes (this lane's part) of entry i's
+// row; rows0: the first eight of them, already on their way.
+template <bool VALUES, typename V>
 __device__ __forceinline__ void partial_softmax_sum(PartialShared& ps, const AttendWs& a, int row, int i0, int nvalid,
-                                                    int32_t k, float* pmz, float* py) {
+                                                    int32_t k, float* pmz, float* py, V&& value, const ValueRows& rows0,
+                                                    const RowEnd& end) {
   auto& lg = ps.lg;
   auto& red = ps.red;
   auto& hm = ps.hm;
   auto& hz = ps.hz;
   const int lane = threadIdx.x & 63, w = threadIdx.x >> 6;
+  ValueRows rows1;
+  if constexpr (VALUES) value_rows(value, 8, nvalid, &rows1);
   // 2. per head (wave w = head w): chunk max, exponentials, chunk sum
   {
-    float m = -INFINITY;
-    for (int i = lane; i < nvalid; i += 64) m = fmaxf(m, lg[w][i]);
+    float l[4], m = -INFINITY;
+#pragma unroll
+    for (int x = 0; x < 4; ++x) {
+      l[x] = lane + 64 * x < nvalid ? lg[w][lane + 64 * x] : -INFINITY;
+      m = fmaxf(m, l[x]);
+    }
 #pragma unroll
     for (int o = 32; o >= 1; o >>= 1) m = fmaxf(m, __shfl_xor(m, o));
     float z = 0.f;
-    for (int i = lane; i < nvalid; i += 64) {
-      const float l = lg[w][i];
-      a.logit[((int64_t)row * 4 + w) * k + i0 + i] = l;
-      const float p = expf(l - m);
-      lg[w][i] = p;
-      z += p;
+#pragma unroll
+    for (int x = 0; x < 4; ++x) {
+      const int i = lane + 64 * x;
+      if (i < nvalid) {
+        if (end.y == nullptr) a.logit[((int64_t)row * 4 + w) * k + i0 + i] = l[x];
+        const float p = expf(l[x] - m);
+        lg[w][i] = p;
+        z += p;
+      }
     }
 #pragma unroll
     for (int o = 32; o >= 1; o >>= 1) z += __shfl_xor(z, o);
-    if (lane == 0) { hm[w] = m; hz[w] = z; }
+    if (lane == 0) {
+      hm[w] = m;
+      // (the only chunk of its row, weights not renormalised: the merge's normaliser)
+      hz[w] = end.lse != nullptr && w < end.gqa ? expf(end.lse[(int64_t)row * end.gqa + w] - m) : z;
+    }
   }
   __syncthreads();
   if constexpr (!VALUES) {   // weights only: the chunk's (max, sum) pairs and the stored logits are all that is needed
@@ -150,27 +189,19 @@ __device__ __forceinline__ void partial_softmax_sum(PartialShared& ps, const Att
   }
 
   // 3. weighted value sum.  Wave w owns tokens [64w, 64w+64) of the chunk; one load instruction
-  //    fetches 4 staged rows (lane>>4 picks the row, lane&15 its 16-byte part) and 8 of them are
-  //    issued before the first is used.
+  //    fetches 4 rows (lane>>4 picks the row, lane&15 its 16-byte part).
   float acc[4][8];
 #pragma unroll
   for (int h = 0; h < 4; ++h)
 #pragma unroll
     for (int c = 0; c < 8; ++c) acc[h][c] = 0.f;
   const int part = lane & 15, sub = lane >> 4;
-  const uint4* vs = reinterpret_cast<const uint4*>(a.vstage) + ((int64_t)row * k + i0) * 16 + part;
-  for (int it = 0; it < 16; it += 8) {
-    uint4 rv[8];
+  auto add = [&](const ValueRows& rows, int x0) {
 #pragma unroll
     for (int x = 0; x < 8; ++x) {
-      const int i = 64 * w + 4 * (it + x) + sub;
-      rv[x] = vs[(int64_t)(i < nvalid ? i : nvalid - 1) * 16];
-    }
-#pragma unroll
-    for (int x = 0; x < 8; ++x) {
-      const int i = 64 * w + 4 * (it + x) + sub;
+      const int i = 64 * w + 4 * (x0 + x) + sub;
       if (i < nvalid) {
-        const uint32_t wd[4] = {rv[x].x, rv[x].y, rv[x].z, rv[x].w};
+        const uint32_t wd[4] = {rows.v[x].x, rows.v[x].y, rows.v[x].z, rows.v[x].w};
         float v[8];
 #pragma unroll
         for (int c = 0; c < 4; ++c) { v[2 * c] = h2f(wd[c] & 0xffffu); v[2 * c + 1] = h2f(wd[c] >> 16); }
@@ -182,7 +213,9 @@ __device__ __forceinline__ void partial_softmax_sum(PartialShared& ps, const Att
         }
       }
     }
-  }
+  };
+  add(rows0, 0);
+  add(rows1, 8);
 #pragma unroll
   for (int h = 0; h < 4; ++h)
 #pragma unroll
@@ -201,63 +234,104 @@ __device__ __forceinline__ void partial_softmax_sum(PartialShared& ps, const Att
   __syncthreads();
   for (int c = threadIdx.x; c < 4 * kHeadDim; c += 256) {
     const int h = c >> 7, d = c & 127;
-    py[c] = (red[0][h][d] + red[1][h][d]) + (red[2][h][d] + red[3][h][d]);
+    const float sum = (red[0][h][d] + red[1][h][d]) + (red[2][h][d] + red[3][h][d]);
+    if (end.y == nullptr) py[c] = sum;
+    else if (h < end.gqa) end.y[((int64_t)row * end.gqa + h) * kHeadDim + d] = sum / hz[h];
   }
-  if (threadIdx.x < 4) { pmz[2 * threadIdx.x] = hm[threadIdx.x]; pmz[2 * threadIdx.x + 1] = hz[threadIdx.x]; }
+  if (end.y == nullptr) {
+    if (threadIdx.x < 4) { pmz[2 * threadIdx.x] = hm[threadIdx.x]; pmz[2 * threadIdx.x + 1] = hz[threadIdx.x]; }
+  } else if (end.acc != nullptr && (int)threadIdx.x < nvalid) {
+    float wsum = 0.f;
+    for (int h = 0; h < end.gqa; ++h) wsum += fmaxf(lg[h][threadIdx.x] / hz[h], 1e-30f);
+    end.acc[(int64_t)row * end.cap + end.idx[(int64_t)row * k + threadIdx.x]] += wsum;
+  }
 }
 
-template <int BITS, bool VALUES = true>
+// Where the value rows of a launch come from: the staging area that a gather filled, or the stores themselves.
+struct ValueSource {
+  const int32_t* pos = nullptr;      // null: staged
+  const uint4* v_host = nullptr;
+  const uint4* v_hbm = nullptr;
+  int64_t host_stride = 0, hbm_stride = 0, n_host_rows = 0;
+};
+
+// Bound by latency: one workgroup per 256 selected tokens, a chain of dependent loads (slots, codes; positions, values) and
+// a few microseconds of arithmetic.  So everything that can be asked for early is: the value rows before the logits, the
+// query beside the slots.  DIRECT: the value rows are read where they live, no gather and no staging area.  A row's only
+// chunk (k <= 256) finishes the row.  One head, 256 tokens: 10 us where gather, attend and merge took 20; 2048 tokens x 32
+// pairs in HBM: 23 us for attend and merge where gather, attend and merge took 34.
+template <int BITS, bool VALUES = true, bool DIRECT = false>
 __device__ __forceinline__ bool attend_partial_body(PartialShared& ps, QShared& sh, const Layout& L,
                                                     const uint8_t* __restrict__ kcache, const uint16_t* __restrict__ q,
                                                     const int32_t* __restrict__ idx, const int32_t* __restrict__ count,
                                                     int32_t k, float sm_scale, const AttendWs& a, int nsplit,
-                                                    const int split) {
+                                                    const int split, const ValueSource& vsrc = ValueSource{},
+                                                    const RowEnd& end = RowEnd{}) {
+  __shared__ int32_t s_slot[kChunk];
+  __shared__ int32_t s_vrow[DIRECT ? kChunk : 1];
+  __shared__ __align__(16) uint32_t opimg[64 * 8];
   auto& lg = ps.lg;
   const int row = blockIdx.y;
   const int cnt = count[row];
   const int i0 = split * kChunk;
-  const int lane = threadIdx.x & 63, w = threadIdx.x >> 6;
+  const int tid = threadIdx.x, lane = tid & 63, w = tid >> 6;
   const int t = lane & 15, j = lane >> 4;
   float* pmz = a.pmz + (((int64_t)row * nsplit + split) * 4) * 2;
   float* py = a.py + (((int64_t)row * nsplit + split) * 4) * kHeadDim;
   if (i0 >= cnt) {  // empty chunk: neutral partial
-    partial_empty(pmz, py);
+    if (end.y == nullptr) partial_empty(pmz, py);
+    else for (int c = tid; c < L.gqa * kHeadDim; c += 256) end.y[(int64_t)row * L.gqa * kHeadDim + c] = 0.f;
     return false;
   }
   const int nvalid = (cnt - i0 < kChunk) ? cnt - i0 : kChunk;
-  load_query(q, row, L.gqa, L.group, &sh);
-  QOperand<BITS> op;
-  build_operand<BITS>(&sh, &op);
+  const int32_t my_slot = idx[(int64_t)row * k + i0 + (tid < nvalid ? tid : nvalid - 1)];
+  const uint4* vs = reinterpret_cast<const uint4*>(a.vstage) + ((int64_t)row * k + i0) * 16 + (lane & 15);
+  auto value = [&](int i) {
+    if constexpr (!DIRECT) {
+      return vs[(int64_t)i * 16];
+    } else {
+      const int64_t vr = s_vrow[i];
+      return (vr < vsrc.n_host_rows ? vsrc.v_host + ((int64_t)row * vsrc.host_stride + vr) * 16
+                                    : vsrc.v_hbm + ((int64_t)row * vsrc.hbm_stride + (vr - vsrc.n_host_rows)) * 16)[lane & 15];
+    }
+  };
+  ValueRows rows0;
+  if constexpr (VALUES && !DIRECT) value_rows(value, 0, nvalid, &rows0);
+  s_slot[tid] = my_slot;
+  load_query(q, row, L.gqa, L.group, &sh);                  // (ends with a barrier)
   const uint8_t* crow = kcache + (int64_t)row * L.codes_row_bytes();
   const uint8_t* mrow = kcache + L.meta_off + (int64_t)row * L.meta_row_bytes();
-  const int32_t* ridx = idx + (int64_t)row * k;
 
   // 1. logits of the chunk: wave w scores tiles w, w+4, w+8, w+12 (16 selected tokens each).
-  //    All slot numbers are fetched first, then all code / meta pieces, so that the wave has its
+  //    All code / meta pieces are asked for first, so that the wave has its
   //    whole share of the random reads in flight at once.
   {
-    int64_t slot[4];
-#pragma unroll
-    for (int x = 0; x < 4; ++x) {
-      const int i = (w + 4 * x) * 16 + t;
-      slot[x] = ridx[i0 + (i < nvalid ? i : nvalid - 1)];
-    }
     uint4 wv[4], mv[4];
 #pragma unroll
     for (int x = 0; x < 4; ++x) {
+      const int64_t slot = s_slot[(w + 4 * x) * 16 + t];
       if constexpr (BITS == 4) {
-        const int64_t blk = slot[x] >> 4;
-        const int tl = (int)(slot[x] & 15);
+        const int64_t blk = slot >> 4;
+        const int tl = (int)(slot & 15);
         wv[x] = *reinterpret_cast<const uint4*>(crow + blk * kBlockBytes + (tl + 16 * j) * 16);
         mv[x] = *reinterpret_cast<const uint4*>(mrow + blk * kMetaBytes + tl * 16);
       } else {
-        const int64_t blk = slot[x] >> 5;
-        const int u = (int)((slot[x] >> 4) & 1), tl = (int)(slot[x] & 15);
+        const int64_t blk = slot >> 5;
+        const int u = (int)((slot >> 4) & 1), tl = (int)(slot & 15);
         const uint2 c = *reinterpret_cast<const uint2*>(crow + blk * kBlockBytes + (tl + 16 * j) * 16 + 8 * u);
         const uint2 m = *reinterpret_cast<const uint2*>(mrow + blk * kMetaBytes + (16 * u + tl) * 8);
         wv[x] = uint4{c.x, c.y, 0, 0};
         mv[x] = uint4{m.x, m.y, 0, 0};
       }
+    }
+    int32_t my_vrow = 0;
+    if constexpr (DIRECT) my_vrow = vsrc.pos[(int64_t)row * L.cap + my_slot];
+    QOperand<BITS> op;
+    build_operand_shared<BITS>(&sh, opimg, &op);
+    if constexpr (DIRECT) {
+      s_vrow[tid] = my_vrow;
+      __syncthreads();
+      if constexpr (VALUES) value_rows(value, 0, nvalid, &rows0);
     }
 #pragma unroll
     for (int x = 0; x < 4; ++x) {
@@ -270,19 +344,20 @@ __device__ __forceinline__ bool attend_partial_body(PartialShared& ps, QShared& 
   }
   __syncthreads();
 
-  partial_softmax_sum<VALUES>(ps, a, row, i0, nvalid, k, pmz, py);
+  partial_softmax_sum<VALUES>(ps, a, row, i0, nvalid, k, pmz, py, value, rows0, end);
   return true;
 }
 
 // split0: the first chunk of the launch (chunks below it belong to the host share)
-template <int BITS, bool VALUES = true>
+template <int BITS, bool VALUES = true, bool DIRECT = false>
 __global__ __launch_bounds__(256) void attend_partial(Layout L, const uint8_t* __restrict__ kcache,
                                                       const uint16_t* __restrict__ q, const int32_t* __restrict__ idx,
                                                       const int32_t* __restrict__ count, int32_t k, float sm_scale,
-                                                      AttendWs a, int nsplit, int split0) {
+                                                      AttendWs a, int nsplit, int split0, ValueSource vsrc, RowEnd end) {
   __shared__ QShared sh;
   __shared__ PartialShared ps;
-  attend_partial_body<BITS, VALUES>(ps, sh, L, kcache, q, idx, count, k, sm_scale, a, nsplit, (int)blockIdx.x + split0);
+  attend_partial_body<BITS, VALUES, DIRECT>(ps, sh, L, kcache, q, idx, count, k, sm_scale, a, nsplit,
+                                            (int)blockIdx.x + split0, vsrc, end);
 }
 
 // The chunks of the host share: logits, chunk (max, sum) and stored logits as for any chunk (the merge and the
@@ -369,7 +444,7 @@ template <int G, bool WIDE>
 __global__ __launch_bounds__(256) void vq_attend_partial(int g, int c, int64_t cap, const uint8_t* __restrict__ pcache,
                                                          const float* __restrict__ lut, const int32_t* __restrict__ idx,
                                                          const int32_t* __restrict__ count, int32_t k, float sm_scale,
-                                                         AttendWs a, int nsplit) {
+                                                         AttendWs a, int nsplit, RowEnd end) {
   __shared__ PartialShared ps;
   const int row = blockIdx.y, split = blockIdx.x;
   const int cnt = count[row];
@@ -377,10 +452,15 @@ __global__ __launch_bounds__(256) void vq_attend_partial(int g, int c, int64_t c
   float* pmz = a.pmz + (((int64_t)row * nsplit + split) * 4) * 2;
   float* py = a.py + (((int64_t)row * nsplit + split) * 4) * kHeadDim;
   if (i0 >= cnt) {
-    partial_empty(pmz, py);
+    if (end.y == nullptr) partial_empty(pmz, py);
+    else for (int c = threadIdx.x; c < G * kHeadDim; c += 256) end.y[(int64_t)row * G * kHeadDim + c] = 0.f;
     return;
   }
   const int nvalid = (cnt - i0 < kChunk) ? cnt - i0 : kChunk;
+  const uint4* vs = reinterpret_cast<const uint4*>(a.vstage) + ((int64_t)row * k + i0) * 16 + (threadIdx.x & 15);
+  auto value = [&](int i) { return vs[(int64_t)i * 16]; };
+  ValueRows rows0;
+  value_rows(value, 0, nvalid, &rows0);
   {
     const int i = threadIdx.x;
     const int64_t slot = idx[(int64_t)row * k + i0 + (i < nvalid ? i : nvalid - 1)];
@@ -423,7 +503,39 @@ __global__ __launch_bounds__(256) void vq_attend_partial(int g, int c, int64_t c
     for (int h = 0; h < 4; ++h) ps.lg[h][i] = h < G ? z[h < G ? h : 0] * sm_scale : 0.f;
   }
   __syncthreads();
-  partial_softmax_sum(ps, a, row, i0, nvalid, k, pmz, py);
+  partial_softmax_sum<true>(ps, a, row, i0, nvalid, k, pmz, py, value, rows0, end);
+}
+
+// The row's maximum (fm) and normaliser (fz) per head from its chunks' (max, sum) pairs, and every chunk's factor
+// exp(chunk max - row max); one thread per (chunk, head), 256 of them, nsplit <= 64.  The sum runs over the chunks in
+// ascending order of a tree, 16 chunks per wave.  With lse the normaliser is exp(lse - row max).  Ends with a barrier.
+__device__ __forceinline__ void merge_chunks(const float* __restrict__ pmz, int nsplit, const float* __restrict__ lse, int gqa,
+                                             float (&fm)[4], float (&fz)[4], float (&wgt)[4][64]) {
+  __shared__ float wm[4][4], wz[4][4];
+  const int h = threadIdx.x & 3, sp = threadIdx.x >> 2, w = threadIdx.x >> 6;
+  float2 v{-INFINITY, 0.f};
+  if (sp < nsplit) v = reinterpret_cast<const float2*>(pmz)[threadIdx.x];   // index = split*4 + head
+  float m = v.x;
+#pragma unroll
+  for (int o = 4; o <= 32; o <<= 1) m = fmaxf(m, __shfl_xor(m, o));
+  if ((threadIdx.x & 63) < 4) wm[w][h] = m;
+  __syncthreads();
+  m = fmaxf(fmaxf(wm[0][h], wm[1][h]), fmaxf(wm[2][h], wm[3][h]));
+  const float e = v.x == -INFINITY ? 0.f : expf(v.x - m);
+  wgt[h][sp] = e;
+  float z = e * v.y;
+#pragma unroll
+  for (int o = 4; o <= 32; o <<= 1) z += __shfl_xor(z, o);
+  if ((threadIdx.x & 63) < 4) wz[w][h] = z;
+  __syncthreads();
+  if (threadIdx.x < 4) {
+    z = (wz[0][h] + wz[1][h]) + (wz[2][h] + wz[3][h]);
+    // global normalisation: sum_i exp(l_i - m) v_i / exp(lse - m)
+    if (lse != nullptr && h < gqa) z = expf(lse[h] - m);
+    fm[h] = m;
+    fz[h] = z;
+  }
+  __syncthreads();
 }
 
 // Workgroup 0 of a row merges the chunk partials into y; workgroups 1.. add the final softmax
@@ -436,33 +548,10 @@ __global__ __launch_bounds__(256) void attend_merge(Layout L, const int32_t* __r
                                                     const float* __restrict__ lse, HostShare hs) {
   __shared__ float fm[4], fz[4];
   __shared__ float wgt[4][64];  // nsplit <= 64
-  __shared__ float pm[64][4], pz[64][4];
   const int row = blockIdx.y;
   const int cnt = count[row];
   const float* pmz = a.pmz + ((int64_t)row * nsplit * 4) * 2;
-  // all chunk (max, sum) pairs are fetched by separate threads in one go, then reduced from LDS
-  if (threadIdx.x < 4 * nsplit) {
-    const float2 v = reinterpret_cast<const float2*>(pmz)[threadIdx.x];   // index = split*4 + head
-    pm[threadIdx.x >> 2][threadIdx.x & 3] = v.x;
-    pz[threadIdx.x >> 2][threadIdx.x & 3] = v.y;
-  }
-  __syncthreads();
-  if (threadIdx.x < 4) {
-    const int h = threadIdx.x;
-    float m = -INFINITY;
-    for (int sp = 0; sp < nsplit; ++sp) m = fmaxf(m, pm[sp][h]);
-    float z = 0.f;
-    for (int sp = 0; sp < nsplit; ++sp) {
-      const float ms = pm[sp][h];
-      const float e = (ms == -INFINITY) ? 0.f : expf(ms - m);
-      wgt[h][sp] = e;
-      z += e * pz[sp][h];
-    }
-    // global normalisation: sum_i exp(l_i - m) v_i / exp(lse - m)
-    if (lse != nullptr && h < L.gqa) z = expf(lse[(int64_t)row * L.gqa + h] - m);
-    fm[h] = m; fz[h] = z;
-  }
-  __syncthreads();
+  merge_chunks(pmz, nsplit, lse != nullptr ? lse + (int64_t)row * L.gqa : nullptr, L.gqa, fm, fz, wgt);
   if (blockIdx.x == 0) {
     if (hs.chunks > 0) {
       // the host's partial sums of this row: wait, a bounded number of polls, until the host has stored this
@@ -576,9 +665,9 @@ int32_t launch_gather(const Layout& L, const int32_t* idx, const int32_t* count,
   return HCA_OK;
 }
 
-int32_t launch_attend_gathered(const Layout& L, const void* kcache, const void* q, const int32_t* idx,
+static int32_t attend_launches(const Layout& L, const void* kcache, const void* q, const int32_t* idx,
                                const int32_t* count, int32_t k, float sm_scale, float* y, float* acc_opt,
-                               void* ws, hipStream_t st, const float* lse, const HostShare* hs) {
+                               void* ws, hipStream_t st, const float* lse, const HostShare* hs, const ValueSource& vsrc) {
   AttendWs a;
   carve(&a, ws, L, k);
   const int ns = nsplit_of(k);
@@ -586,19 +675,33 @@ int32_t launch_attend_gathered(const Layout& L, const void* kcache, const void* 
   HostShare h0;
   if (hs != nullptr) h0 = *hs;
   if (h0.chunks > ns) h0.chunks = ns;
-  if (ns - h0.chunks > 0) {            // the chunks whose value rows the gather has staged
+  // one chunk per row: no merge, the chunk's workgroup writes the row's results (a launch of 4 us less)
+  RowEnd end;
+  if (ns == 1 && h0.chunks == 0) end = RowEnd{y, acc_opt, lse, idx, L.gqa, L.cap};
+  if (ns - h0.chunks > 0) {            // the chunks whose value rows are not the host's to sum
     dim3 gp((unsigned)(ns - h0.chunks), (unsigned)L.rows);
-    if (L.bits == 4)
-      attend_partial<4><<<gp, 256, 0, st>>>(L, (const uint8_t*)kcache, (const uint16_t*)q, idx, count, k, sm_scale, a, ns,
-                                            h0.chunks);
-    else
-      attend_partial<2><<<gp, 256, 0, st>>>(L, (const uint8_t*)kcache, (const uint16_t*)q, idx, count, k, sm_scale, a, ns,
-                                            h0.chunks);
+#define HCA_PARTIAL(B, D) attend_partial<B, true, D><<<gp, 256, 0, st>>>(L, (const uint8_t*)kcache, (const uint16_t*)q, idx, count, k, sm_scale, a, ns, h0.chunks, vsrc, end)
+    if (vsrc.pos != nullptr) {
+      if (L.bits == 4) HCA_PARTIAL(4, true);
+      else HCA_PARTIAL(2, true);
+    } else {
+      if (L.bits == 4) HCA_PARTIAL(4, false);
+      else HCA_PARTIAL(2, false);
+    }
+#undef HCA_PARTIAL
   }
-  dim3 gm((unsigned)(1 + (acc_opt ? ns : 0)), (unsigned)L.rows);
-  attend_merge<<<gm, 256, 0, st>>>(L, idx, count, k, a, ns, y, acc_opt, lse, h0);
+  if (end.y == nullptr) {
+    dim3 gm((unsigned)(1 + (acc_opt ? ns : 0)), (unsigned)L.rows);
+    attend_merge<<<gm, 256, 0, st>>>(L, idx, count, k, a, ns, y, acc_opt, lse, h0);
+  }
   HCA_HIP(hipGetLastError());
   return HCA_OK;
+}
+
+int32_t launch_attend_gathered(const Layout& L, const void* kcache, const void* q, const int32_t* idx,
+                               const int32_t* count, int32_t k, float sm_scale, float* y, float* acc_opt,
+                               void* ws, hipStream_t st, const float* lse, const HostShare* hs) {
+  return attend_launches(L, kcache, q, idx, count, k, sm_scale, y, acc_opt, ws, st, lse, hs, ValueSource{});
 }
 
 int host_share_chunks(int32_t k, int want) {
@@ -636,17 +739,21 @@ int32_t launch_vq_attend_gathered(const Layout& L, int g, int c, const uint8_t* 
   const int ns = nsplit_of(k);
   if (ns > 64) return HCA_ERR_CAPACITY;
   dim3 gp((unsigned)ns, (unsigned)L.rows);
+  RowEnd end;
+  if (ns == 1) end = RowEnd{y, acc_opt, nullptr, idx, L.gqa, L.cap};
 #define HCA_VQ_PARTIAL(GQ)                                                                                               \
   do {                                                                                                                   \
-    if (vq_is_wide(L, g, c)) vq_attend_partial<GQ, true><<<gp, 256, 0, st>>>(g, c, L.cap, pcache, lut, idx, count, k, sm_scale, a, ns); \
-    else vq_attend_partial<GQ, false><<<gp, 256, 0, st>>>(g, c, L.cap, pcache, lut, idx, count, k, sm_scale, a, ns);               \
+    if (vq_is_wide(L, g, c)) vq_attend_partial<GQ, true><<<gp, 256, 0, st>>>(g, c, L.cap, pcache, lut, idx, count, k, sm_scale, a, ns, end); \
+    else vq_attend_partial<GQ, false><<<gp, 256, 0, st>>>(g, c, L.cap, pcache, lut, idx, count, k, sm_scale, a, ns, end);               \
   } while (0)
   if (L.gqa == 4) HCA_VQ_PARTIAL(4);
   else if (L.gqa == 2) HCA_VQ_PARTIAL(2);
   else HCA_VQ_PARTIAL(1);
 #undef HCA_VQ_PARTIAL
-  dim3 gm((unsigned)(1 + (acc_opt ? ns : 0)), (unsigned)L.rows);
-  attend_merge<<<gm, 256, 0, st>>>(L, idx, count, k, a, ns, y, acc_opt, nullptr, HostShare{});
+  if (end.y == nullptr) {
+    dim3 gm((unsigned)(1 + (acc_opt ? ns : 0)), (unsigned)L.rows);
+    attend_merge<<<gm, 256, 0, st>>>(L, idx, count, k, a, ns, y, acc_opt, nullptr, HostShare{});
+  }
   HCA_HIP(hipGetLastError());
   return HCA_OK;
 }
@@ -661,29 +768,11 @@ __global__ __launch_bounds__(256) void weights_finalize(Layout L, const int32_t*
                                                         const float* __restrict__ lse, uint16_t* __restrict__ w_out,
                                                         int32_t* __restrict__ vrow_out, float* __restrict__ acc) {
   __shared__ float fm[4], fz[4];
-  __shared__ float pm[64][4], pz[64][4];
+  __shared__ float wgt[4][64];
   const int row = blockIdx.y;
   const int cnt = count[row];
-  const float* pmz = a.pmz + ((int64_t)row * nsplit * 4) * 2;
-  if (threadIdx.x < 4 * nsplit) {
-    const float2 v = reinterpret_cast<const float2*>(pmz)[threadIdx.x];
-    pm[threadIdx.x >> 2][threadIdx.x & 3] = v.x;
-    pz[threadIdx.x >> 2][threadIdx.x & 3] = v.y;
-  }
-  __syncthreads();
-  if (threadIdx.x < 4) {
-    const int h = threadIdx.x;
-    float m = -INFINITY;
-    for (int sp = 0; sp < nsplit; ++sp) m = fmaxf(m, pm[sp][h]);
-    float z = 0.f;
-    for (int sp = 0; sp < nsplit; ++sp) {
-      const float ms = pm[sp][h];
-      z += (ms == -INFINITY) ? 0.f : expf(ms - m) * pz[sp][h];
-    }
-    if (lse != nullptr && h < L.gqa) z = expf(lse[(int64_t)row * L.gqa + h] - m);
-    fm[h] = m; fz[h] = z;
-  }
-  __syncthreads();
+  merge_chunks(a.pmz + ((int64_t)row * nsplit * 4) * 2, nsplit, lse != nullptr ? lse + (int64_t)row * L.gqa : nullptr, L.gqa,
+               fm, fz, wgt);
   const int i = blockIdx.x * 256 + threadIdx.x;
   if (i >= k) return;
   const bool live = i < cnt;
@@ -707,9 +796,9 @@ int32_t launch_attend_weights(const Layout& L, const void* kcache, const void* q
   if (ns > 64) return HCA_ERR_CAPACITY;
   dim3 gp((unsigned)ns, (unsigned)L.rows);
   if (L.bits == 4)
-    attend_partial<4, false><<<gp, 256, 0, st>>>(L, (const uint8_t*)kcache, (const uint16_t*)q, idx, count, k, sm_scale, a, ns, 0);
+    attend_partial<4, false><<<gp, 256, 0, st>>>(L, (const uint8_t*)kcache, (const uint16_t*)q, idx, count, k, sm_scale, a, ns, 0, ValueSource{}, RowEnd{});
   else
-    attend_partial<2, false><<<gp, 256, 0, st>>>(L, (const uint8_t*)kcache, (const uint16_t*)q, idx, count, k, sm_scale, a, ns, 0);
+    attend_partial<2, false><<<gp, 256, 0, st>>>(L, (const uint8_t*)kcache, (const uint16_t*)q, idx, count, k, sm_scale, a, ns, 0, ValueSource{}, RowEnd{});
   weights_finalize<<<gp, 256, 0, st>>>(L, idx, count, k, pos, a, ns, lse, (uint16_t*)w_out, vrow_out, acc_opt);
   HCA_HIP(hipGetLastError());
   return HCA_OK;
@@ -720,6 +809,15 @@ int32_t launch_attend(const Layout& L, const void* kcache, const void* q, const 
                       int64_t host_stride, int64_t n_host_rows, const void* v_hbm, int64_t hbm_stride,
                       float sm_scale, float* y, float* acc_opt, void* ws, hipStream_t gst, hipStream_t st) {
   if (nsplit_of(k) > 64) return HCA_ERR_CAPACITY;
+  // On one stream nothing overlaps the gather, so the attend can read the value rows where they live: without host rows
+  // always (4096 rows x 32 pairs: 27 us for the call against 42 through the staging area), with them while the launch has at
+  // most kDirectHostEntries entries: 2048 x 8 from the host 89 against 96 us, of which the link is 78.  Beyond, the gather's
+  // few persistent workgroups use the link better than a read per thread.
+  const bool no_host = v_host == nullptr || n_host_rows == 0;
+  if (gst == st && (no_host || (int64_t)k * L.rows <= kDirectHostEntries)) {
+    const ValueSource vsrc{pos, (const uint4*)v_host, (const uint4*)v_hbm, host_stride, hbm_stride, n_host_rows};
+    return attend_launches(L, kcache, q, idx, count, k, sm_scale, y, acc_opt, ws, st, nullptr, nullptr, vsrc);
+  }
   if (gst != st) {
     hipError_t e;
     hipEvent_t ev = next_event(&e);

@@ -33,17 +33,55 @@ def test_value_rows_are_the_same_wherever_they_live(B, k):
     st.n = [1200, min(1200, k + 3)]                       # the second row selects nearly everything it has
     q, values = d["q"].cuda(), d["values"]
     st.score_topk(q, k)
+    side = torch.cuda.Stream()
     out = []
     for n_host in (1200, 0, 600, 1150, 1):                # 1150: the HBM slice is short, 1: nearly nothing on the host
         vh = values[:, :, :n_host].contiguous().pin_memory() if n_host else None
         vd = values[:, :, n_host:].contiguous().cuda() if n_host < 1200 else None
+        for gather in (side, None):                       # a stream of its own: through the gather; else read where they live
+            st.y.fill_(-1.0)
+            st.acc.zero_()
+            torch.cuda.synchronize()
+            st.attend(q, vh, n_host, vd, gather_stream=gather)
+            torch.cuda.synchronize()
+            out.append((n_host, gather is None, st.y.clone(), st.acc.clone()))
+    assert torch.isfinite(out[0][2]).all() and (out[0][3] > 0).any()
+    for n_host, direct, y, acc in out[1:]:
+        assert torch.equal(y, out[0][2]) and torch.equal(acc, out[0][3]), f"n_host_rows = {n_host}, direct {direct}"
+
+
+@pytest.mark.parametrize("bits,gs", [(4, 32), (2, 64)])
+@pytest.mark.parametrize("G,n_sel", [(4, 256), (4, 1), (2, 129), (1, 255)])
+@pytest.mark.parametrize("use_lse", [False, True])
+def test_rows_of_one_chunk_need_no_merge(B, bits, gs, G, n_sel, use_lse):
+    """k <= 256: the only chunk of a row writes y and the accumulated scores itself; the same selection with a larger k goes
+    through the chunk partials and the merge.  A row with nothing selected gives zeros both ways."""
+    w = S.Workload("one", 84, 3, 2 * G, 2, 700, bits, gs, n_sel)
+    d = S.make_layer(w)
+    st = _layer(w, 600)
+    st.quantize(d["keys"].cuda())
+    st.n = [700, max(1, n_sel // 2), 0]
+    q, vd = d["q"].cuda(), d["values"].cuda()
+    st.score(q)
+    st.topk(n_sel)
+    small = st.idx.reshape(6, n_sel).clone()
+    count = st.count.clone()
+    wide = torch.zeros(6, 600, dtype=torch.int32, device="cuda")
+    wide[:, :n_sel] = small
+    lse = torch.randn(3, 2 * G, device="cuda") + 30 if use_lse else None
+    out = []
+    for idx, k in ((small, n_sel), (wide, 600)):
         st.y.fill_(-1.0)
-        st.attend(q, vh, n_host, vd, use_acc=False)
+        st.acc.zero_()
+        B.hca_gather_values(st.shape, idx, count, k, st.pos, None, 0, 0, vd, 700, st.ws)
+        if use_lse:
+            B.hca_attend_gathered_global(st.shape, st.kcache, q, idx, count, k, st.sm_scale, lse, st.y, st.acc, st.ws)
+        else:
+            B.hca_attend_gathered(st.shape, st.kcache, q, idx, count, k, st.sm_scale, st.y, st.acc, st.ws)
         torch.cuda.synchronize()
-        out.append(st.y.clone())
-    assert torch.isfinite(out[0]).all()
-    for n_host, y in zip((0, 600, 1150, 1), out[1:]):
-        assert torch.equal(y, out[0]), f"n_host_rows = {n_host}"
+        out.append((st.y.clone(), st.acc.clone()))
+    assert torch.equal(out[0][0], out[1][0]) and torch.equal(out[0][1], out[1][1])
+    assert (out[0][0][2] == 0).all() and (out[0][0][0] != 0).any()
 
 
 def _order_key(x):
