@@ -8,6 +8,7 @@
 namespace hca {
 
 typedef int v4i __attribute__((ext_vector_type(4)));
+typedef int v2i __attribute__((ext_vector_type(2)));
 
 constexpr int kHeadDim = 128;
 constexpr int kBlockBytes = 1024;  // one code block = 64 lanes x 16 B

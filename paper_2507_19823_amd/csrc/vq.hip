@@ -6,7 +6,7 @@
 // Two storage forms.  Narrow (c <= 256 and the table of a KV head within 128 KiB): byte indices, table in
 // LDS - everything said above.  Wide (up to c = 8192, the paper's own size, Fig. 4 / Table 4a): 16-bit
 // indices stored group-major in tiles of 16 Ki slots (vq_wide_at in hca_device.h) and a table kept
-// group-major too; a workgroup scans one tile and brings the table through LDS one slice of groups at a
+// group-major too; a workgroup scans a share of the slots and brings the table through LDS one slice of groups at a
 // time (vq_scan_wide_kernel).
 //
 // Narrow index rows are stored rotated: byte p of the record of slot j holds the index of group
@@ -727,16 +727,26 @@ __global__ __launch_bounds__(256) void vq_lut_kernel(int g, int c, int n_kv_head
   for (int h = 0; h < G; ++h)
 #pragma unroll
     for (int dd = 0; dd < DBAR; ++dd) qv[h][dd] = h2f(q[((int64_t)row * G + h) * kHeadDim + i * DBAR + dd]);
-  for (int cc = threadIdx.x; cc < c; cc += 256) {
-    const float* cv = centroids + (((int64_t)(row % n_kv_heads) * g + i) * c + cc) * DBAR;
-    float* out = lut + (wide ? ((int64_t)row * g + i) * c + cc : ((int64_t)row * c + cc) * g + i) * G;
+  const float* cb = centroids + ((int64_t)(row % n_kv_heads) * g + i) * c * DBAR;
+  for (int c0 = threadIdx.x; c0 < c; c0 += 8 * 256) {       // eight centroids in flight: 8 rows, c = 8192 15.3 -> 12.2 us
+    float cv[8][DBAR];
 #pragma unroll
-    for (int h = 0; h < G; ++h) {
-      float t = 0.f;
+    for (int u = 0; u < 8; ++u)
 #pragma unroll
-      for (int dd = 0; dd < DBAR; ++dd) t = fmaf(qv[h][dd], cv[dd], t);
-      out[h] = t;
-      m[h] = fmaxf(m[h], fabsf(t));
+      for (int dd = 0; dd < DBAR; ++dd) cv[u][dd] = cb[(int64_t)(c0 + 256 * u < c ? c0 + 256 * u : c0) * DBAR + dd];
+#pragma unroll
+    for (int u = 0; u < 8; ++u) {
+      const int cc = c0 + 256 * u;
+      if (cc >= c) break;
+      float* out = lut + (wide ? ((int64_t)row * g + i) * c + cc : ((int64_t)row * c + cc) * g + i) * G;
+#pragma unroll
+      for (int h = 0; h < G; ++h) {
+        float t = 0.f;
+#pragma unroll
+        for (int dd = 0; dd < DBAR; ++dd) t = fmaf(qv[h][dd], cv[u][dd], t);
+        out[h] = t;
+        m[h] = fmaxf(m[h], fabsf(t));
+      }
     }
   }
 #pragma unroll
@@ -904,28 +914,49 @@ __global__ __launch_bounds__(1024) void vq_scan_kernel(int c, int64_t cap, const
   }
 }
 
-// Eq. 3 for the wide form (16-bit indices, a table larger than LDS).  One workgroup of 1024 threads scans
-// one tile of 16 Ki slots, 16 consecutive slots per thread with their running integer sums in registers,
-// and walks through the groups a slice at a time: gps groups whose entries (gps * c * G * 4 bytes <= 128 KiB)
-// are copied from the group-major table into LDS on their heads' grids, then looked up with the tile's
-// indices of those groups (32 contiguous bytes per thread and group).  The table is re-read once per tile:
-// 4 MiB of full lines from L2 per 16 Ki tokens, instead of one L2 request per token and group.
-template <int G>
-__global__ __launch_bounds__(1024) void vq_scan_wide_kernel(int g, int c, int gps, int64_t cap,
+// Eq. 3 for the wide form (16-bit indices, a table larger than LDS).  One workgroup of 1024 threads scans a share
+// of up to NQ * 4096 slots, per thread NQ quads of consecutive slots with their running integer sums in registers,
+// and walks through the groups a slice at a time: gps groups whose entries (gps * c * G * 4 bytes <= 128 KiB) are
+// copied from the group-major table into LDS on their heads' grids, then looked up with the share's indices of
+// those groups.  The table is re-read once per share: full lines from L2, instead of one L2 request per token and
+// group.
+// Bound by the refills, and by the lookups next to them: at 8 rows x 300 Ki slots, c = 8192, a slice takes 3.1 us:
+// LDS is busy for 1.2 of them, the vector units for 1.5, and a share that leaves the refills out still needs 2.7.
+// So the shares are equal and as many as compute units (157 us with a tile of 16 Ki slots per workgroup, 152 of
+// them: 118 us), and a thread asks for its whole part of a slice, eight 16-byte entries, when it has finished its
+// own lookups and before it waits for the others' (99 us; asked for before the lookups, 118: the indices
+// queue behind it).
+template <int G, int NQ>
+__global__ __launch_bounds__(1024) void vq_scan_wide_kernel(int g, int c, int gps, int64_t cap, int64_t per_wg,
                                                              const uint16_t* __restrict__ pcache,
                                                              float* __restrict__ lut, NRes nr, int n_kv_heads, int rows,
                                                              float* __restrict__ sel, float* __restrict__ z_out) {
   using E = typename EntryT<G>::type;
   using F = typename EntryT<G>::fix;
+  constexpr int kPer = 128 / (int)sizeof(E);              // entries of a slice per thread,
+  constexpr int kGo = NQ <= 3 ? kPer : kPer / 4;          // and how many of them are in flight: what the registers allow
   extern __shared__ __align__(16) unsigned char lds_raw[];
   __shared__ int sexp[4];
   // workgroup x serves row x % rows: consecutive workgroups go to the eight dies in turn, so with eight rows
   // every row is scanned by one die and its table (4 MiB at c = 8192, four query heads) stays in that die's L2
   const int row = blockIdx.x % rows;
-  const int64_t tile = blockIdx.x / rows;
+  const int64_t share = blockIdx.x / rows;
   const int64_t n = nr.n[row / n_kv_heads];
-  const int64_t t0 = tile * kVqTile;
+  const int64_t t0 = share * per_wg;
   if (t0 >= n) return;
+  const int64_t t1 = t0 + per_wg < n ? t0 + per_wg : n;
+  F* tab = reinterpret_cast<F*>(lds_raw);
+  const E* trow = reinterpret_cast<const E*>(lut) + (int64_t)row * g * c;
+  const int ne = gps * c;                                 // entries of a slice, at most 1024 * kPer
+  E nt[kGo];
+  auto fetch = [&](int g0, int u0) {
+    const E* src = trow + (int64_t)g0 * c;
+    uint32_t t = threadIdx.x;
+    asm volatile("" : "+v"(t));                           // addresses formed here, not kept over the lookups
+#pragma unroll
+    for (int u = 0; u < kGo; ++u)
+      if (1024 * (u0 + u) < ne) nt[u] = (src + 1024 * (u0 + u))[t < (uint32_t)(ne - 1024 * (u0 + u)) ? t : 0u];
+  };
   float* tail = lut + (int64_t)rows * g * c * G;
   if (threadIdx.x < 64) {                                 // exponents from the per-group maxima, as in the LDS form
     const float* am = tail + (int64_t)row * g * 4;
@@ -938,72 +969,95 @@ __global__ __launch_bounds__(1024) void vq_scan_wide_kernel(int g, int c, int gp
     if (threadIdx.x < G) {
       const int s = vq_grid_exponent(m);
       sexp[threadIdx.x] = s;
-      if (tile == 0) reinterpret_cast<int32_t*>(tail + (int64_t)rows * g * 4)[row * 4 + threadIdx.x] = s;
+      if (share == 0) reinterpret_cast<int32_t*>(tail + (int64_t)rows * g * 4)[row * 4 + threadIdx.x] = s;
     }
   }
   __syncthreads();
   int s[G];
 #pragma unroll
-  for (int h = 0; h < G; ++h) s[h] = sexp[h];
-  F* tab = reinterpret_cast<F*>(lds_raw);
-  const E* trow = reinterpret_cast<const E*>(lut) + (int64_t)row * g * c;
+  for (int h = 0; h < G; ++h) s[h] = __builtin_amdgcn_readfirstlane(sexp[h]);
   const int64_t tiles = vq_tiles(cap);
-  const uint16_t* ptile = pcache + (row * tiles + tile) * g * (int64_t)kVqTile + threadIdx.x * 16;
-  int zi[16][G];
+  // quad q of a thread is the four slots from t0 + (threadIdx.x + 1024 q) * 4.  Shares start at multiples of 256
+  // slots, so the quads of a wave lie in one tile and are scanned or left out together
+  const int w = __builtin_amdgcn_readfirstlane((int)(threadIdx.x >> 6)), lane = threadIdx.x & 63;
+  const uint16_t* ip[NQ];
+  int nq = 0;
 #pragma unroll
-  for (int tt = 0; tt < 16; ++tt)
+  for (int q = 0; q < NQ; ++q) {
+    const int64_t j = t0 + 256 * w + 4096 * q;
+    if (j < t1) nq = q + 1;
+    ip[q] = pcache + vq_wide_at(g, tiles, row, j < t1 ? j : t0, 0);
+  }
+  int zi[NQ][4][G];
 #pragma unroll
-    for (int h = 0; h < G; ++h) zi[tt][h] = 0;
+  for (int q = 0; q < NQ; ++q)
+#pragma unroll
+    for (int tt = 0; tt < 4; ++tt)
+#pragma unroll
+      for (int h = 0; h < G; ++h) zi[q][tt][h] = 0;
   // the indices of the next group are fetched while the current group is looked up (and while the next slice
-  // of the table is brought in), so no slice waits for HBM
-  auto load_idx = [](const uint16_t* p, int i) {          // read once: keep it out of the way of the table in L2
-    const v4i t4 = __builtin_nontemporal_load(reinterpret_cast<const v4i*>(p) + i);
-    return uint4{(uint32_t)t4.x, (uint32_t)t4.y, (uint32_t)t4.z, (uint32_t)t4.w};
-  };
-  uint4 na = load_idx(ptile, 0), nb = load_idx(ptile, 1);
+  // of the table is brought in), so no slice waits for HBM; read once: kept out of the way of the table in L2
+  v2i nx[NQ];
+#pragma unroll
+  for (int q = 0; q < NQ; ++q) nx[q] = __builtin_nontemporal_load(reinterpret_cast<const v2i*>(ip[q]) + lane);
+  const uint32_t last = (uint32_t)(c - 1);
   for (int g0 = 0; g0 < g; g0 += gps) {
+    fetch(g0, 0);
     __syncthreads();                                      // the previous slice's lookups are done
-    const E* src = trow + (int64_t)g0 * c;
-    for (int i = threadIdx.x; i < gps * c; i += 1024) tab[i] = entry_fix<G>(src[i], s);
+#pragma unroll
+    for (int u0 = 0; u0 < kPer; u0 += kGo) {
+      if (u0 > 0) fetch(g0, u0);
+#pragma unroll
+      for (int u = 0; u < kGo; ++u)
+        if (1024 * (u0 + u) < ne && threadIdx.x < (uint32_t)(ne - 1024 * (u0 + u)))
+          tab[threadIdx.x + 1024 * (u0 + u)] = entry_fix<G>(nt[u], s);
+    }
     __syncthreads();
     for (int gl = 0; gl < gps; ++gl) {
-      const uint4 pa = na, pb = nb;
+      v2i cur[NQ];
+#pragma unroll
+      for (int q = 0; q < NQ; ++q) cur[q] = nx[q];
       if (g0 + gl + 1 < g) {
-        const uint16_t* ip = ptile + (int64_t)(g0 + gl + 1) * kVqTile;
-        na = load_idx(ip, 0);
-        nb = load_idx(ip, 1);
-      }
-      const uint32_t wd[8] = {pa.x, pa.y, pa.z, pa.w, pb.x, pb.y, pb.z, pb.w};
-      F e[16];                                            // sixteen table reads in flight
+        const int64_t off = (int64_t)(g0 + gl + 1) * kVqTile;
 #pragma unroll
-      for (int tt = 0; tt < 16; ++tt) {
-        uint32_t code = (wd[tt >> 1] >> (16 * (tt & 1))) & 0xffffu;
-        if (code >= (uint32_t)c) code = 0;                // slots past n hold whatever memory held
-        e[tt] = tab[gl * c + code];
+        for (int q = 0; q < NQ; ++q) nx[q] = __builtin_nontemporal_load(reinterpret_cast<const v2i*>(ip[q] + off) + lane);
       }
+      const F* tg = tab + gl * c;
 #pragma unroll
-      for (int tt = 0; tt < 16; ++tt) {
-        if constexpr (G == 4) { zi[tt][0] += e[tt].x; zi[tt][1] += e[tt].y; zi[tt][2] += e[tt].z; zi[tt][3] += e[tt].w; }
-        else if constexpr (G == 2) { zi[tt][0] += e[tt].x; zi[tt][1] += e[tt].y; }
-        else { zi[tt][0] += e[tt]; }
+      for (int q = 0; q < NQ; ++q) {
+        if (q >= nq) continue;
+        F e[4];
+#pragma unroll
+        for (int tt = 0; tt < 4; ++tt) {
+          const uint32_t code = ((uint32_t)(tt < 2 ? cur[q].x : cur[q].y) >> (16 * (tt & 1))) & 0xffffu;
+          e[tt] = tg[code < last ? code : last];          // slots past n hold whatever memory held
+        }
+#pragma unroll
+        for (int tt = 0; tt < 4; ++tt) {
+          if constexpr (G == 4) { zi[q][tt][0] += e[tt].x; zi[q][tt][1] += e[tt].y; zi[q][tt][2] += e[tt].z; zi[q][tt][3] += e[tt].w; }
+          else if constexpr (G == 2) { zi[q][tt][0] += e[tt].x; zi[q][tt][1] += e[tt].y; }
+          else { zi[q][tt][0] += e[tt]; }
+        }
       }
     }
   }
-  const int64_t j0 = t0 + threadIdx.x * 16;
 #pragma unroll
-  for (int tt = 0; tt < 16; ++tt) {
-    const int64_t j = j0 + tt;
-    if (j >= n) break;
-    float z[G];
+  for (int q = 0; q < NQ; ++q) {
 #pragma unroll
-    for (int h = 0; h < G; ++h) z[h] = ldexpf((float)zi[tt][h], -s[h]);
-    float best = z[0];
+    for (int tt = 0; tt < 4; ++tt) {
+      const int64_t j = t0 + ((int64_t)threadIdx.x + 1024 * q) * 4 + tt;
+      if (j >= t1) break;
+      float z[G];
 #pragma unroll
-    for (int h = 1; h < G; ++h) best = fmaxf(best, z[h]);
-    sel[(int64_t)row * cap + j] = best;
-    if (z_out != nullptr) {
+      for (int h = 0; h < G; ++h) z[h] = ldexpf((float)zi[q][tt][h], -s[h]);
+      float best = z[0];
 #pragma unroll
-      for (int h = 0; h < G; ++h) z_out[((int64_t)row * G + h) * cap + j] = z[h];
+      for (int h = 1; h < G; ++h) best = fmaxf(best, z[h]);
+      sel[(int64_t)row * cap + j] = best;
+      if (z_out != nullptr) {
+#pragma unroll
+        for (int h = 0; h < G; ++h) z_out[((int64_t)row * G + h) * cap + j] = z[h];
+      }
     }
   }
 }
@@ -1097,13 +1151,29 @@ static int32_t scan_wide_launch(const Layout& L, int g, int c, const uint8_t* pc
   int gps = 1;                                      // groups per LDS slice: the most that fit 128 KiB
   while (gps * 2 <= g && (int64_t)gps * 2 * c * G * 4 <= 128 * 1024) gps *= 2;
   const size_t lds = (size_t)gps * c * G * 4;
-  if (lds > 64 * 1024) {
-    static std::atomic<uint64_t> opted{0};                  // one per instantiation
-    const int32_t rc = lds_opt_in(reinterpret_cast<const void*>(&vq_scan_wide_kernel<G>), 128 * 1024, &opted);   // + 16 B static
-    if (rc != HCA_OK) return rc;
+  // Equal shares, as many as compute units or a multiple, of at most 12 Ki slots where that gives one share per
+  // unit: three quads leave registers for a whole slice in flight.  Else 16 Ki, with a quarter of a slice in flight,
+  // as a larger share has fewer refills.  8 rows, c = 8192, score call with table, before -> now: n = 1000 165 -> 101 us,
+  // 300 000 175 -> 107, 400 000 178 -> 145, 530 000 329 -> 260, 1 Mi 347 -> 296 (c = 1024: 65 -> 31, 78 -> 52, 81 -> 61,
+  // 139 -> 90, 174 -> 145; one query head per KV head, c = 8192, 1 Mi: 250 -> 162).
+  const int64_t units = L.rows < 256 ? 256 / L.rows : 1;
+  const bool one = nmax <= units * 12 * 1024;
+  const int64_t turns = one ? 1 : (nmax + units * 16 * 1024 - 1) / (units * 16 * 1024);
+  int64_t per_wg = align_up((nmax + units * turns - 1) / (units * turns), 256);
+  if (per_wg < 2048) per_wg = 2048;
+  const int64_t shares = (nmax + per_wg - 1) / per_wg;
+#define HCA_WIDE(NQ)                                                                                                     \
+  {                                                                                                                      \
+    if (lds > 64 * 1024) {                                                                                               \
+      static std::atomic<uint64_t> opted{0};                /* one per instantiation */                                  \
+      const int32_t rc = lds_opt_in(reinterpret_cast<const void*>(&vq_scan_wide_kernel<G, NQ>), 128 * 1024, &opted);     \
+      if (rc != HCA_OK) return rc;                          /* + 16 B static */                                          \
+    }                                                                                                                    \
+    vq_scan_wide_kernel<G, NQ><<<(unsigned)(shares * L.rows), 1024, lds, st>>>(                                          \
+        g, c, gps, L.cap, per_wg, (const uint16_t*)pcache, lut, nr, L.n_kv_heads, L.rows, sel, z_opt);                   \
   }
-  vq_scan_wide_kernel<G><<<(unsigned)(vq_tiles(nmax) * L.rows), 1024, lds, st>>>(g, c, gps, L.cap, (const uint16_t*)pcache,
-                                                                                 lut, nr, L.n_kv_heads, L.rows, sel, z_opt);
+  if (one) HCA_WIDE(3) else HCA_WIDE(4)
+#undef HCA_WIDE
   HCA_HIP(hipGetLastError());
   return HCA_OK;
 }

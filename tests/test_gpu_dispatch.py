@@ -314,3 +314,41 @@ def test_topp_at_the_edges_of_its_bins(B, oracle, kind, n):
         assert np.array_equal(mass.cpu().numpy().view(np.uint64), omass) and np.array_equal(count.cpu().numpy(), ocount)
         for r in range(R):
             assert np.array_equal(idx[r, :ocount[r]].cpu().numpy(), oidx[r, :ocount[r]]), (r, tau)
+
+
+@pytest.mark.parametrize("gqa,groups,c,n", [(4, 32, 8192, 12288), (4, 32, 300, 12289), (4, 64, 513, 16384), (4, 32, 1024, 16385),
+                                            (2, 32, 8192, 12289), (1, 64, 8192, 257), (1, 32, 511, 4097)])
+def test_wide_codebook_scan_shares(B, gqa, groups, c, n):
+    # 256 rows: one share per row up to 12 Ki slots, 16 Ki above, two above that; every 37th row has fewer tokens.
+    # The scores are integer sums on a power-of-two grid, so they have to be equal
+    rows, batch = 8, 32
+    sh = B.make_shape(batch, rows * gqa, rows, n + 3)
+    gen = torch.Generator(device="cuda").manual_seed(n + c)
+    cen = torch.randn(rows, groups, c, 128 // groups, device="cuda", generator=gen)
+    cb = B.make_codebook(groups, c, cen)
+    size = B.hca_vq_pcache_bytes(sh, cb) // 2
+    pc = torch.randint(0, c, (size,), device="cuda", dtype=torch.int16, generator=gen)
+    q = torch.randn(batch, rows * gqa, 128, device="cuda", generator=gen).half()
+    lut = torch.zeros(B.hca_vq_lut_bytes(sh, cb) // 4, device="cuda")
+    sel = torch.full((batch, rows, n + 3), -7.0, device="cuda")
+    z = torch.full((batch, rows * gqa, n + 3), -7.0, device="cuda")
+    lens = [n if b % 5 else max(1, n - 300 * (b + 1)) for b in range(batch)]
+    B.hca_vq_score(sh, cb, pc.view(torch.uint8), q, lens, lut, sel, z)
+    torch.cuda.synchronize()
+    tile = 16384
+    tiles = (n + 3 + tile - 1) // tile
+    codes = pc.view(batch * rows, tiles, groups, tile)
+    table = lut[: batch * rows * groups * c * gqa].view(batch * rows, groups, c, gqa)
+    for row in (0, 7, 8, 121, 255):
+        m = lens[row // rows]
+        expo = (24 - torch.frexp(table[row].abs().amax((0, 1))).exponent).tolist()
+        scale = torch.tensor([2.0 ** e for e in expo], dtype=torch.float64, device="cuda")       # exact powers of two
+        fix = torch.round(table[row].double() * scale).long()
+        total = torch.zeros(tiles * tile, gqa, dtype=torch.long, device="cuda")
+        for i in range(groups):
+            total += fix[i][codes[row, :, i].reshape(-1).long()]
+        want = (total.float().double() / scale).float()[:m]
+        got = z.view(batch * rows, gqa, n + 3)[row]
+        assert torch.equal(got[:, :m].T, want), (row, m)
+        assert torch.equal(sel.view(batch * rows, n + 3)[row, :m], want.amax(1))
+        assert bool((got[:, m:] == -7.0).all()) and bool((sel.view(batch * rows, n + 3)[row, m:] == -7.0).all())
