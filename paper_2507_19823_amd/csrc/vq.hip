@@ -731,13 +731,15 @@ __global__ __launch_bounds__(256) void vq_lut_kernel(int g, int c, int n_kv_head
   for (int c0 = threadIdx.x; c0 < c; c0 += 8 * 256) {       // eight centroids in flight: 8 rows, c = 8192 15.3 -> 12.2 us
     float cv[8][DBAR];
 #pragma unroll
-    for (int u = 0; u < 8; ++u)
+    for (int u = 0; u < 8; ++u) {
+      if (256 * u >= c) break;                              // (a codebook of at most 256: one centroid per thread)
 #pragma unroll
       for (int dd = 0; dd < DBAR; ++dd) cv[u][dd] = cb[(int64_t)(c0 + 256 * u < c ? c0 + 256 * u : c0) * DBAR + dd];
+    }
 #pragma unroll
     for (int u = 0; u < 8; ++u) {
       const int cc = c0 + 256 * u;
-      if (cc >= c) break;
+      if (256 * u >= c || cc >= c) break;
       float* out = lut + (wide ? ((int64_t)row * g + i) * c + cc : ((int64_t)row * c + cc) * g + i) * G;
 #pragma unroll
       for (int h = 0; h < G; ++h) {
