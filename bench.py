@@ -935,10 +935,10 @@ def prefill_blocks(w, sizes=(1024, 4096, 16384, 65536, 262144)):
             ms, nb = run(lambda blk, T_, n: B.hca_vq_assign(shape, cb, P, blk, T_, n), total, T)
             tf = rows * T * g * c * (128 // g) * 3 / ms / 1e9          # the exhaustive exact search's flops
             r = {"block_tokens": T, "blocks": nb, "ms_per_block": ms, "tokens_per_s": w.batch * T / ms * 1e3}
-            if T >= 1024 and c >= 512 and T * c >= (1 << 21):
-                # the library's bulk form from this size on: two passes of v_mfma_f32_32x32x16_f16 over every
+            if c > 256 or (T >= 256 and rows * T * g * c >= (1 << 27)):
+                # the library's bulk form from this size on: one pass of v_mfma_f32_32x32x16_f16 over every
                 # (token, group, centroid), 16 products each, then the exact search on the shortlist only
-                mt = rows * T * g * c * 2 * 16 * 2 / ms / 1e9
+                mt = rows * T * g * c * 2 * 16 / ms / 1e9
                 r.update({"form": "matrix-core shortlist + exact chain on the shortlist", "matrix_TFLOPs": mt,
                           "frac_of_f16_matrix_peak": mt / 2500.0, "exhaustive_search_equivalent_TFLOPs": tf})
             else:
