@@ -471,7 +471,7 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(4))) void v
   __shared__ float s_cmax[2][4];
   __shared__ __align__(16) uint8_t s_win[WIDE ? 1 : 256][kGroups];         // narrow form: a token's sixteen record bytes
   __shared__ uint16_t s_queue[512];                             // (token, group) pairs left to the exhaustive chain
-  __shared__ uint32_t s_nq;
+  __shared__ uint32_t s_added[kGroups];                         // how many of them each group added
   const int row = blockIdx.y, g0 = blockIdx.z * kGroups;
   const int tid = threadIdx.x, lane = tid & 63, w = tid >> 6;
   const int col = lane & 31, kb = lane >> 5;
@@ -531,8 +531,12 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(4))) void v
   fetch(0);
   load_x(0);
   commit(0);
-  if (tid == 0) s_nq = 0;
+  if (tid < kGroups) s_added[tid] = 0;
   __syncthreads();
+  // entries in the queue when a group begins.  Every wave keeps it for itself, from counts that no longer change: a wave
+  // still deciding about group gi reads s_added[gi] while another may already be appending to s_added[gi + 1], and all of
+  // them decide the same - the branch below holds a barrier
+  uint32_t queued = 0;
   for (int gi = 0; gi < kGroups; ++gi) {
     const int buf = gi & 1;
     float x2[TT];
@@ -606,22 +610,22 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(4))) void v
       const bool queue = (halves_of((uint32_t)rivals).lo | halves_of((uint32_t)rivals).hi) != 0;
       if (kb == 0) {
         const int tok = w * 64 + 32 * tt + col;
-        if (queue) s_queue[atomicAdd(&s_nq, 1u)] = (uint16_t)(tok | gi << 8);
+        if (queue) s_queue[queued + atomicAdd(&s_added[gi], 1u)] = (uint16_t)(tok | gi << 8);
         else put(tok, gi, (int)win);
       }
     }
     __syncthreads();
-    if (s_nq > 256 || gi + 1 == kGroups) {                  // room for another group's 256 tokens, or the end
-      for (uint32_t e = tid >> 3; e < s_nq; e += 32) {      // eight lanes per queued token
+    queued += s_added[gi];
+    if (queued > 256 || gi + 1 == kGroups) {                // no room for another group's 256 tokens, or the end
+      for (uint32_t e = tid >> 3; e < queued; e += 32) {    // eight lanes per queued token
         const int tok = s_queue[e] & 255, qi = s_queue[e] >> 8;
         const int64_t t = wg0 + tok;
         const int win = am_exhaustive<DBAR, 8>(k_new + ((int64_t)row * T + (t < T ? t : T - 1)) * kHeadDim + (g0 + qi) * DBAR,
                                                cb + (int64_t)qi * c * DBAR, c, tid & 7);
         if ((tid & 7) == 0) put(tok, qi, win);
       }
-      __syncthreads();
-      if (tid == 0) s_nq = 0;
-      __syncthreads();
+      __syncthreads();                                      // the entries have been read, and s_win is complete
+      queued = 0;
     }
   }
   const int64_t t = wg0 + tid;

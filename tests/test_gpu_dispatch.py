@@ -228,6 +228,38 @@ def test_bulk_assignment_equals_the_exhaustive_chain(B, g, c, G, T, rows):
     assert (acc[0, :, 4:4 + T] == 0).all() and (acc[0, :, :4] == 7).all() and (acc[0, :, 4 + T:] == 7).all()
 
 
+@pytest.mark.parametrize("g,c,G", [(32, 256, 4), (64, 256, 4), (64, 256, 1), (32, 96, 4), (32, 250, 1)])
+def test_assignment_queue_fills_at_any_group(B, oracle, g, c, G):
+    """Up to 256 centroids: a share of every group's centroids (none to all, another one in each group) exists twice, so
+    that a workgroup of 256 tokens has from none to all of them queued for the exact chain of every centroid in a group.  Its
+    queue passes the fill that makes room for the next group after one, two or several groups, and in both halves of
+    the record, with the last workgroup of a row ragged."""
+    dbar, rows = 128 // g, 8
+    T = -(-(1 << 27) // (rows * g * c)) + 131
+    rng = np.random.default_rng(g + c + G)
+    cen = rng.standard_normal((rows, g, c, dbar)).astype(np.float32)
+    for i in range(g):
+        twice = int(c // 2 * ((5 * i) % 8) / 7)
+        cen[:, i, c - twice:] = cen[:, i, :twice]
+    k = rng.standard_normal((1, rows, T, 128)).astype(np.float16)
+    shape = B.make_shape(1, rows * G, rows, T + 3)
+    dcen = torch.from_numpy(cen).cuda()
+    cb = B.make_codebook(g, c, dcen)
+    pc = torch.zeros(B.hca_vq_pcache_bytes(shape, cb), dtype=torch.uint8, device="cuda")
+    oc = oracle.VQCache(rows, T, cen)
+    oracle.vq_assign(oc, k.reshape(rows, T, 128))
+    dk = torch.from_numpy(k).cuda()
+    wide = g * c * G > 32768
+    for _ in range(3):
+        pc.fill_(0xEE)
+        B.hca_vq_assign(shape, cb, pc, dk, T, [2])
+        out = torch.full((rows, T + 3, g * (2 if wide else 1)), 0xEE, dtype=torch.uint8, device="cuda")
+        B.hca_vq_export_pcache(shape, cb, pc, [T + 2], out)
+        got = out.cpu().numpy()
+        got = got.view(np.uint16) if wide else got
+        assert np.array_equal(got[:, 2:T + 2], oc.P[:, :T].astype(got.dtype))
+
+
 @pytest.mark.parametrize("bits,gs", [(4, 32), (2, 64)])
 @pytest.mark.parametrize("n,M,protect,kind,spare", [
     (4096, 4095, 0, "zeros", False), (4097, 2049, 1, "dense", True), (9000, 1, 0, "dense", False),
