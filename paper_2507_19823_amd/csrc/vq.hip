@@ -113,20 +113,25 @@ __global__ __launch_bounds__(256) void vq_assign_kernel(int g, int c, int n_kv_h
 //     k 0..3   A = -hi(c_d)            B = x_d        hi(c) = fp16(c), lo(c) = fp16(c - hi(c))
 //     k 4..7   A = -lo(c_d)            B = x_d        (x is fp16 as it arrives)
 //     k 8..10  A = h1, h2, h3          B = 1          h = fp32 |c|^2 / 2 cut into three fp16 pieces
-//   Errors against the exact e(c), with S = |x|^2 + max_c |c|^2 < 2^15 (so that no piece overflows fp16; fp16
-//   denormals are kept by the instruction): c_d - hi - lo is at most 2^-22 |c_d| + 2^-25, h loses at most
+//   Errors of e(c), for S = |x|^2 + max_c |c|^2 < 2^15 (so that no piece overflows fp16; fp16 denormals are kept by the
+//   instruction) and with s(c) = |x|^2 + |c|^2: c_d - hi - lo is at most 2^-22 |c_d| + 2^-25, h loses at most
 //   2^-33 of itself + 2^-25, the fp32 |c|^2 chain 4 u |c|^2 (u = 2^-24), and the instruction's 15 additions at
-//   most 2^-23 each of sum |terms| <= 2.01 S whatever their order and rounding: together below 2^-17.9 S + 2^-23.
-//   The exact chain d(c) itself is within 7 u d <= 2^-20.2 S of the truth (in units of e).  With
-//   delta = 2^-17 S + 2^-21 - one and a half times the sum of those - the winner c* of the exact chain (first smallest
-//   d) has e(c*) <= min_c e(c) + 2 delta as computed.
+//   most 2^-23 each of sum |terms| <= 2.01 s(c) whatever their order and rounding: together below
+//   E(c) = 2^-17.9 s(c) + 2^-23.  The exact chain d(c) itself is within 7 u d of the truth.
+//   Let c1 have the smallest e as computed and c* be the winner of the exact chain (first smallest d): then
+//   e(c*) <= e(c1) + E(c*) + E(c1) + 7.5 u d(c1) as computed.  Both lie near x: d(c*) <= (1 + 15 u) d(c1), and
+//   d(c1) = |x|^2 + 2 e(c1) is known up to 2 E(c1) <= 2^-16.9 S + 2^-22, so that |c| <= |x| + sqrt(d2) for both, d2 an
+//   upper bound of d(c1), and  S' = |x|^2 + (|x| + sqrt(d2))^2  bounds both s(c), however far away other centroids
+//   are.  With  delta = 2^-17 S' + 2^-21 - one and a half times the sum of the errors -  e(c*) <= e(c1) + 2 delta.
+//   (S in the place of S' sent 19 % of normal tokens to the queue below at two channels and 8192 centroids, and 86 %
+//   where one channel has eight times the other's scale; S' sends 0.7 % and 10 %.)
 //   One pass takes the minimum of e over every block of centroids and half wave (eight v_min3 per instruction) and
 //   keeps the smallest ones per token, each with its block's number in the low mantissa bits (4 more per block): a
 //   v_and_or, v_med3 and v_min in place of compares and selects.  That moves a value by less than 2^-16 of itself, so a
 //   block counts as a candidate up to  m1 + 2.1 delta + 2^-14.9 |m1|  (m1 the smallest).  The exact chain then runs over
 //   the 16 rows of a tile that the half wave holds, both halves sharing the work, for one block per token and now and
 //   then two.  Tokens with more blocks in question than were kept, or with S out of range, are noted in an LDS queue
-//   and go through the exact chain of every centroid at the end.
+//   and go through the exact chain of every centroid at the end.  (|m1| < 1.01 S moves d2 by at most 2^-15 S more.)
 // What bounds it is the vector ALU's issue (a second pass of products with the threshold folded in, a sign test and a
 // list of candidates in the loop took twice the instructions): 17.6 per matrix instruction with everything, 90 % of
 // the issue slots, the matrix cores 40 % busy.  16 Ki tokens x 8 KV heads against 8192 centroids: 1.23 ms (2.44 in two
@@ -181,9 +186,12 @@ __device__ __forceinline__ v8h am_token(const uint32_t (&xw)[DBAR / 2], int kb, 
   return kb == 0 ? v8h{xh[0], xh[1], xh[2], xh[3], xh[0], xh[1], xh[2], xh[3]}
                  : v8h{one, one, one, zero, zero, zero, zero, zero};
 }
-// How far above the smallest value a block can still hold the winner.
-__device__ __forceinline__ float am_limit(float m1, float S) {
-  const float delta = S * 7.62939453125e-6f + 4.76837158203125e-7f;       // 2^-17 S + 2^-21
+// How far above the smallest value a block can still hold the winner (m1: the smallest value with its block number in it,
+// S = |x|^2 + max |c|^2 in range).
+__device__ __forceinline__ float am_limit(float m1, float x2, float S) {
+  const float d2 = fmaxf(2.f * m1 + x2 + (5e-5f * S + 9.5367431640625e-7f), 0.f);
+  const float near = 2.f * x2 + d2 + 2.f * __builtin_amdgcn_sqrtf(x2 * d2);
+  const float delta = fminf(near, S) * 7.62939453125e-6f + 4.76837158203125e-7f;      // 2^-17 S' + 2^-21
   return m1 + (2.1f * delta + 3.3e-5f * fabsf(m1));
 }
 // (value of the lower half, value of the upper half) of a wave, on every lane of a column
@@ -364,7 +372,7 @@ __global__ __launch_bounds__(512) __attribute__((amdgpu_waves_per_eu(4))) void v
       const float S = x2[tt] + cmax2;
       const Halves a1 = halves_of(__float_as_uint(m1[tt])), a2 = halves_of(__float_as_uint(m2[tt])),
                    a3 = halves_of(__float_as_uint(m3[tt]));
-      const float lim = am_limit(fminf(__uint_as_float(a1.lo), __uint_as_float(a1.hi)), S);
+      const float lim = am_limit(fminf(__uint_as_float(a1.lo), __uint_as_float(a1.hi)), x2[tt], S);
       // the token's candidates, one byte each (block, 255: none): smallest of the lower half, of the upper half, then
       // the second smallest
       auto cand = [&](uint32_t v) { return __uint_as_float(v) <= lim ? (v & 127u) : 255u; };
@@ -582,7 +590,7 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(4))) void v
       const float f0 = __uint_as_float(a1.lo), f1 = __uint_as_float(a1.hi);
       const bool upper = f1 < f0;
       const float S = x2[tt] + cmax2;
-      const float lim = am_limit(upper ? f1 : f0, S);
+      const float lim = am_limit(upper ? f1 : f0, x2[tt], S);
       const bool rivals = fmaxf(f0, f1) <= lim || m2[tt] <= lim || !(S < 32768.f);
       float x[DBAR];
 #pragma unroll

@@ -228,6 +228,46 @@ def test_bulk_assignment_equals_the_exhaustive_chain(B, g, c, G, T, rows):
     assert (acc[0, :, 4:4 + T] == 0).all() and (acc[0, :, :4] == 7).all() and (acc[0, :, 4 + T:] == 7).all()
 
 
+def _passes_us(run, passes=20):
+    """Time of one pass in microseconds, the best of five batches."""
+    run()
+    best = float("inf")
+    for _ in range(5):
+        a, b = torch.cuda.Event(enable_timing=True), torch.cuda.Event(enable_timing=True)
+        a.record()
+        for _ in range(passes):
+            run()
+        b.record()
+        b.synchronize()
+        best = min(best, a.elapsed_time(b) * 1000 / passes)
+    return best
+
+
+@pytest.mark.parametrize("g,c,T", [(64, 1024, 8192), (64, 8192, 2048), (32, 4096, 4096)])
+def test_a_far_centroid_does_not_slow_the_assignment(B, g, c, T):
+    """One centroid per group far from all keys (one that no training round ever moved, say) can win no token, so it must
+    not widen the shortlist: a token with too many candidates costs the exact chain of every centroid, several times the
+    call.  The time may rise by half at most; the indices are those without it."""
+    rows, dbar = 8, 128 // g
+    gen = torch.Generator(device="cuda").manual_seed(c + T)
+    cen = torch.randn(rows, g, c, dbar, generator=gen, device="cuda")
+    far = cen.clone()
+    far[:, :, c // 3] = 0.0
+    far[:, :, c // 3, 0] = 100.0                           # |c|^2 = 10^4, within the shortlist's range
+    near = cen.clone()
+    near[:, :, c // 3] = near[:, :, 0]                     # never chosen either: the lower index wins
+    k = torch.randn(1, rows, T, 128, generator=gen, device="cuda").half()
+    shape = B.make_shape(1, rows, rows, T)
+    took, out = [], []
+    for book in (near, far):
+        cb = B.make_codebook(g, c, book)
+        pc = torch.zeros(B.hca_vq_pcache_bytes(shape, cb), dtype=torch.uint8, device="cuda")
+        took.append(_passes_us(lambda: B.hca_vq_assign(shape, cb, pc, k, T, [0])))
+        out.append(pc)
+    assert torch.equal(out[0], out[1])
+    assert took[1] < 1.5 * took[0], f"{took[0]:.0f} us without the far centroid, {took[1]:.0f} us with it"
+
+
 @pytest.mark.parametrize("g,c,G", [(32, 256, 4), (64, 256, 4), (64, 256, 1), (32, 96, 4), (32, 250, 1)])
 def test_assignment_queue_fills_at_any_group(B, oracle, g, c, G):
     """Up to 256 centroids: a share of every group's centroids (none to all, another one in each group) exists twice, so
