@@ -254,15 +254,17 @@ constexpr int kMaxChunks = 1024;
 struct TopkWs {
   uint32_t* hist;      // [rows][4096]
   uint32_t* ncand;     // [rows][1024] entries in each chunk's list
-  uint32_t* state;     // [rows][4]: T (after resolve), r_eq / still-to-take, b*, unused
-  uint32_t* above;     // [rows][1024] slots strictly above bin b* per chunk
-  uint32_t* coff;      // [rows][1024][2]
+  uint32_t* state;     // [rows][4]: T (after resolve), r_eq / still-to-take, b*, unused; the cumulative walk has the smallest
+                       // and the largest key of its bin in the last two
+  uint32_t* above;     // [rows][1024] slots strictly above bin b* per chunk; before that, the cumulative walk's row maxima
+                       // per group of chunks
+  uint32_t* coff;      // [rows][1024][2]; before the chunk prefixes, the cumulative walk's wave extremes
   uint2* cand;         // [rows][row_entries]: chunk c owns entries [c*chunk, (c+1)*chunk)
   int64_t row_entries;
   // cumulative-weight selection only
-  uint32_t* pcount;    // [rows][4096] slots per 12-bit bin
-  uint64_t* pmass;     // [rows][4096] integer weight per bin
-  uint64_t* pstate;    // [rows][4]: target still to reach, Theta, Z, (unused)
+  uint32_t* pcount;    // [rows][4096] slots per bin, the first kTpBins in use
+  uint64_t* pmass;     // [rows][4096] integer weight per bin, likewise
+  uint64_t* pstate;    // [rows][4]: weight still to reach inside the bin; window of the fine bins (two floats)
   uint32_t* prow;      // [rows][4]: key of the row maximum, slots still allowed, selected count, (unused)
   // scan + top-k in one call only
   uint32_t* samples;   // [rows][kSampleMax] keys of the sampled slots
@@ -485,10 +487,10 @@ __global__ __launch_bounds__(256) void tk_findbin(int n_kv_heads, SelRows sr, To
 // in bin b* or above into its own list (room for the whole chunk, so it cannot overflow), and
 // counts the ones strictly above the bin.  Lists are per chunk so that no two workgroups ever
 // contend for an append position.
-// bin_of: a key's bin, increasing with the key.
+// range(&first, &last): the smallest and the largest key of the bin, asked for while the first tile is on its way.
 template <typename F>
 __device__ __forceinline__ void collect_chunk(const float* __restrict__ vals, int64_t stride, int64_t chunk, int64_t nsel,
-                                              int row, const TopkWs& t, const uint32_t bin, F&& bin_of) {
+                                              int row, const TopkWs& t, F&& range) {
   __shared__ uint32_t wsum[4];
   __shared__ uint32_t pc[64], po[64];
   __shared__ uint32_t s_total;
@@ -504,17 +506,19 @@ __device__ __forceinline__ void collect_chunk(const float* __restrict__ vals, in
   uint2* dst = t.cand + (int64_t)row * t.row_entries + (int64_t)blockIdx.x * chunk;
   const int lane = threadIdx.x & 63, w = threadIdx.x >> 6;
   uint32_t cnt = 0, base = 0;
+  uint32_t key[16];
+  bool valid[16];
+  load_tile_keys(v, c0, c1, key, valid);
+  uint32_t first, last;
+  range(&first, &last);
   for (int64_t s0 = c0; s0 < c1; s0 += 4096) {
-    uint32_t key[16];
-    bool valid[16];
-    load_tile_keys(v, s0, c1, key, valid);
+    if (s0 != c0) load_tile_keys(v, s0, c1, key, valid);
     // slot order inside the tile is (x, wave, lane): one ballot per (x, wave), prefix over the 64 of them
     uint64_t mask[16];
 #pragma unroll
     for (int x = 0; x < 16; ++x) {
-      const uint32_t b = bin_of(key[x]);
-      cnt += valid[x] && b > bin;
-      mask[x] = __ballot(valid[x] && b >= bin);
+      cnt += valid[x] && key[x] > last;
+      mask[x] = __ballot(valid[x] && key[x] >= first);
       if (lane == 0) pc[x * 4 + w] = (uint32_t)__popcll(mask[x]);
     }
     __syncthreads();
@@ -554,8 +558,10 @@ __global__ __launch_bounds__(256) void tk_collect(const float* __restrict__ vals
                                                   int n_kv_heads, SelRows sr, TopkWs t) {
   const int row = blockIdx.y;
   if (sr.want[row / n_kv_heads] <= 0) return;
-  collect_chunk(vals, stride, chunk, sr.nsel[row / n_kv_heads], row, t, t.state[4 * row + 2],
-                [](uint32_t key) { return key >> 20; });
+  collect_chunk(vals, stride, chunk, sr.nsel[row / n_kv_heads], row, t, [&](uint32_t* first, uint32_t* last) {
+    *first = t.state[4 * row + 2] << 20;
+    *last = *first | 0xfffffu;
+  });
 }
 
 // exclusive prefix sum of one value per thread over a 1024-thread workgroup
@@ -1792,26 +1798,35 @@ __device__ __forceinline__ uint64_t tp_weight(float u) {
   return sh >= 64 ? 0 : mant >> sh;
 }
 
-// Bins of the cumulative walk: 32 per factor of two in weight, from the row maximum down (kTpBins - 1) to 2^-64 of it and
-// below (0).  A bin that holds a typical threshold has tens to hundreds of slots in it, so little is left to resolve
-// inside; bins of the key's leading 12 bits, an eighth of an octave of the score, held thousands for a flat row: 8 rows
-// of 500 Ki slots, 8192 to select, 130 us per call in seven launches, 54 now in five (88 of it the resolve stage, 17 now).
+// Bins of the cumulative walk, from the row maximum down: every slot's bin number is the sum of two steps that fall with
+// its score.  The coarse one has 24 steps per factor of two in weight, down to 2^-64 of the maximum.  The fine one has
+// 512 over the window in which most of the row lies (tp_rowmax, tp_hist): a row whose weights are nearly equal spans a
+// fraction of one coarse step, and without the window nearly all its slots lie in the bin to be resolved, by one workgroup
+// over lists that no longer fit its LDS.  Per call, key bins of 12 bits / 32 steps per factor of two / both kinds, 4096 to
+// select: 8 rows of 131 072 scores with a spread of 0.1, 64 / 209 / 44 us, with a spread of 11, 64 / 42 / 42; 8 x 500 000
+// with 11, 65 / 52 / 55.  More fine steps make the histograms' flush longer, with 256 a bin in the middle of a flat row of
+// 500 000 slots no longer fits LDS (118 -> 362 us).
+// The bins only steer the walk; any bin number that grows with the key gives the same selection.
 constexpr int kTpBins = 2048;
+constexpr int kTpFine = kTpBins / 4;
 struct TpBin {
-  float m, sm;      // the row maximum's logit, the softmax scale
-  __device__ __forceinline__ uint32_t operator()(uint32_t key) const {
-    // increasing with the key: a product with a positive factor, a difference, a product, a truncation
-    const float down = (m - key_to_float(key) * sm) * (1.44269504f * kTpBins / 64.0f);
-    const uint32_t b = (uint32_t)(down < (float)(kTpBins - 1) ? down : (float)(kTpBins - 1));
-    return (uint32_t)(kTpBins - 1) - b;
+  float m, sm;           // the row maximum's logit, the softmax scale
+  float top, per_unit;   // the window's upper end and the fine steps per unit of score (0: no window)
+  __device__ __forceinline__ uint32_t operator()(float f) const {
+    const uint32_t coarse = (uint32_t)__builtin_amdgcn_fmed3f((f * sm - m) * (-1.44269504f * (kTpBins - kTpFine) / 64.0f), 0.0f,
+                                                              (float)(kTpBins - kTpFine - 1));
+    const uint32_t fine = (uint32_t)__builtin_amdgcn_fmed3f((top - f) * per_unit, 0.0f, (float)kTpFine);
+    return (uint32_t)(kTpBins - 1) - coarse - fine;
   }
 };
 
-// Row maximum of every group of chunks, as an order key (tmax, in the room of the chunk counts), and clean counters for the
-// histogram pass.
+// Row maximum of every group of chunks, as an order key (in `above`, the room of the chunk counts), the largest and the
+// smallest score of each of the group's first two waves (in `coff`, the room of the chunk prefixes), and clean counters
+// for the histogram pass.  span: the difference of scores beyond which a weight is less than 2^-64 of the larger one; a
+// smallest score takes no account of those, a mask's lowest value must not widen the window.
 __global__ __launch_bounds__(256) void tp_rowmax(const float* __restrict__ vals, int64_t stride, int64_t chunk,
-                                                 int n_kv_heads, SelRows sr, TopkWs t) {
-  __shared__ uint32_t wmax[4];
+                                                 int n_kv_heads, SelRows sr, float span, TopkWs t) {
+  __shared__ float wmax[4];
   const int row = blockIdx.y;
   if (sr.want[row / n_kv_heads] <= 0) return;
   for (int i = blockIdx.x * 256 + threadIdx.x; i < kTpBins; i += gridDim.x * 256) {
@@ -1823,33 +1838,48 @@ __global__ __launch_bounds__(256) void tp_rowmax(const float* __restrict__ vals,
   int64_t c1 = c0 + chunk;
   if (c1 > nsel) c1 = nsel;
   const float* v = vals + (int64_t)row * stride;
-  uint32_t best = 0;
+  const int w = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+  float hi = -INFINITY, lo = INFINITY;
   for (int64_t s0 = c0; s0 < c1; s0 += 4096) {
-    uint32_t key[16];
-    bool valid[16];
-    load_tile_keys(v, s0, c1, key, valid);
+    float f[16];
 #pragma unroll
-    for (int x = 0; x < 16; ++x)
-      if (valid[x] && key[x] > best) best = key[x];
+    for (int x = 0; x < 16; ++x) {
+      const int64_t j = s0 + x * 256 + threadIdx.x;
+      f[x] = v[j < c1 ? j : c1 - 1];
+    }
+#pragma unroll
+    for (int x = 0; x < 16; ++x) {
+      if (s0 + x * 256 + threadIdx.x >= c1) f[x] = -INFINITY;
+      hi = fmaxf(hi, f[x]);
+    }
+    if (w < 2) {
+#pragma unroll
+      for (int x = 0; x < 16; ++x)
+        if (f[x] > hi - span) lo = fminf(lo, f[x]);
+    }
   }
 #pragma unroll
   for (int o = 32; o >= 1; o >>= 1) {
-    const uint32_t other = __shfl_xor(best, o);
-    if (other > best) best = other;
+    const float oh = __shfl_xor(hi, o), ol = __shfl_xor(lo, o), most = fmaxf(hi, oh), cut = most - span;
+    lo = fminf(hi > cut ? fmaxf(lo, cut) : INFINITY, oh > cut ? fmaxf(ol, cut) : INFINITY);
+    hi = most;
   }
-  if ((threadIdx.x & 63) == 0) wmax[threadIdx.x >> 6] = best;
+  if ((threadIdx.x & 63) == 0) {
+    wmax[w] = hi;
+    if (w < 2) reinterpret_cast<float2*>(t.coff)[(int64_t)row * 1024 + 2 * blockIdx.x + w] = float2{hi, lo};
+  }
   __syncthreads();
-  if (threadIdx.x == 0) {
-    for (int x = 1; x < 4; ++x) if (wmax[x] > best) best = wmax[x];
-    t.above[(int64_t)row * 1024 + blockIdx.x] = best;
-  }
+  if (threadIdx.x == 0)
+    t.above[(int64_t)row * 1024 + blockIdx.x] =
+        c0 < c1 ? order_key(fmaxf(fmaxf(wmax[0], wmax[1]), fmaxf(wmax[2], wmax[3]))) : 0u;
 }
 
 // Histogram of slot counts and integer weights.
 __global__ __launch_bounds__(256) void tp_hist(const float* __restrict__ vals, int64_t stride, int64_t chunk,
-                                               int n_kv_heads, SelRows sr, float sm_scale, TopkWs t) {
+                                               int n_kv_heads, SelRows sr, float sm_scale, float span, TopkWs t) {
   __shared__ uint32_t lc[kTpBins], wmax[4];
   __shared__ unsigned long long lm[kTpBins];
+  __shared__ float s_top, s_low;
   const int row = blockIdx.y;
   if (sr.want[row / n_kv_heads] <= 0) return;
   const int64_t nsel = sr.nsel[row / n_kv_heads];
@@ -1857,6 +1887,16 @@ __global__ __launch_bounds__(256) void tp_hist(const float* __restrict__ vals, i
   if (c0 >= nsel) return;
   int64_t c1 = c0 + chunk;
   if (c1 > nsel) c1 = nsel;
+  const float* v = vals + (int64_t)row * stride;
+  float f[16];
+  auto load = [&](int64_t s0) {
+#pragma unroll
+    for (int x = 0; x < 16; ++x) {
+      const int64_t j = s0 + x * 256 + threadIdx.x;
+      f[x] = v[j < c1 ? j : c1 - 1];
+    }
+  };
+  load(c0);                                                 // on their way while the bins are laid out
   for (int i = threadIdx.x; i < kTpBins; i += 256) { lc[i] = 0; lm[i] = 0; }
   uint32_t kmax = 0;
   for (int c = threadIdx.x; c < (int)gridDim.x; c += 256) {
@@ -1868,22 +1908,51 @@ __global__ __launch_bounds__(256) void tp_hist(const float* __restrict__ vals, i
     const uint32_t other = __shfl_xor(kmax, o);
     if (other > kmax) kmax = other;
   }
-  if ((threadIdx.x & 63) == 0) wmax[threadIdx.x >> 6] = kmax;
+  const int lane = threadIdx.x & 63;
+  if (lane == 0) wmax[threadIdx.x >> 6] = kmax;
+  if (threadIdx.x >> 6 == 1) {
+    // The window: of up to sixteen waves of tp_rowmax, spread over the row, the lower quartile of the largest scores and
+    // the upper quartile of the smallest, waves that weigh nothing left out.  A few outliers either way do not move it, and
+    // what lies outside has the coarse steps.
+    const int pairs = 2 * (int)((nsel + chunk - 1) / chunk);
+    const int ns = pairs < 16 ? pairs : 16;
+    const float2 p = reinterpret_cast<const float2*>(t.coff)[(int64_t)row * 1024 + (lane < ns ? lane : 0) * pairs / ns];
+    float most = p.x;
+#pragma unroll
+    for (int o = 8; o >= 1; o >>= 1) most = fmaxf(most, __shfl_xor(most, o));
+    most = __shfl(most, 0);                                 // (lanes from 16 on hold pair 0 again)
+    const uint64_t counts = __ballot(lane < ns && p.x > most - span);
+    const int quarter = __popcll(counts) / 4;
+    int below = 0, over = 0;
+    for (uint64_t left = counts; left != 0; left &= left - 1) {
+      const int i = __builtin_ctzll(left);
+      const float oh = __int_as_float(__builtin_amdgcn_readlane(__float_as_int(p.x), i));
+      const float ol = __int_as_float(__builtin_amdgcn_readlane(__float_as_int(p.y), i));
+      below += oh < p.x || (oh == p.x && i < lane);
+      over += ol > p.y || (ol == p.y && i < lane);
+    }
+    if (lane == 0) { s_top = -INFINITY; s_low = INFINITY; }
+    __builtin_amdgcn_wave_barrier();
+    if ((counts >> lane & 1) && below == quarter) s_top = p.x;
+    if ((counts >> lane & 1) && over == quarter) s_low = p.y;
+  }
   __syncthreads();
   for (int x = 0; x < 4; ++x) if (wmax[x] > kmax) kmax = wmax[x];
-  if (blockIdx.x == 0 && threadIdx.x == 0) t.prow[4 * row] = kmax;
   const float m = key_to_float(kmax) * sm_scale;
-  const TpBin bin_of{m, sm_scale};
-  const float* v = vals + (int64_t)row * stride;
+  const float per = (float)kTpFine / (s_top - s_low);
+  const bool window = s_top > s_low && per < INFINITY;
+  const TpBin bin_of{m, sm_scale, window ? s_top : 0.0f, window ? per : 0.0f};
+  if (blockIdx.x == 0 && threadIdx.x == 0) {
+    t.prow[4 * row] = kmax;
+    reinterpret_cast<float2*>(t.pstate)[4 * row + 1] = float2{bin_of.top, bin_of.per_unit};
+  }
   for (int64_t s0 = c0; s0 < c1; s0 += 4096) {
-    uint32_t key[16];
-    bool valid[16];
-    load_tile_keys(v, s0, c1, key, valid);
+    if (s0 != c0) load(s0);
 #pragma unroll
     for (int x = 0; x < 16; ++x)
-      if (valid[x]) {
-        const uint64_t w = tp_weight(key_to_float(key[x]) * sm_scale - m);
-        const uint32_t b = bin_of(key[x]);
+      if (s0 + x * 256 + threadIdx.x < c1) {
+        const uint64_t w = tp_weight(f[x] * sm_scale - m);
+        const uint32_t b = bin_of(f[x]);
         // bin 0 weighs nothing and may hold nearly the whole row: it is not counted (its slots are the row's others)
         if (b != 0) atomicAdd(&lc[b], 1u);
         if (w) atomicAdd(&lm[b], (unsigned long long)w);
@@ -1925,49 +1994,70 @@ __global__ __launch_bounds__(256) void tp_collect(const float* __restrict__ vals
                                                   int n_kv_heads, SelRows sr, float sm_scale, uint64_t tau_fix, bool tau_one,
                                                   uint32_t k_max, TopkWs t, uint64_t* __restrict__ mass_out) {
   __shared__ uint64_t wsum64[4];
-  __shared__ uint32_t wsum[4], s_bin;
+  __shared__ uint32_t wsum[4], s_bin, s_first[2];
   const int row = blockIdx.y;
   const bool writer = blockIdx.x == 0;
   if (sr.want[row / n_kv_heads] <= 0) {
     if (mass_out != nullptr && writer && threadIdx.x < 2) mass_out[2 * row + threadIdx.x] = 0;
     return;
   }
-  constexpr int BPT = kTpBins / 256;
-  uint32_t hc[BPT], csum = 0;
-  uint64_t hm[BPT], msum = 0;
+  collect_chunk(vals, stride, chunk, sr.nsel[row / n_kv_heads], row, t, [&](uint32_t* first, uint32_t* last) {
+    const float2 window = reinterpret_cast<const float2*>(t.pstate)[4 * row + 1];
+    const uint32_t kmax = t.prow[4 * row];
+    constexpr int BPT = kTpBins / 256;
+    uint32_t hc[BPT], csum = 0;
+    uint64_t hm[BPT], msum = 0;
 #pragma unroll
-  for (int i = 0; i < BPT; ++i) {
-    const int b = kTpBins - 1 - (BPT * threadIdx.x + i);
-    hc[i] = t.pcount[(int64_t)row * kBins12 + b];
-    hm[i] = t.pmass[(int64_t)row * kBins12 + b];
-    csum += hc[i];
-    msum += hm[i];
-  }
-  uint64_t Z;
-  uint64_t run_m = block_scan_excl_256_u64(msum, wsum64, &Z);
-  uint32_t run_c = block_scan_excl_256(csum, wsum);
-  uint64_t theta = tau_one ? Z : __umul64hi(Z, tau_fix);
-  if (theta < 1) theta = 1;
-  if (threadIdx.x == 255) hc[BPT - 1] = (uint32_t)sr.nsel[row / n_kv_heads] - (run_c + csum);     // bin 0
-#pragma unroll
-  for (int i = 0; i < BPT; ++i) {
-    const bool before = run_m < theta && run_c < k_max;
-    const bool after = run_m + hm[i] >= theta || run_c + hc[i] >= k_max;
-    if (before && after && hc[i] > 0) {
-      s_bin = (uint32_t)(kTpBins - 1 - (BPT * threadIdx.x + i));       // b*
-      if (writer) {
-        t.state[4 * row + 2] = (uint32_t)(kTpBins - 1 - (BPT * threadIdx.x + i));
-        t.pstate[4 * row] = theta - run_m;                              // weight still to reach inside the bin
-        t.prow[4 * row + 1] = k_max - run_c;                            // slots still allowed
-      }
+    for (int i = 0; i < BPT; ++i) {
+      const int b = kTpBins - 1 - (BPT * threadIdx.x + i);
+      hc[i] = t.pcount[(int64_t)row * kBins12 + b];
+      hm[i] = t.pmass[(int64_t)row * kBins12 + b];
+      csum += hc[i];
+      msum += hm[i];
     }
-    run_m += hm[i];
-    run_c += hc[i];
-  }
-  if (writer && threadIdx.x == 0 && mass_out != nullptr) { mass_out[2 * row] = theta; mass_out[2 * row + 1] = Z; }
-  __syncthreads();
-  const TpBin bin_of{key_to_float(t.prow[4 * row]) * sm_scale, sm_scale};
-  collect_chunk(vals, stride, chunk, sr.nsel[row / n_kv_heads], row, t, s_bin, bin_of);
+    uint64_t Z;
+    uint64_t run_m = block_scan_excl_256_u64(msum, wsum64, &Z);
+    uint32_t run_c = block_scan_excl_256(csum, wsum);
+    uint64_t theta = tau_one ? Z : __umul64hi(Z, tau_fix);
+    if (theta < 1) theta = 1;
+    if (threadIdx.x == 255) hc[BPT - 1] = (uint32_t)sr.nsel[row / n_kv_heads] - (run_c + csum);     // bin 0
+#pragma unroll
+    for (int i = 0; i < BPT; ++i) {
+      const bool before = run_m < theta && run_c < k_max;
+      const bool after = run_m + hm[i] >= theta || run_c + hc[i] >= k_max;
+      if (before && after && hc[i] > 0) {
+        s_bin = (uint32_t)(kTpBins - 1 - (BPT * threadIdx.x + i));       // b*
+        if (writer) {
+          t.pstate[4 * row] = theta - run_m;                              // weight still to reach inside the bin
+          t.prow[4 * row + 1] = k_max - run_c;                            // slots still allowed
+        }
+      }
+      run_m += hm[i];
+      run_c += hc[i];
+    }
+    if (writer && threadIdx.x == 0 && mass_out != nullptr) { mass_out[2 * row] = theta; mass_out[2 * row + 1] = Z; }
+    __syncthreads();
+    const TpBin bin_of{key_to_float(kmax) * sm_scale, sm_scale, window.x, window.y};
+    // the smallest key of the bin (wave 0) and of the bins above it (wave 1), 64 keys at a time: the pass over the row and
+    // the resolve stage then compare keys and compute no bins
+    const int lane = threadIdx.x & 63, w = threadIdx.x >> 6;
+    if (w < 2) {
+      const uint32_t bin = s_bin + w;
+      uint32_t below = order_key(-INFINITY) - 1, found = kmax + 1;      // the row maximum lies in the top bin
+      while (found - below > 1) {
+        const uint32_t step = (found - below + 63) / 64, key = below + step * (lane + 1);
+        const bool yes = key - below >= found - below || bin_of(key_to_float(key)) >= bin;
+        const int at = __builtin_ctzll(__builtin_amdgcn_ballot_w64(yes) | 1ull << 63);
+        if (step * (at + 1) < found - below) found = below + step * (at + 1);
+        below += step * at;
+      }
+      if (lane == 0) s_first[w] = bin == 0 ? 0u : found;
+    }
+    __syncthreads();
+    *first = s_first[0];
+    *last = s_first[1] - 1;
+    if (writer && threadIdx.x == 0) { t.state[4 * row + 2] = *first; t.state[4 * row + 3] = *last; }
+  });
 }
 
 // no resident slot anywhere: only the per-row (Theta, Z) report has to be cleared
@@ -1993,6 +2083,8 @@ __device__ __forceinline__ uint64_t block_scan_excl_1024_u64(uint64_t v, uint64_
   return base + inc - v;
 }
 
+constexpr uint32_t kDirectRank = 128;   // keys ranked against each other: 1.5 us; a round of digits takes 2
+
 // One workgroup per row: finishes the walk inside bin b* (digits of the distance from the bin's smallest key, then the
 // group of equal keys, whose members all weigh the same) and builds the chunk offsets for the ordered emit.
 __global__ __launch_bounds__(1024) void tp_resolve(int64_t chunk, int nchunks, int n_kv_heads, SelRows sr, float sm_scale,
@@ -2005,11 +2097,10 @@ __global__ __launch_bounds__(1024) void tp_resolve(int64_t chunk, int nchunks, i
   __shared__ uint2 lc[kResolveLds];
   const int row = blockIdx.x;
   if (sr.want[row / n_kv_heads] <= 0) return;
-  const uint32_t bin = t.state[4 * row + 2];
+  const uint32_t last = t.state[4 * row + 3];               // (the lists hold no key below the bin)
   const uint2* cand = t.cand + (int64_t)row * t.row_entries;
   const int tid = threadIdx.x, lane = tid & 63, wv = tid >> 6;
   const float m = key_to_float(t.prow[4 * row]) * sm_scale;
-  const TpBin bin_of{m, sm_scale};
   uint32_t krem = t.prow[4 * row + 1];
   uint64_t mrem = t.pstate[4 * row];
   cnt[tid] = tid < nchunks ? t.ncand[(int64_t)row * kMaxChunks + tid] : 0;
@@ -2017,8 +2108,27 @@ __global__ __launch_bounds__(1024) void tp_resolve(int64_t chunk, int nchunks, i
   __syncthreads();
   // f(key, slot, hit) over every list entry of the row, hit = the entry exists and lies in bin b*; f is called by all lanes
   // of a wave together.  Each wave takes 8 chunks per step and fetches the first 128 entries of all of them in one batch
-  // of loads, so a step costs one memory round trip; longer lists follow, 8 loads in flight.
+  // of loads, so a step costs one memory round trip; longer lists follow, 8 loads in flight.  Rows of up to 8 chunks: the
+  // waves share a chunk's list.
+  auto stretch = [&](auto&& f, int c, uint32_t from, uint32_t step) {
+    const uint32_t mc = cnt[c];
+    for (uint32_t i0 = from + lane; i0 < mc + lane; i0 += step) {
+      uint2 x[8];
+#pragma unroll
+      for (int v = 0; v < 8; ++v) {
+        x[v] = uint2{0, 0};
+        if (i0 + 64 * v < mc) x[v] = cand[(int64_t)c * chunk + i0 + 64 * v];
+      }
+#pragma unroll
+      for (int v = 0; v < 8; ++v) f(x[v].x, x[v].y, i0 + 64 * v < mc && x[v].x <= last);
+    }
+  };
   auto sweep = [&](auto&& f) {
+    if (nchunks <= 8) {
+      const int parts = 16 / nchunks;
+      if (wv < parts * nchunks) stretch(f, wv % nchunks, 512u * (uint32_t)(wv / nchunks), 512u * (uint32_t)parts);
+      return;
+    }
     for (int c0 = 0; c0 < nchunks; c0 += 128) {
       uint2 ent[16];
       bool has[16];
@@ -2031,22 +2141,10 @@ __global__ __launch_bounds__(1024) void tp_resolve(int64_t chunk, int nchunks, i
         if (has[u]) ent[u] = cand[(int64_t)c * chunk + i];
       }
 #pragma unroll
-      for (int u = 0; u < 16; ++u) f(ent[u].x, ent[u].y, has[u] && bin_of(ent[u].x) == bin);
+      for (int u = 0; u < 16; ++u) f(ent[u].x, ent[u].y, has[u] && ent[u].x <= last);
 #pragma unroll 1
-      for (int u = 0; u < 8; ++u) {
-        const int c = c0 + u * 16 + wv;
-        const uint32_t mc = c < nchunks ? cnt[c] : 0;
-        for (uint32_t i0 = 128 + lane; i0 < mc + lane; i0 += 512) {
-          uint2 x[8];
-#pragma unroll
-          for (int v = 0; v < 8; ++v) {
-            x[v] = uint2{0, 0};
-            if (i0 + 64 * v < mc) x[v] = cand[(int64_t)c * chunk + i0 + 64 * v];
-          }
-#pragma unroll
-          for (int v = 0; v < 8; ++v) f(x[v].x, x[v].y, i0 + 64 * v < mc && bin_of(x[v].x) == bin);
-        }
-      }
+      for (int u = 0; u < 8; ++u)
+        if (c0 + u * 16 + wv < nchunks) stretch(f, c0 + u * 16 + wv, 128u, 512u);
     }
   };
   uint32_t lo = 0xffffffffu, hi = 0;                        // smallest and largest key of the bin
@@ -2076,10 +2174,53 @@ __global__ __launch_bounds__(1024) void tp_resolve(int64_t chunk, int nchunks, i
       sweep(f);
     }
   };
-  // the distances from lo, 10 bits at a time from the top: pd = the digits found, left = the bits below them
   uint32_t cnt_eq = 0, pd = 0;
   int left = 32 - __clz((int)((hi - lo) | 1u));             // 1 .. 32
   bool first = true;
+  if (nst <= kDirectRank) {
+    // a few keys: each is compared with all others, eight threads to a key, instead of two to four rounds of digits
+    const uint32_t i = tid & (kDirectRank - 1), share = tid / kDirectRank, each = kDirectRank / (1024 / kDirectRank);
+    if (tid < (int)kDirectRank) {
+      h[tid] = 0;
+      e[tid] = 0;
+      hm[tid] = 0;
+      hm[kDirectRank + tid] = i < nst ? tp_weight(key_to_float(lc[i].x) * sm_scale - m) : 0;
+    }
+    __syncthreads();
+    if (i < nst) {
+      const uint32_t ki = lc[i].x;
+      uint32_t gt = 0, eq = 0;
+      uint64_t over = 0;
+      for (uint32_t j = share * each; j < (share + 1) * each && j < nst; ++j) {
+        const uint32_t kj = lc[j].x;
+        gt += kj > ki;
+        eq += kj == ki;
+        over += kj > ki ? hm[kDirectRank + j] : 0;
+      }
+      if (gt) atomicAdd(&h[i], gt);
+      if (eq) atomicAdd(&e[i], eq);
+      if (over) atomicAdd(&hm[i], (unsigned long long)over);
+    }
+    __syncthreads();
+    if (tid < (int)nst) {
+      const uint32_t run_c = h[tid], eq = e[tid];
+      const uint64_t run_m = hm[tid];
+      if (run_m < mrem && run_c < krem && (run_m + hm[kDirectRank + tid] * eq >= mrem || run_c + eq >= krem)) {
+        s_digit = lc[tid].x - lo;                           // equal keys write equal values
+        s_eq = eq;
+        s_mrem = mrem - run_m;
+        s_krem = krem - run_c;
+      }
+    }
+    __syncthreads();
+    pd = s_digit;
+    cnt_eq = s_eq;
+    mrem = s_mrem;
+    krem = s_krem;
+    left = 0;
+    __syncthreads();
+  }
+  // the distances from lo, 10 bits at a time from the top: pd = the digits found, left = the bits below them
   while (left > 0) {                                        // uniform over the workgroup
     const int width = left > 10 ? 10 : left, ns = left - width;
     h[tid] = 0;
@@ -2159,8 +2300,9 @@ int32_t launch_topp(const Layout& L, const float* sel, const NRes& nr, int64_t n
   const uint64_t tau_fix = tau_one ? 0 : (uint64_t)ldexp(tau, 64);
   if (nmax > 0) {
     dim3 gh((unsigned)((nchunks + 1) / 2), (unsigned)L.rows);
-    tp_rowmax<<<gh, 256, 0, st>>>(sel, L.cap, 2 * chunk, L.n_kv_heads, sr, t);
-    tp_hist<<<gh, 256, 0, st>>>(sel, L.cap, 2 * chunk, L.n_kv_heads, sr, sm_scale, t);
+    const float span = 44.3614196f / sm_scale;               // 64 ln 2 in scores: lower ones weigh nothing
+    tp_rowmax<<<gh, 256, 0, st>>>(sel, L.cap, 2 * chunk, L.n_kv_heads, sr, span, t);
+    tp_hist<<<gh, 256, 0, st>>>(sel, L.cap, 2 * chunk, L.n_kv_heads, sr, sm_scale, span, t);
     tp_collect<<<g, 256, 0, st>>>(sel, L.cap, chunk, L.n_kv_heads, sr, sm_scale, tau_fix, tau_one, (uint32_t)k_max, t, mass_opt);
     tp_resolve<<<L.rows, 1024, 0, st>>>(chunk, nchunks, L.n_kv_heads, sr, sm_scale, t);
   } else if (mass_opt != nullptr) {

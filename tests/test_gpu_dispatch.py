@@ -356,7 +356,7 @@ def test_evict_at_chunk_edges(B, bits, gs, n, M, protect, kind, spare):
 @pytest.mark.parametrize("kind", ["far", "masked", "steps", "close"])
 @pytest.mark.parametrize("n", [4096, 4097, 8193, 40961])
 def test_topp_at_the_edges_of_its_bins(B, oracle, kind, n):
-    """hca_topp bins by weight, 32 bins per factor of two down to 2^-64: rows whose slots nearly all weigh nothing, lie
+    """hca_topp bins by weight down to 2^-64 and by score within a window: rows whose slots nearly all weigh nothing, lie
     exactly on bin edges, are masked with -inf or the type's lowest value, or share one bin."""
     rng = np.random.default_rng(n)
     cap, R = n + 5, 3
@@ -368,7 +368,7 @@ def test_topp_at_the_edges_of_its_bins(B, oracle, kind, n):
         elif kind == "masked":
             x = rng.standard_normal(n).astype(np.float32) * 3
             x[rng.random(n) < 0.5] = -np.inf if r else np.finfo(np.float32).min
-        elif kind == "steps":                                # multiples of the bin width in logit, ln 2 / 32
+        elif kind == "steps":                                # multiples of a power of two's 32nd part in logit
             x = (rng.integers(0, 2100, n) * (-np.log(2) / 32)).astype(np.float32)
         else:
             x = (5 + rng.random(n) * 1e-5).astype(np.float32)
@@ -386,6 +386,70 @@ def test_topp_at_the_edges_of_its_bins(B, oracle, kind, n):
         assert np.array_equal(mass.cpu().numpy().view(np.uint64), omass) and np.array_equal(count.cpu().numpy(), ocount)
         for r in range(R):
             assert np.array_equal(idx[r, :ocount[r]].cpu().numpy(), oidx[r, :ocount[r]]), (r, tau)
+
+
+def _spread_scores(kind, rows, n, gen):
+    """Rows whose slots crowd in a narrow band, or do not, with and without what lies far outside of it."""
+    x = torch.randn(rows, n, generator=gen, device="cuda")
+    at = torch.arange(n, device="cuda")
+    if kind == "flat":
+        x = x * 0.1
+    elif kind == "flat, sink and low":
+        x = x * 1e-3
+        x[:, 5], x[:, 7] = 120.0, -300.0
+    elif kind == "flat, half masked":
+        x = torch.where(torch.rand(rows, n, generator=gen, device="cuda") < 0.5, torch.finfo(torch.float32).min, x * 0.1)
+    elif kind == "flat, tail masked":
+        x = torch.where(at >= n // 2, -torch.inf, x * 1e-3)
+    elif kind == "far from zero":
+        x = 50 + x * 0.01
+    elif kind == "drift":
+        x = x * 5 + at * (60.0 / n)
+    elif kind == "two bands":
+        x = torch.where(at < n // 100, x * 3 + 60, x)
+    else:
+        x = x * 11
+    return x
+
+
+@pytest.mark.parametrize("kind", ["flat", "flat, sink and low", "flat, half masked", "flat, tail masked", "far from zero",
+                                  "drift", "two bands", "normal"])
+@pytest.mark.parametrize("n", [65, 300, 9000, 140001])
+def test_topp_whatever_the_spread(B, oracle, kind, n):
+    """The window of the fine bins, found from two or from sixteen waves of a row; bins resolved by direct comparison (up to 128
+    keys), from LDS and from the lists; lists shared by the waves (up to eight chunks) and not."""
+    R, cap = 3, n + 2
+    sel = torch.full((R, cap), 1e30, device="cuda")
+    sel[:, :n] = _spread_scores(kind, R, n, torch.Generator(device="cuda").manual_seed(n))
+    lens = [n, n - 1, max(1, n // 2)]
+    shape = B.make_shape(3, 1, 1, cap)
+    host = sel.cpu().numpy()
+    for tau, k_max in ((0.5, n), (0.9, n), (1.0, n), (0.9, max(1, n // 30))):
+        idx = torch.full((R, k_max), -9, dtype=torch.int32, device="cuda")
+        count = torch.full((R,), -9, dtype=torch.int32, device="cuda")
+        mass = torch.full((R, 2), 7, dtype=torch.int64, device="cuda")
+        ws = torch.full((B.hca_workspace_bytes(shape, k_max, 1),), 255, dtype=torch.uint8, device="cuda")
+        B.hca_topp(shape, sel, lens, 0.0884, tau, k_max, idx, count, mass, ws)
+        oidx, ocount, _, omass = oracle.topp(host, lens, 0.0884, tau, k_max)
+        assert np.array_equal(mass.cpu().numpy().view(np.uint64), omass) and np.array_equal(count.cpu().numpy(), ocount)
+        for r in range(R):
+            assert np.array_equal(idx[r, :ocount[r]].cpu().numpy(), oidx[r, :ocount[r]]), (r, tau)
+
+
+@pytest.mark.parametrize("kind", ["flat", "flat, sink and low", "flat, half masked", "flat, tail masked"])
+def test_topp_time_does_not_hang_on_the_spread(B, kind):
+    """A row of nearly equal weights has to be resolved as finely as any other: its bin of interest must not hold most of the
+    row, which one workgroup would then go through alone (five times the call).  Allowed: twice the time of normal rows."""
+    rows, n, k = 8, 131072, 4096
+    shape = B.make_shape(1, rows, rows, n)
+    idx = torch.zeros(rows, k, dtype=torch.int32, device="cuda")
+    count = torch.zeros(rows, dtype=torch.int32, device="cuda")
+    ws = torch.empty(B.hca_workspace_bytes(shape, k, 1), dtype=torch.uint8, device="cuda")
+    took = []
+    for which in ("normal", kind):
+        sel = _spread_scores(which, rows, n, torch.Generator(device="cuda").manual_seed(3))
+        took.append(_passes_us(lambda: B.hca_topp(shape, sel, [n], 0.0884, 0.9, k, idx, count, None, ws)))
+    assert took[1] < 2 * took[0], f"{took[0]:.0f} us for normal rows, {took[1]:.0f} us"
 
 
 @pytest.mark.parametrize("gqa,groups,c,n", [(4, 32, 8192, 12288), (4, 32, 300, 12289), (4, 64, 513, 16384), (4, 32, 1024, 16385),
