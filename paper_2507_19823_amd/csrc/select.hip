@@ -802,13 +802,18 @@ __device__ __forceinline__ float key_to_float(uint32_t key) {
 // ---------------------------------------------------------------------------------------
 // Top-k of short rows in one launch: a 1024-thread workgroup holds a whole row of scores in registers, KPT values per
 // thread, wave w owning the KPT * 64 consecutive slots from w * KPT * 64 on (a wave's x-th load is 64 of them, so slot
-// order is (wave, x, lane)).  hca_topk per call, 8 rows of 4 Ki / 16 Ki / 32 Ki slots: 10 / 12 / 20 us, against 28 / 34 /
-// 37 us for the six launches over the whole chip; with the scan in front (hca_score_topk) 13 / 19 / 28 against 39 / 39 /
-// 41 us for sample, threshold, selecting scan, selection and its fall-back pair.
-//   1. smallest and largest value; 4096 bins spread evenly between them, so that neither the counters are fought over
-//      nor most of them stay empty (the keys of one row share their exponent bits).  Binning by value is monotone in
-//      the key - a difference, a product and a truncation - which is all the selection needs.  Rows with infinities or
-//      NaNs, or too wide for a finite scale, are binned by the key's leading 12 bits.
+// order is (wave, x, lane)).  hca_topk per call, 8 rows of 4 Ki / 16 Ki / 40 Ki slots, 1024 to select: 8 / 12 / 23 us, against
+// 31 / 35 / 39 us for the six launches over the whole chip; with the scan in front (hca_score_topk), 4 Ki / 16 Ki / 32 Ki: 13 / 19 / 28 against
+// 39 / 39 / 41 us for sample, threshold, selecting scan, selection and its fall-back pair.
+//   1. smallest and largest value per wave; 4096 bins spread evenly over a window in which most of the row lies, so that
+//      neither the counters are fought over nor most of them stay empty (the keys of one row share their exponent bits).
+//      The window reaches a quarter of its width beyond the fourth smallest and the fourth largest of the waves' extremes:
+//      a few values far outside - a sink, a few masked slots - fall into the end bins and do not move it (a window from
+//      the smallest to the largest value took 89 us for 8 rows of 40 Ki slots with one such value, 39 over the whole
+//      chip).  Where masked slots are everywhere the smallest values are taken again without them.  Binning by value is
+//      monotone in the key - a difference, a product, a clamp and a truncation - which is all the selection needs.  Rows
+//      with +inf or NaNs, or too wide for a finite scale, are binned by the key's leading 12 bits.  The lowest bin
+//      is not counted, it holds the row's others.
 //   2. the bin that holds the want-th largest key; its keys are ranked against each other when there are at most 512,
 //      else by radix levels over the distance from the bin's smallest key (ties, one far outlier).
 //   3. the ordered emit, positions by ballot:  selected(j) = key_j > T  or  (key_j == T and fewer than r_eq equals
@@ -824,12 +829,34 @@ struct RowSelectFused {      // what hca_score_topk keeps beside the result (nul
   int32_t nchunks;
 };
 
+// f(turn) for the fifteen other lanes of a row of sixteen, turn(v) = that lane's v; and what the row's lanes hold at most
+// and at least, on every lane.
+template <int N>
+struct Row16 {
+  __device__ __forceinline__ float operator()(float v) const {
+    return __int_as_float(__builtin_amdgcn_update_dpp(0, __float_as_int(v), 0x120 + N, 0xf, 0xf, false));
+  }
+};
+template <int N = 1, typename F>
+__device__ __forceinline__ void row16_each(F&& f) {
+  f(Row16<N>());
+  if constexpr (N < 15) row16_each<N + 1>(f);
+}
+__device__ __forceinline__ float row16_min(float v) {
+  v = fminf(v, Row16<8>()(v));
+  v = fminf(v, Row16<4>()(v));
+  v = fminf(v, Row16<2>()(v));
+  return fminf(v, Row16<1>()(v));
+}
+__device__ __forceinline__ float row16_max(float v) { return -row16_min(-v); }
+
 template <int KPT>
 __global__ __launch_bounds__(1024) void tk_row_select(const float* __restrict__ vals, int64_t stride, int n_kv_heads,
                                                       SelRows sr, int32_t k, int32_t* __restrict__ idx,
                                                       int32_t* __restrict__ count, RowSelectFused fu) {
-  __shared__ uint32_t h[kBins12], list[kRankMax], wsum[16], wlo[16], whi[16], wspecial[16];
-  __shared__ uint32_t s_bin, s_rem, s_cb, s_n, s_T, s_req;
+  __shared__ uint32_t h[kBins12], list[kRankMax], wsum[16], wlo[16], whi[16], wplain[16];
+  __shared__ uint32_t s_bin, s_rem, s_cb, s_n, s_T, s_req, s_flags;
+  __shared__ __align__(16) float s_win[8];
   const int row = blockIdx.x;
   const int tid = threadIdx.x, lane = tid & 63, wv = __builtin_amdgcn_readfirstlane(tid >> 6);
   const int64_t want64 = sr.want[row / n_kv_heads];
@@ -867,43 +894,90 @@ __global__ __launch_bounds__(1024) void tk_row_select(const float* __restrict__ 
   for (int i = tid; i < kBins12; i += 1024) h[i] = 0;
   if (tid == 0) s_n = 0;
   float vlo = INFINITY, vhi = -INFINITY;
-  uint32_t mag = 0;                                         // largest magnitude bits: infinities and NaNs show up here
+  bool plain = true;                                        // no NaN and no +infinity
 #pragma unroll
   for (int x = 0; x < KPT; ++x) {
     vlo = fminf(vlo, f[x]);
     vhi = fmaxf(vhi, f[x]);
-    const uint32_t a = __float_as_uint(f[x]) & 0x7fffffffu;
-    mag = a > mag ? a : mag;
+    plain = plain && f[x] < INFINITY;
   }
 #pragma unroll
   for (int o = 32; o >= 1; o >>= 1) {
     vlo = fminf(vlo, __shfl_xor(vlo, o));
     vhi = fmaxf(vhi, __shfl_xor(vhi, o));
-    const uint32_t a = __shfl_xor(mag, o);
-    mag = a > mag ? a : mag;
   }
-  if (lane == 0) { wlo[wv] = __float_as_uint(vlo); whi[wv] = __float_as_uint(vhi); wspecial[wv] = mag; }
+  plain = __builtin_amdgcn_ballot_w64(!plain) == 0;
+  if (lane == 0) { wlo[wv] = __float_as_uint(vlo); whi[wv] = __float_as_uint(vhi); wplain[wv] = plain; }
   __syncthreads();
-  vlo = __uint_as_float(wlo[lane & 15]);
-  vhi = __uint_as_float(whi[lane & 15]);
-  mag = wspecial[lane & 15];
-#pragma unroll
-  for (int o = 8; o >= 1; o >>= 1) {
-    vlo = fminf(vlo, __shfl_xor(vlo, o));
-    vhi = fmaxf(vhi, __shfl_xor(vhi, o));
-    const uint32_t a = __shfl_xor(mag, o);
-    mag = a > mag ? a : mag;
+  // the window of the bins.  lo4, hi4: the fourth smallest and the fourth largest extreme of the waves with slots
+  auto window = [&](float lo4, float hi4) {
+    const float edge = lo4 < hi4 ? 0.25f * (hi4 - lo4) : INFINITY;
+    const float from = fmaxf(vlo, lo4 - edge);
+    return float2{from, 4095.0f / (fminf(vhi, hi4 + edge) - from)};
+  };
+  if (wv == 0) {
+    const uint32_t waves = (n + KPT * 64 - 1) / (KPT * 64), i = (uint32_t)(lane & 15);
+    const uint32_t fourth = waves > 3 ? 3 : waves - 1;
+    vlo = i < waves ? __uint_as_float(wlo[i]) : INFINITY;
+    vhi = i < waves ? __uint_as_float(whi[i]) : -INFINITY;
+    plain = i >= waves || wplain[i] != 0;
+    uint32_t below = 0, over = 0;
+    row16_each([&](auto turn) {
+      below += turn(vlo) < vlo;
+      over += turn(vhi) > vhi;
+    });
+    float lo4 = i < waves && below <= fourth ? vlo : -INFINITY;      // the largest of those with at most three before them
+    float hi4 = i < waves && over <= fourth ? vhi : INFINITY;
+    lo4 = row16_max(lo4);
+    hi4 = row16_min(hi4);
+    vlo = row16_min(vlo);
+    // how much the waves' largest values differ, those left out that hold nothing but the row's smallest value
+    const float apart = hi4 - row16_min(vhi > vlo ? vhi : INFINITY);
+    vhi = row16_max(vhi);
+    plain = __builtin_amdgcn_ballot_w64(!plain) == 0;
+    const float2 w = window(lo4, hi4);
+    if (lane == 0) {
+      // far more below the top than that: masked slots in most waves, say
+      const bool masked = plain && apart > 0.0f && hi4 - lo4 > 512.0f * apart;
+      s_win[0] = vlo; s_win[1] = vhi; s_win[2] = w.x; s_win[3] = w.y;
+      s_win[4] = hi4; s_win[5] = hi4 - 256.0f * apart;
+      s_flags = (plain ? 1u : 0u) | (masked ? 2u : 0u);
+    }
   }
+  __syncthreads();
+  vlo = s_win[0];
+  vhi = s_win[1];
+  plain = (s_flags & 1u) != 0;
+  float from = s_win[2], scale = s_win[3];
   forget();
-  const bool finite = mag < 0x7f800000u;
-  const float scale = 4095.0f / (vhi - vlo);
-  const bool by_value = finite && vhi - vlo < INFINITY && scale < INFINITY;
-  // the bin that holds the rem-th largest entry of the counters in h: published to s_bin / s_rem / s_cb
-  auto find_bin = [&](uint32_t rem) {
+  if (s_flags & 2u) {                                       // the smallest value again, without those
+    const float cut = s_win[5];
+    float m = INFINITY;
+#pragma unroll
+    for (int x = 0; x < KPT; ++x) m = f[x] >= cut ? fminf(m, f[x]) : m;
+#pragma unroll
+    for (int o = 32; o >= 1; o >>= 1) m = fminf(m, __shfl_xor(m, o));
+    if (lane == 0) wlo[wv] = __float_as_uint(m);
+    __syncthreads();
+    for (int x = 0; x < 16; ++x) m = fminf(m, __uint_as_float(wlo[x]));
+    const float2 w = window(m, s_win[4]);
+    from = w.x;
+    scale = w.y;
+    forget();
+  }
+  const bool by_value = plain && scale > 0.0f && scale < INFINITY;
+  if (plain) {                                              // past the row's end: the lowest bin, below every threshold
+#pragma unroll
+    for (int x = 0; x < KPT; ++x) f[x] = s0 + x * 64 < n ? f[x] : -INFINITY;
+  }
+  // the bin that holds the rem-th largest entry of the counters in h: published to s_bin / s_rem / s_cb.  all: the
+  // number of entries, of which the lowest bin's are not counted (0: it is counted)
+  auto find_bin = [&](uint32_t rem, uint32_t all) {
     uint32_t hb[4], sum = 0;
 #pragma unroll
     for (int i = 0; i < 4; ++i) { hb[i] = h[kBins12 - 1 - (4 * tid + i)]; sum += hb[i]; }
     uint32_t running = block_scan_excl_1024(sum, wsum);
+    if (tid == 1023 && all != 0) hb[3] = all - (running + sum);
 #pragma unroll
     for (int i = 0; i < 4; ++i) {
       if (running < rem && rem <= running + hb[i]) {
@@ -916,17 +990,27 @@ __global__ __launch_bounds__(1024) void tk_row_select(const float* __restrict__ 
     __syncthreads();
   };
   uint32_t T, req;
-  if (finite && vlo == vhi) {                               // all equal: the want lowest slots
+  if (plain && vlo == vhi) {                               // all equal: the want lowest slots
     T = order_key(vlo);
     req = want;
   } else {
     auto live = [&](int x) { return s0 + x * 64 < n; };
-    auto bin_of = [&](int x) { return by_value ? (uint32_t)((f[x] - vlo) * scale) : order_key(f[x]) >> 20; };
+    auto bin_of = [&](int x) {
+      return by_value ? (uint32_t)__builtin_amdgcn_fmed3f((f[x] - from) * scale, 0.0f, 4095.0f) : order_key(f[x]) >> 20;
+    };
+    if (by_value) {
 #pragma unroll
-    for (int x = 0; x < KPT; ++x)
-      if (live(x)) atomicAdd(&h[bin_of(x)], 1u);
+      for (int x = 0; x < KPT; ++x) {
+        const uint32_t b = bin_of(x);
+        if (b != 0) atomicAdd(&h[b], 1u);
+      }
+    } else {
+#pragma unroll
+      for (int x = 0; x < KPT; ++x)
+        if (live(x)) atomicAdd(&h[bin_of(x)], 1u);
+    }
     __syncthreads();
-    find_bin(want);
+    find_bin(want, by_value ? n : 0u);
     forget();
     const uint32_t b0 = s_bin;
     uint32_t rem = s_rem, cb = s_cb;
@@ -967,7 +1051,7 @@ __global__ __launch_bounds__(1024) void tk_row_select(const float* __restrict__ 
           lds_count(h, (d >> ns) & ((1u << width) - 1u), live(x) && bin_of(x) == b0 && (first || (d >> left) == pd), true);
         }
         __syncthreads();
-        find_bin(rem);
+        find_bin(rem, 0);
         pd = first ? s_bin : ((pd << width) | s_bin);
         rem = s_rem;
         cb = s_cb;
@@ -1042,11 +1126,9 @@ __global__ __launch_bounds__(1024) void tk_row_select(const float* __restrict__ 
       pg += (uint32_t)__popcll(mg);
     }
   };
-  if (finite) {
-    // finite values compare like their keys (the two zeros are equal both ways); past the row's end: -inf
-    const float tf = key_to_float(T);
-#pragma unroll
-    for (int x = 0; x < KPT; ++x) f[x] = s0 + x * 64 < n ? f[x] : -INFINITY;
+  const float tf = key_to_float(T);
+  if (plain && tf > -INFINITY) {
+    // values compare like their keys (the two zeros are equal both ways); past the row's end: -inf
     emit([&](int x) { return f[x] > tf; }, [&](int x) { return f[x] == tf; });
   } else {
     emit([&](int x) { return s0 + x * 64 < n && order_key(f[x]) > T; },

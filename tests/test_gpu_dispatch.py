@@ -144,6 +144,38 @@ def test_topk_at_the_edges_of_the_one_launch_form(B, kind, n):
             assert np.all(got[b, want:] == -7)
 
 
+@pytest.mark.parametrize("n", [4096, 16384, 40960])
+@pytest.mark.parametrize("kind", ["sink", "low", "sinks and lows", "masked", "tail masked", "-inf"])
+def test_a_few_far_scores_do_not_slow_the_short_rows(B, kind, n):
+    """hca_topk of rows in one workgroup: values far outside of the others, or masked slots, must not widen the bins until the
+    rest of the row shares one of them (two to four times the call).  Allowed: 1.7 times the time of normal rows, and the
+    result is the stable sort's."""
+    rows, k = 8, 1024
+    gen = torch.Generator(device="cuda").manual_seed(n)
+    normal = torch.randn(rows, n, generator=gen, device="cuda") * 10
+    far = normal.clone()
+    if kind in ("sink", "sinks and lows"):
+        far[:, 17] = 1e6
+    if kind in ("low", "sinks and lows"):
+        far[:, n // 2] = -1e6
+    if kind == "sinks and lows":
+        far[:, n - 5], far[:, 3] = 1e4, -1e9
+    if kind == "masked":
+        far[torch.rand(rows, n, generator=gen, device="cuda") < 0.5] = torch.finfo(torch.float32).min
+    if kind == "tail masked":
+        far[:, n // 2:] = torch.finfo(torch.float32).min
+    if kind == "-inf":
+        far[torch.rand(rows, n, generator=gen, device="cuda") < 0.3] = -torch.inf
+    shape = B.make_shape(1, rows, rows, n)
+    idx = torch.zeros(rows, k, dtype=torch.int32, device="cuda")
+    count = torch.zeros(rows, dtype=torch.int32, device="cuda")
+    ws = torch.empty(B.hca_workspace_bytes(shape, k, 1), dtype=torch.uint8, device="cuda")
+    took = [_passes_us(lambda: B.hca_topk(shape, sel, [n], k, idx, count, ws)) for sel in (normal, far)]
+    ref = torch.sort(far, dim=1, descending=True, stable=True).indices[:, :k].sort(dim=1).values.int()
+    assert torch.equal(idx, ref)
+    assert took[1] < 1.7 * took[0], f"{took[0]:.1f} us for normal rows, {took[1]:.1f} us"
+
+
 @pytest.mark.parametrize("bits,gs", [(4, 32), (2, 64)])
 @pytest.mark.parametrize("n", [40960, 40961])
 def test_score_topk_on_both_sides_of_the_short_row_line(B, oracle, bits, gs, n):
