@@ -445,10 +445,6 @@ __global__ __launch_bounds__(512) __attribute__((amdgpu_waves_per_eu(4))) void v
 // the queue.
 // 64 Ki tokens x 8 KV heads against 256 centroids: 0.31 ms (0.99 in the vector form), 64 centroids: 0.17 ms (0.25).
 constexpr int kAsCodewords = 256;
-// Taken from this many (token, KV head, group, centroid) combinations on: below, the launch has too few workgroups and
-// each takes its 25 - 43 us whatever it holds; there the vector form is level (2048 tokens x 8 KV heads against 256
-// centroids: 41 us vector, 43 here; 4096: 69 and 43).  Up to 32 centroids the vector form is ahead at every size.
-constexpr int64_t kAssignMfmaMinWork = (int64_t)1 << 27;
 
 template <int CTRL>
 __device__ __forceinline__ float dpp_max(float v) {
@@ -651,8 +647,7 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(4))) void v
 // share a group, each takes a part of its centroids and spreads it over its lanes (lane, lane + 64, ...; four distances
 // in flight per lane); the lanes' candidates, then the waves', are reduced by (distance, index): the smaller distance
 // wins, equal distances go to the lower index - the same winner as the ascending scan with a strict comparison.
-// Bound by the latency of a lane's chain of loads: with all four waves on one group (from 1024 centroids on, where a
-// single wave would take four or more rounds of four loads) the append of one token x 8 KV heads takes 8 us at 8192
+// Bound by the latency of a lane's chain of loads: with all four waves on one group the append of one token x 8 KV heads takes 8 us at 8192
 // centroids instead of 25.
 template <int DBAR, bool WIDE, int SPLIT>
 __global__ __launch_bounds__(256) void vq_assign_small_kernel(int g, int c, int n_kv_heads, int64_t cap,
@@ -1099,6 +1094,37 @@ __global__ __launch_bounds__(256) void vq_export_wide_kernel(int g, int64_t cap,
   out[(int64_t)row * cap * g + gid] = pcache[vq_wide_at(g, vq_tiles(cap), row, slot, i)];
 }
 
+// Whether at most 256 centroids go to vq_assign_small_c_kernel.  It works on whole sets of 2, 4 or 8 tiles, and each of its
+// workgroups takes its 25 - 43 us whatever it holds, so it wants full tiles and a launch that fills the chip several times
+// over; the vector form's time follows the work alone, and falls with the channels per centroid.  Measured speed-ups over
+// the vector form, 8 KV heads, work in 2^27 (token, KV head, group, centroid) combinations:
+//   4 channels: c = 33  0.65 - 0.82 at any work; c = 48  0.82 (2), 1.12 (16); c = 64  1.21 (1.3), 1.49 (16); c = 65 and 129
+//   (half a set)  0.9 (1.3), 1.09 / 1.28 (2), 1.2 / 1.6 (16); c = 256  0.98 (1), 1.11 (1.3), 3.2 (16).
+//   2 channels: c = 48  0.72 - 1.1; c = 64  1.02 (1.3), 1.33 (3), 1.1 (16); c = 65  0.79 - 1.0; c = 80  0.92 (2), 1.16 (3);
+//   c = 129  0.99 (2), 1.1 (4.2); c = 256  0.7 - 0.99 (1 - 1.6), 1.4 (3), 2.4 (16).
+static bool assign_by_tiles(int g, int c, int64_t work, int64_t T) {
+  if (T < 256 || c > kAsCodewords) return false;
+  const int set = c <= 64 ? 64 : c <= 128 ? 128 : 256;
+  const int64_t unit = (int64_t)1 << 25;                    // a quarter of 2^27
+  if (g == 32) return c >= 56 && work >= (8 * c >= 7 * set ? 5 : 8) * unit;
+  return (c == 64 || c >= 80) && work >= (4 * c >= 3 * set ? 12 : 17) * unit;
+}
+
+// Whether more than 256 centroids and 9 or more tokens go to vq_assign_mfma_kernel: always from 257 tokens on, below by an
+// estimate in us of both, fitted to 500 sizes (none picked more than 6 % slower than the better of the two).  A workgroup of it walks the codebook for up to 1024 tokens, two of them per compute unit at a
+// time; with few tokens most of its waves only help with the operands, and a launch of many (KV head, group) pairs is
+// faster in the vector form, whose waves take 64 tokens each.  Measured, mfma / vector: 8 rows, 32 groups, c = 8192, 9
+// tokens 0.25; 32 rows, 64 groups, 64 tokens: c = 257 1.66, 700 1.03, 1024 0.87; 128 rows, 64 groups, 64 tokens: c = 1024
+// 1.71, 2048 1.47; 128 tokens: 512 1.32, 1024 0.99; 256 tokens: 257 1.31, 400 0.98.
+static bool assign_by_shortlist(int rows, int g, int c, int64_t T) {
+  if (T > 256) return true;
+  const double pairs = (double)rows * g, waves = pairs * (double)((T + 63) / 64);
+  const double alone = g == 64 ? 0.058 : 0.089, each = g == 64 ? 1.38e-5 : 1.99e-5;      // per centroid: one wave; per wave
+  const double vec = c * (waves * each > alone ? waves * each : alone);
+  const double mfma = (pairs > 420 ? pairs : 420) * (0.0108 + 1.1e-5 * c) * (1.0 + T / 940.0);
+  return mfma < vec;
+}
+
 int32_t launch_vq_assign(const Layout& L, int g, int c, const float* centroids, uint8_t* pcache, const void* k_new,
                          int64_t T, const NRes& nr, float* acc_opt, int32_t* pos_opt, const NRes& vrow0, hipStream_t st) {
   if (T == 0) return HCA_OK;
@@ -1119,7 +1145,7 @@ int32_t launch_vq_assign(const Layout& L, int g, int c, const float* centroids, 
     else if (wide) vq_assign_kernel<2, true, GPW><<<GRID, 256, 0, st>>>(g, c, L.n_kv_heads, L.cap, centroids, pcache, kn, T, nr, acc_opt, pos_opt, vrow0);      \
     else vq_assign_kernel<2, false, GPW><<<GRID, 256, 0, st>>>(g, c, L.n_kv_heads, L.cap, centroids, pcache, kn, T, nr, acc_opt, pos_opt, vrow0);               \
   } while (0)
-  if (c > 32 && c <= kAsCodewords && T >= 256 && T * L.rows * g * c >= kAssignMfmaMinWork) {
+  if (assign_by_tiles(g, c, T * L.rows * g * c, T)) {
     dim3 gm((unsigned)((T + 255) / 256), (unsigned)L.rows, (unsigned)(g / 16));
 #define HCA_ASSIGN_SC(D, W, NT) vq_assign_small_c_kernel<D, W, NT><<<gm, 256, 0, st>>>(g, c, L.n_kv_heads, L.cap, centroids, pcache, kn, T, nr, acc_opt, pos_opt, vrow0)
 #define HCA_ASSIGN_SCN(D, W)                                                                                          \
@@ -1132,7 +1158,7 @@ int32_t launch_vq_assign(const Layout& L, int g, int c, const float* centroids, 
     else HCA_ASSIGN_SCN(2, false);
 #undef HCA_ASSIGN_SCN
 #undef HCA_ASSIGN_SC
-  } else if (c > kAsCodewords && T > 8) {
+  } else if (c > kAsCodewords && T > 8 && assign_by_shortlist(L.rows, g, c, T)) {
     // a block or a context: shortlist on the matrix cores, exact chain on the shortlist
     dim3 gm((unsigned)((T + 1023) / 1024), (unsigned)L.rows, (unsigned)g);
 #define HCA_ASSIGN_M(D, BT) vq_assign_mfma_kernel<D, BT><<<gm, 512, 0, st>>>(g, c, L.n_kv_heads, L.cap, centroids, pcache, kn, T, nr, acc_opt, pos_opt, vrow0)
@@ -1142,7 +1168,12 @@ int32_t launch_vq_assign(const Layout& L, int g, int c, const float* centroids, 
     else HCA_ASSIGN_M(2, 1);
 #undef HCA_ASSIGN_M
   } else if (T <= 8) {                              // decode appends: parallel over centroids, not over tokens
-    if (c >= 1024) HCA_ASSIGN_T(4);
+    // four waves on a group shorten a wave's chain of loads but are four times as many workgroups: while those of the
+    // other form fill the chip once, or the codebook is long.  Times of the other form over this one: 64 workgroups of it
+    // 1.3 (c = 1024), 2.5 (8192); 256: 1.07, 1.9; 512: 0.9 - 1.02 (1024), 0.91 (2048), 1.08 (4096); 1024: 0.74, 0.96,
+    // 1.04, 1.0 (8192); 2048: 0.64, 0.8, 0.96, 1.12; 4096: 0.99 (8192) and less.
+    const int64_t wgs = T * L.rows * (g / 4);
+    if (c >= 1024 && (wgs <= 256 || (c >= 4096 && 4 * wgs <= c))) HCA_ASSIGN_T(4);
     else HCA_ASSIGN_T(1);
   } else if ((T + 63) / 64 * L.rows * (g / 4) < 16 * 1024) {
     // a block of a few thousand tokens: with four groups per wave the launch would have at most a few waves per

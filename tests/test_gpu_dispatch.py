@@ -219,7 +219,10 @@ def test_score_topk_on_both_sides_of_the_short_row_line(B, oracle, bits, gs, n):
     (32, 33, 1, 16000, 8), (32, 64, 4, 11000, 6), (32, 65, 1, 8200, 8), (32, 128, 4, 4200, 8), (32, 129, 4, 2100, 16),
     (32, 255, 1, 2100, 8), (32, 256, 4, 2047, 8), (32, 256, 4, 2303, 8), (64, 256, 4, 1100, 8), (64, 200, 1, 1500, 8),
     (32, 257, 1, 9, 2), (32, 300, 4, 127, 2), (32, 511, 1, 1025, 1), (64, 513, 1, 300, 3), (32, 1023, 1, 8, 3),
-    (32, 1024, 1, 5, 3), (32, 2048, 1, 700, 1), (64, 2049, 4, 260, 1), (32, 8192, 1, 150, 2), (64, 8191, 1, 33, 1)])
+    (32, 1024, 1, 5, 3), (32, 2048, 1, 700, 1), (64, 2049, 4, 260, 1), (32, 8192, 1, 150, 2), (64, 8191, 1, 33, 1),
+    (32, 56, 1, 18800, 8), (32, 64, 1, 10300, 8), (32, 65, 1, 16200, 8), (32, 128, 4, 5200, 8), (32, 129, 4, 4100, 16),
+    (32, 255, 1, 2600, 8), (32, 256, 4, 2571, 8), (64, 64, 1, 12400, 8), (64, 80, 1, 14000, 8), (64, 160, 1, 7000, 8),
+    (64, 256, 4, 3100, 8), (64, 257, 1, 40, 32), (32, 300, 1, 65, 128), (64, 700, 1, 129, 64)])
 def test_bulk_assignment_equals_the_exhaustive_chain(B, g, c, G, T, rows):
     """hca_vq_assign: the matrix-core forms (up to 256 centroids, more than 256) and the vector forms give the indices of
     single-token calls, whose kernel evaluates the exact chain for every centroid; awkward tokens and centroids included."""
@@ -307,7 +310,7 @@ def test_assignment_queue_fills_at_any_group(B, oracle, g, c, G):
     queue passes the fill that makes room for the next group after one, two or several groups, and in both halves of
     the record, with the last workgroup of a row ragged."""
     dbar, rows = 128 // g, 8
-    T = -(-(1 << 27) // (rows * g * c)) + 131
+    T = int((3.05 if g == 64 else 2.05 if c == 96 else 1.3) * (1 << 27)) // (rows * g * c) + 131
     rng = np.random.default_rng(g + c + G)
     cen = rng.standard_normal((rows, g, c, dbar)).astype(np.float32)
     for i in range(g):
@@ -330,6 +333,39 @@ def test_assignment_queue_fills_at_any_group(B, oracle, g, c, G):
         got = out.cpu().numpy()
         got = got.view(np.uint16) if wide else got
         assert np.array_equal(got[:, 2:T + 2], oc.P[:, :T].astype(got.dtype))
+
+
+@pytest.mark.parametrize("g,c,rows", [(64, 1024, 8), (32, 2048, 8), (32, 4096, 8), (64, 1500, 3)])
+def test_append_forms_agree(B, g, c, rows):
+    """Eight tokens per call (one wave per group where that fills the chip) and one (four waves share a group's codebook)."""
+    gen = torch.Generator(device="cuda").manual_seed(c)
+    cen = torch.randn(rows, g, c, 128 // g, generator=gen, device="cuda")
+    cen[:, 1, c // 2:] = cen[:, 1, : c - c // 2].clone()
+    k = torch.randn(1, rows, 8, 128, generator=gen, device="cuda").half()
+    shape = B.make_shape(1, rows, rows, 16)
+    cb = B.make_codebook(g, c, cen)
+    both = [torch.zeros(B.hca_vq_pcache_bytes(shape, cb), dtype=torch.uint8, device="cuda") for _ in range(2)]
+    B.hca_vq_assign(shape, cb, both[0], k, 8, [2])
+    for t in range(8):
+        B.hca_vq_assign(shape, cb, both[1], k[:, :, t:t + 1].contiguous(), 1, [2 + t])
+    assert torch.equal(both[0], both[1])
+
+
+@pytest.mark.parametrize("g,c,rows,T", [(32, 33, 8, 32000), (64, 1024, 32, 8), (64, 257, 128, 64)])
+def test_assignment_time_has_no_step(B, g, c, rows, T):
+    """One centroid more, with which a launch rule could change the form: the call takes what the exact chain of one more
+    centroid takes, not 1.6 to 3.3 times as much.  Allowed: 1.3 times."""
+    gen = torch.Generator(device="cuda").manual_seed(c)
+    hkv = min(rows, 8)
+    k = torch.randn(rows // hkv, hkv, T, 128, generator=gen, device="cuda").half()
+    shape = B.make_shape(rows // hkv, hkv, hkv, T)
+    took = []
+    for cc in (c - 1, c):
+        cen = torch.randn(hkv, g, cc, 128 // g, generator=gen, device="cuda")
+        cb = B.make_codebook(g, cc, cen)
+        pc = torch.zeros(B.hca_vq_pcache_bytes(shape, cb), dtype=torch.uint8, device="cuda")
+        took.append(_passes_us(lambda: B.hca_vq_assign(shape, cb, pc, k, T, [0] * (rows // hkv))))
+    assert took[1] < 1.3 * took[0], f"{took[0]:.1f} us with {c - 1} centroids, {took[1]:.1f} with {c}"
 
 
 @pytest.mark.parametrize("bits,gs", [(4, 32), (2, 64)])
