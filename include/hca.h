@@ -193,8 +193,8 @@ int32_t hca_score_topk_monitor(const hca_shape* shape, void* workspace, int32_t*
  *               acc[idx_i] += sum over the row's query heads of max(a_i, 1e-30)
  *   gather_stream  the value rows are first gathered into the workspace on this
  *               stream (ordered after `stream`'s work enqueued so far); `stream`
- *               then waits for the gather.  May equal `stream`: nothing overlaps the gather then, and where no row is
- *               in host memory, or few are selected, the values are read where they live instead. */
+ *               then waits for the gather.  May equal `stream`: where no row is in host memory, or few of the
+ *               selected ones are, the values are then read where they live instead (unless "gather_wgs" is tuned). */
 int32_t hca_sparse_attend(const hca_shape* shape, const void* kcache, const void* q_f16,
                           const int32_t* idx, const int32_t* count, int32_t k,
                           const int32_t* pos,

@@ -5,7 +5,8 @@
 namespace hca {
 
 constexpr int kChunk = kAttendChunk;  // selected tokens per workgroup of the partial kernel
-constexpr int64_t kDirectHostEntries = 16384;
+// Most entries of a one-stream attend that reads values across the host link itself: in all, and of them in host memory.
+constexpr int64_t kDirectEntries = 16384, kDirectHostEntries = 4096;
 
 struct AttendWs {
   uint16_t* vstage;  // [rows][k][128] fp16
@@ -117,7 +118,9 @@ __device__ __forceinline__ void partial_empty(float* pmz, float* py) {
 }
 
 // The first half of the value rows a lane will need: entry 64 w + 4 x + sub of the chunk, 16 bytes (part) of each, x < 8.
-// They depend on nothing but the keep-list, so they are asked for before the logits are formed.
+// They depend on nothing but the keep-list, so they are asked for before the logits are formed.  Past the chunk's end the
+// last row is asked for again: it is in the cache (leaving those loads out costs a branch each, 9.6 -> 10.3 us for 65 rows
+// x 8 from the host).
 struct ValueRows { uint4 v[8]; };
 template <typename V>
 __device__ __forceinline__ void value_rows(V&& value, int x0, int nvalid, ValueRows* out) {
@@ -810,11 +813,16 @@ int32_t launch_attend(const Layout& L, const void* kcache, const void* q, const 
                       float sm_scale, float* y, float* acc_opt, void* ws, hipStream_t gst, hipStream_t st) {
   if (nsplit_of(k) > 64) return HCA_ERR_CAPACITY;
   // On one stream nothing overlaps the gather, so the attend can read the value rows where they live: without host rows
-  // always (4096 rows x 32 pairs: 27 us for the call against 42 through the staging area), with them while the launch has at
-  // most kDirectHostEntries entries: 2048 x 8 from the host 89 against 96 us, of which the link is 78.  Beyond, the gather's
-  // few persistent workgroups use the link better than a read per thread.
+  // always (4096 rows x 32 pairs: 27 us for the call against 42 through the staging area), with them while few are read
+  // there.  Alone, direct / staged: 512 x 8 from the host 31 / 38 us, 128 x 32 26 / 36, 2048 x 8 88 / 96; half of the values
+  // in HBM: 1024 x 8 31 / 41.  But a read per thread clogs the memory pipeline for what runs on other streams, which the
+  // gather's few workgroups do not: a scan of 8 x 1 Mi keys, 123 us, takes 133, 143, 250 and 128 us beside these four.
+  // A caller that shapes the gather (hca_tune, "gather_wgs") gets the gather.
   const bool no_host = v_host == nullptr || n_host_rows == 0;
-  if (gst == st && (no_host || (int64_t)k * L.rows <= kDirectHostEntries)) {
+  const int64_t entries = (int64_t)k * L.rows;
+  const double host_part = v_hbm == nullptr ? 1.0 : (double)n_host_rows / ((double)n_host_rows + (double)hbm_stride);
+  const bool few = entries <= kDirectEntries && entries * host_part <= kDirectHostEntries;
+  if (gst == st && (no_host || few) && tuning().gather_wgs == 0) {
     const ValueSource vsrc{pos, (const uint4*)v_host, (const uint4*)v_hbm, host_stride, hbm_stride, n_host_rows};
     return attend_launches(L, kcache, q, idx, count, k, sm_scale, y, acc_opt, ws, st, nullptr, nullptr, vsrc);
   }

@@ -50,6 +50,59 @@ def test_value_rows_are_the_same_wherever_they_live(B, k):
         assert torch.equal(y, out[0][2]) and torch.equal(acc, out[0][3]), f"n_host_rows = {n_host}, direct {direct}"
 
 
+def _one_stream_attend(B, n, k):
+    """A call of hca_sparse_attend on one stream, 8 KV heads, every value in host memory; stream -> None."""
+    w = S.Workload("hostvals", 82, 1, 32, 8, n, 4, 32, k)
+    d = S.make_layer(w)
+    st = _layer(w, k)
+    st.quantize(d["keys"].cuda())
+    q, values = d["q"].cuda(), d["values"].contiguous().pin_memory()
+    st.score_topk(q, k)
+    torch.cuda.synchronize()
+    return lambda stream=None: B.hca_sparse_attend(st.shape, st.kcache, q, st.idx, st.count, k, st.pos, values, n, n, None, 0,
+                                                   st.sm_scale, st.y, None, st.ws, stream=stream, gather_stream=stream)
+
+
+def test_host_values_on_one_stream_leave_the_others_their_memory(B):
+    """2048 x 8 values from host memory on one stream, a scan of 8 x 512 Ki keys on another: a read per thread across the host
+    link would double the scan's time.  Allowed: 1.4 times the scan alone."""
+    attend = _one_stream_attend(B, 4096, 2048)
+    n = 524288
+    shape = B.make_shape(1, 32, 8, n)
+    kc = torch.zeros(B.hca_kcache_bytes(shape), dtype=torch.uint8, device="cuda")
+    q = torch.randn(1, 32, 128, device="cuda").half()
+    sel = torch.zeros(1, 8, n, device="cuda")
+    ws = torch.empty(B.hca_workspace_bytes(shape, 64, 1), dtype=torch.uint8, device="cuda")
+    side, took = torch.cuda.Stream(), []
+    for beside in (0, 1, 0, 1, 0, 1):
+        torch.cuda.synchronize()
+        a, b = torch.cuda.Event(enable_timing=True), torch.cuda.Event(enable_timing=True)
+        torch.cuda._sleep(3000000)
+        side.wait_stream(torch.cuda.current_stream())
+        a.record()
+        for _ in range(12):
+            B.hca_score_qkeys(shape, kc, q, [n], sel, None, ws)
+        b.record()
+        for _ in range(16 * beside):
+            attend(side)
+        torch.cuda.synchronize()
+        took.append((beside, a.elapsed_time(b) * 1000 / 12))
+    alone, both = (min(t for x, t in took if x == y) for y in (0, 1))
+    assert both < 1.4 * alone, f"{alone:.0f} us alone, {both:.0f} us beside the attends"
+
+
+def test_a_shaped_gather_is_used(B):
+    """hca_tune("gather_wgs") reaches one-stream attends of few host values too: one workgroup per row is slower."""
+    attend = _one_stream_attend(B, 4096, 512)
+    try:
+        own = _passes_us(attend)
+        B.hca_tune("gather_wgs", 1)
+        one = _passes_us(attend)
+    finally:
+        B.hca_tune("gather_wgs", 0)
+    assert one > 1.2 * own, f"{own:.1f} us, {one:.1f} us with one workgroup"
+
+
 @pytest.mark.parametrize("bits,gs", [(4, 32), (2, 64)])
 @pytest.mark.parametrize("G,n_sel", [(4, 256), (4, 1), (2, 129), (1, 255)])
 @pytest.mark.parametrize("use_lse", [False, True])
