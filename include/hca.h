@@ -301,8 +301,8 @@ typedef struct {
   int32_t fused_select;
   void* ws_select[HCA_PIPELINE_MAX_SEL];
   /* optional profiling of the value gather, like scan_stamps: device, uint64 [timing_slots][n_layers][1024][2],
-     zero-filled by the caller; every workgroup of a timed gather launch (at most 1024) stores its start and end
-     wall-clock tick.  NULL: off. */
+     zero-filled by the caller; every workgroup of a timed gather launch stores its start and end wall-clock tick
+     (the 1025th and later ones only their end, in the pair of number mod 1024, if it is the later).  NULL: off. */
   void* gather_stamps;
   /* Hybrid value side (Sec. 3.2 "CPU part", Eq. 5 for a share of the selection; uniform codes only).
      host_chunks > 0: of every row's selected tokens (ascending slot order, chunks of 256) the first host_chunks

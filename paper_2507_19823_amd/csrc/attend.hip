@@ -60,9 +60,11 @@ __global__ __launch_bounds__(256) void gather_values(const int32_t* __restrict__
   // kernel starts only when its predecessor's stores are visible, so the first thing this one does is tell the host
   if (gpu_seq != nullptr && row == 0 && wg == 0 && threadIdx.x == 0)
     __hip_atomic_store(gpu_seq, seq, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_SYSTEM);
-  // optional profiling: every workgroup leaves its start and end time (constant-rate wall clock)
-  uint64_t* stamp = stamps ? stamps + ((int64_t)row * wgs + wg) * 2 : nullptr;
-  if (stamp && threadIdx.x == 0) stamp[0] = wall_clock64();
+  // optional profiling: every workgroup leaves its start and end time (constant-rate wall clock); beyond the buffer's pairs
+  // it leaves its end alone, where that is later than what its pair holds
+  const int64_t number = (int64_t)row * wgs + wg;
+  uint64_t* stamp = stamps ? stamps + number % kGatherStampPairs * 2 : nullptr;
+  if (stamp && threadIdx.x == 0 && number < kGatherStampPairs) stamp[0] = wall_clock64();
   const int cnt = count[row];
   const int part = threadIdx.x & 15;
   const bool host_role = wg < host_wgs;                    // SPLIT only
@@ -100,7 +102,7 @@ __global__ __launch_bounds__(256) void gather_values(const int32_t* __restrict__
   }
   if (stamp) {
     __syncthreads();
-    if (threadIdx.x == 0) stamp[1] = wall_clock64();
+    if (threadIdx.x == 0) atomicMax((unsigned long long*)&stamp[1], (unsigned long long)wall_clock64());
   }
 }
 
@@ -639,27 +641,26 @@ int32_t launch_gather(const Layout& L, const int32_t* idx, const int32_t* count,
   // link; more only take queue entries in the memory system away from the HBM-bound kernels beside it.
   int64_t lim = tn.gather_wgs > 0 ? tn.gather_wgs : (L.rows >= 64 ? 1 : 64 / L.rows);
   if (wgs > lim) wgs = lim;
-  // Rows in HBM: one sweep, every thread's four rows in flight together.  Where the store is shared between host
+  // Rows in HBM: one sweep, a row per thread while that is at most 1024 workgroups (64 rows: 2.6 us, 3.4 with four per
+  // thread), else every thread's four rows in flight together.  Where the store is shared between host
   // and HBM the launch has both kinds of workgroups, unless the HBM slice is only the few rows of the appended
-  // tokens (less than a sixteenth of the host rows): then the host kind takes them along.
-  const int64_t wide = entries > 0 ? (entries + 63) / 64 : 1;
+  // tokens (less than a sixteenth of the host rows) or the launch is small: then the host kind takes them along (half of
+  // the values in HBM, both kinds / one: 64 x 128 25.3 / 24.3 us, 512 x 8 13.9 / 13.6; 256 x 32 24.7 / 25.8, 512 x 32 44 / 47,
+  // 2048 x 8 44 / 45; three quarters in HBM: 100 x 32 8.0 / 8.7, 1024 x 8 15.5 / 16.2, 256 x 49 21.6 / 27.1).
+  const int64_t wide = entries > 0 ? (entries + 63) / 64 : 1, rows16 = entries > 0 ? (entries + 15) / 16 : 1;
   const bool no_host = v_host == nullptr || n_host_rows == 0;
-  const bool split = !no_host && v_hbm != nullptr && hbm_stride > n_host_rows / 16 && tn.gather_wgs == 0 &&
-                     stamps == nullptr;
+  const bool split = !no_host && v_hbm != nullptr && hbm_stride > n_host_rows / 16 && entries > 64 &&
+                     entries * L.rows >= (L.rows >= 16 ? 3072 : 8192) && tn.gather_wgs == 0;
   const int64_t host_wgs = wgs;
-  if (no_host && tn.gather_wgs == 0) wgs = wide;
+  if (no_host && tn.gather_wgs == 0) wgs = rows16 * L.rows <= 1024 ? rows16 : wide;
   else if (split) wgs += wide;
-  if (stamps != nullptr && tn.gather_wgs == 0 && wgs * L.rows > kGatherStampPairs)
-    wgs = kGatherStampPairs / L.rows > 0 ? kGatherStampPairs / L.rows : 1;     // one stamp pair per workgroup
-  if (wgs * L.rows > kGatherStampPairs) stamps = nullptr;      // more workgroups than the stamp buffer holds
   dim3 g((unsigned)wgs, (unsigned)L.rows);
   const uint4 *vh = (const uint4*)v_host, *vd = (const uint4*)v_hbm;
 #define HCA_GATHER_S(U, S)                                                                                            \
   gather_values<U, S><<<g, 256, 0, st>>>(idx, count, k, pos, L.cap, vh, host_stride, n_host_rows, vd, hbm_stride, \
                                          (uint4*)a.vstage, (int)wgs, (int)host_wgs, stamps, first_entry, gpu_seq, seq)
-#define HCA_GATHER(U) HCA_GATHER_S(U, false)
-  if (split) HCA_GATHER_S(4, true);
-  else if (tn.gather_unroll >= 4) HCA_GATHER(4);
+#define HCA_GATHER(U) do { if (split) HCA_GATHER_S(U, true); else HCA_GATHER_S(U, false); } while (0)
+  if (tn.gather_unroll >= 4) HCA_GATHER(4);
   else if (tn.gather_unroll >= 2) HCA_GATHER(2);
   else HCA_GATHER(1);
 #undef HCA_GATHER

@@ -1,5 +1,7 @@
 """The sizes, placements and shapes where a launch rule changes from one form of a kernel to another: the forms must
 agree bit for bit with each other or with the oracle on both sides of the line."""
+import ctypes
+
 import numpy as np
 import pytest
 import torch
@@ -48,6 +50,56 @@ def test_value_rows_are_the_same_wherever_they_live(B, k):
     assert torch.isfinite(out[0][2]).all() and (out[0][3] > 0).any()
     for n_host, direct, y, acc in out[1:]:
         assert torch.equal(y, out[0][2]) and torch.equal(acc, out[0][3]), f"n_host_rows = {n_host}, direct {direct}"
+
+
+@pytest.mark.parametrize("batch,n_host,k,wgs", [(4, 0, 300, 19), (8, 0, 500, 8), (16, 0, 1100, 18), (4, 600, 300, 7), (4, 600, 64, 2),
+                                                (1, 600, 400, 8)])
+def test_gather_stamps_time_the_launch_that_runs(B, batch, n_host, k, wgs):
+    """A timed step gathers with the workgroups of an untimed one - per row: 16 or 64 rows each where the store is in HBM, host
+    and HBM kinds where it is shared and the launch is large, else the host kind alone -, and their stamps say so: one start per
+    workgroup up to 1024, no end before its start."""
+    n, hkv = 1200, 8
+    w = S.Workload("stamps", 83, batch, 32, hkv, n, 4, 32, k)
+    d = S.make_layer(w)
+    st = _layer(w, k, cap=n + 4)
+    st.quantize(d["keys"].cuda())
+    q, values = d["q"].cuda(), d["values"]
+    vh = values[:, :, :n_host].contiguous().pin_memory() if n_host else None
+    vd = torch.zeros(batch, hkv, n + 4 - n_host, 128, dtype=torch.float16, device="cuda")
+    vd[:, :, :n - n_host] = values[:, :, n_host:].cuda()
+    keep = [torch.zeros(batch, hkv, 1, 128, dtype=torch.float16, device="cuda"), torch.zeros(1, 1, 1024, 2, dtype=torch.int64, device="cuda")]
+
+    def buf(*shape, dtype=torch.uint8):
+        keep.append(torch.zeros(shape, dtype=dtype, device="cuda"))
+        return keep[-1].data_ptr()
+    p = B.hca_pipeline_desc()
+    cur = torch.cuda.current_stream().cuda_stream
+    p.stream_scan = p.stream_topk = p.stream_gather = p.stream_attend = cur
+    p.n_sel, p.n_pipe = 3, 4
+    for i in range(3):
+        p.sel[i] = buf(batch, hkv, n + 4, dtype=torch.float32)
+    wsb = B.hca_workspace_bytes(st.shape, k, 1)
+    for i in range(4):
+        p.idx[i], p.count[i] = buf(batch, hkv, k, dtype=torch.int32), buf(batch, hkv, dtype=torch.int32)
+        p.ws_attend[i] = buf(wsb)
+    p.ws_topk = buf(wsb)
+    pairs = B.hca_scan_stamp_pairs(st.shape, n + 4)
+    p.scan_stamps, p.scan_stamp_pairs = buf(1, 1, pairs, 2, dtype=torch.int64), pairs
+    p.gather_stamps = keep[1].data_ptr()
+    ly = (B.hca_layer * 1)()
+    ly[0].kcache, ly[0].acc, ly[0].pos = st.kcache.data_ptr(), st.acc.data_ptr(), st.pos.data_ptr()
+    ly[0].k_new, ly[0].q, ly[0].y = keep[0].data_ptr(), q.data_ptr(), st.y.data_ptr()
+    ly[0].v_host, ly[0].v_hbm = vh.data_ptr() if n_host else None, vd.data_ptr()
+    nres = (ctypes.c_int64 * batch)(*[n] * batch)
+    pl = B.hca_pipeline_create(st.shape, 1, p, 1)
+    B.hca_pipeline_step(pl, ly, nres, n, k, n_host, n_host, vd.shape[2], st.sm_scale, timing_slot=0)
+    torch.cuda.synchronize()
+    B.hca_pipeline_destroy(pl)
+    stamps = keep[1].cpu().numpy()[0, 0]
+    used = min(1024, wgs * batch * hkv)
+    assert (stamps[:used, 0] > 0).all() and (stamps[used:] == 0).all()
+    assert (stamps[:used, 1] >= stamps[:used, 0]).all()
+    assert torch.isfinite(st.y).all()
 
 
 def _one_stream_attend(B, n, k):
