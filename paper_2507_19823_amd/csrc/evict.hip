@@ -313,7 +313,7 @@ static int32_t evict_move(const Layout& L, void* kcache, float* acc, int32_t* po
   if (!pl.any || d1 <= d0) return HCA_OK;
   // at most 2048 workgroups in all: the kernels stride over what there is to move
   const int64_t cap_wg = L.rows >= 2048 ? 1 : 2048 / L.rows;
-  int64_t wg = ((d1 - d0) * 4 + 255) / 256;
+  int64_t wg = (d1 - (d0 & ~(int64_t)63) + 255) / 256;      // 64 slots per wave
   if (wg > cap_wg) wg = cap_wg;
   dim3 gg((unsigned)wg, (unsigned)L.rows);
   if (L.bits == 4)
