@@ -719,7 +719,10 @@ __global__ __launch_bounds__(256) void vq_assign_small_kernel(int g, int c, int 
 // T[row][cc][i][h] (narrow form; T[row][i][cc][h] in the wide form) = qbar_i . C[i][cc] for the G query heads of the row: t = 0; t = fmaf(q, c, t) over
 // the group's channels in ascending order.  grid (g, rows), centroids spread over the threads.  The workgroup also
 // leaves the largest magnitude of its group's entries, per head, in amax[row][i][4] for the scan.
-template <int G, int DBAR>
+// PER: centroids in flight per thread.  8 rows, c = 8192, one -> eight: 15.3 -> 12.2 us; a codebook of at most 256 has one per
+// thread and wants the registers for more workgroups (128 rows, c = 64, the call that fills the table and scans 100 slots:
+// 14.0 us with eight, 13.0 with one).
+template <int G, int DBAR, int PER>
 __global__ __launch_bounds__(256) void vq_lut_kernel(int g, int c, int n_kv_heads, bool wide,
                                                      const float* __restrict__ centroids,
                                                      const uint16_t* __restrict__ q, float* __restrict__ lut,
@@ -735,18 +738,17 @@ __global__ __launch_bounds__(256) void vq_lut_kernel(int g, int c, int n_kv_head
 #pragma unroll
     for (int dd = 0; dd < DBAR; ++dd) qv[h][dd] = h2f(q[((int64_t)row * G + h) * kHeadDim + i * DBAR + dd]);
   const float* cb = centroids + ((int64_t)(row % n_kv_heads) * g + i) * c * DBAR;
-  for (int c0 = threadIdx.x; c0 < c; c0 += 8 * 256) {       // eight centroids in flight: 8 rows, c = 8192 15.3 -> 12.2 us
-    float cv[8][DBAR];
+  for (int c0 = threadIdx.x; c0 < c; c0 += PER * 256) {
+    float cv[PER][DBAR];
 #pragma unroll
-    for (int u = 0; u < 8; ++u) {
-      if (256 * u >= c) break;                              // (a codebook of at most 256: one centroid per thread)
+    for (int u = 0; u < PER; ++u) {
 #pragma unroll
       for (int dd = 0; dd < DBAR; ++dd) cv[u][dd] = cb[(int64_t)(c0 + 256 * u < c ? c0 + 256 * u : c0) * DBAR + dd];
     }
 #pragma unroll
-    for (int u = 0; u < 8; ++u) {
+    for (int u = 0; u < PER; ++u) {
       const int cc = c0 + 256 * u;
-      if (256 * u >= c || cc >= c) break;
+      if (cc >= c) break;
       float* out = lut + (wide ? ((int64_t)row * g + i) * c + cc : ((int64_t)row * c + cc) * g + i) * G;
 #pragma unroll
       for (int h = 0; h < G; ++h) {
@@ -776,17 +778,6 @@ template <> struct EntryT<4> { using type = float4; using fix = int4; };
 template <> struct EntryT<2> { using type = float2; using fix = int2; };
 template <> struct EntryT<1> { using type = float; using fix = int; };
 
-template <int G>
-__device__ __forceinline__ void entry_absmax(float (&m)[G], const typename EntryT<G>::type& e) {
-  if constexpr (G == 4) {
-    m[0] = fmaxf(m[0], fabsf(e.x)); m[1] = fmaxf(m[1], fabsf(e.y));
-    m[2] = fmaxf(m[2], fabsf(e.z)); m[3] = fmaxf(m[3], fabsf(e.w));
-  } else if constexpr (G == 2) {
-    m[0] = fmaxf(m[0], fabsf(e.x)); m[1] = fmaxf(m[1], fabsf(e.y));
-  } else {
-    m[0] = fmaxf(m[0], fabsf(e));
-  }
-}
 template <int G>
 __device__ __forceinline__ typename EntryT<G>::fix entry_fix(const typename EntryT<G>::type& e, const int* s) {
   typename EntryT<G>::fix r;
@@ -1248,13 +1239,15 @@ int32_t launch_vq_score(const Layout& L, int g, int c, const float* centroids, c
   const uint16_t* qq = (const uint16_t*)q;
   dim3 gl((unsigned)g, (unsigned)L.rows);
   float* amax = lut + (int64_t)L.rows * g * c * L.gqa;   // [rows][g][4], then the exponents [rows][4]
-#define HCA_LUT(G, D) vq_lut_kernel<G, D><<<gl, 256, 0, st>>>(g, c, L.n_kv_heads, vq_is_wide(L, g, c), centroids, qq, lut, amax)
+#define HCA_LUT_P(G, D, PER) vq_lut_kernel<G, D, PER><<<gl, 256, 0, st>>>(g, c, L.n_kv_heads, vq_is_wide(L, g, c), centroids, qq, lut, amax)
+#define HCA_LUT(G, D) do { if (c <= 256) HCA_LUT_P(G, D, 1); else HCA_LUT_P(G, D, 8); } while (0)
   if (g == 32) {
     if (L.gqa == 4) HCA_LUT(4, 4); else if (L.gqa == 2) HCA_LUT(2, 4); else HCA_LUT(1, 4);
   } else {
     if (L.gqa == 4) HCA_LUT(4, 2); else if (L.gqa == 2) HCA_LUT(2, 2); else HCA_LUT(1, 2);
   }
 #undef HCA_LUT
+#undef HCA_LUT_P
   HCA_HIP(hipGetLastError());
   if (nmax == 0) return HCA_OK;
   if (vq_is_wide(L, g, c)) {

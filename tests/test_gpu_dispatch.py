@@ -625,6 +625,49 @@ def test_topp_time_does_not_hang_on_the_spread(B, kind):
     assert took[1] < 2 * took[0], f"{took[0]:.0f} us for normal rows, {took[1]:.0f} us"
 
 
+@pytest.mark.parametrize("gqa,groups,c", [(4, 32, 64), (2, 64, 256), (1, 32, 256), (4, 32, 1024)])
+def test_codebook_attend_of_many_rows_equals_that_of_few(B, gqa, groups, c):
+    """hca_vq_attend_gathered asks for the values before the table reads in launches of at most 256 workgroups and in the wide
+    form, else behind them; 17 sequences of 8 KV heads in one call (more than 256 workgroups) and one at a time."""
+    batch, hkv, n, k = 17, 8, 1500, 700
+    gen = torch.Generator(device="cuda").manual_seed(c + gqa)
+    cen = torch.randn(hkv, groups, c, 128 // groups, generator=gen, device="cuda")
+    cb = B.make_codebook(groups, c, cen)
+    keys = torch.randn(batch, hkv, n, 128, generator=gen, device="cuda").half()
+    q = torch.randn(batch, hkv * gqa, 128, generator=gen, device="cuda").half()
+    v = torch.randn(batch, hkv, n, 128, generator=gen, device="cuda").half()
+    idx = torch.stack([torch.randperm(n, generator=gen, device="cuda")[:k].sort().values for _ in range(batch * hkv)])
+    idx = idx.int().view(batch, hkv, k).contiguous()
+    count = torch.full((batch, hkv), k, dtype=torch.int32, device="cuda")
+    count[3], count[5, 2] = 513, 0
+
+    def run(b):
+        part = slice(b, b + 1) if b is not None else slice(0, batch)
+        nb = 1 if b is not None else batch
+        shape = B.make_shape(nb, hkv * gqa, hkv, n)
+        pc = torch.zeros(B.hca_vq_pcache_bytes(shape, cb), dtype=torch.uint8, device="cuda")
+        B.hca_vq_assign(shape, cb, pc, keys[part].contiguous(), n, [0] * nb)
+        lut = torch.zeros(B.hca_vq_lut_bytes(shape, cb) // 4, device="cuda")
+        sel = torch.zeros(nb, hkv, n, device="cuda")
+        qq = q[part].contiguous()
+        B.hca_vq_score(shape, cb, pc, qq, [n] * nb, lut, sel)
+        ws = torch.zeros(B.hca_vq_workspace_bytes(shape, cb, k), dtype=torch.uint8, device="cuda")
+        pos = torch.arange(n, dtype=torch.int32, device="cuda").repeat(nb * hkv).view(nb, hkv, n).contiguous()
+        ii, cc, y = idx[part].contiguous(), count[part].contiguous(), torch.full((nb, hkv * gqa, 128), 9.0, device="cuda")
+        acc = torch.zeros(nb, hkv, n, device="cuda")
+        B.hca_gather_values(shape, ii, cc, k, pos, None, 0, 0, v[part].contiguous(), n, ws)
+        B.hca_vq_attend_gathered(shape, cb, pc, lut, ii, cc, k, 0.0884, y, acc, ws)
+        torch.cuda.synchronize()
+        return y, acc
+    y, acc = run(None)
+    one = [run(b) for b in range(batch)]
+    assert torch.equal(torch.nan_to_num(y, 7.0), torch.nan_to_num(torch.cat([o[0] for o in one]), 7.0))
+    assert torch.equal(acc, torch.cat([o[1] for o in one])) and (acc > 0).any()
+    keep = torch.ones(batch, hkv, dtype=torch.bool)
+    keep[5, 2] = False
+    assert torch.isfinite(y.view(batch, hkv, gqa, 128)[keep.cuda()]).all()
+
+
 @pytest.mark.parametrize("gqa,groups,c,n", [(4, 32, 8192, 12288), (4, 32, 300, 12289), (4, 64, 513, 16384), (4, 32, 1024, 16385),
                                             (2, 32, 8192, 12289), (1, 64, 8192, 257), (1, 32, 511, 4097)])
 def test_wide_codebook_scan_shares(B, gqa, groups, c, n):
