@@ -873,6 +873,15 @@ def cpu_split_probe(w, threads=16, iters=6):
     return out
 
 
+def assigned_by_tiles(g, c, work):
+    """Whether the library assigns a block of more than 256 tokens to at most 256 centroids on the matrix cores (its launch
+    rule: how full its sets of 2, 4 or 8 tiles are, channels per centroid, (token, KV head, group, centroid) combinations)."""
+    tiles = 64 if c <= 64 else 128 if c <= 128 else 256
+    if g == 32:
+        return 56 <= c <= 256 and work >= (5 if 8 * c >= 7 * tiles else 8) << 25
+    return (c == 64 or 80 <= c <= 256) and work >= (12 if 4 * c >= 3 * tiles else 17) << 25
+
+
 def prefill_blocks(w, sizes=(1024, 4096, 16384, 65536, 262144)):
     """Key compression as a block-wise prefill hands it over (App. B: the keys of a block are quantised when the
     block's attention is done): the context arrives in blocks of T tokens per sequence and every block is appended
@@ -935,8 +944,9 @@ def prefill_blocks(w, sizes=(1024, 4096, 16384, 65536, 262144)):
             ms, nb = run(lambda blk, T_, n: B.hca_vq_assign(shape, cb, P, blk, T_, n), total, T)
             tf = rows * T * g * c * (128 // g) * 3 / ms / 1e9          # the exhaustive exact search's flops
             r = {"block_tokens": T, "blocks": nb, "ms_per_block": ms, "tokens_per_s": w.batch * T / ms * 1e3}
-            if c > 256 or (T >= 256 and rows * T * g * c >= (1 << 27)):
-                # the library's bulk form from this size on: one pass of v_mfma_f32_32x32x16_f16 over every
+            if T > 256 and (c > 256 or assigned_by_tiles(g, c, rows * T * g * c)):
+                # the library's bulk form at this size (more than 256 tokens, and up to 256 centroids by how full its tiles
+                # are): one pass of v_mfma_f32_32x32x16_f16 over every
                 # (token, group, centroid), 16 products each, then the exact search on the shortlist only
                 mt = rows * T * g * c * 2 * 16 / ms / 1e9
                 r.update({"form": "matrix-core shortlist + exact chain on the shortlist", "matrix_TFLOPs": mt,

@@ -482,7 +482,7 @@ int32_t hca_host_weighted_sum(const hca_shape* shape, const int32_t* vrow, const
  * shape.  Narrow (c <= 256 and g * c * n_q_heads/n_kv_heads <= 32768): indices are bytes and the whole
  * table of a KV head (<= 128 KiB) sits in the LDS of the compute unit that scans it.  Wide (anything
  * else, up to the paper's own c = 8192 of Fig. 4 / Table 4a): 16-bit indices, the table (up to 4 MiB per
- * KV head) passes through LDS a slice of groups at a time, once per tile of 16 Ki tokens.
+ * KV head) passes through LDS a slice of groups at a time, once per share of at most 16 Ki tokens.
  *
  * Arithmetic (the same on the oracle's side, so that indices, tables and scores match bit for bit):
  *   distance  d = 0; channels of the group ascending: e = x - c; d = fmaf(e, e, d); nearest = smallest d,

@@ -30,7 +30,7 @@ struct Tuning {
   int gather_wgs = 0;      // workgroups of the value gather per row (0 = default)
   int gather_unroll = 4;   // rows in flight per thread
   int score_bpw = 0;       // 1 KiB code blocks per wave (0 = automatic; else kScoreBpwMin .. kScoreBpwMax)
-  int score_depth = 0;     // blocks fetched ahead per wave (4 or 8; 0 = 8 for 4-bit codes, 4 for 2-bit)
+  int score_depth = 0;     // blocks fetched ahead per wave (4 or 8; 0 = 8 from 8 blocks per wave on, else 4)
   int host_spin_us = 100;  // how long the host-sum workers poll for the next call before they sleep
   int host_isa = 0;        // host_chunk_sum: 0 = the widest vector form the CPU has, 2 = the AVX2 form
   int select_wg = 0;       // threads per workgroup of the selection over the candidate lists: 1024 (pairs staged in

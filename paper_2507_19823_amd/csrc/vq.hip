@@ -133,8 +133,8 @@ __global__ __launch_bounds__(256) void vq_assign_kernel(int g, int c, int n_kv_h
 //   then two.  Tokens with more blocks in question than were kept, or with S out of range, are noted in an LDS queue
 //   and go through the exact chain of every centroid at the end.  (|m1| < 1.01 S moves d2 by at most 2^-15 S more.)
 // What bounds it is the vector ALU's issue (a second pass of products with the threshold folded in, a sign test and a
-// list of candidates in the loop took twice the instructions): 17.6 per matrix instruction with everything, 90 % of
-// the issue slots, the matrix cores 40 % busy.  16 Ki tokens x 8 KV heads against 8192 centroids: 1.23 ms (2.44 in two
+// list of candidates in the loop took twice the instructions): 16.3 per matrix instruction with everything, 90 % of
+// the issue slots, the matrix cores 44 % busy.  16 Ki tokens x 8 KV heads against 8192 centroids: 1.23 ms (2.44 in two
 // passes); 64 Ki x 8 against 1024: 0.90 ms (2.30); 100 tokens x 8 against 8192: 0.07 ms (0.94 in the vector form).
 typedef _Float16 v8h __attribute__((ext_vector_type(8)));
 typedef _Float16 v2h __attribute__((ext_vector_type(2)));
