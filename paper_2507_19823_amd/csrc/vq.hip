@@ -194,6 +194,13 @@ __device__ __forceinline__ float am_limit(float m1, float x2, float S) {
   const float delta = fminf(near, S) * 7.62939453125e-6f + 4.76837158203125e-7f;      // 2^-17 S' + 2^-21
   return m1 + (2.1f * delta + 3.3e-5f * fabsf(m1));
 }
+// The smaller of two numbers as one instruction: fminf spends another to quiet each operand that may be a signalling NaN.
+// (NaNs only come from tokens or centroids out of range, which the caller finds by S.)
+__device__ __forceinline__ float am_min(float a, float b) { return __builtin_elementwise_minimum(a, b); }
+// v with the bits of `mask` replaced by those of n (mask in a vector register: one instruction with n in a scalar one)
+__device__ __forceinline__ float am_number(float v, uint32_t n, uint32_t mask) {
+  return __uint_as_float((n & mask) | (__float_as_uint(v) & ~mask));
+}
 // (value of the lower half, value of the upper half) of a wave, on every lane of a column
 struct Halves { uint32_t lo, hi; };
 __device__ __forceinline__ Halves halves_of(uint32_t v) {
@@ -311,6 +318,8 @@ __global__ __launch_bounds__(512) __attribute__((amdgpu_waves_per_eu(4))) void v
   float m1[TT], m2[TT], m3[TT];
 #pragma unroll
   for (int tt = 0; tt < TT; ++tt) { m1[tt] = INFINITY; m2[tt] = INFINITY; m3[tt] = INFINITY; }
+  uint32_t number = 127;
+  asm volatile("" : "+v"(number));
   if (tid == 0) s_nq = 0;
   fetch(0);
   commit(0);
@@ -330,19 +339,19 @@ __global__ __launch_bounds__(512) __attribute__((amdgpu_waves_per_eu(4))) void v
           for (int tt = 0; tt < TT; ++tt) d[tt] = __builtin_amdgcn_mfma_f32_32x32x16_f16(a, bop[tt], zero16, 0, 0, 0);
 #pragma unroll
           for (int tt = 0; tt < TT; ++tt) {
-            float mm = u == 0 ? fminf(d[tt][0], d[tt][1]) : fminf(fminf(tm[tt], d[tt][0]), d[tt][1]);
+            float mm = u == 0 ? am_min(d[tt][14], d[tt][15]) : am_min(am_min(tm[tt], d[tt][14]), d[tt][15]);
 #pragma unroll
-            for (int j = 2; j < 16; j += 2) mm = fminf(fminf(mm, d[tt][j]), d[tt][j + 1]);
+            for (int j = 0; j < 14; j += 2) mm = am_min(am_min(mm, d[tt][j]), d[tt][j + 1]);
             tm[tt] = mm;
           }
         }
         const uint32_t blk = (uint32_t)(ch * (kAmChunk / 32 / kAmBlock) + bl);
 #pragma unroll
         for (int tt = 0; tt < TT; ++tt) {
-          const float pk = __uint_as_float((__float_as_uint(tm[tt]) & ~127u) | blk);
+          const float pk = am_number(tm[tt], blk, number);
           m3[tt] = __builtin_amdgcn_fmed3f(m2[tt], m3[tt], pk);
           m2[tt] = __builtin_amdgcn_fmed3f(m1[tt], m2[tt], pk);
-          m1[tt] = fminf(m1[tt], pk);
+          m1[tt] = am_min(m1[tt], pk);
         }
       }
     }
@@ -568,12 +577,12 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(4))) void v
       for (int tt = 0; tt < TT; ++tt) {
 #pragma unroll
         for (int q = 0; q < 2; ++q) {                       // the half wave's first and last eight rows
-          float tm = fminf(d[tt][8 * q], d[tt][8 * q + 1]);
+          float tm = am_min(d[tt][8 * q], d[tt][8 * q + 1]);
 #pragma unroll
-          for (int j = 2; j < 8; j += 2) tm = fminf(fminf(tm, d[tt][8 * q + j]), d[tt][8 * q + j + 1]);
-          const float pk = __uint_as_float((__float_as_uint(tm) & ~15u) | (uint32_t)(2 * t + q));
+          for (int j = 2; j < 8; j += 2) tm = am_min(am_min(tm, d[tt][8 * q + j]), d[tt][8 * q + j + 1]);
+          const float pk = am_number(tm, (uint32_t)(2 * t + q), 15u);
           m2[tt] = __builtin_amdgcn_fmed3f(m1[tt], m2[tt], pk);
-          m1[tt] = fminf(m1[tt], pk);
+          m1[tt] = am_min(m1[tt], pk);
         }
         asm volatile("" : "+v"(m1[tt]));
       }
