@@ -133,9 +133,9 @@ __global__ __launch_bounds__(256) void vq_assign_kernel(int g, int c, int n_kv_h
 //   then two.  Tokens with more blocks in question than were kept, or with S out of range, are noted in an LDS queue
 //   and go through the exact chain of every centroid at the end.  (|m1| < 1.01 S moves d2 by at most 2^-15 S more.)
 // What bounds it is the vector ALU's issue (a second pass of products with the threshold folded in, a sign test and a
-// list of candidates in the loop took twice the instructions): 16.3 per matrix instruction with everything, 90 % of
-// the issue slots, the matrix cores 44 % busy.  16 Ki tokens x 8 KV heads against 8192 centroids: 1.23 ms (2.44 in two
-// passes); 64 Ki x 8 against 1024: 0.90 ms (2.30); 100 tokens x 8 against 8192: 0.07 ms (0.94 in the vector form).
+// list of candidates in the loop took twice the instructions): 12.9 per matrix instruction with everything, 79 % of
+// the issue slots, the matrix cores 46 % busy.  16 Ki tokens x 8 KV heads against 8192 centroids: 1.09 ms (2.44 in two
+// passes).
 typedef _Float16 v8h __attribute__((ext_vector_type(8)));
 typedef _Float16 v2h __attribute__((ext_vector_type(2)));
 typedef float v16f __attribute__((ext_vector_type(16)));
@@ -186,20 +186,22 @@ __device__ __forceinline__ v8h am_token(const uint32_t (&xw)[DBAR / 2], int kb, 
   return kb == 0 ? v8h{xh[0], xh[1], xh[2], xh[3], xh[0], xh[1], xh[2], xh[3]}
                  : v8h{one, one, one, zero, zero, zero, zero, zero};
 }
-// How far above the smallest value a block can still hold the winner (m1: the smallest value with its block number in it,
-// S = |x|^2 + max |c|^2 in range).
-__device__ __forceinline__ float am_limit(float m1, float x2, float S) {
-  const float d2 = fmaxf(2.f * m1 + x2 + (5e-5f * S + 9.5367431640625e-7f), 0.f);
-  const float near = 2.f * x2 + d2 + 2.f * __builtin_amdgcn_sqrtf(x2 * d2);
-  const float delta = fminf(near, S) * 7.62939453125e-6f + 4.76837158203125e-7f;      // 2^-17 S' + 2^-21
-  return m1 + (2.1f * delta + 3.3e-5f * fabsf(m1));
-}
 // The smaller of two numbers as one instruction: fminf spends another to quiet each operand that may be a signalling NaN.
-// (NaNs only come from tokens or centroids out of range, which the caller finds by S.)
+// (NaNs only come from tokens or centroids out of range, which the caller finds by S.)  16 Ki tokens x 8 KV heads against
+// 8192 centroids: 1168 us with fminf, 1092 with it.
 __device__ __forceinline__ float am_min(float a, float b) { return __builtin_elementwise_minimum(a, b); }
+__device__ __forceinline__ float am_max(float a, float b) { return __builtin_elementwise_maximum(a, b); }
 // v with the bits of `mask` replaced by those of n (mask in a vector register: one instruction with n in a scalar one)
 __device__ __forceinline__ float am_number(float v, uint32_t n, uint32_t mask) {
   return __uint_as_float((n & mask) | (__float_as_uint(v) & ~mask));
+}
+// How far above the smallest value a block can still hold the winner (m1: the smallest value with its block number in it,
+// S = |x|^2 + max |c|^2 in range).
+__device__ __forceinline__ float am_limit(float m1, float x2, float S) {
+  const float d2 = am_max(2.f * m1 + x2 + (5e-5f * S + 9.5367431640625e-7f), 0.f);
+  const float near = 2.f * x2 + d2 + 2.f * __builtin_amdgcn_sqrtf(x2 * d2);
+  const float delta = am_min(near, S) * 7.62939453125e-6f + 4.76837158203125e-7f;      // 2^-17 S' + 2^-21
+  return m1 + (2.1f * delta + 3.3e-5f * fabsf(m1));
 }
 // (value of the lower half, value of the upper half) of a wave, on every lane of a column
 struct Halves { uint32_t lo, hi; };
@@ -452,22 +454,29 @@ __global__ __launch_bounds__(512) __attribute__((amdgpu_waves_per_eu(4))) void v
 // barrier per group, and the sixteen index bytes of a token leave as one 16-byte store (narrow form).  A block is half of
 // a tile's rows in a half wave; two values are kept, a token with rivals in another block (a few in a thousand) goes to
 // the queue.
-// 64 Ki tokens x 8 KV heads against 256 centroids: 0.31 ms (0.99 in the vector form), 64 centroids: 0.17 ms (0.25).
+// Bound by the issue of the vector ALU (86 % of its slots at 256 centroids): the two minima of 16 blocks of products, half
+// of it, and one block's exact chain per token.  Every lane decides about one token - the two tiles' halves change places
+// in one swap each - so that the limit and the chain's set-up are paid once per token, not once per half wave.
+// 64 Ki tokens x 8 KV heads against 256 centroids: 311 -> 239 us (0.99 ms in the vector form), 64 centroids: 178 -> 128
+// (0.25); two channels: 586 -> 433, 335 -> 193.
 constexpr int kAsCodewords = 256;
 
+// largest of a wave's numbers, none of them negative: their bits compare like them
 template <int CTRL>
-__device__ __forceinline__ float dpp_max(float v) {
-  return fmaxf(v, __int_as_float(__builtin_amdgcn_update_dpp(0, __float_as_int(v), CTRL, 0xf, 0xf, true)));
+__device__ __forceinline__ uint32_t dpp_max(uint32_t v) {
+  const uint32_t o = (uint32_t)__builtin_amdgcn_update_dpp(0, (int)v, CTRL, 0xf, 0xf, true);
+  return o > v ? o : v;
 }
-__device__ __forceinline__ float wave_max_nonneg(float v) {
+__device__ __forceinline__ float wave_max_nonneg(float f) {
+  uint32_t v = __float_as_uint(f);
   v = dpp_max<0xB1>(v);               // quad_perm [1,0,3,2]
   v = dpp_max<0x4E>(v);               // quad_perm [2,3,0,1]
   v = dpp_max<0x141>(v);              // row_half_mirror
   v = dpp_max<0x140>(v);              // row_mirror
-  const auto a = __builtin_amdgcn_permlane16_swap(__float_as_uint(v), __float_as_uint(v), false, false);
-  v = fmaxf(__uint_as_float(a[0]), __uint_as_float(a[1]));
-  const Halves h = halves_of(__float_as_uint(v));
-  return fmaxf(__uint_as_float(h.lo), __uint_as_float(h.hi));
+  const auto a = __builtin_amdgcn_permlane16_swap(v, v, false, false);
+  v = a[0] > a[1] ? a[0] : a[1];
+  const Halves h = halves_of(v);
+  return __uint_as_float(h.lo > h.hi ? h.lo : h.hi);
 }
 
 // NT: tiles of 32 centroids (2, 4 or 8)
@@ -518,20 +527,15 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(4))) void v
     const float m = wave_max_nonneg(nn < INFINITY ? nn : INFINITY);     // not finite or not a number: no token is in range
     if (lane == 0) s_cmax[buf][w] = m;
   };
-  // this lane's tokens: a group's DBAR channels as they lie in memory
-  uint32_t xn[TT][DBAR / 2];
-  const uint32_t* xsrc[TT];
-#pragma unroll
-  for (int tt = 0; tt < TT; ++tt) {
-    const int64_t t = tok0 + 32 * tt + col;
-    xsrc[tt] = reinterpret_cast<const uint32_t*>(k_new + ((int64_t)row * T + (t < T ? t : T - 1)) * kHeadDim + g0 * DBAR);
-  }
-  auto load_x = [&](int gi) {
-#pragma unroll
-    for (int tt = 0; tt < TT; ++tt)
-#pragma unroll
-      for (int d = 0; d < DBAR / 2; ++d) xn[tt][d] = xsrc[tt][gi * (DBAR / 2) + d];
-  };
+  // this lane's own token (lane 32 tt + col has column col of the wave's tile tt): 16 bytes of it as they lie in memory,
+  // the channels of two or four groups, the next group's first, and the 16 bytes after them.  (A load per group asks for
+  // every line of the keys sixteen times, and beyond 16 Ki tokens x 8 KV heads not out of L2: with few centroids that is
+  // what bounds the launch.  32 Ki x 8 against 64 centroids: 100 us with 8 bytes per load, 73 with 16.)
+  constexpr int kPer = 8 / DBAR;
+  const int64_t mine = tok0 + lane;
+  const uint4* xsrc =
+      reinterpret_cast<const uint4*>(k_new + ((int64_t)row * T + (mine < T ? mine : T - 1)) * kHeadDim + g0 * DBAR);
+  uint4 xq = xsrc[0], xnext = xq;
   // the winner of token `tok` (of the workgroup's 256) in group gi
   auto put = [&](int tok, int gi, int win) {
     const int64_t t = wg0 + tok;
@@ -542,7 +546,6 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(4))) void v
     }
   };
   fetch(0);
-  load_x(0);
   commit(0);
   if (tid < kGroups) s_added[tid] = 0;
   __syncthreads();
@@ -552,16 +555,27 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(4))) void v
   uint32_t queued = 0;
   for (int gi = 0; gi < kGroups; ++gi) {
     const int buf = gi & 1;
-    float x2[TT];
+    float x2 = 0.f, x[DBAR];
     v8h bop[TT];
-    uint32_t xw[TT][DBAR / 2];
+    {
+      uint32_t xt[TT][DBAR / 2];
 #pragma unroll
-    for (int tt = 0; tt < TT; ++tt) {
+      for (int d = 0; d < DBAR / 2; ++d) {
+        const uint32_t xw = d == 0 ? xq.x : xq.y;
+        const v2h pair = __builtin_bit_cast(v2h, xw);
+        x2 = __builtin_amdgcn_fdot2(pair, pair, x2, false);
+        x[2 * d] = h2f(xw & 0xffffu);
+        x[2 * d + 1] = h2f(xw >> 16);
+        const Halves h = halves_of(xw);
+        xt[0][d] = h.lo;
+        xt[1][d] = h.hi;
+      }
+      float unused;
 #pragma unroll
-      for (int d = 0; d < DBAR / 2; ++d) xw[tt][d] = xn[tt][d];
-      bop[tt] = am_token<DBAR>(xw[tt], kb, &x2[tt]);
+      for (int tt = 0; tt < TT; ++tt) bop[tt] = am_token<DBAR>(xt[tt], kb, &unused);
     }
-    if (gi + 1 < kGroups) { fetch(gi + 1); load_x(gi + 1); }
+    if (gi + 1 < kGroups) fetch(gi + 1);
+    if (gi % kPer == 0 && gi + kPer < kGroups) xnext = xsrc[gi / kPer + 1];
     float m1[TT], m2[TT];
 #pragma unroll
     for (int tt = 0; tt < TT; ++tt) { m1[tt] = INFINITY; m2[tt] = INFINITY; }
@@ -587,46 +601,43 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(4))) void v
         asm volatile("" : "+v"(m1[tt]));
       }
     }
-    const float cmax2 = fmaxf(fmaxf(s_cmax[buf][0], s_cmax[buf][1]), fmaxf(s_cmax[buf][2], s_cmax[buf][3]));
+    const float cmax2 = am_max(am_max(s_cmax[buf][0], s_cmax[buf][1]), am_max(s_cmax[buf][2], s_cmax[buf][3]));
     if (gi + 1 < kGroups) commit(buf ^ 1);
+    // every lane decides about its own token: its tile's values of the lower and of the upper half wave in one swap
+    static_assert(TT == 2, "a token per lane");
+    const auto p1 = __builtin_amdgcn_permlane32_swap(__float_as_uint(m1[0]), __float_as_uint(m1[1]), false, false);
+    const auto p2 = __builtin_amdgcn_permlane32_swap(__float_as_uint(m2[0]), __float_as_uint(m2[1]), false, false);
+    const float f0 = __uint_as_float(p1[0]), f1 = __uint_as_float(p1[1]);
+    const bool upper = f1 < f0;
+    const float S = x2 + cmax2;
+    const float lim = am_limit(upper ? f1 : f0, x2, S);
+    // a second block within the limit, or values that say nothing
+    const float next = am_min(am_min(__uint_as_float(p2[0]), __uint_as_float(p2[1])), am_max(f0, f1));
+    const bool queue = next <= lim || !(S < 32768.f);
+    // rows of a 32 x 32 result held by a half: 8 (j / 4) + 4 half + j % 4, j < 16; block 2 t + q has j = 8 q .. 8 q + 7
+    const uint32_t blk = (upper ? p1[1] : p1[0]) & 15u;
+    const int tile = (int)(blk >> 1) & (NT - 1), r0 = 16 * (int)(blk & 1u) + (upper ? 4 : 0);
+    typedef float cen_t __attribute__((ext_vector_type(DBAR)));
+    const cen_t* cen = reinterpret_cast<const cen_t*>(sC[buf][cen_at(tile, r0)]);
+    float bd = 0.f;
+    int bj = 0;
 #pragma unroll
-    for (int tt = 0; tt < TT; ++tt) {
-      const Halves a1 = halves_of(__float_as_uint(m1[tt]));
-      const float f0 = __uint_as_float(a1.lo), f1 = __uint_as_float(a1.hi);
-      const bool upper = f1 < f0;
-      const float S = x2[tt] + cmax2;
-      const float lim = am_limit(upper ? f1 : f0, x2[tt], S);
-      const bool rivals = fmaxf(f0, f1) <= lim || m2[tt] <= lim || !(S < 32768.f);
-      float x[DBAR];
+    for (int j = 0; j < 8; ++j) {
+      const int r = 8 * (j >> 2) + (j & 3);
+      const cen_t cv = cen[r];
+      float dist = 0.f;
 #pragma unroll
-      for (int d = 0; d < DBAR; ++d) x[d] = h2f((xw[tt][d >> 1] >> (16 * (d & 1))) & 0xffffu);
-      // rows of a 32 x 32 result held by a half: 8 (j / 4) + 4 half + j % 4, j < 16; block 2 t + q has j = 8 q .. 8 q + 7,
-      // this lane takes the four from 8 q + 4 kb on
-      const uint32_t blk = (upper ? a1.hi : a1.lo) & 15u;
-      const int tile = (int)(blk >> 1) & (NT - 1), r0 = 16 * (int)(blk & 1u) + 8 * kb + (upper ? 4 : 0);
-      float bd = 0.f;
-      int bj = 0;
-#pragma unroll
-      for (int j = 0; j < 4; ++j) {
-        float dist = 0.f;
-#pragma unroll
-        for (int d = 0; d < DBAR; ++d) {
-          const float e = x[d] - sC[buf][cen_at(tile, r0) + j][d];
-          dist = fmaf(e, e, dist);
-        }
-        if (j == 0 || dist < bd) { bd = dist; bj = j; }
+      for (int d = 0; d < DBAR; ++d) {
+        const float e = x[d] - cv[d];
+        dist = fmaf(e, e, dist);
       }
-      const uint32_t mine = (uint32_t)(tile * 32 + r0 + bj);
-      const Halves bh = halves_of(__float_as_uint(bd)), bl = halves_of(mine);
-      const float d0 = __uint_as_float(bh.lo), d1 = __uint_as_float(bh.hi);
-      const uint32_t win = d1 < d0 || (d1 == d0 && bl.hi < bl.lo) ? bl.hi : bl.lo;
-      const bool queue = (halves_of((uint32_t)rivals).lo | halves_of((uint32_t)rivals).hi) != 0;
-      if (kb == 0) {
-        const int tok = w * 64 + 32 * tt + col;
-        if (queue) s_queue[queued + atomicAdd(&s_added[gi], 1u)] = (uint16_t)(tok | gi << 8);
-        else put(tok, gi, (int)win);
-      }
+      if (j == 0 || dist < bd) { bd = dist; bj = r; }
     }
+    if (gi % kPer == kPer - 1) xq = xnext;
+    else xq = DBAR == 4 ? uint4{xq.z, xq.w, 0, 0} : uint4{xq.y, xq.z, xq.w, 0};
+    const int tok = w * 64 + lane;
+    if (queue) s_queue[queued + atomicAdd(&s_added[gi], 1u)] = (uint16_t)(tok | gi << 8);
+    else put(tok, gi, tile * 32 + r0 + bj);
     __syncthreads();
     queued += s_added[gi];
     if (queued > 256 || gi + 1 == kGroups) {                // no room for another group's 256 tokens, or the end
@@ -1095,19 +1106,19 @@ __global__ __launch_bounds__(256) void vq_export_wide_kernel(int g, int64_t cap,
 }
 
 // Whether at most 256 centroids go to vq_assign_small_c_kernel.  It works on whole sets of 2, 4 or 8 tiles, and each of its
-// workgroups takes its 25 - 43 us whatever it holds, so it wants full tiles and a launch that fills the chip several times
-// over; the vector form's time follows the work alone, and falls with the channels per centroid.  Measured speed-ups over
-// the vector form, 8 KV heads, work in 2^27 (token, KV head, group, centroid) combinations:
-//   4 channels: c = 33  0.65 - 0.82 at any work; c = 48  0.82 (2), 1.12 (16); c = 64  1.21 (1.3), 1.49 (16); c = 65 and 129
-//   (half a set)  0.9 (1.3), 1.09 / 1.28 (2), 1.2 / 1.6 (16); c = 256  0.98 (1), 1.11 (1.3), 3.2 (16).
-//   2 channels: c = 48  0.72 - 1.1; c = 64  1.02 (1.3), 1.33 (3), 1.1 (16); c = 65  0.79 - 1.0; c = 80  0.92 (2), 1.16 (3);
-//   c = 129  0.99 (2), 1.1 (4.2); c = 256  0.7 - 0.99 (1 - 1.6), 1.4 (3), 2.4 (16).
+// workgroups takes its 18 - 33 us whatever it holds, so it wants a launch that fills the chip; the vector form's time
+// follows the work alone, and falls with the channels per centroid.  Measured speed-ups over the vector form, 8 KV heads,
+// work in 2^27 (token, KV head, group, centroid) combinations (in brackets):
+//   4 channels: c = 33  0.88 (0.5), 1.24 (1.0); c = 48  0.87 (0.5), 1.08 (0.75), 1.6 (1.5); c = 64  0.95 (0.5), 1.37 (1);
+//   c = 65  0.9 (0.7), 1.17 (1); c = 96  0.88 (0.5), 1.08 (0.75); c = 128  0.85 (0.5), 1.4 (1); c = 129  0.85 (0.7), 1.06 (1);
+//   c = 200  0.93 (0.8), 1.23 (1.1); c = 256  0.95 (0.7), 1.16 (1), 3.9 (8).
+//   2 channels: c = 33  0.9 (0.7), 1.06 (1); c = 64  0.86 (0.5), 1.26 (1); c = 65  0.8 (0.7), 1.04 (1); c = 128  0.85 (0.7),
+//   1.22 (1); c = 129  0.88 (1), 1.0 (1.4), 1.3 (2); c = 200  0.9 (1.1), 1.2 (1.6); c = 256  0.83 (1), 1.12 (1.4), 2.5 (4).
 static bool assign_by_tiles(int g, int c, int64_t work, int64_t T) {
-  if (T < 256 || c > kAsCodewords) return false;
-  const int set = c <= 64 ? 64 : c <= 128 ? 128 : 256;
+  if (T < 256 || c <= 32 || c > kAsCodewords) return false;
   const int64_t unit = (int64_t)1 << 25;                    // a quarter of 2^27
-  if (g == 32) return c >= 56 && work >= (8 * c >= 7 * set ? 5 : 8) * unit;
-  return (c == 64 || c >= 80) && work >= (4 * c >= 3 * set ? 12 : 17) * unit;
+  if (g == 32) return work >= (c <= 64 ? 3 : 4) * unit;
+  return work >= (c <= 128 ? 4 : 6) * unit;
 }
 
 // Whether more than 256 centroids and 9 or more tokens go to vq_assign_mfma_kernel: always from 257 tokens on, below by an

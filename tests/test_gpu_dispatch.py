@@ -327,7 +327,8 @@ def test_score_topk_on_both_sides_of_the_short_row_line(B, oracle, bits, gs, n):
     (32, 1024, 1, 5, 3), (32, 2048, 1, 700, 1), (64, 2049, 4, 260, 1), (32, 8192, 1, 150, 2), (64, 8191, 1, 33, 1),
     (32, 56, 1, 18800, 8), (32, 64, 1, 10300, 8), (32, 65, 1, 16200, 8), (32, 128, 4, 5200, 8), (32, 129, 4, 4100, 16),
     (32, 255, 1, 2600, 8), (32, 256, 4, 2571, 8), (64, 64, 1, 12400, 8), (64, 80, 1, 14000, 8), (64, 160, 1, 7000, 8),
-    (64, 256, 4, 3100, 8), (64, 257, 1, 40, 32), (32, 300, 1, 65, 128), (64, 700, 1, 129, 64)])
+    (64, 256, 4, 3100, 8), (64, 257, 1, 40, 32), (32, 300, 1, 65, 128), (64, 700, 1, 129, 64),
+    (32, 33, 1, 12100, 8), (32, 48, 4, 8111, 8), (32, 160, 1, 3333, 8), (64, 33, 4, 8193, 8), (64, 129, 1, 3060, 8)])
 def test_bulk_assignment_equals_the_exhaustive_chain(B, g, c, G, T, rows):
     """hca_vq_assign: the matrix-core forms (up to 256 centroids, more than 256) and the vector forms give the indices of
     single-token calls, whose kernel evaluates the exact chain for every centroid; awkward tokens and centroids included."""
