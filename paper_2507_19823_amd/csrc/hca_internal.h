@@ -33,10 +33,8 @@ struct Tuning {
   int score_depth = 0;     // blocks fetched ahead per wave (4 or 8; 0 = 8 from 8 blocks per wave on, else 4)
   int host_spin_us = 100;  // how long the host-sum workers poll for the next call before they sleep
   int host_isa = 0;        // host_chunk_sum: 0 = the widest vector form the CPU has, 2 = the AVX2 form
-  int select_wg = 0;       // threads per workgroup of the selection over the candidate lists: 1024 (pairs staged in
-                           // LDS, needs a whole compute unit) or 256 (pairs read from L2, fits beside a running
-                           // scan, but measured slower inside a decode step: its dependent passes crawl when a
-                           // scan keeps the memory system busy); 0 = 1024
+  int select_wg = 0;       // threads per workgroup of the selection over the candidate lists, 256 or 1024 (0 = 1024 for
+                           // a call, 512 in a step driver: see tk_resolve_emit_body)
 };
 Tuning& tuning();
 // Blocks per wave of the key scan.  The lower bound sizes the per-wave buffers of a launch (wall-clock stamps,
@@ -155,7 +153,7 @@ int32_t launch_select_rescan_pair(const Layout& L, const void* const kcache[2], 
                                   const int64_t nmax[2], const SelectOut so[2], hipStream_t st);
 int32_t launch_select_finish_pair(const Layout& L, const void* const kcache[2], const void* const q[2], const NRes nr[2],
                                   const int64_t nmax[2], int32_t k, int32_t* const idx[2], int32_t* const count[2],
-                                  void* const ws[2], hipStream_t st, bool small_wg = false);
+                                  void* const ws[2], hipStream_t st, int wg);
 // the SelectOut view of a selection workspace for rows of at most nmax_before slots (before the step's append)
 SelectOut select_view(const Layout& L, void* ws, int64_t nmax_before, int32_t k);
 int32_t launch_select_scan_step(const Layout& L, const void* kcache, const void* q, const NRes& nr, int64_t nmax,
@@ -170,7 +168,7 @@ int32_t launch_select_threshold(const Layout& L, const void* kcache, const void*
 int32_t launch_select_begin(const Layout& L, const void* kcache, const void* q, const NRes& nr, int64_t nmax, int32_t k,
                             void* ws, hipStream_t st, uint64_t* stamps = nullptr);
 int32_t launch_select_finish(const Layout& L, const void* kcache, const void* q, const NRes& nr, int64_t nmax, int32_t k,
-                             int32_t* idx, int32_t* count, void* ws, hipStream_t st, bool small_wg = false);
+                             int32_t* idx, int32_t* count, void* ws, hipStream_t st, int wg);
 int32_t launch_select_monitor(const Layout& L, void* ws, int32_t* out, int reset, hipStream_t st);
 int32_t launch_select_report(const Layout& L, const NRes& nr, int64_t nmax, void* ws, int32_t* candidates,
                              int32_t* rescanned, hipStream_t st);

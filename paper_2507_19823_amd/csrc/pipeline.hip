@@ -426,6 +426,7 @@ int32_t hca_pipeline_step(hca_pipeline* p, hca_layer* layers, int64_t* n_residen
     return HCA_OK;
   };
   const bool fused = p->d.fused_select != 0;
+  const int select_wg = p->tune.select_wg > 0 ? p->tune.select_wg : 512;   // it runs beside the next scan
   // Fused selection: the scan stream carries one launch per layer.  The launch of layer l is its selecting scan
   // plus a few workgroups for the layers behind it: the threshold of layer l + 1 (from samples the previous launch
   // took) with the append of its key, and the sampling of layer l + 2.  The first two layers' samples and the first
@@ -676,7 +677,7 @@ int32_t hca_pipeline_step(hca_pipeline* p, hca_layer* layers, int64_t* n_residen
       int32_t* const idx2[2] = {idx_l, idx_of(l + 1)};
       int32_t* const cnt2[2] = {count_l, count_of(l + 1)};
       void* const ws2[2] = {p->d.ws_select[s3], p->d.ws_select[s3b]};
-      rc = launch_select_finish_pair(L, kc2, q2, nr2, nm2, k, idx2, cnt2, ws2, sb, p->tune.select_wg == 256);
+      rc = launch_select_finish_pair(L, kc2, q2, nr2, nm2, k, idx2, cnt2, ws2, sb, select_wg);
       if (rc != HCA_OK) return rc;
       if (p->sel_waits) {
         HCA_HIP(hipEventRecord(p->sel_free[s3], sb));
@@ -689,7 +690,7 @@ int32_t hca_pipeline_step(hca_pipeline* p, hca_layer* layers, int64_t* n_residen
     } else {
     if (!own_idx && p->slot_free[s4] != nullptr) HCA_HIP(hipStreamWaitEvent(sb, p->slot_free[s4], 0));
     rc = fused ? launch_select_finish(L, ly.kcache, ly.q, nr, nmax, k, idx_l, count_l, p->d.ws_select[s3], sb,
-                                      p->tune.select_wg == 256)
+                                      select_wg)
          : p->d.topp_tau > 0.0
              ? launch_topp(L, p->d.sel[s3], nr, nmax, sm_scale, p->d.topp_tau, k, idx_l, count_l, nullptr,
                            p->d.ws_topk, sb)

@@ -333,7 +333,9 @@ __global__ __launch_bounds__(256) void score_failed_rows_kernel(Layout L, const 
   }
 }
 
-// The same for the two layers of a paired launch: grid.y = 2 x rows.
+// The same for the two layers of a paired launch: grid.y = 2 x rows.  At most 128 registers, so that a workgroup fits into
+// the room of one finished scan workgroup (128 of them): with 160 it waited for two on one compute unit, 165 us beside a
+// scan launch of 195 with not one row to do.
 struct RescanSide {
   const uint8_t* kcache;
   const uint16_t* q;
@@ -351,7 +353,7 @@ __device__ __forceinline__ void rescan_side(const Layout& L, const RescanSide& s
   }
 }
 template <int BITS, int U>
-__global__ __launch_bounds__(256) void score_failed_rows_pair_kernel(Layout L, RescanSide a, RescanSide b) {
+__global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(4))) void score_failed_rows_pair_kernel(Layout L, RescanSide a, RescanSide b) {
   if ((int)blockIdx.y < L.rows) rescan_side<BITS, U>(L, a, (int)blockIdx.y);
   else rescan_side<BITS, U>(L, b, (int)blockIdx.y - L.rows);
 }

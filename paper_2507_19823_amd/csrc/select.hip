@@ -1166,12 +1166,8 @@ static int32_t launch_row_select(const float* vals, int64_t stride, int rows, in
 //   position(j) = #{i < j : key_i > T} + min(#{i < j : key_i == T}, r_eq)
 // A row with fewer pairs than it has to select is marked for a second scan without threshold; `only_failed`
 // launches handle exactly those rows.
-constexpr int kFullLds = 16384;     // pairs held in LDS (128 KiB, dynamic)
-constexpr int kSearchMax = 65536;   // pairs still addressed by position when they do not fit LDS
-constexpr int kSmallLds = 12288;    // pairs the four-wave form of the selection holds in LDS (96 KiB) ...
-// ... when the expected list fits: k <= 4096 (the scan lets about 2.7 times k pairs per row through); longer lists
-// are read where they lie, and the launch then asks for no dynamic LDS at all
-static uint32_t small_stage_cap(int32_t k) { return k <= 4096 ? (uint32_t)kSmallLds : 0u; }
+constexpr int kHeldPairs = 16384;   // pairs per row held in registers
+constexpr int kSearchMax = 65536;   // pairs still addressed by position when they are not held
 
 // counter updates when the lanes of a wave share a handful of bins (the leading bits of keys that all lie
 // just above one threshold): one atomic per distinct bin for the first few, single updates for the rest
@@ -1207,72 +1203,30 @@ __device__ __forceinline__ uint32_t block_scan_excl(uint32_t v, uint32_t* wsum /
   return base + inc - v;
 }
 
-// NT = 1024: one large workgroup per row with the row's pairs staged in up to 128 KiB of LDS - the quickest form
-// when the chip has a compute unit to spare.  NT = 256: four waves, one per SIMD, with at most 128 registers each
-// and up to 96 KiB of LDS for the pairs (stage_cap of them; longer lists are read where they lie, in L2): this
-// one fits into the room that a single finished workgroup of a key scan leaves on a compute unit, where the large
-// form has to wait until a scan launch has drained from a whole unit - beside back-to-back scans that is one
-// chance per launch.  Same result.
 template <int NT>
-__device__ __forceinline__ void tk_resolve_emit_body(const int64_t chunk, const int nchunks, const int64_t want,
-                                                     const SelectOut& so, const int32_t k, int32_t* __restrict__ idx,
-                                                     int32_t* __restrict__ count, const bool only_failed, const int row,
-                                                     const uint32_t stage_cap) {
+struct ResolveShared {
+  uint32_t h[kBins12], off[1025], wsum[16];
+  uint16_t cmap[1024];                     // chunk of position 16 i
+  uint32_t s_prefix, s_rem, s_cb;
+};
+
+// The selection proper, once the chunks' offsets are in sh.off.  HELD: every pair's key in a register.
+template <int NT, bool HELD>
+__device__ __forceinline__ void tk_resolve_pairs(ResolveShared<NT>& sh, const int64_t chunk, const int nchunks,
+                                                 const int64_t want, const SelectOut& so, const int32_t k,
+                                                 int32_t* __restrict__ idx, int32_t* __restrict__ count, const int row,
+                                                 const uint32_t total) {
   constexpr int NW = NT / 64;              // waves
   constexpr int PER = 1024 / NT;           // chunks (and 10-bit bins) per thread
-  extern __shared__ uint2 lc[];
-  __shared__ uint32_t h[kBins12], off[1025], wsum[16];
-  __shared__ uint32_t s_prefix, s_rem, s_cb;
+  auto& h = sh.h;
+  auto& off = sh.off;
+  auto& wsum = sh.wsum;
+  auto& cmap = sh.cmap;
+  uint32_t &s_prefix = sh.s_prefix, &s_rem = sh.s_rem, &s_cb = sh.s_cb;
   const int tid = threadIdx.x;
-  uint32_t* spec = so.spec + 4 * row;
-  if (want <= 0) {
-    if (tid == 0 && !only_failed) count[row] = 0;
-    return;
-  }
-  if (only_failed && spec[1] == 0) return;
-  // off[c] = pairs in the chunks before c; off[1024] = all of them.  Thread tid owns chunks [PER tid, PER tid + PER)
-  {
-    uint32_t mine[PER], sum = 0;
-#pragma unroll
-    for (int x = 0; x < PER; ++x) {
-      const int c = tid * PER + x;
-      mine[x] = c < nchunks ? so.ncand[(int64_t)row * kSelectMaxChunks + c] : 0;
-      sum += mine[x];
-    }
-    uint32_t before = block_scan_excl<NT>(sum, wsum);
-#pragma unroll
-    for (int x = 0; x < PER; ++x) { off[tid * PER + x] = before; before += mine[x]; }
-    if (tid == NT - 1) off[1024] = before;
-  }
-  __syncthreads();
-  const uint32_t total = off[1024];
-  if (!only_failed && tid == 0 && so.mon != nullptr) {      // one workgroup per row and launches in stream order: no atomics
-    uint32_t* m = so.mon + 4 * row;
-    m[0] += 1;
-    m[1] = total < m[1] ? total : m[1];
-    m[2] = total > m[2] ? total : m[2];
-    if (total < (uint32_t)want) m[3] += 1;
-  }
-  if (total < (uint32_t)want) {
-    // the sampled threshold was too high: scan the row again, with the second threshold if the first scan counted
-    // enough slots at or above it, else without one
-    uint32_t sum1 = 0;
-#pragma unroll
-    for (int x = 0; x < PER; ++x) {
-      const int c = tid * PER + x;
-      sum1 += c < nchunks ? so.n1[(int64_t)row * kSelectMaxChunks + c] : 0;
-    }
-    const uint32_t before1 = block_scan_excl<NT>(sum1, wsum);
-    if (tid == NT - 1) {
-      const uint32_t enough = before1 + sum1 >= (uint32_t)want;
-      spec[0] = enough && spec[1] == 0 ? spec[2] : 0;       // (a second failure cannot happen: the count is exact)
-      spec[1] = 1;
-    }
-    return;
-  }
+  const uint32_t* spec = so.spec + 4 * row;
   const uint2* gl = so.lists + (int64_t)row * so.row_entries;
-  const bool staged = total <= stage_cap;                   // stage_cap pairs of dynamic LDS came with the launch
-  // beyond the LDS stage: up to kSearchMax pairs are still addressed by their position in slot order (short lists:
+  // beyond kHeldPairs: up to kSearchMax pairs are still addressed by their position in slot order (short lists:
   // walking them chunk by chunk would cost a memory round trip per chunk), more than that are walked chunk by chunk
   const bool by_position = total <= (uint32_t)kSearchMax;
   // pair p of the row in slot order: the chunk c with off[c] <= p < off[c + 1], entry p - off[c] of its list
@@ -1285,61 +1239,79 @@ __device__ __forceinline__ void tk_resolve_emit_body(const int64_t chunk, const 
   };
   const int lane = tid & 63, wv = tid >> 6;
   uint32_t kmax = 0;                                        // largest key this thread has seen
-  if (staged) {
-    // 16 lanes per chunk: the first 32 pairs of 64 chunks per wave in 32 loads, all in flight together (nearly
-    // all lists are shorter than that); longer lists follow.  Wave wv takes chunks 64 (wv + NW rep) .. + 63
-    const int sub = lane >> 4, i = lane & 15;
-#pragma unroll 1
-    for (int rep = 0; rep < 16 / NW; ++rep) {
-      const int cb0 = (wv + NW * rep) * 64;
-      uint2 x[16], y[16];
+  constexpr int kPer = kHeldPairs / NT, kStep = NT == 512 ? 4 : 8;
+  const uint32_t per = (total + NT - 1) / NT;               // HELD: pairs per thread ...
+  const uint32_t pos0 = (uint32_t)wv * 64 * per + lane;     // ... the first one's position, 64 apart
+  uint32_t held[HELD ? kPer : 1];                           // their keys (0: no pair; no finite score has it)
+  // this thread's pairs u0 .. u0 + 7: their places in the lists (or -1)
+  auto locate = [&](int u0, uint32_t (&at)[kStep]) {
+    uint32_t c[kStep], first = pos0 + 64 * u0;
+    asm volatile("" : "+v"(first));        // (or every call's comparisons are kept for the next one: registers)
 #pragma unroll
-      for (int j = 0; j < 16; ++j) {
-        const int c = cb0 + j * 4 + sub;
-        const uint32_t m = off[c + 1] - off[c];
-        x[j] = (uint32_t)i < m ? gl[(int64_t)c * chunk + i] : uint2{0, 0};
-        y[j] = (uint32_t)i + 16 < m ? gl[(int64_t)c * chunk + i + 16] : uint2{0, 0};
-      }
+    for (int u = 0; u < kStep; ++u) {
+      const uint32_t p = first + 64 * u;
+      c[u] = cmap[p < total ? p >> 4 : 0];
+    }
+    bool more = true;
+    while (__ballot(more) != 0) {
+      more = false;
 #pragma unroll
-      for (int j = 0; j < 16; ++j) {
-        const int c = cb0 + j * 4 + sub;
-        const uint32_t o = off[c], m = off[c + 1] - o;
-        if ((uint32_t)i < m) { lc[o + i] = x[j]; kmax = x[j].x > kmax ? x[j].x : kmax; }
-        if ((uint32_t)i + 16 < m) { lc[o + i + 16] = y[j]; kmax = y[j].x > kmax ? y[j].x : kmax; }
-      }
-#pragma unroll 1
-      for (int j = 0; j < 16; ++j) {
-        const int c = cb0 + j * 4 + sub;
-        const uint32_t o = off[c], m = off[c + 1] - o;
-        for (uint32_t e = 32 + i; e < m; e += 16) {
-          const uint2 z = gl[(int64_t)c * chunk + e];
-          lc[o + e] = z;
-          kmax = z.x > kmax ? z.x : kmax;
-        }
+      for (int u = 0; u < kStep; ++u) {
+        const uint32_t p = first + 64 * u;
+        const bool on = p < total && off[c[u] + 1] <= p;
+        c[u] += on;
+        more |= on;
       }
     }
+#pragma unroll
+    for (int u = 0; u < kStep; ++u) {
+      const uint32_t p = first + 64 * u;
+      at[u] = (uint32_t)(u0 + u) < per && p < total ? c[u] * (uint32_t)chunk + (p - off[c[u]]) : 0xffffffffu;
+    }
+  };
+  if constexpr (HELD) {
+    // chunk of every 16th position, from there on to the chunk of each position
+    for (int c = tid; c < 1024; c += NT) {
+      const uint32_t end = off[c + 1];
+      for (uint32_t i = (off[c] + 15) >> 4; i * 16 < end; ++i) cmap[i] = (uint16_t)c;
+    }
+    __syncthreads();
+#pragma unroll
+    for (int u0 = 0; u0 < kPer; u0 += kStep) {
+      uint32_t at[kStep];
+      if ((uint32_t)u0 < per) {
+        locate(u0, at);
+#pragma unroll
+        for (int u = 0; u < kStep; ++u) held[u0 + u] = at[u] != 0xffffffffu ? gl[at[u]].x : 0;
+      } else {
+#pragma unroll
+        for (int u = 0; u < kStep; ++u) held[u0 + u] = 0;
+      }
+    }
+#pragma unroll
+    for (int u = 0; u < kPer; ++u) kmax = held[u] > kmax ? held[u] : kmax;
   }
   __syncthreads();
   // visit(f): f(key, slot, exists) over every pair of the row, in any order, called by all lanes of a wave
-  // together.  By position: strided over the LDS copy (or, unstaged, through fetch, four pairs in flight per
-  // thread).  Otherwise the lists where they are: wave w takes chunks w, w + NW, ... and reads each list 1024
+  // together.  HELD: from the registers.  By position: through fetch, four pairs in flight per thread.  Otherwise the lists where they are: wave w takes chunks w, w + NW, ... and reads each list 1024
   // pairs at a time (sixteen loads in flight per lane).
   auto visit = [&](auto&& f) {
-    if (by_position) {
-      if (staged) {
-        for (uint32_t i0 = 0; i0 < total; i0 += NT) {
-          const bool hit = i0 + tid < total;
-          const uint2 x = lc[hit ? i0 + tid : 0];
-          f(x.x, x.y, hit);
-        }
-      } else {
-        for (uint32_t i0 = 0; i0 < total; i0 += 4 * NT) {
-          uint2 x[4];
+    if constexpr (HELD) {
 #pragma unroll
-          for (int v = 0; v < 4; ++v) x[v] = fetch(i0 + v * NT + tid < total ? i0 + v * NT + tid : 0);
+      for (int u0 = 0; u0 < kPer; u0 += kStep) {
+        if ((uint32_t)u0 >= per) break;
+        uint32_t none = 0;
+        asm volatile("" : "+s"(none));                      // (no pass's comparisons are kept for the next: registers)
 #pragma unroll
-          for (int v = 0; v < 4; ++v) f(x[v].x, x[v].y, i0 + v * NT + tid < total);
-        }
+        for (int u = 0; u < kStep; ++u) f(held[u0 + u], 0u, held[u0 + u] != none);
+      }
+    } else if (by_position) {
+      for (uint32_t i0 = 0; i0 < total; i0 += 4 * NT) {
+        uint2 x[4];
+#pragma unroll
+        for (int v = 0; v < 4; ++v) x[v] = fetch(i0 + v * NT + tid < total ? i0 + v * NT + tid : 0);
+#pragma unroll
+        for (int v = 0; v < 4; ++v) f(x[v].x, x[v].y, i0 + v * NT + tid < total);
       }
     } else {
       for (int c = wv; c < nchunks; c += NW) {
@@ -1355,7 +1327,7 @@ __device__ __forceinline__ void tk_resolve_emit_body(const int64_t chunk, const 
       }
     }
   };
-  if (!staged) visit([&](uint32_t key, uint32_t, bool hit) { if (hit && key > kmax) kmax = key; });
+  if (!HELD) visit([&](uint32_t key, uint32_t, bool hit) { if (hit && key > kmax) kmax = key; });
 #pragma unroll
   for (int o = 32; o >= 1; o >>= 1) { const uint32_t v = __shfl_xor(kmax, o); kmax = v > kmax ? v : kmax; }
   if (lane == 0) wsum[wv] = kmax;
@@ -1366,7 +1338,7 @@ __device__ __forceinline__ void tk_resolve_emit_body(const int64_t chunk, const 
   // digits of d found so far, s = the number of bits of d below them; rem = how many are still to take among the
   // pairs whose d starts with pd, cb = how many such pairs there are.  The first level spreads the occupied
   // range of d over 4096 bins, so the counters are not fought over although the keys share their leading bits.
-  const uint32_t base = spec[0];
+  const uint32_t base = (uint32_t)__builtin_amdgcn_readfirstlane((int)spec[0]);
   const uint32_t maxd = kmax - base;
   int sbits = 32 - __clz((int)(maxd | 1)) - 12;             // bits of maxd beyond the 12 of the first level
   if (sbits < 0) sbits = 0;
@@ -1374,7 +1346,7 @@ __device__ __forceinline__ void tk_resolve_emit_body(const int64_t chunk, const 
   {
     for (int i = tid; i < kBins12; i += NT) h[i] = 0;
     __syncthreads();
-    visit([&](uint32_t key, uint32_t, bool hit) { lds_count(h, (key - base) >> sbits, hit, !staged); });
+    visit([&](uint32_t key, uint32_t, bool hit) { lds_count(h, (key - base) >> sbits, hit, !HELD); });
     __syncthreads();
     constexpr int BPT = kBins12 / NT;                       // bins per thread, from the top
     uint32_t hb[BPT], sum = 0;
@@ -1409,8 +1381,10 @@ __device__ __forceinline__ void tk_resolve_emit_body(const int64_t chunk, const 
       uint32_t* sl = h;
       if (tid == 0) s_cb = 0;
       __syncthreads();
+      uint32_t base1 = (uint32_t)__builtin_amdgcn_readfirstlane((int)base);
+      asm volatile("" : "+s"(base1));                       // (nor the differences)
       visit([&](uint32_t key, uint32_t, bool hit) {
-        if (hit && ((key - base) >> sbits) == pd) sl[atomicAdd(&s_cb, 1u)] = key;
+        if (hit && ((key - base1) >> sbits) == pd) sl[atomicAdd(&s_cb, 1u)] = key;
       });
       __syncthreads();
       for (uint32_t me = (uint32_t)tid; me < cb; me += NT) {
@@ -1431,9 +1405,11 @@ __device__ __forceinline__ void tk_resolve_emit_body(const int64_t chunk, const 
     const int ns = sbits > 10 ? sbits - 10 : 0, width = sbits - ns;
     for (int i = tid; i < 1024; i += NT) h[i] = 0;
     __syncthreads();
+    uint32_t base1 = (uint32_t)__builtin_amdgcn_readfirstlane((int)base);
+    asm volatile("" : "+s"(base1));
     visit([&](uint32_t key, uint32_t, bool hit) {
-      const uint32_t d = key - base;
-      lds_count(h, (d >> ns) & ((1u << width) - 1), hit && (d >> sbits) == pd, !staged);
+      const uint32_t d = key - base1;
+      lds_count(h, (d >> ns) & ((1u << width) - 1), hit && (d >> sbits) == pd, !HELD);
     });
     __syncthreads();
     uint32_t mine[PER], msum = 0;                           // thread tid owns bins 1023 - (PER tid + x)
@@ -1458,19 +1434,51 @@ __device__ __forceinline__ void tk_resolve_emit_body(const int64_t chunk, const 
   }
   int32_t* out = idx + (int64_t)row * k;
   if (tid == 0) count[row] = (int32_t)want;
+  if constexpr (HELD) {
+    // the wave's pairs above and equal to T, those of the waves before, then every pair's place
+    const uint64_t lt = (1ull << lane) - 1;
+    uint32_t ng = 0, ne = 0;
+#pragma unroll
+    for (int u0 = 0; u0 < kPer; u0 += kStep) {
+      if ((uint32_t)u0 >= per) break;
+#pragma unroll
+      for (int u = 0; u < kStep; ++u) {
+        ng += (uint32_t)__popcll(__ballot(held[u0 + u] > T));
+        ne += (uint32_t)__popcll(__ballot(held[u0 + u] == T));
+      }
+    }
+    if (lane == 0) { wsum[wv] = ng; h[wv] = ne; }
+    __syncthreads();
+    uint32_t pg = 0, pe = 0;
+    for (int x = 0; x < wv; ++x) { pg += wsum[x]; pe += h[x]; }
+#pragma unroll
+    for (int u0 = 0; u0 < kPer; u0 += kStep) {
+      if ((uint32_t)u0 >= per) break;
+      uint32_t at[kStep];
+      locate(u0, at);
+      uint32_t slot[kStep];
+#pragma unroll
+      for (int u = 0; u < kStep; ++u) slot[u] = held[u0 + u] >= T ? gl[at[u]].y : 0;    // (T > 0: a pair)
+#pragma unroll
+      for (int u = 0; u < kStep; ++u) {
+        const bool fg = held[u0 + u] > T, fe = held[u0 + u] == T;
+        const uint64_t mg = __ballot(fg), me = __ballot(fe);
+        const uint32_t gb = pg + (uint32_t)__popcll(mg & lt), eb = pe + (uint32_t)__popcll(me & lt);
+        if (fg) out[gb + (eb < req ? eb : req)] = (int32_t)slot[u];
+        else if (fe && eb < req) out[gb + eb] = (int32_t)slot[u];
+        pg += (uint32_t)__popcll(mg);
+        pe += (uint32_t)__popcll(me);
+      }
+    }
+    return;
+  }
   if (by_position) {
     // ordered part by position (slot order): thread tid owns the run [tid * E, tid * E + E)
     const uint32_t E = (total + NT - 1) / NT;
     const uint32_t p0 = (uint32_t)tid * E;
     const uint32_t p1 = p0 + E < total ? p0 + E : total;
     uint32_t ng = 0, ne = 0;
-    if (staged) {
-      for (uint32_t p = p0; p < p1; ++p) {
-        const uint32_t key = lc[p].x;
-        ng += key > T;
-        ne += key == T;
-      }
-    } else if (p0 < p1) {
+    if (p0 < p1) {
       // the run lies in consecutive entries of consecutive chunks' lists: one search for its start, then a walk
       uint32_t c = 0;
 #pragma unroll
@@ -1487,13 +1495,7 @@ __device__ __forceinline__ void tk_resolve_emit_body(const int64_t chunk, const 
     }
     uint32_t rg = block_scan_excl<NT>(ng, wsum);            // pairs above T on lower slots
     uint32_t re = block_scan_excl<NT>(ne, wsum);            // pairs equal to T on lower slots
-    if (staged) {
-      for (uint32_t p = p0; p < p1; ++p) {
-        const uint2 x = lc[p];
-        if (x.x > T) { out[rg + (re < req ? re : req)] = (int32_t)x.y; ++rg; }
-        else if (x.x == T) { if (re < req) out[rg + re] = (int32_t)x.y; ++re; }
-      }
-    } else if (p0 < p1) {
+    if (p0 < p1) {
       uint32_t c = 0;
 #pragma unroll
       for (int s = 512; s >= 1; s >>= 1)
@@ -1574,12 +1576,81 @@ __device__ __forceinline__ void tk_resolve_emit_body(const int64_t chunk, const 
   }
 }
 
+// One workgroup per row; the keys of the row's pairs (up to 16384 of them) are held in registers, wave w those of the
+// positions [64 w E, 64 (w + 1) E), lane l its positions l, l + 64, ...: the loads are whole lines, no pass over the pairs
+// touches memory, and the order of the slots is that of (wave, u, lane), so ranks are popcounts of ballots.  What bounds it
+// is the chain of passes and barriers.  8 rows of 14 Ki pairs, alone: 28 us with the pairs in 128 KiB of LDS, 21 so.
+// NT = 1024 is the quickest where the chip is free (2 Mi slots x 8, k = 8192: 172 -> 165 us for the call).  Beside a
+// running scan what counts is the room it needs: a scan workgroup has 128 registers and 33 KiB, four of them fill a compute
+// unit, and another launch's workgroup only gets in where one of them ends.  NT = 512 has 64 registers (two waves per SIMD)
+// and 23 KiB: 62 us from launch to end beside a scan where the 1024-thread form waited for the scan's end, 200 us; four
+// layers of 1 Mi tokens in a step driver 810 -> 720 us, eight 1315 -> 1087.  NT = 256 (48 us alone) is for launches that
+// nearly always find nothing to do.  All give the same result.
 template <int NT>
-__global__ __launch_bounds__(NT) void tk_resolve_emit(int64_t chunk, int nchunks, int n_kv_heads, SelRows sr,
+__device__ __forceinline__ void tk_resolve_emit_body(const int64_t chunk, const int nchunks, const int64_t want,
+                                                     const SelectOut& so, const int32_t k, int32_t* __restrict__ idx,
+                                                     int32_t* __restrict__ count, const bool only_failed, const int row) {
+  constexpr int PER = 1024 / NT;           // chunks per thread
+  __shared__ ResolveShared<NT> sh;
+  auto& off = sh.off;
+  auto& wsum = sh.wsum;
+  const int tid = threadIdx.x;
+  uint32_t* spec = so.spec + 4 * row;
+  if (want <= 0) {
+    if (tid == 0 && !only_failed) count[row] = 0;
+    return;
+  }
+  if (only_failed && spec[1] == 0) return;
+  // off[c] = pairs in the chunks before c; off[1024] = all of them.  Thread tid owns chunks [PER tid, PER tid + PER)
+  {
+    uint32_t mine[PER], sum = 0;
+#pragma unroll
+    for (int x = 0; x < PER; ++x) {
+      const int c = tid * PER + x;
+      mine[x] = c < nchunks ? so.ncand[(int64_t)row * kSelectMaxChunks + c] : 0;
+      sum += mine[x];
+    }
+    uint32_t before = block_scan_excl<NT>(sum, wsum);
+#pragma unroll
+    for (int x = 0; x < PER; ++x) { off[tid * PER + x] = before; before += mine[x]; }
+    if (tid == NT - 1) off[1024] = before;
+  }
+  __syncthreads();
+  const uint32_t total = off[1024];
+  if (!only_failed && tid == 0 && so.mon != nullptr) {      // one workgroup per row and launches in stream order: no atomics
+    uint32_t* m = so.mon + 4 * row;
+    m[0] += 1;
+    m[1] = total < m[1] ? total : m[1];
+    m[2] = total > m[2] ? total : m[2];
+    if (total < (uint32_t)want) m[3] += 1;
+  }
+  if (total < (uint32_t)want) {
+    // the sampled threshold was too high: scan the row again, with the second threshold if the first scan counted
+    // enough slots at or above it, else without one
+    uint32_t sum1 = 0;
+#pragma unroll
+    for (int x = 0; x < PER; ++x) {
+      const int c = tid * PER + x;
+      sum1 += c < nchunks ? so.n1[(int64_t)row * kSelectMaxChunks + c] : 0;
+    }
+    const uint32_t before1 = block_scan_excl<NT>(sum1, wsum);
+    if (tid == NT - 1) {
+      const uint32_t enough = before1 + sum1 >= (uint32_t)want;
+      spec[0] = enough && spec[1] == 0 ? spec[2] : 0;       // (a second failure cannot happen: the count is exact)
+      spec[1] = 1;
+    }
+    return;
+  }
+  if (total <= (uint32_t)kHeldPairs) tk_resolve_pairs<NT, true>(sh, chunk, nchunks, want, so, k, idx, count, row, total);
+  else tk_resolve_pairs<NT, false>(sh, chunk, nchunks, want, so, k, idx, count, row, total);
+}
+
+template <int NT>
+__global__ __launch_bounds__(NT) __attribute__((amdgpu_waves_per_eu(NT == 512 ? 8 : 4))) void tk_resolve_emit(int64_t chunk, int nchunks, int n_kv_heads, SelRows sr,
                                                       SelectOut so, int32_t k, int32_t* __restrict__ idx,
-                                                      int32_t* __restrict__ count, bool only_failed, uint32_t stage_cap) {
+                                                      int32_t* __restrict__ count, bool only_failed) {
   tk_resolve_emit_body<NT>(chunk, nchunks, sr.want[blockIdx.x / n_kv_heads], so, k, idx, count, only_failed,
-                           (int)blockIdx.x, stage_cap);
+                           (int)blockIdx.x);
 }
 
 // The selections of two layers in one launch (the step driver's paired form): workgroups [0, rows) take the
@@ -1593,16 +1664,19 @@ struct ResolveSide {
   int32_t* count;
 };
 template <int NT>
-__global__ __launch_bounds__(NT) void tk_resolve_emit_pair(ResolveSide a, ResolveSide b, int rows, int n_kv_heads,
-                                                           int32_t k, bool only_failed, uint32_t stage_cap) {
-  if ((int)blockIdx.x < rows) {
-    tk_resolve_emit_body<NT>(a.chunk, a.nchunks, a.want[blockIdx.x / n_kv_heads], a.so, k, a.idx, a.count, only_failed,
-                             (int)blockIdx.x, stage_cap);
-  } else {
-    const int row = (int)blockIdx.x - rows;
-    tk_resolve_emit_body<NT>(b.chunk, b.nchunks, b.want[row / n_kv_heads], b.so, k, b.idx, b.count, only_failed, row,
-                             stage_cap);
-  }
+__global__ __launch_bounds__(NT) __attribute__((amdgpu_waves_per_eu(NT == 512 ? 8 : 4))) void tk_resolve_emit_pair(ResolveSide a, ResolveSide b, int rows, int n_kv_heads,
+                                                           int32_t k, bool only_failed) {
+  const bool first = (int)blockIdx.x < rows;                // (the body stands once: its scalars fill the registers)
+  const int row = first ? (int)blockIdx.x : (int)blockIdx.x - rows, seq = row / n_kv_heads;
+  SelectOut so;
+  so.spec = first ? a.so.spec : b.so.spec;
+  so.ncand = first ? a.so.ncand : b.so.ncand;
+  so.n1 = first ? a.so.n1 : b.so.n1;
+  so.lists = first ? a.so.lists : b.so.lists;
+  so.row_entries = first ? a.so.row_entries : b.so.row_entries;
+  so.mon = first ? a.so.mon : b.so.mon;
+  tk_resolve_emit_body<NT>(first ? a.chunk : b.chunk, first ? a.nchunks : b.nchunks, first ? a.want[seq] : b.want[seq], so,
+                           k, first ? a.idx : b.idx, first ? a.count : b.count, only_failed, row);
 }
 
 namespace {
@@ -1708,36 +1782,16 @@ int32_t launch_select_begin(const Layout& L, const void* kcache, const void* q, 
 // for rows whose sampled threshold left too few pairs, a scan with every slot a candidate and the selection
 // again (both launches return at once for every other row).
 int32_t launch_select_finish(const Layout& L, const void* kcache, const void* q, const NRes& nr, int64_t nmax, int32_t k,
-                             int32_t* idx, int32_t* count, void* ws, hipStream_t st, bool small_wg) {
+                             int32_t* idx, int32_t* count, void* ws, hipStream_t st, int wg) {
   FusedPlan f;
   int32_t rc = fused_plan(L, nr, nmax, k, ws, &f);
   if (rc != HCA_OK) return rc;
-  if (small_wg) {
-    const uint32_t cap = small_stage_cap(k);
-    static std::atomic<uint64_t> opted_s{0};
-    if (cap * 8 > 64 * 1024) {
-      rc = lds_opt_in(reinterpret_cast<const void*>(&tk_resolve_emit<256>), kSmallLds * 8, &opted_s);
-      if (rc != HCA_OK) return rc;
-    }
-    tk_resolve_emit<256><<<L.rows, 256, cap * 8, st>>>(f.chunk, f.nchunks, L.n_kv_heads, f.sr, f.so, k, idx, count, false, cap);
-    if (nmax > 0) {
-      rc = launch_select_scan(L, kcache, q, nr, nmax, f.so, true, st);
-      if (rc != HCA_OK) return rc;
-      tk_resolve_emit<256><<<L.rows, 256, 0, st>>>(f.chunk, f.nchunks, L.n_kv_heads, f.sr, f.so, k, idx, count, true, 0u);
-    }
-    HCA_HIP(hipGetLastError());
-    return HCA_OK;
-  }
-  static std::atomic<uint64_t> opted{0};
-  rc = lds_opt_in(reinterpret_cast<const void*>(&tk_resolve_emit<1024>), kFullLds * 8, &opted);
-  if (rc != HCA_OK) return rc;
-  tk_resolve_emit<1024><<<L.rows, 1024, kFullLds * 8, st>>>(f.chunk, f.nchunks, L.n_kv_heads, f.sr, f.so, k, idx, count, false,
-                                                            (uint32_t)kFullLds);
+  const auto form = wg == 256 ? tk_resolve_emit<256> : wg == 512 ? tk_resolve_emit<512> : tk_resolve_emit<1024>;
+  form<<<L.rows, wg, 0, st>>>(f.chunk, f.nchunks, L.n_kv_heads, f.sr, f.so, k, idx, count, false);
   if (nmax > 0) {
     rc = launch_select_scan(L, kcache, q, nr, nmax, f.so, true, st);
     if (rc != HCA_OK) return rc;
-    tk_resolve_emit<1024><<<L.rows, 1024, kFullLds * 8, st>>>(f.chunk, f.nchunks, L.n_kv_heads, f.sr, f.so, k, idx, count, true,
-                                                              (uint32_t)kFullLds);
+    form<<<L.rows, wg, 0, st>>>(f.chunk, f.nchunks, L.n_kv_heads, f.sr, f.so, k, idx, count, true);
   }
   HCA_HIP(hipGetLastError());
   return HCA_OK;
@@ -1746,7 +1800,7 @@ int32_t launch_select_finish(const Layout& L, const void* kcache, const void* q,
 // The same for the two layers of a paired scan launch: three launches for the two of them.
 int32_t launch_select_finish_pair(const Layout& L, const void* const kcache[2], const void* const q[2], const NRes nr[2],
                                   const int64_t nmax[2], int32_t k, int32_t* const idx[2], int32_t* const count[2],
-                                  void* const ws[2], hipStream_t st, bool small_wg) {
+                                  void* const ws[2], hipStream_t st, int wg) {
   FusedPlan f[2];
   ResolveSide rs[2];
   for (int i = 0; i < 2; ++i) {
@@ -1760,21 +1814,8 @@ int32_t launch_select_finish_pair(const Layout& L, const void* const kcache[2], 
     rs[i].count = count[i];
   }
   int32_t rc = HCA_OK;
-  if (small_wg) {
-    const uint32_t cap = small_stage_cap(k);
-    static std::atomic<uint64_t> opted_s{0};
-    if (cap * 8 > 64 * 1024) {
-      rc = lds_opt_in(reinterpret_cast<const void*>(&tk_resolve_emit_pair<256>), kSmallLds * 8, &opted_s);
-      if (rc != HCA_OK) return rc;
-    }
-    tk_resolve_emit_pair<256><<<2 * L.rows, 256, cap * 8, st>>>(rs[0], rs[1], L.rows, L.n_kv_heads, k, false, cap);
-  } else {
-    static std::atomic<uint64_t> opted{0};
-    rc = lds_opt_in(reinterpret_cast<const void*>(&tk_resolve_emit_pair<1024>), kFullLds * 8, &opted);
-    if (rc != HCA_OK) return rc;
-    tk_resolve_emit_pair<1024><<<2 * L.rows, 1024, kFullLds * 8, st>>>(rs[0], rs[1], L.rows, L.n_kv_heads, k, false,
-                                                                       (uint32_t)kFullLds);
-  }
+  const auto form = wg == 256 ? tk_resolve_emit_pair<256> : wg == 512 ? tk_resolve_emit_pair<512> : tk_resolve_emit_pair<1024>;
+  form<<<2 * L.rows, wg, 0, st>>>(rs[0], rs[1], L.rows, L.n_kv_heads, k, false);
   if (nmax[0] > 0 && nmax[1] > 0) {
     const SelectOut so2[2] = {f[0].so, f[1].so};
     rc = launch_select_rescan_pair(L, kcache, q, nr, nmax, so2, st);
@@ -1782,7 +1823,7 @@ int32_t launch_select_finish_pair(const Layout& L, const void* const kcache[2], 
     // the selection for rows that had to be scanned again - almost never any - in the four-wave form without an
     // LDS stage: beside a running scan the 1024-thread form would wait for a compute unit to drain just to find
     // that it has nothing to do
-    tk_resolve_emit_pair<256><<<2 * L.rows, 256, 0, st>>>(rs[0], rs[1], L.rows, L.n_kv_heads, k, true, 0u);
+    tk_resolve_emit_pair<256><<<2 * L.rows, 256, 0, st>>>(rs[0], rs[1], L.rows, L.n_kv_heads, k, true);
   }
   HCA_HIP(hipGetLastError());
   return HCA_OK;
@@ -1805,7 +1846,7 @@ int32_t launch_score_topk(const Layout& L, const void* kcache, const void* q, co
   if (rc != HCA_OK) return rc;
   rc = launch_select_begin(L, kcache, q, nr, nmax, k, ws, st, nullptr);
   if (rc != HCA_OK) return rc;
-  return launch_select_finish(L, kcache, q, nr, nmax, k, idx, count, ws, st, tuning().select_wg == 256);
+  return launch_select_finish(L, kcache, q, nr, nmax, k, idx, count, ws, st, tuning().select_wg > 0 ? tuning().select_wg : 1024);
 }
 
 // What the last fused selection on this workspace did, per row: pairs that passed the threshold of the scan that

@@ -18,9 +18,8 @@ def H():
 
 @pytest.fixture(autouse=True, params=[0, 256], ids=["wg1024", "wg256"])
 def select_wg(request, H):
-    """Every case runs with both forms of the selection over the candidate lists: one 1024-thread workgroup per
-    row with the pairs staged in LDS (the per-call default), and the four-wave form that reads them from L2 (what
-    the step driver uses beside a running scan)."""
+    """Every case runs with two forms of the selection over the candidate lists: the default one (1024 threads for a
+    call, 512 in a step driver) and the one of 256 threads."""
     H.hca_tune("select_wg", request.param)
     yield request.param
     H.hca_tune("select_wg", 0)
@@ -81,7 +80,7 @@ def test_score_topk_matches_the_oracle(H, oracle, bits, gs, n, k, lens):
 
 @pytest.mark.parametrize("bits,gs", [(4, 32), (2, 64)])
 def test_the_largest_k(H, oracle, bits, gs):
-    """k = 16384, the most the step driver accepts: more candidates than the LDS stage holds, one row barely
+    """k = 16384, the most the step driver accepts: more candidates than are held in registers, one row barely
     longer than k."""
     n, k = 120000, 16384
     lens = [n, k + 5]
@@ -100,7 +99,7 @@ def test_fewer_query_heads_per_kv_head(H, oracle, hq, hkv):
 
 
 def test_ties_and_a_list_too_long_for_lds(H, oracle):
-    """Every key the same: every slot passes any threshold (50 000 pairs, more than are staged in LDS) and the
+    """Every key the same: every slot passes any threshold (50 000 pairs, more than are held in registers) and the
     k lowest slots win."""
     w = S.Workload("tie", 95, 1, 4, 1, 50000, 4, 32, 777)
     d = S.make_layer(w, want_values=False)
@@ -281,4 +280,70 @@ def test_step_driver_pair_with_a_row_that_needs_the_second_scan(H, oracle, own_i
     m = mon.cpu().numpy()
     assert m[0, 0, 0] == 1 and m[0, 0, 3] == 1, "layer 0 should have needed the second scan"
     assert m[1, 0, 0] == 1 and m[1, 0, 3] == 0
+    B.hca_pipeline_destroy(pl)
+
+
+@pytest.mark.parametrize("dual", [0, 2])
+@pytest.mark.parametrize("k", [60, 8000, 16384])
+def test_step_driver_selects_at_the_edges_of_what_is_held_in_registers(H, oracle, k, dual):
+    """The step driver's own form of the selection (512 threads; 256 in the fixture's second form), on rows whose lists
+    end at and beside the edges: one pair, a wave's worth, a step of registers, all 16384 and one more, and a long row."""
+    import ctypes as C
+    from paper_2507_19823_amd import binding as B
+    lens = [50000, 16384, 16383, 8192, 8191, 4096, 64, 63, 0]
+    n, nb, Lr = max(lens), len(lens), 2
+    cap = n + 8
+    w = S.Workload("held", 92, nb, 4, 1, n, 4, 32, k)
+    dev = "cuda"
+    d = S.make_layer(w, want_values=False)
+    shape = B.make_shape(nb, 4, 1, cap)
+    kc = [torch.zeros(B.hca_kcache_bytes(shape), dtype=torch.uint8, device=dev) for _ in range(Lr)]
+    acc = [torch.zeros(nb, 1, cap, device=dev) for _ in range(Lr)]
+    pos = [torch.zeros(nb, 1, cap, dtype=torch.int32, device=dev) for _ in range(Lr)]
+    keys = [d["keys"], d["keys"].flip(2).contiguous()]
+    ocs = []
+    for l in range(Lr):
+        B.hca_quantize_keys(shape, kc[l], keys[l].cuda(), n, [0] * nb)
+        oc = oracle.Cache(nb, cap, 128, 4, 32)
+        oracle.quantize(oc, keys[l].numpy().reshape(nb, n, 128))
+        oc.n[...] = lens
+        oracle.quantize(oc, np.zeros((nb, 1, 128), np.float16))                # the token that the step appends
+        ocs.append(oc)
+    streams = [torch.cuda.current_stream(), torch.cuda.Stream(), torch.cuda.Stream(), torch.cuda.Stream()]
+    dsc = B.hca_pipeline_desc()
+    dsc.stream_scan, dsc.stream_topk, dsc.stream_gather, dsc.stream_attend = (s_.cuda_stream for s_ in streams)
+    wsb = B.hca_workspace_bytes(shape, k, 1)
+    ws = [torch.zeros(wsb, dtype=torch.uint8, device=dev) for _ in range(8)]
+    bufs = [(torch.zeros(nb, k, dtype=torch.int32, device=dev), torch.zeros(nb, dtype=torch.int32, device=dev))
+            for _ in range(4)]
+    dsc.n_sel, dsc.fused_select, dsc.n_pipe, dsc.dual_scan = 3, 1, 4, dual
+    for i in range(3):
+        dsc.ws_select[i] = ws[i].data_ptr()
+    for i in range(4):
+        dsc.idx[i], dsc.count[i], dsc.ws_attend[i] = bufs[i][0].data_ptr(), bufs[i][1].data_ptr(), ws[3 + i].data_ptr()
+    dsc.ws_topk = ws[7].data_ptr()
+    lidx = torch.full((Lr, nb, k), -3, dtype=torch.int32, device=dev)
+    lcnt = torch.zeros(Lr, nb, dtype=torch.int32, device=dev)
+    dsc.layer_idx, dsc.layer_count, dsc.layer_idx_stride = lidx.data_ptr(), lcnt.data_ptr(), nb * k
+    pl = B.hca_pipeline_create(shape, Lr, dsc, 0)
+    vd = torch.zeros(nb, 1, 8, 128, dtype=torch.float16, device=dev)           # every slot's value is row 0
+    y = torch.zeros(Lr, nb, 4, 128, device=dev)
+    k_new = torch.zeros(nb, 1, 1, 128, dtype=torch.float16, device=dev)
+    qd = d["q"].cuda()
+    layers = (B.hca_layer * Lr)()
+    for l in range(Lr):
+        layers[l].kcache, layers[l].acc, layers[l].pos = kc[l].data_ptr(), acc[l].data_ptr(), pos[l].data_ptr()
+        layers[l].v_hbm, layers[l].y = vd.data_ptr(), y[l].data_ptr()
+        layers[l].k_new, layers[l].q = k_new.data_ptr(), qd.data_ptr()
+    nres = (C.c_int64 * (Lr * nb))(*(lens * Lr))
+    torch.cuda.synchronize()
+    B.hca_pipeline_step(pl, layers, nres, 0, k, 0, 0, 8, 0.0884, None, 0, -1)
+    torch.cuda.synchronize()
+    for l in range(Lr):
+        sel, _ = oracle.score(ocs[l], d["q"].numpy().reshape(-1, 128), want_z=False)
+        oidx, ocount = oracle.topk(sel, ocs[l].n, k)
+        for r in range(nb):
+            c = min(k, lens[r] + 1)
+            assert lcnt[l, r].item() == c == ocount[r]
+            assert np.array_equal(lidx[l, r, :c].cpu().numpy(), oidx[r, :c]), f"layer {l} row {r}: index sets differ"
     B.hca_pipeline_destroy(pl)
