@@ -475,11 +475,16 @@ __global__ __launch_bounds__(256) void select_sample_score(Layout L, const uint8
                           (int)blockIdx.y);
 }
 
-// 256 threads per row: small enough to find room on a chip that another stream's scan keeps full
-__device__ __forceinline__ void sample_rank_body(const int64_t n, int32_t k, const uint32_t* __restrict__ samples,
-                                                 const int m_samples, uint32_t* __restrict__ spec, const int row) {
+// The threshold from a row's samples, key_at(i) = the key of sample i < m_samples (0: no such slot).  NT = 256 threads are
+// small enough to find room on a chip that another stream's scan keeps full; 1024 are quicker on a free one (a chain of
+// passes and barriers: 8 x 32 768 samples 18 -> 10 us).
+// EXACT: sp[0] = the r-th largest sample's whole key (0: r >= m), and no second threshold.
+template <int NT, bool EXACT, typename F>
+__device__ __forceinline__ void sample_rank_body(const int64_t n, int32_t k, F&& key_at, const int m_samples,
+                                                 uint32_t* __restrict__ spec, const int row) {
+  constexpr int kFirst = 4096 / NT, kSecond = 1024 / NT;    // bins per thread
   __shared__ uint32_t hist[4096];
-  __shared__ uint32_t wsum[4];
+  __shared__ uint32_t wsum[NT / 64];
   __shared__ uint32_t s_bin, s_rem, s_bin1;
   const int tid = threadIdx.x, lane = tid & 63, w = tid >> 6;
   const int64_t want = n < k ? n : k;
@@ -488,20 +493,27 @@ __device__ __forceinline__ void sample_rank_body(const int64_t n, int32_t k, con
     if (tid == 0) { sp[0] = 0xffffffffu; sp[1] = 0; sp[2] = 0xffffffffu; }
     return;
   }
-  const uint32_t* in = samples + (int64_t)row * m_samples;
-  for (int i = tid; i < 4096; i += 256) hist[i] = 0;
+  // f(key) for every sample: the first 8 per thread are kept, any others read again for each pass, 8 in flight
+  uint32_t first[8];
+#pragma unroll
+  for (int i = 0; i < 8; ++i) first[i] = key_at(i * NT + tid);
+  auto each = [&](auto&& f) {
+#pragma unroll
+    for (int i = 0; i < 8; ++i) f(first[i]);
+    for (int i0 = 8 * NT; i0 < m_samples; i0 += 8 * NT) {
+      uint32_t key[8];
+#pragma unroll
+      for (int i = 0; i < 8; ++i) key[i] = key_at(i0 + i * NT + tid);
+#pragma unroll
+      for (int i = 0; i < 8; ++i) f(key[i]);
+    }
+  };
+  for (int i = tid; i < 4096; i += NT) hist[i] = 0;
   __syncthreads();
-  for (int i0 = 0; i0 < m_samples; i0 += 8 * 256) {        // 8 loads in flight per thread
-    uint32_t key[8];
-#pragma unroll
-    for (int i = 0; i < 8; ++i) key[i] = in[i0 + i * 256 + tid];
-#pragma unroll
-    for (int i = 0; i < 8; ++i)
-      if (key[i] != 0) atomicAdd(&hist[key[i] >> 20], 1u);
-  }
+  each([&](uint32_t key) { if (key != 0) atomicAdd(&hist[key >> 20], 1u); });
   __syncthreads();
   // exclusive prefix over the threads of `sum`, and the total
-  auto scan256 = [&](uint32_t sum, uint32_t* total) {
+  auto scan = [&](uint32_t sum, uint32_t* total) {
     uint32_t inc = sum;
 #pragma unroll
     for (int o = 1; o < 64; o <<= 1) {
@@ -512,16 +524,16 @@ __device__ __forceinline__ void sample_rank_body(const int64_t n, int32_t k, con
     if (lane == 63) wsum[w] = inc;
     __syncthreads();
     uint32_t running = inc - sum, tot = 0;
-    for (int x = 0; x < 4; ++x) { if (x < w) running += wsum[x]; tot += wsum[x]; }
+    for (int x = 0; x < NT / 64; ++x) { if (x < w) running += wsum[x]; tot += wsum[x]; }
     *total = tot;
     return running;
   };
-  // bins from the top: thread tid owns bins 4095 - 16 tid - i
-  uint32_t h[16], sum = 0;
+  // bins from the top: thread tid owns bins 4095 - kFirst tid - i
+  uint32_t h[kFirst], sum = 0;
 #pragma unroll
-  for (int i = 0; i < 16; ++i) { h[i] = hist[4095 - (16 * tid + i)]; sum += h[i]; }
+  for (int i = 0; i < kFirst; ++i) { h[i] = hist[4095 - (kFirst * tid + i)]; sum += h[i]; }
   uint32_t m;                                               // sampled slots that exist
-  uint32_t running = scan256(sum, &m);
+  uint32_t running = scan(sum, &m);
   const float kappa = (float)want * (float)m / (float)n;
   const float root = 3.0f + sqrtf(9.0f + kappa);
   const uint32_t r = (uint32_t)ceilf(root * root);
@@ -535,43 +547,76 @@ __device__ __forceinline__ void sample_rank_body(const int64_t n, int32_t k, con
   const uint32_t r1 = 8 * r;
   if (tid == 0) sp[2] = 0;
 #pragma unroll
-  for (int i = 0; i < 16; ++i) {
-    if (running < r && r <= running + h[i]) { s_bin = 4095 - (16 * tid + i); s_rem = r - running; }
-    if (running < r1 && r1 <= running + h[i]) s_bin1 = 4095 - (16 * tid + i);
+  for (int i = 0; i < kFirst; ++i) {
+    if (running < r && r <= running + h[i]) { s_bin = 4095 - (kFirst * tid + i); s_rem = r - running; }
+    if (running < r1 && r1 <= running + h[i]) s_bin1 = 4095 - (kFirst * tid + i);
     running += h[i];
   }
   __syncthreads();
-  if (tid == 0 && r1 < m) sp[2] = s_bin1 << 20;
-  const uint32_t bin = s_bin, rem = s_rem;
-  for (int i = tid; i < 1024; i += 256) hist[i] = 0;
-  __syncthreads();
-  for (int i0 = 0; i0 < m_samples; i0 += 8 * 256) {
-    uint32_t key[8];
+  if (!EXACT && tid == 0 && r1 < m) sp[2] = s_bin1 << 20;
+  // the next ten bits of the key, and for the whole of it the last ten
+  uint32_t prefix = s_bin, rem = s_rem;
 #pragma unroll
-    for (int i = 0; i < 8; ++i) key[i] = in[i0 + i * 256 + tid];
+  for (int shift = 10; shift >= (EXACT ? 0 : 10); shift -= 10) {
+    for (int i = tid; i < 1024; i += NT) hist[i] = 0;
+    __syncthreads();
+    each([&](uint32_t key) { if (key != 0 && key >> (shift + 10) == prefix) atomicAdd(&hist[(key >> shift) & 1023u], 1u); });
+    __syncthreads();
+    uint32_t g[kSecond];
+    sum = 0;
 #pragma unroll
-    for (int i = 0; i < 8; ++i)
-      if (key[i] != 0 && (key[i] >> 20) == bin) atomicAdd(&hist[(key[i] >> 10) & 1023u], 1u);
-  }
-  __syncthreads();
-  uint32_t g[4];
-  sum = 0;
+    for (int i = 0; i < kSecond; ++i) { g[i] = hist[1023 - (kSecond * tid + i)]; sum += g[i]; }
+    uint32_t unused;
+    running = scan(sum, &unused);
 #pragma unroll
-  for (int i = 0; i < 4; ++i) { g[i] = hist[1023 - (4 * tid + i)]; sum += g[i]; }
-  uint32_t unused;
-  running = scan256(sum, &unused);
-#pragma unroll
-  for (int i = 0; i < 4; ++i) {
-    if (running < rem && rem <= running + g[i]) {
-      sp[0] = (bin << 20) | ((uint32_t)(1023 - (4 * tid + i)) << 10);
-      sp[1] = 0;
+    for (int i = 0; i < kSecond; ++i) {
+      if (running < rem && rem <= running + g[i]) {
+        s_bin = prefix << 10 | (uint32_t)(1023 - (kSecond * tid + i));
+        s_rem = rem - running;
+      }
+      running += g[i];
     }
-    running += g[i];
+    __syncthreads();
+    prefix = s_bin;
+    rem = s_rem;
   }
+  if (tid == 0) { sp[0] = EXACT ? prefix : prefix << 10; sp[1] = 0; }
+}
+__device__ __forceinline__ void sample_rank_body(const int64_t n, int32_t k, const uint32_t* __restrict__ samples,
+                                                 const int m_samples, uint32_t* __restrict__ spec, const int row) {
+  const uint32_t* in = samples + (int64_t)row * m_samples;
+  sample_rank_body<256, false>(n, k, [&](int i) { return in[i]; }, m_samples, spec, row);
 }
 
-__global__ __launch_bounds__(256) void select_sample_rank(Layout L, NRes nr, int32_t k, SelectOut so) {
-  sample_rank_body(nr.n[blockIdx.x / L.n_kv_heads], k, so.samples, so.m_samples, so.spec, (int)blockIdx.x);
+__global__ __launch_bounds__(1024) void select_sample_rank(Layout L, NRes nr, int32_t k, SelectOut so) {
+  const uint32_t* in = so.samples + (int64_t)blockIdx.x * so.m_samples;
+  sample_rank_body<1024, false>(nr.n[blockIdx.x / L.n_kv_heads], k, [&](int i) { return in[i]; }, so.m_samples, so.spec,
+                         (int)blockIdx.x);
+}
+
+// The same from scores that are there already (hca_topk): sample i is slot i % 16 of a block of 16 slots, block
+// floor((s + h(s)) nblocks / S) of the row, s = i / 16, S = min(nblocks, m / 16), with 0 <= h(s) < 1 scattered by s, so that
+// no period of the row meets that of the samples.
+__global__ __launch_bounds__(1024) void topk_sample_rank(const float* __restrict__ vals, int64_t stride, int n_kv_heads,
+                                                         NRes nr, int32_t k, int m, uint32_t* __restrict__ spec) {
+  const int row = blockIdx.x;
+  const int64_t n = nr.n[row / n_kv_heads];
+  const float* v = vals + (int64_t)row * stride;
+  const uint32_t nblocks = (uint32_t)((n + 15) / 16), most = (uint32_t)m / 16, S = nblocks < most ? nblocks : most;
+  const int shift = __builtin_ctz(most);                    // (m is a power of two)
+  auto key_at = [&](int i) -> uint32_t {
+    const uint32_t s = (uint32_t)i / 16;
+    const uint32_t b = S == nblocks ? s : (uint32_t)(((uint64_t)s * nblocks + ((uint64_t)(s * 2654435761u) * nblocks >> 32)) >> shift);
+    const int64_t j = (int64_t)b * 16 + (i & 15);
+    return s < S && j < n ? order_key(v[j]) : 0u;
+  };
+  sample_rank_body<1024, true>(n, k, key_at, m, spec, row);
+}
+int32_t launch_topk_sample_rank(const float* vals, int64_t stride, int rows, int n_kv_heads, const NRes& nr, int32_t k, int m,
+                                uint32_t* spec, hipStream_t st) {
+  topk_sample_rank<<<rows, 1024, 0, st>>>(vals, stride, n_kv_heads, nr, k, m, spec);
+  HCA_HIP(hipGetLastError());
+  return HCA_OK;
 }
 
 // The two small jobs of a layer that precede its selecting scan in a decode step, as one launch: workgroup
@@ -774,17 +819,24 @@ int32_t launch_select_begin_rank_append(const Layout& L, int n, void* const kcac
 // Slots to sample per row.  More samples give a tighter threshold: with m samples the scan lets through about
 // n r / m pairs per row, r as in the comment above.  The smallest of 8192 .. 65536 that keeps that estimate within
 // what the selection holds in LDS (16384 pairs, less a margin for the spread of the count).
+static bool sample_keeps_lists_short(int64_t nmax, int32_t k, int m) {
+  const double want = (double)(k < nmax ? k : nmax);
+  const double kappa = want * m / (double)(nmax > 0 ? nmax : 1);
+  const double root = 3.0 + sqrt(9.0 + kappa);
+  const double r = root * root;
+  return r < m && (double)nmax * r / m <= 14336.0;
+}
 int select_sample_count(int64_t nmax, int32_t k) {
   int m = 8192;
   for (; m < 65536; m *= 2) {
     const double want = (double)(k < nmax ? k : nmax);
     const double kappa = want * m / (double)(nmax > 0 ? nmax : 1);
     const double root = 3.0 + sqrt(9.0 + kappa);
-    const double r = root * root;
-    if (r >= m || (double)nmax * r / m <= 14336.0) break;
+    if (root * root >= m || sample_keeps_lists_short(nmax, k, m)) break;
   }
   return m;
 }
+bool select_lists_fit(int64_t nmax, int32_t k) { return sample_keeps_lists_short(nmax, k, select_sample_count(nmax, k)); }
 
 int select_scan_bpw(const Layout& L, int64_t nmax) {
   const int64_t nblocks = (nmax + L.tpb - 1) / L.tpb;
@@ -814,7 +866,7 @@ int32_t launch_select_sample(const Layout& L, const void* kcache, const void* q,
                              const SelectOut& so, hipStream_t st) {
   const int32_t rc = launch_select_sample_scores(L, kcache, q, nr, so, st);
   if (rc != HCA_OK) return rc;
-  select_sample_rank<<<L.rows, 256, 0, st>>>(L, nr, k, so);
+  select_sample_rank<<<L.rows, 1024, 0, st>>>(L, nr, k, so);
   HCA_HIP(hipGetLastError());
   return HCA_OK;
 }

@@ -488,7 +488,8 @@ __global__ __launch_bounds__(256) void tk_findbin(int n_kv_heads, SelRows sr, To
 // counts the ones strictly above the bin.  Lists are per chunk so that no two workgroups ever
 // contend for an append position.
 // range(&first, &last): the smallest and the largest key of the bin, asked for while the first tile is on its way.
-template <typename F>
+// ABOVE: the keys above `first` are listed and those equal to it counted.
+template <bool ABOVE, typename F>
 __device__ __forceinline__ void collect_chunk(const float* __restrict__ vals, int64_t stride, int64_t chunk, int64_t nsel,
                                               int row, const TopkWs& t, F&& range) {
   __shared__ uint32_t wsum[4];
@@ -517,8 +518,8 @@ __device__ __forceinline__ void collect_chunk(const float* __restrict__ vals, in
     uint64_t mask[16];
 #pragma unroll
     for (int x = 0; x < 16; ++x) {
-      cnt += valid[x] && key[x] > last;
-      mask[x] = __ballot(valid[x] && key[x] >= first);
+      cnt += valid[x] && (ABOVE ? key[x] == first : key[x] > last);
+      mask[x] = __ballot(valid[x] && (ABOVE ? key[x] > first : key[x] >= first));
       if (lane == 0) pc[x * 4 + w] = (uint32_t)__popcll(mask[x]);
     }
     __syncthreads();
@@ -558,9 +559,20 @@ __global__ __launch_bounds__(256) void tk_collect(const float* __restrict__ vals
                                                   int n_kv_heads, SelRows sr, TopkWs t) {
   const int row = blockIdx.y;
   if (sr.want[row / n_kv_heads] <= 0) return;
-  collect_chunk(vals, stride, chunk, sr.nsel[row / n_kv_heads], row, t, [&](uint32_t* first, uint32_t* last) {
+  collect_chunk<false>(vals, stride, chunk, sr.nsel[row / n_kv_heads], row, t, [&](uint32_t* first, uint32_t* last) {
     *first = t.state[4 * row + 2] << 20;
     *last = *first | 0xfffffu;
+  });
+}
+
+// The same with a sampled key in place of a bin: the keys above it.
+__global__ __launch_bounds__(256) void tk_collect_sampled(const float* __restrict__ vals, int64_t stride, int64_t chunk,
+                                                          int n_kv_heads, SelRows sr, TopkWs t) {
+  const int row = blockIdx.y;
+  if (sr.want[row / n_kv_heads] <= 0) return;
+  collect_chunk<true>(vals, stride, chunk, sr.nsel[row / n_kv_heads], row, t, [&](uint32_t* first, uint32_t* last) {
+    *first = t.state[4 * row];
+    *last = 0;
   });
 }
 
@@ -1166,6 +1178,7 @@ static int32_t launch_row_select(const float* vals, int64_t stride, int rows, in
 //   position(j) = #{i < j : key_i > T} + min(#{i < j : key_i == T}, r_eq)
 // A row with fewer pairs than it has to select is marked for a second scan without threshold; `only_failed`
 // launches handle exactly those rows.
+constexpr uint32_t kDirectRank = 128;   // keys ranked against each other: 1.5 us; a round of digits takes 2
 constexpr int kHeldPairs = 16384;   // pairs per row held in registers
 constexpr int kSearchMax = 65536;   // pairs still addressed by position when they are not held
 
@@ -1213,9 +1226,9 @@ struct ResolveShared {
 // The selection proper, once the chunks' offsets are in sh.off.  HELD: every pair's key in a register.
 template <int NT, bool HELD>
 __device__ __forceinline__ void tk_resolve_pairs(ResolveShared<NT>& sh, const int64_t chunk, const int nchunks,
-                                                 const int64_t want, const SelectOut& so, const int32_t k,
-                                                 int32_t* __restrict__ idx, int32_t* __restrict__ count, const int row,
-                                                 const uint32_t total) {
+                                                 const int64_t want, const SelectOut& so, const uint32_t base_key,
+                                                 const int32_t k, int32_t* __restrict__ idx, int32_t* __restrict__ count,
+                                                 const int row, const uint32_t total) {
   constexpr int NW = NT / 64;              // waves
   constexpr int PER = 1024 / NT;           // chunks (and 10-bit bins) per thread
   auto& h = sh.h;
@@ -1224,7 +1237,6 @@ __device__ __forceinline__ void tk_resolve_pairs(ResolveShared<NT>& sh, const in
   auto& cmap = sh.cmap;
   uint32_t &s_prefix = sh.s_prefix, &s_rem = sh.s_rem, &s_cb = sh.s_cb;
   const int tid = threadIdx.x;
-  const uint32_t* spec = so.spec + 4 * row;
   const uint2* gl = so.lists + (int64_t)row * so.row_entries;
   // beyond kHeldPairs: up to kSearchMax pairs are still addressed by their position in slot order (short lists:
   // walking them chunk by chunk would cost a memory round trip per chunk), more than that are walked chunk by chunk
@@ -1338,7 +1350,7 @@ __device__ __forceinline__ void tk_resolve_pairs(ResolveShared<NT>& sh, const in
   // digits of d found so far, s = the number of bits of d below them; rem = how many are still to take among the
   // pairs whose d starts with pd, cb = how many such pairs there are.  The first level spreads the occupied
   // range of d over 4096 bins, so the counters are not fought over although the keys share their leading bits.
-  const uint32_t base = (uint32_t)__builtin_amdgcn_readfirstlane((int)spec[0]);
+  const uint32_t base = (uint32_t)__builtin_amdgcn_readfirstlane((int)base_key);
   const uint32_t maxd = kmax - base;
   int sbits = 32 - __clz((int)(maxd | 1)) - 12;             // bits of maxd beyond the 12 of the first level
   if (sbits < 0) sbits = 0;
@@ -1375,7 +1387,7 @@ __device__ __forceinline__ void tk_resolve_pairs(ResolveShared<NT>& sh, const in
       req = rem;
       break;
     }
-    if (cb <= 1024) {
+    if (cb <= kDirectRank) {
       // few pairs left: rank them against each other.  sl = their keys; T is the key with fewer than rem keys
       // above it that, together with its equals, reaches rem.
       uint32_t* sl = h;
@@ -1387,9 +1399,10 @@ __device__ __forceinline__ void tk_resolve_pairs(ResolveShared<NT>& sh, const in
         if (hit && ((key - base1) >> sbits) == pd) sl[atomicAdd(&s_cb, 1u)] = key;
       });
       __syncthreads();
-      for (uint32_t me = (uint32_t)tid; me < cb; me += NT) {
-        const uint32_t ki = sl[me];
+      if ((uint32_t)tid < cb) {                             // (cb <= kDirectRank < NT)
+        const uint32_t ki = sl[tid];
         uint32_t gt = 0, eq = 0;
+#pragma unroll 4
         for (uint32_t j = 0; j < cb; ++j) {
           const uint32_t kj = sl[j];
           gt += kj > ki;
@@ -1641,8 +1654,9 @@ __device__ __forceinline__ void tk_resolve_emit_body(const int64_t chunk, const 
     }
     return;
   }
-  if (total <= (uint32_t)kHeldPairs) tk_resolve_pairs<NT, true>(sh, chunk, nchunks, want, so, k, idx, count, row, total);
-  else tk_resolve_pairs<NT, false>(sh, chunk, nchunks, want, so, k, idx, count, row, total);
+  const uint32_t base = spec[0];
+  if (total <= (uint32_t)kHeldPairs) tk_resolve_pairs<NT, true>(sh, chunk, nchunks, want, so, base, k, idx, count, row, total);
+  else tk_resolve_pairs<NT, false>(sh, chunk, nchunks, want, so, base, k, idx, count, row, total);
 }
 
 template <int NT>
@@ -1651,6 +1665,80 @@ __global__ __launch_bounds__(NT) __attribute__((amdgpu_waves_per_eu(NT == 512 ? 
                                                       int32_t* __restrict__ count, bool only_failed) {
   tk_resolve_emit_body<NT>(chunk, nchunks, sr.want[blockIdx.x / n_kv_heads], so, k, idx, count, only_failed,
                            (int)blockIdx.x);
+}
+
+// hca_topk's last launch: the chunks' lists hold the keys above the sampled key K (spec), the chunks' second counts those
+// equal to it.  Enough above it: the selection over the lists.  Enough with the equal ones: all of the lists and the first
+// equal slots.  Neither, which takes a row that its samples misrepresent by six deviations: every slot into the lists, by
+// this workgroup.
+__global__ __launch_bounds__(1024) __attribute__((amdgpu_waves_per_eu(4))) void tk_resolve_scores(
+    const float* __restrict__ vals, int64_t stride, int64_t chunk, int nchunks, int n_kv_heads, SelRows sr, SelectOut so,
+    int32_t k, int32_t* __restrict__ idx, int32_t* __restrict__ count) {
+  __shared__ ResolveShared<1024> sh;
+  auto& off = sh.off;
+  const int row = blockIdx.x, tid = threadIdx.x;
+  const int64_t n = sr.nsel[row / n_kv_heads], want = sr.want[row / n_kv_heads];
+  if (want <= 0) {
+    if (tid == 0) count[row] = 0;
+    return;
+  }
+  const uint32_t K = so.spec[4 * row];
+  const uint32_t mine = tid < nchunks ? so.ncand[(int64_t)row * kSelectMaxChunks + tid] : 0;
+  const uint32_t equal = tid < nchunks ? so.n1[(int64_t)row * kSelectMaxChunks + tid] : 0;
+  const uint32_t before = block_scan_excl<1024>(mine, sh.wsum), before_e = block_scan_excl<1024>(equal, sh.wsum);
+  uint32_t* eoff = sh.h;                                    // equal slots in the chunks before
+  off[tid] = before;
+  eoff[tid] = before_e;
+  if (tid == 1023) { off[1024] = before + mine; eoff[1024] = before_e + equal; }
+  __syncthreads();
+  const uint32_t total = off[1024], with_equal = total + eoff[1024];
+  const float* v = vals + (int64_t)row * stride;
+  uint2* lists = so.lists + (int64_t)row * so.row_entries;
+  if (total >= (uint32_t)want) {
+    __syncthreads();                                        // everybody has read eoff
+    if (total <= (uint32_t)kHeldPairs)
+      tk_resolve_pairs<1024, true>(sh, chunk, nchunks, want, so, K, k, idx, count, row, total);
+    else
+      tk_resolve_pairs<1024, false>(sh, chunk, nchunks, want, so, K, k, idx, count, row, total);
+    return;
+  }
+  if (with_equal < (uint32_t)want) {
+    for (int64_t j = tid; j < n; j += 1024) lists[j] = uint2{order_key(v[j]), (uint32_t)j};
+    for (int i = tid; i < 1025; i += 1024) off[i] = (uint32_t)(i * chunk < n ? i * chunk : n);
+    __syncthreads();
+    tk_resolve_pairs<1024, false>(sh, chunk, nchunks, want, so, 0u, k, idx, count, row, (uint32_t)n);
+    return;
+  }
+  // a wave per chunk, in slot order: from the row itself while equal slots are still to take, then from the lists
+  const uint32_t req = (uint32_t)want - total;
+  const int lane = tid & 63;
+  const uint64_t lt = (1ull << lane) - 1;
+  int32_t* out = idx + (int64_t)row * k;
+  if (tid == 0) count[row] = (int32_t)want;
+  for (int c = tid >> 6; c < nchunks; c += 16) {
+    uint32_t pg = off[c], pe = eoff[c];
+    if (pe >= req || eoff[c + 1] == pe) {
+      const uint32_t m = off[c + 1] - pg, e = pe < req ? pe : req;
+      for (uint32_t i = lane; i < m; i += 64) out[pg + e + i] = (int32_t)lists[(int64_t)c * chunk + i].y;
+      continue;
+    }
+    const int64_t c0 = (int64_t)c * chunk, c1 = c0 + chunk < n ? c0 + chunk : n;
+    for (int64_t s0 = c0; s0 < c1; s0 += 16 * 64) {
+      uint32_t key[16];
+#pragma unroll
+      for (int x = 0; x < 16; ++x) key[x] = order_key(v[s0 + x * 64 + lane < c1 ? s0 + x * 64 + lane : c1 - 1]);
+#pragma unroll
+      for (int x = 0; x < 16; ++x) {
+        const bool live = s0 + x * 64 + lane < c1, fg = live && key[x] > K, fe = live && key[x] == K;
+        const uint64_t mg = __ballot(fg), me = __ballot(fe);
+        const uint32_t gb = pg + (uint32_t)__popcll(mg & lt), eb = pe + (uint32_t)__popcll(me & lt);
+        if (fg) out[gb + (eb < req ? eb : req)] = (int32_t)(s0 + x * 64 + lane);
+        else if (fe && eb < req) out[gb + eb] = (int32_t)(s0 + x * 64 + lane);
+        pg += (uint32_t)__popcll(mg);
+        pe += (uint32_t)__popcll(me);
+      }
+    }
+  }
 }
 
 // The selections of two layers in one launch (the step driver's paired form): workgroups [0, rows) take the
@@ -2124,7 +2212,7 @@ __global__ __launch_bounds__(256) void tp_collect(const float* __restrict__ vals
     if (mass_out != nullptr && writer && threadIdx.x < 2) mass_out[2 * row + threadIdx.x] = 0;
     return;
   }
-  collect_chunk(vals, stride, chunk, sr.nsel[row / n_kv_heads], row, t, [&](uint32_t* first, uint32_t* last) {
+  collect_chunk<false>(vals, stride, chunk, sr.nsel[row / n_kv_heads], row, t, [&](uint32_t* first, uint32_t* last) {
     const float2 window = reinterpret_cast<const float2*>(t.pstate)[4 * row + 1];
     const uint32_t kmax = t.prow[4 * row];
     constexpr int BPT = kTpBins / 256;
@@ -2205,8 +2293,6 @@ __device__ __forceinline__ uint64_t block_scan_excl_1024_u64(uint64_t v, uint64_
   __syncthreads();
   return base + inc - v;
 }
-
-constexpr uint32_t kDirectRank = 128;   // keys ranked against each other: 1.5 us; a round of digits takes 2
 
 // One workgroup per row: finishes the walk inside bin b* (digits of the distance from the bin's smallest key, then the
 // group of equal keys, whose members all weigh the same) and builds the chunk offsets for the ordered emit.
@@ -2455,6 +2541,21 @@ int32_t launch_topk(const Layout& L, const float* sel, const NRes& nr, int64_t n
   int32_t nchunks;
   chunk_geometry(nmax, &chunk, &nchunks);
   dim3 g((unsigned)nchunks, (unsigned)L.rows);
+  // Three launches: a key from samples, the lists above it, the selection over them - where the lists fit the selection's
+  // registers and one workgroup per row can read the samples.  Bound by latency and one pass over the scores.  Per call, the
+  // five launches below / these, k = 1024 - 8192, normal scores: 8 rows of 50 000 39 / 27 us, of 300 000 34 / 28, of
+  // 500 000 49 / 39, of 1 Mi 50 / 43, 56 of 70 000 36 / 29; all scores equal 675 - 1200 / 46 - 56; 99 % masked 42 - 950 /
+  // 32 - 64 (300 000 slots, k = 1024: 43 / 48); 4 Mi slots in one row, 32 768 samples, 53 / 57.
+  const int m = select_sample_count(nmax, k);
+  if (m <= 16384 && select_lists_fit(nmax, k)) {
+    int32_t rc = launch_topk_sample_rank(sel, L.cap, L.rows, L.n_kv_heads, nr, k, m, t.state, st);
+    if (rc != HCA_OK) return rc;
+    tk_collect_sampled<<<g, 256, 0, st>>>(sel, L.cap, chunk, L.n_kv_heads, sr, t);
+    const SelectOut so{t.state, t.ncand, t.above, t.cand, nullptr, t.row_entries, 0, nullptr};
+    tk_resolve_scores<<<L.rows, 1024, 0, st>>>(sel, L.cap, chunk, nchunks, L.n_kv_heads, sr, so, k, idx, count);
+    HCA_HIP(hipGetLastError());
+    return HCA_OK;
+  }
   if (nmax > 0) {
     const int64_t nz = (int64_t)L.rows * kBins12;
     // the histogram sits at the start of the workspace; tk_findbin clears what it reads, so a caller

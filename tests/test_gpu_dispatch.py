@@ -249,6 +249,60 @@ def test_topk_at_the_edges_of_the_one_launch_form(B, kind, n):
             assert np.all(got[b, want:] == -7)
 
 
+def _misread(n, rng, m=8192):
+    """Scores whose sampled blocks (the samples' places as topk_sample_rank takes them) hold all the large ones."""
+    x = -np.abs(rng.standard_normal(n)).astype(np.float32)
+    nblocks, most = (n + 15) // 16, m // 16
+    s = np.arange(most, dtype=np.uint64)
+    h = (s * np.uint64(2654435761)) & np.uint64(0xffffffff)
+    block = (s * np.uint64(nblocks) + ((h * np.uint64(nblocks)) >> np.uint64(32))) // np.uint64(most)
+    j = (block[:, None] * np.uint64(16) + np.arange(16, dtype=np.uint64)).ravel().astype(np.int64)
+    x[j[j < n]] *= -1
+    return x
+
+
+@pytest.mark.parametrize("kind", ["normal", "outlier", "ties", "close", "masked", "nan", "equal", "wide", "few", "misread",
+                                  "lowest nan"])
+@pytest.mark.parametrize("n", [40961, 65536, 300001])
+def test_topk_of_long_rows_by_a_sampled_key(B, kind, n):
+    """hca_topk over the chip: lists above the sampled key, equal slots taken in slot order where the lists fall short
+    (few: more equal slots than others), a row its samples misrepresent, and a key that is all zeros; short rows beside."""
+    rng = np.random.default_rng(n + len(kind))
+    lens = [n, n - 4099, 5000, 1, 0]
+    cap = n + 3
+    sel = np.full((5, cap), 9e9, np.float32)                # past the row's end: larger than anything in it
+    for b in range(5):
+        if kind == "few":
+            x = np.where(rng.random(lens[b]) < 0.99, np.finfo(np.float32).min, rng.standard_normal(lens[b]))
+        elif kind == "misread":
+            x = _misread(lens[b], rng)
+        elif kind == "lowest nan":
+            x = rng.standard_normal(lens[b]).astype(np.float32)
+            x.view(np.uint32)[::3] = 0xffffffff
+        else:
+            x = _scores(kind, lens[b], rng) if lens[b] else 0
+        sel[b, :lens[b]] = x
+        if kind == "lowest nan" and lens[b]:
+            sel[b, :lens[b]].view(np.uint32)[::3] = 0xffffffff        # (the bits, whatever a conversion did to them)
+    shape = B.make_shape(5, 1, 1, cap)
+    dsel = torch.from_numpy(sel).cuda()
+    for k in (1, 5, 700, 3300, 8000):
+        ws = torch.empty(B.hca_workspace_bytes(shape, k, 1), dtype=torch.uint8, device="cuda")
+        idx = torch.full((5, k), -7, dtype=torch.int32, device="cuda")
+        count = torch.full((5,), -7, dtype=torch.int32, device="cuda")
+        for again in range(2):                              # the second time on the workspace as the first left it
+            B.hca_topk(shape, dsel, lens, k, idx, count, ws)
+        torch.cuda.synchronize()
+        got, c = idx.cpu().numpy(), count.cpu().numpy()
+        for b in range(5):
+            want = min(k, lens[b])
+            assert c[b] == want
+            key = _order_key(sel[b, :lens[b]]).astype(np.int64)
+            ref = np.sort(np.argsort(-key, kind="stable")[:want])
+            assert np.array_equal(got[b, :want], ref), f"row {b}, k {k}"
+            assert np.all(got[b, want:] == -7)
+
+
 @pytest.mark.parametrize("n", [4096, 16384, 40960])
 @pytest.mark.parametrize("kind", ["sink", "low", "sinks and lows", "masked", "tail masked", "-inf"])
 def test_a_few_far_scores_do_not_slow_the_short_rows(B, kind, n):
