@@ -75,8 +75,8 @@ __global__ __launch_bounds__(256) void evict_positions(const float* __restrict__
   const uint2* counts = reinterpret_cast<const uint2*>(ccount) + (int64_t)row * nchunks;
   uint32_t sg = 0, se = 0;
   for (int c = threadIdx.x; c < (int)blockIdx.x; c += 256) { sg += counts[c].x; se += counts[c].y; }
-#pragma unroll
-  for (int o = 32; o >= 1; o >>= 1) { sg += __shfl_xor(sg, o); se += __shfl_xor(se, o); }
+  sg = wave_sum(sg);
+  se = wave_sum(se);
   if (lane == 0) { red[0][w] = sg; red[1][w] = se; }
   __syncthreads();
   uint32_t base_g = red[0][0] + red[0][1] + red[0][2] + red[0][3];

@@ -486,7 +486,7 @@ __device__ __forceinline__ void sample_rank_body(const int64_t n, int32_t k, F&&
   __shared__ uint32_t hist[4096];
   __shared__ uint32_t wsum[NT / 64];
   __shared__ uint32_t s_bin, s_rem, s_bin1;
-  const int tid = threadIdx.x, lane = tid & 63, w = tid >> 6;
+  const int tid = threadIdx.x;
   const int64_t want = n < k ? n : k;
   uint32_t* sp = spec + 4 * row;
   if (want <= 0) {
@@ -512,28 +512,12 @@ __device__ __forceinline__ void sample_rank_body(const int64_t n, int32_t k, F&&
   __syncthreads();
   each([&](uint32_t key) { if (key != 0) atomicAdd(&hist[key >> 20], 1u); });
   __syncthreads();
-  // exclusive prefix over the threads of `sum`, and the total
-  auto scan = [&](uint32_t sum, uint32_t* total) {
-    uint32_t inc = sum;
-#pragma unroll
-    for (int o = 1; o < 64; o <<= 1) {
-      const uint32_t a = __shfl_up(inc, o);
-      if (lane >= o) inc += a;
-    }
-    __syncthreads();                                        // earlier readers of wsum are done
-    if (lane == 63) wsum[w] = inc;
-    __syncthreads();
-    uint32_t running = inc - sum, tot = 0;
-    for (int x = 0; x < NT / 64; ++x) { if (x < w) running += wsum[x]; tot += wsum[x]; }
-    *total = tot;
-    return running;
-  };
   // bins from the top: thread tid owns bins 4095 - kFirst tid - i
   uint32_t h[kFirst], sum = 0;
 #pragma unroll
   for (int i = 0; i < kFirst; ++i) { h[i] = hist[4095 - (kFirst * tid + i)]; sum += h[i]; }
   uint32_t m;                                               // sampled slots that exist
-  uint32_t running = scan(sum, &m);
+  uint32_t running = block_scan_excl<NT / 64>(sum, wsum, &m);
   const float kappa = (float)want * (float)m / (float)n;
   const float root = 3.0f + sqrtf(9.0f + kappa);
   const uint32_t r = (uint32_t)ceilf(root * root);
@@ -566,8 +550,7 @@ __device__ __forceinline__ void sample_rank_body(const int64_t n, int32_t k, F&&
     sum = 0;
 #pragma unroll
     for (int i = 0; i < kSecond; ++i) { g[i] = hist[1023 - (kSecond * tid + i)]; sum += g[i]; }
-    uint32_t unused;
-    running = scan(sum, &unused);
+    running = block_scan_excl<NT / 64>(sum, wsum);
 #pragma unroll
     for (int i = 0; i < kSecond; ++i) {
       if (running < rem && rem <= running + g[i]) {

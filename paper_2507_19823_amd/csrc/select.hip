@@ -56,22 +56,13 @@ __device__ __forceinline__ void sel_each(const float* __restrict__ v, int64_t c0
 // histogram by itself - 8 KB from L2 - instead of waiting for a launch of its own that would.
 __device__ __forceinline__ void sel_find_bin(const uint32_t* __restrict__ gh, uint32_t* bin, uint32_t* rem) {
   __shared__ uint32_t wsum[4], s_bin, s_rem;
-  const int t = threadIdx.x, lane = t & 63, w = t >> 6;
+  const int t = threadIdx.x;
   uint32_t h[8];
   uint32_t sum = 0;
 #pragma unroll
   for (int i = 0; i < 8; ++i) { h[i] = gh[kBins - 1 - (8 * t + i)]; sum += h[i]; }     // bins from the top
-  uint32_t inc = sum;
-#pragma unroll
-  for (int o = 1; o < 64; o <<= 1) {
-    const uint32_t x = __shfl_up(inc, o);
-    if (lane >= o) inc += x;
-  }
   __syncthreads();
-  if (lane == 63) wsum[w] = inc;
-  __syncthreads();
-  uint32_t running = inc - sum;
-  for (int x = 0; x < w; ++x) running += wsum[x];
+  uint32_t running = block_scan_excl<4>(sum, wsum);
   const uint32_t want = *rem;
 #pragma unroll
   for (int i = 0; i < 8; ++i) {
@@ -130,8 +121,8 @@ __global__ __launch_bounds__(256) void sel_count(const float* __restrict__ vals,
     gt += live && key > T;
     eq += live && key == T;
   });
-#pragma unroll
-  for (int o = 32; o >= 1; o >>= 1) { gt += __shfl_xor(gt, o); eq += __shfl_xor(eq, o); }
+  gt = wave_sum(gt);
+  eq = wave_sum(eq);
   const int w = threadIdx.x >> 6;
   if ((threadIdx.x & 63) == 0) { red[0][w] = gt; red[1][w] = eq; }
   __syncthreads();
@@ -156,8 +147,8 @@ __device__ __forceinline__ bool sel_try_zero(const uint32_t* __restrict__ ccount
     g += ccount[((int64_t)row * nchunks + c) * 2];
     e += ccount[((int64_t)row * nchunks + c) * 2 + 1];
   }
-#pragma unroll
-  for (int o = 32; o >= 1; o >>= 1) { g += __shfl_xor(g, o); e += __shfl_xor(e, o); }
+  g = wave_sum(g);
+  e = wave_sum(e);
   if ((t & 63) == 0) { red[0][t >> 6] = g; red[1][t >> 6] = e; }
   __syncthreads();
   const uint64_t above = (uint64_t)red[0][0] + red[0][1] + red[0][2] + red[0][3];
@@ -331,23 +322,6 @@ __global__ void tk_zero(uint32_t* p, int64_t n) {
   if (i < n) p[i] = 0;
 }
 
-// exclusive prefix sum of one value per thread over a 256-thread workgroup
-__device__ __forceinline__ uint32_t block_scan_excl_256(uint32_t v, uint32_t* wsum /*[4]*/) {
-  const int lane = threadIdx.x & 63, w = threadIdx.x >> 6;
-  uint32_t inc = v;
-#pragma unroll
-  for (int o = 1; o < 64; o <<= 1) {
-    const uint32_t a = __shfl_up(inc, o);
-    if (lane >= o) inc += a;
-  }
-  if (lane == 63) wsum[w] = inc;
-  __syncthreads();
-  uint32_t base = 0;
-  for (int x = 0; x < w; ++x) base += wsum[x];
-  __syncthreads();
-  return base + inc - v;
-}
-
 // LDS counter updates, to be called by all lanes of a wave together.  When every participating lane
 // targets the same counter (ties, clustered scores) the wave issues one atomic instead of up to 64
 // serialised ones on the same word.
@@ -472,7 +446,7 @@ __global__ __launch_bounds__(256) void tk_findbin(int n_kv_heads, SelRows sr, To
     gh[b] = 0;                 // leave the histogram clean for the next selection on this workspace
     sum += h[i];
   }
-  uint32_t running = block_scan_excl_256(sum, wsum);
+  uint32_t running = block_scan_excl<4>(sum, wsum);
 #pragma unroll
   for (int i = 0; i < 16; ++i) {
     if (running < (uint32_t)want && (uint32_t)want <= running + h[i]) {
@@ -525,12 +499,7 @@ __device__ __forceinline__ void collect_chunk(const float* __restrict__ vals, in
     __syncthreads();
     if (w == 0) {
       const uint32_t mine = pc[lane];
-      uint32_t inc = mine;
-#pragma unroll
-      for (int o = 1; o < 64; o <<= 1) {
-        const uint32_t a2 = __shfl_up(inc, o);
-        if (lane >= o) inc += a2;
-      }
+      const uint32_t inc = wave_scan_incl(mine);
       po[lane] = inc - mine;
       if (lane == 63) s_total = inc;
     }
@@ -545,8 +514,7 @@ __device__ __forceinline__ void collect_chunk(const float* __restrict__ vals, in
     base += s_total;
     __syncthreads();
   }
-#pragma unroll
-  for (int o = 32; o >= 1; o >>= 1) cnt += __shfl_xor(cnt, o);
+  cnt = wave_sum(cnt);
   if (lane == 0) wsum[w] = cnt;
   __syncthreads();
   if (threadIdx.x == 0) {
@@ -576,23 +544,6 @@ __global__ __launch_bounds__(256) void tk_collect_sampled(const float* __restric
   });
 }
 
-// exclusive prefix sum of one value per thread over a 1024-thread workgroup
-__device__ __forceinline__ uint32_t block_scan_excl_1024(uint32_t v, uint32_t* wsum /*[16]*/) {
-  const int lane = threadIdx.x & 63, w = threadIdx.x >> 6;
-  uint32_t inc = v;
-#pragma unroll
-  for (int o = 1; o < 64; o <<= 1) {
-    const uint32_t a = __shfl_up(inc, o);
-    if (lane >= o) inc += a;
-  }
-  if (lane == 63) wsum[w] = inc;
-  __syncthreads();
-  uint32_t base = 0;
-  for (int x = 0; x < w; ++x) base += wsum[x];
-  __syncthreads();
-  return base + inc - v;
-}
-
 // One workgroup per row: finishes the select inside bin b* (two 10-bit passes over the
 // candidates, or over the whole row when there were too many to keep) and builds the chunk
 // offsets of (#key > T, #key == T) for the ordered emit.
@@ -609,7 +560,7 @@ __global__ __launch_bounds__(1024) void tk_resolve(int64_t chunk, int nchunks, i
   if (sr.want[row / n_kv_heads] <= 0) return;
   const uint32_t bin = t.state[4 * row + 2];
   const uint2* cand = t.cand + (int64_t)row * t.row_entries;
-  const int tid = threadIdx.x, lane = tid & 63, wv = tid >> 6;
+  const int tid = threadIdx.x, lane = tid & 63, wv = __builtin_amdgcn_readfirstlane(tid >> 6);
   uint32_t prefix = bin << 20, rem = t.state[4 * row + 1];
   cnt[tid] = tid < nchunks ? t.ncand[(int64_t)row * kMaxChunks + tid] : 0;
   if (tid == 0) s_n = 0;
@@ -722,7 +673,7 @@ __global__ __launch_bounds__(1024) void tk_resolve(int64_t chunk, int nchunks, i
     });
     __syncthreads();
     const uint32_t mine = h[1023 - tid];                    // thread tid owns bin 1023 - tid
-    const uint32_t running = block_scan_excl_1024(mine, wsum);
+    const uint32_t running = block_scan_excl<16>(mine, wsum);
     if (running < rem && rem <= running + mine) {
       s_prefix = prefix | ((uint32_t)(1023 - tid) << shift);
       s_rem = rem - running;
@@ -743,8 +694,8 @@ __global__ __launch_bounds__(1024) void tk_resolve(int64_t chunk, int nchunks, i
   __syncthreads();
   const uint32_t g = (tid < nchunks) ? t.above[(int64_t)row * 1024 + tid] + h[tid] : 0;
   const uint32_t q = (tid < nchunks) ? e[tid] : 0;
-  const uint32_t og = block_scan_excl_1024(g, wsum);
-  const uint32_t oe = block_scan_excl_1024(q, wsum);
+  const uint32_t og = block_scan_excl<16>(g, wsum);
+  const uint32_t oe = block_scan_excl<16>(q, wsum);
   if (tid < nchunks) {
     t.coff[((int64_t)row * nchunks + tid) * 2] = og;
     t.coff[((int64_t)row * nchunks + tid) * 2 + 1] = oe;
@@ -784,12 +735,7 @@ __global__ __launch_bounds__(256) void tk_emit_lists(int64_t chunk, int nchunks,
       fe[i] = p < m && en[i].x == T;
       ng += fg[i]; ne += fe[i];
     }
-    uint32_t ig = ng, ie = ne;
-#pragma unroll
-    for (int o = 1; o < 64; o <<= 1) {
-      const uint32_t ag = __shfl_up(ig, o), ae = __shfl_up(ie, o);
-      if (lane >= o) { ig += ag; ie += ae; }
-    }
+    const uint32_t ig = wave_scan_incl(ng), ie = wave_scan_incl(ne);
     if (lane == 63) { wsum[0][w] = ig; wsum[1][w] = ie; }
     __syncthreads();
     uint32_t pg = base_g + ig - ng, pe = base_e + ie - ne;
@@ -913,11 +859,8 @@ __global__ __launch_bounds__(1024) void tk_row_select(const float* __restrict__ 
     vhi = fmaxf(vhi, f[x]);
     plain = plain && f[x] < INFINITY;
   }
-#pragma unroll
-  for (int o = 32; o >= 1; o >>= 1) {
-    vlo = fminf(vlo, __shfl_xor(vlo, o));
-    vhi = fmaxf(vhi, __shfl_xor(vhi, o));
-  }
+  vlo = wave_min(vlo);
+  vhi = wave_max(vhi);
   plain = __builtin_amdgcn_ballot_w64(!plain) == 0;
   if (lane == 0) { wlo[wv] = __float_as_uint(vlo); whi[wv] = __float_as_uint(vhi); wplain[wv] = plain; }
   __syncthreads();
@@ -967,8 +910,7 @@ __global__ __launch_bounds__(1024) void tk_row_select(const float* __restrict__ 
     float m = INFINITY;
 #pragma unroll
     for (int x = 0; x < KPT; ++x) m = f[x] >= cut ? fminf(m, f[x]) : m;
-#pragma unroll
-    for (int o = 32; o >= 1; o >>= 1) m = fminf(m, __shfl_xor(m, o));
+    m = wave_min(m);
     if (lane == 0) wlo[wv] = __float_as_uint(m);
     __syncthreads();
     for (int x = 0; x < 16; ++x) m = fminf(m, __uint_as_float(wlo[x]));
@@ -988,7 +930,7 @@ __global__ __launch_bounds__(1024) void tk_row_select(const float* __restrict__ 
     uint32_t hb[4], sum = 0;
 #pragma unroll
     for (int i = 0; i < 4; ++i) { hb[i] = h[kBins12 - 1 - (4 * tid + i)]; sum += hb[i]; }
-    uint32_t running = block_scan_excl_1024(sum, wsum);
+    uint32_t running = block_scan_excl<16>(sum, wsum);
     if (tid == 1023 && all != 0) hb[3] = all - (running + sum);
 #pragma unroll
     for (int i = 0; i < 4; ++i) {
@@ -1038,12 +980,8 @@ __global__ __launch_bounds__(1024) void tk_row_select(const float* __restrict__ 
           lo = kk < lo ? kk : lo;
           hi = kk > hi ? kk : hi;
         }
-#pragma unroll
-      for (int o = 32; o >= 1; o >>= 1) {
-        const uint32_t a = __shfl_xor(lo, o), b = __shfl_xor(hi, o);
-        lo = a < lo ? a : lo;
-        hi = b > hi ? b : hi;
-      }
+      lo = wave_min(lo);
+      hi = wave_max(hi);
       __syncthreads();                                      // everybody has read the row's extremes
       if (lane == 0) { wlo[wv] = lo; whi[wv] = hi; }
       __syncthreads();
@@ -1121,7 +1059,8 @@ __global__ __launch_bounds__(1024) void tk_row_select(const float* __restrict__ 
     if (lane == 0) { wlo[wv] = ng; whi[wv] = ne; }
     __syncthreads();
     uint32_t pg = 0, pe = 0;
-    for (int x = 0; x < wv; ++x) { pg += wlo[x]; pe += whi[x]; }
+#pragma unroll
+    for (int x = 0; x < 16; ++x) { pg += x < wv ? wlo[x] : 0; pe += x < wv ? whi[x] : 0; }
 #pragma unroll
     for (int x = 0; x < KPT; ++x) {
       const bool is_g = above(x), is_e = equal(x);
@@ -1198,24 +1137,6 @@ __device__ __forceinline__ void lds_count_few(uint32_t* h, uint32_t bin, bool hi
   if ((todo >> lane) & 1) atomicAdd(&h[bin], 1u);
 }
 
-// exclusive prefix sum of one value per thread over a workgroup of NT threads
-template <int NT>
-__device__ __forceinline__ uint32_t block_scan_excl(uint32_t v, uint32_t* wsum /*[NT / 64]*/) {
-  const int lane = threadIdx.x & 63, w = threadIdx.x >> 6;
-  uint32_t inc = v;
-#pragma unroll
-  for (int o = 1; o < 64; o <<= 1) {
-    const uint32_t a = __shfl_up(inc, o);
-    if (lane >= o) inc += a;
-  }
-  if (lane == 63) wsum[w] = inc;
-  __syncthreads();
-  uint32_t base = 0;
-  for (int x = 0; x < w; ++x) base += wsum[x];
-  __syncthreads();
-  return base + inc - v;
-}
-
 template <int NT>
 struct ResolveShared {
   uint32_t h[kBins12], off[1025], wsum[16];
@@ -1249,7 +1170,7 @@ __device__ __forceinline__ void tk_resolve_pairs(ResolveShared<NT>& sh, const in
       if (off[c + s] <= p) c += s;
     return gl[(int64_t)c * chunk + (p - off[c])];
   };
-  const int lane = tid & 63, wv = tid >> 6;
+  const int lane = tid & 63, wv = __builtin_amdgcn_readfirstlane(tid >> 6);
   uint32_t kmax = 0;                                        // largest key this thread has seen
   constexpr int kPer = kHeldPairs / NT, kStep = NT == 512 ? 4 : 8;
   const uint32_t per = (total + NT - 1) / NT;               // HELD: pairs per thread ...
@@ -1340,10 +1261,10 @@ __device__ __forceinline__ void tk_resolve_pairs(ResolveShared<NT>& sh, const in
     }
   };
   if (!HELD) visit([&](uint32_t key, uint32_t, bool hit) { if (hit && key > kmax) kmax = key; });
-#pragma unroll
-  for (int o = 32; o >= 1; o >>= 1) { const uint32_t v = __shfl_xor(kmax, o); kmax = v > kmax ? v : kmax; }
+  kmax = wave_max(kmax);
   if (lane == 0) wsum[wv] = kmax;
   __syncthreads();
+#pragma unroll
   for (int x = 0; x < NW; ++x) kmax = wsum[x] > kmax ? wsum[x] : kmax;
   __syncthreads();
   // Radix select on d = key - base (every key of the list is >= base, the scan's threshold): pd = the leading
@@ -1364,7 +1285,7 @@ __device__ __forceinline__ void tk_resolve_pairs(ResolveShared<NT>& sh, const in
     uint32_t hb[BPT], sum = 0;
 #pragma unroll
     for (int i = 0; i < BPT; ++i) { hb[i] = h[kBins12 - 1 - (BPT * tid + i)]; sum += hb[i]; }
-    uint32_t running = block_scan_excl<NT>(sum, wsum);
+    uint32_t running = block_scan_excl<NT / 64>(sum, wsum);
 #pragma unroll
     for (int i = 0; i < BPT; ++i) {
       if (running < rem && rem <= running + hb[i]) {
@@ -1428,7 +1349,7 @@ __device__ __forceinline__ void tk_resolve_pairs(ResolveShared<NT>& sh, const in
     uint32_t mine[PER], msum = 0;                           // thread tid owns bins 1023 - (PER tid + x)
 #pragma unroll
     for (int x = 0; x < PER; ++x) { mine[x] = h[1023 - (PER * tid + x)]; msum += mine[x]; }
-    uint32_t running = block_scan_excl<NT>(msum, wsum);
+    uint32_t running = block_scan_excl<NT / 64>(msum, wsum);
 #pragma unroll
     for (int x = 0; x < PER; ++x) {
       if (running < rem && rem <= running + mine[x]) {
@@ -1463,7 +1384,8 @@ __device__ __forceinline__ void tk_resolve_pairs(ResolveShared<NT>& sh, const in
     if (lane == 0) { wsum[wv] = ng; h[wv] = ne; }
     __syncthreads();
     uint32_t pg = 0, pe = 0;
-    for (int x = 0; x < wv; ++x) { pg += wsum[x]; pe += h[x]; }
+#pragma unroll
+    for (int x = 0; x < NW; ++x) { pg += x < wv ? wsum[x] : 0; pe += x < wv ? h[x] : 0; }
 #pragma unroll
     for (int u0 = 0; u0 < kPer; u0 += kStep) {
       if ((uint32_t)u0 >= per) break;
@@ -1506,8 +1428,8 @@ __device__ __forceinline__ void tk_resolve_pairs(ResolveShared<NT>& sh, const in
         ++e;
       }
     }
-    uint32_t rg = block_scan_excl<NT>(ng, wsum);            // pairs above T on lower slots
-    uint32_t re = block_scan_excl<NT>(ne, wsum);            // pairs equal to T on lower slots
+    uint32_t rg = block_scan_excl<NT / 64>(ng, wsum);            // pairs above T on lower slots
+    uint32_t re = block_scan_excl<NT / 64>(ne, wsum);            // pairs equal to T on lower slots
     if (p0 < p1) {
       uint32_t c = 0;
 #pragma unroll
@@ -1553,8 +1475,8 @@ __device__ __forceinline__ void tk_resolve_pairs(ResolveShared<NT>& sh, const in
     uint32_t g[PER], e[PER], gs = 0, es = 0;
 #pragma unroll
     for (int x = 0; x < PER; ++x) { g[x] = cg[PER * tid + x]; e[x] = ce[PER * tid + x]; gs += g[x]; es += e[x]; }
-    uint32_t og = block_scan_excl<NT>(gs, wsum);
-    uint32_t oe = block_scan_excl<NT>(es, wsum);
+    uint32_t og = block_scan_excl<NT / 64>(gs, wsum);
+    uint32_t oe = block_scan_excl<NT / 64>(es, wsum);
 #pragma unroll
     for (int x = 0; x < PER; ++x) {
       cg[PER * tid + x] = og;
@@ -1623,7 +1545,7 @@ __device__ __forceinline__ void tk_resolve_emit_body(const int64_t chunk, const 
       mine[x] = c < nchunks ? so.ncand[(int64_t)row * kSelectMaxChunks + c] : 0;
       sum += mine[x];
     }
-    uint32_t before = block_scan_excl<NT>(sum, wsum);
+    uint32_t before = block_scan_excl<NT / 64>(sum, wsum);
 #pragma unroll
     for (int x = 0; x < PER; ++x) { off[tid * PER + x] = before; before += mine[x]; }
     if (tid == NT - 1) off[1024] = before;
@@ -1646,7 +1568,7 @@ __device__ __forceinline__ void tk_resolve_emit_body(const int64_t chunk, const 
       const int c = tid * PER + x;
       sum1 += c < nchunks ? so.n1[(int64_t)row * kSelectMaxChunks + c] : 0;
     }
-    const uint32_t before1 = block_scan_excl<NT>(sum1, wsum);
+    const uint32_t before1 = block_scan_excl<NT / 64>(sum1, wsum);
     if (tid == NT - 1) {
       const uint32_t enough = before1 + sum1 >= (uint32_t)want;
       spec[0] = enough && spec[1] == 0 ? spec[2] : 0;       // (a second failure cannot happen: the count is exact)
@@ -1685,7 +1607,7 @@ __global__ __launch_bounds__(1024) __attribute__((amdgpu_waves_per_eu(4))) void 
   const uint32_t K = so.spec[4 * row];
   const uint32_t mine = tid < nchunks ? so.ncand[(int64_t)row * kSelectMaxChunks + tid] : 0;
   const uint32_t equal = tid < nchunks ? so.n1[(int64_t)row * kSelectMaxChunks + tid] : 0;
-  const uint32_t before = block_scan_excl<1024>(mine, sh.wsum), before_e = block_scan_excl<1024>(equal, sh.wsum);
+  const uint32_t before = block_scan_excl<16>(mine, sh.wsum), before_e = block_scan_excl<16>(equal, sh.wsum);
   uint32_t* eoff = sh.h;                                    // equal slots in the chunks before
   off[tid] = before;
   eoff[tid] = before_e;
@@ -2114,11 +2036,7 @@ __global__ __launch_bounds__(256) void tp_hist(const float* __restrict__ vals, i
     const uint32_t x = t.above[(int64_t)row * 1024 + c];
     kmax = x > kmax ? x : kmax;
   }
-#pragma unroll
-  for (int o = 32; o >= 1; o >>= 1) {
-    const uint32_t other = __shfl_xor(kmax, o);
-    if (other > kmax) kmax = other;
-  }
+  kmax = wave_max(kmax);
   const int lane = threadIdx.x & 63;
   if (lane == 0) wmax[threadIdx.x >> 6] = kmax;
   if (threadIdx.x >> 6 == 1) {
@@ -2180,24 +2098,6 @@ __global__ __launch_bounds__(256) void tp_hist(const float* __restrict__ vals, i
   }
 }
 
-// exclusive prefix sum of one 64-bit value per thread over a 256-thread workgroup; *total gets the sum
-__device__ __forceinline__ uint64_t block_scan_excl_256_u64(uint64_t v, uint64_t* wsum /*[4]*/, uint64_t* total) {
-  const int lane = threadIdx.x & 63, w = threadIdx.x >> 6;
-  uint64_t inc = v;
-#pragma unroll
-  for (int o = 1; o < 64; o <<= 1) {
-    const uint64_t a = __shfl_up((unsigned long long)inc, o);
-    if (lane >= o) inc += a;
-  }
-  if (lane == 63) wsum[w] = inc;
-  __syncthreads();
-  uint64_t base = 0;
-  for (int x = 0; x < w; ++x) base += wsum[x];
-  *total = wsum[0] + wsum[1] + wsum[2] + wsum[3];
-  __syncthreads();
-  return base + inc - v;
-}
-
 // Z, Theta, and the first bin (from the top) in which the running weight reaches Theta or the running count reaches
 // k_max - found by every workgroup from the finished histogram, 24 KB from L2, instead of in a launch of its own - and
 // then the ordered lists of the slots in or above that bin.
@@ -2227,8 +2127,8 @@ __global__ __launch_bounds__(256) void tp_collect(const float* __restrict__ vals
       msum += hm[i];
     }
     uint64_t Z;
-    uint64_t run_m = block_scan_excl_256_u64(msum, wsum64, &Z);
-    uint32_t run_c = block_scan_excl_256(csum, wsum);
+    uint64_t run_m = block_scan_excl<4>(msum, wsum64, &Z);
+    uint32_t run_c = block_scan_excl<4>(csum, wsum);
     uint64_t theta = tau_one ? Z : __umul64hi(Z, tau_fix);
     if (theta < 1) theta = 1;
     if (threadIdx.x == 255) hc[BPT - 1] = (uint32_t)sr.nsel[row / n_kv_heads] - (run_c + csum);     // bin 0
@@ -2277,23 +2177,6 @@ __global__ void tp_no_mass(uint64_t* __restrict__ mass_out, int n) {
   if (i < n) mass_out[i] = 0;
 }
 
-// exclusive prefix sums over a 1024-thread workgroup (one value per thread)
-__device__ __forceinline__ uint64_t block_scan_excl_1024_u64(uint64_t v, uint64_t* wsum /*[16]*/) {
-  const int lane = threadIdx.x & 63, w = threadIdx.x >> 6;
-  uint64_t inc = v;
-#pragma unroll
-  for (int o = 1; o < 64; o <<= 1) {
-    const uint64_t a = __shfl_up((unsigned long long)inc, o);
-    if (lane >= o) inc += a;
-  }
-  if (lane == 63) wsum[w] = inc;
-  __syncthreads();
-  uint64_t base = 0;
-  for (int x = 0; x < w; ++x) base += wsum[x];
-  __syncthreads();
-  return base + inc - v;
-}
-
 // One workgroup per row: finishes the walk inside bin b* (digits of the distance from the bin's smallest key, then the
 // group of equal keys, whose members all weigh the same) and builds the chunk offsets for the ordered emit.
 __global__ __launch_bounds__(1024) void tp_resolve(int64_t chunk, int nchunks, int n_kv_heads, SelRows sr, float sm_scale,
@@ -2308,7 +2191,7 @@ __global__ __launch_bounds__(1024) void tp_resolve(int64_t chunk, int nchunks, i
   if (sr.want[row / n_kv_heads] <= 0) return;
   const uint32_t last = t.state[4 * row + 3];               // (the lists hold no key below the bin)
   const uint2* cand = t.cand + (int64_t)row * t.row_entries;
-  const int tid = threadIdx.x, lane = tid & 63, wv = tid >> 6;
+  const int tid = threadIdx.x, lane = tid & 63, wv = __builtin_amdgcn_readfirstlane(tid >> 6);
   const float m = key_to_float(t.prow[4 * row]) * sm_scale;
   uint32_t krem = t.prow[4 * row + 1];
   uint64_t mrem = t.pstate[4 * row];
@@ -2361,12 +2244,8 @@ __global__ __launch_bounds__(1024) void tp_resolve(int64_t chunk, int nchunks, i
     if (hit) { lo = key < lo ? key : lo; hi = key > hi ? key : hi; }
     lds_append(&s_n, lc, (uint32_t)kResolveLds, key, slot, hit);
   });
-#pragma unroll
-  for (int o = 32; o >= 1; o >>= 1) {
-    const uint32_t a = __shfl_xor(lo, o), b = __shfl_xor(hi, o);
-    lo = a < lo ? a : lo;
-    hi = b > hi ? b : hi;
-  }
+  lo = wave_min(lo);
+  hi = wave_max(hi);
   if (lane == 0) { wmin[wv] = lo; wmax[wv] = hi; }
   __syncthreads();
   for (int x = 0; x < 16; ++x) { lo = wmin[x] < lo ? wmin[x] : lo; hi = wmax[x] > hi ? wmax[x] : hi; }
@@ -2444,8 +2323,8 @@ __global__ __launch_bounds__(1024) void tp_resolve(int64_t chunk, int nchunks, i
     __syncthreads();
     const uint32_t mine_c = h[1023 - tid];                  // thread tid owns digit 1023 - tid
     const uint64_t mine_m = hm[1023 - tid];
-    const uint32_t run_c = block_scan_excl_1024(mine_c, wsum);
-    const uint64_t run_m = block_scan_excl_1024_u64(mine_m, wsum64);
+    const uint32_t run_c = block_scan_excl<16>(mine_c, wsum);
+    const uint64_t run_m = block_scan_excl<16>(mine_m, wsum64);
     const bool before = run_m < mrem && run_c < krem;
     const bool after = run_m + mine_m >= mrem || run_c + mine_c >= krem;
     if (before && after && mine_c > 0) {
@@ -2481,8 +2360,8 @@ __global__ __launch_bounds__(1024) void tp_resolve(int64_t chunk, int nchunks, i
   __syncthreads();
   const uint32_t g = (tid < nchunks) ? t.above[(int64_t)row * 1024 + tid] + h[tid] : 0;
   const uint32_t q = (tid < nchunks) ? e[tid] : 0;
-  const uint32_t og = block_scan_excl_1024(g, wsum);
-  const uint32_t oe = block_scan_excl_1024(q, wsum);
+  const uint32_t og = block_scan_excl<16>(g, wsum);
+  const uint32_t oe = block_scan_excl<16>(q, wsum);
   if (tid < nchunks) {
     t.coff[((int64_t)row * nchunks + tid) * 2] = og;
     t.coff[((int64_t)row * nchunks + tid) * 2 + 1] = oe;
