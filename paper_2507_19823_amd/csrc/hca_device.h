@@ -258,8 +258,8 @@ __device__ __forceinline__ float score_tile2(const QOperand<2>& op, uint32_t c0,
 }
 
 // ---- wave-wide scans and reductions by DPP: six dependent vector instructions where six __shfl_up or __shfl_xor go through
-// the LDS crossbar.  Called by all 64 lanes.  (With the workgroup scans reading the waves
-// sums at once: cumulative-weight selection and attend over 8 x 500 003 tokens 157.4 -> 155.0 us, eviction 126.2 -> 124.9.)
+// the LDS crossbar.  Called by all 64 lanes.  (With the workgroup scans reading the
+// waves' sums at once: cumulative-weight selection and attend over 8 x 500 003 tokens 157.4 -> 155.0 us, eviction 126.2 -> 124.9.)
 template <int CTRL, int ROWS>
 __device__ __forceinline__ uint32_t dpp_or(uint32_t other, uint32_t v) {      // `other` where no lane is shifted in
   return (uint32_t)__builtin_amdgcn_update_dpp((int)other, (int)v, CTRL, ROWS, 0xf, false);

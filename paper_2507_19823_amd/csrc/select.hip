@@ -462,10 +462,15 @@ __global__ __launch_bounds__(256) void tk_findbin(int n_kv_heads, SelRows sr, To
 // counts the ones strictly above the bin.  Lists are per chunk so that no two workgroups ever
 // contend for an append position.
 // range(&first, &last): the smallest and the largest key of the bin, asked for while the first tile is on its way.
-// ABOVE: the keys above `first` are listed and those equal to it counted.
+// ABOVE: the keys above `first` are listed, in `room`, and those equal to it counted.
+struct ListRoom {          // lists of a selection by a sampled key
+  uint2* pairs;            // [rows][pair_row]: (key, slot), pair_chunk per chunk, the rest of a longer list left out
+  uint32_t* slots;         // [rows][slot_row]: the whole list's slots, a chunk's slots per chunk (null: pair_chunk suffices)
+  int64_t pair_row, pair_chunk, slot_row;
+};
 template <bool ABOVE, typename F>
 __device__ __forceinline__ void collect_chunk(const float* __restrict__ vals, int64_t stride, int64_t chunk, int64_t nsel,
-                                              int row, const TopkWs& t, F&& range) {
+                                              int row, const TopkWs& t, F&& range, const ListRoom& room = ListRoom{}) {
   __shared__ uint32_t wsum[4];
   __shared__ uint32_t pc[64], po[64];
   __shared__ uint32_t s_total;
@@ -508,7 +513,13 @@ __device__ __forceinline__ void collect_chunk(const float* __restrict__ vals, in
     for (int x = 0; x < 16; ++x) {
       if ((mask[x] >> lane) & 1) {
         const uint32_t at = base + po[x * 4 + w] + (uint32_t)__popcll(mask[x] & ((1ull << lane) - 1));
-        dst[at] = uint2{key[x], (uint32_t)(s0 + x * 256 + threadIdx.x)};
+        const uint32_t slot = (uint32_t)(s0 + x * 256 + threadIdx.x);
+        if constexpr (ABOVE) {
+          if (at < room.pair_chunk) room.pairs[row * room.pair_row + blockIdx.x * room.pair_chunk + at] = uint2{key[x], slot};
+          if (room.slots != nullptr) room.slots[row * room.slot_row + blockIdx.x * chunk + at] = slot;
+        } else {
+          dst[at] = uint2{key[x], slot};
+        }
       }
     }
     base += s_total;
@@ -535,13 +546,14 @@ __global__ __launch_bounds__(256) void tk_collect(const float* __restrict__ vals
 
 // The same with a sampled key in place of a bin: the keys above it.
 __global__ __launch_bounds__(256) void tk_collect_sampled(const float* __restrict__ vals, int64_t stride, int64_t chunk,
-                                                          int n_kv_heads, SelRows sr, TopkWs t) {
+                                                          int n_kv_heads, SelRows sr, TopkWs t,
+                                                          ListRoom room) {
   const int row = blockIdx.y;
   if (sr.want[row / n_kv_heads] <= 0) return;
   collect_chunk<true>(vals, stride, chunk, sr.nsel[row / n_kv_heads], row, t, [&](uint32_t* first, uint32_t* last) {
     *first = t.state[4 * row];
     *last = 0;
-  });
+  }, room);
 }
 
 // One workgroup per row: finishes the select inside bin b* (two 10-bit passes over the
@@ -1144,10 +1156,25 @@ struct ResolveShared {
   uint32_t s_prefix, s_rem, s_cb;
 };
 
+// A row's lists: (key, slot) pairs, or slots alone beside the row's scores.
+struct PairList {
+  const uint2* p;
+  __device__ __forceinline__ uint2 operator[](int64_t at) const { return p[at]; }
+  __device__ __forceinline__ uint32_t key(int64_t at) const { return p[at].x; }
+  __device__ __forceinline__ uint32_t slot(int64_t at) const { return p[at].y; }
+};
+struct SlotList {
+  const uint32_t* p;
+  const float* scores;
+  __device__ __forceinline__ uint2 operator[](int64_t at) const { return uint2{order_key(scores[p[at]]), p[at]}; }
+  __device__ __forceinline__ uint32_t key(int64_t at) const { return order_key(scores[p[at]]); }
+  __device__ __forceinline__ uint32_t slot(int64_t at) const { return p[at]; }
+};
+
 // The selection proper, once the chunks' offsets are in sh.off.  HELD: every pair's key in a register.
-template <int NT, bool HELD>
+template <int NT, bool HELD, typename List>
 __device__ __forceinline__ void tk_resolve_pairs(ResolveShared<NT>& sh, const int64_t chunk, const int nchunks,
-                                                 const int64_t want, const SelectOut& so, const uint32_t base_key,
+                                                 const int64_t want, const List& gl, const uint32_t base_key,
                                                  const int32_t k, int32_t* __restrict__ idx, int32_t* __restrict__ count,
                                                  const int row, const uint32_t total) {
   constexpr int NW = NT / 64;              // waves
@@ -1158,7 +1185,6 @@ __device__ __forceinline__ void tk_resolve_pairs(ResolveShared<NT>& sh, const in
   auto& cmap = sh.cmap;
   uint32_t &s_prefix = sh.s_prefix, &s_rem = sh.s_rem, &s_cb = sh.s_cb;
   const int tid = threadIdx.x;
-  const uint2* gl = so.lists + (int64_t)row * so.row_entries;
   // beyond kHeldPairs: up to kSearchMax pairs are still addressed by their position in slot order (short lists:
   // walking them chunk by chunk would cost a memory round trip per chunk), more than that are walked chunk by chunk
   const bool by_position = total <= (uint32_t)kSearchMax;
@@ -1215,7 +1241,7 @@ __device__ __forceinline__ void tk_resolve_pairs(ResolveShared<NT>& sh, const in
       if ((uint32_t)u0 < per) {
         locate(u0, at);
 #pragma unroll
-        for (int u = 0; u < kStep; ++u) held[u0 + u] = at[u] != 0xffffffffu ? gl[at[u]].x : 0;
+        for (int u = 0; u < kStep; ++u) held[u0 + u] = at[u] != 0xffffffffu ? gl.key(at[u]) : 0;
       } else {
 #pragma unroll
         for (int u = 0; u < kStep; ++u) held[u0 + u] = 0;
@@ -1249,11 +1275,11 @@ __device__ __forceinline__ void tk_resolve_pairs(ResolveShared<NT>& sh, const in
     } else {
       for (int c = wv; c < nchunks; c += NW) {
         const uint32_t m = off[c + 1] - off[c];
-        const uint2* src = gl + (int64_t)c * chunk;
+        const int64_t src = (int64_t)c * chunk;
         for (uint32_t i0 = 0; i0 < m; i0 += 1024) {
           uint2 x[16];
 #pragma unroll
-          for (int v = 0; v < 16; ++v) x[v] = i0 + v * 64 + lane < m ? src[i0 + v * 64 + lane] : uint2{0, 0};
+          for (int v = 0; v < 16; ++v) x[v] = i0 + v * 64 + lane < m ? gl[src + i0 + v * 64 + lane] : uint2{0, 0};
 #pragma unroll
           for (int v = 0; v < 16; ++v) f(x[v].x, x[v].y, i0 + v * 64 + lane < m);
         }
@@ -1393,7 +1419,7 @@ __device__ __forceinline__ void tk_resolve_pairs(ResolveShared<NT>& sh, const in
       locate(u0, at);
       uint32_t slot[kStep];
 #pragma unroll
-      for (int u = 0; u < kStep; ++u) slot[u] = held[u0 + u] >= T ? gl[at[u]].y : 0;    // (T > 0: a pair)
+      for (int u = 0; u < kStep; ++u) slot[u] = held[u0 + u] >= T ? gl.slot(at[u]) : 0;    // (T > 0: a pair)
 #pragma unroll
       for (int u = 0; u < kStep; ++u) {
         const bool fg = held[u0 + u] > T, fe = held[u0 + u] == T;
@@ -1422,7 +1448,7 @@ __device__ __forceinline__ void tk_resolve_pairs(ResolveShared<NT>& sh, const in
       uint32_t e = p0 - off[c];
       for (uint32_t p = p0; p < p1; ++p) {
         while (e >= off[c + 1] - off[c]) { ++c; e = 0; }
-        const uint32_t key = gl[(int64_t)c * chunk + e].x;
+        const uint32_t key = gl.key((int64_t)c * chunk + e);
         ng += key > T;
         ne += key == T;
         ++e;
@@ -1455,11 +1481,11 @@ __device__ __forceinline__ void tk_resolve_pairs(ResolveShared<NT>& sh, const in
     uint32_t g = 0, e = 0;
     if (c < nchunks) {
       const uint32_t m = off[c + 1] - off[c];
-      const uint2* src = gl + (int64_t)c * chunk;
+      const int64_t src = (int64_t)c * chunk;
       for (uint32_t i0 = 0; i0 < m; i0 += 1024) {
         uint32_t key[16];
 #pragma unroll
-        for (int v = 0; v < 16; ++v) key[v] = i0 + v * 64 + lane < m ? src[i0 + v * 64 + lane].x : 0u;
+        for (int v = 0; v < 16; ++v) key[v] = i0 + v * 64 + lane < m ? gl.key(src + i0 + v * 64 + lane) : 0u;
 #pragma unroll
         for (int v = 0; v < 16; ++v) {
           const bool live = i0 + v * 64 + lane < m;
@@ -1489,12 +1515,12 @@ __device__ __forceinline__ void tk_resolve_pairs(ResolveShared<NT>& sh, const in
   const uint64_t lt = (1ull << lane) - 1;
   for (int c = wv; c < nchunks; c += NW) {
     const uint32_t m = off[c + 1] - off[c];
-    const uint2* src = gl + (int64_t)c * chunk;
+    const int64_t src = (int64_t)c * chunk;
     uint32_t pg = cg[c], pe = ce[c];
     for (uint32_t i0 = 0; i0 < m; i0 += 512) {
       uint2 xs[8];
 #pragma unroll
-      for (int v = 0; v < 8; ++v) xs[v] = i0 + v * 64 + lane < m ? src[i0 + v * 64 + lane] : uint2{0, 0};
+      for (int v = 0; v < 8; ++v) xs[v] = i0 + v * 64 + lane < m ? gl[src + i0 + v * 64 + lane] : uint2{0, 0};
 #pragma unroll
       for (int v = 0; v < 8; ++v) {
         const bool live = i0 + v * 64 + lane < m;
@@ -1577,8 +1603,9 @@ __device__ __forceinline__ void tk_resolve_emit_body(const int64_t chunk, const 
     return;
   }
   const uint32_t base = spec[0];
-  if (total <= (uint32_t)kHeldPairs) tk_resolve_pairs<NT, true>(sh, chunk, nchunks, want, so, base, k, idx, count, row, total);
-  else tk_resolve_pairs<NT, false>(sh, chunk, nchunks, want, so, base, k, idx, count, row, total);
+  const PairList lists{so.lists + (int64_t)row * so.row_entries};
+  if (total <= (uint32_t)kHeldPairs) tk_resolve_pairs<NT, true>(sh, chunk, nchunks, want, lists, base, k, idx, count, row, total);
+  else tk_resolve_pairs<NT, false>(sh, chunk, nchunks, want, lists, base, k, idx, count, row, total);
 }
 
 template <int NT>
@@ -1589,24 +1616,20 @@ __global__ __launch_bounds__(NT) __attribute__((amdgpu_waves_per_eu(NT == 512 ? 
                            (int)blockIdx.x);
 }
 
-// hca_topk's last launch: the chunks' lists hold the keys above the sampled key K (spec), the chunks' second counts those
-// equal to it.  Enough above it: the selection over the lists.  Enough with the equal ones: all of the lists and the first
-// equal slots.  Neither, which takes a row that its samples misrepresent by six deviations: every slot into the lists, by
-// this workgroup.
+// The last launch of a selection from scores: the chunks' lists hold the slots of the keys above the sampled key K
+// (t.state), the chunks' second counts (t.above) the slots equal to it.  Enough above it: the selection over the lists.
+// Enough with the equal ones: all of the lists and the first equal slots.  Neither, which takes a row that its samples
+// misrepresent by six deviations: every slot into the lists, by this workgroup.
 __global__ __launch_bounds__(1024) __attribute__((amdgpu_waves_per_eu(4))) void tk_resolve_scores(
-    const float* __restrict__ vals, int64_t stride, int64_t chunk, int nchunks, int n_kv_heads, SelRows sr, SelectOut so,
-    int32_t k, int32_t* __restrict__ idx, int32_t* __restrict__ count) {
+    const float* __restrict__ vals, int64_t stride, int64_t chunk, int nchunks, int n_kv_heads, SelRows sr, TopkWs t,
+    ListRoom room, int32_t k, int32_t* __restrict__ idx, int32_t* __restrict__ count, RowSelectFused fu) {
   __shared__ ResolveShared<1024> sh;
   auto& off = sh.off;
   const int row = blockIdx.x, tid = threadIdx.x;
   const int64_t n = sr.nsel[row / n_kv_heads], want = sr.want[row / n_kv_heads];
-  if (want <= 0) {
-    if (tid == 0) count[row] = 0;
-    return;
-  }
-  const uint32_t K = so.spec[4 * row];
-  const uint32_t mine = tid < nchunks ? so.ncand[(int64_t)row * kSelectMaxChunks + tid] : 0;
-  const uint32_t equal = tid < nchunks ? so.n1[(int64_t)row * kSelectMaxChunks + tid] : 0;
+  const bool live = want > 0 && tid < nchunks;
+  const uint32_t mine = live ? t.ncand[(int64_t)row * kMaxChunks + tid] : 0;
+  const uint32_t equal = live ? t.above[(int64_t)row * 1024 + tid] : 0;
   const uint32_t before = block_scan_excl<16>(mine, sh.wsum), before_e = block_scan_excl<16>(equal, sh.wsum);
   uint32_t* eoff = sh.h;                                    // equal slots in the chunks before
   off[tid] = before;
@@ -1614,21 +1637,50 @@ __global__ __launch_bounds__(1024) __attribute__((amdgpu_waves_per_eu(4))) void 
   if (tid == 1023) { off[1024] = before + mine; eoff[1024] = before_e + equal; }
   __syncthreads();
   const uint32_t total = off[1024], with_equal = total + eoff[1024];
-  const float* v = vals + (int64_t)row * stride;
-  uint2* lists = so.lists + (int64_t)row * so.row_entries;
-  if (total >= (uint32_t)want) {
-    __syncthreads();                                        // everybody has read eoff
-    if (total <= (uint32_t)kHeldPairs)
-      tk_resolve_pairs<1024, true>(sh, chunk, nchunks, want, so, K, k, idx, count, row, total);
-    else
-      tk_resolve_pairs<1024, false>(sh, chunk, nchunks, want, so, K, k, idx, count, row, total);
+  const bool misread = want > 0 && with_equal < (uint32_t)want;
+  if (fu.spec != nullptr) {                                 // the figures of hca_score_topk's report and monitor
+    for (int c = tid; c < fu.nchunks; c += 1024)
+      fu.ncand[(int64_t)row * kSelectMaxChunks + c] = c == 0 && want > 0 ? (misread ? (uint32_t)n : with_equal) : 0u;
+    if (tid == 0) {
+      fu.spec[4 * row + 1] = misread;
+      if (want > 0 && fu.mon != nullptr) {
+        uint32_t* m = fu.mon + 4 * row;
+        m[0] += 1;
+        m[1] = with_equal < m[1] ? with_equal : m[1];
+        m[2] = with_equal > m[2] ? with_equal : m[2];
+        m[3] += misread;
+      }
+    }
+  }
+  if (want <= 0) {
+    if (tid == 0) count[row] = 0;
     return;
   }
-  if (with_equal < (uint32_t)want) {
-    for (int64_t j = tid; j < n; j += 1024) lists[j] = uint2{order_key(v[j]), (uint32_t)j};
+  const uint32_t K = t.state[4 * row];
+  const float* v = vals + (int64_t)row * stride;
+  const PairList pairs{room.pairs + row * room.pair_row};
+  const SlotList slots{room.slots + row * room.slot_row, v};
+  const bool in_pairs = __syncthreads_and(mine <= (uint32_t)room.pair_chunk);     // (and everybody has read eoff's end)
+  if (total >= (uint32_t)want) {
+    if (in_pairs && total <= (uint32_t)kHeldPairs)
+      tk_resolve_pairs<1024, true>(sh, room.pair_chunk, nchunks, want, pairs, K, k, idx, count, row, total);
+    else if (in_pairs)
+      tk_resolve_pairs<1024, false>(sh, room.pair_chunk, nchunks, want, pairs, K, k, idx, count, row, total);
+    else
+      tk_resolve_pairs<1024, false>(sh, chunk, nchunks, want, slots, K, k, idx, count, row, total);
+    return;
+  }
+  if (misread) {
+    for (int64_t j = tid; j < n; j += 1024) {
+      if (room.slots != nullptr) room.slots[row * room.slot_row + j] = (uint32_t)j;
+      else room.pairs[row * room.pair_row + j] = uint2{order_key(v[j]), (uint32_t)j};
+    }
     for (int i = tid; i < 1025; i += 1024) off[i] = (uint32_t)(i * chunk < n ? i * chunk : n);
     __syncthreads();
-    tk_resolve_pairs<1024, false>(sh, chunk, nchunks, want, so, 0u, k, idx, count, row, (uint32_t)n);
+    if (room.slots != nullptr)
+      tk_resolve_pairs<1024, false>(sh, chunk, nchunks, want, slots, 0u, k, idx, count, row, (uint32_t)n);
+    else
+      tk_resolve_pairs<1024, false>(sh, chunk, nchunks, want, pairs, 0u, k, idx, count, row, (uint32_t)n);
     return;
   }
   // a wave per chunk, in slot order: from the row itself while equal slots are still to take, then from the lists
@@ -1641,7 +1693,8 @@ __global__ __launch_bounds__(1024) __attribute__((amdgpu_waves_per_eu(4))) void 
     uint32_t pg = off[c], pe = eoff[c];
     if (pe >= req || eoff[c + 1] == pe) {
       const uint32_t m = off[c + 1] - pg, e = pe < req ? pe : req;
-      for (uint32_t i = lane; i < m; i += 64) out[pg + e + i] = (int32_t)lists[(int64_t)c * chunk + i].y;
+      for (uint32_t i = lane; i < m; i += 64)
+        out[pg + e + i] = (int32_t)(in_pairs ? pairs.slot(c * room.pair_chunk + i) : slots.slot(c * chunk + i));
       continue;
     }
     const int64_t c0 = (int64_t)c * chunk, c1 = c0 + chunk < n ? c0 + chunk : n;
@@ -1839,6 +1892,31 @@ int32_t launch_select_finish_pair(const Layout& L, const void* const kcache[2], 
   return HCA_OK;
 }
 
+// Top-k of long rows from their scores in three launches: a key from samples, the lists of the slots above it, the selection
+// over them.  Bound by the launches' latency and one pass over the scores.
+static int32_t launch_topk_sampled(const Layout& L, const float* scores, const NRes& nr, int64_t nmax, const SelRows& sr,
+                                   int32_t k, int32_t* idx, int32_t* count, const TopkWs& t, ListRoom room,
+                                   const RowSelectFused& fu, hipStream_t st) {
+  int64_t chunk;
+  int32_t nchunks;
+  chunk_geometry(nmax, &chunk, &nchunks);
+  if (room.slots == nullptr) room.pair_chunk = chunk;
+  else if ((room.pair_chunk = room.pair_row / nchunks) > chunk) room.pair_chunk = chunk;
+  const int32_t rc = launch_topk_sample_rank(scores, L.cap, L.rows, L.n_kv_heads, nr, k, select_sample_count(nmax, k), t.state, st);
+  if (rc != HCA_OK) return rc;
+  tk_collect_sampled<<<dim3((unsigned)nchunks, (unsigned)L.rows), 256, 0, st>>>(scores, L.cap, chunk, L.n_kv_heads, sr, t, room);
+  tk_resolve_scores<<<L.rows, 1024, 0, st>>>(scores, L.cap, chunk, nchunks, L.n_kv_heads, sr, t, room, k, idx, count, fu);
+  HCA_HIP(hipGetLastError());
+  return HCA_OK;
+}
+
+// Rows up to which, and slots in all rows below which, hca_score_topk writes the scores and selects from them - four launches
+// - instead of sampling and scanning the codes for a threshold and looking for rows to scan again - six.  What the scores
+// cost is 8 bytes per slot.  The call by the six / these four, us: 8 rows of 41 000 47 / 40, 64 Ki 49 / 42, 128 Ki 64 / 52
+// (2-bit 52 / 47), 200 000 76 / 60, 300 000 73 / 72 (78 / 66); 1 row of 128 Ki 44 / 35; 16 of 128 Ki 85 / 68; 32 of 64 Ki
+// 71 / 65; 56 of 70 000 100 / 97; 32 of 128 Ki 90 / 95 (76 / 76).
+constexpr int64_t kScoresMax = 196608, kScoresAll = 4000000;
+
 int32_t launch_score_topk(const Layout& L, const void* kcache, const void* q, const NRes& nr, int64_t nmax, int32_t k,
                           int32_t* idx, int32_t* count, void* ws, hipStream_t st) {
   if (nmax > 0 && nmax <= kRowSelectMax) {
@@ -1851,6 +1929,22 @@ int32_t launch_score_topk(const Layout& L, const void* kcache, const void* q, co
     if (rc != HCA_OK) return rc;
     return launch_row_select(scores, L.cap, L.rows, L.n_kv_heads, f.sr, nmax, k, idx, count,
                              RowSelectFused{f.t.spec, f.t.ncand, f.t.mon, f.nchunks}, st);
+  }
+  if (nmax > kRowSelectMax && nmax <= kScoresMax && L.rows * nmax < kScoresAll && select_sample_count(nmax, k) <= 16384 &&
+      select_lists_fit(nmax, k)) {
+    // rows of medium length: the scores into the first half of the room of the lists, the lists' slots into the second, and
+    // the lists' (key, slot) pairs, as far as they fit - where the row's best are not crowded in a chunk, all of them - into
+    // the room of the samples (by slots alone, a dependent load per pair, 8 rows of 1 Mi scores take 54 us for 43)
+    FusedPlan f;
+    int32_t rc = fused_plan(L, nr, nmax, k, ws, &f);
+    if (rc != HCA_OK) return rc;
+    float* scores = reinterpret_cast<float*>(f.t.cand);
+    rc = launch_score(L, kcache, q, nr, nmax, scores, nullptr, st);
+    if (rc != HCA_OK) return rc;
+    const ListRoom room{reinterpret_cast<uint2*>(f.t.samples), reinterpret_cast<uint32_t*>(f.t.cand) + L.rows * f.t.row_entries,
+                        kSampleMax / 2, 0, f.t.row_entries};
+    return launch_topk_sampled(L, scores, nr, nmax, f.sr, k, idx, count, f.t, room,
+                               RowSelectFused{f.t.spec, f.t.ncand, f.t.mon, f.nchunks}, st);
   }
   int32_t rc = launch_select_threshold(L, kcache, q, nr, nmax, k, ws, st);
   if (rc != HCA_OK) return rc;
@@ -1867,8 +1961,7 @@ __global__ __launch_bounds__(256) void tk_select_report(TopkWs t, int nchunks, i
   const int row = blockIdx.x;
   uint32_t v = 0;
   for (int c = threadIdx.x; c < nchunks; c += 256) v += t.ncand[(int64_t)row * kMaxChunks + c];
-#pragma unroll
-  for (int o = 32; o >= 1; o >>= 1) v += __shfl_xor(v, o);
+  v = wave_sum(v);
   if ((threadIdx.x & 63) == 0) wsum[threadIdx.x >> 6] = v;
   __syncthreads();
   if (threadIdx.x == 0) {
@@ -2420,21 +2513,12 @@ int32_t launch_topk(const Layout& L, const float* sel, const NRes& nr, int64_t n
   int32_t nchunks;
   chunk_geometry(nmax, &chunk, &nchunks);
   dim3 g((unsigned)nchunks, (unsigned)L.rows);
-  // Three launches: a key from samples, the lists above it, the selection over them - where the lists fit the selection's
-  // registers and one workgroup per row can read the samples.  Bound by latency and one pass over the scores.  Per call, the
-  // five launches below / these, k = 1024 - 8192, normal scores: 8 rows of 50 000 39 / 27 us, of 300 000 34 / 28, of
+  // Where the sampled form's lists fit the selection's registers and one workgroup per row can read the samples.  Per call,
+  // the five launches below / its three, k = 1024 - 8192, normal scores: 8 rows of 50 000 39 / 27 us, of 300 000 34 / 28, of
   // 500 000 49 / 39, of 1 Mi 50 / 43, 56 of 70 000 36 / 29; all scores equal 675 - 1200 / 46 - 56; 99 % masked 42 - 950 /
   // 32 - 64 (300 000 slots, k = 1024: 43 / 48); 4 Mi slots in one row, 32 768 samples, 53 / 57.
-  const int m = select_sample_count(nmax, k);
-  if (m <= 16384 && select_lists_fit(nmax, k)) {
-    int32_t rc = launch_topk_sample_rank(sel, L.cap, L.rows, L.n_kv_heads, nr, k, m, t.state, st);
-    if (rc != HCA_OK) return rc;
-    tk_collect_sampled<<<g, 256, 0, st>>>(sel, L.cap, chunk, L.n_kv_heads, sr, t);
-    const SelectOut so{t.state, t.ncand, t.above, t.cand, nullptr, t.row_entries, 0, nullptr};
-    tk_resolve_scores<<<L.rows, 1024, 0, st>>>(sel, L.cap, chunk, nchunks, L.n_kv_heads, sr, so, k, idx, count);
-    HCA_HIP(hipGetLastError());
-    return HCA_OK;
-  }
+  if (select_sample_count(nmax, k) <= 16384 && select_lists_fit(nmax, k))
+    return launch_topk_sampled(L, sel, nr, nmax, sr, k, idx, count, t, ListRoom{t.cand, nullptr, t.row_entries, 0, 0}, RowSelectFused{}, st);
   if (nmax > 0) {
     const int64_t nz = (int64_t)L.rows * kBins12;
     // the histogram sits at the start of the workspace; tk_findbin clears what it reads, so a caller

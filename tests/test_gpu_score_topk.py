@@ -158,6 +158,35 @@ def test_second_scan_with_the_deeper_threshold(H, oracle):
     assert resc[0] == 1 and k <= cand[0] < n // 4
 
 
+@pytest.mark.parametrize("kind", ["crowded", "misread", "equal"])
+@pytest.mark.parametrize("n", [41000, 100000, 196608])
+def test_rows_of_medium_length(H, oracle, n, kind):
+    """Rows whose scores are written and selected from: the best slots crowded into a few thousand neighbours (more than a
+    chunk's room for pairs), a row its samples misrepresent (their places as topk_sample_rank takes them), equal scores."""
+    k = 3000
+    w = S.Workload("mid", 91, 2, 4, 1, n, 4, 32, k)
+    d = S.make_layer(w, want_values=False)
+    q = d["q"].clone()
+    q[:, 1:] = q[:, :1]                                       # four equal query heads
+    g = torch.Generator().manual_seed(n)
+    large = torch.zeros(n, dtype=torch.bool)
+    if kind == "crowded":
+        large[20000:24500] = True
+    elif kind == "misread":
+        nblocks, most = (n + 15) // 16, 8192 // 16
+        s = torch.arange(most, dtype=torch.int64)
+        block = (s * nblocks + ((((s * 2654435761) & 0xffffffff) * nblocks) >> 32)) // most
+        large[(block[:, None] * 16 + torch.arange(16)).flatten().clamp(max=n - 1)] = True
+    size = torch.where(large, 1.0, -1.0)[:, None] * (0.5 + torch.rand(n, 1, generator=g))
+    keys = (size * q[:, 0].float()[:, None, :] + 0.02 * torch.randn(2, n, 128, generator=g)).to(torch.float16)[:, None]
+    if kind == "equal":
+        keys = keys[:, :, :1].expand(-1, -1, n, -1).contiguous()
+    lens = [n, n - 7 if kind == "crowded" else 5000]
+    cand, resc = _run(H, oracle, w, keys, q, lens, k)
+    # misread: only sampled slots score high, so those above the r-th largest sample are r - 1 <= 766 (n = 41 000) < k
+    assert cand[0] >= k and resc[0] == (kind == "misread")
+
+
 def test_running_monitor_over_several_calls(H):
     """hca_score_topk_monitor: calls counted, fewest / most pairs of a first scan and second scans per row, over
     three selections at different lengths (compared with the per-call report after each)."""
