@@ -135,17 +135,25 @@ __device__ __forceinline__ void score_body(const Layout& L, const uint8_t* __res
   const bool head_live = hd < L.gqa;
   const int ntok = (int)n;
   // LSE: running max and sum of 2^(logit - max) of this lane's logits, in units of log2 (one multiply by
-  // sm_scale * log2(e)); branch-free, raw v_exp_f32 (accurate to ~1 ulp here).
+  // sm_scale * log2(e)); branch-free, raw v_exp_f32 (accurate to ~1 ulp here), a quarter of the other instructions' rate: the
+  // scores of a group of blocks share one new maximum, N + 1 exponentials for N scores where each score on its own took two.
+  // -inf: no such token or head.  8 x 500 003 tokens at 4 bits, with whole groups only: 69 - 72 -> 65 us.
   float lm = -INFINITY, ls = 0.f;
   const float sm2 = sm_scale * 1.44269504f;
-  auto lse_add = [&](float zv, bool valid) {
-    const float l = valid ? zv * sm2 : -INFINITY;
-    const float nm = fmaxf(lm, l);
-    const float base = (nm == -INFINITY) ? 0.f : nm;        // nothing valid yet: both terms are 2^-inf = 0
-    ls = fmaf(ls, __builtin_amdgcn_exp2f(lm - base), __builtin_amdgcn_exp2f(l - base));
+  auto lse_add = [&](auto& zv) {
+    constexpr int N = sizeof(zv) / sizeof(float);
+    float l[N], nm = lm;
+#pragma unroll
+    for (int i = 0; i < N; ++i) {
+      l[i] = zv[i] == -INFINITY ? -INFINITY : zv[i] * sm2;
+      nm = fmax_raw(nm, l[i]);
+    }
+    const float base = (nm == -INFINITY) ? 0.f : nm;        // nothing valid yet: all terms are 2^-inf = 0
+    ls *= __builtin_amdgcn_exp2f(lm - base);
+#pragma unroll
+    for (int i = 0; i < N; ++i) ls += __builtin_amdgcn_exp2f(l[i] - base);
     lm = nm;
   };
-  auto lse_fold = [&]() {};
   const RowGather gather_rows(lane);
   // scores block b: this lane's (token, head) score of the block's tile (4-bit) or two tiles (2-bit); -inf on the
   // lanes of query heads that do not exist
@@ -154,7 +162,6 @@ __device__ __forceinline__ void score_body(const Layout& L, const uint8_t* __res
       const float zv = score_block4(op, wv, mv);
       zt0 = head_live ? zv : -INFINITY;
       if (WRITE_Z && head_live && b * 16 + t < ntok) zrow[b * 16] = zv;
-      if constexpr (LSE) lse_add(zv, head_live && b * 16 + t < ntok);
     } else {
       const float z0 = score_tile2(op, wv.x, wv.y, uint2{mv.x, mv.y});
       const float z1 = score_tile2(op, wv.z, wv.w, uint2{mv.z, mv.w});
@@ -163,10 +170,6 @@ __device__ __forceinline__ void score_body(const Layout& L, const uint8_t* __res
       if (WRITE_Z && head_live) {
         if (b * 32 + t < ntok) zrow[b * 32] = z0;
         if (b * 32 + 16 + t < ntok) zrow[b * 32 + 16] = z1;
-      }
-      if constexpr (LSE) {
-        lse_add(z0, head_live && b * 32 + t < ntok);
-        lse_add(z1, head_live && b * 32 + 16 + t < ntok);
       }
     }
   };
@@ -226,7 +229,18 @@ __device__ __forceinline__ void score_body(const Layout& L, const uint8_t* __res
 #pragma unroll
       for (int u = 0; u < U; u += 2) store4((g0 + u) * 32, lo[u], hi[u], lo[u + 1], hi[u + 1]);
     }
-    if constexpr (LSE) lse_fold();
+    if constexpr (LSE) {
+      if ((g0 + U) * L.tpb > ntok) {                        // the row's last group: lanes past its end
+#pragma unroll
+        for (int u = 0; u < U; ++u) {
+          const int tok = (g0 + u) * (BITS == 4 ? 16 : 32) + t;
+          if (tok >= ntok) lo[u] = -INFINITY;
+          if (BITS == 2 && tok + 16 >= ntok) hi[u] = -INFINITY;
+        }
+      }
+      lse_add(lo);
+      if constexpr (BITS == 2) lse_add(hi);
+    }
   };
   int b0 = wave_first;
   const int ngroups = (wave_end - wave_first) / U;
@@ -254,9 +268,15 @@ __device__ __forceinline__ void score_body(const Layout& L, const uint8_t* __res
     const uint32_t mw = __builtin_nontemporal_load(&mptr[(int64_t)b0 * 64]);
     float lo, hi;
     score_one(b0, wv, gather_rows(mw), lo, hi);
+    if constexpr (LSE) {
+      const int tok = b0 * (BITS == 4 ? 16 : 32) + t;
+      float one[BITS == 4 ? 1 : 2];
+      one[0] = tok < ntok ? lo : -INFINITY;
+      if constexpr (BITS == 2) one[1] = tok + 16 < ntok ? hi : -INFINITY;
+      lse_add(one);
+    }
     lo = max_over_heads(lo);
     if constexpr (BITS == 2) hi = max_over_heads(hi);
-    if constexpr (LSE) lse_fold();
     if constexpr (SELECT) {
       // lanes 0..15 carry tile 0; with 2-bit codes lanes 16..31 carry tile 1: lane order is slot order
       if constexpr (BITS == 4) emit_pairs(lo, b0 * 16 + t, hd == 0 && b0 * 16 + t < ntok);
@@ -370,13 +390,19 @@ __global__ __launch_bounds__(256) void lse_merge(Layout L, NRes nr, int bpw, int
   const int live = (int)(live_wgs * 4);
   const float2* p = part + ((int64_t)row * 4 + h) * waves_per_row;
   float m = -INFINITY, s = 0.f;
-  for (int i = threadIdx.x; i < live; i += 256) {
-    const float2 v = p[i];
-    if (v.x != -INFINITY) {
-      const float mm = fmaxf(m, v.x);
-      s = (m == -INFINITY ? 0.f : s * expf(m - mm)) + v.y * expf(v.x - mm);
-      m = mm;
+  for (int i0 = threadIdx.x; i0 < live; i0 += 16 * 256) {   // 16 loads in flight: 2084 pairs per head 7.0 -> 4.7 us
+    float2 v[16];
+    float mm = m;
+#pragma unroll
+    for (int x = 0; x < 16; ++x) {
+      v[x] = i0 + x * 256 < live ? p[i0 + x * 256] : float2{-INFINITY, 0.f};
+      mm = fmaxf(mm, v[x].x);
     }
+    s = m == -INFINITY ? 0.f : s * expf(m - mm);
+#pragma unroll
+    for (int x = 0; x < 16; ++x)
+      if (v[x].x != -INFINITY) s += v[x].y * expf(v[x].x - mm);
+    m = mm;
   }
 #pragma unroll
   for (int o = 32; o >= 1; o >>= 1) {
@@ -821,13 +847,23 @@ int select_sample_count(int64_t nmax, int32_t k) {
 }
 bool select_lists_fit(int64_t nmax, int32_t k) { return sample_keeps_lists_short(nmax, k, select_sample_count(nmax, k)); }
 
+// Blocks per wave of a scan over `total` blocks in all rows, a multiple of `step` (what a wave fetches at a time; blocks left
+// over go one by one): as many as make one round of the 1024 workgroups that the chip holds, up to 32.  Times per scan, us,
+// 4-bit / 2-bit codes, 16 waves per SIMD (1 to 15 left over one by one) -> this: 24 Ki blocks 11.4 -> 9.4 / 15.8 -> 11.4;
+// 64 Ki 22.3 -> 16.5 / 30 -> 21; 96 Ki 30.7 -> 23.3 / 39 -> 28; 128 Ki 38 -> 31 / 47.5 -> 36; 256 Ki 71 -> 61 / 85 -> 71;
+// the selecting scan's call 64 Ki 66 -> 48 / 72 -> 51; 128 Ki 83 -> 58 / 92 -> 62; 256 Ki 100 -> 86 / 110 -> 92.  Longer
+// launches gain nothing from it: 4-bit codes 16 from 384 Ki on (512 Ki blocks 119 us, with 32 121).
+static int64_t scan_blocks_per_wave(int bits, int64_t total, int64_t step) {
+  if (bits == 4 && total >= 384 * 1024) return 16;
+  int64_t bpw = (total + 4096 - 1024) / 4096;               // (a quarter of a round more is no second round)
+  bpw = (bpw + step - 1) / step * step;
+  return bpw < step ? step : bpw > 32 ? 32 : bpw;
+}
+
 int select_scan_bpw(const Layout& L, int64_t nmax) {
   const int64_t nblocks = (nmax + L.tpb - 1) / L.tpb;
-  const int64_t total = nblocks * L.rows;
-  int64_t bpw = total / (256 * 4 * 16);
-  if (bpw < 4) bpw = 4;
-  const int64_t bpw_max = L.bits == 4 ? 16 : 32;
-  if (bpw > bpw_max) bpw = bpw_max;
+  int64_t bpw = scan_blocks_per_wave(L.bits, nblocks * L.rows, 8);
+  if (bpw < 16) bpw = 16;                                   // (fewer, longer lists: 24 Ki blocks 42.6 -> 42.2 us, 16 Ki 43.8 -> 41.2)
   const int64_t need = (nblocks + 4 * kSelectMaxChunks - 1) / (4 * kSelectMaxChunks);   // chunks per row <= 1024
   if (bpw < need) bpw = (need + 7) / 8 * 8;
   if (4 * bpw * L.tpb * (int64_t)sizeof(uint2) > 64 * 1024) return 0;                     // wave lists no longer fit
@@ -1038,20 +1074,15 @@ int32_t launch_score(const Layout& L, const void* kcache, const void* q, const N
                      float* sel, float* z_opt, hipStream_t st, uint64_t* stamps, const Tuning* tune) {
   if (nmax == 0) return HCA_OK;
   const int64_t nblocks = (nmax + L.tpb - 1) / L.tpb;
-  // aim at ~16 waves per SIMD over the whole chip when the cache is large, >= 4 blocks per wave
-  const int64_t total = nblocks * L.rows;
   const Tuning& tn = tune != nullptr ? *tune : tuning();
-  int64_t bpw = total / (256 * 4 * 16);
-  if (bpw < 4) bpw = 4;
-  // measured best on MI355X: 4-bit codes 8 blocks ahead, 16 per wave; 2-bit codes (two tiles per block,
-  // more registers) 4 ahead, 32 per wave
-  const int64_t bpw_max = L.bits == 4 ? 16 : 32;
-  if (bpw > bpw_max) bpw = bpw_max;
+  int64_t bpw = scan_blocks_per_wave(L.bits, nblocks * L.rows, 4);
+  if (bpw > 16) bpw = scan_blocks_per_wave(L.bits, nblocks * L.rows, 8);
   if (tn.score_bpw > 0) bpw = tn.score_bpw;
   if (bpw < kScoreBpwMin) bpw = kScoreBpwMin;
   if (bpw > kScoreBpwMax) bpw = kScoreBpwMax;
-  // a wave of fewer than 8 blocks would go through the one-at-a-time tail with the deeper look-ahead
-  const int depth = tn.score_depth > 0 ? tn.score_depth : (bpw >= 8 ? 8 : 4);
+  // the deeper look-ahead pays for long waves (64 Ki blocks, 16 per wave: 4-bit 17.0 / 16.3 us, 2-bit 20.6 / 21.3) and sends
+  // what is no multiple of it through the one-at-a-time tail
+  const int depth = tn.score_depth > 0 ? tn.score_depth : (bpw >= (L.bits == 4 ? 16 : 24) && bpw % 8 == 0 ? 8 : 4);
   dim3 grid((unsigned)((nblocks + 4 * bpw - 1) / (4 * bpw)), (unsigned)L.rows);
   // every wave of the launch owns one stamp pair: the caller's buffer holds score_stamp_pairs() of them
   if (stamps != nullptr && (int64_t)grid.x * 4 * L.rows > score_stamp_pairs(L, nmax)) return HCA_ERR_CAPACITY;
@@ -1083,12 +1114,8 @@ int32_t launch_score_lse(const Layout& L, const void* kcache, const void* q, con
     return HCA_OK;
   }
   const int64_t nblocks = (nmax + L.tpb - 1) / L.tpb;
-  const int64_t total = nblocks * L.rows;
   const Tuning& tn = tuning();
-  int64_t bpw = total / (256 * 4 * 16);
-  if (bpw < 4) bpw = 4;
-  const int64_t bpw_max = L.bits == 4 ? 16 : 32;
-  if (bpw > bpw_max) bpw = bpw_max;
+  int64_t bpw = scan_blocks_per_wave(L.bits, nblocks * L.rows, 4);
   if (tn.score_bpw >= kScoreBpwMin) bpw = tn.score_bpw;
   dim3 grid((unsigned)((nblocks + 4 * bpw - 1) / (4 * bpw)), (unsigned)L.rows);
   if ((size_t)L.rows * 4 * grid.x * 4 * sizeof(float2) > score_workspace_bytes(L)) return HCA_ERR_CAPACITY;

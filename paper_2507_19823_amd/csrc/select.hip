@@ -1912,10 +1912,10 @@ static int32_t launch_topk_sampled(const Layout& L, const float* scores, const N
 
 // Rows up to which, and slots in all rows below which, hca_score_topk writes the scores and selects from them - four launches
 // - instead of sampling and scanning the codes for a threshold and looking for rows to scan again - six.  What the scores
-// cost is 8 bytes per slot.  The call by the six / these four, us: 8 rows of 41 000 47 / 40, 64 Ki 49 / 42, 128 Ki 64 / 52
-// (2-bit 52 / 47), 200 000 76 / 60, 300 000 73 / 72 (78 / 66); 1 row of 128 Ki 44 / 35; 16 of 128 Ki 85 / 68; 32 of 64 Ki
-// 71 / 65; 56 of 70 000 100 / 97; 32 of 128 Ki 90 / 95 (76 / 76).
-constexpr int64_t kScoresMax = 196608, kScoresAll = 4000000;
+// cost is 8 bytes per slot.  The call by the six / these four, us: 1 row of 60 000 37 / 34, of 128 Ki 40 / 35; 8 rows of
+// 41 000 40 / 38, of 64 Ki 42 / 40, of 100 000 45 / 44 (2-bit 44 / 42), of 128 Ki 46 / 46 (44 / 43), of 196 000 52 / 53
+// (47 / 48); 16 of 41 000 44 / 41, of 64 Ki 47 / 45, of 100 000 56 / 57; 32 of 41 000 53 / 51, of 64 Ki 64 / 61 (51 / 52).
+constexpr int64_t kScoresMax = 131072, kScoresAll = 1500000;
 
 int32_t launch_score_topk(const Layout& L, const void* kcache, const void* q, const NRes& nr, int64_t nmax, int32_t k,
                           int32_t* idx, int32_t* count, void* ws, hipStream_t st) {
@@ -2101,9 +2101,10 @@ __global__ __launch_bounds__(256) void tp_rowmax(const float* __restrict__ vals,
 }
 
 // Histogram of slot counts and integer weights.
-__global__ __launch_bounds__(256) void tp_hist(const float* __restrict__ vals, int64_t stride, int64_t chunk,
-                                               int n_kv_heads, SelRows sr, float sm_scale, float span, TopkWs t) {
-  __shared__ uint32_t lc[kTpBins], wmax[4];
+template <int NT>
+__global__ __launch_bounds__(NT) void tp_hist(const float* __restrict__ vals, int64_t stride, int64_t chunk, int64_t group,
+                                              int groups, int n_kv_heads, SelRows sr, float sm_scale, float span, TopkWs t) {
+  __shared__ uint32_t lc[kTpBins], wmax[NT / 64];
   __shared__ unsigned long long lm[kTpBins];
   __shared__ float s_top, s_low;
   const int row = blockIdx.y;
@@ -2118,14 +2119,14 @@ __global__ __launch_bounds__(256) void tp_hist(const float* __restrict__ vals, i
   auto load = [&](int64_t s0) {
 #pragma unroll
     for (int x = 0; x < 16; ++x) {
-      const int64_t j = s0 + x * 256 + threadIdx.x;
+      const int64_t j = s0 + x * NT + threadIdx.x;
       f[x] = v[j < c1 ? j : c1 - 1];
     }
   };
   load(c0);                                                 // on their way while the bins are laid out
-  for (int i = threadIdx.x; i < kTpBins; i += 256) { lc[i] = 0; lm[i] = 0; }
+  for (int i = threadIdx.x; i < kTpBins; i += NT) { lc[i] = 0; lm[i] = 0; }
   uint32_t kmax = 0;
-  for (int c = threadIdx.x; c < (int)gridDim.x; c += 256) {
+  for (int c = threadIdx.x; c < groups; c += NT) {
     const uint32_t x = t.above[(int64_t)row * 1024 + c];
     kmax = x > kmax ? x : kmax;
   }
@@ -2136,7 +2137,7 @@ __global__ __launch_bounds__(256) void tp_hist(const float* __restrict__ vals, i
     // The window: of up to sixteen waves of tp_rowmax, spread over the row, the lower quartile of the largest scores and
     // the upper quartile of the smallest, waves that weigh nothing left out.  A few outliers either way do not move it, and
     // what lies outside has the coarse steps.
-    const int pairs = 2 * (int)((nsel + chunk - 1) / chunk);
+    const int pairs = 2 * (int)((nsel + group - 1) / group);
     const int ns = pairs < 16 ? pairs : 16;
     const float2 p = reinterpret_cast<const float2*>(t.coff)[(int64_t)row * 1024 + (lane < ns ? lane : 0) * pairs / ns];
     float most = p.x;
@@ -2159,7 +2160,7 @@ __global__ __launch_bounds__(256) void tp_hist(const float* __restrict__ vals, i
     if ((counts >> lane & 1) && over == quarter) s_low = p.y;
   }
   __syncthreads();
-  for (int x = 0; x < 4; ++x) if (wmax[x] > kmax) kmax = wmax[x];
+  for (int x = 0; x < NT / 64; ++x) if (wmax[x] > kmax) kmax = wmax[x];
   const float m = key_to_float(kmax) * sm_scale;
   const float per = (float)kTpFine / (s_top - s_low);
   const bool window = s_top > s_low && per < INFINITY;
@@ -2168,11 +2169,11 @@ __global__ __launch_bounds__(256) void tp_hist(const float* __restrict__ vals, i
     t.prow[4 * row] = kmax;
     reinterpret_cast<float2*>(t.pstate)[4 * row + 1] = float2{bin_of.top, bin_of.per_unit};
   }
-  for (int64_t s0 = c0; s0 < c1; s0 += 4096) {
+  for (int64_t s0 = c0; s0 < c1; s0 += 16 * NT) {
     if (s0 != c0) load(s0);
 #pragma unroll
     for (int x = 0; x < 16; ++x)
-      if (s0 + x * 256 + threadIdx.x < c1) {
+      if (s0 + x * NT + threadIdx.x < c1) {
         const uint64_t w = tp_weight(f[x] * sm_scale - m);
         const uint32_t b = bin_of(f[x]);
         // bin 0 weighs nothing and may hold nearly the whole row: it is not counted (its slots are the row's others)
@@ -2181,7 +2182,7 @@ __global__ __launch_bounds__(256) void tp_hist(const float* __restrict__ vals, i
       }
   }
   __syncthreads();
-  for (int i = threadIdx.x; i < kTpBins; i += 256) {
+  for (int i = threadIdx.x; i < kTpBins; i += NT) {
     const uint32_t c = lc[i];
     if (c) {
       atomicAdd(&t.pcount[(int64_t)row * kBins12 + i], c);
@@ -2483,7 +2484,14 @@ int32_t launch_topp(const Layout& L, const float* sel, const NRes& nr, int64_t n
     dim3 gh((unsigned)((nchunks + 1) / 2), (unsigned)L.rows);
     const float span = 44.3614196f / sm_scale;               // 64 ln 2 in scores: lower ones weigh nothing
     tp_rowmax<<<gh, 256, 0, st>>>(sel, L.cap, 2 * chunk, L.n_kv_heads, sr, span, t);
-    tp_hist<<<gh, 256, 0, st>>>(sel, L.cap, 2 * chunk, L.n_kv_heads, sr, sm_scale, span, t);
+    // one batch of loads per thread; each workgroup flushes its bins with global atomics, so the larger ones where they fill
+    // the chip.  256 threads and two batches / 512 / 1024, the whole chain of calls: 8 rows of 500 003 slots 153.2 / 149.8 /
+    // 146.9 us, 32 of 130 000 151.9 / 148.8 / 147.7, 8 of 300 001 170.8 / 168.0 / 168.6, of 64 000 76.8 / 74.0 / 76.1
+    if ((nchunks + 3) / 4 * L.rows >= 192)
+      tp_hist<1024><<<dim3((unsigned)((nchunks + 3) / 4), (unsigned)L.rows), 1024, 0, st>>>(
+          sel, L.cap, 4 * chunk, 2 * chunk, (int)gh.x, L.n_kv_heads, sr, sm_scale, span, t);
+    else
+      tp_hist<512><<<gh, 512, 0, st>>>(sel, L.cap, 2 * chunk, 2 * chunk, (int)gh.x, L.n_kv_heads, sr, sm_scale, span, t);
     tp_collect<<<g, 256, 0, st>>>(sel, L.cap, chunk, L.n_kv_heads, sr, sm_scale, tau_fix, tau_one, (uint32_t)k_max, t, mass_opt);
     tp_resolve<<<L.rows, 1024, 0, st>>>(chunk, nchunks, L.n_kv_heads, sr, sm_scale, t);
   } else if (mass_opt != nullptr) {

@@ -159,7 +159,7 @@ def test_second_scan_with_the_deeper_threshold(H, oracle):
 
 
 @pytest.mark.parametrize("kind", ["crowded", "misread", "equal"])
-@pytest.mark.parametrize("n", [41000, 100000, 196608])
+@pytest.mark.parametrize("n", [41000, 100000, 131072])
 def test_rows_of_medium_length(H, oracle, n, kind):
     """Rows whose scores are written and selected from: the best slots crowded into a few thousand neighbours (more than a
     chunk's room for pairs), a row its samples misrepresent (their places as topk_sample_rank takes them), equal scores."""
