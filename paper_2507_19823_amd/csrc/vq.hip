@@ -934,6 +934,27 @@ __global__ __launch_bounds__(1024) void vq_scan_kernel(int c, int64_t cap, const
   }
 }
 
+// The grid exponents of a row's heads from the table's per-group maxima, into sexp and, by one workgroup, behind the maxima.
+template <int G>
+__device__ __forceinline__ void vq_row_exponents(float* __restrict__ lut, int g, int c, int rows, int row, bool writer,
+                                                 int* sexp) {
+  float* tail = lut + (int64_t)rows * g * c * G;
+  if (threadIdx.x < 64) {
+    const float* am = tail + (int64_t)row * g * 4;
+    const int h = threadIdx.x & 3, part = threadIdx.x >> 2;
+    float m = 0.f;
+    if (h < G)
+      for (int i = part; i < g; i += 16) m = fmaxf(m, am[i * 4 + h]);
+#pragma unroll
+    for (int o = 32; o >= 4; o >>= 1) m = fmaxf(m, __shfl_xor(m, o));
+    if (threadIdx.x < G) {
+      const int s = vq_grid_exponent(m);
+      sexp[threadIdx.x] = s;
+      if (writer) reinterpret_cast<int32_t*>(tail + (int64_t)rows * g * 4)[row * 4 + threadIdx.x] = s;
+    }
+  }
+}
+
 // Eq. 3 for the wide form (16-bit indices, a table larger than LDS).  One workgroup of 1024 threads scans a share
 // of up to NQ * 4096 slots, per thread NQ quads of consecutive slots with their running integer sums in registers,
 // and walks through the groups a slice at a time: gps groups whose entries (gps * c * G * 4 bytes <= 128 KiB) are
@@ -977,21 +998,7 @@ __global__ __launch_bounds__(1024) void vq_scan_wide_kernel(int g, int c, int gp
     for (int u = 0; u < kGo; ++u)
       if (1024 * (u0 + u) < ne) nt[u] = (src + 1024 * (u0 + u))[t < (uint32_t)(ne - 1024 * (u0 + u)) ? t : 0u];
   };
-  float* tail = lut + (int64_t)rows * g * c * G;
-  if (threadIdx.x < 64) {                                 // exponents from the per-group maxima, as in the LDS form
-    const float* am = tail + (int64_t)row * g * 4;
-    const int h = threadIdx.x & 3, part = threadIdx.x >> 2;
-    float m = 0.f;
-    if (h < G)
-      for (int i = part; i < g; i += 16) m = fmaxf(m, am[i * 4 + h]);
-#pragma unroll
-    for (int o = 32; o >= 4; o >>= 1) m = fmaxf(m, __shfl_xor(m, o));
-    if (threadIdx.x < G) {
-      const int s = vq_grid_exponent(m);
-      sexp[threadIdx.x] = s;
-      if (share == 0) reinterpret_cast<int32_t*>(tail + (int64_t)rows * g * 4)[row * 4 + threadIdx.x] = s;
-    }
-  }
+  vq_row_exponents<G>(lut, g, c, rows, row, share == 0, sexp);
   __syncthreads();
   int s[G];
 #pragma unroll
@@ -1079,6 +1086,66 @@ __global__ __launch_bounds__(1024) void vq_scan_wide_kernel(int g, int c, int gp
         for (int h = 0; h < G; ++h) z_out[((int64_t)row * G + h) * cap + j] = z[h];
       }
     }
+  }
+}
+
+// The wide scan of few slots: every entry where it lies, in L2, instead of the whole table through every compute unit's
+// LDS, whose 30 to 100 us do not fall with the number of slots.  A thread per slot, eight groups' indices and then their
+// entries in flight; rows on dies as above.  Bound by the rate at which L2 answers scattered lines:
+// 8 rows of 24 000 slots, c = 8192, table included: 97 -> 42 us.
+template <int G>
+__global__ __launch_bounds__(256) void vq_scan_direct_kernel(int g, int c, int64_t cap, const uint16_t* __restrict__ pcache,
+                                                             float* __restrict__ lut, NRes nr, int n_kv_heads, int rows,
+                                                             float* __restrict__ sel, float* __restrict__ z_out) {
+  using E = typename EntryT<G>::type;
+  using F = typename EntryT<G>::fix;
+  __shared__ int sexp[4];
+  const int row = blockIdx.x % rows;
+  const int64_t n = nr.n[row / n_kv_heads], t0 = (int64_t)(blockIdx.x / rows) * 256;
+  if (t0 >= n) return;
+  const E* trow = reinterpret_cast<const E*>(lut) + (int64_t)row * g * c;
+  const int64_t j = t0 + threadIdx.x < n ? t0 + threadIdx.x : n - 1;
+  const uint16_t* ip = pcache + vq_wide_at(g, vq_tiles(cap), row, j, 0);
+  constexpr int U = 8;
+  uint32_t nx[U];
+#pragma unroll
+  for (int u = 0; u < U; ++u) nx[u] = ip[(int64_t)u * kVqTile];
+  vq_row_exponents<G>(lut, g, c, rows, row, t0 == 0, sexp);
+  __syncthreads();
+  int s[G];
+#pragma unroll
+  for (int h = 0; h < G; ++h) s[h] = __builtin_amdgcn_readfirstlane(sexp[h]);
+  int zi[G];
+#pragma unroll
+  for (int h = 0; h < G; ++h) zi[h] = 0;
+  const uint32_t last = (uint32_t)(c - 1);
+  for (int g0 = 0; g0 < g; g0 += U) {
+    E e[U];
+#pragma unroll
+    for (int u = 0; u < U; ++u) e[u] = trow[(int64_t)(g0 + u) * c + (nx[u] < last ? nx[u] : last)];
+    if (g0 + U < g) {
+#pragma unroll
+      for (int u = 0; u < U; ++u) nx[u] = ip[(int64_t)(g0 + U + u) * kVqTile];
+    }
+#pragma unroll
+    for (int u = 0; u < U; ++u) {
+      const F f = entry_fix<G>(e[u], s);
+      if constexpr (G == 4) { zi[0] += f.x; zi[1] += f.y; zi[2] += f.z; zi[3] += f.w; }
+      else if constexpr (G == 2) { zi[0] += f.x; zi[1] += f.y; }
+      else { zi[0] += f; }
+    }
+  }
+  if (t0 + threadIdx.x >= n) return;
+  float z[G];
+#pragma unroll
+  for (int h = 0; h < G; ++h) z[h] = ldexpf((float)zi[h], -s[h]);
+  float best = z[0];
+#pragma unroll
+  for (int h = 1; h < G; ++h) best = fmaxf(best, z[h]);
+  sel[(int64_t)row * cap + j] = best;
+  if (z_out != nullptr) {
+#pragma unroll
+    for (int h = 0; h < G; ++h) z_out[((int64_t)row * G + h) * cap + j] = z[h];
   }
 }
 
@@ -1201,9 +1268,29 @@ int32_t launch_vq_assign(const Layout& L, int g, int c, const float* centroids, 
   return HCA_OK;
 }
 
+// Whether the wide scan looks its entries up where they lie: by an estimate of both in us.  The form through LDS takes as
+// long as the whole table takes to pass through it; a lookup in L2 takes 1.7 to 4 us per million while a die's tables fit
+// its L2 (rows go to the eight dies in turn), 9.5 beyond.  Measured, through LDS / directly, table included: 8 rows of four
+// heads, 32 groups, c = 8192: 4000 slots 99 / 28, 24 000 97 / 42, 60 000 98 / 81, 90 000 100 / 109; c = 4096: 4000 63 / 21,
+// 40 000 63 / 50, 60 000 64 / 69; c = 1024: 4000 30 / 14, 24 000 30 / 25, 40 000 30 / 34; c = 300: 23 / 12, 23 / 16, 23 / 21;
+// 64 groups, c = 8192: 187 / 43, 182 / 77, 183 / 169 (60 000); 32 rows, c = 8192: 4000 128 / 73, 12 000 125 / 142;
+// 3 rows, c = 8192: 40 000 98 / 41, 131 000 95 / 98; 1 row: 262 000 95 / 50, 500 000 96 / 81, 1 Mi 100 / 149.
+static bool scan_directly(int rows, int g, int c, int gqa, int64_t nmax) {
+  const double table = (double)c * g * gqa * 4 / (1 << 20), lookups = (double)rows * (double)nmax * g * 1e-6;
+  const double on_die = table * (rows % 8 == 0 ? rows / 8 : rows);
+  const double rate = on_die <= 0.3 ? 1.7 : on_die <= 0.6 ? 2.6 : on_die <= 4.0 ? 3.9 : on_die <= 8.0 ? 5.7 : 9.5;
+  return 12.0 + 4.0 * table + rate * lookups < 12.0 + 0.36 * g + 17.0 * table;
+}
+
 template <int G>
 static int32_t scan_wide_launch(const Layout& L, int g, int c, const uint8_t* pcache, float* lut, const NRes& nr,
                                 int64_t nmax, float* sel, float* z_opt, hipStream_t st) {
+  if (scan_directly(L.rows, g, c, G, nmax)) {
+    vq_scan_direct_kernel<G><<<(unsigned)((nmax + 255) / 256 * L.rows), 256, 0, st>>>(
+        g, c, L.cap, (const uint16_t*)pcache, lut, nr, L.n_kv_heads, L.rows, sel, z_opt);
+    HCA_HIP(hipGetLastError());
+    return HCA_OK;
+  }
   int gps = 1;                                      // groups per LDS slice: the most that fit 128 KiB
   while (gps * 2 <= g && (int64_t)gps * 2 * c * G * 4 <= 128 * 1024) gps *= 2;
   const size_t lds = (size_t)gps * c * G * 4;

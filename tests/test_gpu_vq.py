@@ -524,3 +524,36 @@ def test_native_step_driver_in_the_papers_form(B, oracle, tau, Lr, n_sel, c):
         assert np.array_equal(pos[l].cpu().numpy().reshape(R, cap)[:, :n], opos[l][:, :n])
         assert np.allclose(acc[l].cpu().numpy().reshape(R, cap)[:, :n], oacc[l][:, :n], rtol=1e-3, atol=1e-6)
     B.hca_pipeline_destroy(pl)
+
+
+@pytest.mark.parametrize("rows,gqa,g,c,many", [(8, 4, 32, 1024, 60000), (8, 2, 64, 300, 120000), (8, 1, 32, 8192, 120000),
+                                               (2, 4, 64, 256, 300000), (3, 4, 32, 8192, 200000)])
+def test_wide_scan_of_few_slots_is_that_of_many(B, rows, gqa, g, c, many):
+    """The two forms of the wide scan - entries looked up where they lie, the table through LDS - on the same indices: a
+    slot's scores do not depend on how many slots there are, bit for bit, and slots past a sequence's end are left alone."""
+    gen = torch.Generator(device="cuda").manual_seed(c + g)
+    shape = B.make_shape(rows, gqa, 1, many)
+    cen = torch.randn(1, g, c, 128 // g, generator=gen, device="cuda")
+    cb = B.make_codebook(g, c, cen)
+    pc = torch.zeros(B.hca_vq_pcache_bytes(shape, cb), dtype=torch.uint8, device="cuda")
+    pc.view(torch.int16).random_(0, c, generator=gen)
+    q = torch.randn(rows, gqa, 128, generator=gen, device="cuda").half()
+    out = []
+    for n in (many, 1, 255, 256, 257, 4099):
+        lens = [max(0, n - 300 * (r % 2)) for r in range(rows)]
+        lut = torch.zeros(B.hca_vq_lut_bytes(shape, cb) // 4, device="cuda")
+        sel = torch.full((rows, 1, many), -7.0, device="cuda")
+        z = torch.full((rows, gqa, many), -7.0, device="cuda")
+        B.hca_vq_score(shape, cb, pc, q, lens, lut, sel, z)
+        torch.cuda.synchronize()
+        out.append((lens, lut, sel, z))
+    for lens, lut, sel, z in out[1:]:
+        at = rows * g * (c * gqa + 4)                           # the table and its maxima, then four exponents per row
+        assert torch.equal(lut[:at], out[0][1][:at])
+        for r in range(rows):
+            m = lens[r]
+            if m > 0:                                           # (a row without slots gets no exponents)
+                a = at + 4 * r
+                assert torch.equal(lut[a:a + gqa].view(torch.int32), out[0][1][a:a + gqa].view(torch.int32))
+            assert torch.equal(sel[r, :, :m], out[0][2][r, :, :m]) and torch.equal(z[r, :, :m], out[0][3][r, :, :m])
+            assert (sel[r, :, m:] == -7).all() and (z[r, :, m:] == -7).all()
