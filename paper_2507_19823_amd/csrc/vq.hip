@@ -252,14 +252,14 @@ __device__ __forceinline__ int am_exhaustive(const uint16_t* src, const float* c
   return (bi == 0x7fffffff || first_nan) ? 0 : bi;
 }
 
-// More than 256 centroids (always the wide form).  One workgroup of 8 waves = 1024 tokens x one group; a wave holds
+// More than 256 centroids, and blocks of few tokens against 96 and more.  One workgroup of 8 waves = 1024 tokens x one group; a wave holds
 // 128 tokens (four 32-token B operands) against centroids that pass through LDS 512 at a time (A operands only,
 // double-buffered, one barrier per chunk).  kAmBlock: tiles of 32 centroids per block, two beyond 2048 centroids (128 blocks
 // at 8192, half the bookkeeping), else one (half the rows to look into).  The three smallest values are kept, so two
 // blocks per half wave can be looked into.
 constexpr int kAmChunk = 512;       // centroids per LDS chunk
 
-template <int DBAR, int kAmBlock>
+template <int DBAR, int kAmBlock, bool WIDE>
 __global__ __launch_bounds__(512) __attribute__((amdgpu_waves_per_eu(4))) void vq_assign_mfma_kernel(
     int g, int c, int n_kv_heads, int64_t cap, const float* __restrict__ centroids, uint8_t* __restrict__ pcache,
     const uint16_t* __restrict__ k_new, int64_t T, NRes nr, float* __restrict__ acc, int32_t* __restrict__ pos,
@@ -371,7 +371,8 @@ __global__ __launch_bounds__(512) __attribute__((amdgpu_waves_per_eu(4))) void v
   auto put = [&](int64_t t, int win) {
     if (t >= T) return;
     const int64_t slot = nr.n[b] + t;
-    reinterpret_cast<uint16_t*>(pcache)[vq_wide_at(g, vq_tiles(cap), row, slot, grp)] = (uint16_t)win;
+    if constexpr (WIDE) reinterpret_cast<uint16_t*>(pcache)[vq_wide_at(g, vq_tiles(cap), row, slot, grp)] = (uint16_t)win;
+    else pcache[((int64_t)row * cap + slot) * g + vq_byte_of(grp, slot)] = (uint8_t)win;
     if (grp == 0) {
       if (acc != nullptr) acc[(int64_t)row * cap + slot] = 0.0f;
       if (pos != nullptr) pos[(int64_t)row * cap + slot] = (int32_t)(vrow0.n[b] + t);
@@ -1172,35 +1173,53 @@ __global__ __launch_bounds__(256) void vq_export_wide_kernel(int g, int64_t cap,
   out[(int64_t)row * cap * g + gid] = pcache[vq_wide_at(g, vq_tiles(cap), row, slot, i)];
 }
 
-// Whether at most 256 centroids go to vq_assign_small_c_kernel.  It works on whole sets of 2, 4 or 8 tiles, and each of its
+// Whether fewer than 96 centroids go to vq_assign_small_c_kernel.  It works on whole sets of 2, 4 or 8 tiles, and each of its
 // workgroups takes its 18 - 33 us whatever it holds, so it wants a launch that fills the chip; the vector form's time
 // follows the work alone, and falls with the channels per centroid.  Measured speed-ups over the vector form, 8 KV heads,
 // work in 2^27 (token, KV head, group, centroid) combinations (in brackets):
 //   4 channels: c = 33  0.88 (0.5), 1.24 (1.0); c = 48  0.87 (0.5), 1.08 (0.75), 1.6 (1.5); c = 64  0.95 (0.5), 1.37 (1);
-//   c = 65  0.9 (0.7), 1.17 (1); c = 96  0.88 (0.5), 1.08 (0.75); c = 128  0.85 (0.5), 1.4 (1); c = 129  0.85 (0.7), 1.06 (1);
-//   c = 200  0.93 (0.8), 1.23 (1.1); c = 256  0.95 (0.7), 1.16 (1), 3.9 (8).
-//   2 channels: c = 33  0.9 (0.7), 1.06 (1); c = 64  0.86 (0.5), 1.26 (1); c = 65  0.8 (0.7), 1.04 (1); c = 128  0.85 (0.7),
-//   1.22 (1); c = 129  0.88 (1), 1.0 (1.4), 1.3 (2); c = 200  0.9 (1.1), 1.2 (1.6); c = 256  0.83 (1), 1.12 (1.4), 2.5 (4).
+//   c = 65  0.9 (0.7), 1.17 (1).  2 channels: c = 33  0.9 (0.7), 1.06 (1); c = 64  0.86 (0.5), 1.26 (1); c = 65  0.8 (0.7),
+//   1.04 (1).
 static bool assign_by_tiles(int g, int c, int64_t work, int64_t T) {
-  if (T < 256 || c <= 32 || c > kAsCodewords) return false;
+  if (T < 256 || c <= 32) return false;
   const int64_t unit = (int64_t)1 << 25;                    // a quarter of 2^27
-  if (g == 32) return work >= (c <= 64 ? 3 : 4) * unit;
-  return work >= (c <= 128 ? 4 : 6) * unit;
+  return work >= (g == 32 && c <= 64 ? 3 : 4) * unit;
 }
 
-// Whether more than 256 centroids and 9 or more tokens go to vq_assign_mfma_kernel: always from 257 tokens on, below by an
-// estimate in us of both, fitted to 500 sizes (none picked more than 6 % slower than the better of the two).  A workgroup of it walks the codebook for up to 1024 tokens, two of them per compute unit at a
-// time; with few tokens most of its waves only help with the operands, and a launch of many (KV head, group) pairs is
+// Estimates in us of the vector form and of vq_assign_mfma_kernel, fitted to 500 sizes (none picked more than 6 % slower than
+// the better of the two).  A workgroup of the latter walks the codebook for up to 1024 tokens, two of them per compute unit
+// at a time; with few tokens most of its waves only help with the operands, and a launch of many (KV head, group) pairs is
 // faster in the vector form, whose waves take 64 tokens each.  Measured, mfma / vector: 8 rows, 32 groups, c = 8192, 9
 // tokens 0.25; 32 rows, 64 groups, 64 tokens: c = 257 1.66, 700 1.03, 1024 0.87; 128 rows, 64 groups, 64 tokens: c = 1024
 // 1.71, 2048 1.47; 128 tokens: 512 1.32, 1024 0.99; 256 tokens: 257 1.31, 400 0.98.
-static bool assign_by_shortlist(int rows, int g, int c, int64_t T) {
-  if (T > 256) return true;
-  const double pairs = (double)rows * g, waves = pairs * (double)((T + 63) / 64);
+static double vector_us(int rows, int g, int c, int64_t T) {
+  const double waves = (double)rows * g * (double)((T + 63) / 64);
   const double alone = g == 64 ? 0.058 : 0.089, each = g == 64 ? 1.38e-5 : 1.99e-5;      // per centroid: one wave; per wave
-  const double vec = c * (waves * each > alone ? waves * each : alone);
-  const double mfma = (pairs > 420 ? pairs : 420) * (0.0108 + 1.1e-5 * c) * (1.0 + T / 940.0);
-  return mfma < vec;
+  return c * (waves * each > alone ? waves * each : alone);
+}
+static double shortlist_us(int rows, int g, int c, int64_t T) {
+  const double pairs = (double)rows * g, each = 0.0108 + 1.1e-5 * c;
+  if (pairs * (double)((T + 1023) / 1024) <= 420) return 420 * each * (1.0 + (T < 1024 ? T : 1024) / 940.0);    // one round
+  return (pairs > 420 ? pairs : 420) * each * (1.0 + T / 940.0);
+}
+
+// More than 256 centroids: the shortlist always from 257 tokens on, below by the estimates.  96 to 256: the least of three
+// estimates - the tiles' workgroups take 16 groups one after another, 25 or 35 us whatever there is to do, the vector form
+// all centroids of a group in a chain.  Per call, vector / tiles / shortlist, us, 8 rows, 32 groups: c = 256, 9 - 256 tokens
+// 27 / 34 / 10, 1000 28 / 34 / 14, 2000 43 / 35 / 20, 4000 71 / 35 / 34, 8000 122 / 42 / 62; c = 128, 256 tokens 15 / 25 / 10,
+// 1000 16 / 25 / 12, 2000 23 / 26 / 17, 4000 38 / 28 / 30; 64 groups, c = 256, 1000 32 / 36 / 21, 4000 98 / 44 / 66; 32 rows,
+// 64 groups, 64 tokens: c = 256 19 / - / 29, c = 128 11 / - / 25.  c = 64: 4000 22 / 21 / 27.
+enum class AssignForm { kVector, kTiles, kShortlist };
+static AssignForm assign_form(int rows, int g, int c, int64_t T) {
+  if (T <= 8) return AssignForm::kVector;
+  const double vec = vector_us(rows, g, c, T), mfma = shortlist_us(rows, g, c, T);
+  if (c > kAsCodewords) return T > 256 || mfma < vec ? AssignForm::kShortlist : AssignForm::kVector;
+  if (c < 96) return assign_by_tiles(g, c, T * rows * g * c, T) ? AssignForm::kTiles : AssignForm::kVector;
+  const double least = c <= 128 ? 22.0 : 31.0, work = 2.0 + 1e-6 * (double)rows * g * (double)T * (4.0 + 0.043 * c);
+  const double tiles = T < 256 ? 1e30 : work > least ? work : least;
+  // (beyond a million of them the shortlist's single index bytes crowd the L2s: 64 groups, c = 256, 33 000 x 8 573 us, tiles 232)
+  if (mfma < vec && mfma < tiles && (double)rows * g * (double)T <= 1.1e6) return AssignForm::kShortlist;
+  return tiles < vec ? AssignForm::kTiles : AssignForm::kVector;
 }
 
 int32_t launch_vq_assign(const Layout& L, int g, int c, const float* centroids, uint8_t* pcache, const void* k_new,
@@ -1223,7 +1242,8 @@ int32_t launch_vq_assign(const Layout& L, int g, int c, const float* centroids, 
     else if (wide) vq_assign_kernel<2, true, GPW><<<GRID, 256, 0, st>>>(g, c, L.n_kv_heads, L.cap, centroids, pcache, kn, T, nr, acc_opt, pos_opt, vrow0);      \
     else vq_assign_kernel<2, false, GPW><<<GRID, 256, 0, st>>>(g, c, L.n_kv_heads, L.cap, centroids, pcache, kn, T, nr, acc_opt, pos_opt, vrow0);               \
   } while (0)
-  if (assign_by_tiles(g, c, T * L.rows * g * c, T)) {
+  const AssignForm form = assign_form(L.rows, g, c, T);
+  if (form == AssignForm::kTiles) {
     dim3 gm((unsigned)((T + 255) / 256), (unsigned)L.rows, (unsigned)(g / 16));
 #define HCA_ASSIGN_SC(D, W, NT) vq_assign_small_c_kernel<D, W, NT><<<gm, 256, 0, st>>>(g, c, L.n_kv_heads, L.cap, centroids, pcache, kn, T, nr, acc_opt, pos_opt, vrow0)
 #define HCA_ASSIGN_SCN(D, W)                                                                                          \
@@ -1236,14 +1256,16 @@ int32_t launch_vq_assign(const Layout& L, int g, int c, const float* centroids, 
     else HCA_ASSIGN_SCN(2, false);
 #undef HCA_ASSIGN_SCN
 #undef HCA_ASSIGN_SC
-  } else if (c > kAsCodewords && T > 8 && assign_by_shortlist(L.rows, g, c, T)) {
+  } else if (form == AssignForm::kShortlist) {
     // a block or a context: shortlist on the matrix cores, exact chain on the shortlist
     dim3 gm((unsigned)((T + 1023) / 1024), (unsigned)L.rows, (unsigned)g);
-#define HCA_ASSIGN_M(D, BT) vq_assign_mfma_kernel<D, BT><<<gm, 512, 0, st>>>(g, c, L.n_kv_heads, L.cap, centroids, pcache, kn, T, nr, acc_opt, pos_opt, vrow0)
-    if (g == 32 && c > 2048) HCA_ASSIGN_M(4, 2);
-    else if (g == 32) HCA_ASSIGN_M(4, 1);
-    else if (c > 2048) HCA_ASSIGN_M(2, 2);
-    else HCA_ASSIGN_M(2, 1);
+#define HCA_ASSIGN_M(D, BT, W) vq_assign_mfma_kernel<D, BT, W><<<gm, 512, 0, st>>>(g, c, L.n_kv_heads, L.cap, centroids, pcache, kn, T, nr, acc_opt, pos_opt, vrow0)
+    if (g == 32 && c > 2048) HCA_ASSIGN_M(4, 2, true);
+    else if (g == 32 && wide) HCA_ASSIGN_M(4, 1, true);
+    else if (g == 32) HCA_ASSIGN_M(4, 1, false);
+    else if (c > 2048) HCA_ASSIGN_M(2, 2, true);
+    else if (wide) HCA_ASSIGN_M(2, 1, true);
+    else HCA_ASSIGN_M(2, 1, false);
 #undef HCA_ASSIGN_M
   } else if (T <= 8) {                              // decode appends: parallel over centroids, not over tokens
     // four waves on a group shorten a wave's chain of loads but are four times as many workgroups: while those of the
