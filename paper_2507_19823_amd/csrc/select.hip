@@ -1201,6 +1201,8 @@ __device__ __forceinline__ void tk_resolve_pairs(ResolveShared<NT>& sh, const in
   constexpr int kPer = kHeldPairs / NT, kStep = NT == 512 ? 4 : 8;
   const uint32_t per = (total + NT - 1) / NT;               // HELD: pairs per thread ...
   const uint32_t pos0 = (uint32_t)wv * 64 * per + lane;     // ... the first one's position, 64 apart
+  constexpr bool kKeep = HELD && NT == 1024;                // room for the slots too: 147 -> 142 us for a codebook step at 1 Mi
+  uint32_t held_slot[kKeep ? kPer : 1];
   uint32_t held[HELD ? kPer : 1];                           // their keys (0: no pair; no finite score has it)
   // this thread's pairs u0 .. u0 + 7: their places in the lists (or -1)
   auto locate = [&](int u0, uint32_t (&at)[kStep]) {
@@ -1241,7 +1243,15 @@ __device__ __forceinline__ void tk_resolve_pairs(ResolveShared<NT>& sh, const in
       if ((uint32_t)u0 < per) {
         locate(u0, at);
 #pragma unroll
-        for (int u = 0; u < kStep; ++u) held[u0 + u] = at[u] != 0xffffffffu ? gl.key(at[u]) : 0;
+        for (int u = 0; u < kStep; ++u) {
+          if constexpr (kKeep) {
+            const uint2 x = at[u] != 0xffffffffu ? gl[at[u]] : uint2{0, 0};
+            held[u0 + u] = x.x;
+            held_slot[u0 + u] = x.y;
+          } else {
+            held[u0 + u] = at[u] != 0xffffffffu ? gl.key(at[u]) : 0;
+          }
+        }
       } else {
 #pragma unroll
         for (int u = 0; u < kStep; ++u) held[u0 + u] = 0;
@@ -1415,11 +1425,16 @@ __device__ __forceinline__ void tk_resolve_pairs(ResolveShared<NT>& sh, const in
 #pragma unroll
     for (int u0 = 0; u0 < kPer; u0 += kStep) {
       if ((uint32_t)u0 >= per) break;
-      uint32_t at[kStep];
-      locate(u0, at);
       uint32_t slot[kStep];
+      if constexpr (kKeep) {
 #pragma unroll
-      for (int u = 0; u < kStep; ++u) slot[u] = held[u0 + u] >= T ? gl.slot(at[u]) : 0;    // (T > 0: a pair)
+        for (int u = 0; u < kStep; ++u) slot[u] = held_slot[u0 + u];
+      } else {
+        uint32_t at[kStep];
+        locate(u0, at);
+#pragma unroll
+        for (int u = 0; u < kStep; ++u) slot[u] = held[u0 + u] >= T ? gl.slot(at[u]) : 0;    // (T > 0: a pair)
+      }
 #pragma unroll
       for (int u = 0; u < kStep; ++u) {
         const bool fg = held[u0 + u] > T, fe = held[u0 + u] == T;
