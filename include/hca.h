@@ -149,8 +149,8 @@ int32_t hca_topk_noalloc(const hca_shape* shape, const float* sel, const int64_t
                          int32_t* idx, int32_t* count, void* stream);
 
 /* Steps 2 and 3a in one call (Eq. 2, then the sorted prefix Pi_k of Sec. 3.2): idx and count exactly as
- * hca_score_qkeys followed by hca_topk would leave them.  When no row is longer than 40 Ki slots that is what it
- * does, with the scores in the workspace.  Longer rows are selected without the score of every slot ever reaching
+ * hca_score_qkeys followed by hca_topk would leave them.  When no row is longer than 40 Ki slots, or 128 Ki
+ * with few rows, that is what it does, with the scores in the workspace.  Longer rows are selected without the score of every slot ever reaching
  * memory: a strided sample of each row (8192 to 65536 slots) is scored first and gives a threshold that at least k
  * slots of the row pass with overwhelming probability; the scan then keeps only the (score, slot) pairs
  * at or above it, and the selection runs on those few thousand pairs.  A row whose sample misled (fewer

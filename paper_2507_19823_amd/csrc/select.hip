@@ -2537,8 +2537,8 @@ int32_t launch_topk(const Layout& L, const float* sel, const NRes& nr, int64_t n
   chunk_geometry(nmax, &chunk, &nchunks);
   dim3 g((unsigned)nchunks, (unsigned)L.rows);
   // Where the sampled form's lists fit the selection's registers and one workgroup per row can read the samples.  Per call,
-  // the five launches below / its three, k = 1024 - 8192, normal scores: 8 rows of 50 000 39 / 27 us, of 300 000 34 / 28, of
-  // 500 000 49 / 39, of 1 Mi 50 / 43, 56 of 70 000 36 / 29; all scores equal 675 - 1200 / 46 - 56; 99 % masked 42 - 950 /
+  // the five launches below / its three, k = 1024 - 8192, normal scores: 8 rows of 50 000 39 / 25 us, of 300 000 34 / 26, of
+  // 500 000 49 / 34, of 1 Mi 50 / 38, 56 of 70 000 36 / 27; all scores equal 675 - 1200 / 46 - 56; 99 % masked 42 - 950 /
   // 32 - 64 (300 000 slots, k = 1024: 43 / 48); 4 Mi slots in one row, 32 768 samples, 53 / 57.
   if (select_sample_count(nmax, k) <= 16384 && select_lists_fit(nmax, k))
     return launch_topk_sampled(L, sel, nr, nmax, sr, k, idx, count, t, ListRoom{t.cand, nullptr, t.row_entries, 0, 0}, RowSelectFused{}, st);
