@@ -376,3 +376,53 @@ def test_step_driver_selects_at_the_edges_of_what_is_held_in_registers(H, oracle
             assert lcnt[l, r].item() == c == ocount[r]
             assert np.array_equal(lidx[l, r, :c].cpu().numpy(), oidx[r, :c]), f"layer {l} row {r}: index sets differ"
     B.hca_pipeline_destroy(pl)
+
+
+def _runs(n, kind):
+    """Slots with large scores: the two ends of the row, three runs far apart, the last chunk's neighbourhood, or forty
+    short runs - thousands of pairs in a few lists, with hundreds of empty ones before, between and after them."""
+    large = torch.zeros(n, dtype=torch.bool)
+    if kind == "ends":
+        large[:n // 25] = large[-(n // 25):] = True
+    elif kind == "three":
+        for a in (n // 7, n // 2, n - n // 9):
+            large[a:a + n // 33] = True
+    elif kind == "last":
+        large[-(n // 12):] = True
+    else:
+        for i in range(40):
+            a = (i * n) // 40 + 37 * (i % 5)
+            large[a:a + n // 500] = True
+    return large
+
+
+def _runs_layer(w, kind):
+    d = S.make_layer(w, want_values=False)
+    g = torch.Generator().manual_seed(w.n)
+    q = d["q"].clone()
+    q[:, 1:] = q[:, :1]                                       # four equal query heads
+    size = torch.where(_runs(w.n, kind), 1.0, -1.0)[:, None] * (0.5 + torch.rand(w.n, 1, generator=g))
+    keys = size * q[:, 0].float()[:, None, :] + 0.02 * torch.randn(w.batch, w.n, 128, generator=g)
+    return dict(d, q=q, keys=keys.to(torch.float16)[:, None])
+
+
+@pytest.mark.parametrize("kind", ["ends", "three", "last", "short"])
+@pytest.mark.parametrize("n", [150000, 300000])
+def test_pairs_in_a_few_lists_far_apart(H, oracle, n, kind):
+    w = S.Workload("runs", 94, 2, 4, 1, n, 4, 32, 4000)
+    d = _runs_layer(w, kind)
+    _run(H, oracle, w, d["keys"], d["q"], [n, n - n // 3], w.k)
+
+
+@pytest.mark.parametrize("kind", ["ends", "three", "short"])
+@pytest.mark.parametrize("dual", [0, 2])
+def test_step_driver_with_pairs_in_a_few_lists_far_apart(H, oracle, monkeypatch, dual, kind):
+    """The step driver's forms on such rows (its 512-thread form holds 128 groups of positions per wave)."""
+    make = S.make_layer
+
+    def clustered(w, want_values=True):
+        monkeypatch.setattr(S, "make_layer", make)
+        return _runs_layer(w, kind)
+
+    monkeypatch.setattr(S, "make_layer", clustered)
+    test_step_driver_selects_at_the_edges_of_what_is_held_in_registers(H, oracle, 3000, dual)
