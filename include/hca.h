@@ -149,14 +149,17 @@ int32_t hca_topk_noalloc(const hca_shape* shape, const float* sel, const int64_t
                          int32_t* idx, int32_t* count, void* stream);
 
 /* Steps 2 and 3a in one call (Eq. 2, then the sorted prefix Pi_k of Sec. 3.2): idx and count exactly as
- * hca_score_qkeys followed by hca_topk would leave them.  When no row is longer than 40 Ki slots, or 128 Ki
- * with few rows, that is what it does, with the scores in the workspace.  Longer rows are selected without the score of every slot ever reaching
- * memory: a strided sample of each row (8192 to 65536 slots) is scored first and gives a threshold that at least k
+ * hca_score_qkeys followed by hca_topk would leave them.  When no row is longer than 40 Ki slots - or than 96 Ki, while
+ * batch * n_kv_heads times the longest is below 1.2 M and k small enough for hca_topk to select by a sampled key (about
+ * 12 000) - that is what it does, with the scores in the workspace.  Longer rows are selected without the score of every
+ * slot ever reaching memory: a strided sample of each row (8192 to 65536 slots) is scored first and gives a threshold that at least k
  * slots of the row pass with overwhelming probability; the scan then keeps only the (score, slot) pairs
  * at or above it, and the selection runs on those few thousand pairs.  A row whose sample misled (fewer
  * than k pairs) is scanned a second time inside the same call - with a lower threshold that a count taken
  * during the first scan proves sufficient, else with none -, so the result never depends on the sample;
- * only the time does.
+ * only the time does.  (Rows of 40 to 96 Ki are not scanned again: one workgroup lists such a row anew from the scores
+ * already there, by a lower key, else whole - 0.2 to 0.4 ms - and the report and the monitor below count it as a second
+ * scan.)
  *   workspace  device, hca_workspace_bytes(shape, k, 1) bytes
  * Errors: HCA_ERR_CAPACITY if k < 1, k > capacity, or a row holds more than 8 Mi resident slots. */
 int32_t hca_score_topk(const hca_shape* shape, const void* kcache, const void* q_f16, const int64_t* n_resident,

@@ -111,8 +111,8 @@ constexpr int kSampleMax = 65536;
 int select_sample_count(int64_t nmax, int32_t k);
 // whether a selection of k in rows of up to nmax slots has lists that the selection holds in registers
 bool select_lists_fit(int64_t nmax, int32_t k);
-int32_t launch_topk_sample_rank(const float* vals, int64_t stride, int rows, int n_kv_heads, const NRes& nr, int32_t k, int m,
-                                uint32_t* spec, hipStream_t st);
+int32_t launch_topk_sample_rank(const float* vals, int64_t stride, int rows, int n_kv_heads, const NRes& nr, int64_t nmax,
+                                int32_t k, int m, uint32_t* keys, int64_t key_row, uint32_t* spec, hipStream_t st);
 // blocks per wave of the selecting scan over nmax slots (chunks per row <= kSelectMaxChunks); 0: too long a row
 int select_scan_bpw(const Layout& L, int64_t nmax);
 int32_t launch_select_sample(const Layout& L, const void* kcache, const void* q, const NRes& nr, int32_t k,

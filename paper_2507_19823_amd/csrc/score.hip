@@ -504,7 +504,7 @@ __global__ __launch_bounds__(256) void select_sample_score(Layout L, const uint8
 // The threshold from a row's samples, key_at(i) = the key of sample i < m_samples (0: no such slot).  NT = 256 threads are
 // small enough to find room on a chip that another stream's scan keeps full; 1024 are quicker on a free one (a chain of
 // passes and barriers: 8 x 32 768 samples 18 -> 10 us).
-// EXACT: sp[0] = the r-th largest sample's whole key (0: r >= m), and no second threshold.
+// EXACT: sp[0] = the r-th largest sample's whole key (0: r >= m); the second threshold from the 4r-th.
 template <int NT, bool EXACT, typename F>
 __device__ __forceinline__ void sample_rank_body(const int64_t n, int32_t k, F&& key_at, const int m_samples,
                                                  uint32_t* __restrict__ spec, const int row) {
@@ -519,24 +519,46 @@ __device__ __forceinline__ void sample_rank_body(const int64_t n, int32_t k, F&&
     if (tid == 0) { sp[0] = 0xffffffffu; sp[1] = 0; sp[2] = 0xffffffffu; }
     return;
   }
-  // f(key) for every sample: the first 8 per thread are kept, any others read again for each pass, 8 in flight
-  uint32_t first[8];
+  // f(key) for every sample: the first kKeep per thread are kept, any others read again for each pass, 8 in flight
+  constexpr int kKeep = EXACT ? 16 : 8;
+  uint32_t first[kKeep];
 #pragma unroll
-  for (int i = 0; i < 8; ++i) first[i] = key_at(i * NT + tid);
-  auto each = [&](auto&& f) {
+  for (int i0 = 0; i0 < kKeep; i0 += 8) {
+    if (i0 * NT < m_samples) {
 #pragma unroll
-    for (int i = 0; i < 8; ++i) f(first[i]);
-    for (int i0 = 8 * NT; i0 < m_samples; i0 += 8 * NT) {
+      for (int i = i0; i < i0 + 8; ++i) first[i] = key_at(i * NT + tid);
+    } else {
+#pragma unroll
+      for (int i = i0; i < i0 + 8; ++i) first[i] = 0;
+    }
+  }
+  // a thread's samples of the same bin as its first - in rows of equal or masked scores nearly all - are one update
+  auto count = [&](const uint32_t* key, auto&& bin, auto&& hit) {
+    const uint32_t b0 = bin(key[0]);
+    uint32_t same = 0;
+#pragma unroll
+    for (int i = 0; i < 8; ++i) same += hit(key[i]) && bin(key[i]) == b0;
+    if (same != 0) atomicAdd(&hist[b0], same);
+#pragma unroll
+    for (int i = 1; i < 8; ++i)
+      if (hit(key[i]) && bin(key[i]) != b0) atomicAdd(&hist[bin(key[i])], 1u);
+  };
+  auto count_all = [&](auto&& bin, auto&& hit) {
+#pragma unroll
+    for (int i0 = 0; i0 < kKeep; i0 += 8) {
+      if (i0 * NT >= m_samples) break;
+      count(first + i0, bin, hit);
+    }
+    for (int i0 = kKeep * NT; i0 < m_samples; i0 += 8 * NT) {
       uint32_t key[8];
 #pragma unroll
       for (int i = 0; i < 8; ++i) key[i] = key_at(i0 + i * NT + tid);
-#pragma unroll
-      for (int i = 0; i < 8; ++i) f(key[i]);
+      count(key, bin, hit);
     }
   };
   for (int i = tid; i < 4096; i += NT) hist[i] = 0;
   __syncthreads();
-  each([&](uint32_t key) { if (key != 0) atomicAdd(&hist[key >> 20], 1u); });
+  count_all([](uint32_t key) { return key >> 20; }, [](uint32_t key) { return key != 0; });
   __syncthreads();
   // bins from the top: thread tid owns bins 4095 - kFirst tid - i
   uint32_t h[kFirst], sum = 0;
@@ -553,8 +575,9 @@ __device__ __forceinline__ void sample_rank_body(const int64_t n, int32_t k, F&&
   }
   // a second, deeper threshold for the case that the first one turns out too high: the lower bound of the 12-bit
   // bin that holds the 8r-th largest sample (0 if there is no such sample).  The scan counts the slots at or
-  // above it, so that the selection knows whether a second scan with it is enough.
-  const uint32_t r1 = 8 * r;
+  // above it, so that the selection knows whether a second scan with it is enough.  (EXACT: the selection lists the row
+  // with it by itself.)
+  const uint32_t r1 = (EXACT ? 4 : 8) * r;
   if (tid == 0) sp[2] = 0;
 #pragma unroll
   for (int i = 0; i < kFirst; ++i) {
@@ -563,14 +586,15 @@ __device__ __forceinline__ void sample_rank_body(const int64_t n, int32_t k, F&&
     running += h[i];
   }
   __syncthreads();
-  if (!EXACT && tid == 0 && r1 < m) sp[2] = s_bin1 << 20;
+  if (tid == 0 && r1 < m) sp[2] = s_bin1 << 20;
   // the next ten bits of the key, and for the whole of it the last ten
   uint32_t prefix = s_bin, rem = s_rem;
 #pragma unroll
   for (int shift = 10; shift >= (EXACT ? 0 : 10); shift -= 10) {
     for (int i = tid; i < 1024; i += NT) hist[i] = 0;
     __syncthreads();
-    each([&](uint32_t key) { if (key != 0 && key >> (shift + 10) == prefix) atomicAdd(&hist[(key >> shift) & 1023u], 1u); });
+    count_all([&](uint32_t key) { return (key >> shift) & 1023u; },
+              [&](uint32_t key) { return key != 0 && key >> (shift + 10) == prefix; });
     __syncthreads();
     uint32_t g[kSecond];
     sum = 0;
@@ -603,27 +627,62 @@ __global__ __launch_bounds__(1024) void select_sample_rank(Layout L, NRes nr, in
                          (int)blockIdx.x);
 }
 
-// The same from scores that are there already (hca_topk): sample i is slot i % 16 of a block of 16 slots, block
-// floor((s + h(s)) nblocks / S) of the row, s = i / 16, S = min(nblocks, m / 16), with 0 <= h(s) < 1 scattered by s, so that
-// no period of the row meets that of the samples.
+// The same from scores that are there already (hca_topk).  Sample i is the slot floor((i + h(i)) n / S) of the row, S =
+// min(n, m): one slot of each of S equal strata, at a place 0 <= h(i) < 1 within it that is scattered by i, so that no period
+// of the row meets that of the samples (with h(i) = frac(i phi) some periods did, by 20 deviations).  The number of samples
+// among a row's best then spreads no more than that of independent ones, however much neighbours resemble each other, and
+// six deviations are six.  Of 120 calls over 8 rows whose scores come in runs of 16 or 64, samples of 16 neighbouring slots
+// misread a row in up to 45 (a call of 185 - 1700 us) and left 8 rows of 1 Mi more pairs than the selection holds (78 - 96
+// us, k = 4096); one slot per place: no row, 43 us.
+struct TopkSample {
+  const float* v;
+  uint32_t n, S;
+  int shift;
+  __device__ __forceinline__ TopkSample(const float* row, int64_t slots, int m)
+      : v(row), n((uint32_t)slots), S(n < (uint32_t)m ? n : (uint32_t)m), shift(__builtin_ctz(m)) {}      // (m is a power of two)
+  __device__ __forceinline__ uint32_t key(uint32_t i) const {
+    uint32_t h = i * 0x9E3779B1u;                           // xxHash32's avalanche of i
+    h = (h ^ h >> 15) * 0x85EBCA77u;
+    h = (h ^ h >> 13) * 0xC2B2AE3Du;
+    h ^= h >> 16;
+    const uint32_t j = S == n ? i : (uint32_t)(((uint64_t)i * n + ((uint64_t)h * n >> 32)) >> shift);
+    return i < S ? order_key(v[j]) : 0u;
+  }
+};
 __global__ __launch_bounds__(1024) void topk_sample_rank(const float* __restrict__ vals, int64_t stride, int n_kv_heads,
                                                          NRes nr, int32_t k, int m, uint32_t* __restrict__ spec) {
   const int row = blockIdx.x;
   const int64_t n = nr.n[row / n_kv_heads];
-  const float* v = vals + (int64_t)row * stride;
-  const uint32_t nblocks = (uint32_t)((n + 15) / 16), most = (uint32_t)m / 16, S = nblocks < most ? nblocks : most;
-  const int shift = __builtin_ctz(most);                    // (m is a power of two)
-  auto key_at = [&](int i) -> uint32_t {
-    const uint32_t s = (uint32_t)i / 16;
-    const uint32_t b = S == nblocks ? s : (uint32_t)(((uint64_t)s * nblocks + ((uint64_t)(s * 2654435761u) * nblocks >> 32)) >> shift);
-    const int64_t j = (int64_t)b * 16 + (i & 15);
-    return s < S && j < n ? order_key(v[j]) : 0u;
-  };
-  sample_rank_body<1024, true>(n, k, key_at, m, spec, row);
+  const TopkSample at(vals + (int64_t)row * stride, n, m);
+  sample_rank_body<1024, true>(n, k, [&](int i) { return at.key((uint32_t)i); }, m, spec, row);
 }
-int32_t launch_topk_sample_rank(const float* vals, int64_t stride, int rows, int n_kv_heads, const NRes& nr, int32_t k, int m,
-                                uint32_t* spec, hipStream_t st) {
-  topk_sample_rank<<<rows, 1024, 0, st>>>(vals, stride, n_kv_heads, nr, k, m, spec);
+// The same in two launches, the samples' keys on their way through `keys`.  A line per sample is more than one compute unit
+// can ask for in rows longer than kSampleOneUnit.  8 rows, one launch / two, the scores in HBM (in L2), us per call: 65 536
+// slots 29 / 31 (26 / 29), 200 000 33 / 31 (27 / 29), 300 000 36 / 33 (29 / 29), 1 Mi 53 / 44 (42 / 37).
+__global__ __launch_bounds__(256) void topk_sample(const float* __restrict__ vals, int64_t stride, int n_kv_heads, NRes nr,
+                                                   int m, uint32_t* __restrict__ keys, int64_t key_row) {
+  const int row = blockIdx.y;
+  const TopkSample at(vals + (int64_t)row * stride, nr.n[row / n_kv_heads], m);
+  uint32_t key[4];
+#pragma unroll
+  for (int u = 0; u < 4; ++u) key[u] = at.key(blockIdx.x * 1024 + u * 256 + threadIdx.x);
+#pragma unroll
+  for (int u = 0; u < 4; ++u) keys[row * key_row + blockIdx.x * 1024 + u * 256 + threadIdx.x] = key[u];
+}
+__global__ __launch_bounds__(1024) void topk_rank(int n_kv_heads, NRes nr, int32_t k, int m, const uint32_t* __restrict__ keys,
+                                                  int64_t key_row, uint32_t* __restrict__ spec) {
+  const uint32_t* in = keys + (int64_t)blockIdx.x * key_row;
+  sample_rank_body<1024, true>(nr.n[blockIdx.x / n_kv_heads], k, [&](int i) { return in[i]; }, m, spec, (int)blockIdx.x);
+}
+constexpr int64_t kSampleOneUnit = 196608;
+int32_t launch_topk_sample_rank(const float* vals, int64_t stride, int rows, int n_kv_heads, const NRes& nr, int64_t nmax,
+                                int32_t k, int m, uint32_t* keys, int64_t key_row, uint32_t* spec, hipStream_t st) {
+  if (nmax <= kSampleOneUnit) {
+    topk_sample_rank<<<rows, 1024, 0, st>>>(vals, stride, n_kv_heads, nr, k, m, spec);
+  } else {
+    topk_sample<<<dim3((unsigned)(m / 1024), (unsigned)rows), 256, 0, st>>>(vals, stride, n_kv_heads, nr, m, keys, key_row);
+    topk_rank<<<rows, 1024, 0, st>>>(n_kv_heads, nr, k, m, keys, key_row, spec);
+  }
   HCA_HIP(hipGetLastError());
   return HCA_OK;
 }

@@ -1644,13 +1644,14 @@ __global__ __launch_bounds__(NT) __attribute__((amdgpu_waves_per_eu(NT == 512 ? 
 // The last launch of a selection from scores: the chunks' lists hold the slots of the keys above the sampled key K
 // (t.state), the chunks' second counts (t.above) the slots equal to it.  Enough above it: the selection over the lists.
 // Enough with the equal ones: all of the lists and the first equal slots.  Neither, which takes a row that its samples
-// misrepresent by six deviations: every slot into the lists, by this workgroup.
+// misrepresent by six deviations: the slots at or above the second key into the lists, by this workgroup - or every slot,
+// should they be too few as well.
 __global__ __launch_bounds__(1024) __attribute__((amdgpu_waves_per_eu(4))) void tk_resolve_scores(
     const float* __restrict__ vals, int64_t stride, int64_t chunk, int nchunks, int n_kv_heads, SelRows sr, TopkWs t,
     ListRoom room, int32_t k, int32_t* __restrict__ idx, int32_t* __restrict__ count, RowSelectFused fu) {
   __shared__ ResolveShared<1024> sh;
   auto& off = sh.off;
-  const int row = blockIdx.x, tid = threadIdx.x;
+  const int row = blockIdx.x, tid = threadIdx.x, lane = tid & 63;
   const int64_t n = sr.nsel[row / n_kv_heads], want = sr.want[row / n_kv_heads];
   const bool live = want > 0 && tid < nchunks;
   const uint32_t mine = live ? t.ncand[(int64_t)row * kMaxChunks + tid] : 0;
@@ -1660,12 +1661,51 @@ __global__ __launch_bounds__(1024) __attribute__((amdgpu_waves_per_eu(4))) void 
   off[tid] = before;
   eoff[tid] = before_e;
   if (tid == 1023) { off[1024] = before + mine; eoff[1024] = before_e + equal; }
-  __syncthreads();
-  const uint32_t total = off[1024], with_equal = total + eoff[1024];
+  const bool fits = __syncthreads_and(mine <= (uint32_t)room.pair_chunk);
+  uint32_t total = off[1024];
+  const uint32_t with_equal = total + eoff[1024];
   const bool misread = want > 0 && with_equal < (uint32_t)want;
+  uint32_t K = want > 0 ? t.state[4 * row] : 0;
+  const float* v = vals + (int64_t)row * stride;
+  bool in_pairs = fits;
+  if (misread) {
+    in_pairs = room.slots == nullptr;
+    K = t.state[4 * row + 2];
+    for (;;) {
+      __syncthreads();                                      // off and eoff have been read
+      for (int c = tid >> 6; c < 1024; c += 16) {           // a wave per chunk, in slot order
+        const int64_t c0 = (int64_t)c * chunk, c1 = c0 + chunk < n ? c0 + chunk : n;
+        uint32_t m = 0;
+        for (int64_t s0 = c0; s0 < c1; s0 += 16 * 64) {
+          uint32_t key[16];
+#pragma unroll
+          for (int x = 0; x < 16; ++x) key[x] = order_key(v[s0 + x * 64 + lane < c1 ? s0 + x * 64 + lane : c1 - 1]);
+#pragma unroll
+          for (int x = 0; x < 16; ++x) {
+            const uint32_t slot = (uint32_t)(s0 + x * 64 + lane);
+            const bool hit = slot < c1 && key[x] >= K;
+            const uint64_t hits = __ballot(hit);
+            const uint32_t at = m + (uint32_t)__popcll(hits & ((1ull << lane) - 1));
+            if (hit && in_pairs) room.pairs[row * room.pair_row + c * chunk + at] = uint2{key[x], slot};
+            else if (hit) room.slots[row * room.slot_row + c * chunk + at] = slot;
+            m += (uint32_t)__popcll(hits);
+          }
+        }
+        if (lane == 0) sh.h[c] = m;
+      }
+      __syncthreads();
+      const uint32_t listed = sh.h[tid], first = block_scan_excl<16>(listed, sh.wsum);
+      off[tid] = first;
+      if (tid == 1023) off[1024] = first + listed;
+      __syncthreads();
+      total = off[1024];
+      if (total >= (uint32_t)want) break;
+      K = 0;
+    }
+  }
   if (fu.spec != nullptr) {                                 // the figures of hca_score_topk's report and monitor
     for (int c = tid; c < fu.nchunks; c += 1024)
-      fu.ncand[(int64_t)row * kSelectMaxChunks + c] = c == 0 && want > 0 ? (misread ? (uint32_t)n : with_equal) : 0u;
+      fu.ncand[(int64_t)row * kSelectMaxChunks + c] = c == 0 && want > 0 ? (misread ? total : with_equal) : 0u;
     if (tid == 0) {
       fu.spec[4 * row + 1] = misread;
       if (want > 0 && fu.mon != nullptr) {
@@ -1681,36 +1721,22 @@ __global__ __launch_bounds__(1024) __attribute__((amdgpu_waves_per_eu(4))) void 
     if (tid == 0) count[row] = 0;
     return;
   }
-  const uint32_t K = t.state[4 * row];
-  const float* v = vals + (int64_t)row * stride;
   const PairList pairs{room.pairs + row * room.pair_row};
   const SlotList slots{room.slots + row * room.slot_row, v};
-  const bool in_pairs = __syncthreads_and(mine <= (uint32_t)room.pair_chunk);     // (and everybody has read eoff's end)
+  const int64_t list_chunk = misread ? chunk : room.pair_chunk;
   if (total >= (uint32_t)want) {
-    if (in_pairs && total <= (uint32_t)kHeldPairs)
-      tk_resolve_pairs<1024, true>(sh, room.pair_chunk, nchunks, want, pairs, K, k, idx, count, row, total);
+    __syncthreads();                                        // eoff has been read
+    // (a second key of 0 lets the key 0 in, which a register could not tell from no pair)
+    if (in_pairs && total <= (uint32_t)kHeldPairs && !(misread && K == 0))
+      tk_resolve_pairs<1024, true>(sh, list_chunk, nchunks, want, pairs, K, k, idx, count, row, total);
     else if (in_pairs)
-      tk_resolve_pairs<1024, false>(sh, room.pair_chunk, nchunks, want, pairs, K, k, idx, count, row, total);
+      tk_resolve_pairs<1024, false>(sh, list_chunk, nchunks, want, pairs, K, k, idx, count, row, total);
     else
       tk_resolve_pairs<1024, false>(sh, chunk, nchunks, want, slots, K, k, idx, count, row, total);
     return;
   }
-  if (misread) {
-    for (int64_t j = tid; j < n; j += 1024) {
-      if (room.slots != nullptr) room.slots[row * room.slot_row + j] = (uint32_t)j;
-      else room.pairs[row * room.pair_row + j] = uint2{order_key(v[j]), (uint32_t)j};
-    }
-    for (int i = tid; i < 1025; i += 1024) off[i] = (uint32_t)(i * chunk < n ? i * chunk : n);
-    __syncthreads();
-    if (room.slots != nullptr)
-      tk_resolve_pairs<1024, false>(sh, chunk, nchunks, want, slots, 0u, k, idx, count, row, (uint32_t)n);
-    else
-      tk_resolve_pairs<1024, false>(sh, chunk, nchunks, want, pairs, 0u, k, idx, count, row, (uint32_t)n);
-    return;
-  }
   // a wave per chunk, in slot order: from the row itself while equal slots are still to take, then from the lists
   const uint32_t req = (uint32_t)want - total;
-  const int lane = tid & 63;
   const uint64_t lt = (1ull << lane) - 1;
   int32_t* out = idx + (int64_t)row * k;
   if (tid == 0) count[row] = (int32_t)want;
@@ -1917,8 +1943,8 @@ int32_t launch_select_finish_pair(const Layout& L, const void* const kcache[2], 
   return HCA_OK;
 }
 
-// Top-k of long rows from their scores in three launches: a key from samples, the lists of the slots above it, the selection
-// over them.  Bound by the launches' latency and one pass over the scores.
+// Top-k of long rows from their scores in three or four launches: a key from samples, the lists of the slots above it, the
+// selection over them.  Bound by the launches' latency and one pass over the scores.
 static int32_t launch_topk_sampled(const Layout& L, const float* scores, const NRes& nr, int64_t nmax, const SelRows& sr,
                                    int32_t k, int32_t* idx, int32_t* count, const TopkWs& t, ListRoom room,
                                    const RowSelectFused& fu, hipStream_t st) {
@@ -1927,7 +1953,10 @@ static int32_t launch_topk_sampled(const Layout& L, const float* scores, const N
   chunk_geometry(nmax, &chunk, &nchunks);
   if (room.slots == nullptr) room.pair_chunk = chunk;
   else if ((room.pair_chunk = room.pair_row / nchunks) > chunk) room.pair_chunk = chunk;
-  const int32_t rc = launch_topk_sample_rank(scores, L.cap, L.rows, L.n_kv_heads, nr, k, select_sample_count(nmax, k), t.state, st);
+  // (the samples' keys, where they need a place, in that of the row's pairs, which are written later; a row has more room
+  // for pairs than samples)
+  const int32_t rc = launch_topk_sample_rank(scores, L.cap, L.rows, L.n_kv_heads, nr, nmax, k, select_sample_count(nmax, k),
+                                             reinterpret_cast<uint32_t*>(room.pairs), 2 * room.pair_row, t.state, st);
   if (rc != HCA_OK) return rc;
   tk_collect_sampled<<<dim3((unsigned)nchunks, (unsigned)L.rows), 256, 0, st>>>(scores, L.cap, chunk, L.n_kv_heads, sr, t, room);
   tk_resolve_scores<<<L.rows, 1024, 0, st>>>(scores, L.cap, chunk, nchunks, L.n_kv_heads, sr, t, room, k, idx, count, fu);
@@ -1937,10 +1966,11 @@ static int32_t launch_topk_sampled(const Layout& L, const float* scores, const N
 
 // Rows up to which, and slots in all rows below which, hca_score_topk writes the scores and selects from them - four launches
 // - instead of sampling and scanning the codes for a threshold and looking for rows to scan again - six.  What the scores
-// cost is 8 bytes per slot.  The call by the six / these four, us: 1 row of 60 000 37 / 34, of 128 Ki 40 / 35; 8 rows of
-// 41 000 40 / 38, of 64 Ki 42 / 40, of 100 000 45 / 44 (2-bit 44 / 42), of 128 Ki 46 / 46 (44 / 43), of 196 000 52 / 53
-// (47 / 48); 16 of 41 000 44 / 41, of 64 Ki 47 / 45, of 100 000 56 / 57; 32 of 41 000 53 / 51, of 64 Ki 64 / 61 (51 / 52).
-constexpr int64_t kScoresMax = 131072, kScoresAll = 1500000;
+// cost is 8 bytes per slot.  The call by the six / these four, k = 2048, 4-bit (2-bit) codes, us: 1 row of 65 536 36 / 34 (39
+// / 36), of 131 072 36 / 38 (39 / 38); 8 rows of 41 000 41 / 38 (42 / 38), of 65 536 41 / 39 (42 / 39), of 100 000 44.5 / 43.7
+// (43.5 / 42.1), of 131 072 45.4 / 46.8 (43.3 / 44.1); 16 of 65 536 46.5 / 45.4 (43.7 / 42.8), of 80 000 49.5 / 51.1 (45.1 /
+// 46.1); 32 of 41 000 51.5 / 51.4 (46.7 / 46.3).
+constexpr int64_t kScoresMax = 98304, kScoresAll = 1200000;
 
 int32_t launch_score_topk(const Layout& L, const void* kcache, const void* q, const NRes& nr, int64_t nmax, int32_t k,
                           int32_t* idx, int32_t* count, void* ws, hipStream_t st) {
@@ -2546,10 +2576,11 @@ int32_t launch_topk(const Layout& L, const float* sel, const NRes& nr, int64_t n
   int32_t nchunks;
   chunk_geometry(nmax, &chunk, &nchunks);
   dim3 g((unsigned)nchunks, (unsigned)L.rows);
-  // Where the sampled form's lists fit the selection's registers and one workgroup per row can read the samples.  Per call,
-  // the five launches below / its three, k = 1024 - 8192, normal scores: 8 rows of 50 000 39 / 25 us, of 300 000 34 / 26, of
-  // 500 000 49 / 34, of 1 Mi 50 / 38, 56 of 70 000 36 / 27; all scores equal 675 - 1200 / 46 - 56; 99 % masked 42 - 950 /
-  // 32 - 64 (300 000 slots, k = 1024: 43 / 48); 4 Mi slots in one row, 32 768 samples, 53 / 57.
+  // Where the sampled form's lists fit the selection's registers and one workgroup per row can rank the samples.  Per call,
+  // the five launches below / its three or four, 8 rows, us: normal scores, 50 000 slots and k = 1024 42 / 27, 300 000 and
+  // 1024 37 / 30, 4096 48 / 31, 500 000 and 8192 54 / 38, 1 Mi and 4096 48 / 41, 8192 52 / 47; in runs of 64 500 000 52 -
+  // 100 / 38, 1 Mi 53 - 104 / 44 - 47; all equal 674 - 1170 / 30 - 41; 99 % masked 44 - 920 / 30 - 44.  4 Mi slots in one
+  // row, 32 768 samples by one workgroup, 53 / 57.
   if (select_sample_count(nmax, k) <= 16384 && select_lists_fit(nmax, k))
     return launch_topk_sampled(L, sel, nr, nmax, sr, k, idx, count, t, ListRoom{t.cand, nullptr, t.row_entries, 0, 0}, RowSelectFused{}, st);
   if (nmax > 0) {

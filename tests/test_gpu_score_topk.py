@@ -159,10 +159,11 @@ def test_second_scan_with_the_deeper_threshold(H, oracle):
 
 
 @pytest.mark.parametrize("kind", ["crowded", "misread", "equal"])
-@pytest.mark.parametrize("n", [41000, 100000, 131072])
+@pytest.mark.parametrize("n", [41000, 70000, 98304])
 def test_rows_of_medium_length(H, oracle, n, kind):
     """Rows whose scores are written and selected from: the best slots crowded into a few thousand neighbours (more than a
     chunk's room for pairs), a row its samples misrepresent (their places as topk_sample_rank takes them), equal scores."""
+    from test_gpu_dispatch import _sampled_slots
     k = 3000
     w = S.Workload("mid", 91, 2, 4, 1, n, 4, 32, k)
     d = S.make_layer(w, want_values=False)
@@ -173,18 +174,40 @@ def test_rows_of_medium_length(H, oracle, n, kind):
     if kind == "crowded":
         large[20000:24500] = True
     elif kind == "misread":
-        nblocks, most = (n + 15) // 16, 8192 // 16
-        s = torch.arange(most, dtype=torch.int64)
-        block = (s * nblocks + ((((s * 2654435761) & 0xffffffff) * nblocks) >> 32)) // most
-        large[(block[:, None] * 16 + torch.arange(16)).flatten().clamp(max=n - 1)] = True
+        large[torch.from_numpy(_sampled_slots(n))] = True
     size = torch.where(large, 1.0, -1.0)[:, None] * (0.5 + torch.rand(n, 1, generator=g))
     keys = (size * q[:, 0].float()[:, None, :] + 0.02 * torch.randn(2, n, 128, generator=g)).to(torch.float16)[:, None]
     if kind == "equal":
         keys = keys[:, :, :1].expand(-1, -1, n, -1).contiguous()
     lens = [n, n - 7 if kind == "crowded" else 5000]
     cand, resc = _run(H, oracle, w, keys, q, lens, k)
-    # misread: only sampled slots score high, so those above the r-th largest sample are r - 1 <= 766 (n = 41 000) < k
+    # misread: only sampled slots score high, so those above the r-th largest sample are r - 1 <= 766 (n = 41 000) < k; the
+    # second key, the 4r-th, lets 3064 or more through there and too few (4r = 1460, at 98 304) in the longest rows
     assert cand[0] >= k and resc[0] == (kind == "misread")
+    if kind == "misread" and n != 70000:
+        assert (cand[0] == n) == (n == 98304)
+
+
+@pytest.mark.parametrize("run", [16, 64])
+def test_rows_of_medium_length_whose_neighbours_resemble_each_other(H, run):
+    """No row of 320 in runs of equal direction misleads its samples (16 neighbouring slots per sample do so in one of 75)."""
+    from paper_2507_19823_amd import binding as B
+    from paper_2507_19823_amd.session import LayerState
+    b, hkv, n, k = 2, 8, 65536, 1024
+    g = torch.Generator(device="cuda").manual_seed(run)
+    st = LayerState(b, hkv, hkv, n, 4, 32, k_max=k, want_z=False)
+    idx = torch.zeros(b, hkv, k, dtype=torch.int32, device="cuda")
+    cand, resc, count = (torch.zeros(b, hkv, dtype=torch.int32, device="cuda") for _ in range(3))
+    for turn in range(20):
+        base = torch.randn(b, hkv, n // run, 128, generator=g, device="cuda").repeat_interleave(run, 2)
+        st.n = [0] * b
+        st.quantize((base + 0.05 * torch.randn(base.shape, generator=g, device="cuda")).half())
+        q = torch.randn(b, hkv, 128, generator=g, device="cuda").half()
+        B.hca_score_topk(st.shape, st.kcache, q, st.n, k, idx, count, st.ws)
+        B.hca_score_topk_report(st.shape, st.n, st.ws, cand, resc)
+        st.score(q)
+        assert (count == k).all() and (resc == 0).all() and (cand >= k).all(), f"turn {turn}: {resc.tolist()}"
+        assert torch.equal(st.sel.gather(2, idx.long()).sort(dim=2).values, st.sel.topk(k, dim=2).values.sort(dim=2).values)
 
 
 def test_running_monitor_over_several_calls(H):
