@@ -340,9 +340,14 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(4))) void s
 
 // The selecting scan once more for the rows whose sampled threshold left too few pairs (spec[row][1] != 0, with
 // the threshold already reset to 0).  Almost always there is no such row, so the launch is kept small - up to 256
-// workgroups per row that walk over the row's chunks - and costs next to nothing when it has nothing to do.
+// workgroups per row that walk over the row's chunks - and costs next to nothing when it has nothing to do.  At most 128
+// registers, so that a workgroup fits into the room of one finished scan workgroup (128 of them): with 160 the paired launch
+// waited for two on one compute unit, 165 us beside a scan launch of 195 with not one row to do.  Four blocks ahead and the
+// body once take 116 without spilling (eight ahead 128 and 45 - 69 spilled).  Step driver, two layers, 8 rows of one of them
+// scanned again with the second threshold, 160 registers / eight ahead and spills / this, us: 200 000 slots 520 / 310 / 310
+// (2-bit 460 / 295 / 288), 1 Mi 905 / 936 / 930 (760 / 730 / 705); a call, 1 Mi: 317 / 314 / 310 (237 / 224 / 222).
 template <int BITS, int U>
-__global__ __launch_bounds__(256) void score_failed_rows_kernel(Layout L, const uint8_t* __restrict__ kcache,
+__global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(4))) void score_failed_rows_kernel(Layout L, const uint8_t* __restrict__ kcache,
                                                                 const uint16_t* __restrict__ q, NRes nr, int bpw,
                                                                 int nchunks, SelectOut so) {
   if (so.spec[4 * blockIdx.y + 1] == 0) return;
@@ -353,9 +358,7 @@ __global__ __launch_bounds__(256) void score_failed_rows_kernel(Layout L, const 
   }
 }
 
-// The same for the two layers of a paired launch: grid.y = 2 x rows.  At most 128 registers, so that a workgroup fits into
-// the room of one finished scan workgroup (128 of them): with 160 it waited for two on one compute unit, 165 us beside a
-// scan launch of 195 with not one row to do.
+// The same for the two layers of a paired launch: grid.y = 2 x rows.
 struct RescanSide {
   const uint8_t* kcache;
   const uint16_t* q;
@@ -364,18 +367,17 @@ struct RescanSide {
   NRes32 nr;
 };
 template <int BITS, int U>
-__device__ __forceinline__ void rescan_side(const Layout& L, const RescanSide& s, const int row) {
-  if (s.so.spec[4 * row + 1] == 0) return;
-  for (int bx = blockIdx.x; bx < s.nchunks; bx += gridDim.x) {
-    score_body<BITS, false, U, false, true>(L, s.kcache, s.q, s.nr.n[row / L.n_kv_heads], s.bpw, nullptr, nullptr, nullptr,
-                                            0.f, nullptr, s.so, bx, s.nchunks, row);
+__global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(4))) void score_failed_rows_pair_kernel(Layout L, RescanSide a, RescanSide b) {
+  const bool first = (int)blockIdx.y < L.rows;              // (the body stands once)
+  const int row = first ? (int)blockIdx.y : (int)blockIdx.y - L.rows;
+  SelectOut so = first ? a.so : b.so;
+  if (so.spec[4 * row + 1] == 0) return;
+  const int nchunks = first ? a.nchunks : b.nchunks, seq = row / L.n_kv_heads;
+  for (int bx = blockIdx.x; bx < nchunks; bx += gridDim.x) {
+    score_body<BITS, false, U, false, true>(L, first ? a.kcache : b.kcache, first ? a.q : b.q, first ? a.nr.n[seq] : b.nr.n[seq],
+                                            first ? a.bpw : b.bpw, nullptr, nullptr, nullptr, 0.f, nullptr, so, bx, nchunks, row);
     __syncthreads();
   }
-}
-template <int BITS, int U>
-__global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(4))) void score_failed_rows_pair_kernel(Layout L, RescanSide a, RescanSide b) {
-  if ((int)blockIdx.y < L.rows) rescan_side<BITS, U>(L, a, (int)blockIdx.y);
-  else rescan_side<BITS, U>(L, b, (int)blockIdx.y - L.rows);
 }
 
 // lse[row * G + h] = log sum exp over the first `live` wave pairs of the row (waves of workgroups that
@@ -1089,8 +1091,8 @@ int32_t launch_select_rescan_pair(const Layout& L, const void* const kcache[2], 
   // 16 workgroups per row, not the 256 of the per-call path: nearly always no row failed and every workgroup
   // returns at once, but beside a running scan 4096 of them take a slot each first (0.2 ms per step at config 4)
   dim3 grid(gx < 16 ? gx : 16, (unsigned)(2 * L.rows));
-  if (L.bits == 4) score_failed_rows_pair_kernel<4, 8><<<grid, 256, lds, st>>>(L, rs[0], rs[1]);
-  else score_failed_rows_pair_kernel<2, 8><<<grid, 256, lds, st>>>(L, rs[0], rs[1]);
+  if (L.bits == 4) score_failed_rows_pair_kernel<4, 4><<<grid, 256, lds, st>>>(L, rs[0], rs[1]);
+  else score_failed_rows_pair_kernel<2, 4><<<grid, 256, lds, st>>>(L, rs[0], rs[1]);
   HCA_HIP(hipGetLastError());
   return HCA_OK;
 }
@@ -1107,8 +1109,8 @@ int32_t launch_select_scan(const Layout& L, const void* kcache, const void* q, c
   const uint16_t* qq = (const uint16_t*)q;
   if (only_failed) {
     dim3 small(grid.x < 256 ? grid.x : 256, (unsigned)L.rows);
-    if (L.bits == 4) score_failed_rows_kernel<4, 8><<<small, 256, lds, st>>>(L, kc, qq, nr, bpw, (int)grid.x, so);
-    else score_failed_rows_kernel<2, 8><<<small, 256, lds, st>>>(L, kc, qq, nr, bpw, (int)grid.x, so);
+    if (L.bits == 4) score_failed_rows_kernel<4, 4><<<small, 256, lds, st>>>(L, kc, qq, nr, bpw, (int)grid.x, so);
+    else score_failed_rows_kernel<2, 4><<<small, 256, lds, st>>>(L, kc, qq, nr, bpw, (int)grid.x, so);
   } else if (L.bits == 4) {
     score_select_kernel<4, 8><<<grid, 256, lds, st>>>(L, kc, qq, nr, bpw, stamps, so);
   } else {

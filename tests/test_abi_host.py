@@ -341,3 +341,41 @@ def test_host_chunk_sum_against_numpy(B, gqa, isa):
     assert np.allclose(py[:gqa], ref[:gqa], rtol=1e-5, atol=1e-6)
     assert L.hca_debug_host_chunk_sum(5, p.ctypes.data, vrow.ctypes.data, V.ctypes.data, n_rows, py.ctypes.data) == -1
     B.hca_tune("host_isa", 0)
+
+
+def _kernels(path):
+    """Registers and scratch of every gfx950 kernel in the library, from the metadata the compiler left in it."""
+    import struct
+    import subprocess
+    import tempfile
+    blob, out = open(path, "rb").read(), {}
+    for m in re.finditer(b"__CLANG_OFFLOAD_BUNDLE__", blob):
+        at = m.end()
+        (n,) = struct.unpack_from("<Q", blob, at)
+        at += 8
+        for _ in range(n):
+            off, size, length = struct.unpack_from("<QQQ", blob, at)
+            target = blob[at + 24:at + 24 + length]
+            at += 24 + length
+            if not target.endswith(b"gfx950") or size == 0:
+                continue
+            with tempfile.NamedTemporaryFile() as f:
+                f.write(blob[m.start() + off:m.start() + off + size])
+                f.flush()
+                notes = subprocess.run(["/opt/rocm/llvm/bin/llvm-readelf", "--notes", f.name], capture_output=True,
+                                       text=True, check=True).stdout
+            for k in re.split(r"^  - \.", notes, flags=re.M)[1:]:
+                name = re.search(r"\.name: +(\S+)", k)
+                if name and ".vgpr_count" in k:
+                    out[name.group(1)] = {x: int(re.search(rf"\.{x}: +(\d+)", k).group(1))
+                                          for x in ("vgpr_count", "private_segment_fixed_size")}
+    return out
+
+
+def test_the_scan_of_failed_rows_fits_beside_a_scan_without_scratch(B):
+    """One finished workgroup of a scan leaves 128 registers per lane; a kernel that is to start there takes no more, and
+    not by spilling the rest."""
+    found = {k: v for k, v in _kernels(B.LIB_PATH).items() if "score_failed_rows" in k}
+    assert len(found) == 4
+    for name, use in found.items():
+        assert use["vgpr_count"] <= 128 and use["private_segment_fixed_size"] == 0, (name, use)
