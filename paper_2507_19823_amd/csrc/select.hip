@@ -1354,7 +1354,7 @@ __device__ __forceinline__ void tk_resolve_pairs(ResolveShared<NT>& sh, const in
       req = rem;
       break;
     }
-    if (cb <= kDirectRank) {
+    if (cb <= (HELD ? kDirectRank : 1024)) {                // (unheld, a round is one more walk through the lists)
       // few pairs left: rank them against each other.  sl = their keys; T is the key with fewer than rem keys
       // above it that, together with its equals, reaches rem.
       uint32_t* sl = h;
@@ -1366,8 +1366,8 @@ __device__ __forceinline__ void tk_resolve_pairs(ResolveShared<NT>& sh, const in
         if (hit && ((key - base1) >> sbits) == pd) sl[atomicAdd(&s_cb, 1u)] = key;
       });
       __syncthreads();
-      if ((uint32_t)tid < cb) {                             // (cb <= kDirectRank < NT)
-        const uint32_t ki = sl[tid];
+      for (uint32_t me = (uint32_t)tid; me < cb; me += NT) {
+        const uint32_t ki = sl[me];
         uint32_t gt = 0, eq = 0;
 #pragma unroll 4
         for (uint32_t j = 0; j < cb; ++j) {

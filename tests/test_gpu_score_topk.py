@@ -16,10 +16,11 @@ def H():
     return H
 
 
-@pytest.fixture(autouse=True, params=[0, 256], ids=["wg1024", "wg256"])
+@pytest.fixture(autouse=True, params=[0, 256], ids=["default", "wg256"])
 def select_wg(request, H):
     """Every case runs with two forms of the selection over the candidate lists: the default one (1024 threads for a
-    call, 512 in a step driver) and the one of 256 threads."""
+    call, 512 in a step driver) and the one of 256 threads.  (Rows of up to 96 Ki in small batches are selected from their
+    scores, whatever the form.)"""
     H.hca_tune("select_wg", request.param)
     yield request.param
     H.hca_tune("select_wg", 0)
@@ -98,14 +99,39 @@ def test_fewer_query_heads_per_kv_head(H, oracle, hq, hkv):
     _run(H, oracle, w, d["keys"], d["q"], [40000, 12345], 512)
 
 
-def test_ties_and_a_list_too_long_for_lds(H, oracle):
-    """Every key the same: every slot passes any threshold (50 000 pairs, more than are held in registers) and the
-    k lowest slots win."""
+def test_ties_in_a_row_of_medium_length(H, oracle):
+    """Every key the same, 50 000 slots: none scores above the sampled key, the k lowest slots of those equal to it win."""
     w = S.Workload("tie", 95, 1, 4, 1, 50000, 4, 32, 777)
     d = S.make_layer(w, want_values=False)
     keys = d["keys"][:, :, :1].expand(-1, -1, w.n, -1).contiguous()
     cand, resc = _run(H, oracle, w, keys, d["q"], [w.n], w.k)
-    assert cand[0] == w.n and resc[0] == 0        # one key value: every slot passes the threshold
+    assert cand[0] == w.n and resc[0] == 0        # one key value: none below the sampled key
+
+
+def _tied_layer(w, tied):
+    """Keys of which `tied` per row, here and there, are the same and score highest; the others random."""
+    d = S.make_layer(w, want_values=False)
+    q = d["q"].clone()
+    q[:, 1:] = q[:, :1]                                       # four equal query heads
+    keys = d["keys"].clone()
+    g = torch.Generator().manual_seed(tied)
+    for b in range(w.batch):
+        at = torch.randperm(w.n, generator=g)[:tied]
+        keys[b, 0, at] = (q[b, 0].float() * 100 / q[b, 0].float().norm()).half()
+    return dict(d, q=q, keys=keys)
+
+
+@pytest.mark.parametrize("bits,gs", [(4, 32), (2, 64)])
+@pytest.mark.parametrize("n,tied,k,second", [
+    (150000, 150000, 777, 150000), (150000, 20000, 4000, 60000), (150000, 60000, 1, 33333), (200000, 66000, 16000, 200000),
+    (150000, 17000, 16999, 20000), (120000, 30000, 31000, 100000)])
+def test_ties_in_lists_too_long_for_the_registers(H, oracle, bits, gs, n, tied, k, second):
+    """The selecting scan's lists with more than 16 384 pairs at one key, some or all of them to be taken: up to 65 536
+    pairs found by position, more walked chunk by chunk; the lowest slots win."""
+    w = S.Workload("tied", 93 + bits, 2, 4, 1, n, bits, gs, k)
+    d = _tied_layer(w, tied)
+    cand, resc = _run(H, oracle, w, d["keys"], d["q"], [n, second], k)
+    assert cand[0] >= max(k, tied) and resc[0] == 0
 
 
 @pytest.mark.parametrize("bits,gs,tpb", [(4, 32, 16), (2, 64, 32)])
@@ -337,12 +363,13 @@ def test_step_driver_pair_with_a_row_that_needs_the_second_scan(H, oracle, own_i
 
 @pytest.mark.parametrize("dual", [0, 2])
 @pytest.mark.parametrize("k", [60, 8000, 16384])
-def test_step_driver_selects_at_the_edges_of_what_is_held_in_registers(H, oracle, k, dual):
+def test_step_driver_selects_at_the_edges_of_what_is_held_in_registers(
+        H, oracle, k, dual, lens=(50000, 16384, 16383, 8192, 8191, 4096, 64, 63, 0)):
     """The step driver's own form of the selection (512 threads; 256 in the fixture's second form), on rows whose lists
     end at and beside the edges: one pair, a wave's worth, a step of registers, all 16384 and one more, and a long row."""
     import ctypes as C
     from paper_2507_19823_amd import binding as B
-    lens = [50000, 16384, 16383, 8192, 8191, 4096, 64, 63, 0]
+    lens = list(lens)
     n, nb, Lr = max(lens), len(lens), 2
     cap = n + 8
     w = S.Workload("held", 92, nb, 4, 1, n, 4, 32, k)
@@ -449,3 +476,23 @@ def test_step_driver_with_pairs_in_a_few_lists_far_apart(H, oracle, monkeypatch,
 
     monkeypatch.setattr(S, "make_layer", clustered)
     test_step_driver_selects_at_the_edges_of_what_is_held_in_registers(H, oracle, 3000, dual)
+
+
+@pytest.mark.parametrize("dual", [0, 2])
+@pytest.mark.parametrize("tied,k", [(70000, 777), (20000, 3000), (17000, 16384)])
+def test_step_driver_with_ties_in_lists_too_long_for_the_registers(H, oracle, monkeypatch, dual, tied, k):
+    make = S.make_layer
+
+    def ties(w, want_values=True):
+        monkeypatch.setattr(S, "make_layer", make)
+        return _tied_layer(w, tied)
+
+    monkeypatch.setattr(S, "make_layer", ties)
+    test_step_driver_selects_at_the_edges_of_what_is_held_in_registers(H, oracle, k, dual, (90000, 71000, 16385, 0))
+
+
+@pytest.mark.parametrize("dual", [0, 2])
+def test_step_driver_with_the_1024_thread_form(H, oracle, dual):
+    """select_wg = 1024 in a step driver, which takes 512 threads by itself: single layers and pairs of them."""
+    H.hca_tune("select_wg", 1024)
+    test_step_driver_selects_at_the_edges_of_what_is_held_in_registers(H, oracle, 8000, dual)
