@@ -309,6 +309,40 @@ def test_topk_of_long_rows_by_a_sampled_key(B, kind, n):
             assert np.all(got[b, want:] == -7)
 
 
+@pytest.mark.parametrize("kind", ["normal", "outlier", "ties", "close", "masked", "nan", "tiny", "equal", "wide", "few",
+                                  "lowest nan"])
+@pytest.mark.parametrize("n,k", [(40961, 14400), (90000, 20000), (300001, 15000)])
+def test_topk_of_long_rows_beyond_the_sampled_key(B, kind, n, k):
+    """hca_topk in its histogram form: a k whose lists the sampled form could not hold in registers; short rows beside."""
+    rng = np.random.default_rng(n + len(kind))
+    lens = [n, n - 4099, 16000, 1, 0]
+    sel = np.full((5, n + 3), 9e9, np.float32)              # past the row's end: larger than anything in it
+    for b in range(5):
+        if kind == "few":
+            x = np.where(rng.random(lens[b]) < 0.99, np.finfo(np.float32).min, rng.standard_normal(lens[b]))
+        else:
+            x = _scores(kind, lens[b], rng) if lens[b] else 0
+        sel[b, :lens[b]] = x
+        if kind == "lowest nan" and lens[b]:
+            sel[b, :lens[b]].view(np.uint32)[::3] = 0xffffffff
+    shape = B.make_shape(5, 1, 1, n + 3)
+    dsel = torch.from_numpy(sel).cuda()
+    ws = torch.empty(B.hca_workspace_bytes(shape, k, 1), dtype=torch.uint8, device="cuda")
+    idx = torch.full((5, k), -7, dtype=torch.int32, device="cuda")
+    count = torch.full((5,), -7, dtype=torch.int32, device="cuda")
+    for again in range(2):                                  # the second time on the workspace as the first left it
+        B.hca_topk(shape, dsel, lens, k, idx, count, ws)
+    torch.cuda.synchronize()
+    got, c = idx.cpu().numpy(), count.cpu().numpy()
+    for b in range(5):
+        want = min(k, lens[b])
+        assert c[b] == want
+        key = _order_key(sel[b, :lens[b]]).astype(np.int64)
+        ref = np.sort(np.argsort(-key, kind="stable")[:want])
+        assert np.array_equal(got[b, :want], ref), f"row {b}"
+        assert np.all(got[b, want:] == -7)
+
+
 @pytest.mark.parametrize("kind", ["runs of 16", "runs of 64", "period"])
 @pytest.mark.parametrize("n,k", [(65536, 1024), (300000, 4096), (1048576, 4096)])
 def test_scores_that_resemble_their_neighbours_do_not_slow_the_long_rows(B, kind, n, k):
