@@ -389,8 +389,10 @@ __global__ __launch_bounds__(512) __attribute__((amdgpu_waves_per_eu(4))) void v
       // the second smallest
       auto cand = [&](uint32_t v) { return __uint_as_float(v) <= lim ? (v & 127u) : 255u; };
       uint32_t todo = cand(a1.lo) | cand(a1.hi) << 8 | cand(a2.lo) << 16 | cand(a2.hi) << 24;
-      const bool queue = !(S < 32768.f) || __uint_as_float(a3.lo) <= lim || __uint_as_float(a3.hi) <= lim;
-      if (queue) todo = 0xffffffffu;
+      // (a column past the last token holds a copy of that token, up to 127 of them, and has nothing to look up)
+      const bool real = tok0 + 32 * tt + col < T;
+      const bool queue = real && (!(S < 32768.f) || __uint_as_float(a3.lo) <= lim || __uint_as_float(a3.hi) <= lim);
+      if (queue || !real) todo = 0xffffffffu;
       uint64_t best = kAmNoKey;
       float x[DBAR];
       {
@@ -612,9 +614,9 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(4))) void v
     const bool upper = f1 < f0;
     const float S = x2 + cmax2;
     const float lim = am_limit(upper ? f1 : f0, x2, S);
-    // a second block within the limit, or values that say nothing
+    // a second block within the limit, or values that say nothing (and a token: past the last there are copies of it)
     const float next = am_min(am_min(__uint_as_float(p2[0]), __uint_as_float(p2[1])), am_max(f0, f1));
-    const bool queue = next <= lim || !(S < 32768.f);
+    const bool queue = mine < T && (next <= lim || !(S < 32768.f));
     // rows of a 32 x 32 result held by a half: 8 (j / 4) + 4 half + j % 4, j < 16; block 2 t + q has j = 8 q .. 8 q + 7
     const uint32_t blk = (upper ? p1[1] : p1[0]) & 15u;
     const int tile = (int)(blk >> 1) & (NT - 1), r0 = 16 * (int)(blk & 1u) + (upper ? 4 : 0);

@@ -515,6 +515,23 @@ def _passes_us(run, passes=20):
     return best
 
 
+@pytest.mark.parametrize("g,c,T,full,rows", [(64, 8192, 257, 384, 8), (64, 4096, 257, 384, 8), (32, 8192, 130, 256, 8),
+                                             (32, 256, 1800, 2048, 16)])
+def test_a_ragged_end_does_not_slow_the_assignment(B, g, c, T, full, rows):
+    """The matrix-core forms take tokens by the wave; the places past a block's last token hold copies of that token, which
+    must not be looked up one by one when it is one of the few that need the chain of every centroid (in one of a hundred
+    groups it is).  A ragged block may take a quarter longer than the full one."""
+    gen = torch.Generator(device="cuda").manual_seed(c + T)
+    cen = torch.randn(rows, g, c, 128 // g, generator=gen, device="cuda")
+    cb = B.make_codebook(g, c, cen)
+    k = torch.randn(1, rows, full, 128, generator=gen, device="cuda").half()
+    shape = B.make_shape(1, rows, rows, full)
+    pc = torch.zeros(B.hca_vq_pcache_bytes(shape, cb), dtype=torch.uint8, device="cuda")
+    part = k[:, :, :T].contiguous()
+    took = [_passes_us(lambda: B.hca_vq_assign(shape, cb, pc, x, x.shape[2], [0])) for x in (k, part)]
+    assert took[1] < 1.25 * took[0], f"{full} tokens {took[0]:.1f} us, {T} tokens {took[1]:.1f} us"
+
+
 @pytest.mark.parametrize("g,c,T", [(64, 1024, 8192), (64, 8192, 2048), (32, 4096, 4096)])
 def test_a_far_centroid_does_not_slow_the_assignment(B, g, c, T):
     """One centroid per group far from all keys (one that no training round ever moved, say) can win no token, so it must
