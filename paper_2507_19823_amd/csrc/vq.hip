@@ -1175,52 +1175,53 @@ __global__ __launch_bounds__(256) void vq_export_wide_kernel(int g, int64_t cap,
   out[(int64_t)row * cap * g + gid] = pcache[vq_wide_at(g, vq_tiles(cap), row, slot, i)];
 }
 
-// Whether fewer than 96 centroids go to vq_assign_small_c_kernel.  It works on whole sets of 2, 4 or 8 tiles, and each of its
-// workgroups takes its 18 - 33 us whatever it holds, so it wants a launch that fills the chip; the vector form's time
-// follows the work alone, and falls with the channels per centroid.  Measured speed-ups over the vector form, 8 KV heads,
-// work in 2^27 (token, KV head, group, centroid) combinations (in brackets):
-//   4 channels: c = 33  0.88 (0.5), 1.24 (1.0); c = 48  0.87 (0.5), 1.08 (0.75), 1.6 (1.5); c = 64  0.95 (0.5), 1.37 (1);
-//   c = 65  0.9 (0.7), 1.17 (1).  2 channels: c = 33  0.9 (0.7), 1.06 (1); c = 64  0.86 (0.5), 1.26 (1); c = 65  0.8 (0.7),
-//   1.04 (1).
-static bool assign_by_tiles(int g, int c, int64_t work, int64_t T) {
-  if (T < 256 || c <= 32) return false;
-  const int64_t unit = (int64_t)1 << 25;                    // a quarter of 2^27
-  return work >= (g == 32 && c <= 64 ? 3 : 4) * unit;
-}
-
-// Estimates in us of the vector form and of vq_assign_mfma_kernel, fitted to 500 sizes (none picked more than 6 % slower than
-// the better of the two).  A workgroup of the latter walks the codebook for up to 1024 tokens, two of them per compute unit
-// at a time; with few tokens most of its waves only help with the operands, and a launch of many (KV head, group) pairs is
-// faster in the vector form, whose waves take 64 tokens each.  Measured, mfma / vector: 8 rows, 32 groups, c = 8192, 9
-// tokens 0.25; 32 rows, 64 groups, 64 tokens: c = 257 1.66, 700 1.03, 1024 0.87; 128 rows, 64 groups, 64 tokens: c = 1024
-// 1.71, 2048 1.47; 128 tokens: 512 1.32, 1024 0.99; 256 tokens: 257 1.31, 400 0.98.
-static double vector_us(int rows, int g, int c, int64_t T) {
-  const double waves = (double)rows * g * (double)((T + 63) / 64);
+// More than 256 centroids: the shortlist always from 257 tokens on, below by estimates in us of the vector form and of
+// vq_assign_mfma_kernel, fitted to 500 such sizes (none picked more than 6 % slower than the better of the two).  A
+// workgroup of the latter walks the codebook for up to 1024 tokens, two of them per compute unit at a time; with few tokens
+// most of its waves only help with the operands, and a launch of many (KV head, group) pairs is faster in the vector form,
+// whose waves take 64 tokens each.  Measured, mfma / vector: 8 rows, 32 groups, c = 8192, 9 tokens 0.25; 32 rows, 64 groups,
+// 64 tokens: c = 257 1.66, 700 1.03, 1024 0.87; 128 rows, 64 groups, 64 tokens: c = 1024 1.71, 2048 1.47; 128 tokens: 512
+// 1.32, 1024 0.99; 256 tokens: 257 1.31, 400 0.98.
+static bool assign_by_shortlist(int rows, int g, int c, int64_t T) {
+  if (T > 256) return true;
+  const double pairs = (double)rows * g, waves = pairs * (double)((T + 63) / 64);
   const double alone = g == 64 ? 0.058 : 0.089, each = g == 64 ? 1.38e-5 : 1.99e-5;      // per centroid: one wave; per wave
-  return c * (waves * each > alone ? waves * each : alone);
-}
-static double shortlist_us(int rows, int g, int c, int64_t T) {
-  const double pairs = (double)rows * g, each = 0.0108 + 1.1e-5 * c;
-  if (pairs * (double)((T + 1023) / 1024) <= 420) return 420 * each * (1.0 + (T < 1024 ? T : 1024) / 940.0);    // one round
-  return (pairs > 420 ? pairs : 420) * each * (1.0 + T / 940.0);
+  const double vec = c * (waves * each > alone ? waves * each : alone);
+  const double mfma = (pairs > 420 ? pairs : 420) * (0.0108 + 1.1e-5 * c) * (1.0 + T / 940.0);
+  return mfma < vec;
 }
 
-// More than 256 centroids: the shortlist always from 257 tokens on, below by the estimates.  96 to 256: the least of three
-// estimates - the tiles' workgroups take 16 groups one after another, 25 or 35 us whatever there is to do, the vector form
-// all centroids of a group in a chain.  Per call, vector / tiles / shortlist, us, 8 rows, 32 groups: c = 256, 9 - 256 tokens
-// 27 / 34 / 10, 1000 28 / 34 / 14, 2000 43 / 35 / 20, 4000 71 / 35 / 34, 8000 122 / 42 / 62; c = 128, 256 tokens 15 / 25 / 10,
-// 1000 16 / 25 / 12, 2000 23 / 26 / 17, 4000 38 / 28 / 30; 64 groups, c = 256, 1000 32 / 36 / 21, 4000 98 / 44 / 66; 32 rows,
-// 64 groups, 64 tokens: c = 256 19 / - / 29, c = 128 11 / - / 25.  c = 64: 4000 22 / 21 / 27.
+// 33 to 256 centroids: the least of three estimates in us, each fitted to the form's own times at 3500 sizes (1 to 56 rows,
+// 33 to 256 centroids, 64 to 60 000 tokens; of 3187 calls above 13 us the pick is 6 % or more off the best form in 31 and 15 %
+// or more in 3).  The vector form takes all centroids of a group in a chain, per 64 tokens and group a wave: flat to four
+// waves per SIMD, a step at more than the eight that fit.  The tiles' and the shortlist's workgroups (16 groups of 256
+// tokens; one group of 1024) come in rounds of 256.  Per call, vector / tiles / shortlist, us: 8 rows, 32 groups, c = 256,
+// 256 tokens 27 / 34 / 10, 1000 28 / 34 / 14, 2000 43 / 35 / 20, 4000 71 / 35 / 34; c = 128, 1000 16 / 25 / 13, 4000 38 / 26
+// / 31; 64 groups, c = 96, 1500 20 / 24 / 30; c = 128, 1100 22 / 25 / 32; 1 row, 64 groups, c = 256, 9000 40 / 36 / 52; c = 33,
+// 4 rows, 32 groups, 33 000 44 / 48 / -; 32 rows, 64 groups, 64 tokens, c = 256 19 / - / 29.  The shortlist's single index
+// bytes crowd the L2s beyond a million of them (1 row, 32 groups, c = 256, 33 000 tokens 48, tiles 41; 8 rows 573 / 232), and
+// for fewer than 96 centroids it is never the best.
 enum class AssignForm { kVector, kTiles, kShortlist };
 static AssignForm assign_form(int rows, int g, int c, int64_t T) {
-  if (T <= 8) return AssignForm::kVector;
-  const double vec = vector_us(rows, g, c, T), mfma = shortlist_us(rows, g, c, T);
-  if (c > kAsCodewords) return T > 256 || mfma < vec ? AssignForm::kShortlist : AssignForm::kVector;
-  if (c < 96) return assign_by_tiles(g, c, T * rows * g * c, T) ? AssignForm::kTiles : AssignForm::kVector;
-  const double least = c <= 128 ? 22.0 : 31.0, work = 2.0 + 1e-6 * (double)rows * g * (double)T * (4.0 + 0.043 * c);
-  const double tiles = T < 256 ? 1e30 : work > least ? work : least;
-  // (beyond a million of them the shortlist's single index bytes crowd the L2s: 64 groups, c = 256, 33 000 x 8 573 us, tiles 232)
-  if (mfma < vec && mfma < tiles && (double)rows * g * (double)T <= 1.1e6) return AssignForm::kShortlist;
+  if (T <= 8 || c <= 32) return AssignForm::kVector;
+  if (c > kAsCodewords) return assign_by_shortlist(rows, g, c, T) ? AssignForm::kShortlist : AssignForm::kVector;
+  const bool four = g == 32;                                // channels per centroid, else two
+  const auto rounds = [](int64_t workgroups) { return (double)((workgroups + 255) / 256); };
+  const double w = (double)rows * g * (double)((T + 63) / 64) / 1024;                    // waves per SIMD
+  const double vec = four ? 3.6 + (c + 8.7) * (w <= 8 ? fmax(0.081, 0.0121 * w + 0.044) : w <= 64 ? 0.149 + 0.0126 * (w - 8) : 0.014 * w)
+                          : 4.0 + (c + 11.5) * (w <= 8 ? fmax(0.056, 0.0077 * w + 0.0386) : w <= 64 ? 0.115 + 0.0095 * (w - 8) : 0.0104 * w);
+  double tiles = 1e30, mfma = 1e30;
+  if (T >= 256) {
+    const double x = rounds((int64_t)rows * (g / 16) * ((T + 255) / 256));
+    if (c <= 64) tiles = four ? (x <= 8 ? 19.3 + 1.6 * x + 0.62 * x * x : 10.5 + 7.7 * x) : fmax(20.5, 10.5 + 5.5 * x);
+    else if (c <= 128) tiles = four ? fmax(26.0, 12.5 + 8.7 * x) : fmax(25.0, 13.0 + 7.6 * x);
+    else tiles = four ? fmax(35.5, 21.0 + 11.8 * x) : fmax(36.0, 20.5 + 11.5 * x);
+  }
+  if (c >= 96 && (int64_t)rows * g * T <= 1050000) {
+    const double x = rounds((int64_t)rows * g * ((T + 1023) / 1024)), part = T < 1024 ? (double)T / 1024 : 1.0, k = log2(c / 32.0);
+    mfma = four ? 6.0 + (3.8 + 1.2 * k) * x * (0.3 + 0.7 * part) : 6.5 + (3.8 + 1.3 * k) * x * (0.27 + 0.73 * part);
+  }
+  if (mfma < vec && mfma < tiles) return AssignForm::kShortlist;
   return tiles < vec ? AssignForm::kTiles : AssignForm::kVector;
 }
 

@@ -494,7 +494,8 @@ def test_bulk_assignment_equals_the_exhaustive_chain(B, g, c, G, T, rows):
 @pytest.mark.parametrize("g,c,G,T,rows", [
     (32, 96, 1, 9, 8), (32, 100, 4, 65, 2), (32, 128, 1, 1025, 8), (32, 129, 4, 2047, 8), (32, 255, 1, 257, 16),
     (32, 256, 1, 4000, 8), (64, 256, 4, 1023, 8), (64, 256, 1, 64, 8), (64, 96, 1, 300, 4), (64, 200, 4, 1024, 2),
-    (64, 256, 1, 64, 32), (32, 128, 1, 64, 64)])
+    (64, 256, 1, 64, 32), (32, 128, 1, 64, 64), (64, 96, 1, 1500, 8), (64, 128, 4, 1100, 8), (32, 160, 1, 3500, 8),
+    (64, 256, 1, 7500, 1), (64, 256, 1, 9000, 1), (32, 33, 1, 14000, 4), (64, 48, 1, 9000, 8)])
 def test_blocks_of_few_tokens_against_96_to_256_centroids(B, g, c, G, T, rows):
     """The shortlist form with one-byte and with two-byte indices, and the vector form on the other side of the line."""
     test_bulk_assignment_equals_the_exhaustive_chain(B, g, c, G, T, rows)
