@@ -1136,14 +1136,21 @@ int32_t launch_score(const Layout& L, const void* kcache, const void* q, const N
   if (nmax == 0) return HCA_OK;
   const int64_t nblocks = (nmax + L.tpb - 1) / L.tpb;
   const Tuning& tn = tune != nullptr ? *tune : tuning();
-  int64_t bpw = scan_blocks_per_wave(L.bits, nblocks * L.rows, 4);
-  if (bpw > 16) bpw = scan_blocks_per_wave(L.bits, nblocks * L.rows, 8);
+  // A little more than one round of long waves leaves a second round that is nearly empty, and this scan, with four blocks
+  // ahead, starts a wave cheaply: beyond one round 8 blocks per wave at 4 bits, 16 at 2 and from 512 Ki on.  Per scan, 32
+  // blocks and 8 ahead / 16 / 8, 4-bit, us: 130 Ki blocks 37.0 / 33.3 / 32.9, 140 Ki 37.7 / 37.5 / 34.8, 200 Ki 49.8 / 50.1 /
+  // 47.9, 300 Ki 73.6 / 72.8 / 71.0, 400 Ki - / 95.4 / 93.3, 560 Ki - / 130.5 / 131.6; 2-bit 130 Ki 43.8 / 38.7 / 42.1, 200
+  // Ki 57.6 / 56.1 / 59.3, 400 Ki 105.6 / 105.0 / 110, 1 Mi 254 / 250 / 265.
+  const int64_t total = nblocks * L.rows;
+  const bool rounds = tn.score_bpw == 0 && total > 4 * 1024 * 32;
+  int64_t bpw = !rounds ? scan_blocks_per_wave(L.bits, total, 4) : L.bits == 4 && total < 512 * 1024 ? 8 : 16;
+  if (bpw > 16) bpw = scan_blocks_per_wave(L.bits, total, 8);
   if (tn.score_bpw > 0) bpw = tn.score_bpw;
   if (bpw < kScoreBpwMin) bpw = kScoreBpwMin;
   if (bpw > kScoreBpwMax) bpw = kScoreBpwMax;
   // the deeper look-ahead pays for long waves (64 Ki blocks, 16 per wave: 4-bit 17.0 / 16.3 us, 2-bit 20.6 / 21.3) and sends
   // what is no multiple of it through the one-at-a-time tail
-  const int depth = tn.score_depth > 0 ? tn.score_depth : (bpw >= (L.bits == 4 ? 16 : 24) && bpw % 8 == 0 ? 8 : 4);
+  const int depth = tn.score_depth > 0 ? tn.score_depth : (!rounds && bpw >= (L.bits == 4 ? 16 : 24) && bpw % 8 == 0 ? 8 : 4);
   dim3 grid((unsigned)((nblocks + 4 * bpw - 1) / (4 * bpw)), (unsigned)L.rows);
   // every wave of the launch owns one stamp pair: the caller's buffer holds score_stamp_pairs() of them
   if (stamps != nullptr && (int64_t)grid.x * 4 * L.rows > score_stamp_pairs(L, nmax)) return HCA_ERR_CAPACITY;
