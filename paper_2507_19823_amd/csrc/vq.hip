@@ -1196,9 +1196,9 @@ static bool assign_by_shortlist(int rows, int g, int c, int64_t T) {
 // or more in 3).  The vector form takes all centroids of a group in a chain, per 64 tokens and group a wave: flat to four
 // waves per SIMD, a step at more than the eight that fit.  The tiles' and the shortlist's workgroups (16 groups of 256
 // tokens; one group of 1024) come in rounds of 256.  Per call, vector / tiles / shortlist, us: 8 rows, 32 groups, c = 256,
-// 256 tokens 27 / 34 / 10, 1000 28 / 34 / 14, 2000 43 / 35 / 20, 4000 71 / 35 / 34; c = 128, 1000 16 / 25 / 13, 4000 38 / 26
-// / 31; 64 groups, c = 96, 1500 20 / 24 / 30; c = 128, 1100 22 / 25 / 32; 1 row, 64 groups, c = 256, 9000 40 / 36 / 52; c = 33,
-// 4 rows, 32 groups, 33 000 44 / 48 / -; 32 rows, 64 groups, 64 tokens, c = 256 19 / - / 29.  The shortlist's single index
+// 256 tokens 27 / 34 / 12, 1000 27 / 35 / 14, 2000 41 / 35 / 20, 4000 69 / 36 / 34; c = 128, 1000 15 / 26 / 13, 4000 37 / 27
+// / 30; 64 groups, c = 96, 1500 20 / 25 / 30; c = 128, 1100 22 / 25 / 32; 1 row, 64 groups, c = 256, 9000 39 / 37 / 30; c = 33,
+// 4 rows, 32 groups, 33 000 44 / 49 / -; 32 rows, 64 groups, 64 tokens, c = 256 19 / - / 26.  The shortlist's single index
 // bytes crowd the L2s beyond a million of them (1 row, 32 groups, c = 256, 33 000 tokens 48, tiles 41; 8 rows 573 / 232), and
 // for fewer than 96 centroids it is never the best.
 enum class AssignForm { kVector, kTiles, kShortlist };
