@@ -74,8 +74,8 @@ const char* hca_version(void);
 /* Overrides a launch-shape knob for the per-call entry points (process-wide state, meant for tuning and
  * profiling sessions, not needed for correct results; a step driver takes its knobs from its own
  * hca_pipeline_desc instead and only starts from these).  Names: "gather_wgs", "gather_unroll", "score_bpw", "score_depth", "select_wg" (threads per workgroup of the
- * selection over the candidate lists of hca_score_topk: 1024 or 256, the keys in
- * registers either way; 0: 1024 for a call, 512 in a step driver, where it has to fit into the room that one finished
+ * selection over the lists that the scan of hca_score_topk leaves - rows that are selected from their scores, see there,
+ * have forms of their own -: 1024 or 256, the keys in registers either way; 0: 1024 for a call, 512 in a step driver, where it has to fit into the room that one finished
  * scan workgroup leaves; the launch for rows that needed a second scan always takes the 256 form when two layers are
  * selected by one launch),
  * "host_isa" (2: the hybrid value side's host threads use their AVX2 form even where the CPU has AVX-512; 0: the

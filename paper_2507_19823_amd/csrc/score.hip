@@ -886,27 +886,29 @@ int32_t launch_select_begin_rank_append(const Layout& L, int n, void* const kcac
   return HCA_OK;
 }
 
-// Slots to sample per row.  More samples give a tighter threshold: with m samples the scan lets through about
-// n r / m pairs per row, r as in the comment above.  The smallest of 8192 .. 65536 that keeps that estimate within
-// what the selection holds in LDS (16384 pairs, less a margin for the spread of the count).
-static bool sample_keeps_lists_short(int64_t nmax, int32_t k, int m) {
-  const double want = (double)(k < nmax ? k : nmax);
-  const double kappa = want * m / (double)(nmax > 0 ? nmax : 1);
+// The rank r of the threshold among m samples of a row, as in sample_rank_body, and whether the about n r / m slots above it
+// are what the selection holds in registers (16384 pairs, less a margin for the spread of the count).
+static double sample_threshold_rank(int64_t nmax, int32_t k, int m) {
+  const double kappa = (double)(k < nmax ? k : nmax) * m / (double)(nmax > 0 ? nmax : 1);
   const double root = 3.0 + sqrt(9.0 + kappa);
-  const double r = root * root;
-  return r < m && (double)nmax * r / m <= 14336.0;
+  return root * root;
 }
+static bool sampled_lists_held(int64_t nmax, double r, int m) { return (double)nmax * r / m <= 14336.0; }
+
+// Slots to sample per row: more samples give a tighter threshold.  The smallest of 8192 .. 65536 whose lists are held.
 int select_sample_count(int64_t nmax, int32_t k) {
   int m = 8192;
   for (; m < 65536; m *= 2) {
-    const double want = (double)(k < nmax ? k : nmax);
-    const double kappa = want * m / (double)(nmax > 0 ? nmax : 1);
-    const double root = 3.0 + sqrt(9.0 + kappa);
-    if (root * root >= m || sample_keeps_lists_short(nmax, k, m)) break;
+    const double r = sample_threshold_rank(nmax, k, m);
+    if (r >= m || sampled_lists_held(nmax, r, m)) break;
   }
   return m;
 }
-bool select_lists_fit(int64_t nmax, int32_t k) { return sample_keeps_lists_short(nmax, k, select_sample_count(nmax, k)); }
+bool select_lists_fit(int64_t nmax, int32_t k) {
+  const int m = select_sample_count(nmax, k);
+  const double r = sample_threshold_rank(nmax, k, m);
+  return r < m && sampled_lists_held(nmax, r, m);
+}
 
 // Blocks per wave of a scan over `total` blocks in all rows, a multiple of `step` (what a wave fetches at a time; blocks left
 // over go one by one): as many as make one round of the 1024 workgroups that the chip holds, up to 32.  Times per scan, us,

@@ -1122,9 +1122,9 @@ static int32_t launch_row_select(const float* vals, int64_t stride, int rows, in
 
 // ---------------------------------------------------------------------------------------
 // Top-k straight from the scan (Sec. 3.2): the selecting scan has left, per chunk and in slot order, the
-// (key, slot) pairs at or above the row's sampled threshold.  One workgroup per row strings the chunks' lists
-// together (in LDS when they fit) - the result is the row's candidates in ascending slot order -, runs the whole
-// radix select (12 + 10 + 10 bits) over it and writes the selected slots in ascending order:
+// (key, slot) pairs at or above the row's sampled threshold.  One workgroup per row takes the chunks' lists one behind
+// the other - the row's candidates in ascending slot order, their keys in registers when they fit -, runs the whole
+// radix select (12 + 10 + 10 bits) over them and writes the selected slots in ascending order:
 //   selected(j) = key_j > T  or  (key_j == T and #{i < j : key_i == T} < r_eq)
 //   position(j) = #{i < j : key_i > T} + min(#{i < j : key_i == T}, r_eq)
 // A row with fewer pairs than it has to select is marked for a second scan without threshold; `only_failed`
@@ -1568,7 +1568,7 @@ __device__ __forceinline__ void tk_resolve_pairs(ResolveShared<NT>& sh, const in
 // is the chain of passes and barriers.  8 rows of 14 Ki pairs, alone: 28 us with the pairs in 128 KiB of LDS, 21 so.
 // NT = 1024 is the quickest where the chip is free (2 Mi slots x 8, k = 8192: 172 -> 165 us for the call).  Beside a
 // running scan what counts is the room it needs: a scan workgroup has 128 registers and 33 KiB, four of them fill a compute
-// unit, and another launch's workgroup only gets in where one of them ends.  NT = 512 has 64 registers (two waves per SIMD)
+// unit, and another launch's workgroup only gets in where one of them ends.  NT = 512 has 64 registers, three spilled (two waves per SIMD)
 // and 23 KiB: 62 us from launch to end beside a scan where the 1024-thread form waited for the scan's end, 200 us; four
 // layers of 1 Mi tokens in a step driver 810 -> 720 us, eight 1315 -> 1087.  NT = 256 (48 us alone) is for launches that
 // nearly always find nothing to do.  All give the same result.
@@ -1934,9 +1934,8 @@ int32_t launch_select_finish_pair(const Layout& L, const void* const kcache[2], 
     const SelectOut so2[2] = {f[0].so, f[1].so};
     rc = launch_select_rescan_pair(L, kcache, q, nr, nmax, so2, st);
     if (rc != HCA_OK) return rc;
-    // the selection for rows that had to be scanned again - almost never any - in the four-wave form without an
-    // LDS stage: beside a running scan the 1024-thread form would wait for a compute unit to drain just to find
-    // that it has nothing to do
+    // the selection for rows that had to be scanned again - almost never any - in the four-wave form: beside a running
+    // scan the 1024-thread form would wait for a compute unit to drain just to find that it has nothing to do
     tk_resolve_emit_pair<256><<<2 * L.rows, 256, 0, st>>>(rs[0], rs[1], L.rows, L.n_kv_heads, k, true);
   }
   HCA_HIP(hipGetLastError());
