@@ -158,8 +158,8 @@ int32_t hca_topk_noalloc(const hca_shape* shape, const float* sel, const int64_t
  * than k pairs) is scanned a second time inside the same call - with a lower threshold that a count taken
  * during the first scan proves sufficient, else with none -, so the result never depends on the sample;
  * only the time does.  (Rows of 40 to 96 Ki are not scanned again: one workgroup lists such a row anew from the scores
- * already there, by a lower key, else whole - 0.2 to 0.4 ms - and the report and the monitor below count it as a second
- * scan.)
+ * already there, by a lower key, else whole - 0.03 or 0.3 ms more - and the report and the monitor below count it as a
+ * second scan.)
  *   workspace  device, hca_workspace_bytes(shape, k, 1) bytes
  * Errors: HCA_ERR_CAPACITY if k < 1, k > capacity, or a row holds more than 8 Mi resident slots. */
 int32_t hca_score_topk(const hca_shape* shape, const void* kcache, const void* q_f16, const int64_t* n_resident,
