@@ -666,6 +666,591 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(4))) void v
   }
 }
 
+// Thousands of centroids and enough tokens per workgroup: the same shortlist and the same winner, but each wave looks at
+// the few blocks of centroids that its tokens are near.  One workgroup of 16 waves = up to 16 Ki tokens x one group.
+//   Order.  Tokens and centroids are each put in the order of a nested grid of quantiles (cells_order): every channel in
+//   turn cuts each cell into equal parts, more parts where the spread is wider.  32 neighbours of that order lie close
+//   together: 32 tokens are one B operand, 32 centroids one block with a bounding box.  The sorted tokens live in registers
+//   (their numbers), the sorted centroids in LDS as (fp16, fp16 of twice the rest) per channel, 16 bytes at four channels,
+//   so that 8192 of them fit; |c|^2 / 2 is formed from the same bytes when a block is multiplied.
+//   Search, per 32 tokens: the distance from the tokens' box to every block's box (a lane has four blocks); the blocks at
+//   the least distance are multiplied; then each block whose distance does not exceed the worst token's upper bound is
+//   tested token by token (two blocks at once, one per half wave) and multiplied if it can still hold any token's winner.
+//   The products' accumulator starts from |x|^2 / 2, so the results are d(c) / 2 and the blocks' numbers in the low 8 bits
+//   cost 2^-15 of d, not of |x|^2.
+//   Errors, for S and s(c) as above: with p = hi^2 / 2 rounded to fp16 and q = fp16(rest of it + hi lo), the pieces lose at most
+//   2^-20.3 s(c) + 2^-21.3, sixteen additions 2^-17.6 s(c): E(c) = 2^-17.3 s(c) + 2^-21.3, and cells_limit takes 1.4 times that.
+//   A box can be passed over when its squared distance exceeds 1.002 times the upper bound 2.0002 m1 + 5e-5 S + 1e-6: gaps
+//   are fp16 differences (2^-11 each), boxes are rounded outwards, the chain's own error is 2^-20.
+//   The candidates' distances come from the two halves in LDS in packed fp16; only where the second best is within the
+//   error of that (one token in a hundred) does the exact chain decide.  Out-of-range tokens and those with three blocks of a half
+//   wave in question go through every centroid.
+// Per 32 normal tokens of 16 Ki against 8192 centroids 21 of 256 blocks are multiplied and 46 tested, of 1 Ki tokens 38 and
+// 93.  Bound by the issue of the vector ALU (three quarters of its slots): 1700 instructions per 32 tokens, 500 of them products
+// and their minima, 400 tests, 150 the two orderings, which take 64 us of the launch's 500 (38 with 2 Ki tokens).  16 Ki tokens x 8 KV heads,
+// c = 8192: 1140 us in vq_assign_mfma_kernel, 500 here; with the waves left to the order of age 560.
+constexpr int kCellTokens = 16384, kCellBins = 4096;
+
+__device__ __forceinline__ v2h cells_min(v2h a, v2h b) { return __builtin_elementwise_minimum(a, b); }
+__device__ __forceinline__ v2h cells_max(v2h a, v2h b) { return __builtin_elementwise_maximum(a, b); }
+__device__ __forceinline__ uint32_t cells_bits(v2h v) { return __builtin_bit_cast(uint32_t, v); }
+__device__ __forceinline__ v2h cells_pair(uint32_t v) { return __builtin_bit_cast(v2h, v); }
+
+// min over the 32 lanes of a half wave (every lane gets it); packed fp16
+template <int CTRL> __device__ __forceinline__ uint32_t cells_dpp(uint32_t v) {
+  return (uint32_t)__builtin_amdgcn_update_dpp((int)v, (int)v, CTRL, 0xf, 0xf, false);
+}
+template <class Op> __device__ __forceinline__ uint32_t cells_over_half(uint32_t v, Op op) {
+  v = op(v, cells_dpp<0xB1>(v));
+  v = op(v, cells_dpp<0x4E>(v));
+  v = op(v, cells_dpp<0x141>(v));
+  v = op(v, cells_dpp<0x140>(v));
+  const auto a = __builtin_amdgcn_permlane16_swap(v, v, false, false);
+  return op(a[0], a[1]);
+}
+
+__device__ __forceinline__ float cells_sum(float v) {
+  dpp_steps([&](auto&& shift) { v += __uint_as_float(shift(0u, __float_as_uint(v))); });
+  return __uint_as_float(wave_last(__float_as_uint(v)));
+}
+
+// Positions of n items in the order of the nested grid: item number i * 1024 + thread has channels value(i, d).  Cells of
+// a round are cut at exact ranks; inside a bin (a 16th to a 256th of the channel's softsign-scaled range) items stay in any order.
+// hist: twice kCellBins words of LDS, one histogram for even and one for odd rounds; the caller synchronises before reusing it.
+template <int P, int DBAR, class Value>
+__device__ __forceinline__ void cells_order(Value value, int n, const float (&mu)[DBAR], const float (&sd)[DBAR], uint32_t* hist,
+                                            uint32_t* s_wave, int (&pos)[P]) {
+  const int tid = threadIdx.x;
+  int nb[DBAR];
+  {
+    float v[DBAR];
+#pragma unroll
+    for (int d = 0; d < DBAR; ++d) { nb[d] = 0; v[d] = sd[d]; }
+    for (int cells = 32; cells < n; cells *= 2) {            // the widest channel is halved
+      float top = v[0];
+#pragma unroll
+      for (int d = 1; d < DBAR; ++d) top = fmaxf(top, v[d]);
+      bool done = false;
+#pragma unroll
+      for (int d = 0; d < DBAR; ++d)
+        if (!done && (v[d] >= top || d == DBAR - 1)) { ++nb[d]; v[d] *= 0.5f; done = true; }
+    }
+  }
+#pragma unroll
+  for (int i = 0; i < P; ++i) pos[i] = i * 1024 + tid;
+  int logn = 0;
+  bool first = true;
+  uint4* hz = reinterpret_cast<uint4*>(hist) + tid;          // this thread's bins of this round's histogram
+  uint4* hn = hz + kCellBins / 4;
+  hz[0] = uint4{0, 0, 0, 0};
+  hn[0] = uint4{0, 0, 0, 0};
+  __syncthreads();
+#pragma unroll
+  for (int d = 0; d < DBAR; ++d) {
+    const int bits = __builtin_amdgcn_readfirstlane(nb[d]);
+    if (bits == 0) continue;
+    const int lb = 12 - logn < 8 ? 12 - logn : 8;
+    const float half = 0.5f * (float)(1 << lb), last = (float)((1 << lb) - 1);
+    const float inv = sd[d] > 0.f ? __builtin_amdgcn_rcpf(sd[d]) : 0.f;
+    const float parts = (float)(1 << logn) / (float)((n + 31) >> 5);
+    uint32_t* bins = reinterpret_cast<uint32_t*>(hz - tid);
+    // four items at a time, so that their updates are in flight together
+#pragma unroll
+    for (int i0 = 0; i0 < P; i0 += 4) {
+      if (i0 * 1024 >= n) continue;
+      uint32_t key[4], rank[4];
+#pragma unroll
+      for (int u = 0; u < 4; ++u) {
+        const int i = i0 + u;
+        const float v = (value(i, d) - mu[d]) * inv;
+        const float f = fminf(fmaxf(fmaf(v * __builtin_amdgcn_rcpf(1.f + fabsf(v)), half, half), 0.f), last);
+        int node = first ? 0 : (int)((float)(pos[i] >> 5) * parts);      // cells are cut between 32s, which are never in two
+        node = node < (1 << logn) - 1 ? node : (1 << logn) - 1;
+        key[u] = (uint32_t)node << lb | (uint32_t)f;
+      }
+#pragma unroll
+      for (int u = 0; u < 4; ++u) {
+        rank[u] = 0;
+        if ((i0 + u) * 1024 + tid < n) rank[u] = atomicAdd(&bins[key[u]], 1u);
+      }
+#pragma unroll
+      for (int u = 0; u < 4; ++u) pos[i0 + u] = (int)(key[u] | rank[u] << 12);
+    }
+    __syncthreads();
+    uint4 a = hz[0];
+    const uint32_t own = a.x + a.y + a.z + a.w, inc = wave_scan_incl(own);
+    if ((tid & 63) == 63) s_wave[tid >> 6] = inc;
+    hn[0] = uint4{0, 0, 0, 0};                               // (read before the last barrier)
+    __syncthreads();
+    uint32_t run = inc - own, t;
+    {
+      const uint32_t before = wave_scan_incl((tid & 63) < 16 ? s_wave[tid & 15] : 0u);        // lane x: of waves 0 .. x
+      if (tid >= 64) run += (uint32_t)__builtin_amdgcn_readlane((int)before, __builtin_amdgcn_readfirstlane((tid >> 6) - 1));
+    }
+    t = a.x; a.x = run; run += t;
+    t = a.y; a.y = run; run += t;
+    t = a.z; a.z = run; run += t;
+    a.w = run;
+    hz[0] = a;
+    __syncthreads();
+#pragma unroll
+    for (int i0 = 0; i0 < P; i0 += 4) {
+      if (i0 * 1024 >= n) continue;
+#pragma unroll
+      for (int u = 0; u < 4; ++u)        // (past the last item: key and rank 0, a position nobody reads)
+        pos[i0 + u] = (int)(bins[pos[i0 + u] & (kCellBins - 1)] + ((uint32_t)pos[i0 + u] >> 12));
+    }
+    uint4* swap = hz;
+    hz = hn;
+    hn = swap;
+    logn += bits;
+    first = false;
+  }
+}
+
+// Mean and deviation of the items' channels.
+template <int P, int DBAR, class Value>
+__device__ __forceinline__ void cells_moments(Value value, int n, float (&mu)[DBAR], float (&sd)[DBAR], float* s_stat) {
+  const int tid = threadIdx.x;
+  if (tid < 2 * DBAR) s_stat[tid] = 0.f;
+  __syncthreads();
+#pragma unroll
+  for (int d = 0; d < DBAR; ++d) {
+    float a = 0.f, b = 0.f;
+#pragma unroll
+    for (int i = 0; i < P; ++i) {
+      if (i * 1024 >= n) continue;
+      const float v = i * 1024 + tid < n ? value(i, d) : 0.f;
+      a += v;
+      b = fmaf(v, v, b);
+    }
+    a = cells_sum(a);
+    b = cells_sum(b);
+    if ((tid & 63) == 0) { atomicAdd(&s_stat[2 * d], a); atomicAdd(&s_stat[2 * d + 1], b); }
+  }
+  __syncthreads();
+#pragma unroll
+  for (int d = 0; d < DBAR; ++d) {
+    mu[d] = s_stat[2 * d] / (float)n;
+    sd[d] = sqrtf(fmaxf(s_stat[2 * d + 1] / (float)n - mu[d] * mu[d], 0.f));
+  }
+}
+
+// As am_limit, of a value that is half a squared distance with a number in its low 8 bits.
+__device__ __forceinline__ float cells_bound(float m1, float S) { return am_max(fmaf(2.0002f, m1, fmaf(5e-5f, S, 1e-6f)), 0.f); }
+__device__ __forceinline__ float cells_limit(float m1, float x2, float S) {
+  const float d2 = cells_bound(m1, S);
+  const float near = 2.f * x2 + d2 + 2.f * __builtin_amdgcn_sqrtf(x2 * d2);
+  return m1 + (2.1f * (am_min(near, S) * 9e-6f + 7e-7f) + 6.6e-5f * fabsf(m1));
+}
+
+// LDS bytes: operands, their centroids' numbers, boxes; before that (tokens and centroids being ordered) the histogram and the token list.
+__host__ __device__ constexpr size_t cells_lds(int c, int dbar) {
+  const size_t pad = (size_t)(c + 31) / 32 * 32, need = pad * 4 * dbar + pad * 2 + pad / 32 * 4 * dbar;
+  return need > kCellBins * 8 + kCellTokens * 2 ? need : kCellBins * 8 + kCellTokens * 2;
+}
+
+template <int DBAR>
+__global__ __launch_bounds__(1024) void vq_assign_cells_kernel(int g, int c, int n_kv_heads, int rows, int64_t cap,
+                                                                const float* __restrict__ centroids,
+                                                                uint16_t* __restrict__ pcache,
+                                                                const uint16_t* __restrict__ k_new, int64_t T, int chunk,
+                                                                NRes nr, float* __restrict__ acc, int32_t* __restrict__ pos_out,
+                                                                NRes vrow0) {
+  constexpr int H = DBAR / 2;                                // dwords of a token's channels
+  constexpr int kTokPer = kCellTokens / 1024, kCenPer = 8, kBlkPer = 4;
+  typedef uint32_t op_t __attribute__((ext_vector_type(DBAR)));        // hi pairs, then pairs of twice the rest
+  extern __shared__ __align__(16) unsigned char lds_raw[];
+  __shared__ float s_stat[2 * DBAR];
+  constexpr uint32_t kQueue = 512;
+  __shared__ uint32_t s_cmax, s_done, s_queued;
+  __shared__ uint16_t s_queue[kQueue];
+  __shared__ uint32_t s_wave[16];
+  __shared__ uint8_t s_ids[16 * 256 + 32];                   // each wave's list of blocks (stale entries are blocks too)
+  // workgroup x serves row x % rows: with eight rows all groups of a row, which share its tokens' lines, run on one die
+  const int row = blockIdx.x % rows, rest = blockIdx.x / rows;
+  const int grp = rest % g;
+  const int64_t first = (int64_t)(rest / g) * chunk;
+  const int n = (int)(T - first < chunk ? T - first : chunk);
+  const int tid = threadIdx.x, lane = tid & 63, w = tid >> 6;
+  const int col = lane & 31, kb = lane >> 5;
+  const int b = row / n_kv_heads;
+  const float* cg = centroids + ((int64_t)(row % n_kv_heads) * g + grp) * c * DBAR;
+  const uint16_t* keys = k_new + ((int64_t)row * T + first) * kHeadDim + grp * DBAR;
+  const int cpad = (c + 31) & ~31, nblk = cpad >> 5;
+  op_t* s_op = reinterpret_cast<op_t*>(lds_raw);
+  uint16_t* s_perm = reinterpret_cast<uint16_t*>(lds_raw + (size_t)cpad * sizeof(op_t));
+  op_t* s_box = reinterpret_cast<op_t*>(lds_raw + (size_t)cpad * (sizeof(op_t) + 2));    // lower corner, upper corner
+  uint32_t* hist = reinterpret_cast<uint32_t*>(lds_raw);
+  uint16_t* s_list = reinterpret_cast<uint16_t*>(lds_raw + kCellBins * 8);
+  const int64_t slot0 = nr.n[b] + first;
+  if (grp == 0) {
+    for (int t = tid; t < n; t += 1024) {
+      if (acc != nullptr) acc[(int64_t)row * cap + slot0 + t] = 0.0f;
+      if (pos_out != nullptr) pos_out[(int64_t)row * cap + slot0 + t] = (int32_t)(vrow0.n[b] + first + t);
+    }
+  }
+  if (tid == 0) { s_cmax = 0; s_done = 0; s_queued = 0; }
+  for (int i = tid; i < 16 * 256 + 32; i += 1024) s_ids[i] = 0;
+  // the codebook's lines are asked for while the tokens are put in order
+  const float warm = cg[(size_t)tid * 32 < (size_t)c * DBAR ? tid * 32 : 0];
+  auto words_of = [&](int t, uint32_t (&xw)[H]) {
+    const uint16_t* src = keys + (int64_t)t * kHeadDim;
+#pragma unroll
+    for (int d = 0; d < H; ++d) xw[d] = (uint32_t)src[2 * d] | (uint32_t)src[2 * d + 1] << 16;
+  };
+
+  // the tokens' order: this wave takes the 32-token tiles tile_of(0), tile_of(1), ...; lane (col, kb) keeps the tokens of column col of
+  // its tiles 4 j + kb (low half of lst[j]) and 4 j + 2 + kb
+  const int tiles = (n + 31) >> 5, mine = (tiles + 15) >> 4;
+  auto tile_of = [&](int k) { return 16 * k + ((w + 5 * k) & 15); };
+  uint32_t lst[8];
+  {
+    uint32_t xw[kTokPer][H];
+    int pos[kTokPer];
+#pragma unroll
+    for (int i = 0; i < kTokPer; ++i)
+      words_of(i * 1024 + tid < n ? i * 1024 + tid : n - 1, xw[i]);
+    float mu[DBAR], sd[DBAR];
+    auto value = [&](int i, int d) { return h2f((xw[i][d >> 1] >> (16 * (d & 1))) & 0xffffu); };
+    cells_moments<kTokPer, DBAR>(value, n, mu, sd, s_stat);
+    cells_order<kTokPer, DBAR>(value, n, mu, sd, hist, s_wave, pos);
+#pragma unroll
+    for (int i = 0; i < kTokPer; ++i)
+      if (i * 1024 + tid < n) s_list[pos[i]] = (uint16_t)(i * 1024 + tid);
+    __syncthreads();
+#pragma unroll
+    for (int j = 0; j < 8; ++j) {
+      lst[j] = 0;
+      if (4 * j < mine) {
+        const int p0 = tile_of(4 * j + kb) * 32 + col, p1 = tile_of(4 * j + 2 + kb) * 32 + col;
+        lst[j] = (uint32_t)s_list[p0 < n ? p0 : n - 1] | (uint32_t)s_list[p1 < n ? p1 : n - 1] << 16;
+      }
+    }
+    __syncthreads();
+  }
+  asm volatile("" ::"v"(warm));
+  {
+    float cv[kCenPer][DBAR];
+    int pos[kCenPer];
+    float most = 0.f;
+#pragma unroll
+    for (int i = 0; i < kCenPer; ++i) {
+      const int ci = i * 1024 + tid < c ? i * 1024 + tid : c - 1;
+      float nn = 0.f;
+#pragma unroll
+      for (int d = 0; d < DBAR; ++d) { cv[i][d] = cg[(int64_t)ci * DBAR + d]; nn = fmaf(cv[i][d], cv[i][d], nn); }
+      most = nn < INFINITY ? fmaxf(most, nn) : INFINITY;     // not finite or not a number: no token is in range
+    }
+    most = wave_max_nonneg(most);
+    if (lane == 0) atomicMax(&s_cmax, __float_as_uint(most));
+    float mu[DBAR], sd[DBAR];
+    auto value = [&](int i, int d) { return cv[i][d]; };
+    cells_moments<kCenPer, DBAR>(value, c, mu, sd, s_stat);
+    cells_order<kCenPer, DBAR>(value, c, mu, sd, hist, s_wave, pos);
+    __syncthreads();
+#pragma unroll
+    for (int i = 0; i < kCenPer; ++i) {
+      if (i * 1024 + tid < c) {
+        op_t o;
+#pragma unroll
+        for (int d = 0; d < H; ++d) {
+          const _Float16 h0 = am_f16(cv[i][2 * d]), h1 = am_f16(cv[i][2 * d + 1]);
+          o[d] = cells_bits(v2h{h0, h1});
+          o[H + d] = cells_bits(v2h{am_f16(2.f * (cv[i][2 * d] - (float)h0)), am_f16(2.f * (cv[i][2 * d + 1] - (float)h1))});
+        }
+        const int last = pos[i] == c - 1 ? cpad : pos[i] + 1;          // the last one also fills up its block
+        for (int p = pos[i]; p < last; ++p) {
+          s_op[p] = o;
+          s_perm[p] = (uint16_t)(i * 1024 + tid);
+        }
+      }
+    }
+    __syncthreads();
+  }
+  // the two halves of a channel as one number (2^-21.6 of it off the centroid)
+  auto channel = [&](const op_t& o, int d) {
+    const v2h hi = cells_pair(o[d >> 1]), lo = cells_pair(o[H + (d >> 1)]);
+    return fmaf((float)lo[d & 1], 0.5f, (float)hi[d & 1]);
+  };
+  for (int blk = 2 * w + kb; blk < nblk + (nblk & 1); blk += 32) {
+    const op_t o = s_op[(blk < nblk ? blk : nblk - 1) * 32 + col];
+    op_t box;
+#pragma unroll
+    for (int d = 0; d < H; ++d) {
+      v2h lo, hi;
+#pragma unroll
+      for (int e = 0; e < 2; ++e) {                          // corners rounded outwards: 2^-10 covers fp16 and the halves
+        const float v = channel(o, 2 * d + e), slack = fmaf(fabsf(v), 9.765625e-4f, 9.5367431640625e-7f);
+        lo[e] = am_f16(v - slack);
+        hi[e] = am_f16(v + slack);
+      }
+      box[d] = cells_over_half(cells_bits(lo), [](uint32_t a, uint32_t z) { return cells_bits(cells_min(cells_pair(a), cells_pair(z))); });
+      box[H + d] = cells_over_half(cells_bits(hi), [](uint32_t a, uint32_t z) { return cells_bits(cells_max(cells_pair(a), cells_pair(z))); });
+    }
+    if (col == 0 && blk < nblk) s_box[blk] = box;
+  }
+  __syncthreads();
+  const float cmax2 = __uint_as_float(s_cmax);
+  // squared distance between [alo, ahi] and a box, per channel pair in fp16
+  const v2h zero2 = {(_Float16)0.f, (_Float16)0.f};
+  auto gap2 = [&](const uint32_t (&alo)[H], const uint32_t (&ahi)[H], const op_t& box) {
+    float s = 0.f;
+#pragma unroll
+    for (int d = 0; d < H; ++d) {
+      const v2h q = cells_max(cells_max(cells_pair(box[d]) - cells_pair(ahi[d]), cells_pair(alo[d]) - cells_pair(box[H + d])), zero2);
+      s = __builtin_amdgcn_fdot2(q, q, s, false);
+    }
+    return s;
+  };
+  op_t mybox[kBlkPer];                                       // of blocks lane, lane + 64, ...
+#pragma unroll
+  for (int i = 0; i < kBlkPer; ++i) mybox[i] = s_box[lane + 64 * i < nblk ? lane + 64 * i : nblk - 1];
+  const v2h kS = kb ? v2h{(_Float16)0.5f, (_Float16)0.5f} : zero2, kO = kb ? zero2 : v2h{(_Float16)1.f, (_Float16)1.f};
+  uint32_t number = 255;
+  asm volatile("" : "+v"(number));
+  uint32_t turn[4];
+#pragma unroll
+  for (int j = 0; j < 4; ++j) turn[j] = (uint32_t)(j + col) & 3u;
+
+  auto put = [&](int t, int win) { pcache[vq_wide_at(g, vq_tiles(cap), row, slot0 + t, grp)] = (uint16_t)win; };
+  auto exhaust = [&](int t) {                                // by the whole wave
+    const int win = am_exhaustive<DBAR, 64>(keys + (int64_t)t * kHeadDim, cg, c, lane);
+    if (lane == 0) put(t, win);
+  };
+  auto token_of = [&](int k) {                               // of this column in tile k of the wave (4 j .. 4 j + 3: lst[0])
+    const Halves h = halves_of(k & 2 ? lst[0] >> 16 : lst[0] & 0xffffu);
+    return (int)(k & 1 ? h.hi : h.lo);
+  };
+  int tok = 0;
+  uint32_t xw[H];
+  if (mine > 0) {
+    tok = token_of(0);
+    words_of(tok, xw);
+  }
+  for (int k = 0; k < mine; ++k) {
+    const int t = tok;
+    uint32_t x01[H];
+#pragma unroll
+    for (int d = 0; d < H; ++d) x01[d] = xw[d];
+    if (k + 1 < mine) {                                      // the next tile's channels
+      if (((k + 1) & 3) == 0) {
+#pragma unroll
+        for (int j = 0; j < 7; ++j) lst[j] = lst[j + 1];
+      }
+      tok = token_of(k + 1);
+      words_of(tok, xw);
+    }
+    const bool real = tile_of(k) * 32 + col < n;
+    if (tile_of(k) >= tiles) continue;
+    // waves behind the workgroup's average go first: left to the order of age, the last wave of a SIMD ends alone
+    uint32_t done = 0;
+    if (lane == 0) done = atomicAdd(&s_done, 1u);
+    if (16u * (uint32_t)k < (uint32_t)__builtin_amdgcn_readfirstlane((int)done)) __builtin_amdgcn_s_setprio(2);
+    else __builtin_amdgcn_s_setprio(0);
+    float x2 = 0.f;
+#pragma unroll
+    for (int d = 0; d < H; ++d) x2 = __builtin_amdgcn_fdot2(cells_pair(x01[d]), cells_pair(x01[d]), x2, false);
+    const float S = x2 + cmax2;
+    const bool in = S < 32768.f;
+    float m1 = INFINITY, m2 = INFINITY, m3 = INFINITY;
+    if (__builtin_amdgcn_ballot_w64(in) != 0) {
+      v8h bop;
+      {
+        const v2h one = {(_Float16)1.f, (_Float16)1.f};
+        v2h r[4] = {zero2, zero2, zero2, zero2};
+#pragma unroll
+        for (int d = 0; d < H; ++d) {
+          r[d] = kb ? one : -cells_pair(x01[d]);
+          r[H + d] = kb ? one : cells_pair(x01[d]) * v2h{(_Float16)-0.5f, (_Float16)-0.5f};
+        }
+        bop = v8h{r[0][0], r[0][1], r[1][0], r[1][1], r[2][0], r[2][1], r[3][0], r[3][1]};
+      }
+      const float hx = 0.5f * x2;
+      const v16f start = {hx, hx, hx, hx, hx, hx, hx, hx, hx, hx, hx, hx, hx, hx, hx, hx};
+      auto multiply = [&](const op_t& o, int blk) {
+        v2h r[4] = {zero2, zero2, zero2, zero2};
+#pragma unroll
+        for (int d = 0; d < H; ++d) {                        // k block 0: hi, 2 lo; k block 1: hi^2 / 2 in two pieces, with hi lo
+          const v2h hi = cells_pair(o[d]), lo = cells_pair(o[H + d]);
+          const v2h m = __builtin_elementwise_fma(hi, kS, kO);
+          r[d] = hi * m;
+          r[H + d] = __builtin_elementwise_fma(lo, m, __builtin_elementwise_fma(hi, m, -r[d]));
+        }
+        const v8h a = {r[0][0], r[0][1], r[1][0], r[1][1], r[2][0], r[2][1], r[3][0], r[3][1]};
+        const v16f d = __builtin_amdgcn_mfma_f32_32x32x16_f16(a, bop, start, 0, 0, 0);
+        float mm = am_min(d[14], d[15]);
+#pragma unroll
+        for (int j = 0; j < 14; j += 2) mm = am_min(am_min(mm, d[j]), d[j + 1]);
+        const float pk = am_number(mm, (uint32_t)blk, number);
+        m3 = __builtin_amdgcn_fmed3f(m2, m3, pk);
+        m2 = __builtin_amdgcn_fmed3f(m1, m2, pk);
+        m1 = am_min(m1, pk);
+      };
+      // blocks of this wave's list, from number `from` on, whose bits in `which` are set; each operand is read while the one
+      // before it is multiplied
+      const uint8_t* ids = s_ids + w * 256;
+      auto multiply_all = [&](int from, uint32_t which) {
+        const int mine = ids[from + (lane & 31)];
+        int blk = __builtin_amdgcn_readlane(mine, __builtin_ctz(which));
+        op_t o = s_op[blk * 32 + col];
+        for (;;) {
+          which &= which - 1;
+          const int after = which != 0 ? __builtin_amdgcn_readlane(mine, __builtin_ctz(which)) : blk;
+          const op_t next = s_op[after * 32 + col];
+          multiply(o, blk);
+          if (which == 0) break;
+          o = next;
+          blk = after;
+        }
+      };
+      // the tile's box, over the tokens in range
+      uint32_t tlo[H], thi[H];
+      float lb[kBlkPer];
+#pragma unroll
+      for (int d = 0; d < H; ++d) {
+        tlo[d] = cells_over_half(in ? x01[d] : 0x7bff7bffu, [](uint32_t a, uint32_t z) { return cells_bits(cells_min(cells_pair(a), cells_pair(z))); });
+        thi[d] = cells_over_half(in ? x01[d] : 0xfbfffbffu, [](uint32_t a, uint32_t z) { return cells_bits(cells_max(cells_pair(a), cells_pair(z))); });
+      }
+#pragma unroll
+      for (int i = 0; i < kBlkPer; ++i) lb[i] = gap2(tlo, thi, mybox[i]);
+      if (nblk <= 192) lb[3] = INFINITY;
+      if (nblk <= 128) lb[2] = INFINITY;
+      if (nblk <= 64) lb[1] = INFINITY;
+      const float least = __uint_as_float(wave_min(__float_as_uint(am_min(am_min(lb[0], lb[1]), am_min(lb[2], lb[3])))));
+      // the numbers of the blocks with lb in (low, high] into the wave's list, ascending; how many
+      auto list = [&](float low, float high) {
+        int count = 0;
+        __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
+#pragma unroll
+        for (int i = 0; i < kBlkPer; ++i) {
+          const bool in_list = lb[i] > low && lb[i] <= high && lane + 64 * i < nblk;
+          const uint64_t ball = __builtin_amdgcn_ballot_w64(in_list);
+          const int at = count + (int)__builtin_amdgcn_mbcnt_hi((uint32_t)(ball >> 32), __builtin_amdgcn_mbcnt_lo((uint32_t)ball, 0));
+          if (in_list) s_ids[w * 256 + at] = (uint8_t)(lane + 64 * i);
+          count += (int)__builtin_popcountll(ball);
+        }
+        __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
+        return count;
+      };
+      for (int count = list(-1.f, least), from = 0; from < count; from += 32)
+        multiply_all(from, count - from >= 32 ? ~0u : (1u << (count - from)) - 1u);
+      // twice: the blocks within half the distance of the worst token's bound, and, with that bound lowered by them, the others.
+      // Sixteen blocks are tested at a time, two per product of boxes and tokens
+      float low = least;
+      for (int round = 0; round < 2; ++round) {
+        float d2;
+        auto bound = [&]() {
+          const Halves h = halves_of(__float_as_uint(m1));
+          d2 = in ? 1.002f * cells_bound(am_min(__uint_as_float(h.lo), __uint_as_float(h.hi)), S) : 0.f;
+        };
+        bound();
+        const float high = __uint_as_float(wave_max(__float_as_uint(d2))) * (round == 0 ? 0.25f : 1.f);
+        const int count = list(low, high);
+        low = am_max(low, high);
+        for (int from = 0; from < count; from += 16) {
+          const int left = count - from;
+          uint32_t hits = 0;
+#pragma unroll
+          for (int half = 0; half < 2; ++half) {
+            if (8 * half >= left) continue;
+            op_t box[4];
+#pragma unroll
+            for (int u = 0; u < 4; ++u) box[u] = s_box[ids[from + 8 * half + 2 * u + kb]];
+#pragma unroll
+            for (int u = 0; u < 4; ++u) {
+              const uint64_t hit = __builtin_amdgcn_ballot_w64(gap2(x01, x01, box[u]) <= d2);
+              hits |= ((uint32_t)hit != 0 ? 1u : 0u) << (8 * half + 2 * u) | ((hit >> 32) != 0 ? 2u : 0u) << (8 * half + 2 * u);
+            }
+          }
+          if (left < 16) hits &= (1u << left) - 1u;
+          if (hits != 0) {
+            multiply_all(from, hits);
+            bound();
+          }
+        }
+      }
+    }
+
+    // candidates as in vq_assign_mfma_kernel: the smallest of each half, then the second smallest
+    const Halves a1 = halves_of(__float_as_uint(m1)), a2 = halves_of(__float_as_uint(m2)), a3 = halves_of(__float_as_uint(m3));
+    const float lim = cells_limit(am_min(__uint_as_float(a1.lo), __uint_as_float(a1.hi)), x2, S);
+    const uint32_t blocks = (a1.lo & 255u) | (a1.hi & 255u) << 8 | (a2.lo & 255u) << 16 | a2.hi << 24;
+    auto below = [&](uint32_t v) { return __uint_as_float(v) <= lim ? 1u : 0u; };
+    const bool queue = real && (!in || below(a3.lo) != 0 || below(a3.hi) != 0);
+    const uint32_t mask = queue || !real ? 0u : below(a1.lo) | below(a1.hi) << 1 | below(a2.lo) << 2 | below(a2.hi) << 3;
+    float bd = INFINITY, sd = INFINITY;
+    uint32_t bp = 0;
+    // rows of a 32 x 32 result held by a half: 8 (j / 4) + 4 half + j % 4, j < 16; this lane takes j = 8 kb .. (each
+    // lane begins with another one of four neighbours: they are on different banks)
+    auto place = [&](uint32_t which) { return ((blocks >> (8 * which)) & 255u) * 32 + 16 * kb + 4 * (which & 1u); };
+    for (uint32_t left = mask; __builtin_amdgcn_ballot_w64(left != 0) != 0;) {
+      if (left != 0) {
+        const uint32_t which = (uint32_t)__builtin_ctz(left), base = place(which);
+        left &= left - 1;
+#pragma unroll
+        for (int j = 0; j < 8; ++j) {
+          const op_t o = s_op[base + turn[j & 3] + 8 * (j >> 2)];
+          float dist = 0.f;
+#pragma unroll
+          for (int d = 0; d < H; ++d) {
+            const v2h e = __builtin_elementwise_fma(cells_pair(o[H + d]), v2h{(_Float16)-0.5f, (_Float16)-0.5f}, cells_pair(x01[d]) - cells_pair(o[d]));
+            dist = __builtin_amdgcn_fdot2(e, e, dist, false);
+          }
+          sd = __builtin_amdgcn_fmed3f(bd, sd, dist);
+          bp = dist < bd ? which * 8 + j : bp;
+          bd = am_min(bd, dist);
+        }
+      }
+    }
+    bp = place(bp >> 3) + ((bp + col) & 3u) + 2 * (bp & 4u);
+    const Halves hb = halves_of(__float_as_uint(bd)), hs = halves_of(__float_as_uint(sd)), hp = halves_of(bp);
+    const float b0 = __uint_as_float(hb.lo), b1 = __uint_as_float(hb.hi), best = am_min(b0, b1);
+    const float next = am_min(am_max(b0, b1), am_min(__uint_as_float(hs.lo), __uint_as_float(hs.hi)));
+    int win = s_perm[b1 < b0 ? hp.hi : hp.lo];
+    // what that leaves undecided: the differences are fp16, 2^-10 off, of halves 2^-20.9 |c| off the centroid: with r the
+    // distance, r^2 is off by less than 2^-9 r^2 + 2^-19.9 r (|x| + r) + 2^-23 r
+    const float ax = __builtin_amdgcn_sqrtf(x2), r = __builtin_amdgcn_sqrtf(best) + fmaf(ax, 9.5367431640625e-7f, 5.9604644775390625e-8f);
+    const bool close = mask != 0 && !(next - best > r * fmaf(ax, 2.9e-6f, fmaf(r, 4.9e-3f, 6e-7f)));
+    if (__builtin_amdgcn_ballot_w64(close) != 0) {
+      uint64_t key = kAmNoKey;
+      for (uint32_t left = close ? mask : 0u; __builtin_amdgcn_ballot_w64(left != 0) != 0;) {
+        if (left != 0) {
+          const uint32_t base = place((uint32_t)__builtin_ctz(left));
+          left &= left - 1;
+#pragma unroll
+          for (int j = 0; j < 8; ++j) {
+            const int ci = s_perm[base + (j & 3) + 8 * (j >> 2)];
+            float dist = 0.f;
+#pragma unroll
+            for (int d = 0; d < DBAR; ++d) {
+              const float e = h2f((x01[d >> 1] >> (16 * (d & 1))) & 0xffffu) - cg[(int64_t)ci * DBAR + d];
+              dist = fmaf(e, e, dist);
+            }
+            const uint64_t kk = am_key(dist, ci);
+            if (kk < key) key = kk;
+          }
+        }
+      }
+      const Halves kh = halves_of((uint32_t)(key >> 32)), kl = halves_of((uint32_t)key);
+      const uint64_t k0 = (uint64_t)kh.lo << 32 | kl.lo, k1 = (uint64_t)kh.hi << 32 | kl.hi;
+      if (close) win = (int)(uint32_t)(k0 < k1 ? k0 : k1);
+    }
+    if (kb == 0 && real && !queue) put(t, win);
+    // every centroid: at the end, shared by all waves, as far as the queue has room
+    uint32_t place_in_queue = kQueue;
+    if (queue && kb == 0) {
+      place_in_queue = atomicAdd(&s_queued, 1u);
+      if (place_in_queue < kQueue) s_queue[place_in_queue] = (uint16_t)t;
+    }
+    for (uint64_t left = __builtin_amdgcn_ballot_w64(queue && kb == 0 && place_in_queue >= kQueue); left != 0; left &= left - 1)
+      exhaust(__builtin_amdgcn_readlane(t, (int)__builtin_ctzll(left)));
+  }
+  __syncthreads();
+  const int queued = s_queued < kQueue ? (int)s_queued : (int)kQueue;
+  for (int e = w; e < queued; e += 16) exhaust(s_queue[e]);
+}
+
 // Few tokens per call (decode appends): one workgroup of four waves per (token, row, 4 / SPLIT groups).  SPLIT waves
 // share a group, each takes a part of its centroids and spreads it over its lanes (lane, lane + 64, ...; four distances
 // in flight per lane); the lanes' candidates, then the waves', are reduced by (distance, index): the smaller distance
@@ -1201,9 +1786,45 @@ static bool assign_by_shortlist(int rows, int g, int c, int64_t T) {
 // 4 rows, 32 groups, 33 000 44 / 49 / -; 32 rows, 64 groups, 64 tokens, c = 256 19 / - / 26.  The shortlist's single index
 // bytes crowd the L2s beyond a million of them (1 row, 32 groups, c = 256, 33 000 tokens 48, tiles 41; 8 rows 573 / 232), and
 // for fewer than 96 centroids it is never the best.
-enum class AssignForm { kVector, kTiles, kShortlist };
+enum class AssignForm { kVector, kTiles, kShortlist, kCells };
+
+// Tokens per workgroup of vq_assign_cells_kernel: as many workgroups as compute units where the blocks allow it.
+static int assign_cells_chunk(int rows, int g, int64_t T) {
+  const int64_t pairs = (int64_t)rows * g;
+  int64_t parts = pairs < 256 ? 256 / pairs : 1;
+  if ((T + parts - 1) / parts < 1024) parts = (T + 1023) / 1024;
+  const int64_t least = (T + kCellTokens - 1) / kCellTokens;
+  if (parts < least) parts = least;
+  return (int)align_up((T + parts - 1) / parts, 32);
+}
+
+// More than 256 centroids and tokens: vq_assign_cells_kernel against vq_assign_mfma_kernel by estimates in us, fitted to 600
+// sizes (1 to 49 rows, 1024 to 8192 centroids, 256 to 33 000 tokens; half of them within 2.5 %, nineteen in twenty within 8 %).  A
+// workgroup of the former pays for two orderings before its first token, and what it multiplies grows with less than the
+// codebook; the 4 % are for what the fit does not see.  Measured, mfma / cells: 8 rows, 32 groups, c = 8192: 1000 tokens
+// 105 / 95 us, 2000 166 / 118, 4000 298 / 196, 16 000 1169 / 500; c = 4096: 4000 164 / 148, 16 000 597 / 405; c = 2048:
+// 16 000 336 / 366; 24 rows, c = 8192: 1000 tokens 245 / 266; 64 groups, 8 rows: c = 8192, 512 178 / 75, 16 000 2700 / 540; c =
+// 2048: 512 38 / 47, 2000 104 / 80, 16 000 700 / 380.
+static bool assign_by_cells(int rows, int g, int c, int64_t T) {
+  const int chunk = assign_cells_chunk(rows, g, T);
+  const double pairs = (double)rows * g, n = (double)(T < chunk ? T : chunk) / 1000, k = (double)c / 1000;
+  const double rounds = ceil(pairs * (double)((T + chunk - 1) / chunk) / 256);
+  const double part = T < 1024 ? (double)T / 1024 : 1.0;
+  double turns = pairs * (double)((T + 1023) / 1024) / 512;
+  double cells, mfma;
+  if (g == 32) {
+    cells = 6.5 + rounds * (23.3 + 0.93 * k + 14.1 * n + 2.22 * n * sqrt(k) + 4.0 * sqrt(n) * k);
+    mfma = 11.5 + (turns > 0.56 ? turns : 0.56) * (8.2 + 17.1 * k) * (0.37 + 0.63 * part);
+  } else {
+    cells = 5.8 + rounds * (13.5 + 1.35 * k + 8.08 * n + 1.37 * n * sqrt(k) + 0.62 * sqrt(n) * k);
+    mfma = 11.3 + (turns > 0.62 ? turns : 0.62) * (6.3 + 19.0 * k) * (0.34 + 0.66 * part);
+  }
+  return 1.04 * cells < mfma;
+}
+
 static AssignForm assign_form(int rows, int g, int c, int64_t T) {
   if (T <= 8 || c <= 32) return AssignForm::kVector;
+  if (c > kAsCodewords && T > 256 && assign_by_cells(rows, g, c, T)) return AssignForm::kCells;
   if (c > kAsCodewords) return assign_by_shortlist(rows, g, c, T) ? AssignForm::kShortlist : AssignForm::kVector;
   const bool four = g == 32;                                // channels per centroid, else two
   const auto rounds = [](int64_t workgroups) { return (double)((workgroups + 255) / 256); };
@@ -1259,6 +1880,18 @@ int32_t launch_vq_assign(const Layout& L, int g, int c, const float* centroids, 
     else HCA_ASSIGN_SCN(2, false);
 #undef HCA_ASSIGN_SCN
 #undef HCA_ASSIGN_SC
+  } else if (form == AssignForm::kCells) {
+    const int chunk = assign_cells_chunk(L.rows, g, T);
+    const unsigned wgs = (unsigned)(L.rows * g * ((T + chunk - 1) / chunk));
+#define HCA_ASSIGN_CELLS(D)                                                                                           \
+  do {                                                                                                                \
+    static std::atomic<uint64_t> opted{0};                /* one per instantiation */                                 \
+    const int32_t rc = lds_opt_in(reinterpret_cast<const void*>(&vq_assign_cells_kernel<D>), (int)cells_lds(8192, D), &opted); \
+    if (rc != HCA_OK) return rc;                                                                                      \
+    vq_assign_cells_kernel<D><<<wgs, 1024, cells_lds(c, D), st>>>(g, c, L.n_kv_heads, L.rows, L.cap, centroids, (uint16_t*)pcache, kn, T, chunk, nr, acc_opt, pos_opt, vrow0); \
+  } while (0)
+    if (g == 32) HCA_ASSIGN_CELLS(4); else HCA_ASSIGN_CELLS(2);
+#undef HCA_ASSIGN_CELLS
   } else if (form == AssignForm::kShortlist) {
     // a block or a context: shortlist on the matrix cores, exact chain on the shortlist
     dim3 gm((unsigned)((T + 1023) / 1024), (unsigned)L.rows, (unsigned)g);

@@ -220,6 +220,56 @@ def test_blockwise_bulk_assign_equals_one_shot(B, oracle, g, c):
     assert np.array_equal(Pref[:, sample], oc.P[:, :len(sample)].astype(ref.idx_dtype()))
 
 
+# (g, c, batch, hkv, n): one token more than the smallest call of this form; codebooks that do not fill their last block of 32;
+# n one off a multiple of 32 and of 1024; one and several workgroups per (row, group), with a ragged last one; four
+# and two channels; more than 512 tokens left to the exhaustive chain in one workgroup (kind "far")
+@pytest.mark.parametrize("g,c,batch,hkv,n,kind", [(64, 8192, 1, 1, 257, "plain"), (64, 4100, 2, 1, 1025, "awkward"), (64, 8161, 1, 1, 2047, "awkward"),
+                                                  (32, 8192, 2, 4, 2049, "awkward"), (32, 8191, 1, 8, 3001, "skewed"),
+                                                  (32, 6000, 1, 8, 16001, "plain"), (32, 8192, 1, 3, 33001, "skewed"), (64, 4096, 1, 1, 16385, "skewed"),
+                                                  (64, 8192, 1, 1, 1500, "equal"), (64, 8192, 1, 1, 1500, "far")])
+def test_assign_by_cells_equals_short_blocks(B, g, c, batch, hkv, n, kind):
+    """Many tokens against thousands of centroids (both put in order of nested cells, only near blocks multiplied)
+    leave the indices that blocks of 200 tokens leave, which go through forms that look at every centroid: bit for
+    bit, with outlier channels, duplicate and neighbouring centroids, infinite, subnormal and out-of-range keys, keys
+    on a centroid, and all keys equal."""
+    rng = np.random.default_rng(g + c + n)
+    dbar = D // g
+    keys = rng.standard_normal((batch, hkv, n, g, dbar)).astype(np.float32)
+    cen = (rng.standard_normal((hkv, g, c, dbar)) * 1.1).astype(np.float32)
+    if kind == "skewed":
+        keys[..., 0] *= 8
+        cen[..., 0] *= 8
+        keys[:, :, : n // 3, :, 1] = keys[:, :, : n // 3, :, 0] * 0.5 + 0.01 * keys[:, :, : n // 3, :, 1]
+    if kind == "awkward":
+        cen[:, :, 7] = cen[:, :, 3]
+        cen[:, :, 40] = np.nextafter(cen[:, :, 41], np.float32(np.inf))
+        cen[:, :, 100:110] *= 9.0
+        cen[:, :, 110:120] *= 1e-3
+        cen[:, :, c - 1] = cen[:, :, c - 2]
+        cen[:, :, c // 2: c // 2 + 100] = cen[:, :, 200:300]
+        keys[:, :, 10] = 0.0
+        keys[:, :, 11] = 6e-8
+        keys[:, :, 12, :, 0] = np.inf
+        keys[:, :, 13, :, 0] = -np.inf
+        keys[:, :, 14] = 300.0
+        keys[:, :, 15, ::2] = -250.0
+        for t in range(20, 240):
+            keys[:, :, t] = cen[:, :, (t * 13) % c]
+    if kind == "equal":
+        keys[:] = keys[:, :, :1]
+    if kind == "far":
+        keys[:, :, : n // 2, 1::2] += 200.0
+    kt = torch.from_numpy(keys.reshape(batch, hkv, n, D).astype(np.float16))
+    one, blocks = (_State(B, batch, hkv, hkv, n + 40, g, c, cen, 1) for _ in range(2))
+    for st in (one, blocks):
+        st.assign(kt[:, :, :9])                                        # so that the block begins behind resident tokens
+    one.assign(kt[:, :, 9:])
+    for t in range(9, n, 200):
+        blocks.assign(kt[:, :, t:min(n, t + 200)])
+    torch.cuda.synchronize()
+    assert torch.equal(one.P, blocks.P) and torch.equal(one.pos, blocks.pos) and torch.equal(one.acc, blocks.acc)
+
+
 @pytest.mark.parametrize("g,c,G,n,k", [(32, 256, 4, 9000, 512), (64, 128, 4, 3001, 100), (32, 64, 2, 5000, 5000),
                                        (32, 256, 1, 700, 1), (32, 1024, 4, 6000, 300), (64, 512, 2, 2500, 2500),
                                        (32, 512, 4, 20000, 700)])     # the last: two index tiles, the second ragged
