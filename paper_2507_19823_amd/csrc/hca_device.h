@@ -257,6 +257,46 @@ __device__ __forceinline__ float score_tile2(const QOperand<2>& op, uint32_t c0,
   return (t0 + t1) * op.unscale;
 }
 
+// max of two finite floats (plain v_max_f32: the inputs are never NaN, so no canonicalisation)
+__device__ __forceinline__ float fmax_raw(float a, float b) {
+  float r;
+  asm("v_max_f32 %0, %1, %2" : "=v"(r) : "v"(a), "v"(b));
+  return r;
+}
+
+// max over the four 16-lane rows of a wave (the four query heads of a token), result on every lane
+__device__ __forceinline__ float max_over_heads(float x) {
+  const uint32_t xi = __float_as_uint(x);
+  const auto r16 = __builtin_amdgcn_permlane16_swap(xi, xi, false, false);   // rows {0,1} and {2,3}
+  const float m = fmax_raw(__uint_as_float(r16[0]), __uint_as_float(r16[1]));
+  const uint32_t mi = __float_as_uint(m);
+  const auto r32 = __builtin_amdgcn_permlane32_swap(mi, mi, false, false);   // halves
+  return fmax_raw(__uint_as_float(r32[0]), __uint_as_float(r32[1]));
+}
+
+// 16-byte load with the non-temporal hint: the code stream is read once per decode step and
+// should not displace anything in the caches.
+__device__ __forceinline__ uint4 load_stream16(const uint4* p) {
+  const v4i v = __builtin_nontemporal_load(reinterpret_cast<const v4i*>(p));
+  return uint4{(uint32_t)v.x, (uint32_t)v.y, (uint32_t)v.z, (uint32_t)v.w};
+}
+
+// All-gather over the four 16-lane rows of a wave: returns, on every lane, the values that the
+// lanes of the same column hold in rows 0..3.
+__device__ __forceinline__ uint4 allgather_rows(uint32_t v) {
+  const auto a = __builtin_amdgcn_permlane16_swap(v, v, false, false);        // [r0 r0 r2 r2], [r1 r1 r3 r3]
+  const auto b = __builtin_amdgcn_permlane32_swap(a[0], a[0], false, false);  // r0 everywhere, r2 everywhere
+  const auto c = __builtin_amdgcn_permlane32_swap(a[1], a[1], false, false);  // r1 everywhere, r3 everywhere
+  return uint4{b[0], c[0], b[1], c[1]};
+}
+
+// The float whose order key is `key`, or -inf for keys below those of all finite floats (0: "no threshold"):
+// v >= key_floor(key) <=> order_key(v) >= key for every finite v (-0 and +0 share a key and compare equal).
+__device__ __forceinline__ float key_floor(uint32_t key) {
+  if (key <= 0x007fffffu) return -INFINITY;
+  return __uint_as_float((key & 0x80000000u) ? (key & 0x7fffffffu) : ~key);
+}
+
 // ---- wave-wide scans and reductions by DPP: six dependent vector instructions where six __shfl_up or __shfl_xor go through
 // the LDS crossbar.  Called by all 64 lanes.  (With the workgroup scans reading the
 // waves' sums at once: cumulative-weight selection and attend over 8 x 500 003 tokens 157.4 -> 155.0 us, eviction 126.2 -> 124.9.)

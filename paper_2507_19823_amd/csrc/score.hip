@@ -10,39 +10,6 @@ namespace hca {
 
 struct NRes32 { int32_t n[kMaxBatch]; };   // row lengths as kernel arguments of the paired launches
 
-// max of two finite floats (plain v_max_f32: the inputs are never NaN, so no canonicalisation)
-__device__ __forceinline__ float fmax_raw(float a, float b) {
-  float r;
-  asm("v_max_f32 %0, %1, %2" : "=v"(r) : "v"(a), "v"(b));
-  return r;
-}
-
-// max over the four 16-lane rows of a wave (the four query heads of a token), result on every lane
-__device__ __forceinline__ float max_over_heads(float x) {
-  const uint32_t xi = __float_as_uint(x);
-  const auto r16 = __builtin_amdgcn_permlane16_swap(xi, xi, false, false);   // rows {0,1} and {2,3}
-  const float m = fmax_raw(__uint_as_float(r16[0]), __uint_as_float(r16[1]));
-  const uint32_t mi = __float_as_uint(m);
-  const auto r32 = __builtin_amdgcn_permlane32_swap(mi, mi, false, false);   // halves
-  return fmax_raw(__uint_as_float(r32[0]), __uint_as_float(r32[1]));
-}
-
-// 16-byte load with the non-temporal hint: the code stream is read once per decode step and
-// should not displace anything in the caches.
-__device__ __forceinline__ uint4 load_stream16(const uint4* p) {
-  const v4i v = __builtin_nontemporal_load(reinterpret_cast<const v4i*>(p));
-  return uint4{(uint32_t)v.x, (uint32_t)v.y, (uint32_t)v.z, (uint32_t)v.w};
-}
-
-// All-gather over the four 16-lane rows of a wave: returns, on every lane, the values that the
-// lanes of the same column hold in rows 0..3.
-__device__ __forceinline__ uint4 allgather_rows(uint32_t v) {
-  const auto a = __builtin_amdgcn_permlane16_swap(v, v, false, false);        // [r0 r0 r2 r2], [r1 r1 r3 r3]
-  const auto b = __builtin_amdgcn_permlane32_swap(a[0], a[0], false, false);  // r0 everywhere, r2 everywhere
-  const auto c = __builtin_amdgcn_permlane32_swap(a[1], a[1], false, false);  // r1 everywhere, r3 everywhere
-  return uint4{b[0], c[0], b[1], c[1]};
-}
-
 // The same all-gather through the LDS crossbar (ds_bpermute_b32: no LDS memory is touched): four reads with the
 // byte addresses of lanes column + 16 r, r = 0..3.  The scan is bound by vector-ALU issue, the LDS pipe is idle.
 struct RowGather {
@@ -68,13 +35,6 @@ __device__ __forceinline__ float max_over_heads_scatter(float z0, float z1, floa
   const auto r = __builtin_amdgcn_permlane16_swap(__float_as_uint(m02), __float_as_uint(m13), false, false);
   // r[0] = [m02.r0 m13.r0 m02.r2 m13.r2], r[1] = [m02.r1 m13.r1 m02.r3 m13.r3]
   return fmax_raw(__uint_as_float(r[0]), __uint_as_float(r[1]));
-}
-
-// The float whose order key is `key`, or -inf for keys below those of all finite floats (0: "no threshold"):
-// v >= key_floor(key) <=> order_key(v) >= key for every finite v (-0 and +0 share a key and compare equal).
-__device__ __forceinline__ float key_floor(uint32_t key) {
-  if (key <= 0x007fffffu) return -INFINITY;
-  return __uint_as_float((key & 0x80000000u) ? (key & 0x7fffffffu) : ~key);
 }
 
 // Work split: grid.y = row, grid.x = chunk; a workgroup has 4 waves and each wave scans `bpw`
@@ -521,6 +481,7 @@ __device__ __forceinline__ void sample_rank_body(const int64_t n, int32_t k, F&&
     if (tid == 0) { sp[0] = 0xffffffffu; sp[1] = 0; sp[2] = 0xffffffffu; }
     return;
   }
+  if (!EXACT && tid == 0) sp[3] = 0;
   // f(key) for every sample: the first kKeep per thread are kept, any others read again for each pass, 8 in flight
   constexpr int kKeep = EXACT ? 16 : 8;
   uint32_t first[kKeep];

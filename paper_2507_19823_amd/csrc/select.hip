@@ -1575,7 +1575,8 @@ __device__ __forceinline__ void tk_resolve_pairs(ResolveShared<NT>& sh, const in
 template <int NT>
 __device__ __forceinline__ void tk_resolve_emit_body(const int64_t chunk, const int nchunks, const int64_t want,
                                                      const SelectOut& so, const int32_t k, int32_t* __restrict__ idx,
-                                                     int32_t* __restrict__ count, const bool only_failed, const int row) {
+                                                     int32_t* __restrict__ count, const bool only_failed, const int row,
+                                                     const bool mark = true) {
   constexpr int PER = 1024 / NT;           // chunks per thread
   __shared__ ResolveShared<NT> sh;
   auto& off = sh.off;
@@ -1610,6 +1611,7 @@ __device__ __forceinline__ void tk_resolve_emit_body(const int64_t chunk, const 
     m[2] = total > m[2] ? total : m[2];
     if (total < (uint32_t)want) m[3] += 1;
   }
+  if (total < (uint32_t)want && !mark) return;              // (other workgroups of the launch scan the row again)
   if (total < (uint32_t)want) {
     // the sampled threshold was too high: scan the row again, with the second threshold if the first scan counted
     // enough slots at or above it, else without one
@@ -1639,6 +1641,152 @@ __global__ __launch_bounds__(NT) __attribute__((amdgpu_waves_per_eu(NT == 512 ? 
                                                       int32_t* __restrict__ count, bool only_failed) {
   tk_resolve_emit_body<NT>(chunk, nchunks, sr.want[blockIdx.x / n_kv_heads], so, k, idx, count, only_failed,
                            (int)blockIdx.x);
+}
+
+// The last launch of hca_score_topk's selecting scan, one 1024-thread workgroup per row and behind them some for rows that have
+// to be scanned again.  A row whose lists hold enough is selected by its own workgroup.  The others add up every row's
+// counts and return, nearly always, as none falls short; those that do are dealt out among them and scanned again, a share of the chunks each, into
+// the same lists, whose new counts go to the room of the samples (the first ones still have readers), and the one that
+// finishes last makes the selection.  Nobody waits for anybody, so any number may be resident.  One launch where a selection,
+// a second scan and a second selection were three, the last two of them 9 us to find that they have nothing to do.
+// What the shares write goes through to memory (a release fence would write the whole L2 back, 512 times over: 12.5 ms for eight
+// rows of 1 Mi); only the last one fences.  The row totals are not added up by the scan: its workgroups' atomics, on eight
+// dies, took it from 106 to 490 us.  A call, three launches / this one, us: 4 x 128 Ki x 8 rows 109.9 / 106.1 (step), 2 Mi x 8, 2-bit 149 /
+// 145.5; with one of 8 rows misread 200 000 slots 75 / 67, 1 Mi 246 / 229; with all eight 85 / 92, 312 / 347.
+template <typename T>
+__device__ __forceinline__ void store_through(T* p, T v) { __hip_atomic_store(p, v, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT); }
+
+template <int BITS>
+__device__ __forceinline__ void rescan_chunks(const Layout& L, const uint8_t* __restrict__ kcache, const uint16_t* __restrict__ q,
+                                              const int64_t n, const int row, const uint32_t from_key, const int chunk_blocks,
+                                              const int nchunks, const int first, const int step, const SelectOut& so,
+                                              uint32_t* __restrict__ counts) {
+  constexpr int U = 4, kTpb = BITS == 4 ? 16 : 32;          // (eight blocks ahead: 8 rows of 1 Mi 347 -> 417 us)
+  __shared__ QShared qs;
+  __shared__ uint32_t wn[2][16];
+  const int lane = threadIdx.x & 63, w = __builtin_amdgcn_readfirstlane((int)(threadIdx.x >> 6));
+  const int t = lane & 15, hd = lane >> 4;
+  const int nblocks = (int)((n + kTpb - 1) / kTpb);
+  const uint4* cptr = reinterpret_cast<const uint4*>(kcache + (int64_t)row * L.codes_row_bytes()) + lane;
+  const uint32_t* mptr = reinterpret_cast<const uint32_t*>(kcache + L.meta_off + (int64_t)row * L.meta_row_bytes()) +
+                         (BITS == 4 ? 4 * t + hd : 2 * (16 * (hd >> 1) + t) + (hd & 1));
+  const float from = key_floor(from_key);
+  const bool head_live = hd < L.gqa;
+  QOperand<BITS> op;
+  load_query(q, row, L.gqa, L.group, &qs);
+  build_operand<BITS>(&qs, &op);
+  int turn = 0;
+  for (int c = first; c < nchunks; c += step) {
+    const int b1 = (c + 1) * chunk_blocks < nblocks ? (c + 1) * chunk_blocks : nblocks;
+    uint2* dst = so.lists + (int64_t)row * so.row_entries + (int64_t)c * chunk_blocks * kTpb;
+    uint32_t base = 0;
+    for (int b0 = c * chunk_blocks; b0 < b1; b0 += 16 * U) {            // U consecutive blocks per wave, in wave order
+      const int wb = b0 + U * w;
+      uint4 wv[U];
+      uint32_t mw[U];
+#pragma unroll
+      for (int u = 0; u < U; ++u) {
+        const int blk = wb + u < b1 ? wb + u : b1 - 1;
+        wv[u] = load_stream16(&cptr[(int64_t)blk * 64]);
+        mw[u] = __builtin_nontemporal_load(&mptr[(int64_t)blk * 64]);
+      }
+      float v[U];
+      uint32_t mine = 0;
+      auto hit = [&](int u) {
+        return hd < kTpb / 16 && wb + u < b1 && (int64_t)(wb + u) * kTpb + 16 * hd + t < n && v[u] >= from;
+      };
+#pragma unroll
+      for (int u = 0; u < U; ++u) {
+        const uint4 mv = allgather_rows(mw[u]);
+        if constexpr (BITS == 4) {
+          const float z = score_block4(op, wv[u], mv);       // (by all lanes: they hold parts of each other's products)
+          v[u] = max_over_heads(head_live ? z : -INFINITY);
+        } else {
+          const float z0 = score_tile2(op, wv[u].x, wv[u].y, uint2{mv.x, mv.y});
+          const float z1 = score_tile2(op, wv[u].z, wv[u].w, uint2{mv.z, mv.w});
+          const float m0 = max_over_heads(head_live ? z0 : -INFINITY), m1 = max_over_heads(head_live ? z1 : -INFINITY);
+          v[u] = hd == 0 ? m0 : m1;
+        }
+        mine += (uint32_t)__popcll(__builtin_amdgcn_ballot_w64(hit(u)));
+      }
+      if (lane == 0) wn[turn][w] = mine;
+      __syncthreads();
+      uint32_t at = base;
+#pragma unroll
+      for (int x = 0; x < 16; ++x) {
+        const uint32_t s = wn[turn][x];
+        at += x < w ? s : 0;
+        base += s;
+      }
+      turn ^= 1;                                            // (written again two barriers from here)
+#pragma unroll
+      for (int u = 0; u < U; ++u) {
+        const uint64_t m = __builtin_amdgcn_ballot_w64(hit(u));
+        if (hit(u))
+          store_through(reinterpret_cast<uint64_t*>(dst + at + (uint32_t)__popcll(m & ((1ull << lane) - 1))),
+                        (uint64_t)((wb + u) * kTpb + 16 * hd + t) << 32 | order_key(v[u]));
+        at += (uint32_t)__popcll(m);
+      }
+    }
+    if (threadIdx.x == 0) store_through(&counts[c], base);
+  }
+}
+
+constexpr int kFinishRows = 64;         // rows that tk_finish takes
+
+template <int BITS>
+__global__ __launch_bounds__(1024) __attribute__((amdgpu_waves_per_eu(4))) void tk_finish(
+    Layout L, const uint8_t* __restrict__ kcache, const uint16_t* __restrict__ q, NRes nr, int64_t chunk, int nchunks, SelRows sr,
+    SelectOut so, int32_t k, int32_t* __restrict__ idx, int32_t* __restrict__ count) {
+  __shared__ uint32_t wsum[16], s_flag;
+  __shared__ uint32_t s_total[kFinishRows];
+  const int tid = threadIdx.x, rows = L.rows;
+  auto want_of = [&](int row) { return sr.want[row / L.n_kv_heads]; };
+  if ((int)blockIdx.x < rows) {
+    const int row = (int)blockIdx.x;
+    tk_resolve_emit_body<1024>(chunk, nchunks, want_of(row), so, k, idx, count, false, row, false);
+    return;
+  }
+  const int lane = tid & 63, w = tid >> 6;
+  for (int row = w; row < rows; row += 16) {                // a wave per row, all of its counts in flight
+    uint32_t n[kSelectMaxChunks / 64], sum = 0;
+#pragma unroll
+    for (int i = 0; i < kSelectMaxChunks / 64; ++i) {
+      const int c = i * 64 + lane;
+      n[i] = c < nchunks ? so.ncand[(int64_t)row * kSelectMaxChunks + c] : 0u;
+    }
+#pragma unroll
+    for (int i = 0; i < kSelectMaxChunks / 64; ++i) sum += n[i];
+    sum = wave_sum(sum);
+    if (lane == 0) s_total[row] = sum;
+  }
+  __syncthreads();
+  const bool lacks = lane < rows && want_of(lane) > 0 && s_total[lane] < (uint32_t)want_of(lane);
+  uint64_t failed = __builtin_amdgcn_ballot_w64(lacks);
+  if (failed == 0) return;
+  // the failed rows in turn: this workgroup is number `at` of the `of` that share its row
+  const int helpers = (int)gridDim.x - rows, h = (int)blockIdx.x - rows, many = (int)__builtin_popcountll(failed);
+  const int at = h / many, of = (helpers - h % many + many - 1) / many;
+  for (int x = h % many; x > 0; --x) failed &= failed - 1;
+  const int row = (int)__builtin_ctzll(failed);
+  // the second threshold if the first scan counted enough slots at or above it, else none
+  const uint32_t above = tid < nchunks ? so.n1[(int64_t)row * kSelectMaxChunks + tid] : 0u;
+  uint32_t all;
+  block_scan_excl<16>(above, wsum, &all);
+  const uint32_t from = all >= (uint32_t)want_of(row) ? so.spec[4 * row + 2] : 0u;
+  SelectOut again = so;
+  again.ncand = so.samples;                                 // [rows][kSelectMaxChunks]: a row has at least 8192 samples
+  rescan_chunks<BITS>(L, kcache, q, nr.n[row / L.n_kv_heads], row, from, (int)(chunk / L.tpb), nchunks, at, of, so,
+                      again.ncand + (int64_t)row * kSelectMaxChunks);
+  __builtin_amdgcn_s_waitcnt(0);                            // this wave's pairs and counts are in memory
+  __syncthreads();
+  if (tid == 0) s_flag = atomicAdd(&so.spec[4 * row + 3], 1u) == (uint32_t)(of - 1);
+  __syncthreads();
+  if (s_flag == 0) return;
+  __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "agent");
+  if (tid == 0) { so.spec[4 * row] = from; so.spec[4 * row + 1] = 2; }          // (2: the counts are with the samples)
+  __syncthreads();
+  tk_resolve_emit_body<1024>(chunk, nchunks, want_of(row), again, k, idx, count, true, row);
 }
 
 // The last launch of a selection from scores: the chunks' lists hold the slots of the keys above the sampled key K
@@ -1912,6 +2060,23 @@ int32_t launch_select_finish(const Layout& L, const void* kcache, const void* q,
   return HCA_OK;
 }
 
+// The same in one launch, for a call that has the chip for itself (beside another stream's scan the workgroups for failed
+// rows would wait for room; there the step driver's three small launches stay): a workgroup per compute unit in all.  With
+// two per unit the last of them begin when the first have ended, and the launch took 26 us for 16.
+static int32_t launch_select_finish_call(const Layout& L, const void* kcache, const void* q, const NRes& nr, int64_t nmax,
+                                         int32_t k, int32_t* idx, int32_t* count, void* ws, hipStream_t st) {
+  FusedPlan f;
+  const int32_t rc = fused_plan(L, nr, nmax, k, ws, &f);
+  if (rc != HCA_OK) return rc;
+  const int64_t chunks = (int64_t)f.nchunks * L.rows;
+  if (L.rows > kFinishRows) return launch_select_finish(L, kcache, q, nr, nmax, k, idx, count, ws, st, 1024);
+  const unsigned wgs = (unsigned)(L.rows + (chunks < 256 - L.rows ? chunks : 256 - L.rows));       // one per compute unit
+  const auto form = L.bits == 4 ? tk_finish<4> : tk_finish<2>;
+  form<<<wgs, 1024, 0, st>>>(L, (const uint8_t*)kcache, (const uint16_t*)q, nr, f.chunk, f.nchunks, f.sr, f.so, k, idx, count);
+  HCA_HIP(hipGetLastError());
+  return HCA_OK;
+}
+
 // The same for the two layers of a paired scan launch: three launches for the two of them.
 int32_t launch_select_finish_pair(const Layout& L, const void* const kcache[2], const void* const q[2], const NRes nr[2],
                                   const int64_t nmax[2], int32_t k, int32_t* const idx[2], int32_t* const count[2],
@@ -2005,7 +2170,9 @@ int32_t launch_score_topk(const Layout& L, const void* kcache, const void* q, co
   if (rc != HCA_OK) return rc;
   rc = launch_select_begin(L, kcache, q, nr, nmax, k, ws, st, nullptr);
   if (rc != HCA_OK) return rc;
-  return launch_select_finish(L, kcache, q, nr, nmax, k, idx, count, ws, st, tuning().select_wg > 0 ? tuning().select_wg : 1024);
+  if (tuning().select_wg > 0 && tuning().select_wg != 1024)
+    return launch_select_finish(L, kcache, q, nr, nmax, k, idx, count, ws, st, tuning().select_wg);
+  return launch_select_finish_call(L, kcache, q, nr, nmax, k, idx, count, ws, st);
 }
 
 // What the last fused selection on this workspace did, per row: pairs that passed the threshold of the scan that
@@ -2015,13 +2182,14 @@ __global__ __launch_bounds__(256) void tk_select_report(TopkWs t, int nchunks, i
   __shared__ uint32_t wsum[4];
   const int row = blockIdx.x;
   uint32_t v = 0;
-  for (int c = threadIdx.x; c < nchunks; c += 256) v += t.ncand[(int64_t)row * kMaxChunks + c];
+  const uint32_t* counts = t.spec[4 * row + 1] == 2 ? t.samples : t.ncand;      // (of a second scan by tk_finish: with the samples)
+  for (int c = threadIdx.x; c < nchunks; c += 256) v += counts[(int64_t)row * kMaxChunks + c];
   v = wave_sum(v);
   if ((threadIdx.x & 63) == 0) wsum[threadIdx.x >> 6] = v;
   __syncthreads();
   if (threadIdx.x == 0) {
     candidates[row] = (int32_t)(wsum[0] + wsum[1] + wsum[2] + wsum[3]);
-    rescanned[row] = (int32_t)t.spec[4 * row + 1];
+    rescanned[row] = t.spec[4 * row + 1] != 0;
   }
 }
 

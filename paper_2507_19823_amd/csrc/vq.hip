@@ -680,7 +680,7 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(4))) void v
 //   cost 2^-15 of d, not of |x|^2.
 //   Errors, for S and s(c) as above: with p = hi^2 / 2 rounded to fp16 and q = fp16(rest of it + hi lo), the pieces lose at most
 //   2^-20.3 s(c) + 2^-21.3, sixteen additions 2^-17.6 s(c): E(c) = 2^-17.3 s(c) + 2^-21.3, and cells_limit takes 1.4 times that.
-//   A box can be passed over when its squared distance exceeds 1.002 times the upper bound 2.0002 m1 + 5e-5 S + 1e-6: gaps
+//   A box can be passed over when its squared distance exceeds 1.002 times the upper bound that cells_bound gives: gaps
 //   are fp16 differences (2^-11 each), boxes are rounded outwards, the chain's own error is 2^-20.
 //   The candidates' distances come from the two halves in LDS in packed fp16; only where the second best is within the
 //   error of that (one token in a hundred) does the exact chain decide.  Out-of-range tokens and those with three blocks of a half
@@ -808,38 +808,41 @@ __device__ __forceinline__ void cells_order(Value value, int n, const float (&mu
   }
 }
 
-// Mean and deviation of the items' channels.
+// Mean and mean distance from it of the items' channels (a few items far away hardly move either).
 template <int P, int DBAR, class Value>
 __device__ __forceinline__ void cells_moments(Value value, int n, float (&mu)[DBAR], float (&sd)[DBAR], float* s_stat) {
   const int tid = threadIdx.x;
   if (tid < 2 * DBAR) s_stat[tid] = 0.f;
   __syncthreads();
+  auto mean = [&](int at, auto&& of, float (&out)[DBAR]) {
 #pragma unroll
-  for (int d = 0; d < DBAR; ++d) {
-    float a = 0.f, b = 0.f;
+    for (int d = 0; d < DBAR; ++d) {
+      float a = 0.f;
 #pragma unroll
-    for (int i = 0; i < P; ++i) {
-      if (i * 1024 >= n) continue;
-      const float v = i * 1024 + tid < n ? value(i, d) : 0.f;
-      a += v;
-      b = fmaf(v, v, b);
+      for (int i = 0; i < P; ++i) {
+        if (i * 1024 >= n) continue;
+        a += i * 1024 + tid < n ? of(value(i, d), d) : 0.f;
+      }
+      a = cells_sum(a);
+      if ((tid & 63) == 0) atomicAdd(&s_stat[at + d], a);
     }
-    a = cells_sum(a);
-    b = cells_sum(b);
-    if ((tid & 63) == 0) { atomicAdd(&s_stat[2 * d], a); atomicAdd(&s_stat[2 * d + 1], b); }
-  }
-  __syncthreads();
+    __syncthreads();
 #pragma unroll
-  for (int d = 0; d < DBAR; ++d) {
-    mu[d] = s_stat[2 * d] / (float)n;
-    sd[d] = sqrtf(fmaxf(s_stat[2 * d + 1] / (float)n - mu[d] * mu[d], 0.f));
-  }
+    for (int d = 0; d < DBAR; ++d) out[d] = s_stat[at + d] / (float)n;
+  };
+  mean(0, [&](float v, int) { return v; }, mu);
+  mean(DBAR, [&](float v, int d) { return fabsf(v - mu[d]); }, sd);
 }
 
 // As am_limit, of a value that is half a squared distance with a number in its low 8 bits.
-__device__ __forceinline__ float cells_bound(float m1, float S) { return am_max(fmaf(2.0002f, m1, fmaf(5e-5f, S, 1e-6f)), 0.f); }
+// Upper bound of the squared distance: first with S, then with what that says of the centroid, |c|^2 <= 2 |x|^2 + 2 d, however
+// far away others are.
+__device__ __forceinline__ float cells_bound(float m1, float x2, float S) {
+  const float d0 = am_max(fmaf(2.0002f, m1, fmaf(5e-5f, S, 1e-6f)), 0.f);
+  return am_max(fmaf(2.0002f, m1, fmaf(5e-5f, am_min(S, fmaf(3.f, x2, 2.f * d0)), 1e-6f)), 0.f);
+}
 __device__ __forceinline__ float cells_limit(float m1, float x2, float S) {
-  const float d2 = cells_bound(m1, S);
+  const float d2 = cells_bound(m1, x2, S);
   const float near = 2.f * x2 + d2 + 2.f * __builtin_amdgcn_sqrtf(x2 * d2);
   return m1 + (2.1f * (am_min(near, S) * 9e-6f + 7e-7f) + 6.6e-5f * fabsf(m1));
 }
@@ -1142,7 +1145,7 @@ __global__ __launch_bounds__(1024) void vq_assign_cells_kernel(int g, int c, int
         float d2;
         auto bound = [&]() {
           const Halves h = halves_of(__float_as_uint(m1));
-          d2 = in ? 1.002f * cells_bound(am_min(__uint_as_float(h.lo), __uint_as_float(h.hi)), S) : 0.f;
+          d2 = in ? 1.002f * cells_bound(am_min(__uint_as_float(h.lo), __uint_as_float(h.hi)), x2, S) : 0.f;
         };
         bound();
         const float high = __uint_as_float(wave_max(__float_as_uint(d2))) * (round == 0 ? 0.25f : 1.f);

@@ -156,6 +156,38 @@ def test_a_sample_that_misleads_still_gives_the_exact_set(H, oracle, bits, gs, t
     assert resc[0] == 1 and k <= cand[0] <= n      # the row went through the second scan
 
 
+@pytest.mark.parametrize("bits,gs,tpb", [(4, 32, 16), (2, 64, 32)])
+@pytest.mark.parametrize("lens", [(230001, 100003, 1), (150000, 230001, 0)])
+def test_several_rows_of_a_call_need_the_second_scan(H, oracle, bits, gs, tpb, lens):
+    """Three sequences of two KV heads: the first head's rows are misread as above and scanned again, some with the second
+    threshold and some whole, the other head's are not, and rows shorter than k, of one slot or of none are among them; twice
+    on one workspace, as the second scan's counts live where the next call's samples go."""
+    n, k, batch, hkv = 230001, 3000, 3, 2
+    w = S.Workload("mis3", 97 + bits, batch, 2 * hkv, hkv, n, bits, gs, k)
+    d = S.make_layer(w, want_values=False)
+    q = d["q"].clone()
+    q[:, 1] = q[:, 0]                                          # head 0's two query heads are equal
+    g = torch.Generator().manual_seed(6)
+    keys = d["keys"].clone()
+    for b in range(batch):
+        nblocks = max(1, (lens[b] + tpb - 1) // tpb)
+        Sn = min(nblocks, 8192 // tpb)
+        sampled = torch.zeros((n + tpb - 1) // tpb, dtype=torch.bool)
+        sampled[(torch.arange(Sn, dtype=torch.int64) * nblocks) // Sn] = True
+        inside = sampled.repeat_interleave(tpb)[:n]
+        u = torch.rand(n, generator=g)
+        mid = torch.rand(n, generator=g) < (0.05 if b != 1 else 0.0)
+        proj = torch.where(inside, 1.0 + u, torch.where(mid, 1.85 + 0.1 * u, -1.0 - u))
+        keys[b, 0] = (proj[:, None] * q[b, 0].float()[None, :] / q[b, 0].float().norm() ** 2 * 40.0
+                      + 0.02 * torch.randn(n, 128, generator=g)).to(torch.float16)
+    for _ in range(2):
+        cand, resc = _run(H, oracle, w, keys, q, lens, k)
+        for b in range(batch):
+            if lens[b] > 8192:
+                assert resc[2 * b] == 1 and resc[2 * b + 1] == 0
+                assert k <= cand[2 * b] <= lens[b] and cand[2 * b + 1] >= k
+
+
 def test_second_scan_with_the_deeper_threshold(H, oracle):
     """As above, but the slots outside the sampled blocks score only a little lower than those inside: the first
     threshold (inside the sampled blocks' range) lets too few through, the second one - the 8r-th largest sample,
