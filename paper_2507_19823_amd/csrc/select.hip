@@ -772,9 +772,18 @@ __device__ __forceinline__ float key_to_float(uint32_t key) {
 // ---------------------------------------------------------------------------------------
 // Top-k of short rows in one launch: a 1024-thread workgroup holds a whole row of scores in registers, KPT values per
 // thread, wave w owning the KPT * 64 consecutive slots from w * KPT * 64 on (a wave's x-th load is 64 of them, so slot
-// order is (wave, x, lane)).  hca_topk per call, 8 rows of 4 Ki / 16 Ki / 40 Ki slots, 1024 to select: 8 / 12 / 23 us, against
-// 31 / 35 / 39 us for the six launches over the whole chip; with the scan in front (hca_score_topk), 4 Ki / 16 Ki / 32 Ki: 13 / 19 / 28 against
-// 39 / 39 / 41 us for sample, threshold, selecting scan, selection and its fall-back pair.
+// order is (wave, x, lane)).  hca_topk per call, 8 rows of 4 Ki / 16 Ki / 32 Ki / 40 Ki slots, 1024 to select: 8 / 10.6 / 13 /
+// 14.5 us (8 / 11.7 / 18.2 / 21.8 without step 0), against 31 / 35 / - / 39 us for the six launches over the whole chip; with
+// the scan in front (hca_score_topk), 4 Ki / 16 Ki / 32 Ki: 13 / 18 / 23 (13 / 19 / 28 without step 0) against 39 / 39 / 41 us
+// for sample, threshold, selecting scan, selection and its fall-back pair.
+//   0. Rows of 8 Ki slots and more of which few are wanted: a bound below which the want-th largest lies almost never, from
+//      1024 samples (their rank-th largest, rank = the expected one + 3.5 standard deviations + 6; binned as in step 1).  The
+//      values at or above it - 2000 of 32 Ki for 1024 to select - go to a list in LDS in slot order, and only those, four per
+//      thread, are binned, ranked and placed.  A list longer than kSiftMax, or more than kRankMax of it in the bin of the
+//      last one (ties): steps 2 and 3 over the whole row, with the bound as the end of the bins; too short a list, or a
+//      NaN anywhere: all steps.  At most kSiftMax - 512 are expected: at that end of the rule one row in fifty is too long (18.7
+//      -> 22 us; 13.3 where none is), of 2000 none.  8 rows of 32 Ki slots, 1024 to select: 11.4 us in the kernel - loads
+//      and window 3.5, bound 1, list 4, the rest 3 - for 16.5; beyond kSiftMax the list's own steps would grow.
 //   1. smallest and largest value per wave; 4096 bins spread evenly over a window in which most of the row lies, so that
 //      neither the counters are fought over nor most of them stay empty (the keys of one row share their exponent bits).
 //      The window reaches a quarter of its width beyond the fourth smallest and the fourth largest of the waves' extremes:
@@ -788,9 +797,17 @@ __device__ __forceinline__ float key_to_float(uint32_t key) {
 //      else by radix levels over the distance from the bin's smallest key (ties, one far outlier).
 //   3. the ordered emit, positions by ballot:  selected(j) = key_j > T  or  (key_j == T and fewer than r_eq equals
 //      before it), position(j) = #{i < j : key_i > T} + min(#{i < j : key_i == T}, r_eq).
-// Bound by the issue of one compute unit's vector ALUs, about 40 instructions per slot.  The row in LDS with rolled
+// Steps 1 to 3 are bound by the issue of one compute unit's vector ALUs, about 40 instructions per slot, with step 0 about 13;
+// then the chain of its dozen barriers counts as much.  The row in LDS with rolled
 // loops instead of registers: 35.6 us per 32 Ki slots.
 constexpr int kRankMax = 512;
+constexpr int kSiftMax = 4096;
+constexpr uint32_t kSiftMin = 8192;
+// rank among 1024 samples, expected number of those among the wanted and a margin, whose value bounds the list of step 0
+__host__ __device__ __forceinline__ uint32_t sift_rank(uint32_t want, uint32_t n) {
+  const float mean = (float)want * 1024.0f / (float)n;
+  return (uint32_t)(mean + 3.5f * sqrtf(mean) + 6.0f);
+}
 
 struct RowSelectFused {      // what hca_score_topk keeps beside the result (null spec: a plain top-k)
   uint32_t* spec;
@@ -820,13 +837,15 @@ __device__ __forceinline__ float row16_min(float v) {
 }
 __device__ __forceinline__ float row16_max(float v) { return -row16_min(-v); }
 
-template <int KPT>
+template <int KPT, bool kSift>
 __global__ __launch_bounds__(1024) void tk_row_select(const float* __restrict__ vals, int64_t stride, int n_kv_heads,
                                                       SelRows sr, int32_t k, int32_t* __restrict__ idx,
                                                       int32_t* __restrict__ count, RowSelectFused fu) {
   __shared__ uint32_t h[kBins12], list[kRankMax], wsum[16], wlo[16], whi[16], wplain[16];
   __shared__ uint32_t s_bin, s_rem, s_cb, s_n, s_T, s_req, s_flags;
   __shared__ __align__(16) float s_win[8];
+  __shared__ __align__(16) float s_kept[kSift ? kSiftMax : 4];
+  __shared__ __align__(16) uint32_t s_slot[kSift ? kSiftMax : 4];
   const int row = blockIdx.x;
   const int tid = threadIdx.x, lane = tid & 63, wv = __builtin_amdgcn_readfirstlane(tid >> 6);
   const int64_t want64 = sr.want[row / n_kv_heads];
@@ -851,6 +870,14 @@ __global__ __launch_bounds__(1024) void tk_row_select(const float* __restrict__ 
   const uint32_t want = (uint32_t)want64;
   const float* v = vals + (int64_t)row * stride;
   uint32_t s0 = (uint32_t)wv * (KPT * 64) + (uint32_t)lane;
+  // the sample of step 0, one place in each of 1024 equal parts of the row
+  float sample = 0.0f;
+  const uint32_t rank = kSift ? sift_rank(want, n) : 0u;
+  const bool sift = kSift && n >= kSiftMin && rank * n <= (uint32_t)(kSiftMax - 512) * 1024u;
+  if (sift) {
+    const uint32_t from = ((uint32_t)tid * n) >> 10, part = n >> 10;
+    sample = v[from + ((((uint32_t)tid * 40503u) & 0xffffu) * part >> 16)];
+  }
   float f[KPT];                                             // (lanes past the row's end hold its last slot for now)
 #pragma unroll
   for (int x = 0; x < KPT; ++x) f[x] = v[s0 + x * 64 < n ? s0 + x * 64 : n - 1];
@@ -863,79 +890,70 @@ __global__ __launch_bounds__(1024) void tk_row_select(const float* __restrict__ 
   };
   for (int i = tid; i < kBins12; i += 1024) h[i] = 0;
   if (tid == 0) s_n = 0;
-  float vlo = INFINITY, vhi = -INFINITY;
+  float vlo = INFINITY, vhi = -INFINITY, from = 0.0f, scale = 0.0f;
   bool plain = true;                                        // no NaN and no +infinity
-#pragma unroll
-  for (int x = 0; x < KPT; ++x) {
-    vlo = fminf(vlo, f[x]);
-    vhi = fmaxf(vhi, f[x]);
-    plain = plain && f[x] < INFINITY;
-  }
-  vlo = wave_min(vlo);
-  vhi = wave_max(vhi);
-  plain = __builtin_amdgcn_ballot_w64(!plain) == 0;
-  if (lane == 0) { wlo[wv] = __float_as_uint(vlo); whi[wv] = __float_as_uint(vhi); wplain[wv] = plain; }
-  __syncthreads();
-  // the window of the bins.  lo4, hi4: the fourth smallest and the fourth largest extreme of the waves with slots
-  auto window = [&](float lo4, float hi4) {
-    const float edge = lo4 < hi4 ? 0.25f * (hi4 - lo4) : INFINITY;
-    const float from = fmaxf(vlo, lo4 - edge);
-    return float2{from, 4095.0f / (fminf(vhi, hi4 + edge) - from)};
-  };
-  if (wv == 0) {
-    const uint32_t waves = (n + KPT * 64 - 1) / (KPT * 64), i = (uint32_t)(lane & 15);
-    const uint32_t fourth = waves > 3 ? 3 : waves - 1;
-    vlo = i < waves ? __uint_as_float(wlo[i]) : INFINITY;
-    vhi = i < waves ? __uint_as_float(whi[i]) : -INFINITY;
-    plain = i >= waves || wplain[i] != 0;
-    uint32_t below = 0, over = 0;
-    row16_each([&](auto turn) {
-      below += turn(vlo) < vlo;
-      over += turn(vhi) > vhi;
-    });
-    float lo4 = i < waves && below <= fourth ? vlo : -INFINITY;      // the largest of those with at most three before them
-    float hi4 = i < waves && over <= fourth ? vhi : INFINITY;
-    lo4 = row16_max(lo4);
-    hi4 = row16_min(hi4);
-    vlo = row16_min(vlo);
-    // how much the waves' largest values differ, those left out that hold nothing but the row's smallest value
-    const float apart = hi4 - row16_min(vhi > vlo ? vhi : INFINITY);
-    vhi = row16_max(vhi);
+  // the window of the bins, from the extremes and the plainness of each lane's values; `waves`: those with values;
+  // lowest(cut): the smallest of the lane's values that are not below cut
+  auto find_window = [&](uint32_t waves, auto&& lowest) {
+    vlo = wave_min(vlo);
+    vhi = wave_max(vhi);
     plain = __builtin_amdgcn_ballot_w64(!plain) == 0;
-    const float2 w = window(lo4, hi4);
-    if (lane == 0) {
-      // far more below the top than that: masked slots in most waves, say
-      const bool masked = plain && apart > 0.0f && hi4 - lo4 > 512.0f * apart;
-      s_win[0] = vlo; s_win[1] = vhi; s_win[2] = w.x; s_win[3] = w.y;
-      s_win[4] = hi4; s_win[5] = hi4 - 256.0f * apart;
-      s_flags = (plain ? 1u : 0u) | (masked ? 2u : 0u);
-    }
-  }
-  __syncthreads();
-  vlo = s_win[0];
-  vhi = s_win[1];
-  plain = (s_flags & 1u) != 0;
-  float from = s_win[2], scale = s_win[3];
-  forget();
-  if (s_flags & 2u) {                                       // the smallest value again, without those
-    const float cut = s_win[5];
-    float m = INFINITY;
-#pragma unroll
-    for (int x = 0; x < KPT; ++x) m = f[x] >= cut ? fminf(m, f[x]) : m;
-    m = wave_min(m);
-    if (lane == 0) wlo[wv] = __float_as_uint(m);
+    if (lane == 0) { wlo[wv] = __float_as_uint(vlo); whi[wv] = __float_as_uint(vhi); wplain[wv] = plain; }
     __syncthreads();
-    for (int x = 0; x < 16; ++x) m = fminf(m, __uint_as_float(wlo[x]));
-    const float2 w = window(m, s_win[4]);
-    from = w.x;
-    scale = w.y;
+    // lo4, hi4: the fourth smallest and the fourth largest extreme of the waves with slots
+    auto window = [&](float lo4, float hi4) {
+      const float edge = lo4 < hi4 ? 0.25f * (hi4 - lo4) : INFINITY;
+      const float first = fmaxf(vlo, lo4 - edge);
+      return float2{first, 4095.0f / (fminf(vhi, hi4 + edge) - first)};
+    };
+    if (wv == 0) {
+      const uint32_t i = (uint32_t)(lane & 15);
+      const uint32_t fourth = waves > 3 ? 3 : waves - 1;
+      vlo = i < waves ? __uint_as_float(wlo[i]) : INFINITY;
+      vhi = i < waves ? __uint_as_float(whi[i]) : -INFINITY;
+      plain = i >= waves || wplain[i] != 0;
+      uint32_t below = 0, over = 0;
+      row16_each([&](auto turn) {
+        below += turn(vlo) < vlo;
+        over += turn(vhi) > vhi;
+      });
+      float lo4 = i < waves && below <= fourth ? vlo : -INFINITY;      // the largest of those with at most three before them
+      float hi4 = i < waves && over <= fourth ? vhi : INFINITY;
+      lo4 = row16_max(lo4);
+      hi4 = row16_min(hi4);
+      vlo = row16_min(vlo);
+      // how much the waves' largest values differ, those left out that hold nothing but the row's smallest value
+      const float apart = hi4 - row16_min(vhi > vlo ? vhi : INFINITY);
+      vhi = row16_max(vhi);
+      plain = __builtin_amdgcn_ballot_w64(!plain) == 0;
+      const float2 w = window(lo4, hi4);
+      if (lane == 0) {
+        // far more below the top than that: masked slots in most waves, say
+        const bool masked = plain && apart > 0.0f && hi4 - lo4 > 512.0f * apart;
+        s_win[0] = vlo; s_win[1] = vhi; s_win[2] = w.x; s_win[3] = w.y;
+        s_win[4] = hi4; s_win[5] = hi4 - 256.0f * apart;
+        s_flags = (plain ? 1u : 0u) | (masked ? 2u : 0u);
+      }
+    }
+    __syncthreads();
+    vlo = s_win[0];
+    vhi = s_win[1];
+    plain = (s_flags & 1u) != 0;
+    from = s_win[2];
+    scale = s_win[3];
     forget();
-  }
-  const bool by_value = plain && scale > 0.0f && scale < INFINITY;
-  if (plain) {                                              // past the row's end: the lowest bin, below every threshold
-#pragma unroll
-    for (int x = 0; x < KPT; ++x) f[x] = s0 + x * 64 < n ? f[x] : -INFINITY;
-  }
+    if (s_flags & 2u) {                                     // the smallest value again, without those
+      float m = lowest(s_win[5]);
+      m = wave_min(m);
+      if (lane == 0) wlo[wv] = __float_as_uint(m);
+      __syncthreads();
+      for (int x = 0; x < 16; ++x) m = fminf(m, __uint_as_float(wlo[x]));
+      const float2 w = window(m, s_win[4]);
+      from = w.x;
+      scale = w.y;
+      forget();
+    }
+  };
   // the bin that holds the rem-th largest entry of the counters in h: published to s_bin / s_rem / s_cb.  all: the
   // number of entries, of which the lowest bin's are not counted (0: it is counted)
   auto find_bin = [&](uint32_t rem, uint32_t all) {
@@ -955,6 +973,155 @@ __global__ __launch_bounds__(1024) void tk_row_select(const float* __restrict__ 
     }
     __syncthreads();
   };
+  // the rem-th largest of the cb keys in `list`, published to s_T, and how many of its equals are taken to s_req
+  auto rank_list = [&](uint32_t cb, uint32_t rem) {
+    __syncthreads();
+    if ((uint32_t)tid < cb) {
+      const uint32_t ki = list[tid];
+      uint32_t gt = 0, eq = 0;
+      for (uint32_t j = 0; j < cb; ++j) {
+        const uint32_t kj = list[j];
+        gt += kj > ki;
+        eq += kj == ki;
+      }
+      if (gt < rem && rem <= gt + eq) { s_T = ki; s_req = rem - gt; }         // equal keys write equal values
+    }
+    __syncthreads();
+  };
+  bool sifted = false;                                      // the window is known: it begins at the samples' bound
+  if constexpr (kSift) {
+    // 0. (uniform over the workgroup)
+    if (sift) {
+      vlo = vhi = sample;
+      plain = sample < INFINITY;
+      find_window(16u, [&](float cut) { return sample >= cut ? sample : INFINITY; });
+      // up to the largest sample, where that is not far outside: the largest may all be one wave's
+      if (vhi - from < 16.0f * 4095.0f / scale) scale = 4095.0f / (vhi - from);
+      if (plain && scale > 0.0f && scale < INFINITY) {
+        atomicAdd(&h[(uint32_t)__builtin_amdgcn_fmed3f((sample - from) * scale, 0.0f, 4095.0f)], 1u);
+        __syncthreads();
+        find_bin(rank, 0u);
+        const float cut = from + ((float)s_bin - 0.25f) / scale, top = from + 4095.0f / scale;     // (ties on a bin's edge)
+        const float fine = 4095.0f / (top - cut);
+        for (int i = tid; i < kBins12; i += 1024) h[i] = 0;
+        // those at or above it, in slot order: (wave, x, lane)
+        uint32_t mine = 0;
+        bool odd = false;                                   // a NaN among them
+        const bool whole = (uint32_t)(wv + 1) * (KPT * 64) <= n;
+        if (whole) {
+#pragma unroll
+          for (int x = 0; x < KPT; ++x) {
+            mine += (uint32_t)__popcll(__builtin_amdgcn_ballot_w64(f[x] >= cut));
+            odd = odd || f[x] != f[x];
+          }
+        } else {
+#pragma unroll
+          for (int x = 0; x < KPT; ++x) {
+            mine += (uint32_t)__popcll(__builtin_amdgcn_ballot_w64(f[x] >= cut && s0 + x * 64 < n));
+            odd = odd || f[x] != f[x];
+          }
+        }
+        odd = __builtin_amdgcn_ballot_w64(odd) != 0;
+        forget();
+        if (lane == 0) { wlo[wv] = mine; wplain[wv] = odd ? 1u : 0u; }
+        __syncthreads();
+        uint32_t at = 0, all = 0, odds = 0;
+#pragma unroll
+        for (int x = 0; x < 16; ++x) {
+          at += x < wv ? wlo[x] : 0u;
+          all += wlo[x];
+          odds |= wplain[x];
+        }
+        sifted = odds == 0 && all >= want && fine > 0.0f && fine < INFINITY;
+        if (sifted) {
+          from = cut - 1.0f / fine;                         // (the lowest bin is the others')
+          scale = fine;
+        }
+        if (sifted && all <= (uint32_t)kSiftMax) {
+          auto keep = [&](auto&& hit) {
+#pragma unroll
+            for (int x = 0; x < KPT; ++x) {
+              const uint64_t m = __builtin_amdgcn_ballot_w64(hit(x));
+              const uint32_t p = __builtin_amdgcn_mbcnt_hi((uint32_t)(m >> 32), __builtin_amdgcn_mbcnt_lo((uint32_t)m, at));
+              if (hit(x)) {
+                s_kept[p] = f[x];
+                s_slot[p] = s0 + x * 64;
+              }
+              at += (uint32_t)__popcll(m);
+            }
+          };
+          if (whole) keep([&](int x) { return f[x] >= cut; });
+          else keep([&](int x) { return f[x] >= cut && s0 + x * 64 < n; });
+          __syncthreads();
+          // four of them per thread, one behind the other
+          const float4 c4 = reinterpret_cast<const float4*>(s_kept)[tid];
+          const float c[4] = {c4.x, c4.y, c4.z, c4.w};
+          uint32_t bin[4];
+#pragma unroll
+          for (int i = 0; i < 4; ++i) {
+            bin[i] = 4u * tid + i < all ? (uint32_t)__builtin_amdgcn_fmed3f((c[i] - from) * scale, 0.0f, 4095.0f) : 0xffffffffu;
+            if (bin[i] != 0xffffffffu) atomicAdd(&h[bin[i]], 1u);
+          }
+          __syncthreads();
+          find_bin(want, 0u);
+          const uint32_t cb = s_cb, rem = s_rem, b0 = s_bin;
+          if (cb <= (uint32_t)kRankMax) {
+#pragma unroll
+            for (int i = 0; i < 4; ++i)
+              if (bin[i] == b0) list[atomicAdd(&s_n, 1u)] = order_key(c[i]);
+            rank_list(cb, rem);
+            const uint32_t T = s_T, req = s_req;
+            uint32_t ng = 0, ne = 0;
+#pragma unroll
+            for (int i = 0; i < 4; ++i) {
+              const bool in = bin[i] != 0xffffffffu;
+              ng += in && order_key(c[i]) > T;
+              ne += in && order_key(c[i]) == T;
+            }
+            const uint32_t before = block_scan_excl<16>(ng | ne << 16, wsum);
+            uint32_t g = before & 0xffffu, e = before >> 16;
+            int32_t* out = idx + (int64_t)row * k;
+            if (tid == 0) count[row] = (int32_t)want;
+            const uint4 s4 = reinterpret_cast<const uint4*>(s_slot)[tid];
+            const uint32_t slot[4] = {s4.x, s4.y, s4.z, s4.w};
+#pragma unroll
+            for (int i = 0; i < 4; ++i) {
+              const bool in = bin[i] != 0xffffffffu, is_g = in && order_key(c[i]) > T, is_e = in && order_key(c[i]) == T;
+              if (is_g || (is_e && e < req)) out[g + (e < req ? e : req)] = (int32_t)slot[i];
+              g += is_g;
+              e += is_e;
+            }
+            return;
+          }
+        }
+      }
+      __syncthreads();                                      // everybody has read what the steps below write again
+      for (int i = tid; i < kBins12; i += 1024) h[i] = 0;
+      vlo = INFINITY;
+      vhi = -INFINITY;
+      plain = true;
+      __syncthreads();
+    }
+  }
+  if (!sifted) {
+#pragma unroll
+    for (int x = 0; x < KPT; ++x) {
+      vlo = fminf(vlo, f[x]);
+      vhi = fmaxf(vhi, f[x]);
+      plain = plain && f[x] < INFINITY;
+    }
+    find_window((n + KPT * 64 - 1) / (KPT * 64), [&](float cut) {
+      float m = INFINITY;
+#pragma unroll
+      for (int x = 0; x < KPT; ++x) m = f[x] >= cut ? fminf(m, f[x]) : m;
+      return m;
+    });
+  }
+  const bool by_value = plain && scale > 0.0f && scale < INFINITY;
+  if (plain) {                                              // past the row's end: the lowest bin, below every threshold
+#pragma unroll
+    for (int x = 0; x < KPT; ++x) f[x] = s0 + x * 64 < n ? f[x] : -INFINITY;
+  }
   uint32_t T, req;
   if (plain && vlo == vhi) {                               // all equal: the want lowest slots
     T = order_key(vlo);
@@ -1039,18 +1206,7 @@ __global__ __launch_bounds__(1024) void tk_row_select(const float* __restrict__ 
         at = __builtin_amdgcn_readfirstlane(at);
         if (hit) list[at + (uint32_t)__popcll(m & ((1ull << lane) - 1))] = kk;
       }
-      __syncthreads();
-      if ((uint32_t)tid < cb) {
-        const uint32_t ki = list[tid];
-        uint32_t gt = 0, eq = 0;
-        for (uint32_t j = 0; j < cb; ++j) {
-          const uint32_t kj = list[j];
-          gt += kj > ki;
-          eq += kj == ki;
-        }
-        if (gt < rem && rem <= gt + eq) { s_T = ki; s_req = rem - gt; }       // equal keys write equal values
-      }
-      __syncthreads();
+      rank_list(cb, rem);
       T = s_T;
       req = s_req;
     }
@@ -1109,12 +1265,19 @@ constexpr int64_t kRowSelectMax = 40960;
 static int32_t launch_row_select(const float* vals, int64_t stride, int rows, int n_kv_heads, const SelRows& sr,
                                  int64_t nmax, int32_t k, int32_t* idx, int32_t* count, const RowSelectFused& fu,
                                  hipStream_t st) {
-#define HCA_ROW_SELECT(KPT) tk_row_select<KPT><<<rows, 1024, 0, st>>>(vals, stride, n_kv_heads, sr, k, idx, count, fu)
-  if (nmax <= 4 * 1024) HCA_ROW_SELECT(4);
-  else if (nmax <= 8 * 1024) HCA_ROW_SELECT(8);
-  else if (nmax <= 16 * 1024) HCA_ROW_SELECT(16);
-  else if (nmax <= 32 * 1024) HCA_ROW_SELECT(32);
-  else HCA_ROW_SELECT(40);
+  // step 0 where the longest row's list is expected to fit (a shorter row's is no longer); its code beside the other's costs
+  // a row that does without 1 us of 23
+  const bool sift = nmax > (int64_t)kSiftMin && k < nmax &&
+                    sift_rank((uint32_t)k, (uint32_t)nmax) * (uint64_t)nmax <= (uint64_t)(kSiftMax - 512) * 1024u;
+#define HCA_ROW_SELECT(KPT, SIFT) tk_row_select<KPT, SIFT><<<rows, 1024, 0, st>>>(vals, stride, n_kv_heads, sr, k, idx, count, fu)
+  if (nmax <= 4 * 1024) HCA_ROW_SELECT(4, false);
+  else if (nmax <= 8 * 1024) HCA_ROW_SELECT(8, false);
+  else if (nmax <= 16 * 1024 && sift) HCA_ROW_SELECT(16, true);
+  else if (nmax <= 16 * 1024) HCA_ROW_SELECT(16, false);
+  else if (nmax <= 32 * 1024 && sift) HCA_ROW_SELECT(32, true);
+  else if (nmax <= 32 * 1024) HCA_ROW_SELECT(32, false);
+  else if (sift) HCA_ROW_SELECT(40, true);
+  else HCA_ROW_SELECT(40, false);
 #undef HCA_ROW_SELECT
   HCA_HIP(hipGetLastError());
   return HCA_OK;

@@ -249,6 +249,40 @@ def test_topk_at_the_edges_of_the_one_launch_form(B, kind, n):
             assert np.all(got[b, want:] == -7)
 
 
+@pytest.mark.parametrize("kind", ["normal", "ramp", "ties", "seen", "missed", "nan", "masked"])
+@pytest.mark.parametrize("n", [8191, 8192, 16385, 30011, 40960])
+def test_topk_of_a_row_sifted_by_samples(B, kind, n):
+    """Few of a row in one workgroup's registers: the list above the samples' bound, and rows whose samples mislead."""
+    rng = np.random.default_rng(n + 7 * len(kind))
+    t = np.arange(1024, dtype=np.int64)
+    sampled = (t * n >> 10) + (((t * 40503 & 0xffff) * (n >> 10)) >> 16)
+    x = rng.standard_normal(n).astype(np.float32)
+    if kind == "ramp":
+        x.sort()
+    elif kind == "ties":                                    # more equal values than are ranked against each other
+        x = np.round(x * 2) / 2
+    elif kind == "seen":                                    # the sampled places hold the largest values: a list too short
+        x[sampled] += 20
+    elif kind == "missed":                                  # and the smallest: one too long, or with all its values in the top bin
+        x[sampled] -= 20
+    elif kind == "nan":
+        x[n - 5] = np.nan
+    elif kind == "masked":
+        x[rng.random(n) < 0.5] = -np.inf
+        x[rng.random(n) < 0.001] = np.inf
+    shape = B.make_shape(1, 1, 1, n)
+    dsel = torch.from_numpy(x).cuda()
+    ref = np.argsort(-_order_key(x).astype(np.int64), kind="stable")
+    for k in (1, 64, 777, 2048, 3000):
+        ws = torch.empty(B.hca_workspace_bytes(shape, k, 1), dtype=torch.uint8, device="cuda")
+        idx = torch.full((1, k), -7, dtype=torch.int32, device="cuda")
+        count = torch.full((1,), -7, dtype=torch.int32, device="cuda")
+        B.hca_topk(shape, dsel, [n], k, idx, count, ws)
+        torch.cuda.synchronize()
+        assert count.item() == k
+        assert np.array_equal(idx.cpu().numpy()[0], np.sort(ref[:k])), f"k {k}"
+
+
 def _sampled_slots(n, m=8192):
     """The slots whose scores topk_sample_rank looks at."""
     i = np.arange(min(n, m), dtype=np.uint64)
