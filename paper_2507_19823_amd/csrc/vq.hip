@@ -1558,7 +1558,10 @@ __device__ __forceinline__ void vq_row_exponents(float* __restrict__ lut, int g,
 // them: 118 us), and a thread asks for its whole part of a slice, eight 16-byte entries, when it has finished its
 // own lookups and before it waits for the others' (99 us; asked for before the lookups, 118: the indices
 // queue behind it).
-template <int G, int NQ>
+// RAW: the slice as it lies in memory, straight into LDS, and on the heads' grids at every lookup - where there are not many
+// more lookups than entries (scan_wide_launch).  What is left of a slice then: 1.2 us of refill, and the lookups, whose
+// vector instructions (18 of each with four heads, 7 without RAW) take as long as a share has slots.
+template <int G, int NQ, bool RAW>
 __global__ __launch_bounds__(1024) void vq_scan_wide_kernel(int g, int c, int gps, int64_t cap, int64_t per_wg,
                                                              const uint16_t* __restrict__ pcache,
                                                              float* __restrict__ lut, NRes nr, int n_kv_heads, int rows,
@@ -1577,10 +1580,11 @@ __global__ __launch_bounds__(1024) void vq_scan_wide_kernel(int g, int c, int gp
   const int64_t t0 = share * per_wg;
   if (t0 >= n) return;
   const int64_t t1 = t0 + per_wg < n ? t0 + per_wg : n;
-  F* tab = reinterpret_cast<F*>(lds_raw);
+  using T = typename std::conditional<RAW, E, F>::type;
+  T* tab = reinterpret_cast<T*>(lds_raw);
   const E* trow = reinterpret_cast<const E*>(lut) + (int64_t)row * g * c;
   const int ne = gps * c;                                 // entries of a slice, at most 1024 * kPer
-  E nt[kGo];
+  E nt[RAW ? 1 : kGo];
   auto fetch = [&](int g0, int u0) {
     const E* src = trow + (int64_t)g0 * c;
     uint32_t t = threadIdx.x;
@@ -1620,17 +1624,34 @@ __global__ __launch_bounds__(1024) void vq_scan_wide_kernel(int g, int c, int gp
   for (int q = 0; q < NQ; ++q) nx[q] = __builtin_nontemporal_load(reinterpret_cast<const v2i*>(ip[q]) + lane);
   const uint32_t last = (uint32_t)(c - 1);
   for (int g0 = 0; g0 < g; g0 += gps) {
-    fetch(g0, 0);
-    __syncthreads();                                      // the previous slice's lookups are done
+    if constexpr (RAW) {
+      __syncthreads();                                    // the previous slice's lookups are done
+      // sixteen bytes per lane, a wave's 1 KiB in one piece behind a common address.  (A slice is a multiple of 16 bytes:
+      // one group with four heads, an even number of groups with two, four or more with one)
+      const unsigned char* src = reinterpret_cast<const unsigned char*>(trow + (int64_t)g0 * c);
+      const int n16 = (gps < g - g0 ? gps : g - g0) * c * (int)sizeof(E) / 16;
 #pragma unroll
-    for (int u0 = 0; u0 < kPer; u0 += kGo) {
-      if (u0 > 0) fetch(g0, u0);
+      for (int u = 0; u < 8; ++u) {
+        const int at = 1024 * u + 64 * w;
+        if (at + lane < n16)
+          __builtin_amdgcn_global_load_lds((const __attribute__((address_space(1))) void*)(src + (int64_t)(at + lane) * 16),
+                                           (__attribute__((address_space(3))) void*)(lds_raw + at * 16), 16, 0, 0);
+      }
+      __builtin_amdgcn_s_waitcnt(0x0f70);                 // vmcnt(0): they are in LDS
+      __syncthreads();
+    } else {
+      fetch(g0, 0);
+      __syncthreads();                                    // the previous slice's lookups are done
 #pragma unroll
-      for (int u = 0; u < kGo; ++u)
-        if (1024 * (u0 + u) < ne && threadIdx.x < (uint32_t)(ne - 1024 * (u0 + u)))
-          tab[threadIdx.x + 1024 * (u0 + u)] = entry_fix<G>(nt[u], s);
+      for (int u0 = 0; u0 < kPer; u0 += kGo) {
+        if (u0 > 0) fetch(g0, u0);
+#pragma unroll
+        for (int u = 0; u < kGo; ++u)
+          if (1024 * (u0 + u) < ne && threadIdx.x < (uint32_t)(ne - 1024 * (u0 + u)))
+            tab[threadIdx.x + 1024 * (u0 + u)] = entry_fix<G>(nt[u], s);
+      }
+      __syncthreads();
     }
-    __syncthreads();
     for (int gl = 0; gl < gps; ++gl) {
       v2i cur[NQ];
 #pragma unroll
@@ -1640,21 +1661,24 @@ __global__ __launch_bounds__(1024) void vq_scan_wide_kernel(int g, int c, int gp
 #pragma unroll
         for (int q = 0; q < NQ; ++q) nx[q] = __builtin_nontemporal_load(reinterpret_cast<const v2i*>(ip[q] + off) + lane);
       }
-      const F* tg = tab + gl * c;
+      const T* tg = tab + gl * c;
 #pragma unroll
       for (int q = 0; q < NQ; ++q) {
         if (q >= nq) continue;
-        F e[4];
+        T raw[4];
 #pragma unroll
         for (int tt = 0; tt < 4; ++tt) {
           const uint32_t code = ((uint32_t)(tt < 2 ? cur[q].x : cur[q].y) >> (16 * (tt & 1))) & 0xffffu;
-          e[tt] = tg[code < last ? code : last];          // slots past n hold whatever memory held
+          raw[tt] = tg[code < last ? code : last];        // slots past n hold whatever memory held
         }
 #pragma unroll
         for (int tt = 0; tt < 4; ++tt) {
-          if constexpr (G == 4) { zi[q][tt][0] += e[tt].x; zi[q][tt][1] += e[tt].y; zi[q][tt][2] += e[tt].z; zi[q][tt][3] += e[tt].w; }
-          else if constexpr (G == 2) { zi[q][tt][0] += e[tt].x; zi[q][tt][1] += e[tt].y; }
-          else { zi[q][tt][0] += e[tt]; }
+          F e;
+          if constexpr (RAW) e = entry_fix<G>(raw[tt], s);
+          else e = raw[tt];
+          if constexpr (G == 4) { zi[q][tt][0] += e.x; zi[q][tt][1] += e.y; zi[q][tt][2] += e.z; zi[q][tt][3] += e.w; }
+          else if constexpr (G == 2) { zi[q][tt][0] += e.x; zi[q][tt][1] += e.y; }
+          else { zi[q][tt][0] += e; }
         }
       }
     }
@@ -1963,20 +1987,33 @@ static int32_t scan_wide_launch(const Layout& L, int g, int c, const uint8_t* pc
   const int64_t units = L.rows < 256 ? 256 / L.rows : 1;
   const bool one = nmax <= units * 12 * 1024;
   const int64_t turns = one ? 1 : (nmax + units * 16 * 1024 - 1) / (units * 16 * 1024);
+  // The table's entries straight into LDS (RAW): no registers between, a refill takes 1.2 us for 2.1, but each lookup puts its
+  // entry on the grid instead of each refill.  Measured, as it was / RAW, table included, by slots of a share per
+  // centroid: four heads, 8 rows x 32 groups: c = 8192, 0.28 99 / 87 us, 0.6 102 / 92, 1.16 106 / 104; c = 6000, 1.6 90 / 94; c =
+  // 3000, 1.6 59 / 59, 3.2 70 / 77; c = 1024, 4.8 38 / 44.  Two heads: c = 8192, 1.16 86 / 70, 2 (1 Mi) 180 / 168; c = 4096, 2.3 60
+  // / 55, 3.8 (64 groups) 127 / 131; c = 2048, 4.6 47 / 48; c = 1024, 9.2 40 / 45.  One head: c = 8192, 1.16 68 / 52, 2 163 / 142;
+  // c = 300, 8 27 / 24, 32 36 / 34, 52 (64 groups) 88 / 90.
+  const double per_centroid = (double)nmax / (double)(units * turns * c);
+  const bool raw = per_centroid <= (G == 4 ? 1.3 : G == 2 ? 3.5 : 40.0) && (one || G < 4) && ((uintptr_t)lut & 15) == 0;
   int64_t per_wg = align_up((nmax + units * turns - 1) / (units * turns), 256);
   if (per_wg < 2048) per_wg = 2048;
   const int64_t shares = (nmax + per_wg - 1) / per_wg;
-#define HCA_WIDE(NQ)                                                                                                     \
+#define HCA_WIDE(NQ, RAW)                                                                                                \
   {                                                                                                                      \
     if (lds > 64 * 1024) {                                                                                               \
       static std::atomic<uint64_t> opted{0};                /* one per instantiation */                                  \
-      const int32_t rc = lds_opt_in(reinterpret_cast<const void*>(&vq_scan_wide_kernel<G, NQ>), 128 * 1024, &opted);     \
+      const int32_t rc = lds_opt_in(reinterpret_cast<const void*>(&vq_scan_wide_kernel<G, NQ, RAW>), 128 * 1024, &opted); \
       if (rc != HCA_OK) return rc;                          /* + 16 B static */                                          \
     }                                                                                                                    \
-    vq_scan_wide_kernel<G, NQ><<<(unsigned)(shares * L.rows), 1024, lds, st>>>(                                          \
+    vq_scan_wide_kernel<G, NQ, RAW><<<(unsigned)(shares * L.rows), 1024, lds, st>>>(                                     \
         g, c, gps, L.cap, per_wg, (const uint16_t*)pcache, lut, nr, L.n_kv_heads, L.rows, sel, z_opt);                   \
   }
-  if (one) HCA_WIDE(3) else HCA_WIDE(4)
+  if constexpr (G < 4) {
+    if (raw && !one) HCA_WIDE(4, true)
+  }
+  if (raw && one) HCA_WIDE(3, true)
+  else if (!raw && one) HCA_WIDE(3, false)
+  else if (!raw) HCA_WIDE(4, false)
 #undef HCA_WIDE
   HCA_HIP(hipGetLastError());
   return HCA_OK;

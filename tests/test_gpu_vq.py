@@ -607,3 +607,36 @@ def test_wide_scan_of_few_slots_is_that_of_many(B, rows, gqa, g, c, many):
                 assert torch.equal(lut[a:a + gqa].view(torch.int32), out[0][1][a:a + gqa].view(torch.int32))
             assert torch.equal(sel[r, :, :m], out[0][2][r, :, :m]) and torch.equal(z[r, :, :m], out[0][3][r, :, :m])
             assert (sel[r, :, m:] == -7).all() and (z[r, :, m:] == -7).all()
+
+
+@pytest.mark.parametrize("rows,gqa,g,c,lengths", [
+    (8, 4, 32, 2500, (300001, 40000, 1000)),                    # on the grid at the refill, raw entries, entries from L2
+    (8, 4, 32, 8191, (380001, 300001, 60000, 1000)),            # raw entries: the last of them past a multiple of 1024
+    (8, 2, 32, 1001, (300001, 60000, 1000)),
+    (8, 2, 32, 8192, (450001, 300001, 1000)),                   # four quads per thread and three
+    (8, 1, 64, 300, (450001, 200001, 1000)),
+])
+def test_wide_scan_of_raw_entries(B, rows, gqa, g, c, lengths):
+    """The forms of the wide scan whose table passes through LDS, by slots per centroid, bit for bit; and a table that does
+    not begin at a multiple of 16 bytes."""
+    gen = torch.Generator(device="cuda").manual_seed(c + g)
+    many = lengths[0]
+    shape = B.make_shape(rows, gqa, 1, many)
+    cen = torch.randn(1, g, c, 128 // g, generator=gen, device="cuda")
+    cb = B.make_codebook(g, c, cen)
+    pc = torch.zeros(B.hca_vq_pcache_bytes(shape, cb), dtype=torch.uint8, device="cuda")
+    pc.view(torch.int16).random_(0, c, generator=gen)
+    q = torch.randn(rows, gqa, 128, generator=gen, device="cuda").half()
+    first = None
+    for n, shift in [(n, 0) for n in lengths] + ([(lengths[1], gqa)] if gqa < 4 else []):
+        lens = [n - 300 * (r % 2) for r in range(rows)]
+        lut = torch.zeros(B.hca_vq_lut_bytes(shape, cb) // 4 + shift, device="cuda")[shift:]
+        sel = torch.full((rows, 1, many), -7.0, device="cuda")
+        z = torch.full((rows, gqa, many), -7.0, device="cuda")
+        B.hca_vq_score(shape, cb, pc, q, lens, lut, sel, z)
+        torch.cuda.synchronize()
+        first = first or (sel, z)
+        for r in range(rows):
+            m = lens[r]
+            assert torch.equal(sel[r, :, :m], first[0][r, :, :m]) and torch.equal(z[r, :, :m], first[1][r, :, :m])
+            assert (sel[r, :, m:] == -7).all() and (z[r, :, m:] == -7).all()
