@@ -124,15 +124,24 @@ __device__ __forceinline__ void partial_empty(float* pmz, float* py) {
 // last row is asked for again: it is in the cache (leaving those loads out costs a branch each, 9.6 -> 10.3 us for 65 rows
 // x 8 from the host).
 struct ValueRows { uint4 v[8]; };
+// value.at(i): where entry i's row is, all of them looked up before the first is asked for; value(r): the load.
 template <typename V>
-__device__ __forceinline__ void value_rows(V&& value, int x0, int nvalid, ValueRows* out) {
+__device__ __forceinline__ void value_rows(const V& value, int x0, int nvalid, ValueRows* out) {
   const int w = threadIdx.x >> 6, sub = (threadIdx.x & 63) >> 4;
+  int32_t r[8];
 #pragma unroll
   for (int x = 0; x < 8; ++x) {
     const int i = 64 * w + 4 * (x0 + x) + sub;
-    out->v[x] = value(i < nvalid ? i : nvalid - 1);
+    r[x] = value.at(i < nvalid ? i : nvalid - 1);
   }
+#pragma unroll
+  for (int x = 0; x < 8; ++x) out->v[x] = value(r[x]);
 }
+struct StagedValues {                // the staging area: in the chunk's order
+  const uint4* vs;
+  __device__ __forceinline__ int32_t at(int i) const { return i; }
+  __device__ __forceinline__ uint4 operator()(int32_t i) const { return vs[(int64_t)i * 16]; }
+};
 
 // What the last stage of a row with a single chunk needs: it writes the result itself and no merge follows.
 struct RowEnd {
@@ -145,11 +154,11 @@ struct RowEnd {
 };
 
 // Steps 2 and 3 of a chunk, after its logits sit in ps.lg (and a __syncthreads()): per-head chunk
-// max / exponentials / sum, then the weighted sum of the value rows.  value(i): 16 bytes (this lane's part) of entry i's
+// max / exponentials / sum, then the weighted sum of the value rows.  value: 16 bytes (this lane's part) of an entry's
 // row; rows0: the first eight of them, already on their way.
 template <bool VALUES, typename V>
 __device__ __forceinline__ void partial_softmax_sum(PartialShared& ps, const AttendWs& a, int row, int i0, int nvalid,
-                                                    int32_t k, float* pmz, float* py, V&& value, const ValueRows& rows0,
+                                                    int32_t k, float* pmz, float* py, const V& value, const ValueRows& rows0,
                                                     const RowEnd& end) {
   auto& lg = ps.lg;
   auto& red = ps.red;
@@ -260,6 +269,17 @@ struct ValueSource {
   int64_t host_stride = 0, hbm_stride = 0, n_host_rows = 0;
 };
 
+struct DirectValues {
+  const ValueSource& src;
+  const int32_t* vrow;               // of the chunk's entries, in LDS
+  int row, part;
+  __device__ __forceinline__ int32_t at(int i) const { return vrow[i]; }
+  __device__ __forceinline__ uint4 operator()(int32_t vr) const {
+    return (vr < src.n_host_rows ? src.v_host + ((int64_t)row * src.host_stride + vr) * 16
+                                 : src.v_hbm + ((int64_t)row * src.hbm_stride + (vr - src.n_host_rows)) * 16)[part];
+  }
+};
+
 // Bound by latency: one workgroup per 256 selected tokens, a chain of dependent loads (slots, codes; positions, values) and
 // a few microseconds of arithmetic.  So everything that can be asked for early is: the value rows before the logits, the
 // query beside the slots.  DIRECT: the value rows are read where they live, no gather and no staging area.  A row's only
@@ -277,10 +297,14 @@ __device__ __forceinline__ bool attend_partial_body(PartialShared& ps, QShared& 
   __shared__ __align__(16) uint32_t opimg[64 * 8];
   auto& lg = ps.lg;
   const int row = blockIdx.y;
-  const int cnt = count[row];
   const int i0 = split * kChunk;
   const int tid = threadIdx.x, lane = tid & 63, w = tid >> 6;
   const int t = lane & 15, j = lane >> 4;
+  // slot, query and count are asked for together.  (Past the list's end the slot is whatever memory held: not looked up)
+  int32_t my_slot = idx[(int64_t)row * k + (i0 + tid < k ? i0 + tid : k - 1)];
+  uint32_t pair = query_pair(q, row, L.gqa);
+  const int cnt = count[row];
+  s_slot[tid] = my_slot;
   float* pmz = a.pmz + (((int64_t)row * nsplit + split) * 4) * 2;
   float* py = a.py + (((int64_t)row * nsplit + split) * 4) * kHeadDim;
   if (i0 >= cnt) {  // empty chunk: neutral partial
@@ -289,21 +313,17 @@ __device__ __forceinline__ bool attend_partial_body(PartialShared& ps, QShared& 
     return false;
   }
   const int nvalid = (cnt - i0 < kChunk) ? cnt - i0 : kChunk;
-  const int32_t my_slot = idx[(int64_t)row * k + i0 + (tid < nvalid ? tid : nvalid - 1)];
-  const uint4* vs = reinterpret_cast<const uint4*>(a.vstage) + ((int64_t)row * k + i0) * 16 + (lane & 15);
-  auto value = [&](int i) {
-    if constexpr (!DIRECT) {
-      return vs[(int64_t)i * 16];
-    } else {
-      const int64_t vr = s_vrow[i];
-      return (vr < vsrc.n_host_rows ? vsrc.v_host + ((int64_t)row * vsrc.host_stride + vr) * 16
-                                    : vsrc.v_hbm + ((int64_t)row * vsrc.hbm_stride + (vr - vsrc.n_host_rows)) * 16)[lane & 15];
-    }
-  };
+  // the value rows' numbers before the codes: the values, which wait for them, are then on their way with the codes
+  int32_t my_vrow = 0;
+  if constexpr (DIRECT) my_vrow = vsrc.pos[(int64_t)row * L.cap + (tid < nvalid ? my_slot : 0)];
+  const auto value = [&] {
+    if constexpr (DIRECT) return DirectValues{vsrc, s_vrow, row, lane & 15};
+    else return StagedValues{reinterpret_cast<const uint4*>(a.vstage) + ((int64_t)row * k + i0) * 16 + (lane & 15)};
+  }();
   ValueRows rows0;
   if constexpr (VALUES && !DIRECT) value_rows(value, 0, nvalid, &rows0);
-  s_slot[tid] = my_slot;
-  load_query(q, row, L.gqa, L.group, &sh);                  // (ends with a barrier)
+  asm volatile("" : "+v"(pair));                            // (the query is not waited for before)
+  load_query(pair, L.group, &sh);                           // (ends with a barrier)
   const uint8_t* crow = kcache + (int64_t)row * L.codes_row_bytes();
   const uint8_t* mrow = kcache + L.meta_off + (int64_t)row * L.meta_row_bytes();
 
@@ -314,7 +334,8 @@ __device__ __forceinline__ bool attend_partial_body(PartialShared& ps, QShared& 
     uint4 wv[4], mv[4];
 #pragma unroll
     for (int x = 0; x < 4; ++x) {
-      const int64_t slot = s_slot[(w + 4 * x) * 16 + t];
+      const int at = (w + 4 * x) * 16 + t;
+      const int64_t slot = s_slot[at < nvalid ? at : nvalid - 1];
       if constexpr (BITS == 4) {
         const int64_t blk = slot >> 4;
         const int tl = (int)(slot & 15);
@@ -329,8 +350,6 @@ __device__ __forceinline__ bool attend_partial_body(PartialShared& ps, QShared& 
         mv[x] = uint4{m.x, m.y, 0, 0};
       }
     }
-    int32_t my_vrow = 0;
-    if constexpr (DIRECT) my_vrow = vsrc.pos[(int64_t)row * L.cap + my_slot];
     QOperand<BITS> op;
     build_operand_shared<BITS>(&sh, opimg, &op);
     if constexpr (DIRECT) {
@@ -455,9 +474,11 @@ __global__ __launch_bounds__(256) void vq_attend_partial(int g, int c, int64_t c
                                                          const int32_t* __restrict__ count, int32_t k, float sm_scale,
                                                          AttendWs a, int nsplit, RowEnd end) {
   __shared__ PartialShared ps;
+  __shared__ int32_t s_slot[kChunk];
   const int row = blockIdx.y, split = blockIdx.x;
-  const int cnt = count[row];
   const int i0 = split * kChunk;
+  s_slot[threadIdx.x] = idx[(int64_t)row * k + (i0 + (int)threadIdx.x < k ? i0 + (int)threadIdx.x : k - 1)];    // with the count
+  const int cnt = count[row];
   float* pmz = a.pmz + (((int64_t)row * nsplit + split) * 4) * 2;
   float* py = a.py + (((int64_t)row * nsplit + split) * 4) * kHeadDim;
   if (i0 >= cnt) {
@@ -466,13 +487,13 @@ __global__ __launch_bounds__(256) void vq_attend_partial(int g, int c, int64_t c
     return;
   }
   const int nvalid = (cnt - i0 < kChunk) ? cnt - i0 : kChunk;
-  const uint4* vs = reinterpret_cast<const uint4*>(a.vstage) + ((int64_t)row * k + i0) * 16 + (threadIdx.x & 15);
-  auto value = [&](int i) { return vs[(int64_t)i * 16]; };
+  const StagedValues value{reinterpret_cast<const uint4*>(a.vstage) + ((int64_t)row * k + i0) * 16 + (threadIdx.x & 15)};
   ValueRows rows0;
+  __syncthreads();
   if constexpr (EARLY) value_rows(value, 0, nvalid, &rows0);
   {
     const int i = threadIdx.x;
-    const int64_t slot = idx[(int64_t)row * k + i0 + (i < nvalid ? i : nvalid - 1)];
+    const int64_t slot = s_slot[i < nvalid ? i : nvalid - 1];
     const uint8_t* pr = pcache + ((int64_t)row * cap + slot) * g;                  // narrow form: the slot's record
     const uint16_t* pw = reinterpret_cast<const uint16_t*>(pcache);
     const int64_t tiles = vq_tiles(cap);

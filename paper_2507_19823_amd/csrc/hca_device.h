@@ -120,15 +120,15 @@ __device__ __forceinline__ int operand_channel(int m, int j, int x) {
 
 // Computes the fixed-point query of row `row` into LDS.  Called by all threads of the block
 // (at least 256); wave w < 4 handles query head w of the row.  Ends with a barrier.
-__device__ __forceinline__ void load_query(const uint16_t* __restrict__ q, int row, int gqa, int group,
-                                           QShared* sh) {
+// (pair: this lane's two channels of head w, asked for as early as the caller likes)
+__device__ __forceinline__ uint32_t query_pair(const uint16_t* __restrict__ q, int row, int gqa) {
+  const int w = threadIdx.x >> 6;
+  const uint32_t pair = reinterpret_cast<const uint32_t*>(q + ((int64_t)row * gqa + (w < gqa ? w : gqa - 1)) * kHeadDim)[threadIdx.x & 63];
+  return w < gqa ? pair : 0u;
+}
+__device__ __forceinline__ void load_query(uint32_t pair, int group, QShared* sh) {
   const int tid = threadIdx.x, w = tid >> 6, lane = tid & 63;
-  float x0 = 0.f, x1 = 0.f;
-  if (w < gqa) {
-    const uint32_t pr = reinterpret_cast<const uint32_t*>(q + ((int64_t)row * gqa + w) * kHeadDim)[lane];
-    x0 = h2f(pr & 0xffffu);
-    x1 = h2f(pr >> 16);
-  }
+  const float x0 = h2f(pair & 0xffffu), x1 = h2f(pair >> 16);
   float amax = fmaxf(fabsf(x0), fabsf(x1));
 #pragma unroll
   for (int o = 32; o >= 1; o >>= 1) amax = fmaxf(amax, __shfl_xor(amax, o));
@@ -148,6 +148,10 @@ __device__ __forceinline__ void load_query(const uint16_t* __restrict__ q, int r
     sh->qsum[h][g] = acc;
   }
   __syncthreads();
+}
+__device__ __forceinline__ void load_query(const uint16_t* __restrict__ q, int row, int gqa, int group,
+                                           QShared* sh) {
+  load_query(query_pair(q, row, gqa), group, sh);
 }
 
 template <int BITS>
