@@ -118,34 +118,43 @@ __device__ __forceinline__ int operand_channel(int m, int j, int x) {
   }
 }
 
-// Computes the fixed-point query of row `row` into LDS.  Called by all threads of the block
-// (at least 256); wave w < 4 handles query head w of the row.  Ends with a barrier.
-// (pair: this lane's two channels of head w, asked for as early as the caller likes)
+__device__ __forceinline__ float wave_max(float v);
+template <int CTRL> __device__ __forceinline__ int query_dpp(int v) {
+  return __builtin_amdgcn_update_dpp(0, v, CTRL, 0xf, 0xf, true);
+}
+// This lane's two channels of head w of the row, for load_query below: asked for as early as the caller likes.
 __device__ __forceinline__ uint32_t query_pair(const uint16_t* __restrict__ q, int row, int gqa) {
   const int w = threadIdx.x >> 6;
   const uint32_t pair = reinterpret_cast<const uint32_t*>(q + ((int64_t)row * gqa + (w < gqa ? w : gqa - 1)) * kHeadDim)[threadIdx.x & 63];
   return w < gqa ? pair : 0u;
 }
+// Computes the fixed-point query of row `row` into LDS.  Called by all threads of the block
+// (at least 256); wave w < 4 handles query head w of the row.  Ends with a barrier.
 __device__ __forceinline__ void load_query(uint32_t pair, int group, QShared* sh) {
   const int tid = threadIdx.x, w = tid >> 6, lane = tid & 63;
   const float x0 = h2f(pair & 0xffffu), x1 = h2f(pair >> 16);
-  float amax = fmaxf(fabsf(x0), fabsf(x1));
-#pragma unroll
-  for (int o = 32; o >= 1; o >>= 1) amax = fmaxf(amax, __shfl_xor(amax, o));
+  const float amax = wave_max(fmaxf(fabsf(x0), fabsf(x1)));
   int s = 0;
   if (amax != 0.f) s = 13 - ilogbf(amax);
-  if (w < 4) {                       // workgroups larger than four waves: the extra waves only take the barriers
-    sh->qfx[w][2 * lane] = (int16_t)(int)rintf(ldexpf(x0, s));
-    sh->qfx[w][2 * lane + 1] = (int16_t)(int)rintf(ldexpf(x1, s));
+  if (w < 4) {                       // workgroups larger than four waves: the extra waves only take the barrier
+    const int16_t v0 = (int16_t)(int)rintf(ldexpf(x0, s)), v1 = (int16_t)(int)rintf(ldexpf(x1, s));
+    reinterpret_cast<uint32_t*>(sh->qfx[w])[lane] = (uint16_t)v0 | (uint32_t)(uint16_t)v1 << 16;
     if (lane == 0) sh->sexp[w] = s;
-  }
-  __syncthreads();
-  if (tid < 16) {
-    const int h = tid >> 2, g = tid & 3;
+    // a row of 16 lanes holds 32 channels; a group is one, two or four rows (16 threads that added a group each from LDS,
+    // behind a barrier of their own, took 1 us more)
+    int sum = v0 + v1;
+    sum += query_dpp<0xB1>(sum);     // quad_perm [1,0,3,2]
+    sum += query_dpp<0x4E>(sum);     // quad_perm [2,3,0,1]
+    sum += query_dpp<0x141>(sum);    // row_half_mirror
+    sum += query_dpp<0x140>(sum);    // row_mirror
+    int rows[4];
+#pragma unroll
+    for (int r = 0; r < 4; ++r) rows[r] = __builtin_amdgcn_readlane(sum, 16 * r);
+    const int per = group >> 5, g = lane >> 4;       // rows per group
     int acc = 0;
-    if (g * group < kHeadDim)
-      for (int c = g * group; c < (g + 1) * group; ++c) acc += sh->qfx[h][c];
-    sh->qsum[h][g] = acc;
+#pragma unroll
+    for (int r = 0; r < 4; ++r) acc += r >= g * per && r < (g + 1) * per ? rows[r] : 0;
+    if ((lane & 15) == 0) sh->qsum[w][g] = acc;
   }
   __syncthreads();
 }
