@@ -323,7 +323,7 @@ __device__ __forceinline__ bool attend_partial_body(PartialShared& ps, QShared& 
   ValueRows rows0;
   if constexpr (VALUES && !DIRECT) value_rows(value, 0, nvalid, &rows0);
   asm volatile("" : "+v"(pair));                            // (the query is not waited for before)
-  load_query(pair, L.group, &sh);                           // (ends with a barrier)
+  load_query(pair, L.gqa, L.group, &sh);                           // (ends with a barrier)
   const uint8_t* crow = kcache + (int64_t)row * L.codes_row_bytes();
   const uint8_t* mrow = kcache + L.meta_off + (int64_t)row * L.meta_row_bytes();
 

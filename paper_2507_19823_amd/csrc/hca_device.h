@@ -122,16 +122,17 @@ __device__ __forceinline__ float wave_max(float v);
 template <int CTRL> __device__ __forceinline__ int query_dpp(int v) {
   return __builtin_amdgcn_update_dpp(0, v, CTRL, 0xf, 0xf, true);
 }
-// This lane's two channels of head w of the row, for load_query below: asked for as early as the caller likes.
+// This lane's two channels of head w of the row (past the last head: of that one), for query_on_grid and load_query below:
+// asked for as early as the caller likes.
 __device__ __forceinline__ uint32_t query_pair(const uint16_t* __restrict__ q, int row, int gqa) {
   const int w = threadIdx.x >> 6;
-  const uint32_t pair = reinterpret_cast<const uint32_t*>(q + ((int64_t)row * gqa + (w < gqa ? w : gqa - 1)) * kHeadDim)[threadIdx.x & 63];
-  return w < gqa ? pair : 0u;
+  return reinterpret_cast<const uint32_t*>(q + ((int64_t)row * gqa + (w < gqa ? w : gqa - 1)) * kHeadDim)[threadIdx.x & 63];
 }
-// Computes the fixed-point query of row `row` into LDS.  Called by all threads of the block
-// (at least 256); wave w < 4 handles query head w of the row.  Ends with a barrier.
-__device__ __forceinline__ void load_query(uint32_t pair, int group, QShared* sh) {
-  const int tid = threadIdx.x, w = tid >> 6, lane = tid & 63;
+// Computes the fixed-point query of a row into LDS.  Called by all threads of the block
+// (at least 256); wave w < 4 handles query head w of the row.  A barrier has to follow.
+__device__ __forceinline__ void query_on_grid(uint32_t pair, int gqa, int group, QShared* sh) {
+  const int w = threadIdx.x >> 6, lane = threadIdx.x & 63;
+  if (w >= gqa) pair = 0;
   const float x0 = h2f(pair & 0xffffu), x1 = h2f(pair >> 16);
   const float amax = wave_max(fmaxf(fabsf(x0), fabsf(x1)));
   int s = 0;
@@ -156,11 +157,14 @@ __device__ __forceinline__ void load_query(uint32_t pair, int group, QShared* sh
     for (int r = 0; r < 4; ++r) acc += r >= g * per && r < (g + 1) * per ? rows[r] : 0;
     if ((lane & 15) == 0) sh->qsum[w][g] = acc;
   }
+}
+__device__ __forceinline__ void load_query(uint32_t pair, int gqa, int group, QShared* sh) {
+  query_on_grid(pair, gqa, group, sh);
   __syncthreads();
 }
 __device__ __forceinline__ void load_query(const uint16_t* __restrict__ q, int row, int gqa, int group,
                                            QShared* sh) {
-  load_query(query_pair(q, row, gqa), group, sh);
+  load_query(query_pair(q, row, gqa), gqa, group, sh);
 }
 
 template <int BITS>

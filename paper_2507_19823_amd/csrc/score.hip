@@ -206,8 +206,30 @@ __device__ __forceinline__ void score_body(const Layout& L, const uint8_t* __res
   const int ngroups = (wave_end - wave_first) / U;
   uint4 wa[U], wb[U];
   uint32_t ma[U], mb[U];
-  if (ngroups > 0) fetch(b0, wa, ma);        // first loads go out before the query is prepared
-  load_query(q, row, L.gqa, L.group, &sh);
+  // first loads go out before the query is prepared, the query's own before them: loads come back in order
+  uint32_t pair = query_pair(q, row, L.gqa);
+  asm volatile("" ::: "memory");
+  if constexpr (SELECT || LSE) {             // (without the branch the paired scan spills: four layers of 1 Mi 636 -> 665 us)
+    if (ngroups > 0) {
+      fetch(b0, wa, ma);
+      asm volatile("" : "+v"(pair));
+      query_on_grid(pair, L.gqa, L.group, &sh);
+    } else {
+      query_on_grid(pair, L.gqa, L.group, &sh);
+    }
+    __syncthreads();
+  } else {
+    // no branch around the codes' loads: where it joins, the query would wait for them.  A wave without a whole group
+    // asks for the row's first block instead
+    const int first = ngroups > 0 ? b0 : 0, step = ngroups > 0 ? 1 : 0;
+#pragma unroll
+    for (int u = 0; u < U; ++u) {
+      wa[u] = load_stream16(&cptr[(int64_t)(first + u * step) * 64]);
+      ma[u] = __builtin_nontemporal_load(&mptr[(int64_t)(first + u * step) * 64]);
+    }
+    asm volatile("" : "+v"(pair));
+    load_query(pair, L.gqa, L.group, &sh);
+  }
   build_operand_shared<BITS>(&sh, opimg, &op);
   if (ngroups > 0) {
     int g = 0;
@@ -404,6 +426,7 @@ __device__ __forceinline__ void sample_score_body(const Layout& L, const uint8_t
   constexpr int kTpb = BITS == 4 ? 16 : 32;
   constexpr int kPerWave = kSamplePerWg / kTpb / 4;        // sampled blocks per wave: 8 (4-bit) or 4
   __shared__ QShared sh;
+  __shared__ __align__(16) uint32_t opimg[64 * 8];
   const int lane = threadIdx.x & 63;
   const int w = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
   if (n <= 0) {                                             // nothing to sample: this workgroup's share reads "no slot"
@@ -419,19 +442,23 @@ __device__ __forceinline__ void sample_score_body(const Layout& L, const uint8_t
                          (BITS == 4 ? 4 * t + hd : 2 * (16 * (hd >> 1) + t) + (hd & 1));
   uint32_t* out = samples + (int64_t)row * m;
   const int s0 = (bx * 4 + w) * kPerWave;
+  uint32_t pair = query_pair(q, row, L.gqa);                // (before the codes: loads come back in order)
+  asm volatile("" ::: "memory");
   uint4 wv[kPerWave];
   uint32_t mw[kPerWave];
   int blk[kPerWave];
 #pragma unroll
   for (int u = 0; u < kPerWave; ++u) {
     const int s = s0 + u;
-    blk[u] = s < S ? (int)((int64_t)s * nblocks / S) : 0;
+    // s * nblocks / S: S is nblocks or, m_samples being a power of two, one too (eight 64-bit divisions took 2 us)
+    blk[u] = s >= S ? 0 : S == nblocks ? s : (int)((int64_t)s * nblocks >> __builtin_ctz(S));
     wv[u] = load_stream16(&cptr[(int64_t)blk[u] * 64]);
     mw[u] = __builtin_nontemporal_load(&mptr[(int64_t)blk[u] * 64]);
   }
   QOperand<BITS> op;
-  load_query(q, row, L.gqa, L.group, &sh);
-  build_operand<BITS>(&sh, &op);
+  asm volatile("" : "+v"(pair));
+  load_query(pair, L.gqa, L.group, &sh);
+  build_operand_shared<BITS>(&sh, opimg, &op);
   const bool head_live = hd < L.gqa;
 #pragma unroll
   for (int u = 0; u < kPerWave; ++u) {
