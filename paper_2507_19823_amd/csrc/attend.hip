@@ -281,10 +281,11 @@ struct DirectValues {
 };
 
 // Bound by latency: one workgroup per 256 selected tokens, a chain of dependent loads (slots, codes; positions, values) and
-// a few microseconds of arithmetic.  So everything that can be asked for early is: the value rows before the logits, the
-// query beside the slots.  DIRECT: the value rows are read where they live, no gather and no staging area.  A row's only
-// chunk (k <= 256) finishes the row.  One head, 256 tokens: 10 us where gather, attend and merge took 20; 2048 tokens x 32
-// pairs in HBM: 23 us for attend and merge where gather, attend and merge took 34.
+// a few microseconds of arithmetic.  So everything that can be asked for early is: slots, query and
+// count together, the value rows' numbers before the codes (loads come back in order: behind them the values waited, 16.4 us
+// in the kernel for 14.3 at 2048 x 32), the value rows before the logits.  DIRECT: the value rows are read where they live, no
+// gather and no staging area.  A row's only chunk (k <= 256) finishes the row.  One head, 256 tokens: 9 us where gather, attend
+// and merge took 20; 2048 tokens x 32 pairs in HBM: 22 us for attend and merge where gather, attend and merge took 34.
 template <int BITS, bool VALUES = true, bool DIRECT = false>
 __device__ __forceinline__ bool attend_partial_body(PartialShared& ps, QShared& sh, const Layout& L,
                                                     const uint8_t* __restrict__ kcache, const uint16_t* __restrict__ q,
