@@ -23,20 +23,6 @@ struct RowGather {
   }
 };
 
-// Four values per lane, one per 16-token tile (z0..z3: the score of this lane's (token, head) in tiles 0..3): returns,
-// on the lanes of row r, the maximum over the four rows (= the token's four query heads) of tile r's values - the
-// reduction and the hand-over of tile r to row r in three swaps and three maxima.
-__device__ __forceinline__ float max_over_heads_scatter(float z0, float z1, float z2, float z3) {
-  const auto p = __builtin_amdgcn_permlane32_swap(__float_as_uint(z0), __float_as_uint(z2), false, false);
-  const auto q = __builtin_amdgcn_permlane32_swap(__float_as_uint(z1), __float_as_uint(z3), false, false);
-  // p[0] = [z0.r0 z0.r1 z2.r0 z2.r1], p[1] = [z0.r2 z0.r3 z2.r2 z2.r3]: maxima over the row pairs (0,2), (1,3)
-  const float m02 = fmax_raw(__uint_as_float(p[0]), __uint_as_float(p[1]));
-  const float m13 = fmax_raw(__uint_as_float(q[0]), __uint_as_float(q[1]));
-  const auto r = __builtin_amdgcn_permlane16_swap(__float_as_uint(m02), __float_as_uint(m13), false, false);
-  // r[0] = [m02.r0 m13.r0 m02.r2 m13.r2], r[1] = [m02.r1 m13.r1 m02.r3 m13.r3]
-  return fmax_raw(__uint_as_float(r[0]), __uint_as_float(r[1]));
-}
-
 // Work split: grid.y = row, grid.x = chunk; a workgroup has 4 waves and each wave scans `bpw`
 // consecutive 1 KiB code blocks, U at a time: U code loads (16 B per lane, the lane's own MFMA
 // operand bytes) and U meta loads (4 B per lane, then an all-gather over the four lanes of a

@@ -1735,8 +1735,9 @@ __device__ __forceinline__ void tk_resolve_pairs(ResolveShared<NT>& sh, const in
 // and 23 KiB: 62 us from launch to end beside a scan where the 1024-thread form waited for the scan's end, 200 us; four
 // layers of 1 Mi tokens in a step driver 810 -> 720 us, eight 1315 -> 1087.  NT = 256 (48 us alone) is for launches that
 // nearly always find nothing to do.  All give the same result.
+// Returns true for a row whose lists hold too little (mark: its spec then asks for a second scan).
 template <int NT>
-__device__ __forceinline__ void tk_resolve_emit_body(const int64_t chunk, const int nchunks, const int64_t want,
+__device__ __forceinline__ bool tk_resolve_emit_body(const int64_t chunk, const int nchunks, const int64_t want,
                                                      const SelectOut& so, const int32_t k, int32_t* __restrict__ idx,
                                                      int32_t* __restrict__ count, const bool only_failed, const int row,
                                                      const bool mark = true) {
@@ -1748,9 +1749,9 @@ __device__ __forceinline__ void tk_resolve_emit_body(const int64_t chunk, const 
   uint32_t* spec = so.spec + 4 * row;
   if (want <= 0) {
     if (tid == 0 && !only_failed) count[row] = 0;
-    return;
+    return false;
   }
-  if (only_failed && spec[1] == 0) return;
+  if (only_failed && spec[1] == 0) return false;
   // off[c] = pairs in the chunks before c; off[1024] = all of them.  Thread tid owns chunks [PER tid, PER tid + PER)
   {
     uint32_t mine[PER], sum = 0;
@@ -1774,7 +1775,7 @@ __device__ __forceinline__ void tk_resolve_emit_body(const int64_t chunk, const 
     m[2] = total > m[2] ? total : m[2];
     if (total < (uint32_t)want) m[3] += 1;
   }
-  if (total < (uint32_t)want && !mark) return;              // (other workgroups of the launch scan the row again)
+  if (total < (uint32_t)want && !mark) return true;         // (the launch itself scans the row again)
   if (total < (uint32_t)want) {
     // the sampled threshold was too high: scan the row again, with the second threshold if the first scan counted
     // enough slots at or above it, else without one
@@ -1790,12 +1791,13 @@ __device__ __forceinline__ void tk_resolve_emit_body(const int64_t chunk, const 
       spec[0] = enough && spec[1] == 0 ? spec[2] : 0;       // (a second failure cannot happen: the count is exact)
       spec[1] = 1;
     }
-    return;
+    return true;
   }
   const uint32_t base = spec[0];
   const PairList lists{so.lists + (int64_t)row * so.row_entries};
   if (total <= (uint32_t)kHeldPairs) tk_resolve_pairs<NT, true>(sh, chunk, nchunks, want, lists, base, k, idx, count, row, total);
   else tk_resolve_pairs<NT, false>(sh, chunk, nchunks, want, lists, base, k, idx, count, row, total);
+  return false;
 }
 
 template <int NT>
@@ -1808,90 +1810,132 @@ __global__ __launch_bounds__(NT) __attribute__((amdgpu_waves_per_eu(NT == 512 ? 
 
 // The last launch of hca_score_topk's selecting scan, one 1024-thread workgroup per row and behind them some for rows that have
 // to be scanned again.  A row whose lists hold enough is selected by its own workgroup.  The others add up every row's
-// counts and return, nearly always, as none falls short; those that do are dealt out among them and scanned again, a share of the chunks each, into
-// the same lists, whose new counts go to the room of the samples (the first ones still have readers), and the one that
-// finishes last makes the selection.  Nobody waits for anybody, so any number may be resident.  One launch where a selection,
-// a second scan and a second selection were three, the last two of them 9 us to find that they have nothing to do.
+// counts and return, nearly always, as none falls short; those that do are dealt out among them and their own workgroups and scanned
+// again, a share of the chunks each, into the same lists, whose new counts go to the room of the samples (the first ones still
+// have readers), and the one that finishes last makes the selection.  Nobody waits for anybody, so any number may be resident.  One
+// launch where a selection, a second scan and a second selection were three, the last two of them 9 us to find that they have
+// nothing to do.
 // What the shares write goes through to memory (a release fence would write the whole L2 back, 512 times over: 12.5 ms for eight
 // rows of 1 Mi); only the last one fences.  The row totals are not added up by the scan: its workgroups' atomics, on eight
-// dies, took it from 106 to 490 us.  A call, three launches / this one, us: 4 x 128 Ki x 8 rows 109.9 / 106.1 (step), 2 Mi x 8, 2-bit 149 /
-// 145.5; with one of 8 rows misread 200 000 slots 75 / 67, 1 Mi 246 / 229; with all eight 85 / 92, 312 / 347.
+// dies, took it from 106 to 490 us.  A call, three launches / this one, us, by rows that are scanned again with the second
+// threshold: 8 rows of 200 000 slots, none 52 / 47, one 72 / 60, four 75 / 66, all 79 / 77; 8 of 1 Mi 132 / 127, 176 / 150, 200 /
+// 186, 239 / 234 (2-bit codes 94 / 83, 122 / 102, 138 / 122, 152 / 146); 32 of 128 Ki, none 86 / 80, one 105 / 91, half 122 / 118, all
+// 141 / 143; 64 of 128 Ki 142 / 135, 153 / 144, 200 / 194, 244 / 242; 8 rows of 1 Mi scanned again whole: one 1348 / 1315, all 1438 /
+// 1441.  (Each wave waiting for its own loads, and the failed rows' own workgroups idle: all of 8 x 1 Mi 262, of 32 x 128 Ki 166, of 64
+// 305.)
 template <typename T>
 __device__ __forceinline__ void store_through(T* p, T v) { __hip_atomic_store(p, v, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT); }
 
+// Chunks first, first + step, ... of a row, 64 consecutive blocks at a time, four per wave.  The next 64 are on their way while
+// these are scored, across the chunks too.
 template <int BITS>
 __device__ __forceinline__ void rescan_chunks(const Layout& L, const uint8_t* __restrict__ kcache, const uint16_t* __restrict__ q,
                                               const int64_t n, const int row, const uint32_t from_key, const int chunk_blocks,
                                               const int nchunks, const int first, const int step, const SelectOut& so,
                                               uint32_t* __restrict__ counts) {
-  constexpr int U = 4, kTpb = BITS == 4 ? 16 : 32;          // (eight blocks ahead: 8 rows of 1 Mi 347 -> 417 us)
+  constexpr int U = 4, kTpb = BITS == 4 ? 16 : 32, kStep = 16 * U;
   __shared__ QShared qs;
+  __shared__ __align__(16) uint32_t opimg[64 * 8];
   __shared__ uint32_t wn[2][16];
   const int lane = threadIdx.x & 63, w = __builtin_amdgcn_readfirstlane((int)(threadIdx.x >> 6));
   const int t = lane & 15, hd = lane >> 4;
   const int nblocks = (int)((n + kTpb - 1) / kTpb);
+  const int live = (nblocks + chunk_blocks - 1) / chunk_blocks;         // chunks that hold any of the row
+  for (int c = first + step * (int)threadIdx.x; c < nchunks; c += 1024 * step)
+    if (c >= live) store_through(&counts[c], 0u);
+  if (first >= live) return;
   const uint4* cptr = reinterpret_cast<const uint4*>(kcache + (int64_t)row * L.codes_row_bytes()) + lane;
   const uint32_t* mptr = reinterpret_cast<const uint32_t*>(kcache + L.meta_off + (int64_t)row * L.meta_row_bytes()) +
                          (BITS == 4 ? 4 * t + hd : 2 * (16 * (hd >> 1) + t) + (hd & 1));
   const float from = key_floor(from_key);
   const bool head_live = hd < L.gqa;
+  auto end_of = [&](int c) { return (c + 1) * chunk_blocks < nblocks ? (c + 1) * chunk_blocks : nblocks; };
+  uint4 wv[U];
+  uint32_t mw[U];
+  auto fetch = [&](int b0, int b1) {
+#pragma unroll
+    for (int u = 0; u < U; ++u) {
+      const int at = b0 + U * w + u, blk = at < b1 ? at : b1 - 1;
+      wv[u] = load_stream16(&cptr[(int64_t)blk * 64]);
+      mw[u] = __builtin_nontemporal_load(&mptr[(int64_t)blk * 64]);
+    }
+  };
+  int c = first, b0 = c * chunk_blocks, turn = 0;
+  uint32_t pair = query_pair(q, row, L.gqa);                // (before the codes: loads come back in order)
+  asm volatile("" ::: "memory");
+  fetch(b0, end_of(c));
+  asm volatile("" : "+v"(pair));
   QOperand<BITS> op;
-  load_query(q, row, L.gqa, L.group, &qs);
-  build_operand<BITS>(&qs, &op);
-  int turn = 0;
-  for (int c = first; c < nchunks; c += step) {
-    const int b1 = (c + 1) * chunk_blocks < nblocks ? (c + 1) * chunk_blocks : nblocks;
-    uint2* dst = so.lists + (int64_t)row * so.row_entries + (int64_t)c * chunk_blocks * kTpb;
-    uint32_t base = 0;
-    for (int b0 = c * chunk_blocks; b0 < b1; b0 += 16 * U) {            // U consecutive blocks per wave, in wave order
-      const int wb = b0 + U * w;
-      uint4 wv[U];
-      uint32_t mw[U];
+  load_query(pair, L.gqa, L.group, &qs);
+  build_operand_shared<BITS>(&qs, opimg, &op);
+  uint32_t base = 0;
+  while (c < live) {
+    const int b1 = end_of(c);
+    int next_c = c, next_b = b0 + kStep;
+    if (next_b >= b1) { next_c = c + step; next_b = next_c * chunk_blocks; }
+    uint4 cw[U];
+    uint32_t cm[U];
+#pragma unroll
+    for (int u = 0; u < U; ++u) { cw[u] = wv[u]; cm[u] = mw[u]; }
+    if (next_c < live) fetch(next_b, end_of(next_c));
+    // the wave's slots in order, 64 at a time: lane l has the score of slot tok0 + 64 x + l
+    constexpr int X = U * kTpb / 64;
+    float v[X];
+    if constexpr (BITS == 4) {
+      float z[U];
 #pragma unroll
       for (int u = 0; u < U; ++u) {
-        const int blk = wb + u < b1 ? wb + u : b1 - 1;
-        wv[u] = load_stream16(&cptr[(int64_t)blk * 64]);
-        mw[u] = __builtin_nontemporal_load(&mptr[(int64_t)blk * 64]);
+        z[u] = score_block4(op, cw[u], allgather_rows(cm[u]));
+        z[u] = head_live ? z[u] : -INFINITY;
       }
-      float v[U];
-      uint32_t mine = 0;
-      auto hit = [&](int u) {
-        return hd < kTpb / 16 && wb + u < b1 && (int64_t)(wb + u) * kTpb + 16 * hd + t < n && v[u] >= from;
-      };
+      v[0] = max_over_heads_scatter(z[0], z[1], z[2], z[3]);
+    } else {
 #pragma unroll
-      for (int u = 0; u < U; ++u) {
-        const uint4 mv = allgather_rows(mw[u]);
-        if constexpr (BITS == 4) {
-          const float z = score_block4(op, wv[u], mv);       // (by all lanes: they hold parts of each other's products)
-          v[u] = max_over_heads(head_live ? z : -INFINITY);
-        } else {
-          const float z0 = score_tile2(op, wv[u].x, wv[u].y, uint2{mv.x, mv.y});
-          const float z1 = score_tile2(op, wv[u].z, wv[u].w, uint2{mv.z, mv.w});
-          const float m0 = max_over_heads(head_live ? z0 : -INFINITY), m1 = max_over_heads(head_live ? z1 : -INFINITY);
-          v[u] = hd == 0 ? m0 : m1;
+      for (int x = 0; x < X; ++x) {
+        float z[4];
+#pragma unroll
+        for (int u = 0; u < 2; ++u) {
+          const uint4 b = cw[2 * x + u], m = allgather_rows(cm[2 * x + u]);
+          z[2 * u] = score_tile2(op, b.x, b.y, uint2{m.x, m.y});
+          z[2 * u + 1] = score_tile2(op, b.z, b.w, uint2{m.z, m.w});
+          z[2 * u] = head_live ? z[2 * u] : -INFINITY;
+          z[2 * u + 1] = head_live ? z[2 * u + 1] : -INFINITY;
         }
-        mine += (uint32_t)__popcll(__builtin_amdgcn_ballot_w64(hit(u)));
-      }
-      if (lane == 0) wn[turn][w] = mine;
-      __syncthreads();
-      uint32_t at = base;
-#pragma unroll
-      for (int x = 0; x < 16; ++x) {
-        const uint32_t s = wn[turn][x];
-        at += x < w ? s : 0;
-        base += s;
-      }
-      turn ^= 1;                                            // (written again two barriers from here)
-#pragma unroll
-      for (int u = 0; u < U; ++u) {
-        const uint64_t m = __builtin_amdgcn_ballot_w64(hit(u));
-        if (hit(u))
-          store_through(reinterpret_cast<uint64_t*>(dst + at + (uint32_t)__popcll(m & ((1ull << lane) - 1))),
-                        (uint64_t)((wb + u) * kTpb + 16 * hd + t) << 32 | order_key(v[u]));
-        at += (uint32_t)__popcll(m);
+        v[x] = max_over_heads_scatter(z[0], z[1], z[2], z[3]);
       }
     }
-    if (threadIdx.x == 0) store_through(&counts[c], base);
+    const int64_t tok0 = (int64_t)(b0 + U * w) * kTpb + lane, end = (int64_t)b1 * kTpb < n ? (int64_t)b1 * kTpb : n;
+    uint64_t hits[X];
+    uint32_t mine = 0;
+#pragma unroll
+    for (int x = 0; x < X; ++x) {
+      hits[x] = __builtin_amdgcn_ballot_w64(tok0 + 64 * x < end && v[x] >= from);
+      mine += (uint32_t)__popcll(hits[x]);
+    }
+    if (lane == 0) wn[turn][w] = mine;
+    __syncthreads();
+    uint32_t at = base;
+#pragma unroll
+    for (int x = 0; x < 16; ++x) {
+      const uint32_t s = wn[turn][x];
+      at += x < w ? s : 0;
+      base += s;
+    }
+    turn ^= 1;                                              // (written again two barriers from here)
+    uint2* dst = so.lists + (int64_t)row * so.row_entries + (int64_t)c * chunk_blocks * kTpb;
+#pragma unroll
+    for (int x = 0; x < X; ++x) {
+      if ((hits[x] >> lane) & 1)
+        store_through(reinterpret_cast<uint64_t*>(dst + at + (uint32_t)__popcll(hits[x] & ((1ull << lane) - 1))),
+                      (uint64_t)(tok0 + 64 * x) << 32 | order_key(v[x]));
+      at += (uint32_t)__popcll(hits[x]);
+    }
+    if (next_c != c) {
+      if (threadIdx.x == 0) store_through(&counts[c], base);
+      base = 0;
+    }
+    c = next_c;
+    b0 = next_b;
   }
 }
 
@@ -1903,32 +1947,28 @@ __global__ __launch_bounds__(1024) __attribute__((amdgpu_waves_per_eu(4))) void 
     SelectOut so, int32_t k, int32_t* __restrict__ idx, int32_t* __restrict__ count) {
   __shared__ uint32_t wsum[16], s_flag;
   __shared__ uint32_t s_total[kFinishRows];
-  const int tid = threadIdx.x, rows = L.rows;
+  const int tid = threadIdx.x, lane = tid & 63, w = tid >> 6, rows = L.rows, own = (int)blockIdx.x;
   auto want_of = [&](int row) { return sr.want[row / L.n_kv_heads]; };
-  if ((int)blockIdx.x < rows) {
-    const int row = (int)blockIdx.x;
-    tk_resolve_emit_body<1024>(chunk, nchunks, want_of(row), so, k, idx, count, false, row, false);
-    return;
-  }
-  const int lane = tid & 63, w = tid >> 6;
-  for (int row = w; row < rows; row += 16) {                // a wave per row, all of its counts in flight
+  if (own < rows && !tk_resolve_emit_body<1024>(chunk, nchunks, want_of(own), so, k, idx, count, false, own, false)) return;
+  for (int x = w; x < rows; x += 16) {                    // a wave per row, all of its counts in flight
     uint32_t n[kSelectMaxChunks / 64], sum = 0;
 #pragma unroll
     for (int i = 0; i < kSelectMaxChunks / 64; ++i) {
       const int c = i * 64 + lane;
-      n[i] = c < nchunks ? so.ncand[(int64_t)row * kSelectMaxChunks + c] : 0u;
+      n[i] = c < nchunks ? so.ncand[(int64_t)x * kSelectMaxChunks + c] : 0u;
     }
 #pragma unroll
     for (int i = 0; i < kSelectMaxChunks / 64; ++i) sum += n[i];
     sum = wave_sum(sum);
-    if (lane == 0) s_total[row] = sum;
+    if (lane == 0) s_total[x] = sum;
   }
   __syncthreads();
   const bool lacks = lane < rows && want_of(lane) > 0 && s_total[lane] < (uint32_t)want_of(lane);
   uint64_t failed = __builtin_amdgcn_ballot_w64(lacks);
   if (failed == 0) return;
-  // the failed rows in turn: this workgroup is number `at` of the `of` that share its row
-  const int helpers = (int)gridDim.x - rows, h = (int)blockIdx.x - rows, many = (int)__builtin_popcountll(failed);
+  // the failed rows in turn, their own workgroups behind the others: this one is number `at` of the `of` that share its row
+  const int others = (int)gridDim.x - rows, many = (int)__builtin_popcountll(failed), helpers = others + many;
+  const int h = own >= rows ? own - rows : others + (int)__builtin_popcountll(failed & ((1ull << own) - 1));
   const int at = h / many, of = (helpers - h % many + many - 1) / many;
   for (int x = h % many; x > 0; --x) failed &= failed - 1;
   const int row = (int)__builtin_ctzll(failed);
@@ -1947,7 +1987,7 @@ __global__ __launch_bounds__(1024) __attribute__((amdgpu_waves_per_eu(4))) void 
   __syncthreads();
   if (s_flag == 0) return;
   __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "agent");
-  if (tid == 0) { so.spec[4 * row] = from; so.spec[4 * row + 1] = 2; }          // (2: the counts are with the samples)
+  if (tid == 0) { so.spec[4 * row] = from; so.spec[4 * row + 1] = 2; }        // (2: the counts are with the samples)
   __syncthreads();
   tk_resolve_emit_body<1024>(chunk, nchunks, want_of(row), again, k, idx, count, true, row);
 }

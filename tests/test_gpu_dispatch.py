@@ -405,6 +405,36 @@ def test_scores_that_resemble_their_neighbours_do_not_slow_the_long_rows(B, kind
     assert max(took[1:]) < 2 * took[0], f"{took[0]:.1f} us for independent scores, {max(took[1:]):.1f} us"
 
 
+def test_rows_scanned_again_share_the_whole_chip(B):
+    """hca_score_topk over 64 rows, all of them misread by their samples and scanned again: the second scan takes about as
+    long as the first (the call 1.8 times one without), every compute unit has a part in it and its loads are ahead of its
+    scores.  Allowed: twice; with a quarter of the chip idle and each wave waiting for its loads it was 2.24 times."""
+    from paper_2507_19823_amd.session import LayerState
+    batch, hkv, n, k = 8, 8, 131072, 1024
+    gen = torch.Generator(device="cuda").manual_seed(64)
+    q = torch.randn(batch, hkv, 128, generator=gen, device="cuda").half()
+    st = LayerState(batch, hkv, hkv, n, 4, 32, k_max=k, m_max=1)
+    idx = torch.empty(batch, hkv, k, dtype=torch.int32, device="cuda")
+    count = torch.empty(batch, hkv, dtype=torch.int32, device="cuda")
+    sampled = torch.zeros(n // 16, dtype=torch.bool, device="cuda")
+    sampled[torch.arange(512, device="cuda") * (n // 16) // 512] = True
+    took, resc = [], torch.empty(64, dtype=torch.int32, device="cuda")
+    for misread in (False, True):
+        keys = torch.empty(batch, hkv, n, 128, dtype=torch.float16, device="cuda")
+        for r in range(64):
+            u = torch.rand(n, generator=gen, device="cuda")
+            proj = torch.where(sampled.repeat_interleave(16), 1.0 + u, -1.0 - u) if misread else 4 * u - 2
+            qf = q[r // hkv, r % hkv].float()
+            keys[r // hkv, r % hkv] = (proj[:, None] * qf[None] / qf.norm() ** 2 * 40.0).half()
+        st.n = [0] * batch
+        st.quantize(keys)
+        del keys
+        took.append(_passes_us(lambda: B.hca_score_topk(st.shape, st.kcache, q, st.n, k, idx, count, st.ws)))
+        B.hca_score_topk_report(st.shape, st.n, st.ws, torch.empty_like(resc), resc)
+        assert resc.tolist() == [int(misread)] * 64
+    assert took[1] < 2.0 * took[0], f"{took[0]:.1f} us without, {took[1]:.1f} us with a second scan of every row"
+
+
 @pytest.mark.parametrize("n", [4096, 16384, 40960])
 @pytest.mark.parametrize("kind", ["sink", "low", "sinks and lows", "masked", "tail masked", "-inf"])
 def test_a_few_far_scores_do_not_slow_the_short_rows(B, kind, n):

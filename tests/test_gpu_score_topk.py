@@ -188,6 +188,51 @@ def test_several_rows_of_a_call_need_the_second_scan(H, oracle, bits, gs, tpb, l
                 assert k <= cand[2 * b] <= lens[b] and cand[2 * b + 1] >= k
 
 
+@pytest.mark.parametrize("bits,gs,tpb", [(4, 32, 16), (2, 64, 32)])
+@pytest.mark.parametrize("batch,hkv", [(8, 8), (13, 5)], ids=["64rows", "65rows"])
+@pytest.mark.parametrize("k", [1000, 6000])
+@pytest.mark.parametrize("bad", ["all", "odd", "allbutone"])
+def test_most_rows_of_a_large_call_need_the_second_scan(H, bits, gs, tpb, batch, hkv, k, bad):
+    """64 rows, the most that one launch finishes, and 65, of ragged lengths: every row, every other one or all but one
+    misread by their samples and scanned again, by the second threshold (k = 1000) or whole (6000), so that each workgroup
+    of the launch has a share of a row and some rows' own take part.  Against the selection from written scores, twice
+    on one workspace."""
+    from paper_2507_19823_amd import binding as B
+    from paper_2507_19823_amd.session import LayerState
+    n, rows = 45000, batch * hkv
+    lens = [n - 1301 * (b % 5) for b in range(batch)]
+    g = torch.Generator(device="cuda").manual_seed(rows + k + bits)
+    q = torch.randn(batch, hkv, 128, generator=g, device="cuda").half()
+    misread = [{"all": True, "odd": r % 2 == 1, "allbutone": r != rows // 2}[bad] for r in range(rows)]
+    st = LayerState(batch, hkv, hkv, n, bits, gs, k_max=k)
+    keys = torch.empty(batch, hkv, n, 128, dtype=torch.float16, device="cuda")
+    for r in range(rows):
+        b, h = r // hkv, r % hkv
+        nblocks = (lens[b] + tpb - 1) // tpb
+        Sn = min(nblocks, 8192 // tpb)
+        sampled = torch.zeros((n + tpb - 1) // tpb, dtype=torch.bool, device="cuda")
+        sampled[(torch.arange(Sn, device="cuda") * nblocks) // Sn] = True
+        u = torch.rand(n, generator=g, device="cuda")
+        proj = torch.where(sampled.repeat_interleave(tpb)[:n], 1.0 + u, -1.0 - u) if misread[r] else 4 * u - 2
+        qf = q[b, h].float()
+        noise = 0.02 * torch.randn(n, 128, generator=g, device="cuda")
+        keys[b, h] = (proj[:, None] * qf[None] / qf.norm() ** 2 * 40.0 + noise).half()
+    st.quantize(keys)
+    st.n = list(lens)
+    st.score(q)
+    st.topk(k)
+    ref, ref_count = st.idx.clone(), st.count.clone()
+    for _ in range(2):
+        idx = torch.full((batch, hkv, k), -9, dtype=torch.int32, device="cuda")
+        count = torch.full((batch, hkv), -9, dtype=torch.int32, device="cuda")
+        cand, resc = (torch.full((rows,), -1, dtype=torch.int32, device="cuda") for _ in range(2))
+        B.hca_score_topk(st.shape, st.kcache, q, st.n, k, idx, count, st.ws)
+        B.hca_score_topk_report(st.shape, st.n, st.ws, cand, resc)
+        torch.cuda.synchronize()
+        assert torch.equal(count, ref_count) and torch.equal(idx, ref)
+        assert resc.tolist() == [int(x) for x in misread] and int(cand.min()) >= k
+
+
 def test_second_scan_with_the_deeper_threshold(H, oracle):
     """As above, but the slots outside the sampled blocks score only a little lower than those inside: the first
     threshold (inside the sampled blocks' range) lets too few through, the second one - the 8r-th largest sample,
