@@ -220,18 +220,21 @@ def test_blockwise_bulk_assign_equals_one_shot(B, oracle, g, c):
     assert np.array_equal(Pref[:, sample], oc.P[:, :len(sample)].astype(ref.idx_dtype()))
 
 
-# (g, c, batch, hkv, n): one token more than the smallest call of this form; codebooks that do not fill their last block of 32;
-# n one off a multiple of 32 and of 1024; one and several workgroups per (row, group), with a ragged last one; four
-# and two channels; more than 512 tokens left to the exhaustive chain in one workgroup (kind "far")
-@pytest.mark.parametrize("g,c,batch,hkv,n,kind", [(64, 8192, 1, 1, 257, "plain"), (64, 4100, 2, 1, 1025, "awkward"), (64, 8161, 1, 1, 2047, "awkward"),
-                                                  (32, 8192, 2, 4, 2049, "awkward"), (32, 8191, 1, 8, 3001, "skewed"),
-                                                  (32, 6000, 1, 8, 16001, "plain"), (32, 8192, 1, 3, 33001, "skewed"), (64, 4096, 1, 1, 16385, "skewed"),
-                                                  (64, 8192, 1, 1, 1500, "equal"), (64, 8192, 1, 1, 1500, "far")])
-def test_assign_by_cells_equals_short_blocks(B, g, c, batch, hkv, n, kind):
+# (g, c, batch, hkv, T), T the tokens of the call in question: the fewest that this form takes (257: a last tile of one token);
+# codebooks that do not fill their last block of 32; T one off a multiple of 32 and of 1024; one and several workgroups per
+# (row, group), whole (16 384 tokens) and with a ragged last one; four and two channels; more than 512 tokens left to the
+# exhaustive chain in one workgroup (kind "far")
+@pytest.mark.parametrize("g,c,batch,hkv,T,kind", [
+    (64, 8192, 1, 1, 257, "plain"), (64, 8161, 2, 1, 257, "awkward"), (64, 4100, 2, 1, 1025, "awkward"), (64, 8161, 1, 1, 2047, "awkward"),
+    (32, 8192, 2, 4, 2049, "awkward"), (32, 8191, 1, 8, 3001, "skewed"), (32, 6000, 1, 8, 16001, "plain"),
+    (32, 8192, 1, 3, 33001, "skewed"), (64, 4096, 1, 1, 16385, "skewed"), (64, 2048, 2, 2, 16384, "awkward"),
+    (64, 2048, 2, 2, 16385, "plain"), (32, 8192, 1, 8, 16384, "awkward"), (64, 8192, 1, 1, 1500, "equal"), (64, 8192, 1, 1, 1500, "far")])
+def test_assign_by_cells_equals_short_blocks(B, kernels_of, g, c, batch, hkv, T, kind):
     """Many tokens against thousands of centroids (both put in order of nested cells, only near blocks multiplied)
     leave the indices that blocks of 200 tokens leave, which go through forms that look at every centroid: bit for
     bit, with outlier channels, duplicate and neighbouring centroids, infinite, subnormal and out-of-range keys, keys
     on a centroid, and all keys equal."""
+    n = T + 9                                                          # nine tokens are there before
     rng = np.random.default_rng(g + c + n)
     dbar = D // g
     keys = rng.standard_normal((batch, hkv, n, g, dbar)).astype(np.float32)
@@ -259,11 +262,14 @@ def test_assign_by_cells_equals_short_blocks(B, g, c, batch, hkv, n, kind):
         keys[:] = keys[:, :, :1]
     if kind == "far":
         keys[:, :, : n // 2, 1::2] += 200.0
-    kt = torch.from_numpy(keys.reshape(batch, hkv, n, D).astype(np.float16))
+    kt = torch.from_numpy(keys.reshape(batch, hkv, n, D).astype(np.float16)).cuda()
     one, blocks = (_State(B, batch, hkv, hkv, n + 40, g, c, cen, 1) for _ in range(2))
     for st in (one, blocks):
         st.assign(kt[:, :, :9])                                        # so that the block begins behind resident tokens
-    one.assign(kt[:, :, 9:])
+    new = kt[:, :, 9:].contiguous()
+    form = kernels_of(lambda: B.hca_vq_assign(one.shape, one.cb, one.P, new, T, one.n, one.acc, one.pos, one.n))
+    assert len(form) == 1 and "vq_assign_cells_kernel" in form[0], form
+    one.assign(new)
     for t in range(9, n, 200):
         blocks.assign(kt[:, :, t:min(n, t + 200)])
     torch.cuda.synchronize()
