@@ -682,8 +682,8 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(4))) void v
 //   2^-20.3 s(c) + 2^-21.3, sixteen additions 2^-17.6 s(c): E(c) = 2^-17.3 s(c) + 2^-21.3, and cells_limit takes 1.4 times that.
 //   A box can be passed over when its squared distance exceeds 1.002 times the upper bound that cells_bound gives: gaps
 //   are fp16 differences (2^-11 each), boxes are rounded outwards, the chain's own error is 2^-20.
-//   The candidates' distances come from the two halves in LDS in packed fp16; only where the second best is within the
-//   error of that (one token in a hundred) does the exact chain decide.  Out-of-range tokens and those with three blocks of a half
+//   The candidates' distances come from the two halves in LDS, in 32 bits; only where the second best is within the
+//   error of the halves (one token in ten thousand and fewer) does the exact chain decide.  Out-of-range tokens and those with three blocks of a half
 //   wave in question go through every centroid.
 // Per 32 normal tokens of 16 Ki against 8192 centroids 21 of 256 blocks are multiplied and 46 tested, of 1 Ki tokens 38 and
 // 93.  Bound by the issue of the vector ALU (three quarters of its slots): 1700 instructions per 32 tokens, 500 of them products
@@ -1012,6 +1012,8 @@ __global__ __launch_bounds__(1024) void vq_assign_cells_kernel(int g, int c, int
   const v2h kS = kb ? v2h{(_Float16)0.5f, (_Float16)0.5f} : zero2, kO = kb ? zero2 : v2h{(_Float16)1.f, (_Float16)1.f};
   uint32_t number = 255;
   asm volatile("" : "+v"(number));
+  float minus = -1.f;                                        // (opaque: fma with fp16 operands, one instruction, and no conversion and subtraction)
+  asm volatile("" : "+s"(minus));
   uint32_t turn[4];
 #pragma unroll
   for (int j = 0; j < 4; ++j) turn[j] = (uint32_t)(j + col) & 3u;
@@ -1182,7 +1184,9 @@ __global__ __launch_bounds__(1024) void vq_assign_cells_kernel(int g, int c, int
     auto below = [&](uint32_t v) { return __uint_as_float(v) <= lim ? 1u : 0u; };
     const bool queue = real && (!in || below(a3.lo) != 0 || below(a3.hi) != 0);
     const uint32_t mask = queue || !real ? 0u : below(a1.lo) | below(a1.hi) << 1 | below(a2.lo) << 2 | below(a2.hi) << 3;
-    float bd = INFINITY, sd = INFINITY;
+    float bd = INFINITY, sd = INFINITY, xf[DBAR];
+#pragma unroll
+    for (int d = 0; d < DBAR; ++d) xf[d] = h2f((x01[d >> 1] >> (16 * (d & 1))) & 0xffffu);
     uint32_t bp = 0;
     // rows of a 32 x 32 result held by a half: 8 (j / 4) + 4 half + j % 4, j < 16; this lane takes j = 8 kb .. (each
     // lane begins with another one of four neighbours: they are on different banks)
@@ -1196,9 +1200,10 @@ __global__ __launch_bounds__(1024) void vq_assign_cells_kernel(int g, int c, int
           const op_t o = s_op[base + turn[j & 3] + 8 * (j >> 2)];
           float dist = 0.f;
 #pragma unroll
-          for (int d = 0; d < H; ++d) {
-            const v2h e = __builtin_elementwise_fma(cells_pair(o[H + d]), v2h{(_Float16)-0.5f, (_Float16)-0.5f}, cells_pair(x01[d]) - cells_pair(o[d]));
-            dist = __builtin_amdgcn_fdot2(e, e, dist, false);
+          for (int d = 0; d < DBAR; ++d) {
+            const v2h hi = cells_pair(o[d >> 1]), lo = cells_pair(o[H + (d >> 1)]);
+            const float e = fmaf((float)lo[d & 1], -0.5f, fmaf((float)hi[d & 1], minus, xf[d]));
+            dist = fmaf(e, e, dist);
           }
           sd = __builtin_amdgcn_fmed3f(bd, sd, dist);
           bp = dist < bd ? which * 8 + j : bp;
@@ -1211,10 +1216,10 @@ __global__ __launch_bounds__(1024) void vq_assign_cells_kernel(int g, int c, int
     const float b0 = __uint_as_float(hb.lo), b1 = __uint_as_float(hb.hi), best = am_min(b0, b1);
     const float next = am_min(am_max(b0, b1), am_min(__uint_as_float(hs.lo), __uint_as_float(hs.hi)));
     int win = s_perm[b1 < b0 ? hp.hi : hp.lo];
-    // what that leaves undecided: the differences are fp16, 2^-10 off, of halves 2^-20.9 |c| off the centroid: with r the
-    // distance, r^2 is off by less than 2^-9 r^2 + 2^-19.9 r (|x| + r) + 2^-23 r
+    // what that leaves undecided: the halves are 2^-20.9 |c| off the centroid, and this chain and the exact one 2^-22 of the result
+    // off theirs: with r the distance, r^2 is off by less than 2^-21 r^2 + 2^-19.9 r (|x| + r) + 2^-23 r
     const float ax = __builtin_amdgcn_sqrtf(x2), r = __builtin_amdgcn_sqrtf(best) + fmaf(ax, 9.5367431640625e-7f, 5.9604644775390625e-8f);
-    const bool close = mask != 0 && !(next - best > r * fmaf(ax, 2.9e-6f, fmaf(r, 4.9e-3f, 6e-7f)));
+    const bool close = mask != 0 && !(next - best > r * fmaf(ax, 2.9e-6f, fmaf(r, 5e-6f, 6e-7f)));
     if (__builtin_amdgcn_ballot_w64(close) != 0) {
       uint64_t key = kAmNoKey;
       for (uint32_t left = close ? mask : 0u; __builtin_amdgcn_ballot_w64(left != 0) != 0;) {
@@ -1227,7 +1232,7 @@ __global__ __launch_bounds__(1024) void vq_assign_cells_kernel(int g, int c, int
             float dist = 0.f;
 #pragma unroll
             for (int d = 0; d < DBAR; ++d) {
-              const float e = h2f((x01[d >> 1] >> (16 * (d & 1))) & 0xffffu) - cg[(int64_t)ci * DBAR + d];
+              const float e = xf[d] - cg[(int64_t)ci * DBAR + d];
               dist = fmaf(e, e, dist);
             }
             const uint64_t kk = am_key(dist, ci);

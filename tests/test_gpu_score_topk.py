@@ -192,7 +192,7 @@ def test_several_rows_of_a_call_need_the_second_scan(H, oracle, bits, gs, tpb, l
 @pytest.mark.parametrize("batch,hkv", [(8, 8), (13, 5)], ids=["64rows", "65rows"])
 @pytest.mark.parametrize("k", [1000, 6000])
 @pytest.mark.parametrize("bad", ["all", "odd", "allbutone"])
-def test_most_rows_of_a_large_call_need_the_second_scan(H, bits, gs, tpb, batch, hkv, k, bad):
+def test_most_rows_of_a_large_call_need_the_second_scan(H, kernels_of, select_wg, bits, gs, tpb, batch, hkv, k, bad):
     """64 rows, the most that one launch finishes, and 65, of ragged lengths: every row, every other one or all but one
     misread by their samples and scanned again, by the second threshold (k = 1000) or whole (6000), so that each workgroup
     of the launch has a share of a row and some rows' own take part.  Against the selection from written scores, twice
@@ -222,6 +222,8 @@ def test_most_rows_of_a_large_call_need_the_second_scan(H, bits, gs, tpb, batch,
     st.score(q)
     st.topk(k)
     ref, ref_count = st.idx.clone(), st.count.clone()
+    form = kernels_of(lambda: B.hca_score_topk(st.shape, st.kcache, q, st.n, k, st.idx, st.count, st.ws))
+    assert any("tk_finish" in x for x in form) == (rows <= 64 and select_wg == 0), form
     for _ in range(2):
         idx = torch.full((batch, hkv, k), -9, dtype=torch.int32, device="cuda")
         count = torch.full((batch, hkv), -9, dtype=torch.int32, device="cuda")
