@@ -213,17 +213,21 @@ __device__ __forceinline__ Halves halves_of(uint32_t v) {
 __device__ __forceinline__ uint64_t am_key(float dist, int ci) { return (uint64_t)__float_as_uint(dist) << 32 | (uint32_t)ci; }
 constexpr uint64_t kAmNoKey = ~0ull;
 
-// The exact chain over every centroid of a group for one token, by LANES neighbouring lanes (y = which of them): the
-// winner of the ascending scan of vq_assign_kernel, which starts from centroid 0 whatever its distance - no finite
+// The exact chain over every centroid of a group for N tokens, by LANES neighbouring lanes (y = which of them): the
+// winners of the ascending scan of vq_assign_kernel, which starts from centroid 0 whatever its distance - no finite
 // distance at all, or a first distance that is not a number, leave it the winner.
-template <int DBAR, int LANES>
-__device__ __forceinline__ int am_exhaustive(const uint16_t* src, const float* cg, int c, int y) {
-  float x[DBAR];
+template <int DBAR, int LANES, int N>
+__device__ __forceinline__ void am_exhaustive_of(const uint16_t* const (&src)[N], const float* cg, int c, int y, int (&win)[N]) {
+  float x[N][DBAR], bd[N];
+  int bi[N], first_nan[N];
 #pragma unroll
-  for (int d = 0; d < DBAR; ++d) x[d] = h2f(src[d]);
-  float bd = INFINITY;
-  int bi = 0x7fffffff;
-  int first_nan = 0;
+  for (int i = 0; i < N; ++i) {
+#pragma unroll
+    for (int d = 0; d < DBAR; ++d) x[i][d] = h2f(src[i][d]);
+    bd[i] = INFINITY;
+    bi[i] = 0x7fffffff;
+    first_nan[i] = 0;
+  }
   for (int c0 = y; c0 < c; c0 += 4 * LANES) {               // four centroids in flight
     float cv[4][DBAR];
 #pragma unroll
@@ -231,25 +235,37 @@ __device__ __forceinline__ int am_exhaustive(const uint16_t* src, const float* c
 #pragma unroll
       for (int d = 0; d < DBAR; ++d) cv[u][d] = cg[(c0 + u * LANES < c ? c0 + u * LANES : c0) * DBAR + d];
 #pragma unroll
-    for (int u = 0; u < 4; ++u) {
-      float dist = 0.f;
+    for (int u = 0; u < 4; ++u)
 #pragma unroll
-      for (int d = 0; d < DBAR; ++d) {
-        const float e = x[d] - cv[u][d];
-        dist = fmaf(e, e, dist);
+      for (int i = 0; i < N; ++i) {
+        float dist = 0.f;
+#pragma unroll
+        for (int d = 0; d < DBAR; ++d) {
+          const float e = x[i][d] - cv[u][d];
+          dist = fmaf(e, e, dist);
+        }
+        if (c0 + u * LANES < c && dist < bd[i]) { bd[i] = dist; bi[i] = c0 + u * LANES; }
+        if (c0 == 0 && u == 0) first_nan[i] = dist != dist;
       }
-      if (c0 + u * LANES < c && dist < bd) { bd = dist; bi = c0 + u * LANES; }
-      if (c0 == 0 && u == 0) first_nan = dist != dist;
-    }
   }
 #pragma unroll
-  for (int o = LANES / 2; o >= 1; o >>= 1) {
-    const float od = __shfl_xor(bd, o);
-    const int ob = __shfl_xor(bi, o);
-    first_nan |= __shfl_xor(first_nan, o);
-    if (od < bd || (od == bd && ob < bi)) { bd = od; bi = ob; }
+  for (int i = 0; i < N; ++i) {
+#pragma unroll
+    for (int o = LANES / 2; o >= 1; o >>= 1) {
+      const float od = __shfl_xor(bd[i], o);
+      const int ob = __shfl_xor(bi[i], o);
+      first_nan[i] |= __shfl_xor(first_nan[i], o);
+      if (od < bd[i] || (od == bd[i] && ob < bi[i])) { bd[i] = od; bi[i] = ob; }
+    }
+    win[i] = (bi[i] == 0x7fffffff || first_nan[i]) ? 0 : bi[i];
   }
-  return (bi == 0x7fffffff || first_nan) ? 0 : bi;
+}
+template <int DBAR, int LANES>
+__device__ __forceinline__ int am_exhaustive(const uint16_t* src, const float* cg, int c, int y) {
+  const uint16_t* const one[1] = {src};
+  int win[1];
+  am_exhaustive_of<DBAR, LANES, 1>(one, cg, c, y, win);
+  return win[0];
 }
 
 // More than 256 centroids, and blocks of few tokens against 96 and more.  One workgroup of 8 waves = 1024 tokens x one group; a wave holds
@@ -683,8 +699,8 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(4))) void v
 //   A box can be passed over when its squared distance exceeds 1.002 times the upper bound that cells_bound gives: gaps
 //   are fp16 differences (2^-11 each), boxes are rounded outwards, the chain's own error is 2^-20.
 //   The candidates' distances come from the two halves in LDS, in 32 bits; only where the second best is within the
-//   error of the halves (one token in ten thousand and fewer) does the exact chain decide.  Out-of-range tokens and those with three blocks of a half
-//   wave in question go through every centroid.
+//   error of the halves (one token in ten thousand and fewer) does the exact chain decide.  Tokens with three blocks of a
+//   half wave in question go through the exact chain of all near blocks, out-of-range ones of every centroid (settle).
 // Per 32 normal tokens of 16 Ki against 8192 centroids 21 of 256 blocks are multiplied and 46 tested, of 1 Ki tokens 38 and
 // 93.  Bound by the issue of the vector ALU (three quarters of its slots): 1700 instructions per 32 tokens, 500 of them products
 // and their minima, 400 tests, 150 the two orderings, which take 64 us of the launch's 500 (38 with 2 Ki tokens).  16 Ki tokens x 8 KV heads,
@@ -1019,9 +1035,92 @@ __global__ __launch_bounds__(1024) void vq_assign_cells_kernel(int g, int c, int
   for (int j = 0; j < 4; ++j) turn[j] = (uint32_t)(j + col) & 3u;
 
   auto put = [&](int t, int win) { pcache[vq_wide_at(g, vq_tiles(cap), row, slot0 + t, grp)] = (uint16_t)win; };
-  auto exhaust = [&](int t) {                                // by the whole wave
-    const int win = am_exhaustive<DBAR, 64>(keys + (int64_t)t * kHeadDim, cg, c, lane);
-    if (lane == 0) put(t, win);
+  // the numbers of the blocks with lb in (low, high] into the wave's list, ascending; how many
+  auto list = [&](const float (&lb)[kBlkPer], float low, float high) {
+    int count = 0;
+    __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
+#pragma unroll
+    for (int i = 0; i < kBlkPer; ++i) {
+      const bool in_list = lb[i] > low && lb[i] <= high && lane + 64 * i < nblk;
+      const uint64_t ball = __builtin_amdgcn_ballot_w64(in_list);
+      const int at = count + (int)__builtin_amdgcn_mbcnt_hi((uint32_t)(ball >> 32), __builtin_amdgcn_mbcnt_lo((uint32_t)ball, 0));
+      if (in_list) s_ids[w * 256 + at] = (uint8_t)(lane + 64 * i);
+      count += (int)__builtin_popcountll(ball);
+    }
+    __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
+    return count;
+  };
+  // The exact chain over every centroid that can win, by the whole wave: those of the nearest block, then of the blocks
+  // within the distance that this leaves.  Out of order in memory each costs a line of its own: of more blocks than an
+  // eighth (two channels: a quarter) all centroids in their order, and for a token out of range, two such tokens at a time.
+  // 8 x 16 Ki tokens that all end here, c = 8192, us, every centroid for one token at a time / this: 8 points 1024 times each
+  // 17 300 / 14 300 (by blocks, 32 of them, 20 000), with two channels 29 100 / 13 400; 64 points 128 times 17 100 / 7700; all on one
+  // line 9300 / 1760; 16 dense clusters 3710 / 2370.
+  constexpr int kFew = DBAR == 4 ? 8 : 4;
+  int waiting = -1;                                          // a token that waits for a second one
+  auto in_order = [&](int t0, int t1) {
+    const uint16_t* const src[2] = {keys + (int64_t)t0 * kHeadDim, keys + (int64_t)t1 * kHeadDim};
+    int win[2];
+    am_exhaustive_of<DBAR, 64, 2>(src, cg, c, lane, win);
+    if (lane == 0) { put(t0, win[0]); put(t1, win[1]); }
+  };
+  auto settle = [&](int t) {
+    uint32_t xw[H];
+    words_of(t, xw);
+    float x2 = 0.f, lb[kBlkPer], least = INFINITY;
+#pragma unroll
+    for (int d = 0; d < H; ++d) x2 = __builtin_amdgcn_fdot2(cells_pair(xw[d]), cells_pair(xw[d]), x2, false);
+    bool by_blocks = x2 + cmax2 < 32768.f;
+#pragma unroll
+    for (int i = 0; i < kBlkPer; ++i) {
+      lb[i] = by_blocks && lane + 64 * i < nblk ? gap2(xw, xw, mybox[i]) : INFINITY;
+      least = am_min(least, lb[i]);
+    }
+    least = __uint_as_float(wave_min(__float_as_uint(least)));
+    uint64_t key = kAmNoKey;
+    float low = -1.f, high = least;
+    for (int round = 0; round < 2 && by_blocks; ++round) {
+      const int count = list(lb, low, high);
+      if (count * kFew >= nblk) { by_blocks = false; break; }
+      for (int from = 0; from < count; from += 8) {          // a block per half wave, four of each in flight
+        int ci[4];
+        float cv[4][DBAR];
+#pragma unroll
+        for (int u = 0; u < 4; ++u) {
+          const int at = from + 2 * u + kb;
+          ci[u] = s_perm[s_ids[w * 256 + (at < count ? at : count - 1)] * 32 + col];
+        }
+#pragma unroll
+        for (int u = 0; u < 4; ++u)
+#pragma unroll
+          for (int d = 0; d < DBAR; ++d) cv[u][d] = cg[(int64_t)ci[u] * DBAR + d];
+#pragma unroll
+        for (int u = 0; u < 4; ++u) {
+          float dist = 0.f;
+#pragma unroll
+          for (int d = 0; d < DBAR; ++d) {
+            const float e = h2f((xw[d >> 1] >> (16 * (d & 1))) & 0xffffu) - cv[u][d];
+            dist = fmaf(e, e, dist);
+          }
+          const uint64_t kk = am_key(dist, ci[u]);
+          if (kk < key) key = kk;
+        }
+      }
+      // a box further away than the best so far (1.002 and 1e-6: as for the tiles' boxes) holds no winner
+      low = least;
+      high = fmaf(1.002f, __uint_as_float(wave_min((uint32_t)(key >> 32))), 1e-6f);
+    }
+    if (!by_blocks) {
+      if (waiting >= 0) in_order(waiting, t);
+      waiting = waiting >= 0 ? -1 : t;
+      return;
+    }
+#pragma unroll
+    for (int o = 32; o >= 1; o >>= 1) {
+      const uint64_t other = (uint64_t)__shfl_xor((uint32_t)(key >> 32), o) << 32 | __shfl_xor((uint32_t)key, o);
+      if (other < key) key = other;
+    }
+    if (lane == 0) put(t, (int)(uint32_t)key);
   };
   auto token_of = [&](int k) {                               // of this column in tile k of the wave (4 j .. 4 j + 3: lst[0])
     const Halves h = halves_of(k & 2 ? lst[0] >> 16 : lst[0] & 0xffffu);
@@ -1123,22 +1222,7 @@ __global__ __launch_bounds__(1024) void vq_assign_cells_kernel(int g, int c, int
       if (nblk <= 128) lb[2] = INFINITY;
       if (nblk <= 64) lb[1] = INFINITY;
       const float least = __uint_as_float(wave_min(__float_as_uint(am_min(am_min(lb[0], lb[1]), am_min(lb[2], lb[3])))));
-      // the numbers of the blocks with lb in (low, high] into the wave's list, ascending; how many
-      auto list = [&](float low, float high) {
-        int count = 0;
-        __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
-#pragma unroll
-        for (int i = 0; i < kBlkPer; ++i) {
-          const bool in_list = lb[i] > low && lb[i] <= high && lane + 64 * i < nblk;
-          const uint64_t ball = __builtin_amdgcn_ballot_w64(in_list);
-          const int at = count + (int)__builtin_amdgcn_mbcnt_hi((uint32_t)(ball >> 32), __builtin_amdgcn_mbcnt_lo((uint32_t)ball, 0));
-          if (in_list) s_ids[w * 256 + at] = (uint8_t)(lane + 64 * i);
-          count += (int)__builtin_popcountll(ball);
-        }
-        __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
-        return count;
-      };
-      for (int count = list(-1.f, least), from = 0; from < count; from += 32)
+      for (int count = list(lb, -1.f, least), from = 0; from < count; from += 32)
         multiply_all(from, count - from >= 32 ? ~0u : (1u << (count - from)) - 1u);
       // twice: the blocks within half the distance of the worst token's bound, and, with that bound lowered by them, the others.
       // Sixteen blocks are tested at a time, two per product of boxes and tokens
@@ -1151,7 +1235,7 @@ __global__ __launch_bounds__(1024) void vq_assign_cells_kernel(int g, int c, int
         };
         bound();
         const float high = __uint_as_float(wave_max(__float_as_uint(d2))) * (round == 0 ? 0.25f : 1.f);
-        const int count = list(low, high);
+        const int count = list(lb, low, high);
         low = am_max(low, high);
         for (int from = 0; from < count; from += 16) {
           const int left = count - from;
@@ -1245,18 +1329,19 @@ __global__ __launch_bounds__(1024) void vq_assign_cells_kernel(int g, int c, int
       if (close) win = (int)(uint32_t)(k0 < k1 ? k0 : k1);
     }
     if (kb == 0 && real && !queue) put(t, win);
-    // every centroid: at the end, shared by all waves, as far as the queue has room
+    // the others: at the end, shared by all waves, as far as the queue has room
     uint32_t place_in_queue = kQueue;
     if (queue && kb == 0) {
       place_in_queue = atomicAdd(&s_queued, 1u);
       if (place_in_queue < kQueue) s_queue[place_in_queue] = (uint16_t)t;
     }
     for (uint64_t left = __builtin_amdgcn_ballot_w64(queue && kb == 0 && place_in_queue >= kQueue); left != 0; left &= left - 1)
-      exhaust(__builtin_amdgcn_readlane(t, (int)__builtin_ctzll(left)));
+      settle(__builtin_amdgcn_readlane(t, (int)__builtin_ctzll(left)));
   }
   __syncthreads();
   const int queued = s_queued < kQueue ? (int)s_queued : (int)kQueue;
-  for (int e = w; e < queued; e += 16) exhaust(s_queue[e]);
+  for (int e = w; e < queued; e += 16) settle(s_queue[e]);
+  if (waiting >= 0) in_order(waiting, waiting);
 }
 
 // Few tokens per call (decode appends): one workgroup of four waves per (token, row, 4 / SPLIT groups).  SPLIT waves

@@ -622,6 +622,29 @@ def test_a_far_centroid_does_not_slow_the_assignment(B, g, c, T):
     assert took[1] < 1.5 * took[0], f"{took[0]:.0f} us without the far centroid, {took[1]:.0f} us with it"
 
 
+@pytest.mark.parametrize("kind,most", [("line", 5.0), ("repeated", 14.0)])
+def test_rivals_in_many_blocks_do_not_slow_the_assignment(B, kind, most):
+    """Thousands of centroids of which many lie close together, next to each other on a line or 64 points 128 times each:
+    tokens with more near blocks than are kept look into those, not into all of the codebook.  Allowed: 5 and 14 times an
+    ordinary codebook's time (measured 2.8 and 10; with every centroid looked at 12 and 20)."""
+    rows, g, c, T = 8, 32, 8192, 2000
+    gen = torch.Generator(device="cuda").manual_seed(c)
+    shape = B.make_shape(1, rows, rows, T)
+    took = []
+    for now in ("normal", kind):
+        k = torch.randn(1, rows, T, g, 4, generator=gen, device="cuda")
+        cen = 1.1 * torch.randn(rows, g, c, 4, generator=gen, device="cuda")
+        if now == "line":
+            k, cen = k[..., :1] + 0.01 * k, cen[..., :1] + 0.01 * cen
+        if now == "repeated":
+            cen = cen[:, :, torch.randint(0, 64, (c,), generator=gen, device="cuda")].contiguous()
+        cb = B.make_codebook(g, c, cen)
+        keys = k.reshape(1, rows, T, 128).half()
+        pc = torch.zeros(B.hca_vq_pcache_bytes(shape, cb), dtype=torch.uint8, device="cuda")
+        took.append(_passes_us(lambda: B.hca_vq_assign(shape, cb, pc, keys, T, [0]), 5))
+    assert took[1] < most * took[0], f"{took[0]:.0f} us normal, {took[1]:.0f} us {kind}"
+
+
 @pytest.mark.parametrize("g,c,G", [(32, 256, 4), (64, 256, 4), (64, 256, 1), (32, 96, 4), (32, 250, 1)])
 def test_assignment_queue_fills_at_any_group(B, oracle, g, c, G):
     """Up to 256 centroids: a share of every group's centroids (none to all, another one in each group) exists twice, so

@@ -228,12 +228,15 @@ def test_blockwise_bulk_assign_equals_one_shot(B, oracle, g, c):
     (64, 8192, 1, 1, 257, "plain"), (64, 8161, 2, 1, 257, "awkward"), (64, 4100, 2, 1, 1025, "awkward"), (64, 8161, 1, 1, 2047, "awkward"),
     (32, 8192, 2, 4, 2049, "awkward"), (32, 8191, 1, 8, 3001, "skewed"), (32, 6000, 1, 8, 16001, "plain"),
     (32, 8192, 1, 3, 33001, "skewed"), (64, 4096, 1, 1, 16385, "skewed"), (64, 2048, 2, 2, 16384, "awkward"),
-    (64, 2048, 2, 2, 16385, "plain"), (32, 8192, 1, 8, 16384, "awkward"), (64, 8192, 1, 1, 1500, "equal"), (64, 8192, 1, 1, 1500, "far")])
+    (64, 2048, 2, 2, 16385, "plain"), (32, 8192, 1, 8, 16384, "awkward"), (64, 8192, 1, 1, 1500, "equal"), (64, 8192, 1, 1, 1500, "far"),
+    (64, 8192, 1, 1, 2000, "repeated"), (32, 8161, 1, 8, 2500, "repeated"), (64, 4100, 2, 1, 1025, "clustered"),
+    (32, 8192, 1, 8, 2500, "clustered"), (64, 8161, 1, 1, 3000, "narrow"), (32, 8192, 1, 8, 2500, "narrow")])
 def test_assign_by_cells_equals_short_blocks(B, kernels_of, g, c, batch, hkv, T, kind):
     """Many tokens against thousands of centroids (both put in order of nested cells, only near blocks multiplied)
     leave the indices that blocks of 200 tokens leave, which go through forms that look at every centroid: bit for
     bit, with outlier channels, duplicate and neighbouring centroids, infinite, subnormal and out-of-range keys, keys
-    on a centroid, and all keys equal."""
+    on a centroid, and all keys equal; codebooks of 50 points each many times over (every token has rivals in more blocks
+    than are kept, and the lowest index wins), of 16 dense clusters, and of one."""
     n = T + 9                                                          # nine tokens are there before
     rng = np.random.default_rng(g + c + n)
     dbar = D // g
@@ -262,6 +265,11 @@ def test_assign_by_cells_equals_short_blocks(B, kernels_of, g, c, batch, hkv, T,
         keys[:] = keys[:, :, :1]
     if kind == "far":
         keys[:, :, : n // 2, 1::2] += 200.0
+    if kind in ("repeated", "clustered", "narrow"):
+        points = {"repeated": 50, "clustered": 16, "narrow": 1}[kind]
+        cen = cen[:, :, rng.integers(0, points, c)]
+        if kind != "repeated":
+            cen += (1e-3 * rng.standard_normal(cen.shape)).astype(np.float32)
     kt = torch.from_numpy(keys.reshape(batch, hkv, n, D).astype(np.float16)).cuda()
     one, blocks = (_State(B, batch, hkv, hkv, n + 40, g, c, cen, 1) for _ in range(2))
     for st in (one, blocks):
