@@ -772,18 +772,20 @@ __device__ __forceinline__ float key_to_float(uint32_t key) {
 // ---------------------------------------------------------------------------------------
 // Top-k of short rows in one launch: a 1024-thread workgroup holds a whole row of scores in registers, KPT values per
 // thread, wave w owning the KPT * 64 consecutive slots from w * KPT * 64 on (a wave's x-th load is 64 of them, so slot
-// order is (wave, x, lane)).  hca_topk per call, 8 rows of 4 Ki / 16 Ki / 32 Ki / 40 Ki slots, 1024 to select: 8 / 10.6 / 13 /
-// 14.5 us (8 / 11.7 / 18.2 / 21.8 without step 0), against 31 / 35 / - / 39 us for the six launches over the whole chip; with
+// order is (wave, x, lane)).  hca_topk, 8 rows of 4 Ki / 16 Ki / 32 Ki / 40 Ki slots, 1024 to select: 8 / 10.3 / 13.5 / 14.9
+// us (8 / 11.2 / 18.1 / 21.6 without step 0), against 31 / 35 / - / 39 us for the six launches over the whole chip; with
 // the scan in front (hca_score_topk), 4 Ki / 16 Ki / 32 Ki: 13 / 18 / 23 (13 / 19 / 28 without step 0) against 39 / 39 / 41 us
 // for sample, threshold, selecting scan, selection and its fall-back pair.
 //   0. Rows of 8 Ki slots and more of which few are wanted: a bound below which the want-th largest lies almost never, from
 //      1024 samples (their rank-th largest, rank = the expected one + 3.5 standard deviations + 6; binned as in step 1).  The
-//      values at or above it - 2000 of 32 Ki for 1024 to select - go to a list in LDS in slot order, and only those, four per
-//      thread, are binned, ranked and placed.  A list longer than kSiftMax, or more than kRankMax of it in the bin of the
-//      last one (ties): steps 2 and 3 over the whole row, with the bound as the end of the bins; too short a list, or a
-//      NaN anywhere: all steps.  At most kSiftMax - 512 are expected: at that end of the rule one row in fifty is too long (18.7
-//      -> 22 us; 13.3 where none is), of 2000 none.  8 rows of 32 Ki slots, 1024 to select: 11.4 us in the kernel - loads
-//      and window 3.5, bound 1, list 4, the rest 3 - for 16.5; beyond kSiftMax the list's own steps would grow.
+//      values at or above it and the NaNs - 2000 of 32 Ki for 1024 to select - go to a list in LDS in slot order, and only
+//      those, P per thread, are binned, ranked and placed.  A list longer than that, or more than kRankMax of it in the bin of
+//      the last one (ties): all steps, their window over the values at or above the bound; too short a list: all steps.  The
+//      lists are expected to fill three quarters of the room at most (six entries per thread for rows beyond 16 Ki; of four
+//      one row in fifty was too long at the rule's end, 18.5 -> 22 us), so it takes ties or a row that follows the samples' places.
+//      What those cost, 8 rows of 32 Ki, 1024 to select, without step 0 / with it: all samples among the smallest 18.6 / 24,
+//      among the largest 18 / 24, all slots equal 12.2 / 16; steps of 0.5 between the values 43.6 / 31, a NaN in every
+//      row 36.6 / 13.5.  Of 11.4 us in the kernel loads and window take 3.5, the bound 1, the list 4, the rest 3, for 16.5.
 //   1. smallest and largest value per wave; 4096 bins spread evenly over a window in which most of the row lies, so that
 //      neither the counters are fought over nor most of them stay empty (the keys of one row share their exponent bits).
 //      The window reaches a quarter of its width beyond the fourth smallest and the fourth largest of the waves' extremes:
@@ -801,7 +803,9 @@ __device__ __forceinline__ float key_to_float(uint32_t key) {
 // then the chain of its dozen barriers counts as much.  The row in LDS with rolled
 // loops instead of registers: 35.6 us per 32 Ki slots.
 constexpr int kRankMax = 512;
-constexpr int kSiftMax = 4096;
+// entries of the list per thread, and how many are expected at most: rows of up to 16 Ki slots, longer ones
+__host__ __device__ constexpr int sift_per(int kpt) { return kpt <= 16 ? 4 : 6; }
+__host__ __device__ constexpr uint32_t sift_expected(int kpt) { return kpt <= 16 ? 3072 : 3584; }
 constexpr uint32_t kSiftMin = 8192;
 // rank among 1024 samples, expected number of those among the wanted and a margin, whose value bounds the list of step 0
 __host__ __device__ __forceinline__ uint32_t sift_rank(uint32_t want, uint32_t n) {
@@ -844,8 +848,9 @@ __global__ __launch_bounds__(1024) void tk_row_select(const float* __restrict__ 
   __shared__ uint32_t h[kBins12], list[kRankMax], wsum[16], wlo[16], whi[16], wplain[16];
   __shared__ uint32_t s_bin, s_rem, s_cb, s_n, s_T, s_req, s_flags;
   __shared__ __align__(16) float s_win[8];
+  constexpr int P = sift_per(KPT), kSiftMax = 1024 * P;
   __shared__ __align__(16) float s_kept[kSift ? kSiftMax : 4];
-  __shared__ __align__(16) uint32_t s_slot[kSift ? kSiftMax : 4];
+  __shared__ __align__(16) uint16_t s_slot[kSift ? kSiftMax : 4];         // (rows have at most kRowSelectMax slots)
   const int row = blockIdx.x;
   const int tid = threadIdx.x, lane = tid & 63, wv = __builtin_amdgcn_readfirstlane(tid >> 6);
   const int64_t want64 = sr.want[row / n_kv_heads];
@@ -873,7 +878,7 @@ __global__ __launch_bounds__(1024) void tk_row_select(const float* __restrict__ 
   // the sample of step 0, one place in each of 1024 equal parts of the row
   float sample = 0.0f;
   const uint32_t rank = kSift ? sift_rank(want, n) : 0u;
-  const bool sift = kSift && n >= kSiftMin && rank * n <= (uint32_t)(kSiftMax - 512) * 1024u;
+  const bool sift = kSift && n >= kSiftMin && rank * n <= sift_expected(KPT) * 1024u;
   if (sift) {
     const uint32_t from = ((uint32_t)tid * n) >> 10, part = n >> 10;
     sample = v[from + ((((uint32_t)tid * 40503u) & 0xffffu) * part >> 16)];
@@ -889,7 +894,7 @@ __global__ __launch_bounds__(1024) void tk_row_select(const float* __restrict__ 
     for (int x = 0; x < KPT; ++x) asm volatile("" : "+v"(f[x]));
   };
   for (int i = tid; i < kBins12; i += 1024) h[i] = 0;
-  if (tid == 0) s_n = 0;
+  if (tid == 0) { s_n = 0; s_T = 0xffffffffu; s_req = 0; }
   float vlo = INFINITY, vhi = -INFINITY, from = 0.0f, scale = 0.0f;
   bool plain = true;                                        // no NaN and no +infinity
   // the window of the bins, from the extremes and the plainness of each lane's values; `waves`: those with values;
@@ -988,7 +993,7 @@ __global__ __launch_bounds__(1024) void tk_row_select(const float* __restrict__ 
     }
     __syncthreads();
   };
-  bool sifted = false;                                      // the window is known: it begins at the samples' bound
+  float bound = -INFINITY;                                  // at least `want` values are not below it
   if constexpr (kSift) {
     // 0. (uniform over the workgroup)
     if (sift) {
@@ -1002,42 +1007,29 @@ __global__ __launch_bounds__(1024) void tk_row_select(const float* __restrict__ 
         __syncthreads();
         find_bin(rank, 0u);
         const float cut = from + ((float)s_bin - 0.25f) / scale, top = from + 4095.0f / scale;     // (ties on a bin's edge)
-        const float fine = 4095.0f / (top - cut);
+        const float fine = 4093.0f / (top - cut);
         for (int i = tid; i < kBins12; i += 1024) h[i] = 0;
-        // those at or above it, in slot order: (wave, x, lane)
+        // those at or above it and the NaNs, in slot order: (wave, x, lane)
         uint32_t mine = 0;
-        bool odd = false;                                   // a NaN among them
         const bool whole = (uint32_t)(wv + 1) * (KPT * 64) <= n;
         if (whole) {
 #pragma unroll
-          for (int x = 0; x < KPT; ++x) {
-            mine += (uint32_t)__popcll(__builtin_amdgcn_ballot_w64(f[x] >= cut));
-            odd = odd || f[x] != f[x];
-          }
+          for (int x = 0; x < KPT; ++x) mine += (uint32_t)__popcll(__builtin_amdgcn_ballot_w64(!(f[x] < cut)));
         } else {
 #pragma unroll
-          for (int x = 0; x < KPT; ++x) {
-            mine += (uint32_t)__popcll(__builtin_amdgcn_ballot_w64(f[x] >= cut && s0 + x * 64 < n));
-            odd = odd || f[x] != f[x];
-          }
+          for (int x = 0; x < KPT; ++x) mine += (uint32_t)__popcll(__builtin_amdgcn_ballot_w64(!(f[x] < cut) && s0 + x * 64 < n));
         }
-        odd = __builtin_amdgcn_ballot_w64(odd) != 0;
         forget();
-        if (lane == 0) { wlo[wv] = mine; wplain[wv] = odd ? 1u : 0u; }
+        if (lane == 0) wlo[wv] = mine;
         __syncthreads();
-        uint32_t at = 0, all = 0, odds = 0;
+        uint32_t at = 0, all = 0;
 #pragma unroll
         for (int x = 0; x < 16; ++x) {
           at += x < wv ? wlo[x] : 0u;
           all += wlo[x];
-          odds |= wplain[x];
         }
-        sifted = odds == 0 && all >= want && fine > 0.0f && fine < INFINITY;
-        if (sifted) {
-          from = cut - 1.0f / fine;                         // (the lowest bin is the others')
-          scale = fine;
-        }
-        if (sifted && all <= (uint32_t)kSiftMax) {
+        if (all >= want) bound = cut;
+        if (all >= want && all <= (uint32_t)kSiftMax && fine > 0.0f && fine < INFINITY) {
           auto keep = [&](auto&& hit) {
 #pragma unroll
             for (int x = 0; x < KPT; ++x) {
@@ -1045,35 +1037,38 @@ __global__ __launch_bounds__(1024) void tk_row_select(const float* __restrict__ 
               const uint32_t p = __builtin_amdgcn_mbcnt_hi((uint32_t)(m >> 32), __builtin_amdgcn_mbcnt_lo((uint32_t)m, at));
               if (hit(x)) {
                 s_kept[p] = f[x];
-                s_slot[p] = s0 + x * 64;
+                s_slot[p] = (uint16_t)(s0 + x * 64);
               }
               at += (uint32_t)__popcll(m);
             }
           };
-          if (whole) keep([&](int x) { return f[x] >= cut; });
-          else keep([&](int x) { return f[x] >= cut && s0 + x * 64 < n; });
+          if (whole) keep([&](int x) { return !(f[x] < cut); });
+          else keep([&](int x) { return !(f[x] < cut) && s0 + x * 64 < n; });
           __syncthreads();
-          // four of them per thread, one behind the other
-          const float4 c4 = reinterpret_cast<const float4*>(s_kept)[tid];
-          const float c[4] = {c4.x, c4.y, c4.z, c4.w};
-          uint32_t bin[4];
+          forget();
+          // P of them per thread, one behind the other; bin 0 is for the negative NaNs alone, the smallest keys of all
+          float c[P];
+          uint32_t bin[P];
 #pragma unroll
-          for (int i = 0; i < 4; ++i) {
-            bin[i] = 4u * tid + i < all ? (uint32_t)__builtin_amdgcn_fmed3f((c[i] - from) * scale, 0.0f, 4095.0f) : 0xffffffffu;
-            if (bin[i] != 0xffffffffu) atomicAdd(&h[bin[i]], 1u);
+          for (int i = 0; i < P; ++i) {
+            c[i] = s_kept[P * tid + i];
+            const bool in = (uint32_t)(P * tid + i) < all, nan = c[i] != c[i];
+            const float at_bin = __builtin_amdgcn_fmed3f((c[i] - cut) * fine + 2.0f, 1.0f, 4095.0f);
+            bin[i] = !in ? 0xffffffffu : nan ? ((__float_as_uint(c[i]) >> 31) != 0 ? 0u : 4095u) : (uint32_t)at_bin;
+            if (in) atomicAdd(&h[bin[i]], 1u);
           }
           __syncthreads();
           find_bin(want, 0u);
           const uint32_t cb = s_cb, rem = s_rem, b0 = s_bin;
-          if (cb <= (uint32_t)kRankMax) {
+          if (cb <= (uint32_t)kRankMax && b0 != 0) {        // (bin 0: values below the bound come before these)
 #pragma unroll
-            for (int i = 0; i < 4; ++i)
+            for (int i = 0; i < P; ++i)
               if (bin[i] == b0) list[atomicAdd(&s_n, 1u)] = order_key(c[i]);
             rank_list(cb, rem);
             const uint32_t T = s_T, req = s_req;
             uint32_t ng = 0, ne = 0;
 #pragma unroll
-            for (int i = 0; i < 4; ++i) {
+            for (int i = 0; i < P; ++i) {
               const bool in = bin[i] != 0xffffffffu;
               ng += in && order_key(c[i]) > T;
               ne += in && order_key(c[i]) == T;
@@ -1082,41 +1077,41 @@ __global__ __launch_bounds__(1024) void tk_row_select(const float* __restrict__ 
             uint32_t g = before & 0xffffu, e = before >> 16;
             int32_t* out = idx + (int64_t)row * k;
             if (tid == 0) count[row] = (int32_t)want;
-            const uint4 s4 = reinterpret_cast<const uint4*>(s_slot)[tid];
-            const uint32_t slot[4] = {s4.x, s4.y, s4.z, s4.w};
 #pragma unroll
-            for (int i = 0; i < 4; ++i) {
+            for (int i = 0; i < P; ++i) {
               const bool in = bin[i] != 0xffffffffu, is_g = in && order_key(c[i]) > T, is_e = in && order_key(c[i]) == T;
-              if (is_g || (is_e && e < req)) out[g + (e < req ? e : req)] = (int32_t)slot[i];
+              if (is_g || (is_e && e < req)) out[g + (e < req ? e : req)] = (int32_t)s_slot[P * tid + i];
               g += is_g;
               e += is_e;
             }
             return;
           }
         }
+        __syncthreads();                                    // everybody has read what the steps below write again
+        for (int i = tid; i < kBins12; i += 1024) h[i] = 0;
       }
-      __syncthreads();                                      // everybody has read what the steps below write again
-      for (int i = tid; i < kBins12; i += 1024) h[i] = 0;
       vlo = INFINITY;
       vhi = -INFINITY;
       plain = true;
       __syncthreads();
     }
   }
-  if (!sifted) {
+  // the window of the values that are not below the bound (without one: of all), which at least `want` are
 #pragma unroll
-    for (int x = 0; x < KPT; ++x) {
-      vlo = fminf(vlo, f[x]);
-      vhi = fmaxf(vhi, f[x]);
-      plain = plain && f[x] < INFINITY;
-    }
-    find_window((n + KPT * 64 - 1) / (KPT * 64), [&](float cut) {
-      float m = INFINITY;
-#pragma unroll
-      for (int x = 0; x < KPT; ++x) m = f[x] >= cut ? fminf(m, f[x]) : m;
-      return m;
-    });
+  for (int x = 0; x < KPT; ++x) {
+    const bool counts = !kSift || f[x] >= bound;
+    vlo = counts ? fminf(vlo, f[x]) : vlo;
+    vhi = counts ? fmaxf(vhi, f[x]) : vhi;
+    plain = plain && f[x] < INFINITY;
   }
+  find_window((n + KPT * 64 - 1) / (KPT * 64), [&](float cut) {
+    float m = INFINITY;
+    if (kSift) cut = fmaxf(cut, bound);
+#pragma unroll
+    for (int x = 0; x < KPT; ++x) m = f[x] >= cut ? fminf(m, f[x]) : m;
+    return m;
+  });
+  if (kSift && bound > -INFINITY) from -= 1.5f / scale;     // (the lowest bin is the others')
   const bool by_value = plain && scale > 0.0f && scale < INFINITY;
   if (plain) {                                              // past the row's end: the lowest bin, below every threshold
 #pragma unroll
@@ -1166,7 +1161,7 @@ __global__ __launch_bounds__(1024) void tk_row_select(const float* __restrict__ 
       __syncthreads();
       for (int x = 0; x < 16; ++x) { lo = wlo[x] < lo ? wlo[x] : lo; hi = whi[x] > hi ? whi[x] : hi; }
       base = lo;
-      int left = 32 - __clz((int)((hi - lo) | 1u));         // 1 .. 32
+      int left = lo == hi ? 0 : 32 - __clz((int)(hi - lo));           // 0: all equal
       bool first = true;
       while (left > 0 && cb > (uint32_t)kRankMax) {         // uniform over the workgroup
         forget();
@@ -1255,11 +1250,11 @@ __global__ __launch_bounds__(1024) void tk_row_select(const float* __restrict__ 
   }
 }
 
-// Longest row of the one-launch form: one compute unit per row, so its time grows with the row (64 values per thread:
-// 48 us at 64 Ki slots, level with the other form); eight rows of 32 Ki slots 28 us against 41, of 40 Ki 33
-// against 47, of 48 Ki (both sampled) 48.
-// 40 Ki is what fits the 128 registers of a 1024-thread workgroup, and keeps a 32 Ki context on this side while it
-// grows by the tokens it decodes.
+// Longest row of the one-launch form: 40 Ki slots are what fits the 128 registers of a 1024-thread workgroup, and keep a
+// 32 Ki context on this side while it grows by the tokens it decodes.  The line lies where the registers end and not where
+// the forms are level.  hca_topk / hca_score_topk on the GPU, us, 40 960 slots here and 40 961 over the chip: 8 rows, 1024 to
+// select 13.9 / 20.8 and 27.4 / 33.7, 4096 to select (no step 0) 22.3 / 28.6 and 28.7 / 34.7; 32 rows, 4096: 22.9 / 45.4 and
+// 29.2 / 45.8; one row, 4096: 21.9 / 25.7 and 25.3 / 30.8.
 constexpr int64_t kRowSelectMax = 40960;
 
 static int32_t launch_row_select(const float* vals, int64_t stride, int rows, int n_kv_heads, const SelRows& sr,
@@ -1268,7 +1263,7 @@ static int32_t launch_row_select(const float* vals, int64_t stride, int rows, in
   // step 0 where the longest row's list is expected to fit (a shorter row's is no longer); its code beside the other's costs
   // a row that does without 1 us of 23
   const bool sift = nmax > (int64_t)kSiftMin && k < nmax &&
-                    sift_rank((uint32_t)k, (uint32_t)nmax) * (uint64_t)nmax <= (uint64_t)(kSiftMax - 512) * 1024u;
+                    sift_rank((uint32_t)k, (uint32_t)nmax) * (uint64_t)nmax <= (uint64_t)sift_expected(nmax <= 16 * 1024 ? 16 : 32) * 1024u;
 #define HCA_ROW_SELECT(KPT, SIFT) tk_row_select<KPT, SIFT><<<rows, 1024, 0, st>>>(vals, stride, n_kv_heads, sr, k, idx, count, fu)
   if (nmax <= 4 * 1024) HCA_ROW_SELECT(4, false);
   else if (nmax <= 8 * 1024) HCA_ROW_SELECT(8, false);

@@ -249,8 +249,8 @@ def test_topk_at_the_edges_of_the_one_launch_form(B, kind, n):
             assert np.all(got[b, want:] == -7)
 
 
-@pytest.mark.parametrize("kind", ["normal", "ramp", "ties", "seen", "missed", "nan", "masked"])
-@pytest.mark.parametrize("n", [8191, 8192, 16385, 30011, 40960])
+@pytest.mark.parametrize("kind", ["normal", "ramp", "ties", "steps", "seen", "missed", "lower", "nan", "nans", "seen nans", "masked"])
+@pytest.mark.parametrize("n", [8191, 8192, 16384, 16385, 30011, 40960])
 def test_topk_of_a_row_sifted_by_samples(B, kind, n):
     """Few of a row in one workgroup's registers: the list above the samples' bound, and rows whose samples mislead."""
     rng = np.random.default_rng(n + 7 * len(kind))
@@ -265,8 +265,18 @@ def test_topk_of_a_row_sifted_by_samples(B, kind, n):
         x[sampled] += 20
     elif kind == "missed":                                  # and the smallest: one too long, or with all its values in the top bin
         x[sampled] -= 20
+    elif kind == "steps":                                   # ties whose bins hold as many as are ranked, and more
+        x = np.round(x * 24) / 24
+    elif kind == "lower":                                   # lists up to their room and past it
+        x[sampled] -= 0.25 + 0.1 * rng.random()
     elif kind == "nan":
         x[n - 5] = np.nan
+    elif kind in ("nans", "seen nans"):                     # of both signs, with all keys: the largest and the smallest
+        if kind != "nans":
+            x[sampled] += 20
+        other = np.setdiff1d(np.arange(n), sampled)
+        at = rng.choice(other, min(3000, n // 3), replace=False)
+        x.view(np.uint32)[at] = rng.integers(0x7f800001, 0x80000000, at.size) | np.where(np.arange(at.size) % 9 == 0, 0, 1 << 31)
     elif kind == "masked":
         x[rng.random(n) < 0.5] = -np.inf
         x[rng.random(n) < 0.001] = np.inf
