@@ -82,6 +82,24 @@ def test_topp_bit_exact(B, oracle, case, n, k_max, tau, sm):
     _check(oracle, v, [n, n], hkv, sm, tau, k_max, got)
 
 
+@pytest.mark.parametrize("case", ["normal", "all_equal"])
+def test_topp_of_a_row_that_fills_the_counters(B, oracle, case):
+    """A workgroup's share of more than the 32 768 slots that one 64-bit counter holds the weights of: the counters are
+    flushed in the middle of it; all equal: one counter takes 32 768 slots of the largest weight."""
+    n = 9000001
+    if case == "normal":
+        v = (np.random.default_rng(3).standard_normal((1, n)) * 12).astype(np.float32)
+    else:
+        v = np.full((1, n), -2.5, np.float32)
+    k_max = n if case == "all_equal" else 100000
+    tau = 0.9 if case == "all_equal" else 0.05
+    got = _run(B, v, [n], 1, 0.0884, tau, k_max)
+    oidx, ocount, _, omass = oracle.topp(v, np.array([n]), 0.0884, tau, k_max)
+    assert np.array_equal(got[2], omass), "Theta / Z differ"
+    assert np.array_equal(got[1], ocount) and 0 < ocount[0] < k_max
+    assert np.array_equal(got[0][0, :ocount[0]], oidx[0, :ocount[0]])
+
+
 def test_topp_ragged_empty_and_clip(B, oracle):
     rng = np.random.default_rng(9)
     cap, hkv = 40000, 2

@@ -629,8 +629,9 @@ def test_wide_scan_of_few_slots_is_that_of_many(B, rows, gqa, g, c, many):
     (8, 2, 32, 1001, (300001, 60000, 1000)),
     (8, 2, 32, 8192, (450001, 300001, 1000)),                   # four quads per thread and three
     (8, 1, 64, 300, (450001, 200001, 1000)),
+    (8, 1, 32, 8191, (450001, 300001, 1000)),                   # one head: four quads per thread and three
 ])
-def test_wide_scan_of_raw_entries(B, rows, gqa, g, c, lengths):
+def test_wide_scan_of_raw_entries(B, kernels_of, rows, gqa, g, c, lengths):
     """The forms of the wide scan whose table passes through LDS, by slots per centroid, bit for bit; and a table that does
     not begin at a multiple of 16 bytes."""
     gen = torch.Generator(device="cuda").manual_seed(c + g)
@@ -642,7 +643,7 @@ def test_wide_scan_of_raw_entries(B, rows, gqa, g, c, lengths):
     pc.view(torch.int16).random_(0, c, generator=gen)
     q = torch.randn(rows, gqa, 128, generator=gen, device="cuda").half()
     first = None
-    for n, shift in [(n, 0) for n in lengths] + ([(lengths[1], gqa)] if gqa < 4 else []):
+    for n, shift in [(n, 0) for n in lengths] + ([(n, gqa) for n in lengths[:2]] if gqa < 4 else []):
         lens = [n - 300 * (r % 2) for r in range(rows)]
         lut = torch.zeros(B.hca_vq_lut_bytes(shape, cb) // 4 + shift, device="cuda")[shift:]
         sel = torch.full((rows, 1, many), -7.0, device="cuda")
@@ -654,3 +655,7 @@ def test_wide_scan_of_raw_entries(B, rows, gqa, g, c, lengths):
             m = lens[r]
             assert torch.equal(sel[r, :, :m], first[0][r, :, :m]) and torch.equal(z[r, :, :m], first[1][r, :, :m])
             assert (sel[r, :, m:] == -7).all() and (z[r, :, m:] == -7).all()
+        if c > 8000 and gqa < 4 and n > 300000:                 # <heads, quads, raw>
+            form = kernels_of(lambda: B.hca_vq_score(shape, cb, pc, q, lens, lut, sel, z))
+            want = f"vq_scan_wide_kernelILi{gqa}ELi{4 if n > 393216 else 3}ELb{int(shift == 0)}E"
+            assert any(want in f for f in form), (want, form)
