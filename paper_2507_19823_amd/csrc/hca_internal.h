@@ -97,9 +97,10 @@ size_t topk_hist_bytes(int rows);
 // scan workgroup, at most kSelectMaxChunks of them per row).
 constexpr int kSelectMaxChunks = 1024;
 struct SelectOut {
-  uint32_t* spec;       // [rows][4]: threshold key t0, 1 = the row has to be scanned again (with the threshold then
-                        // in word 0), second threshold t1 <= t0 (only counted against),
-                        // workgroups that have done their part of a second scan (tk_finish)
+  uint32_t* spec;       // [rows][4]: threshold key t0; 0, 1 = the row has to be or was scanned again (with the threshold
+                        // then in word 0), 2 = tk_finish has done so: the pair counts are with the samples; second threshold
+                        // t1 <= t0 (only counted against); workgroups that have done their part of that scan (cleared by the
+                        // kernel that writes the thresholds, counted up by tk_finish)
   uint32_t* ncand;      // [rows][kSelectMaxChunks] pairs in each chunk's list
   uint32_t* n1;         // [rows][kSelectMaxChunks] slots of each chunk with key >= t1
   uint2* lists;         // [rows][row_entries]: chunk c owns entries [c * chunk, (c + 1) * chunk)

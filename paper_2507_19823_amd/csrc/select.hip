@@ -258,8 +258,9 @@ struct TopkWs {
   uint64_t* pstate;    // [rows][4]: weight still to reach inside the bin; window of the fine bins (two floats)
   uint32_t* prow;      // [rows][4]: key of the row maximum, slots still allowed, selected count, (unused)
   // scan + top-k in one call only
-  uint32_t* samples;   // [rows][kSampleMax] keys of the sampled slots
-  uint32_t* spec;      // [rows][4]: threshold key, 1 = row scanned a second time, unused, unused
+  uint32_t* samples;   // [rows][kSampleMax] keys of the sampled slots; after a second scan by tk_finish, the pair counts of
+                       // the rows that it scanned, [rows][kSelectMaxChunks]
+  uint32_t* spec;      // [rows][4]: see SelectOut
   uint32_t* mon;       // [rows][4] since the last reset: fused selections, fewest and most pairs a first scan let
                        // through, selections that needed the second scan
 };

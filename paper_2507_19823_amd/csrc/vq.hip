@@ -473,8 +473,9 @@ __global__ __launch_bounds__(512) __attribute__((amdgpu_waves_per_eu(4))) void v
 // barrier per group, and the sixteen index bytes of a token leave as one 16-byte store (narrow form).  A block is half of
 // a tile's rows in a half wave; two values are kept, a token with rivals in another block (a few in a thousand) goes to
 // the queue.
-// Bound by the issue of the vector ALU (86 % of its slots at 256 centroids): the two minima of 16 blocks of products, half
-// of it, and one block's exact chain per token.  Every lane decides about one token - the two tiles' halves change places
+// Bound by the issue of the vector ALU (97 % of its slots at 64 Ki tokens x 8 KV heads and 256 centroids, 30 instructions per
+// product of two tiles, at the 1.93 GHz that the power limit leaves): the two minima of 16 blocks of products, half of it, and
+// one block's exact chain per token.  Every lane decides about one token - the two tiles' halves change places
 // in one swap each - so that the limit and the chain's set-up are paid once per token, not once per half wave.
 // 64 Ki tokens x 8 KV heads against 256 centroids: 311 -> 239 us (0.99 ms in the vector form), 64 centroids: 178 -> 128
 // (0.25); two channels: 586 -> 433, 335 -> 193.
@@ -696,15 +697,17 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(4))) void v
 //   cost 2^-15 of d, not of |x|^2.
 //   Errors, for S and s(c) as above: with p = hi^2 / 2 rounded to fp16 and q = fp16(rest of it + hi lo), the pieces lose at most
 //   2^-20.3 s(c) + 2^-21.3, sixteen additions 2^-17.6 s(c): E(c) = 2^-17.3 s(c) + 2^-21.3, and cells_limit takes 1.4 times that.
+//   Emulated against 64 bits (1500 tokens and their 24 nearest of 8192, two and four channels: normal; one channel, or all,
+//   20 - 40 times as wide; centroids next to tokens), root mean square, vq_assign_mfma_kernel's form as 1: the products 0.75 -
+//   1.07, with the blocks' numbers in their low bits 0.016 - 0.12.
 //   A box can be passed over when its squared distance exceeds 1.002 times the upper bound that cells_bound gives: gaps
 //   are fp16 differences (2^-11 each), boxes are rounded outwards, the chain's own error is 2^-20.
 //   The candidates' distances come from the two halves in LDS, in 32 bits; only where the second best is within the
 //   error of the halves (one token in ten thousand and fewer) does the exact chain decide.  Tokens with three blocks of a
 //   half wave in question go through the exact chain of all near blocks, out-of-range ones of every centroid (settle).
-// Per 32 normal tokens of 16 Ki against 8192 centroids 21 of 256 blocks are multiplied and 46 tested, of 1 Ki tokens 38 and
-// 93.  Bound by the issue of the vector ALU (three quarters of its slots): 1700 instructions per 32 tokens, 500 of them products
-// and their minima, 400 tests, 150 the two orderings, which take 64 us of the launch's 500 (38 with 2 Ki tokens).  16 Ki tokens x 8 KV heads,
-// c = 8192: 1140 us in vq_assign_mfma_kernel, 500 here; with the waves left to the order of age 560.
+// Bound by the issue of the vector ALU (88 % of its slots by the counters): 16 Ki normal tokens x 8 KV heads, 32 groups, c =
+// 8192: per 32 tokens 20 of 256 blocks are multiplied and 1730 vector instructions issued.  A call of that 1120 us in
+// vq_assign_mfma_kernel, 454 here (with the waves left to the order of age 60 more).
 constexpr int kCellTokens = 16384, kCellBins = 4096;
 
 __device__ __forceinline__ v2h cells_min(v2h a, v2h b) { return __builtin_elementwise_minimum(a, b); }
@@ -1642,15 +1645,15 @@ __device__ __forceinline__ void vq_row_exponents(float* __restrict__ lut, int g,
 // copied from the group-major table into LDS on their heads' grids, then looked up with the share's indices of
 // those groups.  The table is re-read once per share: full lines from L2, instead of one L2 request per token and
 // group.
-// Bound by the refills, and by the lookups next to them: at 8 rows x 300 Ki slots, c = 8192, a slice takes 3.1 us:
-// LDS is busy for 1.2 of them, the vector units for 1.5, and a share that leaves the refills out still needs 2.7.
-// So the shares are equal and as many as compute units (157 us with a tile of 16 Ki slots per workgroup, 152 of
-// them: 118 us), and a thread asks for its whole part of a slice, eight 16-byte entries, when it has finished its
-// own lookups and before it waits for the others' (99 us; asked for before the lookups, 118: the indices
+// Bound by the refills and the lookups, which take turns.  So the shares are equal and as many as compute units (8 rows x
+// 300 Ki slots, c = 8192, entries on the grid at the refill: 157 us with a tile of 16 Ki slots per workgroup, 152 of
+// them, 118 with 256 shares), and there a thread asks for its whole part of a slice, eight 16-byte entries, when it has
+// finished its own lookups and before it waits for the others' (99 us; asked for before the lookups, 118: the indices
 // queue behind it).
 // RAW: the slice as it lies in memory, straight into LDS, and on the heads' grids at every lookup - where there are not many
 // more lookups than entries (scan_wide_launch).  What is left of a slice then: 1.2 us of refill, and the lookups, whose
-// vector instructions (18 of each with four heads, 7 without RAW) take as long as a share has slots.
+// vector instructions (18 of each with four heads, 7 without RAW) take as long as a share has slots: at that size, 93 us in
+// the kernel, the vector ALU issues in 49 % of the clocks, LDS is busy in 28 % (two thirds of it bank conflicts).
 template <int G, int NQ, bool RAW>
 __global__ __launch_bounds__(1024) void vq_scan_wide_kernel(int g, int c, int gps, int64_t cap, int64_t per_wg,
                                                              const uint16_t* __restrict__ pcache,
@@ -1919,9 +1922,10 @@ static int assign_cells_chunk(int rows, int g, int64_t T) {
 // sizes (1 to 49 rows, 1024 to 8192 centroids, 256 to 33 000 tokens; half of them within 2.5 %, nineteen in twenty within 8 %).  A
 // workgroup of the former pays for two orderings before its first token, and what it multiplies grows with less than the
 // codebook; the 4 % are for what the fit does not see.  Measured, mfma / cells: 8 rows, 32 groups, c = 8192: 1000 tokens
-// 105 / 95 us, 2000 166 / 118, 4000 298 / 196, 16 000 1169 / 500; c = 4096: 4000 164 / 148, 16 000 597 / 405; c = 2048:
-// 16 000 336 / 366; 24 rows, c = 8192: 1000 tokens 245 / 266; 64 groups, 8 rows: c = 8192, 512 178 / 75, 16 000 2700 / 540; c =
-// 2048: 512 38 / 47, 2000 104 / 80, 16 000 700 / 380.
+// 108 / 97 us, 2000 177 / 128, 4000 311 / 182, 16 384 1120 / 454; c = 4096: 4000 163 / 143, 16 384 610 / 389; c = 2048:
+// 16 384 350 / 332; 24 rows, c = 8192: 1000 tokens 229 / 255; 64 groups, 8 rows: c = 8192, 512 102 / 69, 16 384 2213 / 414; c =
+// 2048: 512 34 / 50, 2000 92 / 82, 16 384 646 / 357.  Of 75 sizes the pick is 5 % or more off the better form in three, 10 % at
+// most (8 rows, c = 8192, 1000 tokens).
 static bool assign_by_cells(int rows, int g, int c, int64_t T) {
   const int chunk = assign_cells_chunk(rows, g, T);
   const double pairs = (double)rows * g, n = (double)(T < chunk ? T : chunk) / 1000, k = (double)c / 1000;
