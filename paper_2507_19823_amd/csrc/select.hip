@@ -777,7 +777,7 @@ __device__ __forceinline__ float key_to_float(uint32_t key) {
 // us (8 / 11.2 / 18.1 / 21.6 without step 0), against 31 / 35 / - / 39 us for the six launches over the whole chip; with
 // the scan in front (hca_score_topk), 4 Ki / 16 Ki / 32 Ki: 13 / 18 / 23 (13 / 19 / 28 without step 0) against 39 / 39 / 41 us
 // for sample, threshold, selecting scan, selection and its fall-back pair.
-//   0. Rows of 8 Ki slots and more of which few are wanted: a bound below which the want-th largest lies almost never, from
+//   0. Rows of 8 Ki slots and more, in a call whose longest has more than 12 Ki, of which few are wanted: a bound below which the want-th largest lies almost never, from
 //      1024 samples (their rank-th largest, rank = the expected one + 3.5 standard deviations + 6; binned as in step 1).  The
 //      values at or above it and the NaNs - 2000 of 32 Ki for 1024 to select - go to a list in LDS in slot order, and only
 //      those, P per thread, are binned, ranked and placed.  A list longer than that, or more than kRankMax of it in the bin of
@@ -807,7 +807,8 @@ constexpr int kRankMax = 512;
 // entries of the list per thread, and how many are expected at most: rows of up to 16 Ki slots, longer ones
 __host__ __device__ constexpr int sift_per(int kpt) { return kpt <= 16 ? 4 : 6; }
 __host__ __device__ constexpr uint32_t sift_expected(int kpt) { return kpt <= 16 ? 3072 : 3584; }
-constexpr uint32_t kSiftMin = 8192;
+constexpr uint32_t kSiftMin = 8192;           // slots of a row; of the longest one of a call:
+constexpr int64_t kSiftCall = 12288;
 // rank among 1024 samples, expected number of those among the wanted and a margin, whose value bounds the list of step 0
 __host__ __device__ __forceinline__ uint32_t sift_rank(uint32_t want, uint32_t n) {
   const float mean = (float)want * 1024.0f / (float)n;
@@ -1262,8 +1263,9 @@ static int32_t launch_row_select(const float* vals, int64_t stride, int rows, in
                                  int64_t nmax, int32_t k, int32_t* idx, int32_t* count, const RowSelectFused& fu,
                                  hipStream_t st) {
   // step 0 where the longest row's list is expected to fit (a shorter row's is no longer); its code beside the other's costs
-  // a row that does without 1 us of 23
-  const bool sift = nmax > (int64_t)kSiftMin && k < nmax &&
+  // a row that does without 1 us of 23.  Up to 12 Ki slots it saves nothing: 8 rows of 9000, 256 / 1024 / 2250 to select, without
+  // and with it 10.1 / 10.4 / 10.5 and 10.4 / 10.5 / 10.6 us; of 14 336 10.6 / 11.1 / 11.2 and 10.4 / 10.6 / 10.8
+  const bool sift = nmax > kSiftCall && k < nmax &&
                     sift_rank((uint32_t)k, (uint32_t)nmax) * (uint64_t)nmax <= (uint64_t)sift_expected(nmax <= 16 * 1024 ? 16 : 32) * 1024u;
 #define HCA_ROW_SELECT(KPT, SIFT) tk_row_select<KPT, SIFT><<<rows, 1024, 0, st>>>(vals, stride, n_kv_heads, sr, k, idx, count, fu)
   if (nmax <= 4 * 1024) HCA_ROW_SELECT(4, false);

@@ -250,7 +250,7 @@ def test_topk_at_the_edges_of_the_one_launch_form(B, kind, n):
 
 
 @pytest.mark.parametrize("kind", ["normal", "ramp", "ties", "steps", "seen", "missed", "lower", "nan", "nans", "seen nans", "masked"])
-@pytest.mark.parametrize("n", [8191, 8192, 16384, 16385, 30011, 40960])
+@pytest.mark.parametrize("n", [8191, 8192, 12288, 12289, 16384, 16385, 30011, 40960])
 def test_topk_of_a_row_sifted_by_samples(B, kind, n):
     """Few of a row in one workgroup's registers: the list above the samples' bound, and rows whose samples mislead."""
     rng = np.random.default_rng(n + 7 * len(kind))
